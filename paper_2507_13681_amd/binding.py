@@ -92,6 +92,15 @@ def load_library():
     return lib
 
 
+def _load_native():
+    """The CPython module over the C ABI, built beside the library."""
+    try:
+        from . import _lsnative
+    except ImportError as e:
+        raise LoopServeError(f"_lsnative.so cannot be loaded ({e}): build it with `python -m paper_2507_13681_amd.build`") from e
+    return _lsnative
+
+
 def make_shape(B, Hq, Hkv, d, n, n_hat, w, dtype, scale=0.0) -> LsShape:
     code = {torch.bfloat16: LS_BF16, torch.float32: LS_F32, "bf16": LS_BF16, "f32": LS_F32}[dtype]
     return LsShape(B, Hq, Hkv, d, n, n_hat, w, code, float(scale))
@@ -113,7 +122,7 @@ def _ptr(t):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 class Context:
@@ -121,6 +130,7 @@ class Context:
 
     def __init__(self, shape: LsShape | None = None, budget: int = 0, device: int = 0, workspace: int | None = None):
         self.lib = load_library()
+        self.native = _load_native()
         if workspace is None:
             workspace = workspace_bytes(shape, budget)
             if workspace == 0:
@@ -132,11 +142,13 @@ class Context:
         if rc != 0:
             raise LoopServeError(f"ls_create failed with {rc}")
         self.h = h
+        self.hv = h.value                        # what the native marshalling takes; 0 (an error in every call) once closed
 
     def close(self):
         if getattr(self, "h", None):
             self.lib.ls_destroy(self.h)
             self.h = None
+            self.hv = 0
 
     def __del__(self):
         try:
@@ -148,44 +160,49 @@ class Context:
         if rc != 0:
             raise LoopServeError(f"{self.lib.ls_last_error(self.h).decode()} (status {rc})")
 
-    # -- the four entry points, same names as the C ABI -------------------------------------
+    # -- the entry points, same names as the C ABI (the marshalling is native: csrc/ls_py.c) ------------
     def ls_score(self, shape, q_win, k, vert, slash, vmax, smax, total, q_pos=None):
-        self._check(self.lib.ls_score(self.h, C.byref(shape), _ptr(q_win), _ptr(q_pos), _ptr(k), _ptr(vert),
-                                      _ptr(slash), _ptr(vmax), _ptr(smax), _ptr(total), _stream()))
+        rc = self.native.score(self.hv, shape, q_win, q_pos, k, vert, slash, vmax, smax, total)
+        if rc:
+            self._check(rc)
 
     def ls_select(self, shape, alpha, vert, slash, vmax, smax, total, v_idx, v_cnt, s_idx, s_cnt, accounted=None):
-        self._check(self.lib.ls_select(self.h, C.byref(shape), alpha, _ptr(vert), _ptr(slash), _ptr(vmax), _ptr(smax),
-                                       _ptr(total), _ptr(v_idx), _ptr(v_cnt), v_idx.shape[-1], _ptr(s_idx),
-                                       _ptr(s_cnt), s_idx.shape[-1], _ptr(accounted), _stream()))
+        rc = self.native.select_lines(self.hv, shape, alpha, vert, slash, vmax, smax, total, v_idx, v_cnt, s_idx, s_cnt, accounted)
+        if rc:
+            self._check(rc)
 
     def ls_score_window(self, shape, q_win, k, a_win, q_pos=None):
-        self._check(self.lib.ls_score_window(self.h, C.byref(shape), _ptr(q_win), _ptr(q_pos), _ptr(k), _ptr(a_win), _stream()))
+        rc = self.native.score_window(self.hv, shape, q_win, q_pos, k, a_win)
+        if rc:
+            self._check(rc)
 
     def ls_select_exact(self, shape, alpha, a_win, vert, slash, total, v_idx, v_cnt, s_idx, s_cnt, accounted=None, q_pos=None):
-        self._check(self.lib.ls_select_exact(self.h, C.byref(shape), alpha, _ptr(a_win), _ptr(q_pos), _ptr(vert), _ptr(slash),
-                                             _ptr(total), _ptr(v_idx), _ptr(v_cnt), v_idx.shape[-1], _ptr(s_idx),
-                                             _ptr(s_cnt), s_idx.shape[-1], _ptr(accounted), _stream()))
+        rc = self.native.select_exact(self.hv, shape, alpha, a_win, q_pos, vert, slash, total, v_idx, v_cnt, s_idx, s_cnt, accounted)
+        if rc:
+            self._check(rc)
 
     def ls_merge_lines(self, shape, a, b, out):
         """a, b, out: dicts with v_idx, v_cnt, s_idx, s_cnt (as alloc_select returns them)."""
-        args = []
-        for d in (a, b, out):
-            args += [_ptr(d["v_idx"]), _ptr(d["v_cnt"]), d["v_idx"].shape[-1], _ptr(d["s_idx"]), _ptr(d["s_cnt"]), d["s_idx"].shape[-1]]
-        self._check(self.lib.ls_merge_lines(self.h, C.byref(shape), *args, _stream()))
+        rc = self.native.merge_lines(self.hv, shape, a["v_idx"], a["v_cnt"], a["s_idx"], a["s_cnt"],
+                                     b["v_idx"], b["v_cnt"], b["s_idx"], b["s_cnt"],
+                                     out["v_idx"], out["v_cnt"], out["s_idx"], out["s_cnt"])
+        if rc:
+            self._check(rc)
 
     def ls_sparse_prefill(self, shape, q, k, v, v_idx, v_cnt, s_idx, s_cnt, out, lse=None):
-        self._check(self.lib.ls_sparse_prefill(self.h, C.byref(shape), _ptr(q), _ptr(k), _ptr(v), _ptr(v_idx),
-                                               _ptr(v_cnt), v_idx.shape[-1], _ptr(s_idx), _ptr(s_cnt),
-                                               s_idx.shape[-1], _ptr(out), _ptr(lse), _stream()))
+        rc = self.native.sparse_prefill(self.hv, shape, q, k, v, v_idx, v_cnt, s_idx, s_cnt, out, lse)
+        if rc:
+            self._check(rc)
 
     def ls_kv_compress(self, shape, budget, q_obs, k, v, keep_idx, keep_cnt, k_out=None, v_out=None):
-        self._check(self.lib.ls_kv_compress(self.h, C.byref(shape), budget, _ptr(q_obs), _ptr(k), _ptr(v),
-                                            _ptr(keep_idx), _ptr(keep_cnt), _ptr(k_out), _ptr(v_out), _stream()))
+        rc = self.native.kv_compress(self.hv, shape, budget, q_obs, k, v, keep_idx, keep_cnt, k_out, v_out)
+        if rc:
+            self._check(rc)
 
     def ls_decode_attend(self, shape, q, k_c, v_c, cnt, k_t, v_t, out, lse=None):
-        T = 0 if k_t is None else k_t.shape[2]
-        self._check(self.lib.ls_decode_attend(self.h, C.byref(shape), k_c.shape[2], T, _ptr(q), _ptr(k_c), _ptr(v_c),
-                                              _ptr(cnt), _ptr(k_t), _ptr(v_t), _ptr(out), _ptr(lse), _stream()))
+        rc = self.native.decode_attend(self.hv, shape, q, k_c, v_c, cnt, k_t, v_t, out, lse)
+        if rc:
+            self._check(rc)
 
     def ls_poll_status(self) -> int:
         """Waits for the current stream, returns the context's device status word and clears it."""

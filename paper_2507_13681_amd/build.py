@@ -1,12 +1,14 @@
-"""Builds libloopserve.so (HIP, gfx950) in-tree with hipcc."""
+"""Builds libloopserve.so (HIP, gfx950) in-tree with hipcc, and _lsnative.so, its Python marshalling, with the C compiler."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 _DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_DIR, "csrc")
 LIB = os.path.join(_DIR, "libloopserve.so")
+NATIVE = os.path.join(_DIR, "_lsnative.so")
 SOURCES = ["ls_api.hip", "ls_score.hip", "ls_select.hip", "ls_prefill.hip", "ls_decode.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -34,7 +36,18 @@ def build_library(verbose: bool = False) -> str:
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout)
+    build_native()
     return LIB
+
+
+def build_native() -> str:
+    """Compile the CPython module that marshals tensors into the C ABI; it finds libloopserve.so beside itself."""
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_path("include"),
+           os.path.join(CSRC, "ls_py.c"), "-o", NATIVE, "-L" + _DIR, "-l:libloopserve.so", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("native module failed:\n" + r.stdout)
+    return NATIVE
 
 
 if __name__ == "__main__":
