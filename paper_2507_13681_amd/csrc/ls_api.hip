@@ -25,6 +25,7 @@ struct ls_ctx {
     unsigned char* ws;
     size_t ws_bytes;
     int32_t* status;          // device status word (bits LS_STAT_*), OR-ed into by kernels, read and cleared by ls_poll_status
+    uint32_t* done;           // [MAX_KV_HEADS] workgroups finished per (batch, KV head) inside a launch; every launch leaves zeros
     int walk_spin_limit;      // bound of the waits inside walk_kernel (test hook)
     char err[256];
     // optional timing of the sparse attention kernel (ls_profile_*): event pairs on the call's stream
@@ -35,6 +36,7 @@ struct ls_ctx {
 namespace {
 
 constexpr size_t ALIGN = 256;
+constexpr size_t MAX_KV_HEADS = 65536;      // B * Hkv <= 65535 everywhere
 inline size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 int fail(ls_ctx* c, int code, const char* fmt, ...) {
@@ -169,8 +171,10 @@ int ls_create(ls_ctx** out, int device, size_t workspace_bytes) {
     if (init_device_once(device) != hipSuccess) { delete c; return LS_EHIP; }
     {
         void* p = nullptr;
-        if (hipMalloc(&p, ALIGN) != hipSuccess || hipMemset(p, 0, ALIGN) != hipSuccess) { if (p) (void)hipFree(p); delete c; return LS_EWORKSPACE; }
+        const size_t bytes = ALIGN + MAX_KV_HEADS * sizeof(uint32_t);
+        if (hipMalloc(&p, bytes) != hipSuccess || hipMemset(p, 0, bytes) != hipSuccess) { if (p) (void)hipFree(p); delete c; return LS_EWORKSPACE; }
         c->status = static_cast<int32_t*>(p);
+        c->done = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(p) + ALIGN);
     }
     if (workspace_bytes) {
         void* p = nullptr;
@@ -480,26 +484,11 @@ int ls_kv_compress_static(int device, const ls_shape* s, int32_t budget, const v
                           q_obs, k, v, keep_idx, keep_cnt, k_out, v_out, stream);
 }
 
-namespace {
-// split of the key axis for ls_decode_attend: chunks of whole 128-key rounds (4 waves x 32 keys),
-// enough workgroups to cover the chip about twice (more, shorter chunks measured slower: more partials to merge)
-void decode_split(const ls_shape* s, int32_t cap, int32_t T, int* nsplit, int* chunk) {
-    const int64_t L = (int64_t)cap + T;
-    const int64_t rounds = (L + 127) / 128;
-    int64_t want = 512 / ((int64_t)s->B * s->Hkv);
-    if (want < 1) want = 1;
-    if (want > rounds) want = rounds;
-    const int64_t per = (rounds + want - 1) / want;
-    *chunk = (int)(per * 128);
-    *nsplit = (int)((rounds + per - 1) / per);
-}
-}  // namespace
-
 size_t ls_decode_workspace_bytes(const ls_shape* s, int32_t cap, int32_t T) {
     if (!s || s->B <= 0 || s->Hq <= 0 || s->Hkv <= 0 || s->Hq % s->Hkv || (s->d != 64 && s->d != 128) || cap < 1 || T < 0) return 0;
     int nsplit, chunk;
-    decode_split(s, cap, T, &nsplit, &chunk);
-    return up((size_t)s->B * s->Hq * nsplit * (s->d + 2) * 4) + ALIGN;
+    ls::decode_split(s->B * s->Hkv, cap, T, &nsplit, &chunk);
+    return up((size_t)s->B * s->Hq * nsplit * ls::decode_part_floats(s->d) * 4) + ALIGN;
 }
 
 int ls_decode_attend(ls_ctx* c, const ls_shape* s, int32_t cap, int32_t T, const void* q, const void* k_c, const void* v_c,
@@ -519,10 +508,11 @@ int ls_decode_attend(ls_ctx* c, const ls_shape* s, int32_t cap, int32_t T, const
     a.q = q; a.kc = k_c; a.vc = v_c; a.kt = k_t; a.vt = v_t; a.cnt = cnt; a.out = out; a.lse = lse;
     a.B = s->B; a.Hq = s->Hq; a.Hkv = s->Hkv; a.G = s->Hq / s->Hkv; a.cap = cap; a.T = T;
     a.scale_log2e = scale_log2e(s);
-    decode_split(s, cap, T, &a.nsplit, &a.chunk);
-    if (ls::decode_smem_bytes(s->d, a.G) > 160 * 1024) return fail(c, LS_ESHAPE, "ls_decode_attend: group too large for LDS");
+    ls::decode_split(s->B * s->Hkv, cap, T, &a.nsplit, &a.chunk);
+    a.done = c->done;
+    if (ls::decode_smem_bytes(s->d, a.G, a.nsplit) > 156 * 1024) return fail(c, LS_ESHAPE, "ls_decode_attend: group too large for LDS");
     Bump bp{c->ws, c->ws_bytes, 0};
-    a.part = bp.take<float>((size_t)s->B * s->Hq * a.nsplit * (s->d + 2));
+    a.part = bp.take<float>((size_t)s->B * s->Hq * a.nsplit * ls::decode_part_floats(s->d));
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_decode_attend: workspace of %zu bytes is too small", c->ws_bytes);
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_decode_attend: hipSetDevice failed");
     hipError_t e = ls::run_decode(a, s->d, static_cast<hipStream_t>(stream));

@@ -4,241 +4,370 @@
 //     out = softmax(scale * q [K_c; K_t]^T) [V_c; V_t].
 //
 // The step reads every retained K and V row once and does 4 d FLOP per (query head, key): it is bound
-// by HBM bandwidth.  The G query heads of a KV head are the columns of one 32x32 MFMA tile product, so
-// the rows are read once for all of them:
-//   decode_partial_kernel  grid (splits, B*Hkv).  The keys of a KV head are cut into `splits` chunks;
-//                          in a workgroup each of the 4 waves takes 32-key tiles of the chunk.  K
-//                          fragments come straight from global memory (a key per lane), S^T = K Q^T,
-//                          online softmax per head in a lane, P -> bf16, O^T += V^T P^T with the V^T
-//                          fragments read transposed from a wave-private, swizzled LDS copy of the
-//                          32 V rows that a global -> LDS transfer filled.  The waves' partial results
-//                          (reference, normaliser, unnormalised output) are merged through LDS and
-//                          written per split.
-//   decode_combine_kernel  grid (B*Hq): merges the splits, normalises, writes out and lse.
+// by HBM bandwidth, at small sizes by latency.  The query heads of a KV head are the columns of the
+// 16x16 MFMA tile products (NH blocks of 16), so the rows are read once for all of them.
+//   decode_kernel  grid (splits, B*Hkv).  The keys of a KV head are cut into `splits` chunks of whole
+//                  32-key tiles; the waves of a workgroup take the chunk's tiles in turn.  K fragments
+//                  come straight from global memory (a key per lane, 64 contiguous bytes of a row per
+//                  load), S^T = K Q^T, online softmax per head in a lane, P -> bf16, O^T += V^T P^T with
+//                  the V^T fragments read transposed from a wave-private, swizzled LDS copy of the 32 V
+//                  rows that a global -> LDS transfer filled.  A wave has 16 KB in flight, a workgroup of
+//                  8 waves 128 KB: enough for its CU's share of the HBM bandwidth without prefetching
+//                  across tiles.  The waves' partial results (reference, normaliser, unnormalised output)
+//                  are merged through LDS; with one split that is the result, else they are written per
+//                  split and the workgroup that finishes a KV head last (a counter per KV head) merges
+//                  the splits.
+// One launch instead of a partial and a combine kernel: a launch costs 2-4 us in the stream and 2 us of
+// host time.  Merging splits costs about 3 us of memory round trips (write, counter, read), so the keys are
+// spread over the waves of a workgroup first and over workgroups second.  Measured (whole call, against
+// 32x32 tiles, 4 waves, two launches): B 4, 64 / 8 heads of 128, 2048 + 16 rows (34 MB) 19.2 -> 12.6 us, B 1,
+// 32 / 8 heads, 16384 rows (67 MB) 33.9 -> 18.0 us, 512 + 7 rows 12.0 -> 8.0 us, of which 4.7 us are those of
+// an empty kernel.  4 waves: 14.0 / 20.5 / 7.5-8.4 us; 16 waves: 14.9 / 19.5 / 9.1-10.2 us (one CU takes in no
+// more than 64 bytes a clock).
 // bf16 only (the transpose read is 16-bit).
 #include "ls_device.h"
 #include "ls_internal.h"
 
 namespace ls {
 
-constexpr int DEC_THREADS = 256;
 constexpr int DEC_TILE = 32;                   // keys per wave tile
+constexpr int DEC_WAVES = 8;                   // waves per workgroup
+constexpr int DEC_THREADS = 64 * DEC_WAVES;
 
-template <int D>
+template <int D, int NH>
 struct DecCfg {
     static_assert(D == 128 || D == 64, "head dimension");
+    static_assert(NH == 1 || NH == 2, "16 or 32 query heads");
     static constexpr int RB = D * 2;                      // bytes per row
     static constexpr int DS = RB / 16;                    // 16-byte slots per row
     static constexpr int RPI = 64 / DS;                   // rows per transfer instruction
     static constexpr int NIV = DEC_TILE / RPI;            // transfers per V tile
     static constexpr int V_BYTES = DEC_TILE * RB;         // one wave's V stage
-    static constexpr int KSTEPS = D / 16, DBLK = D / 32;
-    // slot swizzle of the staged V rows (XOR on the 16-byte slot index): makes the transpose reads touch
-    // every LDS bank once per pass
-    __device__ static constexpr int vswz(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
+    static constexpr int KC = D / 32;                     // 32-wide contraction chunks of a row
+    static constexpr int DB = D / 16;                     // 16-wide output blocks
+    static constexpr int PS = D + 4;                      // floats of a partial result: output, reference, normaliser, 2 unused
+    // slot swizzle of the staged V rows (XOR on the 16-byte slot index): the 16 rows a transpose read touches fall
+    // into different banks, two per bank as its 512 bytes need anyway
+    __device__ static constexpr int vswz(int row) { return D == 128 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); }
 };
 
-template <int D>
-__global__ __launch_bounds__(DEC_THREADS, 2) void decode_partial_kernel(DecodeArgs a) {
-    using C = DecCfg<D>;
+// Partial results are exchanged between workgroups of one launch, which may run on different XCDs, each with an L2
+// of its own: these accesses go to the memory all of them see.
+__device__ __forceinline__ void put_shared(float* p, float x, float y) {
+    __hip_atomic_store(reinterpret_cast<uint64_t*>(p), (uint64_t)__builtin_bit_cast(uint32_t, x) | ((uint64_t)__builtin_bit_cast(uint32_t, y) << 32),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 get_shared(const float* p) {
+    const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__builtin_bit_cast(float, (uint32_t)u), __builtin_bit_cast(float, (uint32_t)(u >> 32)));
+}
+
+template <int D, int NH>
+__global__ __launch_bounds__(DEC_THREADS) void decode_kernel(DecodeArgs a) {
+    using C = DecCfg<D, NH>;
     using T = bf16_t;
-    extern __shared__ __align__(16) unsigned char dec_lds[];   // 4 V stages; later the waves' partial results
+    extern __shared__ __align__(16) unsigned char dec_lds[];   // a V stage per wave; later the waves' partial results
+    __shared__ int last_s;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int r32 = lane & 31, g = lane >> 5;
+    const int m16 = lane & 15, q = lane >> 4;
     const int split = blockIdx.x, bk = blockIdx.y;
     const int b = bk / a.Hkv, kvh = bk % a.Hkv;
     const int G = a.G;
-    int nc = a.cnt ? a.cnt[bk] : a.cap;
-    if (nc < 0) nc = 0;
-    if (nc > a.cap) nc = a.cap;
-    nc = __builtin_amdgcn_readfirstlane(nc);
-    const int L = nc + a.T;                                    // keys of this KV head
-    const int k0 = split * a.chunk;
-    const int k1 = k0 + a.chunk < L ? k0 + a.chunk : L;
+    const int cnt_raw = a.cnt ? a.cnt[bk] : a.cap;             // asked for ahead of everything else
     const unsigned char* kc = reinterpret_cast<const unsigned char*>(a.kc) + (int64_t)bk * a.cap * C::RB;
     const unsigned char* vc = reinterpret_cast<const unsigned char*>(a.vc) + (int64_t)bk * a.cap * C::RB;
     const unsigned char* kt = reinterpret_cast<const unsigned char*>(a.kt) + (int64_t)bk * a.T * C::RB;
     const unsigned char* vt = reinterpret_cast<const unsigned char*>(a.vt) + (int64_t)bk * a.T * C::RB;
-    auto row_of = [&](const unsigned char* retained, const unsigned char* tail, int key) -> const unsigned char* {
-        return key < nc ? retained + (int64_t)key * C::RB : tail + (int64_t)(key - nc) * C::RB;
-    };
-
-    // query fragments: head r32 of the group is column r32 of the tile product
-    Frag<T> qf[C::KSTEPS];
-    if (r32 < G) {
-        const T* qrow = reinterpret_cast<const T*>(a.q) + ((int64_t)b * a.Hq + kvh * G + r32) * D;
-#pragma unroll
-        for (int c = 0; c < C::KSTEPS; ++c) load_frag(qf[c], qrow + 16 * c + 8 * g);
-    } else {
-#pragma unroll
-        for (int c = 0; c < C::KSTEPS; ++c) zero_frag(qf[c]);
-    }
-    f32x16 oacc[C::DBLK];
-#pragma unroll
-    for (int i = 0; i < C::DBLK; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;                      // m_run in raw logit units
-    const float sc2 = a.scale_log2e;
 
     unsigned char* stage = dec_lds + wv * C::V_BYTES;
     const uint32_t stage_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)stage;
-    // transfers: this lane fills slot sl of tile row RPI*q + lane / DS and fetches the chunk the swizzle assigns to it
-    const int trow = lane / C::DS, sl = lane % C::DS;
-    // transpose reads: key 4g + L16/4 (+8, +16 q4), 64-byte block i
-    int vaddr[C::DBLK];
-    {
-        const int L16 = lane & 15, beta = (lane >> 4) & 1;
-        const int lrow = 4 * g + (L16 >> 2);
-        const int y = C::vswz(lrow) >> 2;
+    const int trow = lane / C::DS, sl = lane % C::DS;          // a transfer: this lane fills slot sl of tile row RPI * i + trow
+    // rows r0 .. r0 + 31 of `v` -> LDS, of `k` -> fragments; rows from `rows` on repeat the last one
+    auto request_v = [&](const unsigned char* v, int r0, int rows) {
 #pragma unroll
-        for (int i = 0; i < C::DBLK; ++i) vaddr[i] = lrow * C::RB + 64 * (i ^ y) + 32 * beta + 8 * (L16 & 3);
-    }
+        for (int i = 0; i < C::NIV; ++i) {
+            const int row = C::RPI * i + trow;
+            const int r = r0 + row < rows ? r0 + row : rows - 1;
+            dma16(v + (int64_t)r * C::RB + 16 * (sl ^ C::vswz(row)), stage_lds + (uint32_t)(i * 1024));
+        }
+    };
+    bf16x8 kf[2][C::KC];                                       // keys m16 and 16 + m16 of the tile, 8 values from 32 c + 8 q on
+    auto request_k = [&](const unsigned char* k, int r0, int rows) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int r = r0 + 16 * h + m16 < rows ? r0 + 16 * h + m16 : rows - 1;
+            const unsigned char* krow = k + (int64_t)r * C::RB;
+#pragma unroll
+            for (int c = 0; c < C::KC; ++c) kf[h][c] = *reinterpret_cast<const bf16x8*>(krow + 64 * c + 16 * q);
+        }
+    };
+    // Tiles of a KV head: first those of the retained rows, then those of the tail.  This wave's first tile is requested
+    // before the count is here, as if every row of the cache were retained: right for all but a tile of the tail behind
+    // a cache that is not full, which is requested again.  Rows past the count may be read then; they are masked (K)
+    // and zeroed (V) below, whatever they hold.
+    const int tail_tiles = (a.T + DEC_TILE - 1) / DEC_TILE;
+    const int tile0 = split * a.chunk;
+    int t = tile0 + wv;
+    auto request_at = [&](int tile, int ctiles, int rows_c, bool v_part, bool k_part) {
+        const bool tail = tile >= ctiles;
+        const int r0 = DEC_TILE * (tail ? tile - ctiles : tile), rows = tail ? a.T : rows_c;
+        if (v_part) request_v(tail ? vt : vc, r0, rows);
+        if (k_part) request_k(tail ? kt : kc, r0, rows);
+    };
+    const int cap_tiles = (a.cap + DEC_TILE - 1) / DEC_TILE;
+    const bool early = wv < a.chunk && t < cap_tiles + tail_tiles;
+    if (early) request_at(t, cap_tiles, a.cap, true, true);
 
-    for (int t0 = k0 + DEC_TILE * wv; t0 < k1; t0 += 4 * DEC_TILE) {
-        // V rows of the tile -> LDS (rows past the chunk re-load its last row; their keys are masked)
+    bf16x8 qf[NH][C::KC];                                      // head 16 h + m16 of the group
 #pragma unroll
-        for (int q = 0; q < C::NIV; ++q) {
-            const int row = C::RPI * q + trow;
-            int key = t0 + row; if (key > k1 - 1) key = k1 - 1;
-            dma16(row_of(vc, vt, key) + 16 * (sl ^ C::vswz(row)), stage_lds + (uint32_t)(q * 1024));
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+        for (int c = 0; c < C::KC; ++c) {
+            const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+            qf[h][c] = __builtin_bit_cast(bf16x8, z);
+            if (16 * h + m16 < G)
+                qf[h][c] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const T*>(a.q) + ((int64_t)b * a.Hq + kvh * G + 16 * h + m16) * D + 32 * c + 8 * q);
         }
-        // K fragments of this lane's key, S^T = K Q^T
-        int mykey = t0 + r32; if (mykey > k1 - 1) mykey = k1 - 1;
-        const unsigned char* krow = row_of(kc, kt, mykey);
-        Frag<T> kf[C::KSTEPS];
+    int nc = cnt_raw < 0 ? 0 : cnt_raw;
+    if (nc > a.cap) nc = a.cap;
+    nc = __builtin_amdgcn_readfirstlane(nc);
+    const int ctiles = (nc + DEC_TILE - 1) / DEC_TILE;         // tiles of this KV head: ctiles + tail_tiles
+    const int tend = tile0 + a.chunk < ctiles + tail_tiles ? tile0 + a.chunk : ctiles + tail_tiles;
+    if (t < tend && t >= ctiles && ctiles != cap_tiles) {
+        wait_transfers();                                      // the rows asked for early have landed: the stage is free
+        request_at(t, ctiles, nc, true, true);
+    }
+    f32x4 oacc[NH][C::DB];                                     // O^T: element r of block i is d = 16 i + 4 q + r of head m16
+    float m_run[NH], l_run[NH];                                // reference in raw logit units; this lane's share of the normaliser
 #pragma unroll
-        for (int c = 0; c < C::KSTEPS; ++c) load_frag(kf[c], krow + 32 * c + 16 * g);
-        f32x16 s = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int h = 0; h < NH; ++h) {
+        m_run[h] = -INFINITY; l_run[h] = 0.f;
 #pragma unroll
-        for (int c = 0; c < C::KSTEPS; ++c) mma(s, kf[c], qf[c]);      // s[r] = <k_{8(r/4)+4g+r%4}, q_head>
-        const int left = k1 - t0;                                      // keys of the tile that exist
-        float mx = -INFINITY;
+        for (int i = 0; i < C::DB; ++i) oacc[h][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const float sc2 = a.scale_log2e;
+    // transpose reads: in a block of 16 lanes lane s points at key 4q + s/4 (+ 16) and d-offset 4 (s%4) of block i, and
+    // receives four keys of column d = 16 i + s
+    const int vrow = 4 * q + (m16 >> 2);
+    const int vbase = vrow * C::RB + 8 * (m16 & 1);
+    const int vslot = (m16 >> 1) & 1;                          // 16-byte slot inside block i's 32 bytes
+
+    for (; t < tend; t += DEC_WAVES) {
+        wait_transfers();                                              // this tile's rows are here (the same wave reads them)
+        const int left = t < ctiles ? nc - DEC_TILE * t : a.T - DEC_TILE * (t - ctiles);      // keys of the tile that exist
+        if (left < DEC_TILE) {                                         // the V rows of masked keys meet weight 0: make them finite
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int key = 8 * (r >> 2) + 4 * g + (r & 3);
-            const float x = key < left ? s[r] : -INFINITY;
-            s[r] = x;
-            mx = fmaxf(mx, x);
+            for (int i = 0; i < C::NIV; ++i)
+                if (C::RPI * i + trow >= left) *reinterpret_cast<f32x4*>(stage + i * 1024 + 16 * lane) = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        mx = fmaxf(mx, xor32(mx));
-        const float m_new = fmaxf(m_run, mx);                          // finite: the tile holds at least one key
-        const float corr = fast_exp2((m_run - m_new) * sc2);
-        const float mneg = -m_new * sc2;
-        m_run = m_new;
-        float ps = 0.f;
+        f32x4 s[NH][2];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const float p = fast_exp2(__builtin_fmaf(s[r], sc2, mneg));
-            s[r] = p;
-            ps += p;
-        }
-        l_run = l_run * corr + ps;
-        if (__ballot(corr != 1.0f) != 0ull) {
+        for (int h = 0; h < NH; ++h)
 #pragma unroll
-            for (int i = 0; i < C::DBLK; ++i)
+            for (int e = 0; e < 2; ++e) {
+                s[h][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[i][r] *= corr;
-        }
-        wait_transfers();                                              // the V rows have landed (same wave reads them)
-#pragma unroll
-        for (int q4 = 0; q4 < 2; ++q4) {
-            float pv[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) pv[e] = s[8 * q4 + e];
-            Frag<T> pf;
-            pack_frag(pf, pv);
-#pragma unroll
-            for (int i = 0; i < C::DBLK; ++i) {
-                Frag<T> vf;
-                const unsigned char* va = stage + vaddr[i] + 16 * q4 * C::RB;
-                load_frag_tr(vf, va, va + 8 * C::RB);
-                mma(oacc[i], vf, pf);
+                for (int c = 0; c < C::KC; ++c)                        // s[h][e][r] = <k_{16 e + 4 q + r}, q_{head 16 h + m16}>
+                    s[h][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[e][c], qf[h][c], s[h][e], 0, 0, 0);
             }
+        const bool more = t + DEC_WAVES < tend;
+        if (more) request_at(t + DEC_WAVES, ctiles, nc, false, true);
+        bf16x8 pf[NH];
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+            float x[8], mx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                x[r] = 16 * (r >> 2) + 4 * q + (r & 3) < left ? s[h][r >> 2][r & 3] : -INFINITY;
+                mx = fmaxf(mx, x[r]);
+            }
+            mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+            const float m_new = fmaxf(m_run[h], mx);                   // finite: the tile holds at least one key
+            const float corr = fast_exp2((m_run[h] - m_new) * sc2);
+            const float mneg = -m_new * sc2;
+            m_run[h] = m_new;
+            float ps = 0.f;
+#pragma unroll
+            for (int r = 0; r < 8; ++r) { x[r] = fast_exp2(__builtin_fmaf(x[r], sc2, mneg)); ps += x[r]; }
+            l_run[h] = l_run[h] * corr + ps;
+            if (__ballot(corr != 1.0f) != 0ull) {
+#pragma unroll
+                for (int i = 0; i < C::DB; ++i) oacc[h][i] *= corr;
+            }
+            Frag<T> f;
+            pack_frag(f, x);                                           // contraction index 8 q + r <-> key 16 (r / 4) + 4 q + r % 4
+            pf[h] = f.v;
+        }
+#pragma unroll
+        for (int i = 0; i < C::DB; ++i) {
+            const unsigned char* va = stage + vbase + 16 * ((2 * i + vslot) ^ C::vswz(vrow));      // vswz(vrow + 16) is the same
+            Frag<T> vf;
+            load_frag_tr(vf, va, va + 16 * C::RB);
+#pragma unroll
+            for (int h = 0; h < NH; ++h) oacc[h][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf.v, pf[h], oacc[h][i], 0, 0, 0);
+        }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // the stage has been read
+            request_at(t + DEC_WAVES, ctiles, nc, true, false);
         }
     }
 
-    // ---- merge the four waves through LDS: part[wv][head][D + 2] (output, reference, normaliser)
-    const float l_tot = l_run + xor32(l_run);
+    // ---- merge the waves through LDS: part[wv][head][PS]
     __syncthreads();                                                   // every wave is done with its V stage
     float* part = reinterpret_cast<float*>(dec_lds);
-    constexpr int PS = D + 2;
-    if (r32 < G) {
-        float* mine = part + ((int64_t)wv * G + r32) * PS;
+    constexpr int PS = C::PS;
 #pragma unroll
-        for (int i = 0; i < C::DBLK; ++i)
+    for (int h = 0; h < NH; ++h) {
+        float l = l_run[h] + __shfl_xor(l_run[h], 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (16 * h + m16 < G) {
+            float* mine = part + (wv * G + 16 * h + m16) * PS;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) mine[32 * i + 8 * (r >> 2) + 4 * g + (r & 3)] = oacc[i][r];
-        if (g == 0) { mine[D] = m_run; mine[D + 1] = l_tot; }
+            for (int i = 0; i < C::DB; ++i) *reinterpret_cast<f32x4*>(mine + 16 * i + 4 * q) = oacc[h][i];
+            if (q == 0) { mine[D] = m_run[h]; mine[D + 1] = l; }
+        }
     }
     __syncthreads();
-    for (int idx = tid; idx < G * PS; idx += DEC_THREADS) {
-        const int head = idx / PS, dd = idx % PS;
-        float m = -INFINITY;
+    bf16_t* out = reinterpret_cast<bf16_t*>(a.out) + ((int64_t)b * a.Hq + kvh * G) * D;
+    float* lse = a.lse ? a.lse + (int64_t)b * a.Hq + kvh * G : nullptr;
+    auto finish = [&](int head, int dd, float m, float o0, float o1, float l) {   // two output elements (dd == 0 also writes lse)
+        *reinterpret_cast<uint32_t*>(out + head * D + dd) = (uint32_t)f2bf(l > 0.f ? o0 / l : 0.f) | ((uint32_t)f2bf(l > 0.f ? o1 / l : 0.f) << 16);
+        if (lse && dd == 0) lse[head] = l > 0.f ? (m * sc2 + log2f(l)) * 0.69314718055994531f : -INFINITY;
+    };
+    float* shared_part = a.part + (int64_t)bk * a.nsplit * G * PS;     // [split][head][PS]
+    const int items = G * (D / 2);                                     // two neighbouring elements of a head
+    for (int idx = tid; idx < items; idx += DEC_THREADS) {
+        const int head = idx / (D / 2), dd = 2 * (idx % (D / 2));
+        float m = -INFINITY, o0 = 0.f, o1 = 0.f, l = 0.f;
+        float2 ml[DEC_WAVES], x[DEC_WAVES];                                    // (a wave without a tile: reference -inf, zeros)
 #pragma unroll
-        for (int w = 0; w < 4; ++w) m = fmaxf(m, part[((int64_t)w * G + head) * PS + D]);
-        float acc = 0.f;
-        if (dd != D) {                                                 // output element or normaliser: scaled sum over the waves
+        for (int w = 0; w < DEC_WAVES; ++w) {
+            const float* pw = part + (w * G + head) * PS;
+            ml[w] = *reinterpret_cast<const float2*>(pw + D);
+            x[w] = *reinterpret_cast<const float2*>(pw + dd);
+            m = fmaxf(m, ml[w].x);
+        }
 #pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const float mw = part[((int64_t)w * G + head) * PS + D];
-                if (mw > -INFINITY) acc += part[((int64_t)w * G + head) * PS + dd] * fast_exp2((mw - m) * sc2);
+        for (int w = 0; w < DEC_WAVES; ++w) {
+            const float wgt = ml[w].x > -INFINITY ? fast_exp2((ml[w].x - m) * sc2) : 0.f;
+            o0 += x[w].x * wgt; o1 += x[w].y * wgt;
+            l += ml[w].y * wgt;
+        }
+        if (a.nsplit == 1) { finish(head, dd, m, o0, o1, l); continue; }
+        float* dst = shared_part + ((int64_t)split * G + head) * PS;
+        put_shared(dst + dd, o0, o1);
+        if (dd == 0) put_shared(dst + D, m, l);
+    }
+    if (a.nsplit == 1) return;
+
+    // ---- the last workgroup of this KV head to get here merges the splits
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // this wave's part of the result has been written
+    __syncthreads();
+    if (tid == 0) {
+        const uint32_t before = __hip_atomic_fetch_add(a.done + bk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last_s = before == (uint32_t)a.nsplit - 1u;
+        if (last_s) __hip_atomic_store(a.done + bk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
+    }
+    __syncthreads();
+    if (!last_s) return;
+    // A thread owns two elements of a head and every `subs`-th split; the subsets are added through LDS.
+    const int subs = items >= DEC_THREADS ? 1 : DEC_THREADS / items;
+    float2* ml = reinterpret_cast<float2*>(dec_lds);                   // [head][split] reference, normaliser
+    float* add = reinterpret_cast<float*>(dec_lds) + 2 * G * a.nsplit; // [sub][item][2]
+    constexpr int BATCH = 8;                                           // splits whose values are in flight together
+    for (int idx0 = 0; idx0 < items; idx0 += DEC_THREADS) {
+        const int idx = idx0 + (subs == 1 ? tid : tid % items), sub = subs == 1 ? 0 : tid / items;
+        const bool on = idx < items && sub < subs;
+        const int head = on ? idx / (D / 2) : 0, dd = on ? 2 * (idx % (D / 2)) : 0;
+        const float* src = shared_part + (int64_t)head * PS + dd;
+        float2 x[BATCH];
+        auto fetch = [&](int s0) {
+#pragma unroll
+            for (int e = 0; e < BATCH; ++e) {
+                const int s = s0 + e * subs;
+                x[e] = get_shared(src + (int64_t)(s < a.nsplit ? s : a.nsplit - 1) * G * PS);
+            }
+        };
+        fetch(sub);
+        if (idx0 == 0) {
+            for (int i = tid; i < G * a.nsplit; i += DEC_THREADS) ml[i] = get_shared(shared_part + ((int64_t)(i % a.nsplit) * G + i / a.nsplit) * PS + D);
+            __syncthreads();
+        }
+        const float2* mh = ml + head * a.nsplit;
+        float m = -INFINITY, o0 = 0.f, o1 = 0.f, l = 0.f;
+        for (int s = 0; s < a.nsplit; ++s) m = fmaxf(m, mh[s].x);
+        for (int s0 = sub; s0 < a.nsplit; s0 += BATCH * subs) {
+            if (s0 != sub) fetch(s0);
+#pragma unroll
+            for (int e = 0; e < BATCH; ++e) {
+                const int s = s0 + e * subs;
+                if (s < a.nsplit && mh[s].x > -INFINITY) {
+                    const float wgt = fast_exp2((mh[s].x - m) * sc2);
+                    o0 += x[e].x * wgt; o1 += x[e].y * wgt;
+                    l += mh[s].y * wgt;
+                }
             }
         }
-        float* dst = a.part + (((int64_t)bk * a.nsplit + split) * G + head) * PS;
-        dst[dd] = dd == D ? m : acc;
-    }
-}
-
-// grid (B*Hq), D threads: thread dd owns one output element.
-template <int D>
-__global__ __launch_bounds__(D) void decode_combine_kernel(DecodeArgs a) {
-    constexpr int PS = D + 2;
-    const int bh = blockIdx.x, dd = threadIdx.x;
-    const int b = bh / a.Hq, h = bh % a.Hq, kvh = h / a.G, hh = h % a.G;
-    const int bk = b * a.Hkv + kvh;
-    const float* base = a.part + ((int64_t)bk * a.nsplit * a.G + hh) * PS;
-    const int64_t stride = (int64_t)a.G * PS;
-    float m = -INFINITY;
-    for (int s = 0; s < a.nsplit; ++s) m = fmaxf(m, base[s * stride + D]);
-    float o = 0.f, l = 0.f;
-    for (int s = 0; s < a.nsplit; ++s) {
-        const float ms = base[s * stride + D];
-        if (ms > -INFINITY) {
-            const float wgt = fast_exp2((ms - m) * a.scale_log2e);
-            o += base[s * stride + dd] * wgt;
-            l += base[s * stride + D + 1] * wgt;
+        if (subs > 1) {
+            if (on && sub > 0) { float* p = add + 4 * ((sub - 1) * items + idx); p[0] = o0; p[1] = o1; p[2] = l; }
+            __syncthreads();
+            if (on && sub == 0)
+                for (int u = 1; u < subs; ++u) { const float* p = add + 4 * ((u - 1) * items + idx); o0 += p[0]; o1 += p[1]; l += p[2]; }
         }
+        if (on && sub == 0) finish(head, dd, m, o0, o1, l);
     }
-    bf16_t* out = reinterpret_cast<bf16_t*>(a.out) + (int64_t)bh * D;
-    bf16_t r; r.bits = f2bf(l > 0.f ? o / l : 0.f);
-    out[dd] = r;
-    if (a.lse && dd == 0) a.lse[bh] = l > 0.f ? (m * a.scale_log2e + log2f(l)) * 0.69314718055994531f : -INFINITY;
 }
 
-size_t decode_smem_bytes(int d, int G) {
-    const size_t stages = 4 * (size_t)DEC_TILE * d * 2;
-    const size_t merge = 4 * (size_t)G * (d + 2) * 4;
-    return stages > merge ? stages : merge;
+template <int D, int NH>
+static size_t decode_smem_t(int G, int nsplit) {
+    using C = DecCfg<D, NH>;
+    const size_t stages = (size_t)DEC_WAVES * C::V_BYTES;
+    const size_t merge = (size_t)DEC_WAVES * G * C::PS * 4;
+    const size_t splits = nsplit == 1 ? 0 : 2 * (size_t)G * nsplit * 4 + 4 * (size_t)DEC_THREADS * 4;
+    const size_t m = stages > merge ? stages : merge;
+    return m > splits ? m : splits;
+}
+size_t decode_smem_bytes(int d, int G, int nsplit) {
+    if (d == 128) return G <= 16 ? decode_smem_t<128, 1>(G, nsplit) : decode_smem_t<128, 2>(G, nsplit);
+    return G <= 16 ? decode_smem_t<64, 1>(G, nsplit) : decode_smem_t<64, 2>(G, nsplit);
+}
+size_t decode_part_floats(int d) { return (size_t)d + 4; }
+
+// Split of the key axis: `chunk` tiles of a KV head per workgroup.  As many workgroups as the chip has compute units,
+// but at least four tiles in each, and no split at all while the waves of one workgroup get through with two or three
+// tiles each (measured at 8 KV heads of 128: 17 tiles 8.0 us in one workgroup, 8.2 us in four, 7.9 us in eight; 32
+// tiles 10.7 / 8.3 / 8.2 us; 512 workgroups instead of 256 cost 10 to 50 % on large caches).
+void decode_split(int BK, int cap, int T, int* nsplit, int* chunk) {
+    const int tiles = (cap + DEC_TILE - 1) / DEC_TILE + (T + DEC_TILE - 1) / DEC_TILE;
+    int want = 256 / BK;
+    const int most = tiles <= 2 * DEC_WAVES + 2 ? 1 : tiles / 4;
+    if (want > most) want = most;
+    if (want > 128) want = 128;
+    if (want < 1) want = 1;
+    *chunk = (tiles + want - 1) / want;
+    *nsplit = (tiles + *chunk - 1) / *chunk;
 }
 
-template <int D>
+template <int D, int NH>
 static hipError_t run_decode_t(const DecodeArgs& a, hipStream_t st) {
-    const size_t smem = decode_smem_bytes(D, a.G);
-    hipLaunchKernelGGL((decode_partial_kernel<D>), dim3(a.nsplit, a.B * a.Hkv), dim3(DEC_THREADS), smem, st, a);
-    hipLaunchKernelGGL((decode_combine_kernel<D>), dim3(a.B * a.Hq), dim3(D), 0, st, a);
+    const size_t smem = decode_smem_t<D, NH>(a.G, a.nsplit);
+    hipLaunchKernelGGL((decode_kernel<D, NH>), dim3(a.nsplit, a.B * a.Hkv), dim3(DEC_THREADS), smem, st, a);
     return hipGetLastError();
 }
 
 hipError_t init_decode_kernels() {
-    const hipError_t e = allow_full_lds(&decode_partial_kernel<128>);
-    return e != hipSuccess ? e : allow_full_lds(&decode_partial_kernel<64>);
+    hipError_t e;
+    if ((e = allow_full_lds(&decode_kernel<128, 1>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&decode_kernel<128, 2>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&decode_kernel<64, 1>)) != hipSuccess) return e;
+    return allow_full_lds(&decode_kernel<64, 2>);
 }
 
 hipError_t run_decode(const DecodeArgs& a, int d, hipStream_t st) {
-    if (d == 128) return run_decode_t<128>(a, st);
-    if (d == 64) return run_decode_t<64>(a, st);
+    if (d == 128) return a.G <= 16 ? run_decode_t<128, 1>(a, st) : run_decode_t<128, 2>(a, st);
+    if (d == 64) return a.G <= 16 ? run_decode_t<64, 1>(a, st) : run_decode_t<64, 2>(a, st);
     return hipErrorInvalidValue;
 }
 

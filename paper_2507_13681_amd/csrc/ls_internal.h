@@ -105,7 +105,8 @@ struct DecodeArgs {
     const int32_t* cnt;       // [B][Hkv] or NULL (all cap rows)
     void* out;                // [B][Hq][d]
     float* lse;               // [B][Hq] or NULL
-    float* part;              // [B*Hkv][nsplit][G][d + 2] per-split output, reference, normaliser
+    float* part;              // [B*Hkv][nsplit][G][d + 4] per-split output, reference, normaliser
+    uint32_t* done;           // [B*Hkv] splits finished; zero between calls
     int B, Hq, Hkv, G, cap, T, nsplit, chunk;
     float scale_log2e;
 };
@@ -134,7 +135,9 @@ hipError_t init_decode_kernels();
 
 hipError_t run_score(const ScoreArgs& a, int dtype, int d, int mode, hipStream_t st);
 hipError_t run_decode(const DecodeArgs& a, int d, hipStream_t st);
-size_t decode_smem_bytes(int d, int G);
+size_t decode_smem_bytes(int d, int G, int nsplit);
+size_t decode_part_floats(int d);                                   // floats of one partial result
+void decode_split(int BK, int cap, int T, int* nsplit, int* chunk);   // chunk: 32-key tiles per workgroup
 size_t score_lines_smem(int w, int dtype, int d, int mode);
 // Union of two selections per head (the accumulated line set of Alg. 1): lists a and b in, ascending unique list out.
 struct MergeArgs {
