@@ -134,7 +134,7 @@ inline int tab_len_of(int64_t n) { return (int)(n / 64) + 4; }
 size_t ws_prefill(const ls_shape* s) {
     const size_t BH = (size_t)s->B * s->Hq;
     const size_t items = BH * (size_t)(s->n / 128 + 2);          // (head, row block) work items, upper bound
-    return up(BH * (size_t)(words_of(s->n) + 1) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(BH) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
+    return up(BH * (size_t)(words_of(s->n) + 4) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(BH) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
            up(8 * items * 4) + 2 * up(8 * 4);
 }
 size_t ws_compress(const ls_shape* s) {
@@ -333,7 +333,7 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     const int BH = s->B * s->Hq;
     const int words = words_of(s->n), tab_len = tab_len_of(s->n);
     Bump bp{c->ws, c->ws_bytes, 0};
-    w.obits = bp.take<uint32_t>((size_t)BH * (words + 1));
+    w.obits = bp.take<uint32_t>((size_t)BH * (words + 4));
     w.hflag = bp.take<uint8_t>((size_t)BH);
     w.cost = bp.take<uint32_t>((size_t)BH);
     w.pref = bp.take<uint16_t>((size_t)BH * (tab_len + 1));
@@ -367,7 +367,7 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
     if (cap_v <= 0 || cap_s <= 0) return fail(c, LS_ESHAPE, "ls_sparse_prefill: capacities must be positive");
     const int BH = s->B * s->Hq;
     const int words = words_of(s->n), tab_len = tab_len_of(s->n);
-    if (ls::prefill_smem_bytes(s->dtype, s->d, words, tab_len) > 160 * 1024)
+    if (ls::prefill_smem_bytes(s->dtype, s->d, tab_len) > 160 * 1024)
         return fail(c, LS_ESHAPE, "ls_sparse_prefill: n too large for the LDS bitmaps");
     PrefillCarve w;
     if (const char* m = carve_prefill(c, s, w)) return fail(c, w.code, "ls_sparse_prefill: %s", m);

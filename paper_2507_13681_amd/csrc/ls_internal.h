@@ -59,7 +59,7 @@ struct PlanArgs {
     int words, tab_len;
     const int32_t *v_idx, *v_cnt, *s_idx, *s_cnt;
     int cap_v, cap_s;
-    uint32_t* obits;          // [BH][words]
+    uint32_t* obits;          // [BH][4 + words], four zero words first
     uint8_t* tab;             // [BH][tab_len]
     uint8_t* hflag;           // [BH]
     uint32_t* cost;           // [BH] estimated tiles per row block (for the work queues)
@@ -160,7 +160,7 @@ hipError_t launch_plan(const PlanArgs& a, int BH, hipStream_t st);
 hipError_t launch_sched(const SchedArgs& a, hipStream_t st);
 // ev0 / ev1 (both or neither): events that receive the start and stop time of the attention kernel's own dispatch
 hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-size_t prefill_smem_bytes(int dtype, int d, int words, int tab_len);
+size_t prefill_smem_bytes(int dtype, int d, int tab_len);
 int prefill_block_rows();
 
 }  // namespace ls

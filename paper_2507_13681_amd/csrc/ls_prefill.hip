@@ -40,7 +40,7 @@ constexpr int PREFILL_THREADS = 256;
 
 // ---------------------------------------------------------------------------------------------
 // plan: per (batch, head) bitmap of the selected diagonals, the per-j activity table, a head flag.
-//   obits : [BH][words + 1] uint32: one zero word, then bit o in word 1 + o/32; words = n/32 rounded up + 8 zero words
+//   obits : [BH][4 + words] uint32: four zero words, then bit o in word 4 + o/32; words = n/32 rounded up + 8 zero words
 //   tab   : [BH][tab_len] bytes, entry j+1 for j = -1 .. ; bit0 = some diagonal of
 //           [64j-63, 64j+127] is selected, bit1 = all of them are (and none is cut off at 0 or n-1)
 //   hflag : [BH] bytes, bit0 = every diagonal 0..n-1 is selected (the mask is plain causal),
@@ -64,6 +64,7 @@ __device__ __forceinline__ uint32_t block_scan_1024(uint32_t v, uint32_t* wsum, 
     return before + inc - v;
 }
 
+constexpr int OB_PAD = 4;                    // zero words in front of a head's bitmap (rows above a tile's keys)
 constexpr int LS_MAX_TAB = 262144 / 64 + 8;  // table entries at the largest supported context
 __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     extern __shared__ uint32_t sm[];
@@ -140,9 +141,9 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     }
     __syncthreads();
     int mine = 0;
-    uint32_t* og = a.obits + (int64_t)bh * (words + 1);       // one zero word, then the bitmap
-    if (tid == 0) og[0] = 0u;
-    for (int i = tid; i < words; i += blockDim.x) { og[i + 1] = sm[i]; mine += __popc(sm[i]); }
+    uint32_t* og = a.obits + (int64_t)bh * (OB_PAD + words);  // zero words, then the bitmap
+    if (tid < OB_PAD) og[tid] = 0u;
+    for (int i = tid; i < words; i += blockDim.x) { og[OB_PAD + i] = sm[i]; mine += __popc(sm[i]); }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mine += __shfl_down(mine, off, 64);       // one atomic per wave, not per thread
     if ((tid & 63) == 0) atomicAdd(&total_bits, mine);
@@ -359,13 +360,81 @@ __device__ __forceinline__ void store_out4(float* p, float a, float b, float c, 
     *reinterpret_cast<f32x4*>(p) = v;
 }
 
-// 32 consecutive bits of a bitmap starting at bit `base` (may be negative: those bits read 0).
-// `bits1` is the bitmap preceded by one zero word (bits1[i + 1] = word i), which makes this branch-free.
-__device__ __forceinline__ uint32_t window32(const uint32_t* bits1, int64_t base) {
-    const int b32 = (int)(base < -32 ? -32 : base) + 32;     // >= 0, bit index in the padded map
-    const int wd = b32 >> 5, sh = b32 & 31;
-    const uint64_t x = (uint64_t)bits1[wd] | ((uint64_t)bits1[wd + 1] << 32);
-    return (uint32_t)(x >> sh);
+// ---- cell masks -------------------------------------------------------------------------------
+// A wave's 32 rows start at a position that is a multiple of 32 and a contiguous tile at a key that is one of 64, so
+// row i and key k of the tile meet on diagonal 32 Q + i - k with a wave-uniform Q: three words of the bitmap cover the
+// wave's part of the tile, and the bits a lane needs are a shift by its row.  The words are uniform (scalar loads,
+// requested one tile ahead), and so are the questions whether a 32 x 32 sub-tile has an allowed cell at all and
+// whether all of its cells are allowed.  (Bit by bit windows with 64-bit index arithmetic per lane and a ballot per
+// question took 103 instructions per wave and tile of about 600.)
+typedef const __attribute__((address_space(4))) uint32_t* const_words;    // read-only for the whole kernel: scalar loads
+
+struct DiagWords { uint32_t x0, x1, x2; };                // diagonals 32 Q - 64 .. 32 Q + 31
+__device__ __forceinline__ DiagWords diag_words(const_words ob, int posw, int key0) {
+    const int q = (posw - key0) >> 5;                     // >= -2
+    return {ob[q - 2 + OB_PAD], ob[q - 1 + OB_PAD], ob[q + OB_PAD]};
+}
+// What a wave may see of a 64-key tile: bit 8 (r/4) + r % 4 of am[h] = key 32 h + 8 (r/4) + 4 g + r % 4 is allowed for
+// this lane's row (the key that accumulator register r of the lane holds)
+struct TileMask { uint32_t am[2]; bool act[2], full[2]; };
+__device__ __forceinline__ TileMask diag_mask(const DiagWords& w, int r32, int g) {
+    TileMask m;
+    m.act[0] = ((w.x1 & ~1u) | w.x2) != 0u;
+    m.act[1] = ((w.x0 & ~1u) | w.x1) != 0u;
+    m.full[0] = (w.x2 & (w.x1 | 1u)) == 0xFFFFFFFFu;
+    m.full[1] = (w.x1 & (w.x0 | 1u)) == 0xFFFFFFFFu;
+    m.am[0] = __brev((uint32_t)((((uint64_t)w.x2 << 32) | w.x1) >> (r32 + 1))) >> (4 * g);
+    m.am[1] = __brev((uint32_t)((((uint64_t)w.x1 << 32) | w.x0) >> (r32 + 1))) >> (4 * g);
+    return m;
+}
+// 32 x 32 bit transpose inside each half of the wave: bit c of lane r <- bit r of lane c
+__device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane) {
+#define LS_STEP(j, m, moved)                                                                          \
+    { const uint32_t p = (uint32_t)(moved); x = (lane & (j)) ? (((p >> (j)) & (m)) | (x & ~(m))) : ((x & (m)) | ((p & (m)) << (j))); }
+    LS_STEP(16, 0x0000FFFFu, __builtin_amdgcn_ds_swizzle((int)x, 0x401F))                              // lane ^ 16
+    LS_STEP(8, 0x00FF00FFu, __builtin_amdgcn_update_dpp(0, (int)x, 0x128 /* row_ror:8 */, 0xF, 0xF, false))
+    LS_STEP(4, 0x0F0F0F0Fu, __builtin_amdgcn_ds_swizzle((int)x, 0x101F))                               // lane ^ 4
+    LS_STEP(2, 0x33333333u, __builtin_amdgcn_update_dpp(0, (int)x, 0x4E /* quad_perm 2,3,0,1 */, 0xF, 0xF, false))
+    LS_STEP(1, 0x55555555u, __builtin_amdgcn_update_dpp(0, (int)x, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, false))
+#undef LS_STEP
+    return x;
+}
+// Packed columns: lane l answers for column `col` (slot l of the tile; -1: none) and all 32 rows of the wave at once,
+// 32 bits of the bitmap in two words, and one bit transpose hands the rows their columns.  (Each lane testing the
+// columns of its row one after the other was a chain of up to 64 LDS reads per tile.)  A cell whose diagonal is selected
+// is left out: phase 1 counted it.
+struct ColWords { uint32_t lo, hi; };
+__device__ __forceinline__ int col_offset(int posw, int col) { return posw - col < -96 ? -96 : posw - col; }   // row i meets the column on diagonal offset + i
+__device__ __forceinline__ ColWords col_words(const uint32_t* ob, int posw, int col, bool diags) {
+    ColWords w = {0u, 0u};
+    if (diags && col >= 0) {
+        const int q = (col_offset(posw, col) >> 5) + OB_PAD;
+        w.lo = ob[q]; w.hi = ob[q + 1];
+    }
+    return w;
+}
+__device__ __forceinline__ TileMask col_mask(const ColWords& w, int posw, int col, int lane) {
+    const int o = col_offset(posw, col);
+    const uint32_t sel = (uint32_t)((((uint64_t)w.hi << 32) | w.lo) >> (o & 31));
+    uint32_t rows = (o >= 0 ? 0xFFFFFFFFu : o > -32 ? 0xFFFFFFFFu << (-o & 31) : 0u) & ~sel;
+    if (col < 0) rows = 0u;
+    const uint32_t t = transpose32(rows, lane);
+    const auto both = __builtin_amdgcn_permlane32_swap(t, t, false, false);   // every lane: its row's columns 0-31 and 32-63
+    TileMask m;
+    m.act[0] = __ballot(both[0] != 0u) != 0ull;
+    m.act[1] = __ballot(both[1] != 0u) != 0ull;
+    m.full[0] = m.full[1] = false;
+    const int g4 = (lane >> 5) * 4;
+    m.am[0] = both[0] >> g4; m.am[1] = both[1] >> g4;
+    return m;
+}
+__device__ __forceinline__ float masked(float x, uint32_t am, int r) {      // x, or -inf if register r's key is not allowed
+    const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)am, 8 * (r >> 2) + (r & 3), 1);     // 0 or ~0
+    return __builtin_bit_cast(float, (__builtin_bit_cast(uint32_t, x) & keep) | (0xFF800000u & ~keep));
+}
+__device__ __forceinline__ float max32(float x) {                           // the larger of this lane's and lane ^ 32's value
+    const auto b = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+    return fmaxf(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
 }
 
 // Tile sequence of one workgroup: first the n1 key blocks crossed by a selected diagonal (ascending),
@@ -377,13 +446,12 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* k_lds = smem;                                         // [2][K_BYTES]
     unsigned char* vt_lds = smem + 2 * C::K_BYTES;                       // [2][VT_BYTES]
-    uint32_t* ob = reinterpret_cast<uint32_t*>(smem + 2 * C::K_BYTES + 2 * C::VT_BYTES);
-    int32_t* colring = reinterpret_cast<int32_t*>(ob + a.words + 1);     // [2][64]; ob = zero word + bitmap
+    int32_t* colring = reinterpret_cast<int32_t*>(smem + 2 * C::K_BYTES + 2 * C::VT_BYTES);   // [2][64]
     int32_t* wcnt = colring + 128;                                       // [8]
     uint16_t* kbl = reinterpret_cast<uint16_t*>(wcnt + 8);               // [tab_len] active key blocks
-    uint8_t* tab = reinterpret_cast<uint8_t*>(kbl + ((a.tab_len + 7) & ~7));
 
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, g = lane >> 5;
 
     __shared__ int item_s;
@@ -391,7 +459,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     __syncthreads();                                       // everyone is done with the previous item's LDS
     if (tid == 0) item_s = pop_item(a, blockIdx.x & 7);    // taken only when needed: items are coarse, reserving early hurts the tail
     __syncthreads();
-    const int item = item_s;
+    const int item = __builtin_amdgcn_readfirstlane(item_s);
     if (item < 0) break;
     const int bh = item >> 16, qb = item & 0xFFFF;
     const int b = bh / a.Hq, h = bh % a.Hq, kvh = h / a.G;
@@ -402,13 +470,14 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     const T* Vg = reinterpret_cast<const T*>(a.v) + ((int64_t)b * a.Hkv + kvh) * n * D;
     const T* Qg = reinterpret_cast<const T*>(a.q) + (int64_t)bh * a.n_hat * D;
 
-    // diagonal bitmap and activity table of this head -> LDS
-    for (int i = tid; i < a.words + 1; i += PREFILL_THREADS) ob[i] = a.obits[(int64_t)bh * (a.words + 1) + i];
-    for (int i = tid; i < a.tab_len; i += PREFILL_THREADS) tab[i] = a.tab[(int64_t)bh * a.tab_len + i];
+    const uint8_t* tab = a.tab + (int64_t)bh * a.tab_len;
+    const uint32_t* obg = a.obits + (int64_t)bh * (OB_PAD + a.words);    // zero words + bitmap of this head
 
-    // this lane's query row and its fragments
+    // this lane's query row and its fragments (a row that does not exist has zeros: its results are finite and unused)
     const int64_t pos = blockpos + 32 * wv + r32;
+    const int posw = (int)blockpos + 32 * wv;              // the wave's first row
     const bool row_ok = (pos >= row0) && (pos < n);
+    const bool rows_here = posw < n && posw + 31 >= row0;
     Frag<T> qf[C::KSTEPS];
     if (row_ok) {
         const T* qrow = Qg + (pos - row0) * D;
@@ -456,18 +525,15 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     float m_run = -INFINITY, l_run = 0.f;                  // m_run in raw logit units
     const float sc2 = a.scale_log2e;
 
-    // ---- one staged tile: masks am0 / am1 say which of the 2 x 32 keys this lane's row may see
-    auto process = [&](const unsigned char* kt, const unsigned char* vt, uint32_t am0, uint32_t am1, bool full) {
+    // ---- one staged tile
+    auto process = [&](const unsigned char* kt, const unsigned char* vt, const TileMask& tm) {
         f32x16 s[2];
-        bool act[2];
-        act[0] = __ballot(am0 != 0u) != 0ull;
-        act[1] = __ballot(am1 != 0u) != 0ull;
-        if (!act[0] && !act[1]) return;
+        if (!tm.act[0] && !tm.act[1]) return;
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[sub][r] = 0.f;
-            if (act[sub]) {
+            if (tm.act[sub]) {
                 const unsigned char* krow = kt + (32 * sub + r32) * C::K_STRIDE + 8 * g * C::EB;
 #pragma unroll
                 for (int c = 0; c < C::KSTEPS; ++c) {
@@ -478,23 +544,14 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
             }
         }
         float mx = -INFINITY;
-        if (full) {
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < 2; ++sub) {
+            if (!tm.full[sub]) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
-        } else {
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                const uint32_t am = sub ? am1 : am0;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int kbit = 8 * (r >> 2) + 4 * g + (r & 3);
-                    const float x = ((am >> kbit) & 1u) ? s[sub][r] : -INFINITY;
-                    s[sub][r] = x;
-                    mx = fmaxf(mx, x);
-                }
+                for (int r = 0; r < 16; ++r) s[sub][r] = masked(s[sub][r], tm.am[sub], r);
             }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
         }
         mx = fmaxf(mx, xor32(mx));
         const float m_new = fmaxf(m_run, mx);
@@ -520,7 +577,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
         }
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
-            if (!act[sub]) continue;
+            if (!tm.act[sub]) continue;
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
                 float pv[8];
@@ -601,46 +658,15 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
         const int32_t colv_next = colv;
         if (more) load_cols(t + 2);
         // ---- masks of tile t
-        uint32_t am0 = 0u, am1 = 0u;
-        bool full = false;
+        TileMask tm;
         if (t < n1) {
-            const int64_t key0 = (int64_t)kbl[t] * BN;
-            const uint8_t f = tab[jb - kbl[t] + 1];
-            if (!row_ok) { am0 = am1 = 0u; }
-            else if (f & 2) { am0 = am1 = 0xFFFFFFFFu; }
-            else {
-                // bit i of the mask <-> key key0 + 32*sub + i <-> diagonal pos - key
-                const int64_t d0 = pos - key0;             // diagonal of the tile's first key
-                am0 = __brev(window32(ob, d0 - 31));
-                am1 = __brev(window32(ob, d0 - 63));
-            }
-            full = (f & 2) && (__ballot(row_ok) == ~0ull);
+            tm = diag_mask(diag_words((const_words)obg, posw, __builtin_amdgcn_readfirstlane((int)kbl[t]) * BN), r32, g);
         } else {
-            const int32_t* cols = colring + (t & 1) * BN;
-            const int base = (t - n1) * BN;
-            const int cnt = nv - base < BN ? nv - base : BN;
-            // slot `lane`: is the column's key block crossed by selected diagonals for this row block?
-            const int32_t mycol = lane < cnt ? cols[lane] : 0;
-            const uint8_t f = lane < cnt ? tab[jb - (mycol >> 6) + 1] : (uint8_t)3;
-            const uint64_t drop = __ballot(f == 3);        // wholly covered by phase 1 (or no such slot)
-            const uint64_t chk = __ballot(f == 1);         // partly covered: test cell by cell
-            uint64_t am = 0ull;
-            if (row_ok) {
-                // causal: columns ascend, the visible ones form a prefix
-                if ((int64_t)cols[cnt - 1] <= pos) am = cnt >= 64 ? ~0ull : ((1ull << cnt) - 1ull);
-                else for (int i = 0; i < cnt; ++i) if ((int64_t)cols[i] <= pos) am |= 1ull << i;
-                am &= ~drop;
-                uint64_t todo = chk & am;
-                while (todo) {
-                    const int i = __ffsll((unsigned long long)todo) - 1;
-                    todo &= todo - 1;
-                    const int64_t o = pos - cols[i];       // >= 0 here
-                    if ((ob[(o >> 5) + 1] >> (o & 31)) & 1u) am &= ~(1ull << i);   // cell already counted on its diagonal
-                }
-            }
-            am0 = (uint32_t)am; am1 = (uint32_t)(am >> 32);
+            const int col = colring[(t & 1) * BN + lane];
+            tm = col_mask(col_words(obg, posw, col, n1 > 0), posw, col, lane);
         }
-        process(k_lds + (t & 1) * C::K_BYTES, vt_lds + (t & 1) * C::VT_BYTES, am0, am1, full);
+        if (!rows_here) tm.act[0] = tm.act[1] = false;
+        process(k_lds + (t & 1) * C::K_BYTES, vt_lds + (t & 1) * C::VT_BYTES, tm);
         if (more) {
             const int32_t keep = colv; colv = colv_next;   // stash() records the columns of tile t+1
             stash(t + 1);
@@ -707,20 +733,15 @@ struct DirectCfg {
     __device__ static constexpr int vswz(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
 };
 
-// OBLDS: the head's diagonal bitmap is copied to LDS (short contexts); otherwise it is read from global
-// memory where needed (the masks of a tile are computed one tile ahead, under the transfer wait), which
-// keeps two workgroups per CU at long contexts.
-template <int D, bool OBLDS>
+template <int D>
 __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(PrefillArgs a) {
     using C = DirectCfg<D>;
     using T = bf16_t;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* tiles = smem;                                         // [2][TILE_BYTES]
-    uint32_t* ob_lds = reinterpret_cast<uint32_t*>(smem + 2 * C::TILE_BYTES);
-    int32_t* colring = reinterpret_cast<int32_t*>(ob_lds + (OBLDS ? a.words + 1 : 0));   // [3][64]
-    int32_t* wcnt = colring + 192;                                       // [8]
-    uint16_t* kbl = reinterpret_cast<uint16_t*>(wcnt + 8);               // [tab_len] active key blocks | flags << 14
-    uint8_t* tab = reinterpret_cast<uint8_t*>(kbl + ((a.tab_len + 7) & ~7));   // [tab_len] this head's per-j table
+    int32_t* colring = reinterpret_cast<int32_t*>(smem + 2 * C::TILE_BYTES);   // [4][64]
+    int32_t* wcnt = colring + 256;                                       // [8]
+    uint16_t* kbl = reinterpret_cast<uint16_t*>(wcnt + 8);               // [tab_len] active key blocks
     const uint32_t tiles_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)tiles;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -769,12 +790,11 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
     const T* Qg = reinterpret_cast<const T*>(a.q) + (int64_t)bh * a.n_hat * D;
     const uint8_t* tabg = a.tab + (int64_t)bh * a.tab_len;
 
-    const uint32_t* obg = a.obits + (int64_t)bh * (a.words + 1);          // zero word + bitmap of this head
-    if (OBLDS) for (int i = tid; i < a.words + 1; i += PREFILL_THREADS) ob_lds[i] = obg[i];
-    const uint32_t* ob = OBLDS ? ob_lds : obg;
-    for (int i = tid; i < a.tab_len; i += PREFILL_THREADS) tab[i] = tabg[i];
+    const uint32_t* obg = a.obits + (int64_t)bh * (OB_PAD + a.words);     // zero words + bitmap of this head
     const int64_t pos = blockpos + 32 * wv + r32;
-    const bool row_ok = (pos >= row0) && (pos < n);
+    const int posw = (int)blockpos + 32 * wv;              // the wave's first row
+    const bool row_ok = (pos >= row0) && (pos < n);        // a row that does not exist has zeros: finite results, not stored
+    const bool rows_here = posw < n && posw + 31 >= row0;
     Frag<T> qf[C::KSTEPS];
     if (row_ok) {
         const T* qrow = Qg + (pos - row0) * D;
@@ -784,22 +804,20 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
 #pragma unroll
         for (int c = 0; c < C::KSTEPS; ++c) zero_frag(qf[c]);
     }
-    const bool all_ok = __ballot(row_ok) == ~0ull;
 
-    // ---- ordered list of the key blocks phase 1 visits (flags of the per-j table ride in bits 14-15)
+    // ---- ordered list of the key blocks phase 1 visits
     const int64_t jb = blockpos / BN;                      // even
     const int kb_hi = (int)(posmax / BN);
     int n1 = 0;
     for (int base = 0; base <= kb_hi; base += PREFILL_THREADS) {
         const int kb = base + tid;
-        const uint8_t f = kb <= kb_hi ? tabg[jb - kb + 1] : (uint8_t)0;
-        const bool act = f & 1;
+        const bool act = kb <= kb_hi && (tabg[jb - kb + 1] & 1);
         const uint64_t bal = __ballot(act);
         if (lane == 0) wcnt[wv] = __popcll(bal);
         __syncthreads();
         int off = n1;
         for (int w2 = 0; w2 < wv; ++w2) off += wcnt[w2];
-        if (act) kbl[off + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)(kb | ((f & 2) << 13));
+        if (act) kbl[off + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)kb;
         n1 += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
         __syncthreads();
     }
@@ -833,55 +851,50 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
     // (Measured: spreading the transfers over the products of the previous tile instead of issuing
     // them together is slower; a transfer stalls the wave that issues it for as long as the vector
     // memory pipeline is busy, which then also stalls its matrix pipeline.)
-    auto issue = [&](int t) {                              // global -> LDS buffer t & 1 for tile t
-        const uint32_t dst = tiles_lds + (uint32_t)((t & 1) * C::TILE_BYTES);
-        const uint32_t kdst = dst + (uint32_t)(wv * C::K_ISTR), vdst = dst + (uint32_t)(C::K_BYTES + wv * C::V_ISTR);
-        if (t < n1) {
-            const int64_t key0 = (int64_t)(__builtin_amdgcn_readfirstlane((int)kbl[t]) & 0x3FFF) * BN;
-            const unsigned char* kb_ = Kg + key0 * C::RB;
-            const unsigned char* vb_ = Vg + key0 * C::RB;
-            if (key0 + BN <= n) {
+    const uint32_t kdst0 = tiles_lds + (uint32_t)(wv * C::K_ISTR), vdst0 = tiles_lds + (uint32_t)(C::K_BYTES + wv * C::V_ISTR);
+    auto issue_block = [&](int kb, int t) {                // key block kb -> LDS buffer t & 1
+        const uint32_t bo = (uint32_t)((t & 1) * C::TILE_BYTES);
+        const int64_t key0 = (int64_t)kb * BN;
+        const unsigned char* kb_ = Kg + key0 * C::RB;
+        const unsigned char* vb_ = Vg + key0 * C::RB;
+        if (key0 + BN <= n) {
 #pragma unroll
-                for (int i = 0; i < C::IPW; ++i) dma16(kb_ + i * C::STEP, kvoff0, kdst + (uint32_t)(4 * i * C::K_ISTR));
+            for (int i = 0; i < C::IPW; ++i) dma16(kb_ + i * C::STEP, kvoff0, kdst0 + bo + (uint32_t)(4 * i * C::K_ISTR));
 #pragma unroll
-                for (int i = 0; i < C::IPW; ++i) dma16(vb_ + i * C::STEP, vvoff0, vdst + (uint32_t)(4 * i * C::V_ISTR));
-            } else {                                       // last key block of the context: clamp the rows
-                const int last = (int)(n - 1 - key0);
-#pragma unroll
-                for (int i = 0; i < C::IPW; ++i) {
-                    const int row = rowlane + 4 * C::RPI * i;
-                    const uint32_t ro = (uint32_t)(row <= last ? row : last) * C::RB;
-                    dma16(kb_, ro + kcpart, kdst + (uint32_t)(4 * i * C::K_ISTR));
-                    dma16(vb_, ro + vcpart, vdst + (uint32_t)(4 * i * C::V_ISTR));
-                }
-            }
-        } else {
-            const int32_t* cols = colring + (t % 3) * BN;
+            for (int i = 0; i < C::IPW; ++i) dma16(vb_ + i * C::STEP, vvoff0, vdst0 + bo + (uint32_t)(4 * i * C::V_ISTR));
+        } else {                                           // last key block of the context: clamp the rows
+            const int last = (int)(n - 1 - key0);
 #pragma unroll
             for (int i = 0; i < C::IPW; ++i) {
-                int32_t col = cols[rowlane + 4 * C::RPI * i];
-                if (col < 0) col = 0;
-                const uint32_t ro = (uint32_t)col * C::RB;
-                dma16(Kg, ro + kcpart, kdst + (uint32_t)(4 * i * C::K_ISTR));
-                dma16(Vg, ro + vcpart, vdst + (uint32_t)(4 * i * C::V_ISTR));
+                const int row = rowlane + 4 * C::RPI * i;
+                const uint32_t ro = (uint32_t)(row <= last ? row : last) * C::RB;
+                dma16(kb_, ro + kcpart, kdst0 + bo + (uint32_t)(4 * i * C::K_ISTR));
+                dma16(vb_, ro + vcpart, vdst0 + bo + (uint32_t)(4 * i * C::V_ISTR));
             }
+        }
+    };
+    auto issue_cols = [&](int t) {                         // the columns of packed tile t -> LDS buffer t & 1
+        const uint32_t bo = (uint32_t)((t & 1) * C::TILE_BYTES);
+        const int32_t* cols = colring + (t & 3) * BN;
+#pragma unroll
+        for (int i = 0; i < C::IPW; ++i) {
+            int32_t col = cols[rowlane + 4 * C::RPI * i];
+            if (col < 0) col = 0;
+            const uint32_t ro = (uint32_t)col * C::RB;
+            dma16(Kg, ro + kcpart, kdst0 + bo + (uint32_t)(4 * i * C::K_ISTR));
+            dma16(Vg, ro + vcpart, vdst0 + bo + (uint32_t)(4 * i * C::V_ISTR));
         }
     };
 
     // One tile: S^T = K Q^T, online softmax, O^T += V^T P^T.  The products run in a pinned order
     // (a scheduling barrier after each) with the LDS fragment reads a fixed number of products ahead.
-    auto process = [&](int tileoff, uint32_t am0, uint32_t am1, bool full) {
+    auto process = [&](int tileoff, const TileMask& tm) {
         const unsigned char* tile = tiles + tileoff;
         f32x16 s[2];
-        bool act[2];
-        act[0] = __ballot(am0 != 0u) != 0ull;
-        act[1] = __ballot(am1 != 0u) != 0ull;
-        if (!act[0] && !act[1]) return;                    // none of this wave's rows has an allowed cell here
+        if (!tm.act[0] && !tm.act[1]) return;              // none of this wave's rows has an allowed cell here
         const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        s[0] = zero16; s[1] = zero16;
         constexpr int SUB = (32 / C::RPI) * C::K_ISTR;     // LDS bytes from key r to key r + 32
-        const bool both = act[0] && act[1];
-        if (both) {
+        if (tm.act[0] && tm.act[1]) {
             // 2 * KSTEPS products in a fixed order; K fragments are read RING_S products ahead of their use
             constexpr int NP = 2 * C::KSTEPS, R = LS_RING_S;
             Frag<T> kf[NP];
@@ -892,6 +905,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
 #pragma unroll
             for (int i = 0; i < R; ++i) kload(i);
             __builtin_amdgcn_sched_barrier(0);
+            s[0] = zero16; s[1] = zero16;
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
                 mma(s[i & 1], kf[i], qf[i >> 1]);          // s[r] = <k_{8(r/4)+4g+r%4}, q_row>
@@ -908,6 +922,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
 #pragma unroll
                 for (int c = 0; c < R; ++c) kload(c);
                 __builtin_amdgcn_sched_barrier(0);
+                s[sub] = zero16;
 #pragma unroll
                 for (int c = 0; c < C::KSTEPS; ++c) {
                     mma(s[sub], kf[c], qf[c]);
@@ -915,43 +930,28 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
                     __builtin_amdgcn_sched_barrier(0);
                 }
             };
-            if (act[0]) half(std::integral_constant<int, 0>{}); else half(std::integral_constant<int, 1>{});
+            if (tm.act[0]) half(std::integral_constant<int, 0>{}); else half(std::integral_constant<int, 1>{});
         }
         float mx = -INFINITY;
-        if (full) {
 #pragma unroll
-            for (int sub = 0; sub < 2; ++sub)
+        for (int sub = 0; sub < 2; ++sub) {
+            if (tm.act[sub]) {
+                if (!tm.full[sub]) {
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[sub][r] = masked(s[sub][r], tm.am[sub], r);
+                }
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
-        } else {
-#pragma unroll
-            for (int sub = 0; sub < 2; ++sub) {
-                const uint32_t amg = (sub ? am1 : am0) >> (4 * g);   // register r of this lane: key 8(r/4) + 4g + r%4
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float x = (amg & (1u << (8 * (r >> 2) + (r & 3)))) ? s[sub][r] : -INFINITY;
-                    s[sub][r] = x;
-                    mx = fmaxf(mx, x);
-                }
             }
         }
-        mx = fmaxf(mx, xor32(mx));
+        mx = max32(mx);
         const float m_new = (mx > m_run + lazy) ? mx : m_run;            // -inf + lazy = -inf: the first finite tile always moves it
         const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
         const float corr = fast_exp2((m_run - m_safe) * sc2);
         const float mneg = -m_safe * sc2;
         m_run = m_new;
-        float ps4[4] = {0.f, 0.f, 0.f, 0.f};               // four short add chains instead of one long one
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float p = fast_exp2(__builtin_fmaf(s[sub][r], sc2, mneg));
-                s[sub][r] = p;
-                ps4[r & 3] += p;
-            }
-        l_run = l_run * corr + ((ps4[0] + ps4[1]) + (ps4[2] + ps4[3]));
         if (__ballot(corr != 1.0f) != 0ull) {
+            l_run *= corr;
 #pragma unroll
             for (int i = 0; i < C::DBLK; ++i)
 #pragma unroll
@@ -959,17 +959,21 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
         }
         auto vt_frag = [&](Frag<T>& vf, int q4, int i) {     // V^T fragment: keys 16*q4.., output block i
             const unsigned char* va = tile + vaddr[i] + 16 * q4 * C::RB;
-            const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(va));
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(va + 8 * C::RB));
-            struct U { s16x4 a, b; } u = {lo, hi};
-            vf.v = __builtin_bit_cast(bf16x8, u);
+            load_frag_tr(vf, va, va + 8 * C::RB);
         };
         // P*V: per 32-key half, 2 * DBLK products in a fixed order (16-key chunk q4, output block i); V^T
         // fragments are read RING_P products ahead
+        float ps4[4] = {0.f, 0.f, 0.f, 0.f};               // four short add chains instead of one long one
 #pragma unroll
         for (int sub = 0; sub < 2; ++sub) {
-            if (act[sub]) {
+            if (tm.act[sub]) {
                 constexpr int NPV = 2 * C::DBLK, R = LS_RING_P < NPV ? LS_RING_P : NPV;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const float p = fast_exp2(__builtin_fmaf(s[sub][r], sc2, mneg));
+                    s[sub][r] = p;
+                    ps4[r & 3] += p;
+                }
                 Frag<T> pf[2];
 #pragma unroll
                 for (int h2 = 0; h2 < 2; ++h2) {
@@ -990,52 +994,11 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
                 }
             }
         }
+        l_run += (ps4[0] + ps4[1]) + (ps4[2] + ps4[3]);
     };
 
-    // cell masks of tile t for this lane's row: bit j of am0 / am1 = key j / 32 + j of the tile is allowed
-    uint32_t am0 = 0u, am1 = 0u;
-    bool full = false;
-    auto masks = [&](int t) {
-        am0 = 0u; am1 = 0u; full = false;
-        if (t < n1) {
-            const int e = __builtin_amdgcn_readfirstlane((int)kbl[t]);
-            const int64_t key0 = (int64_t)(e & 0x3FFF) * BN;
-            const bool fullflag = (e >> 14) & 1;
-            if (!row_ok) { am0 = am1 = 0u; }
-            else if (fullflag) { am0 = am1 = 0xFFFFFFFFu; }
-            else {
-                const int64_t d0 = pos - key0;             // diagonal of the tile's first key
-                am0 = __brev(window32(ob, d0 - 31));
-                am1 = __brev(window32(ob, d0 - 63));
-            }
-            full = fullflag && all_ok;
-        } else {
-            const int32_t* cols = colring + (t % 3) * BN;
-            const int base = (t - n1) * BN;
-            const int cnt = nv - base < BN ? nv - base : BN;
-            const int32_t mycol = lane < cnt ? cols[lane] : 0;
-            const uint8_t f = lane < cnt ? tab[jb - (mycol >> 6) + 1] : (uint8_t)3;
-            const uint64_t drop = __ballot(f == 3);        // wholly covered by phase 1 (or no such slot)
-            const uint64_t chk = __ballot(f == 1);         // partly covered: test cell by cell
-            uint64_t am = 0ull;
-            if (row_ok) {
-                if ((int64_t)cols[cnt - 1] <= pos) am = cnt >= 64 ? ~0ull : ((1ull << cnt) - 1ull);
-                else for (int i = 0; i < cnt; ++i) if ((int64_t)cols[i] <= pos) am |= 1ull << i;
-                am &= ~drop;
-                uint64_t todo = chk & am;
-                while (todo) {
-                    const int i = __ffsll((unsigned long long)todo) - 1;
-                    todo &= todo - 1;
-                    const int64_t o = pos - cols[i];       // >= 0 here
-                    if ((ob[(o >> 5) + 1] >> (o & 31)) & 1u) am &= ~(1ull << i);   // cell already counted on its diagonal
-                }
-            }
-            am0 = (uint32_t)am; am1 = (uint32_t)(am >> 32);
-        }
-    };
-
-    // column ids of gathered tile t: fetched into a register one iteration before they are written to
-    // LDS (slot t % 3), which happens one iteration before tile t is issued.  The global load is thus
+    // column ids of packed tile t: fetched into a register one iteration before they are written to
+    // LDS (slot t & 3), which happens one iteration before tile t is issued.  The global load is thus
     // never waited for while transfers are in flight.
     auto fetch_cols = [&](int t) -> int32_t {
         if (t >= n1 && t < ntiles && tid < BN) {
@@ -1045,23 +1008,51 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
         return -1;
     };
     auto store_cols = [&](int t, int32_t c) {
-        if (t >= n1 && t < ntiles && tid < BN) colring[(t % 3) * BN + tid] = c;
+        if (t >= n1 && t < ntiles && tid < BN) colring[(t & 3) * BN + tid] = c;
+    };
+    auto block_at = [&](int t) -> int { return __builtin_amdgcn_readfirstlane((int)kbl[t]); };
+    // what the masks of tile t are made of (requested before tile t - 1 is multiplied)
+    DiagWords dw = {0u, 0u, 0u};
+    ColWords cw = {0u, 0u};
+    int32_t mycol = -1;
+    TileMask tm;
+    auto mask_words = [&](int t, int kb) {
+        if (t < n1) dw = diag_words((const_words)obg, posw, kb * BN);
+        else { mycol = colring[(t & 3) * BN + lane]; cw = col_words(obg, posw, mycol, n1 > 0); }
+    };
+    auto masks = [&](int t) {
+        tm = t < n1 ? diag_mask(dw, r32, g) : col_mask(cw, posw, mycol, lane);
+        if (!rows_here) tm.act[0] = tm.act[1] = false;
     };
 
     store_cols(0, fetch_cols(0));
     store_cols(1, fetch_cols(1));
     int32_t colpre = fetch_cols(2);
-    __syncthreads();                                       // bitmap, table, kbl, first column ids visible
-    if (ntiles > 0) { issue(0); masks(0); }
+    __syncthreads();                                       // kbl and the first column ids are visible
+    int kb_next = 0;                                       // key block of tile t + 1 (phase 1)
+    if (ntiles > 0) {
+        kb_next = 0 < n1 ? block_at(0) : 0;
+        mask_words(0, kb_next);
+        if (0 < n1) issue_block(kb_next, 0); else issue_cols(0);
+        masks(0);
+        kb_next = 1 < n1 ? block_at(1) : 0;
+    }
     wait_transfers();
     __syncthreads();
 
     for (int t = 0; t < ntiles; ++t) {
-        store_cols(t + 2, colpre);
-        colpre = fetch_cols(t + 3);
-        if (t + 1 < ntiles) issue(t + 1);
-        process((t & 1) * C::TILE_BYTES, am0, am1, full);
-        if (t + 1 < ntiles) masks(t + 1);                  // its LDS reads overlap the wait below
+        if (t + 3 >= n1) {                                 // column ids only matter around phase 2
+            store_cols(t + 2, colpre);
+            colpre = fetch_cols(t + 3);
+        }
+        if (t + 1 < ntiles) {
+            mask_words(t + 1, kb_next);
+            if (t + 1 < n1) issue_block(kb_next, t + 1); else issue_cols(t + 1);
+        }
+        const int kb_after = t + 2 < n1 ? (int)kbl[t + 2] : 0;
+        process((t & 1) * C::TILE_BYTES, tm);
+        kb_next = __builtin_amdgcn_readfirstlane(kb_after);
+        if (t + 1 < ntiles) masks(t + 1);
         wait_transfers();                                  // this wave's transfers of tile t+1 have landed
         __syncthreads();
     }
@@ -1086,39 +1077,28 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
 }
 
 template <int D>
-static size_t prefill_bf16_smem(int words, int tab_len, bool oblds) {
-    return 2 * (size_t)DirectCfg<D>::TILE_BYTES + (oblds ? (size_t)(words + 1) * 4 : 0) + 192 * 4 + 8 * 4 +
-           (size_t)((tab_len + 7) & ~7) * 2 + (size_t)tab_len + 16;
-}
-// the bitmap goes to LDS when two workgroups still fit a CU's 160 KB with it
-template <int D>
-static bool prefill_bf16_oblds(int words, int tab_len) {
-    return 2 * (prefill_bf16_smem<D>(words, tab_len, true) + 1024) <= 160 * 1024;
+static size_t prefill_bf16_smem(int tab_len) {
+    return 2 * (size_t)DirectCfg<D>::TILE_BYTES + 256 * 4 + 8 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
 }
 
-template <int D, bool OBLDS>
-static hipError_t launch_prefill_bf16_t(const PrefillArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    const size_t smem = prefill_bf16_smem<D>(a.words, a.tab_len, OBLDS);
-    // with events: they take the start and stop time stamps of this dispatch itself, no marker goes into the stream
-    if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_bf16_kernel<D, OBLDS>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
-    else hipLaunchKernelGGL((prefill_bf16_kernel<D, OBLDS>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), smem, st, a);
-    return hipGetLastError();
-}
 template <int D>
 static hipError_t launch_prefill_bf16(const PrefillArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    return prefill_bf16_oblds<D>(a.words, a.tab_len) ? launch_prefill_bf16_t<D, true>(a, st, ev0, ev1) : launch_prefill_bf16_t<D, false>(a, st, ev0, ev1);
+    const size_t smem = prefill_bf16_smem<D>(a.tab_len);
+    // with events: they take the start and stop time stamps of this dispatch itself, no marker goes into the stream
+    if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
+    else hipLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), smem, st, a);
+    return hipGetLastError();
 }
 
 template <typename T, int D>
-static size_t prefill_smem_t(int words, int tab_len) {
+static size_t prefill_smem_t(int tab_len) {
     using C = TileCfg<T, D>;
-    return 2 * (size_t)C::K_BYTES + 2 * (size_t)C::VT_BYTES + (size_t)(words + 1) * 4 + 128 * 4 + 8 * 4 +
-           (size_t)((tab_len + 7) & ~7) * 2 + (size_t)tab_len + 16;
+    return 2 * (size_t)C::K_BYTES + 2 * (size_t)C::VT_BYTES + 128 * 4 + 8 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
 }
 
 template <typename T, int D>
 static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    const size_t smem = prefill_smem_t<T, D>(a.words, a.tab_len);
+    const size_t smem = prefill_smem_t<T, D>(a.tab_len);
     if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_kernel<T, D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
     else hipLaunchKernelGGL((prefill_kernel<T, D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), smem, st, a);
     return hipGetLastError();
@@ -1126,20 +1106,18 @@ static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t st, hipEven
 
 hipError_t init_prefill_kernels() {
     hipError_t e;
-    if ((e = allow_full_lds(&prefill_bf16_kernel<128, true>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&prefill_bf16_kernel<128, false>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&prefill_bf16_kernel<64, true>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&prefill_bf16_kernel<64, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_bf16_kernel<128>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_bf16_kernel<64>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&prefill_kernel<float, 128>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&prefill_kernel<float, 64>)) != hipSuccess) return e;
     return allow_full_lds(&plan_kernel);
 }
 
-size_t prefill_smem_bytes(int dtype, int d, int words, int tab_len) {
-    if (dtype == 0 && d == 128) return prefill_bf16_smem<128>(words, tab_len, prefill_bf16_oblds<128>(words, tab_len));
-    if (dtype == 0 && d == 64) return prefill_bf16_smem<64>(words, tab_len, prefill_bf16_oblds<64>(words, tab_len));
-    if (dtype == 1 && d == 128) return prefill_smem_t<float, 128>(words, tab_len);
-    return prefill_smem_t<float, 64>(words, tab_len);
+size_t prefill_smem_bytes(int dtype, int d, int tab_len) {
+    if (dtype == 0 && d == 128) return prefill_bf16_smem<128>(tab_len);
+    if (dtype == 0 && d == 64) return prefill_bf16_smem<64>(tab_len);
+    if (dtype == 1 && d == 128) return prefill_smem_t<float, 128>(tab_len);
+    return prefill_smem_t<float, 64>(tab_len);
 }
 
 hipError_t launch_plan(const PlanArgs& a, int BH, hipStream_t st) {
