@@ -133,9 +133,11 @@ inline int words_of(int64_t n) { return (int)((n + 31) / 32) + 8; }
 inline int tab_len_of(int64_t n) { return (int)(n / 64) + 4; }
 size_t ws_prefill(const ls_shape* s) {
     const size_t BH = (size_t)s->B * s->Hq;
-    const size_t items = BH * (size_t)(s->n / 128 + 2);          // (head, row block) work items, upper bound
+    const int64_t rows = s->n_hat > 0 && s->n_hat <= s->n ? s->n_hat : s->n;
+    const size_t items = BH * (size_t)(rows / 128 + 2);          // (head, row block) work items, upper bound
+    const size_t slots = (size_t)ls::prefill_split_slots((int64_t)items);
     return up(BH * (size_t)(words_of(s->n) + 4) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(BH) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
-           up(8 * items * 4) + 2 * up(8 * 4);
+           up(8 * (items + slots) * 8) + 2 * up(8 * 4) + up(slots * 8) + up(8) + up(slots * ls::prefill_slot_bytes(s->d)) + ALIGN;
 }
 size_t ws_compress(const ls_shape* s) {
     return ws_score(s, false) + up((size_t)s->B * s->Hkv * (size_t)s->n * 4) +
@@ -326,8 +328,9 @@ namespace {
 // Where ls_sparse_prefill keeps its per-call state in the workspace (one place, so that the test hook that
 // reads the work queues back finds them where the call put them).
 struct PrefillCarve {
-    uint32_t* obits; uint8_t* hflag; uint32_t* cost; uint16_t* pref; uint32_t* queue; int32_t* qlen; int32_t* qhead; uint8_t* tab;
-    int nqb; int64_t pos0; int code;
+    uint32_t* obits; uint8_t* hflag; uint32_t* cost; uint16_t* pref; uint2* queue; int32_t* qlen; int32_t* qhead; uint8_t* tab;
+    uint2* split; int32_t* split_count; float* part_o; float* part_ml;
+    int nqb, qcap, slots; int64_t pos0; int code;
 };
 const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     const int BH = s->B * s->Hq;
@@ -343,12 +346,28 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     w.code = LS_ESHAPE;
     if (w.nqb > 65535) return "too many row blocks";
     if (BH > 8192) return "B * Hq exceeds 8192";
-    w.queue = bp.take<uint32_t>(8 * (size_t)BH * w.nqb);
     w.qlen = bp.take<int32_t>(8);
     w.qhead = bp.take<int32_t>(8);
+    w.split_count = bp.take<int32_t>(2);
     w.tab = bp.take<uint8_t>((size_t)BH * tab_len);
+    // long items are split as far as the workspace has room for their parts' results (sized for it by
+    // ls_workspace_bytes; a smaller workspace that holds the rest still works)
+    const size_t items = (size_t)BH * w.nqb;
+    w.slots = ls::prefill_split_slots((int64_t)items);
     w.code = LS_EWORKSPACE;
     if (!bp.ok()) return "workspace is too small";
+    const Bump mark = bp;
+    for (;;) {
+        bp = mark;
+        w.qcap = (int)items + w.slots;
+        w.queue = bp.take<uint2>(8 * (size_t)w.qcap);
+        w.split = w.slots ? bp.take<uint2>((size_t)w.slots) : nullptr;
+        w.part_o = w.slots ? bp.take<float>((size_t)w.slots * 128 * s->d) : nullptr;
+        w.part_ml = w.slots ? bp.take<float>((size_t)w.slots * 128 * 2) : nullptr;
+        if (bp.ok()) break;
+        if (w.slots == 0) return "workspace is too small";
+        w.slots = w.slots > 16 ? w.slots / 2 : 0;
+    }
     w.code = LS_OK;
     return nullptr;
 }
@@ -372,24 +391,26 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
     PrefillCarve w;
     if (const char* m = carve_prefill(c, s, w)) return fail(c, w.code, "ls_sparse_prefill: %s", m);
     uint32_t* obits = w.obits; uint8_t* hflag = w.hflag; uint32_t* cost = w.cost; uint16_t* pref = w.pref;
-    uint32_t* queue = w.queue; int32_t* qlen = w.qlen; int32_t* qhead = w.qhead; uint8_t* tab = w.tab;
+    int32_t* qlen = w.qlen; int32_t* qhead = w.qhead; uint8_t* tab = w.tab;
     const int nqb = w.nqb; const int64_t pos0 = w.pos0;
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill: hipSetDevice failed");
     ls::PlanArgs p{};
     p.n = s->n; p.words = words; p.tab_len = tab_len; p.v_idx = v_idx; p.v_cnt = v_cnt; p.s_idx = s_idx; p.s_cnt = s_cnt;
     p.cap_v = cap_v; p.cap_s = cap_s; p.obits = obits; p.tab = tab; p.hflag = hflag; p.cost = cost; p.pref = pref;
-    p.status = c->status;
+    p.status = c->status; p.split_count = w.split_count;
     hipError_t e = ls::launch_plan(p, BH, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(plan): %s", hipGetErrorString(e));
     ls::SchedArgs sa{};
     sa.BH = BH; sa.G = s->Hq / s->Hkv; sa.Hq = s->Hq; sa.Hkv = s->Hkv; sa.nqb = nqb; sa.cost = cost;
-    sa.queue = queue; sa.qlen = qlen; sa.qhead = qhead;
+    sa.queue = w.queue; sa.qcap = w.qcap; sa.qlen = qlen; sa.qhead = qhead;
+    sa.slots = w.slots; sa.split = w.split; sa.split_count = w.split_count;
     sa.pref = pref; sa.v_cnt = v_cnt; sa.hflag = hflag; sa.tab_len = tab_len; sa.cap_v = cap_v; sa.n = s->n; sa.pos0 = pos0;
     e = ls::launch_sched(sa, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(sched): %s", hipGetErrorString(e));
     ls::PrefillArgs a{};
     a.q = q; a.k = k; a.v = v; a.out = out; a.lse = lse; a.n = s->n; a.n_hat = s->n_hat;
-    a.queue = queue; a.qlen = qlen; a.qhead = qhead; a.qcap = BH * nqb;
+    a.queue = w.queue; a.qlen = qlen; a.qhead = qhead; a.qcap = w.qcap;
+    a.slots = w.slots; a.split = w.split; a.split_count = w.split_count; a.part_o = w.part_o; a.part_ml = w.part_ml;
     a.pos0 = pos0;
     a.Hq = s->Hq; a.Hkv = s->Hkv; a.G = s->Hq / s->Hkv; a.BH = BH;
     a.nqb = nqb;
@@ -572,10 +593,19 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
     if (carve_prefill(c, s, w)) return w.code;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t items = (size_t)s->B * s->Hq * w.nqb;
+    std::vector<uint2> q(8 * (size_t)w.qcap);
+    int32_t len[8];
     if (hipSetDevice(c->device) != hipSuccess) return LS_EHIP;
-    if (hipMemcpyAsync(host_queue, w.queue, 8 * items * sizeof(uint32_t), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
-    if (hipMemcpyAsync(host_qlen, w.qlen, 8 * sizeof(int32_t), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
+    if (hipMemcpyAsync(q.data(), w.queue, q.size() * sizeof(uint2), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
+    if (hipMemcpyAsync(len, w.qlen, sizeof(len), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
     if (hipStreamSynchronize(st) != hipSuccess) return LS_EHIP;
+    for (int x = 0; x < 8; ++x) {                          // an item in parts is listed once, by its first part
+        host_qlen[x] = 0;
+        for (int i = 0; i < len[x] && i < w.qcap; ++i) {
+            const uint2 e = q[(size_t)x * w.qcap + i];
+            if ((e.y & 0xFF) == 0 && (size_t)host_qlen[x] < items) host_queue[x * items + host_qlen[x]++] = e.x;
+        }
+    }
     *nqb_out = w.nqb;
     return LS_OK;
 }

@@ -64,10 +64,11 @@ struct PlanArgs {
     uint8_t* hflag;           // [BH]
     uint32_t* cost;           // [BH] estimated tiles per row block (for the work queues)
     uint16_t* pref;           // [BH][tab_len + 1] prefix counts of table entries with a selected diagonal
+    int32_t* split_count;     // [2] cleared here for sched_kernel
     int32_t* status;          // device status word of the context (bits LS_STAT_*), OR-ed into
 };
 
-// Work queues of the sparse attention kernel: one list of (head, row block) items per XCD.
+// Work queues of the sparse attention kernel: one list per XCD of (head, row block) items or parts of them.
 struct SchedArgs {
     int BH, G, Hq, Hkv, nqb;
     const uint32_t* cost;     // [BH]
@@ -76,9 +77,13 @@ struct SchedArgs {
     const uint8_t* hflag;     // [BH]
     int tab_len, cap_v;
     int64_t n, pos0;
-    uint32_t* queue;          // [8][BH * nqb] items: bh << 16 | qb
+    uint2* queue;             // [8][qcap] entries: {bh << 16 | qb, part | parts << 8 | first slot << 16}
+    int qcap;
     int32_t* qlen;            // [8]
-    int32_t* qhead;           // [8] next item to hand out
+    int32_t* qhead;           // [8] next entry to hand out
+    int slots;                // results of parts that the workspace holds (0: no item is split)
+    uint2* split;             // [slots] split items: {bh << 16 | qb, parts | first slot << 16}
+    int32_t* split_count;     // [2] slots in use, split items
 };
 
 struct PrefillArgs {
@@ -92,10 +97,14 @@ struct PrefillArgs {
     const uint8_t *tab, *hflag;
     const int32_t *v_idx, *v_cnt;
     int cap_v;
-    const uint32_t* queue;    // work queues built by sched_kernel
+    const uint2* queue;       // work queues built by sched_kernel
     const int32_t* qlen;
     int32_t* qhead;
     int qcap;                 // entries per queue
+    int slots;
+    const uint2* split;
+    const int32_t* split_count;
+    float *part_o, *part_ml;  // [slots][128][d] accumulators in lane order, [slots][128][2] reference and normaliser
 };
 
 struct DecodeArgs {
@@ -162,5 +171,7 @@ hipError_t launch_sched(const SchedArgs& a, hipStream_t st);
 hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 size_t prefill_smem_bytes(int dtype, int d, int tab_len);
 int prefill_block_rows();
+int prefill_split_slots(int64_t items);       // parts of split items that a call with so many (head, row block) items may use
+size_t prefill_slot_bytes(int d);
 
 }  // namespace ls

@@ -185,6 +185,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     // head flag and cost estimate: table entries with a selected diagonal (key blocks a late row block
     // visits) plus packed column tiles
     s_bad = __syncthreads_or(s_bad);
+    if (bh == 0 && tid < 2) a.split_count[tid] = 0;
     if (tid == 0) {
         a.hflag[bh] = ((total_bits == (int)n) ? 1 : 0) | (v_bad ? 2 : 0);
         if (v_bad) atomicOr(a.status, STAT_V_INVALID);
@@ -200,11 +201,24 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // tiles in one L2); KV groups are dealt to the XCDs heaviest first, each to the XCD with the least
 // work so far.
 // One workgroup per queue; groups beyond SCHED_MAX_GROUPS fall back to round-robin dealing.  Inside a
-// queue items are ordered by decreasing tile count, so the long ones start first.
+// queue entries are ordered by decreasing tile count, so the long ones start first.
+//
+// Split items.  A (head, row block) item of a dense head late in the context has hundreds of tiles, and a short turn
+// has fewer items than the chip has compute units: one workgroup walking such an item alone decides the kernel's time.
+// An item with more than lmax tiles is therefore cut into equal parts that are queued like items; their unnormalised
+// results go to `slots` of the workspace and combine_kernel puts them together.  lmax is the mean number of tiles per
+// resident workgroup over SPLIT_SHARE, so the longest entry is a fraction of the run, but at least SPLIT_MIN: a part costs a
+// 64 KB result written and read (3-4 us of one CU's share of the memory bandwidth) against about 2 us per tile.
 // ---------------------------------------------------------------------------------------------
 constexpr int SCHED_MAX_GROUPS = 2048;
 constexpr int SCHED_MAX_HEADS = 8192;      // heads one XCD's queue can take
 constexpr int SCHED_THREADS = 1024;
+constexpr int SPLIT_ITEMS = 4096;          // most items for which splitting is considered (more of them balance by themselves)
+constexpr int SPLIT_SLOTS = 1024;          // most parts of split items
+constexpr int SPLIT_MIN = 4;               // tiles
+constexpr int SPLIT_SHARE = 2;
+constexpr int SPLIT_WGS = 512;             // workgroups resident on the chip (d = 128)
+constexpr int SPLIT_MAX_PARTS = 64;
 __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     __shared__ uint32_t gcost[SCHED_MAX_GROUPS];
     __shared__ uint16_t order[SCHED_MAX_GROUPS];          // groups by decreasing cost
@@ -245,8 +259,8 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     __shared__ uint32_t hist[4097];
     __shared__ uint16_t heads[SCHED_MAX_HEADS];
     __shared__ int nheads;
+    __shared__ uint32_t wsum[16];
     const int x = blockIdx.x;
-    const int64_t qcap = (int64_t)a.BH * a.nqb;
     auto item_cost = [&](int bh, int qb) -> int {
         const int64_t blockpos = a.pos0 + (int64_t)qb * BM;
         const int64_t posmax = (blockpos + BM - 1 < a.n - 1) ? blockpos + BM - 1 : a.n - 1;
@@ -266,49 +280,110 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
         const int bin = sorted ? (int)bin_of[gi] : (gi & 7);
         if (bin == x) { const int i = atomicAdd(&nheads, 1); if (i < SCHED_MAX_HEADS) heads[i] = (uint16_t)bh; }
     }
+    // longest part: the same in every block, from the costs of all items
+    int lmax = 4096;
+    if (a.slots > 0) {
+        int c4[SPLIT_ITEMS / SCHED_THREADS];
+        uint32_t mine = 0, total, used;
+#pragma unroll
+        for (int j = 0; j < SPLIT_ITEMS / SCHED_THREADS; ++j) {
+            const int it = tid + j * SCHED_THREADS;
+            c4[j] = it < a.BH * a.nqb ? item_cost(it / a.nqb, it % a.nqb) : 0;
+            mine += (uint32_t)c4[j];
+        }
+        (void)block_scan_1024(mine, wsum, total);
+        lmax = (int)(total / (SPLIT_WGS * SPLIT_SHARE));
+        if (lmax < SPLIT_MIN) lmax = SPLIT_MIN;
+        for (;;) {                                         // until the parts fit the slots (lmax >= 4096: nothing is split)
+            mine = 0;
+#pragma unroll
+            for (int j = 0; j < SPLIT_ITEMS / SCHED_THREADS; ++j) {
+                int parts = (c4[j] + lmax - 1) / lmax;
+                if (parts > SPLIT_MAX_PARTS) parts = SPLIT_MAX_PARTS;
+                mine += parts > 1 ? (uint32_t)parts : 0u;
+            }
+            (void)block_scan_1024(mine, wsum, used);
+            if (used <= (uint32_t)a.slots || lmax >= 4096) break;
+            lmax += (lmax + 1) / 2;
+        }
+        if (used > (uint32_t)a.slots) lmax = 1 << 30;
+    } else {
+        lmax = 1 << 30;
+    }
+    auto parts_of = [&](int c) -> int {
+        const int p = lmax >= 4096 ? 1 : (c + lmax - 1) / lmax;
+        return p < 1 ? 1 : p > SPLIT_MAX_PARTS ? SPLIT_MAX_PARTS : p;
+    };
     __syncthreads();
     const int nh_ = nheads < SCHED_MAX_HEADS ? nheads : SCHED_MAX_HEADS;
     const int64_t items = (int64_t)nh_ * a.nqb;
-    for (int64_t it = tid; it < items; it += SCHED_THREADS)
-        atomicAdd(&hist[4095 - item_cost(heads[it / a.nqb], (int)(it % a.nqb))], 1u);
+    for (int64_t it = tid; it < items; it += SCHED_THREADS) {
+        const int c = item_cost(heads[it / a.nqb], (int)(it % a.nqb)), p = parts_of(c);
+        atomicAdd(&hist[4095 - (c + p - 1) / p], (uint32_t)p);
+    }
     __syncthreads();
+    uint32_t entries;
     {                                                      // exclusive scan in decreasing-cost order
-        __shared__ uint32_t wsum[16];
-        uint32_t h4[4], mine = 0, all;
+        uint32_t h4[4], mine = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) { h4[q] = hist[4 * tid + q]; mine += h4[q]; }
-        uint32_t run = block_scan_1024(mine, wsum, all);
+        uint32_t run = block_scan_1024(mine, wsum, entries);
 #pragma unroll
         for (int q = 0; q < 4; ++q) { hist[4 * tid + q] = run; run += h4[q]; }
     }
     __syncthreads();
     for (int64_t it = tid; it < items; it += SCHED_THREADS) {
         const int bh = heads[it / a.nqb], qb = (int)(it % a.nqb);
-        const uint32_t posn = atomicAdd(&hist[4095 - item_cost(bh, qb)], 1u);
-        a.queue[(int64_t)x * qcap + posn] = ((uint32_t)bh << 16) | (uint32_t)qb;
+        const int c = item_cost(bh, qb), p = parts_of(c);
+        const uint32_t item = ((uint32_t)bh << 16) | (uint32_t)qb;
+        uint32_t posn = atomicAdd(&hist[4095 - (c + p - 1) / p], (uint32_t)p), slot0 = 0;
+        if (p > 1) {                                       // slots and the list of split items are shared by the 8 blocks
+            slot0 = (uint32_t)atomicAdd(&a.split_count[0], p);
+            a.split[atomicAdd(&a.split_count[1], 1)] = make_uint2(item, (uint32_t)p | (slot0 << 16));
+        }
+        uint2* q = a.queue + (int64_t)x * a.qcap + posn;
+        for (int e = 0; e < p; ++e) q[e] = make_uint2(item, (uint32_t)e | ((uint32_t)p << 8) | (slot0 << 16));
     }
-    if (tid == 0) { a.qlen[x] = (int)items; a.qhead[x] = 0; }
+    if (tid == 0) { a.qlen[x] = (int)entries; a.qhead[x] = 0; }
 }
 
 // Persistent launch: enough workgroups to fill the chip at any occupancy this kernel reaches
 // (256 CUs x up to 4 resident workgroups); surplus workgroups find the queues empty and leave.
 static int persistent_grid(const PrefillArgs& a) {
-    const int64_t total = (int64_t)a.BH * a.nqb;
+    const int64_t total = (int64_t)a.BH * a.nqb + a.slots;
     return (int)(total < 1024 ? total : 1024);
 }
 
-// Next work item for this workgroup: its own XCD's queue first, then the others in ring order.
-// Returns -1 when every queue is drained (each queue hands out each item once; the scan is finite).
-__device__ __forceinline__ int pop_item(const PrefillArgs& a, int my_x) {
-    for (int k = 0; k < 8; ++k) {
-        const int x = (my_x + k) & 7;
-        const int len = a.qlen[x];
-        if (__atomic_load_n(&a.qhead[x], __ATOMIC_RELAXED) < len) {
-            const int i = atomicAdd(&a.qhead[x], 1);
-            if (i < len) return (int)a.queue[(int64_t)x * a.qcap + i];
-        }
+// Next queue entry for this workgroup, called by one whole wave: its own XCD's queue first, then the others in
+// ring order, all eight looked at in one round trip.  x = ~0 when every queue is drained (each queue hands out
+// each entry once and never refills, so the loop ends).
+__device__ __forceinline__ uint2 pop_entry(const PrefillArgs& a, int my_x, int lane) {
+    const int x = (my_x + lane) & 7;
+    const int len = lane < 8 ? a.qlen[x] : 0;
+    for (;;) {
+        const bool some = lane < 8 && __atomic_load_n(&a.qhead[x], __ATOMIC_RELAXED) < len;
+        const uint64_t any = __ballot(some);
+        if (any == 0ull) return make_uint2(0xFFFFFFFFu, 0u);
+        const int src = __ffsll((unsigned long long)any) - 1;
+        int i = 0;
+        if (lane == src) i = atomicAdd(&a.qhead[x], 1);
+        i = __builtin_amdgcn_readlane(i, src);
+        const int xs = __builtin_amdgcn_readlane(x, src), ls = __builtin_amdgcn_readlane(len, src);
+        if (i < ls) return a.queue[(int64_t)xs * a.qcap + i];
     }
-    return -1;
+}
+
+// Unnormalised result of one part of a split item: accumulators lane by lane (16 bytes a lane, 1 KB a store) and
+// {reference, normaliser} per row.
+template <int DBLK>
+__device__ __forceinline__ void store_part(const PrefillArgs& a, int slot, int wv, int lane, const f32x16 (&oacc)[DBLK], float m, float l) {
+    float* o = a.part_o + (int64_t)slot * (BM * 32 * DBLK) + wv * (DBLK * 4 * 256) + lane * 4;
+#pragma unroll
+    for (int i = 0; i < DBLK; ++i)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq)
+            *reinterpret_cast<f32x4*>(o + (i * 4 + rq) * 256) = f32x4{oacc[i][4 * rq], oacc[i][4 * rq + 1], oacc[i][4 * rq + 2], oacc[i][4 * rq + 3]};
+    if (lane < 32) reinterpret_cast<float2*>(a.part_ml)[(int64_t)slot * BM + 32 * wv + lane] = make_float2(m, l);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -358,6 +433,45 @@ __device__ __forceinline__ void store_out4(bf16_t* p, float a, float b, float c,
 __device__ __forceinline__ void store_out4(float* p, float a, float b, float c, float d) {
     const f32x4 v = {a, b, c, d};
     *reinterpret_cast<f32x4*>(p) = v;
+}
+
+// Puts the parts of the split items together.  A unit is one wave's 32 rows of a split item, taken by one workgroup in
+// the layout store_part wrote: wave w adds the groups w, w + 4, ... of 16 bytes a lane.  grid-stride over the units.
+template <typename T, int D>
+__global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
+    constexpr int DBLK = D / 32;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r32 = lane & 31, g = lane >> 5;
+    const int units = a.split_count[1] * 4;
+    const float sc2 = a.scale_log2e;
+    for (int u = blockIdx.x; u < units; u += gridDim.x) {
+        const uint2 e = a.split[u >> 2];
+        const int wv = u & 3, bh = e.x >> 16, qb = e.x & 0xFFFF, parts = e.y & 0xFFFF, slot0 = e.y >> 16;
+        const int64_t row0 = a.n - a.n_hat, pos = a.pos0 + (int64_t)qb * BM + 32 * wv + r32;
+        if (pos < row0 || pos >= a.n) continue;
+        const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + (int64_t)slot0 * BM + 32 * wv + r32;
+        const float* o = a.part_o + (int64_t)slot0 * (BM * D) + wv * (DBLK * 4 * 256) + lane * 4;
+        f32x4 acc[DBLK];
+#pragma unroll
+        for (int k = 0; k < DBLK; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float m = -INFINITY, l = 0.f;
+        for (int p = 0; p < parts; ++p) m = fmaxf(m, ml[(int64_t)p * BM].x);
+        for (int p = 0; p < parts; ++p) {
+            const float2 t = ml[(int64_t)p * BM];
+            const float wgt = t.x > -INFINITY ? fast_exp2((t.x - m) * sc2) : 0.f;
+            l += t.y * wgt;
+#pragma unroll
+            for (int k = 0; k < DBLK; ++k) acc[k] += *reinterpret_cast<const f32x4*>(o + (int64_t)p * (BM * D) + (w + 4 * k) * 256) * wgt;
+        }
+        const float inv = l > 0.f ? 1.0f / l : 0.f;
+        T* orow = reinterpret_cast<T*>(a.out) + ((int64_t)bh * a.n_hat + (pos - row0)) * D;
+#pragma unroll
+        for (int k = 0; k < DBLK; ++k) {
+            const int grp = w + 4 * k, d0 = 32 * (grp >> 2) + 8 * (grp & 3) + 4 * g;
+            store_out4(orow + d0, acc[k].x * inv, acc[k].y * inv, acc[k].z * inv, acc[k].w * inv);
+        }
+        if (a.lse && g == 0 && w == 0)
+            a.lse[(int64_t)bh * a.n_hat + (pos - row0)] = l > 0.f ? (m * sc2 + log2f(l)) * 0.69314718055994531f : -INFINITY;
+    }
 }
 
 // ---- cell masks -------------------------------------------------------------------------------
@@ -454,14 +568,18 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, g = lane >> 5;
 
-    __shared__ int item_s;
-  for (;;) {                                               // persistent: one (head, row block) item per trip
-    __syncthreads();                                       // everyone is done with the previous item's LDS
-    if (tid == 0) item_s = pop_item(a, blockIdx.x & 7);    // taken only when needed: items are coarse, reserving early hurts the tail
+    __shared__ uint2 entry_s;
+  for (;;) {                                               // persistent: one queue entry per trip
+    __syncthreads();                                       // everyone is done with the previous entry's LDS
+    if (wv == 0) {                                         // taken only when needed: entries are coarse, reserving early hurts the tail
+        const uint2 e = pop_entry(a, blockIdx.x & 7, lane);
+        if (lane == 0) entry_s = e;
+    }
     __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(item_s);
-    if (item < 0) break;
+    const uint32_t item = __builtin_amdgcn_readfirstlane(entry_s.x), info = __builtin_amdgcn_readfirstlane(entry_s.y);
+    if (item == 0xFFFFFFFFu) break;
     const int bh = item >> 16, qb = item & 0xFFFF;
+    const int part = info & 0xFF, parts = (info >> 8) & 0xFF;           // this entry's share of the item's tiles
     const int b = bh / a.Hq, h = bh % a.Hq, kvh = h / a.G;
     const int64_t n = a.n, row0 = n - a.n_hat;
     const int64_t blockpos = a.pos0 + (int64_t)qb * BM;                  // multiple of 128
@@ -515,7 +633,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
         nv = lo;
     }
     const int n2 = (nv + BN - 1) / BN;
-    const int ntiles = n1 + n2;
+    const int tbeg = (n1 + n2) * part / parts, ntiles = (n1 + n2) * (part + 1) / parts;   // tiles tbeg .. ntiles - 1
 
     f32x16 oacc[C::DBLK];
 #pragma unroll
@@ -644,15 +762,15 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
         if (t >= n1 && tid < BN) colring[(t & 1) * BN + tid] = colv;
     };
 
-    if (ntiles > 0) {
-        load_cols(0);
-        fetch(0);
-        stash(0);
-        load_cols(1);
+    if (tbeg < ntiles) {
+        load_cols(tbeg);
+        fetch(tbeg);
+        stash(tbeg);
+        load_cols(tbeg + 1);
     }
     __syncthreads();
 
-    for (int t = 0; t < ntiles; ++t) {
+    for (int t = tbeg; t < ntiles; ++t) {
         const bool more = t + 1 < ntiles;
         if (more) fetch(t + 1);                            // uses the columns loaded one iteration ago
         const int32_t colv_next = colv;
@@ -678,7 +796,9 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     // ================= epilogue =================
     const float l_tot = l_run + xor32(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    if (row_ok) {
+    if (parts > 1) {
+        store_part<C::DBLK>(a, (int)(info >> 16) + part, wv, lane, oacc, m_run, l_tot);
+    } else if (row_ok) {
         T* orow = reinterpret_cast<T*>(a.out) + ((int64_t)bh * a.n_hat + (pos - row0)) * D;
 #pragma unroll
         for (int i = 0; i < C::DBLK; ++i)
@@ -773,14 +893,18 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
         for (int i = 0; i < C::DBLK; ++i) vaddr[i] = C::K_BYTES + lrow * C::RB + 64 * (i ^ y) + 32 * beta + 8 * (L16 & 3);
     }
 
-    __shared__ int item_s;
-  for (;;) {                                               // persistent: one (head, row block) item per trip
-    __syncthreads();                                       // everyone is done with the previous item's LDS
-    if (tid == 0) item_s = pop_item(a, blockIdx.x & 7);    // taken only when needed: items are coarse, reserving early hurts the tail
+    __shared__ uint2 entry_s;
+  for (;;) {                                               // persistent: one queue entry per trip
+    __syncthreads();                                       // everyone is done with the previous entry's LDS
+    if (wv == 0) {                                         // taken only when needed: entries are coarse, reserving early hurts the tail
+        const uint2 e = pop_entry(a, blockIdx.x & 7, lane);
+        if (lane == 0) entry_s = e;
+    }
     __syncthreads();
-    const int item = __builtin_amdgcn_readfirstlane(item_s);
-    if (item < 0) break;
+    const uint32_t item = __builtin_amdgcn_readfirstlane(entry_s.x), info = __builtin_amdgcn_readfirstlane(entry_s.y);
+    if (item == 0xFFFFFFFFu) break;
     const int bh = item >> 16, qb = item & 0xFFFF;
+    const int part = info & 0xFF, parts = (info >> 8) & 0xFF;           // this entry's share of the item's tiles
     const int b = bh / a.Hq, h = bh % a.Hq, kvh = h / a.G;
     const int64_t n = a.n, row0 = n - a.n_hat;
     const int64_t blockpos = a.pos0 + (int64_t)qb * BM;                  // multiple of 128
@@ -831,7 +955,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
         nv = lo;
     }
     const int n2 = (nv + BN - 1) / BN;
-    const int ntiles = n1 + n2;
+    const int tbeg = (n1 + n2) * part / parts, ntiles = (n1 + n2) * (part + 1) / parts;   // tiles tbeg .. ntiles - 1
 
     f32x16 oacc[C::DBLK];
 #pragma unroll
@@ -1025,22 +1149,22 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
         if (!rows_here) tm.act[0] = tm.act[1] = false;
     };
 
-    store_cols(0, fetch_cols(0));
-    store_cols(1, fetch_cols(1));
-    int32_t colpre = fetch_cols(2);
+    store_cols(tbeg, fetch_cols(tbeg));
+    store_cols(tbeg + 1, fetch_cols(tbeg + 1));
+    int32_t colpre = fetch_cols(tbeg + 2);
     __syncthreads();                                       // kbl and the first column ids are visible
     int kb_next = 0;                                       // key block of tile t + 1 (phase 1)
-    if (ntiles > 0) {
-        kb_next = 0 < n1 ? block_at(0) : 0;
-        mask_words(0, kb_next);
-        if (0 < n1) issue_block(kb_next, 0); else issue_cols(0);
-        masks(0);
-        kb_next = 1 < n1 ? block_at(1) : 0;
+    if (tbeg < ntiles) {
+        kb_next = tbeg < n1 ? block_at(tbeg) : 0;
+        mask_words(tbeg, kb_next);
+        if (tbeg < n1) issue_block(kb_next, tbeg); else issue_cols(tbeg);
+        masks(tbeg);
+        kb_next = tbeg + 1 < n1 ? block_at(tbeg + 1) : 0;
     }
     wait_transfers();
     __syncthreads();
 
-    for (int t = 0; t < ntiles; ++t) {
+    for (int t = tbeg; t < ntiles; ++t) {
         if (t + 3 >= n1) {                                 // column ids only matter around phase 2
             store_cols(t + 2, colpre);
             colpre = fetch_cols(t + 3);
@@ -1059,7 +1183,9 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
 
     const float l_tot = l_run + xor32(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    if (row_ok) {
+    if (parts > 1) {
+        store_part<C::DBLK>(a, (int)(info >> 16) + part, wv, lane, oacc, m_run, l_tot);
+    } else if (row_ok) {
         T* orow = reinterpret_cast<T*>(a.out) + ((int64_t)bh * a.n_hat + (pos - row0)) * D;
 #pragma unroll
         for (int i = 0; i < C::DBLK; ++i)
@@ -1076,6 +1202,11 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
   }                                                        // next item
 }
 
+template <typename T, int D>
+static void launch_combine(const PrefillArgs& a, hipStream_t st) {
+    if (a.slots > 0) hipLaunchKernelGGL((combine_kernel<T, D>), dim3(a.slots < 256 ? 2 * a.slots : 512), dim3(256), 0, st, a);
+}
+
 template <int D>
 static size_t prefill_bf16_smem(int tab_len) {
     return 2 * (size_t)DirectCfg<D>::TILE_BYTES + 256 * 4 + 8 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
@@ -1087,6 +1218,7 @@ static hipError_t launch_prefill_bf16(const PrefillArgs& a, hipStream_t st, hipE
     // with events: they take the start and stop time stamps of this dispatch itself, no marker goes into the stream
     if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
     else hipLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), smem, st, a);
+    launch_combine<bf16_t, D>(a, st);
     return hipGetLastError();
 }
 
@@ -1101,6 +1233,7 @@ static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t st, hipEven
     const size_t smem = prefill_smem_t<T, D>(a.tab_len);
     if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_kernel<T, D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
     else hipLaunchKernelGGL((prefill_kernel<T, D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), smem, st, a);
+    launch_combine<T, D>(a, st);
     return hipGetLastError();
 }
 
@@ -1127,6 +1260,8 @@ hipError_t launch_plan(const PlanArgs& a, int BH, hipStream_t st) {
 }
 
 int prefill_block_rows() { return BM; }
+int prefill_split_slots(int64_t items) { return items > SPLIT_ITEMS ? 0 : items * 16 < SPLIT_SLOTS ? (int)items * 16 : SPLIT_SLOTS; }
+size_t prefill_slot_bytes(int d) { return (size_t)BM * d * 4 + BM * 2 * 4; }
 
 hipError_t launch_sched(const SchedArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(sched_kernel, dim3(8), dim3(SCHED_THREADS), 0, st, a);
