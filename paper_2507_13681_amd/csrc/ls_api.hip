@@ -136,8 +136,8 @@ size_t ws_prefill(const ls_shape* s) {
     const int64_t rows = s->n_hat > 0 && s->n_hat <= s->n ? s->n_hat : s->n;
     const size_t items = BH * (size_t)(rows / 128 + 2);          // (head, row block) work items, upper bound
     const size_t slots = (size_t)ls::prefill_split_slots((int64_t)items);
-    return up(BH * (size_t)(words_of(s->n) + 4) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(BH) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
-           up(8 * (items + slots) * 8) + 2 * up(8 * 4) + up(slots * 8) + up(8) + up(slots * ls::prefill_slot_bytes(s->d)) + ALIGN;
+    return up(BH * (size_t)(words_of(s->n) + 4) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(items * 4) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
+           up(8 * (items + slots) * 16) + 2 * up(8 * 4) + up(slots * 8) + up(8) + up(slots * ls::prefill_slot_bytes(s->d)) + ALIGN;
 }
 size_t ws_compress(const ls_shape* s) {
     return ws_score(s, false) + up((size_t)s->B * s->Hkv * (size_t)s->n * 4) +
@@ -328,7 +328,7 @@ namespace {
 // Where ls_sparse_prefill keeps its per-call state in the workspace (one place, so that the test hook that
 // reads the work queues back finds them where the call put them).
 struct PrefillCarve {
-    uint32_t* obits; uint8_t* hflag; uint32_t* cost; uint16_t* pref; uint2* queue; int32_t* qlen; int32_t* qhead; uint8_t* tab;
+    uint32_t* obits; uint32_t* ncol; uint32_t* cost; uint16_t* pref; uint4* queue; int32_t* qlen; int32_t* qhead; uint8_t* tab;
     uint2* split; int32_t* split_count; float* part_o; float* part_ml;
     int nqb, qcap, slots; int64_t pos0; int code;
 };
@@ -337,7 +337,6 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     const int words = words_of(s->n), tab_len = tab_len_of(s->n);
     Bump bp{c->ws, c->ws_bytes, 0};
     w.obits = bp.take<uint32_t>((size_t)BH * (words + 4));
-    w.hflag = bp.take<uint8_t>((size_t)BH);
     w.cost = bp.take<uint32_t>((size_t)BH);
     w.pref = bp.take<uint16_t>((size_t)BH * (tab_len + 1));
     const int bm = ls::prefill_block_rows();
@@ -346,6 +345,7 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     w.code = LS_ESHAPE;
     if (w.nqb > 65535) return "too many row blocks";
     if (BH > 8192) return "B * Hq exceeds 8192";
+    w.ncol = bp.take<uint32_t>((size_t)BH * w.nqb);
     w.qlen = bp.take<int32_t>(8);
     w.qhead = bp.take<int32_t>(8);
     w.split_count = bp.take<int32_t>(2);
@@ -360,7 +360,7 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     for (;;) {
         bp = mark;
         w.qcap = (int)items + w.slots;
-        w.queue = bp.take<uint2>(8 * (size_t)w.qcap);
+        w.queue = bp.take<uint4>(8 * (size_t)w.qcap);
         w.split = w.slots ? bp.take<uint2>((size_t)w.slots) : nullptr;
         w.part_o = w.slots ? bp.take<float>((size_t)w.slots * 128 * s->d) : nullptr;
         w.part_ml = w.slots ? bp.take<float>((size_t)w.slots * 128 * 2) : nullptr;
@@ -390,32 +390,33 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
         return fail(c, LS_ESHAPE, "ls_sparse_prefill: n too large for the LDS bitmaps");
     PrefillCarve w;
     if (const char* m = carve_prefill(c, s, w)) return fail(c, w.code, "ls_sparse_prefill: %s", m);
-    uint32_t* obits = w.obits; uint8_t* hflag = w.hflag; uint32_t* cost = w.cost; uint16_t* pref = w.pref;
+    uint32_t* obits = w.obits; uint32_t* cost = w.cost; uint16_t* pref = w.pref;
     int32_t* qlen = w.qlen; int32_t* qhead = w.qhead; uint8_t* tab = w.tab;
     const int nqb = w.nqb; const int64_t pos0 = w.pos0;
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill: hipSetDevice failed");
     ls::PlanArgs p{};
     p.n = s->n; p.words = words; p.tab_len = tab_len; p.v_idx = v_idx; p.v_cnt = v_cnt; p.s_idx = s_idx; p.s_cnt = s_cnt;
-    p.cap_v = cap_v; p.cap_s = cap_s; p.obits = obits; p.tab = tab; p.hflag = hflag; p.cost = cost; p.pref = pref;
+    p.cap_v = cap_v; p.cap_s = cap_s; p.obits = obits; p.tab = tab; p.nqb = nqb; p.pos0 = pos0; p.ncol = w.ncol; p.cost = cost; p.pref = pref;
     p.status = c->status; p.split_count = w.split_count;
     hipError_t e = ls::launch_plan(p, BH, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(plan): %s", hipGetErrorString(e));
     ls::SchedArgs sa{};
     sa.BH = BH; sa.G = s->Hq / s->Hkv; sa.Hq = s->Hq; sa.Hkv = s->Hkv; sa.nqb = nqb; sa.cost = cost;
     sa.queue = w.queue; sa.qcap = w.qcap; sa.qlen = qlen; sa.qhead = qhead;
+    sa.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)BH * nqb, w.slots);
     sa.slots = w.slots; sa.split = w.split; sa.split_count = w.split_count;
-    sa.pref = pref; sa.v_cnt = v_cnt; sa.hflag = hflag; sa.tab_len = tab_len; sa.cap_v = cap_v; sa.n = s->n; sa.pos0 = pos0;
+    sa.pref = pref; sa.ncol = w.ncol; sa.tab_len = tab_len; sa.n = s->n; sa.pos0 = pos0;
     e = ls::launch_sched(sa, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(sched): %s", hipGetErrorString(e));
     ls::PrefillArgs a{};
     a.q = q; a.k = k; a.v = v; a.out = out; a.lse = lse; a.n = s->n; a.n_hat = s->n_hat;
-    a.queue = w.queue; a.qlen = qlen; a.qhead = qhead; a.qcap = w.qcap;
+    a.queue = w.queue; a.qlen = qlen; a.qhead = qhead; a.qcap = w.qcap; a.grid = sa.grid;
     a.slots = w.slots; a.split = w.split; a.split_count = w.split_count; a.part_o = w.part_o; a.part_ml = w.part_ml;
     a.pos0 = pos0;
     a.Hq = s->Hq; a.Hkv = s->Hkv; a.G = s->Hq / s->Hkv; a.BH = BH;
     a.nqb = nqb;
     a.words = words; a.tab_len = tab_len; a.scale_log2e = scale_log2e(s);
-    a.obits = obits; a.tab = tab; a.hflag = hflag; a.v_idx = v_idx; a.v_cnt = v_cnt; a.cap_v = cap_v;
+    a.obits = obits; a.tab = tab; a.v_idx = v_idx; a.cap_v = cap_v;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->profile) {
         if (hipEventCreate(&e0) != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill: hipEventCreate failed");
@@ -593,16 +594,16 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
     if (carve_prefill(c, s, w)) return w.code;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t items = (size_t)s->B * s->Hq * w.nqb;
-    std::vector<uint2> q(8 * (size_t)w.qcap);
+    std::vector<uint4> q(8 * (size_t)w.qcap);
     int32_t len[8];
     if (hipSetDevice(c->device) != hipSuccess) return LS_EHIP;
-    if (hipMemcpyAsync(q.data(), w.queue, q.size() * sizeof(uint2), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
+    if (hipMemcpyAsync(q.data(), w.queue, q.size() * sizeof(uint4), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
     if (hipMemcpyAsync(len, w.qlen, sizeof(len), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
     if (hipStreamSynchronize(st) != hipSuccess) return LS_EHIP;
     for (int x = 0; x < 8; ++x) {                          // an item in parts is listed once, by its first part
         host_qlen[x] = 0;
         for (int i = 0; i < len[x] && i < w.qcap; ++i) {
-            const uint2 e = q[(size_t)x * w.qcap + i];
+            const uint4 e = q[(size_t)x * w.qcap + i];
             if ((e.y & 0xFF) == 0 && (size_t)host_qlen[x] < items) host_queue[x * items + host_qlen[x]++] = e.x;
         }
     }

@@ -93,6 +93,10 @@ __device__ __forceinline__ void dma16(const unsigned char* gbase, uint32_t voff,
 __device__ __forceinline__ void dma16(const unsigned char* gptr, uint32_t lds) {                    // per-lane address
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(gptr) : "memory", "m0");
 }
+// The same with 4 bytes per lane, landing at lds + 4 * l.
+__device__ __forceinline__ void dma4(const void* gbase, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(gbase) : "memory", "m0");
+}
 // (The builtin says the same to the compiler, which does not look into asm statements: it then knows that its own loads
 // have landed too.  Without it, one of them that may still be pending on some path made it wait for every outstanding
 // transfer ahead of the products of each tile: 5 % of the attention kernel.)

@@ -61,7 +61,9 @@ struct PlanArgs {
     int cap_v, cap_s;
     uint32_t* obits;          // [BH][4 + words], four zero words first
     uint8_t* tab;             // [BH][tab_len]
-    uint8_t* hflag;           // [BH]
+    int nqb;                  // row blocks of the turn
+    int64_t pos0;             // position of the first
+    uint32_t* ncol;           // [BH][nqb] selected columns each row block gathers
     uint32_t* cost;           // [BH] estimated tiles per row block (for the work queues)
     uint16_t* pref;           // [BH][tab_len + 1] prefix counts of table entries with a selected diagonal
     int32_t* split_count;     // [2] cleared here for sched_kernel
@@ -73,14 +75,14 @@ struct SchedArgs {
     int BH, G, Hq, Hkv, nqb;
     const uint32_t* cost;     // [BH]
     const uint16_t* pref;     // [BH][tab_len + 1]
-    const int32_t* v_cnt;     // [BH]
-    const uint8_t* hflag;     // [BH]
-    int tab_len, cap_v;
+    const uint32_t* ncol;     // [BH][nqb]
+    int tab_len;
     int64_t n, pos0;
-    uint2* queue;             // [8][qcap] entries: {bh << 16 | qb, part | parts << 8 | first slot << 16}
+    uint4* queue;             // [8][qcap] entries: {bh << 16 | qb, part | parts << 8 | first slot << 16, key blocks, columns}
     int qcap;
     int32_t* qlen;            // [8]
-    int32_t* qhead;           // [8] next entry to hand out
+    int32_t* qhead;           // [8] next entry to hand out (the first ones go by workgroup number)
+    int grid;                 // workgroups of the attention kernel
     int slots;                // results of parts that the workspace holds (0: no item is split)
     uint2* split;             // [slots] split items: {bh << 16 | qb, parts | first slot << 16}
     int32_t* split_count;     // [2] slots in use, split items
@@ -94,13 +96,14 @@ struct PrefillArgs {
     int Hq, Hkv, G, BH, nqb, words, tab_len;
     float scale_log2e;
     const uint32_t* obits;
-    const uint8_t *tab, *hflag;
-    const int32_t *v_idx, *v_cnt;
+    const uint8_t* tab;
+    const int32_t* v_idx;
     int cap_v;
-    const uint2* queue;       // work queues built by sched_kernel
+    const uint4* queue;       // work queues built by sched_kernel
     const int32_t* qlen;
     int32_t* qhead;
     int qcap;                 // entries per queue
+    int grid;
     int slots;
     const uint2* split;
     const int32_t* split_count;
@@ -171,6 +174,7 @@ hipError_t launch_sched(const SchedArgs& a, hipStream_t st);
 hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 size_t prefill_smem_bytes(int dtype, int d, int tab_len);
 int prefill_block_rows();
+int prefill_grid(int dtype, int d, int64_t items, int slots);
 int prefill_split_slots(int64_t items);       // parts of split items that a call with so many (head, row block) items may use
 size_t prefill_slot_bytes(int d);
 

@@ -12,10 +12,9 @@
 // per-head table built by plan_kernel says, for each j, whether any (or every) diagonal in that range
 // is selected.
 //   phase 1: key blocks whose diagonal range holds a selected diagonal are streamed as contiguous
-//            64-key tiles; the cell mask is the diagonal bit, read from a bitmap in LDS.
+//            64-key tiles; the cell mask is the diagonal bit, read from the head's bitmap.
 //   phase 2: the selected columns (up to the block's last row) are gathered, 64 at a time, into
-//            packed tiles; a cell is dropped there if its diagonal is selected (phase 1 counted it),
-//            which the per-j table decides for whole columns in the common cases.
+//            packed tiles; a cell is dropped there if its diagonal is selected (phase 1 counted it).
 // So every allowed cell is visited exactly once.  Each wave owns 32 rows and skips the 32 x 32
 // sub-tiles in which none of its rows has an allowed cell.
 //
@@ -43,8 +42,8 @@ constexpr int PREFILL_THREADS = 256;
 //   obits : [BH][4 + words] uint32: four zero words, then bit o in word 4 + o/32; words = n/32 rounded up + 8 zero words
 //   tab   : [BH][tab_len] bytes, entry j+1 for j = -1 .. ; bit0 = some diagonal of
 //           [64j-63, 64j+127] is selected, bit1 = all of them are (and none is cut off at 0 or n-1)
-//   hflag : [BH] bytes, bit0 = every diagonal 0..n-1 is selected (the mask is plain causal),
-//           bit1 = the column list is not strictly ascending inside [0, n): its columns are ignored
+//   ncol  : [BH][nqb] columns that a row block gathers (none if every diagonal is selected: the mask is plain causal
+//           then, or if the column list is not strictly ascending inside [0, n): its columns are ignored)
 // ---------------------------------------------------------------------------------------------
 // Exclusive prefix sum over the 1024 threads of a workgroup (wave shuffles + one LDS round).
 // `wsum` must hold 16 words; returns the sum of `v` over the threads before this one and, in
@@ -65,11 +64,30 @@ __device__ __forceinline__ uint32_t block_scan_1024(uint32_t v, uint32_t* wsum, 
 }
 
 constexpr int OB_PAD = 4;                    // zero words in front of a head's bitmap (rows above a tile's keys)
+// The same for the maximum: the largest `v` of the threads before this one (0 for the first).
+__device__ __forceinline__ uint32_t block_max_1024(uint32_t v, uint32_t* wsum) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t inc = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) { const uint32_t t = __shfl_up(inc, off, 64); if (lane >= off && t > inc) inc = t; }
+    __syncthreads();
+    if (lane == 63) wsum[wv] = inc;
+    uint32_t ex = __shfl_up(inc, 1, 64);
+    if (lane == 0) ex = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < 16; ++w) if (w < wv && wsum[w] > ex) ex = wsum[w];
+    return ex;
+}
+
+constexpr int LS_MAX_BLOCKS = 262144 / 128 + 2;   // row blocks at the largest supported context
 constexpr int LS_MAX_TAB = 262144 / 64 + 8;  // table entries at the largest supported context
 __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     extern __shared__ uint32_t sm[];
     __shared__ int total_bits;
     __shared__ uint8_t tabs[LS_MAX_TAB];
+    __shared__ uint32_t colh[LS_MAX_BLOCKS];               // list position behind the last column that each row block is the first to see
+    __shared__ uint32_t wsum[16];
     const int bh = blockIdx.x;
     const int64_t n = a.n;
     const int words = a.words;
@@ -77,28 +95,38 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     int ns = a.s_cnt[bh]; if (ns > a.cap_s) ns = a.cap_s; if (ns < 0) ns = 0;
     const int32_t* si = a.s_idx + (int64_t)bh * a.cap_s;
     for (int i = tid; i < words; i += blockDim.x) sm[i] = 0u;
+    for (int i = tid; i < a.nqb; i += blockDim.x) colh[i] = 0u;
     if (tid == 0) total_bits = 0;
-    // The column list must be strictly ascending and inside [0, n) (the attention kernel bisects it and
-    // gathers K / V rows through it): a head whose list is not has its columns ignored (hflag bit 1) and the
-    // context's status word says so.  Diagonals outside [0, n) are skipped below and reported likewise.
+    __syncthreads();
+    // The column list must be strictly ascending and inside [0, n) (the attention kernel gathers K / V rows through
+    // a prefix of it): a head whose list is not has its columns ignored and the context's status word says so.  Diagonals outside [0, n) are skipped below and reported likewise.
     int nvl = a.v_cnt[bh]; if (nvl > a.cap_v) nvl = a.cap_v; if (nvl < 0) nvl = 0;
     const int32_t* vl = a.v_idx + (int64_t)bh * a.cap_v;
     bool v_bad = false, s_bad = false;
+    // the last column that each row block is the first to see leaves its list position behind (columns before the turn
+    // count for the first block)
+    auto block_of = [&](int32_t c) -> int { return c < a.pos0 + BM ? 0 : (int)((c - a.pos0) / BM); };
+    auto mark_col = [&](int i, int32_t c, int32_t next, bool last) {
+        if (c >= 0 && c < n && (last || block_of(next) != block_of(c))) colh[block_of(c)] = (uint32_t)i + 1u;
+    };
     if ((reinterpret_cast<uintptr_t>(vl) & 15) == 0 && a.cap_v % 4 == 0) {     // four entries per load (and the one before them)
         typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
         for (int i0 = 4 * tid; i0 < nvl; i0 += 4 * (int)blockDim.x) {
             const i32x4 c4 = *reinterpret_cast<const i32x4*>(vl + i0);     // entries past nvl (inside the capacity, a multiple of 4 here) are not looked at
             int32_t prev = i0 > 0 ? vl[i0 - 1] : -1;
+            const int32_t next = i0 + 4 < nvl ? vl[i0 + 4] : 0;
             const int32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if (i0 + e < nvl) { v_bad = v_bad || c[e] <= prev || c[e] >= n; prev = c[e]; }
+                if (i0 + e < nvl) mark_col(i0 + e, c[e], e < 3 ? c[(e + 1) & 3] : next, i0 + e == nvl - 1);
             }
         }
     } else {
         for (int i = tid; i < nvl; i += blockDim.x) {
             const int32_t c = vl[i];
             v_bad = v_bad || c < 0 || c >= n || (i > 0 && vl[i - 1] >= c);
+            mark_col(i, c, i + 1 < nvl ? vl[i + 1] : 0, i == nvl - 1);
         }
     }
     v_bad = __syncthreads_or(v_bad);
@@ -172,7 +200,6 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     }
     __syncthreads();
     // prefix counts of active entries: pref[e] = number of active entries below e
-    __shared__ uint32_t wsum[16];
     const int chunk = (a.tab_len + (int)blockDim.x - 1) / (int)blockDim.x;
     const int e0 = tid * chunk < a.tab_len ? tid * chunk : a.tab_len, e1 = (e0 + chunk < a.tab_len) ? e0 + chunk : a.tab_len;
     int mine2 = 0;
@@ -182,12 +209,25 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     uint16_t* pref = a.pref + (int64_t)bh * (a.tab_len + 1);
     for (int e = e0; e < e1; ++e) { pref[e] = (uint16_t)run; run += tabs[e] & 1; }
     if (e1 == a.tab_len && e0 < a.tab_len) pref[a.tab_len] = (uint16_t)run;
+    // columns each row block gathers: those up to its last row (none where every diagonal is selected, phase 1 covers
+    // all cells then, or where the list is unusable)
+    {
+        const bool none = total_bits == (int)n || v_bad;
+        const int per = (a.nqb + (int)blockDim.x - 1) / (int)blockDim.x;
+        const int q0 = tid * per < a.nqb ? tid * per : a.nqb, q1 = q0 + per < a.nqb ? q0 + per : a.nqb;
+        uint32_t top = 0;                                  // positions grow with the block: a running maximum fills the gaps
+        for (int q = q0; q < q1; ++q) top = top > colh[q] ? top : colh[q];
+        uint32_t before = block_max_1024(top, wsum);
+        for (int q = q0; q < q1; ++q) {
+            before = before > colh[q] ? before : colh[q];
+            a.ncol[(int64_t)bh * a.nqb + q] = none ? 0u : before;
+        }
+    }
     // head flag and cost estimate: table entries with a selected diagonal (key blocks a late row block
     // visits) plus packed column tiles
     s_bad = __syncthreads_or(s_bad);
     if (bh == 0 && tid < 2) a.split_count[tid] = 0;
     if (tid == 0) {
-        a.hflag[bh] = ((total_bits == (int)n) ? 1 : 0) | (v_bad ? 2 : 0);
         if (v_bad) atomicOr(a.status, STAT_V_INVALID);
         if (s_bad) atomicOr(a.status, STAT_S_RANGE);
         int nv = a.v_cnt[bh]; if (nv > a.cap_v) nv = a.cap_v; if (nv < 0) nv = 0;
@@ -223,9 +263,34 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     __shared__ uint32_t gcost[SCHED_MAX_GROUPS];
     __shared__ uint16_t order[SCHED_MAX_GROUPS];          // groups by decreasing cost
     __shared__ uint16_t bin_of[SCHED_MAX_GROUPS];
+    __shared__ uint32_t hist[4097];
+    __shared__ uint16_t heads[SCHED_MAX_HEADS];
+    __shared__ uint16_t cost_s[SPLIT_ITEMS];              // costs of all items, where they are few
+    __shared__ int nheads;
+    __shared__ uint32_t wsum[16];
     const int tid = threadIdx.x;
     const int groups = a.BH / a.G;
     const bool sorted = groups <= SCHED_MAX_GROUPS;
+    const int x = blockIdx.x;
+    // Item cost = key blocks with a selected diagonal that the row block visits (from the prefix counts) + packed
+    // column tiles.
+    auto blocks_of = [&](int bh, int qb) -> int {
+        const int64_t blockpos = a.pos0 + (int64_t)qb * BM;
+        const int64_t posmax = (blockpos + BM - 1 < a.n - 1) ? blockpos + BM - 1 : a.n - 1;
+        const int jb = (int)(blockpos / BN), kb_hi = (int)(posmax / BN);
+        const uint16_t* pref = a.pref + (int64_t)bh * (a.tab_len + 1);
+        return pref[jb + 2] - pref[jb - kb_hi + 1];       // entries jb-kb_hi+1 .. jb+1
+    };
+    auto item_cost = [&](int bh, int qb) -> int {
+        const int c = blocks_of(bh, qb) + (int)(a.ncol[(int64_t)bh * a.nqb + qb] + 63) / 64;
+        return c > 4095 ? 4095 : c;
+    };
+    const uint32_t all_items = (uint32_t)a.BH * (uint32_t)a.nqb, nqb = (uint32_t)a.nqb;      // at most 8192 * 2050
+    const bool cached = all_items <= SPLIT_ITEMS;
+    if (cached)
+        for (uint32_t it = tid; it < all_items; it += SCHED_THREADS) cost_s[it] = (uint16_t)item_cost((int)(it / nqb), (int)(it % nqb));
+    for (int i = tid; i < 4097; i += SCHED_THREADS) hist[i] = 0u;
+    if (tid == 0) nheads = 0;
     if (sorted) {                                          // every block repeats this small computation
         for (int gi = tid; gi < groups; gi += SCHED_THREADS) {
             const int b = gi / a.Hkv, kvh = gi % a.Hkv;
@@ -241,39 +306,19 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
             order[rank] = (uint16_t)gi;
         }
         __syncthreads();
-        if (tid == 0) {
-            uint64_t load[8];
-            for (int x = 0; x < 8; ++x) load[x] = 0;
+        if (tid < 64) {                                    // one wave deals them out; lane l < 8 holds bin l's load
+            uint32_t load = 0;                             // (a group's cost is at most G * 4 * 4096 tiles)
             for (int r = 0; r < groups; ++r) {
                 const int gi = order[r];
-                int best = 0;
-                for (int x = 1; x < 8; ++x) if (load[x] < load[best]) best = x;
-                bin_of[gi] = (uint16_t)best;
-                load[best] += gcost[gi] + 1;
+                uint32_t best = tid < 8 ? (load << 3 | tid) : 0xFFFFFFFFu;           // least load, then least index
+#pragma unroll
+                for (int off = 4; off > 0; off >>= 1) { const uint32_t o = __shfl_xor(best, off, 64); best = o < best ? o : best; }
+                const int bin = (int)(__builtin_amdgcn_readfirstlane((int)best) & 7);
+                if (tid == bin) load += gcost[gi] + 1;
+                if (tid == 0) bin_of[gi] = (uint16_t)bin;
             }
         }
-        __syncthreads();
     }
-    // Work items (head, row block) of this block's bin, heaviest first.  Item cost = key blocks with a
-    // selected diagonal that the row block visits (from the prefix counts) + packed column tiles.
-    __shared__ uint32_t hist[4097];
-    __shared__ uint16_t heads[SCHED_MAX_HEADS];
-    __shared__ int nheads;
-    __shared__ uint32_t wsum[16];
-    const int x = blockIdx.x;
-    auto item_cost = [&](int bh, int qb) -> int {
-        const int64_t blockpos = a.pos0 + (int64_t)qb * BM;
-        const int64_t posmax = (blockpos + BM - 1 < a.n - 1) ? blockpos + BM - 1 : a.n - 1;
-        const int jb = (int)(blockpos / BN), kb_hi = (int)(posmax / BN);
-        const uint16_t* pref = a.pref + (int64_t)bh * (a.tab_len + 1);
-        int c = pref[jb + 2] - pref[jb - kb_hi + 1];      // entries jb-kb_hi+1 .. jb+1
-        int nv = a.v_cnt[bh]; if (nv > a.cap_v) nv = a.cap_v; if (nv < 0) nv = 0;
-        if (a.hflag[bh] & 3) nv = 0;
-        c += (nv + 63) / 64;
-        return c > 4095 ? 4095 : c;
-    };
-    for (int i = tid; i < 4097; i += SCHED_THREADS) hist[i] = 0u;
-    if (tid == 0) nheads = 0;
     __syncthreads();
     for (int bh = tid; bh < a.BH; bh += SCHED_THREADS) {   // heads of this bin (order inside the list is free)
         const int b = bh / a.Hq, h = bh % a.Hq, gi = b * a.Hkv + h / a.G;
@@ -281,14 +326,14 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
         if (bin == x) { const int i = atomicAdd(&nheads, 1); if (i < SCHED_MAX_HEADS) heads[i] = (uint16_t)bh; }
     }
     // longest part: the same in every block, from the costs of all items
-    int lmax = 4096;
-    if (a.slots > 0) {
+    int lmax = 1 << 30;
+    if (a.slots > 0 && cached) {
         int c4[SPLIT_ITEMS / SCHED_THREADS];
         uint32_t mine = 0, total, used;
 #pragma unroll
         for (int j = 0; j < SPLIT_ITEMS / SCHED_THREADS; ++j) {
             const int it = tid + j * SCHED_THREADS;
-            c4[j] = it < a.BH * a.nqb ? item_cost(it / a.nqb, it % a.nqb) : 0;
+            c4[j] = it < (int)all_items ? cost_s[it] : 0;
             mine += (uint32_t)c4[j];
         }
         (void)block_scan_1024(mine, wsum, total);
@@ -307,8 +352,6 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
             lmax += (lmax + 1) / 2;
         }
         if (used > (uint32_t)a.slots) lmax = 1 << 30;
-    } else {
-        lmax = 1 << 30;
     }
     auto parts_of = [&](int c) -> int {
         const int p = lmax >= 4096 ? 1 : (c + lmax - 1) / lmax;
@@ -316,9 +359,10 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     };
     __syncthreads();
     const int nh_ = nheads < SCHED_MAX_HEADS ? nheads : SCHED_MAX_HEADS;
-    const int64_t items = (int64_t)nh_ * a.nqb;
-    for (int64_t it = tid; it < items; it += SCHED_THREADS) {
-        const int c = item_cost(heads[it / a.nqb], (int)(it % a.nqb)), p = parts_of(c);
+    const uint32_t items = (uint32_t)nh_ * nqb;
+    for (uint32_t it = tid; it < items; it += SCHED_THREADS) {
+        const int bh = heads[it / nqb], qb = (int)(it % nqb);
+        const int c = cached ? cost_s[bh * a.nqb + qb] : item_cost(bh, qb), p = parts_of(c);
         atomicAdd(&hist[4095 - (c + p - 1) / p], (uint32_t)p);
     }
     __syncthreads();
@@ -332,46 +376,72 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
         for (int q = 0; q < 4; ++q) { hist[4 * tid + q] = run; run += h4[q]; }
     }
     __syncthreads();
-    for (int64_t it = tid; it < items; it += SCHED_THREADS) {
-        const int bh = heads[it / a.nqb], qb = (int)(it % a.nqb);
-        const int c = item_cost(bh, qb), p = parts_of(c);
+    for (uint32_t it = tid; it < items; it += SCHED_THREADS) {
+        const int bh = heads[it / nqb], qb = (int)(it % nqb);
+        const uint32_t n1 = (uint32_t)blocks_of(bh, qb), nv = a.ncol[(int64_t)bh * a.nqb + qb];
+        const int c = cached ? cost_s[bh * a.nqb + qb] : item_cost(bh, qb), p = parts_of(c);
         const uint32_t item = ((uint32_t)bh << 16) | (uint32_t)qb;
         uint32_t posn = atomicAdd(&hist[4095 - (c + p - 1) / p], (uint32_t)p), slot0 = 0;
         if (p > 1) {                                       // slots and the list of split items are shared by the 8 blocks
             slot0 = (uint32_t)atomicAdd(&a.split_count[0], p);
             a.split[atomicAdd(&a.split_count[1], 1)] = make_uint2(item, (uint32_t)p | (slot0 << 16));
         }
-        uint2* q = a.queue + (int64_t)x * a.qcap + posn;
-        for (int e = 0; e < p; ++e) q[e] = make_uint2(item, (uint32_t)e | ((uint32_t)p << 8) | (slot0 << 16));
+        uint4* q = a.queue + (int64_t)x * a.qcap + posn;
+        const uint32_t bkv = (uint32_t)(bh / a.Hq * a.Hkv + bh % a.Hq / a.G);
+        for (int e = 0; e < p; ++e) q[e] = make_uint4(item, (uint32_t)e | ((uint32_t)p << 8) | (slot0 << 16), n1 | (bkv << 16), nv);
     }
-    if (tid == 0) { a.qlen[x] = (int)entries; a.qhead[x] = 0; }
+    if (tid == 0) { a.qlen[x] = (int)entries; a.qhead[x] = (a.grid - x + 7) / 8; }
 }
 
-// Persistent launch: enough workgroups to fill the chip at any occupancy this kernel reaches
-// (256 CUs x up to 4 resident workgroups); surplus workgroups find the queues empty and leave.
-static int persistent_grid(const PrefillArgs& a) {
-    const int64_t total = (int64_t)a.BH * a.nqb + a.slots;
-    return (int)(total < 1024 ? total : 1024);
+// Persistent launch: the workgroups that are resident at once (256 CUs x per_cu); any number drains the queues, but a
+// surplus one only starts when another ends and lengthens the run by its look at the queues.
+int prefill_grid(int dtype, int d, int64_t items, int slots) {
+    const int per_cu = dtype == 0 ? (d == 128 ? 2 : 3) : (d == 128 ? 1 : 2);
+    return (int)(items + slots < 256 * per_cu ? items + slots : 256 * per_cu);
 }
 
-// Next queue entry for this workgroup, called by one whole wave: its own XCD's queue first, then the others in
-// ring order, all eight looked at in one round trip.  x = ~0 when every queue is drained (each queue hands out
-// each entry once and never refills, so the loop ends).
-__device__ __forceinline__ uint2 pop_entry(const PrefillArgs& a, int my_x, int lane) {
-    const int x = (my_x + lane) & 7;
-    const int len = lane < 8 ? a.qlen[x] : 0;
-    for (;;) {
-        const bool some = lane < 8 && __atomic_load_n(&a.qhead[x], __ATOMIC_RELAXED) < len;
-        const uint64_t any = __ballot(some);
-        if (any == 0ull) return make_uint2(0xFFFFFFFFu, 0u);
-        const int src = __ffsll((unsigned long long)any) - 1;
+// Queue entries for this workgroup, called by one whole wave.  The first entry is the workgroup's own place in its
+// XCD's queue (sched_kernel starts the counters behind those), later ones come from the counters: the own queue while
+// it has any, then the others in ring order, all eight looked at in one round trip.  While the own queue is far from
+// its end the counter is updated without a look, and beside the other waves' stores of the last results (`ahead`); near
+// the end every workgroup would update it once for nothing, and updates of one counter take turns.  item = ~0 when every
+// queue is drained (each queue hands out each entry once and never refills, so the search ends).
+struct EntrySource {
+    int own, x, len;                          // lane l < 8: queue (own + l) % 8 and its length
+    int at;                                   // place taken in the own queue, -1: none
+    bool plenty;
+    __device__ __forceinline__ void init(const PrefillArgs& a, int lane) {
+        own = blockIdx.x & 7; x = (own + lane) & 7; len = lane < 8 ? a.qlen[x] : 0;
+        at = (int)(blockIdx.x >> 3); plenty = true;
+    }
+    __device__ __forceinline__ void ahead(const PrefillArgs& a, int lane) {
+        if (!plenty) return;
         int i = 0;
-        if (lane == src) i = atomicAdd(&a.qhead[x], 1);
-        i = __builtin_amdgcn_readlane(i, src);
-        const int xs = __builtin_amdgcn_readlane(x, src), ls = __builtin_amdgcn_readlane(len, src);
-        if (i < ls) return a.queue[(int64_t)xs * a.qcap + i];
+        if (lane == 0) i = atomicAdd(&a.qhead[own], 1);
+        at = __builtin_amdgcn_readfirstlane(i);
     }
-}
+    __device__ __forceinline__ uint4 next(const PrefillArgs& a, int lane) {
+        const int own_len = __builtin_amdgcn_readfirstlane(len);
+        if (at >= 0 && at < own_len) {
+            const int i = at;
+            at = -1;
+            plenty = own_len - i > 128;
+            return a.queue[(int64_t)own * a.qcap + i];
+        }
+        plenty = false;
+        for (;;) {
+            const bool some = lane < 8 && __atomic_load_n(&a.qhead[x], __ATOMIC_RELAXED) < len;
+            const uint64_t any = __ballot(some);
+            if (any == 0ull) return make_uint4(0xFFFFFFFFu, 0u, 0u, 0u);
+            const int src = __ffsll((unsigned long long)any) - 1;
+            int i = 0;
+            if (lane == src) i = atomicAdd(&a.qhead[x], 1);
+            i = __builtin_amdgcn_readlane(i, src);
+            const int xs = __builtin_amdgcn_readlane(x, src), ls = __builtin_amdgcn_readlane(len, src);
+            if (i < ls) return a.queue[(int64_t)xs * a.qcap + i];
+        }
+    }
+};
 
 // Unnormalised result of one part of a split item: accumulators lane by lane (16 bytes a lane, 1 KB a store) and
 // {reference, normaliser} per row.
@@ -425,10 +495,8 @@ __device__ __forceinline__ void store_vt<float>(unsigned char* vt, int stride, i
 }
 
 __device__ __forceinline__ void store_out4(bf16_t* p, float a, float b, float c, float d) {
-    struct U2 { uint32_t x, y; } u;
-    u.x = (uint32_t)f2bf(a) | ((uint32_t)f2bf(b) << 16);
-    u.y = (uint32_t)f2bf(c) | ((uint32_t)f2bf(d) << 16);
-    *reinterpret_cast<U2*>(p) = u;
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+    *reinterpret_cast<bf16x4*>(p) = __builtin_convertvector((f32x4{a, b, c, d}), bf16x4);      // round to nearest even
 }
 __device__ __forceinline__ void store_out4(float* p, float a, float b, float c, float d) {
     const f32x4 v = {a, b, c, d};
@@ -454,13 +522,30 @@ __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
 #pragma unroll
         for (int k = 0; k < DBLK; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
         float m = -INFINITY, l = 0.f;
-        for (int p = 0; p < parts; ++p) m = fmaxf(m, ml[(int64_t)p * BM].x);
-        for (int p = 0; p < parts; ++p) {
-            const float2 t = ml[(int64_t)p * BM];
-            const float wgt = t.x > -INFINITY ? fast_exp2((t.x - m) * sc2) : 0.f;
-            l += t.y * wgt;
+        for (int p0 = 0; p0 < parts; p0 += 4) {            // four parts' loads in flight (the last part is repeated with weight 0)
+            float2 t[4];
+            f32x4 x[4][DBLK];
 #pragma unroll
-            for (int k = 0; k < DBLK; ++k) acc[k] += *reinterpret_cast<const f32x4*>(o + (int64_t)p * (BM * D) + (w + 4 * k) * 256) * wgt;
+            for (int e = 0; e < 4; ++e) {
+                const int p = p0 + e < parts ? p0 + e : parts - 1;
+                t[e] = ml[(int64_t)p * BM];
+                if (p0 + e >= parts) t[e].x = -INFINITY;
+#pragma unroll
+                for (int k = 0; k < DBLK; ++k) x[e][k] = *reinterpret_cast<const f32x4*>(o + (int64_t)p * (BM * D) + (w + 4 * k) * 256);
+            }
+            const float m_new = fmaxf(fmaxf(fmaxf(m, t[0].x), fmaxf(t[1].x, t[2].x)), t[3].x);
+            const float corr = m > -INFINITY ? fast_exp2((m - m_new) * sc2) : 0.f;
+            m = m_new;
+            l *= corr;
+#pragma unroll
+            for (int k = 0; k < DBLK; ++k) acc[k] *= corr;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float wgt = t[e].x > -INFINITY ? fast_exp2((t[e].x - m) * sc2) : 0.f;
+                l += t[e].y * wgt;
+#pragma unroll
+                for (int k = 0; k < DBLK; ++k) acc[k] += x[e][k] * wgt;
+            }
         }
         const float inv = l > 0.f ? 1.0f / l : 0.f;
         T* orow = reinterpret_cast<T*>(a.out) + ((int64_t)bh * a.n_hat + (pos - row0)) * D;
@@ -568,24 +653,27 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, g = lane >> 5;
 
-    __shared__ uint2 entry_s;
+    __shared__ uint4 entry_s;
+    EntrySource src;
+    src.init(a, lane);
   for (;;) {                                               // persistent: one queue entry per trip
     __syncthreads();                                       // everyone is done with the previous entry's LDS
-    if (wv == 0) {                                         // taken only when needed: entries are coarse, reserving early hurts the tail
-        const uint2 e = pop_entry(a, blockIdx.x & 7, lane);
+    if (wv == 0) {
+        const uint4 e = src.next(a, lane);
         if (lane == 0) entry_s = e;
     }
     __syncthreads();
     const uint32_t item = __builtin_amdgcn_readfirstlane(entry_s.x), info = __builtin_amdgcn_readfirstlane(entry_s.y);
+    const int bkv = (int)(__builtin_amdgcn_readfirstlane(entry_s.z) >> 16);
+    const int nv = __builtin_amdgcn_readfirstlane(entry_s.w);           // columns phase 2 gathers (those up to the block's last row)
     if (item == 0xFFFFFFFFu) break;
     const int bh = item >> 16, qb = item & 0xFFFF;
     const int part = info & 0xFF, parts = (info >> 8) & 0xFF;           // this entry's share of the item's tiles
-    const int b = bh / a.Hq, h = bh % a.Hq, kvh = h / a.G;
     const int64_t n = a.n, row0 = n - a.n_hat;
     const int64_t blockpos = a.pos0 + (int64_t)qb * BM;                  // multiple of 128
     const int64_t posmax = (blockpos + BM - 1 < n - 1) ? blockpos + BM - 1 : n - 1;
-    const T* Kg = reinterpret_cast<const T*>(a.k) + ((int64_t)b * a.Hkv + kvh) * n * D;
-    const T* Vg = reinterpret_cast<const T*>(a.v) + ((int64_t)b * a.Hkv + kvh) * n * D;
+    const T* Kg = reinterpret_cast<const T*>(a.k) + (int64_t)bkv * n * D;
+    const T* Vg = reinterpret_cast<const T*>(a.v) + (int64_t)bkv * n * D;
     const T* Qg = reinterpret_cast<const T*>(a.q) + (int64_t)bh * a.n_hat * D;
 
     const uint8_t* tab = a.tab + (int64_t)bh * a.tab_len;
@@ -623,15 +711,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
         n1 += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
         __syncthreads();
     }
-    // ---- how many selected columns phase 2 gathers (columns beyond the block's last row are invisible)
-    int nv = a.v_cnt[bh]; if (nv > a.cap_v) nv = a.cap_v; if (nv < 0) nv = 0;
     const int32_t* vi = a.v_idx + (int64_t)bh * a.cap_v;
-    if (a.hflag[bh] & 3) nv = 0;                           // every diagonal is selected (phase 1 covers all cells), or the list is unusable
-    if (nv > 0 && (int64_t)vi[nv - 1] > posmax) {          // ascending list: binary search for the first column > posmax
-        int lo = 0, hi = nv - 1;
-        while (lo < hi) { const int mid = (lo + hi) >> 1; if ((int64_t)vi[mid] > posmax) hi = mid; else lo = mid + 1; }
-        nv = lo;
-    }
     const int n2 = (nv + BN - 1) / BN;
     const int tbeg = (n1 + n2) * part / parts, ntiles = (n1 + n2) * (part + 1) / parts;   // tiles tbeg .. ntiles - 1
 
@@ -854,18 +934,20 @@ struct DirectCfg {
 };
 
 template <int D>
-__global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf16_kernel(PrefillArgs a) {
     using C = DirectCfg<D>;
     using T = bf16_t;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* tiles = smem;                                         // [2][TILE_BYTES]
-    int32_t* colring = reinterpret_cast<int32_t*>(smem + 2 * C::TILE_BYTES);   // [4][64]
-    int32_t* wcnt = colring + 256;                                       // [8]
+    int32_t* colring = reinterpret_cast<int32_t*>(smem + 2 * C::TILE_BYTES);   // [4][64] column ids of packed tiles
+    uint32_t* colbits = reinterpret_cast<uint32_t*>(colring + 256);      // [4 waves][2][64] bitmap words for the masks of a packed tile
+    int32_t* wcnt = reinterpret_cast<int32_t*>(colbits + 512);           // [8]
     uint16_t* kbl = reinterpret_cast<uint16_t*>(wcnt + 8);               // [tab_len] active key blocks
     const uint32_t tiles_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)tiles;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t colring_lds = tiles_lds + 2u * C::TILE_BYTES, colbits_lds = colring_lds + 1024u + (uint32_t)wv * 512u;
     const int r32 = lane & 31, g = lane >> 5;
 
     // ---- per-lane constants of the transfers: this lane fills slot sl of row rowlane (+ 4*RPI per
@@ -893,24 +975,27 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
         for (int i = 0; i < C::DBLK; ++i) vaddr[i] = C::K_BYTES + lrow * C::RB + 64 * (i ^ y) + 32 * beta + 8 * (L16 & 3);
     }
 
-    __shared__ uint2 entry_s;
+    __shared__ uint4 entry_s;
+    EntrySource src;
+    src.init(a, lane);
   for (;;) {                                               // persistent: one queue entry per trip
-    __syncthreads();                                       // everyone is done with the previous entry's LDS
-    if (wv == 0) {                                         // taken only when needed: entries are coarse, reserving early hurts the tail
-        const uint2 e = pop_entry(a, blockIdx.x & 7, lane);
+    if (wv == 0) {                                         // (the other waves have read the last entry: barriers came after it)
+        const uint4 e = src.next(a, lane); // taken only when needed: entries are coarse, reserving early hurts the tail
         if (lane == 0) entry_s = e;
     }
     __syncthreads();
     const uint32_t item = __builtin_amdgcn_readfirstlane(entry_s.x), info = __builtin_amdgcn_readfirstlane(entry_s.y);
+    const int n1 = (int)(__builtin_amdgcn_readfirstlane(entry_s.z) & 0xFFFF);   // key blocks phase 1 visits
+    const int bkv = (int)(__builtin_amdgcn_readfirstlane(entry_s.z) >> 16);
+    const int nv = __builtin_amdgcn_readfirstlane(entry_s.w);           // columns phase 2 gathers (those up to the block's last row)
     if (item == 0xFFFFFFFFu) break;
     const int bh = item >> 16, qb = item & 0xFFFF;
     const int part = info & 0xFF, parts = (info >> 8) & 0xFF;           // this entry's share of the item's tiles
-    const int b = bh / a.Hq, h = bh % a.Hq, kvh = h / a.G;
     const int64_t n = a.n, row0 = n - a.n_hat;
     const int64_t blockpos = a.pos0 + (int64_t)qb * BM;                  // multiple of 128
     const int64_t posmax = (blockpos + BM - 1 < n - 1) ? blockpos + BM - 1 : n - 1;
-    const unsigned char* Kg = reinterpret_cast<const unsigned char*>(a.k) + ((int64_t)b * a.Hkv + kvh) * n * C::RB;
-    const unsigned char* Vg = reinterpret_cast<const unsigned char*>(a.v) + ((int64_t)b * a.Hkv + kvh) * n * C::RB;
+    const unsigned char* Kg = reinterpret_cast<const unsigned char*>(a.k) + (int64_t)bkv * n * C::RB;
+    const unsigned char* Vg = reinterpret_cast<const unsigned char*>(a.v) + (int64_t)bkv * n * C::RB;
     const T* Qg = reinterpret_cast<const T*>(a.q) + (int64_t)bh * a.n_hat * D;
     const uint8_t* tabg = a.tab + (int64_t)bh * a.tab_len;
 
@@ -919,6 +1004,10 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
     const int posw = (int)blockpos + 32 * wv;              // the wave's first row
     const bool row_ok = (pos >= row0) && (pos < n);        // a row that does not exist has zeros: finite results, not stored
     const bool rows_here = posw < n && posw + 31 >= row0;
+    // the first table entries are asked for ahead of the queries: the list below waits for them only
+    const int jb = (int)(blockpos / BN), kb_hi = (int)(posmax / BN);    // jb is even
+    uint8_t tab0 = n1 > 0 && tid <= kb_hi ? tabg[jb - tid + 1] : (uint8_t)0;
+    asm volatile("" ::: "memory");
     Frag<T> qf[C::KSTEPS];
     if (row_ok) {
         const T* qrow = Qg + (pos - row0) * D;
@@ -930,30 +1019,22 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
     }
 
     // ---- ordered list of the key blocks phase 1 visits
-    const int64_t jb = blockpos / BN;                      // even
-    const int kb_hi = (int)(posmax / BN);
-    int n1 = 0;
-    for (int base = 0; base <= kb_hi; base += PREFILL_THREADS) {
-        const int kb = base + tid;
-        const bool act = kb <= kb_hi && (tabg[jb - kb + 1] & 1);
-        const uint64_t bal = __ballot(act);
-        if (lane == 0) wcnt[wv] = __popcll(bal);
-        __syncthreads();
-        int off = n1;
-        for (int w2 = 0; w2 < wv; ++w2) off += wcnt[w2];
-        if (act) kbl[off + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)kb;
-        n1 += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
-        __syncthreads();
+    if (n1 > 0) {
+        int done = 0;
+        for (int base = 0; base <= kb_hi; base += PREFILL_THREADS) {
+            const int kb = base + tid;
+            const bool act = kb <= kb_hi && ((base == 0 ? tab0 : tabg[jb - kb + 1]) & 1);
+            const uint64_t bal = __ballot(act);
+            if (lane == 0) wcnt[wv] = __popcll(bal);
+            __syncthreads();
+            int off = done;
+            for (int w2 = 0; w2 < wv; ++w2) off += wcnt[w2];
+            if (act) kbl[off + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)kb;
+            done += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+            __syncthreads();
+        }
     }
-    n1 = __builtin_amdgcn_readfirstlane(n1);
-    int nv = a.v_cnt[bh]; if (nv > a.cap_v) nv = a.cap_v; if (nv < 0) nv = 0;
     const int32_t* vi = a.v_idx + (int64_t)bh * a.cap_v;
-    if (a.hflag[bh] & 3) nv = 0;                           // every diagonal is selected (phase 1 covers all cells), or the list is unusable
-    if (nv > 0 && (int64_t)vi[nv - 1] > posmax) {          // ascending list: binary search for the first column > posmax
-        int lo = 0, hi = nv - 1;
-        while (lo < hi) { const int mid = (lo + hi) >> 1; if ((int64_t)vi[mid] > posmax) hi = mid; else lo = mid + 1; }
-        nv = lo;
-    }
     const int n2 = (nv + BN - 1) / BN;
     const int tbeg = (n1 + n2) * part / parts, ntiles = (n1 + n2) * (part + 1) / parts;   // tiles tbeg .. ntiles - 1
 
@@ -1002,9 +1083,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
         const int32_t* cols = colring + (t & 3) * BN;
 #pragma unroll
         for (int i = 0; i < C::IPW; ++i) {
-            int32_t col = cols[rowlane + 4 * C::RPI * i];
-            if (col < 0) col = 0;
-            const uint32_t ro = (uint32_t)col * C::RB;
+            const uint32_t ro = (uint32_t)cols[rowlane + 4 * C::RPI * i] * C::RB;
             dma16(Kg, ro + kcpart, kdst0 + bo + (uint32_t)(4 * i * C::K_ISTR));
             dma16(Vg, ro + vcpart, vdst0 + bo + (uint32_t)(4 * i * C::V_ISTR));
         }
@@ -1121,54 +1200,63 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
         l_run += (ps4[0] + ps4[1]) + (ps4[2] + ps4[3]);
     };
 
-    // column ids of packed tile t: fetched into a register one iteration before they are written to
-    // LDS (slot t & 3), which happens one iteration before tile t is issued.  The global load is thus
-    // never waited for while transfers are in flight.
-    auto fetch_cols = [&](int t) -> int32_t {
-        if (t >= n1 && t < ntiles && tid < BN) {
-            const int idx = (t - n1) * BN + tid;
-            return idx < nv ? vi[idx] : -1;
+    // What a packed tile needs besides its rows goes through LDS by transfers of its own: the ids of its columns two
+    // tiles ahead (slots past the end of the list repeat the last column), the bitmap words of its masks one tile ahead.
+    // (As loads into registers they made the compiler put waits for all outstanding memory operations, the transfers of
+    // the next tile among them, into the tile loop.)
+    auto request_cols = [&](int t) {                       // column ids of packed tile t -> slot t & 3
+        if (wv == 0) {
+            int i = (t - n1) * BN + lane;
+            if (i > nv - 1) i = nv - 1;
+            dma4(vi, (uint32_t)i * 4u, colring_lds + (uint32_t)((t & 3) * BN * 4));
         }
-        return -1;
-    };
-    auto store_cols = [&](int t, int32_t c) {
-        if (t >= n1 && t < ntiles && tid < BN) colring[(t & 3) * BN + tid] = c;
     };
     auto block_at = [&](int t) -> int { return __builtin_amdgcn_readfirstlane((int)kbl[t]); };
-    // what the masks of tile t are made of (requested before tile t - 1 is multiplied)
+    // what the masks of tile t are made of
     DiagWords dw = {0u, 0u, 0u};
-    ColWords cw = {0u, 0u};
     int32_t mycol = -1;
     TileMask tm;
-    auto mask_words = [&](int t, int kb) {
+    auto mask_words = [&](int t, int kb) {                 // ahead of the transfers of tile t
         if (t < n1) dw = diag_words((const_words)obg, posw, kb * BN);
-        else { mycol = colring[(t & 3) * BN + lane]; cw = col_words(obg, posw, mycol, n1 > 0); }
+        else {
+            mycol = (t - n1) * BN + lane < nv ? colring[(t & 3) * BN + lane] : -1;
+            if (n1 > 0) {
+                const uint32_t off = (uint32_t)((col_offset(posw, mycol < 0 ? 0 : mycol) >> 5) + OB_PAD) * 4u;
+                dma4(obg, off, colbits_lds);
+                dma4(obg, off + 4u, colbits_lds + 256u);
+            }
+        }
     };
-    auto masks = [&](int t) {
-        tm = t < n1 ? diag_mask(dw, r32, g) : col_mask(cw, posw, mycol, lane);
+    auto masks_cols = [&]() {                              // once the transfers have landed
+        ColWords cw = {0u, 0u};
+        if (n1 > 0) { cw.lo = colbits[wv * 128 + lane]; cw.hi = colbits[wv * 128 + 64 + lane]; }
+        tm = col_mask(cw, posw, mycol, lane);
+        if (!rows_here) tm.act[0] = tm.act[1] = false;
+    };
+    auto masks_block = [&]() {
+        tm = diag_mask(dw, r32, g);
         if (!rows_here) tm.act[0] = tm.act[1] = false;
     };
 
-    store_cols(tbeg, fetch_cols(tbeg));
-    store_cols(tbeg + 1, fetch_cols(tbeg + 1));
-    int32_t colpre = fetch_cols(tbeg + 2);
+    if (ntiles > n1 && tbeg < ntiles && tbeg + 1 >= n1) {  // a packed tile among the first two
+        if (tbeg >= n1) request_cols(tbeg);
+        if (tbeg + 1 < ntiles) request_cols(tbeg + 1);
+        wait_transfers();
+    }
     __syncthreads();                                       // kbl and the first column ids are visible
     int kb_next = 0;                                       // key block of tile t + 1 (phase 1)
     if (tbeg < ntiles) {
         kb_next = tbeg < n1 ? block_at(tbeg) : 0;
         mask_words(tbeg, kb_next);
         if (tbeg < n1) issue_block(kb_next, tbeg); else issue_cols(tbeg);
-        masks(tbeg);
         kb_next = tbeg + 1 < n1 ? block_at(tbeg + 1) : 0;
     }
     wait_transfers();
+    if (tbeg < ntiles) { if (tbeg < n1) masks_block(); else masks_cols(); }
     __syncthreads();
 
     for (int t = tbeg; t < ntiles; ++t) {
-        if (t + 3 >= n1) {                                 // column ids only matter around phase 2
-            store_cols(t + 2, colpre);
-            colpre = fetch_cols(t + 3);
-        }
+        if (t + 2 >= n1 && t + 2 < ntiles) request_cols(t + 2);
         if (t + 1 < ntiles) {
             mask_words(t + 1, kb_next);
             if (t + 1 < n1) issue_block(kb_next, t + 1); else issue_cols(t + 1);
@@ -1176,26 +1264,39 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_bf16_kernel(Prefil
         const int kb_after = t + 2 < n1 ? (int)kbl[t + 2] : 0;
         process((t & 1) * C::TILE_BYTES, tm);
         kb_next = __builtin_amdgcn_readfirstlane(kb_after);
-        if (t + 1 < ntiles) masks(t + 1);
+        if (t + 1 < n1) masks_block();
         wait_transfers();                                  // this wave's transfers of tile t+1 have landed
+        if (t + 1 >= n1 && t + 1 < ntiles) masks_cols();
         __syncthreads();
     }
 
+    if (wv == 0) src.ahead(a, lane);                       // the next entry's place in the queue, under the stores below
     const float l_tot = l_run + xor32(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
     if (parts > 1) {
         store_part<C::DBLK>(a, (int)(info >> 16) + part, wv, lane, oacc, m_run, l_tot);
-    } else if (row_ok) {
-        T* orow = reinterpret_cast<T*>(a.out) + ((int64_t)bh * a.n_hat + (pos - row0)) * D;
+    } else if (rows_here) {
+        // A lane holds four neighbouring values of its row at a time; through LDS (32 rows of this wave in the tile
+        // buffers, which nobody reads any more) they become whole rows, 1 KB a store.  (Stored as they are, 8 bytes a
+        // lane in 32 rows, they kept a wave for 4.5-7 thousand cycles an entry.)
+        constexpr int OS = C::RB + 16;                     // LDS bytes from row to row
+        unsigned char* ow = tiles + wv * (32 * OS);
 #pragma unroll
         for (int i = 0; i < C::DBLK; ++i)
 #pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-                const int d0 = 32 * i + 8 * rq + 4 * g;
-                store_out4(orow + d0, oacc[i][4 * rq] * inv, oacc[i][4 * rq + 1] * inv,
+            for (int rq = 0; rq < 4; ++rq)
+                store_out4(reinterpret_cast<T*>(ow + r32 * OS) + 32 * i + 8 * rq + 4 * g, oacc[i][4 * rq] * inv, oacc[i][4 * rq + 1] * inv,
                            oacc[i][4 * rq + 2] * inv, oacc[i][4 * rq + 3] * inv);
-            }
-        if (a.lse && g == 0)
+        __builtin_amdgcn_wave_barrier();
+        unsigned char* og = reinterpret_cast<unsigned char*>(a.out) + ((int64_t)bh * a.n_hat + (posw - row0)) * C::RB;   // row posw may lie before the turn
+        const int cr = lane / C::DS, cs = lane % C::DS;
+#pragma unroll
+        for (int j = 0; j < 32 / C::RPI; ++j) {
+            const int r = C::RPI * j + cr;
+            const f32x4 v = *reinterpret_cast<const f32x4*>(ow + r * OS + 16 * cs);
+            if (posw + r >= row0 && posw + r < n) *reinterpret_cast<f32x4*>(og + (int64_t)r * C::RB + 16 * cs) = v;
+        }
+        if (a.lse && row_ok && g == 0)
             a.lse[(int64_t)bh * a.n_hat + (pos - row0)] =
                 l_tot > 0.f ? (m_run * sc2 + log2f(l_tot)) * 0.69314718055994531f : -INFINITY;
     }
@@ -1209,15 +1310,15 @@ static void launch_combine(const PrefillArgs& a, hipStream_t st) {
 
 template <int D>
 static size_t prefill_bf16_smem(int tab_len) {
-    return 2 * (size_t)DirectCfg<D>::TILE_BYTES + 256 * 4 + 8 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
+    return 2 * (size_t)DirectCfg<D>::TILE_BYTES + 256 * 4 + 512 * 4 + 8 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
 }
 
 template <int D>
 static hipError_t launch_prefill_bf16(const PrefillArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     const size_t smem = prefill_bf16_smem<D>(a.tab_len);
     // with events: they take the start and stop time stamps of this dispatch itself, no marker goes into the stream
-    if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
-    else hipLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), smem, st, a);
+    if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
+    else hipLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
     launch_combine<bf16_t, D>(a, st);
     return hipGetLastError();
 }
@@ -1231,8 +1332,8 @@ static size_t prefill_smem_t(int tab_len) {
 template <typename T, int D>
 static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     const size_t smem = prefill_smem_t<T, D>(a.tab_len);
-    if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_kernel<T, D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
-    else hipLaunchKernelGGL((prefill_kernel<T, D>), dim3(persistent_grid(a)), dim3(PREFILL_THREADS), smem, st, a);
+    if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_kernel<T, D>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
+    else hipLaunchKernelGGL((prefill_kernel<T, D>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
     launch_combine<T, D>(a, st);
     return hipGetLastError();
 }
