@@ -86,8 +86,7 @@ const char* ls_last_error(const ls_ctx* ctx);
  *   slash  [B,Hq,n]  slash[o] = sum_t A[t][p_t - o]        (diagonal o = query pos - key pos)
  *   vmax, smax [B,Hq,n]  the largest single entry of each line (the w^max of Alg. 2)
  *   total  [B,Hq]    sum of all entries of A (about w)
- * The softmax is causal (row t sees keys <= p_t).  With q_pos == NULL and w <= 128 all sums are
- * formed in a fixed order (bit-reproducible); otherwise the diagonal sums use fp32 atomics.
+ * The softmax is causal (row t sees keys <= p_t).  All sums are formed in a fixed order (bit-reproducible).
  */
 int ls_score(ls_ctx* ctx, const ls_shape* shape, const void* q_win, const int64_t* q_pos, const void* k,
              float* vert, float* slash, float* vmax, float* smax, float* total, void* hip_stream);

@@ -119,10 +119,19 @@ inline size_t part_floats(const ls_shape* s) {
     const size_t a = BH * s->w * nkb_of(s->n) * 2, b = BH * 8;
     return a > b ? a : b;
 }
+// Window matrix of explicit scoring positions: all heads at once up to 256 MB, at least one KV head's.
+inline size_t win_bytes_kv(const ls_shape* s) { return (size_t)(s->Hq / s->Hkv) * s->w * (size_t)s->n * 4; }
+inline size_t win_bytes(const ls_shape* s) {
+    const size_t one = win_bytes_kv(s), all = one * s->B * s->Hkv, most = 256u << 20;
+    return one > most ? one : all < most ? all : most;
+}
 size_t ws_score(const ls_shape* s, bool lines) {
     const size_t BH = (size_t)s->B * s->Hq;
     size_t b = up(part_floats(s) * 4) + up(BH * s->w * 2 * 4);
-    if (lines) b += up(2 * BH * (size_t)s->n * 2 * 4);
+    if (lines) {
+        const size_t diag = 2 * BH * (size_t)s->n * 2 * 4, win = win_bytes(s);
+        b += up(diag > win ? diag : win);
+    }
     return b;
 }
 size_t ws_select(const ls_shape* s) {
@@ -131,10 +140,15 @@ size_t ws_select(const ls_shape* s) {
 }
 inline int words_of(int64_t n) { return (int)((n + 31) / 32) + 8; }
 inline int tab_len_of(int64_t n) { return (int)(n / 64) + 4; }
+// row blocks of the turn; they start at multiples of the block
+inline int64_t row_blocks(int64_t n, int64_t n_hat) {
+    const int64_t bm = ls::prefill_block_rows(), pos0 = (n - n_hat) / bm * bm;
+    return (n - pos0 + bm - 1) / bm;
+}
 size_t ws_prefill(const ls_shape* s) {
     const size_t BH = (size_t)s->B * s->Hq;
-    const int64_t rows = s->n_hat > 0 && s->n_hat <= s->n ? s->n_hat : s->n;
-    const size_t items = BH * (size_t)(rows / 128 + 2);          // (head, row block) work items, upper bound
+    const int64_t n_hat = s->n_hat > 0 && s->n_hat <= s->n ? s->n_hat : s->n;
+    const size_t items = BH * (size_t)row_blocks(s->n, n_hat);   // (head, row block) work items
     const size_t slots = (size_t)ls::prefill_split_slots((int64_t)items);
     return up(BH * (size_t)(words_of(s->n) + 4) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(items * 4) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
            up(8 * (items + slots) * 16) + 2 * up(8 * 4) + up(slots * 8) + up(8) + up(slots * ls::prefill_slot_bytes(s->d)) + ALIGN;
@@ -212,12 +226,20 @@ int ls_score(ls_ctx* c, const ls_shape* s, const void* q_win, const int64_t* q_p
     Bump bp{c->ws, c->ws_bytes, 0};
     a.part = bp.take<float>(part_floats(s));
     a.rowstat = bp.take<float>((size_t)a.BH * a.w * 2);
-    a.spart = bp.take<float>(2 * (size_t)a.BH * (size_t)a.n * 2);
+    const int mode = (q_pos == nullptr && s->w <= 128) ? 0 : 1;
+    if (mode == 0) {
+        a.spart = bp.take<float>(2 * (size_t)a.BH * (size_t)a.n * 2);
+    } else {
+        const size_t kv = win_bytes_kv(s), left = bp.ok() && bp.cap > bp.off ? bp.cap - bp.off : 0;
+        const size_t heads = left / kv < (size_t)s->B * s->Hkv ? left / kv : (size_t)s->B * s->Hkv;
+        if (heads == 0) return fail(c, LS_EWORKSPACE, "ls_score: workspace of %zu bytes is too small", c->ws_bytes);
+        a.win_heads = (int)heads;
+        a.a_win = reinterpret_cast<float*>(bp.base + bp.off);
+    }
+    a.done = c->done;
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_score: workspace of %zu bytes is too small", c->ws_bytes);
     a.vert = vert; a.slash = slash; a.vmax = vmax; a.smax = smax; a.total = total; a.gscore = nullptr;
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_score: hipSetDevice failed");
-    const int mode = (q_pos == nullptr && s->w <= 128) ? 0 : 1;
-    if (ls::score_lines_smem(s->w, s->dtype, s->d, mode) > 160 * 1024) return fail(c, LS_ESHAPE, "ls_score: w too large for LDS");
     const hipError_t e = ls::run_score(a, s->dtype, s->d, mode, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_score: %s", hipGetErrorString(e));
     return LS_OK;
@@ -238,7 +260,6 @@ int ls_score_window(ls_ctx* c, const ls_shape* s, const void* q_win, const int64
     a.rowstat = bp.take<float>((size_t)a.BH * a.w * 2);
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_score_window: workspace of %zu bytes is too small", c->ws_bytes);
     a.a_win = a_win;
-    if (ls::score_lines_smem(s->w, s->dtype, s->d, 3) > 160 * 1024) return fail(c, LS_ESHAPE, "ls_score_window: w too large for LDS");
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_score_window: hipSetDevice failed");
     const hipError_t e = ls::run_score(a, s->dtype, s->d, 3, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_score_window: %s", hipGetErrorString(e));
@@ -341,7 +362,7 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     w.pref = bp.take<uint16_t>((size_t)BH * (tab_len + 1));
     const int bm = ls::prefill_block_rows();
     w.pos0 = (s->n - s->n_hat) / bm * bm;
-    w.nqb = (int)((s->n - w.pos0 + bm - 1) / bm);
+    w.nqb = (int)row_blocks(s->n, s->n_hat);
     w.code = LS_ESHAPE;
     if (w.nqb > 65535) return "too many row blocks";
     if (BH > 8192) return "B * Hq exceeds 8192";
@@ -449,7 +470,6 @@ int kv_compress_on(const ErrSink& fail, const char* who, int device, unsigned ch
     if (const char* m = check_shape(s, false, true, false)) return fail(LS_ESHAPE, "%s: %s", who, m);
     if (budget <= 0) return fail(LS_ESHAPE, "%s: budget must be positive", who);
     if (s->n > ls::TOPB_MAX_LEN) return fail(LS_ESHAPE, "%s: cache length %lld exceeds LS_MAX_N", who, (long long)s->n);
-    if (ls::score_lines_smem(s->w, s->dtype, s->d, 2) > 160 * 1024) return fail(LS_ESHAPE, "%s: w too large for LDS", who);
     if (!q_obs || !k || !keep_idx || !keep_cnt || (v_out && !v)) return fail(LS_EINVAL, "%s: NULL tensor", who);
     if (!aligned16(q_obs) || !aligned16(k) || !aligned16(v) || !aligned16(k_out) || !aligned16(v_out))
         return fail(LS_EINVAL, "%s: misaligned tensor", who);

@@ -51,17 +51,6 @@ struct DecCfg {
     __device__ static constexpr int vswz(int row) { return D == 128 ? 2 * (row & 7) : 2 * ((row >> 1) & 3); }
 };
 
-// Partial results are exchanged between workgroups of one launch, which may run on different XCDs, each with an L2
-// of its own: these accesses go to the memory all of them see.
-__device__ __forceinline__ void put_shared(float* p, float x, float y) {
-    __hip_atomic_store(reinterpret_cast<uint64_t*>(p), (uint64_t)__builtin_bit_cast(uint32_t, x) | ((uint64_t)__builtin_bit_cast(uint32_t, y) << 32),
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float2 get_shared(const float* p) {
-    const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return make_float2(__builtin_bit_cast(float, (uint32_t)u), __builtin_bit_cast(float, (uint32_t)(u >> 32)));
-}
-
 template <int D, int NH>
 __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(DecodeArgs a) {
     using C = DecCfg<D, NH>;
@@ -257,8 +246,8 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(DecodeArgs a) {
         }
         if (a.nsplit == 1) { finish(head, dd, m, o0, o1, l); continue; }
         float* dst = shared_part + ((int64_t)split * G + head) * PS;
-        put_shared(dst + dd, o0, o1);
-        if (dd == 0) put_shared(dst + D, m, l);
+        put_shared2(dst + dd, o0, o1);
+        if (dd == 0) put_shared2(dst + D, m, l);
     }
     if (a.nsplit == 1) return;
 
@@ -266,9 +255,8 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(DecodeArgs a) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                   // this wave's part of the result has been written
     __syncthreads();
     if (tid == 0) {
-        const uint32_t before = __hip_atomic_fetch_add(a.done + bk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last_s = before == (uint32_t)a.nsplit - 1u;
-        if (last_s) __hip_atomic_store(a.done + bk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next call
+        last_s = count_shared(a.done + bk) == (uint32_t)a.nsplit - 1u;
+        if (last_s) clear_shared(a.done + bk);                         // for the next call
     }
     __syncthreads();
     if (!last_s) return;
@@ -287,12 +275,12 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(DecodeArgs a) {
 #pragma unroll
             for (int e = 0; e < BATCH; ++e) {
                 const int s = s0 + e * subs;
-                x[e] = get_shared(src + (int64_t)(s < a.nsplit ? s : a.nsplit - 1) * G * PS);
+                x[e] = get_shared2(src + (int64_t)(s < a.nsplit ? s : a.nsplit - 1) * G * PS);
             }
         };
         fetch(sub);
         if (idx0 == 0) {
-            for (int i = tid; i < G * a.nsplit; i += DEC_THREADS) ml[i] = get_shared(shared_part + ((int64_t)(i % a.nsplit) * G + i / a.nsplit) * PS + D);
+            for (int i = tid; i < G * a.nsplit; i += DEC_THREADS) ml[i] = get_shared2(shared_part + ((int64_t)(i % a.nsplit) * G + i / a.nsplit) * PS + D);
             __syncthreads();
         }
         const float2* mh = ml + head * a.nsplit;

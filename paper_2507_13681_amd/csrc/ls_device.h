@@ -93,7 +93,13 @@ __device__ __forceinline__ void dma16(const unsigned char* gbase, uint32_t voff,
 __device__ __forceinline__ void dma16(const unsigned char* gptr, uint32_t lds) {                    // per-lane address
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(gptr) : "memory", "m0");
 }
-// The same with 4 bytes per lane, landing at lds + 4 * l.
+// A wave-uniform address, told so to the compiler (which may compute it in vector registers all the same).
+__device__ __forceinline__ const unsigned char* uniform_ptr(const void* p) {
+    const uint64_t u = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+    return reinterpret_cast<const unsigned char*>(((uint64_t)hi << 32) | lo);
+}
+// dma16 with 4 bytes per lane, landing at lds + 4 * l.
 __device__ __forceinline__ void dma4(const void* gbase, uint32_t voff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds), "v"(voff), "s"(gbase) : "memory", "m0");
 }
@@ -118,6 +124,21 @@ __device__ __forceinline__ void load_frag_tr(Frag<bf16_t>& f, const unsigned cha
     struct U { s16x4 a, b; } u = {lo, hi};
     f.v = __builtin_bit_cast(bf16x8, u);
 }
+
+// Results exchanged between workgroups of one launch, which may run on different XCDs, each with an L2 of its own: these
+// accesses go to the memory all of them see.  A writer waits for its stores (vmcnt) before it counts itself.
+__device__ __forceinline__ void put_shared(float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float get_shared(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void put_shared2(float* p, float x, float y) {
+    __hip_atomic_store(reinterpret_cast<uint64_t*>(p), (uint64_t)__builtin_bit_cast(uint32_t, x) | ((uint64_t)__builtin_bit_cast(uint32_t, y) << 32),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 get_shared2(const float* p) {
+    const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__builtin_bit_cast(float, (uint32_t)u), __builtin_bit_cast(float, (uint32_t)(u >> 32)));
+}
+__device__ __forceinline__ uint32_t count_shared(uint32_t* c) { return __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void clear_shared(uint32_t* c) { __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 __device__ __forceinline__ float to_float(bf16_t x) { return bf2f(x.bits); }
 __device__ __forceinline__ float to_float(float x) { return x; }

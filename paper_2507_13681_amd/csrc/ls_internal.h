@@ -13,12 +13,15 @@ struct ScoreArgs {
     int64_t n;
     int w, G, Hq, Hkv, B, BH, nkb;
     float scale_log2e;
-    float* part;              // [BH*w][nkb][2]   per key block max / sum
+    float* part;              // [B*Hkv][nkb][G*w][2] per key block max / sum of every row; later the shares of the totals
     float* rowstat;           // [BH*w][2]        row max, 1 / row sum
     float* spart;             // [2][BH][n][2]    diagonal partial sum / max by key-block parity
     float *vert, *slash, *vmax, *smax, *total;
     float* gscore;            // [B*Hkv][n]       group-summed column sums (retention score)
-    float* a_win;             // [BH][w][n]       the window matrix itself (mode 3)
+    float* a_win;             // [heads][w][n]    the window matrix (mode 3), or that of the heads from bh_first on (mode 1)
+    int bk0, bh_first;        // first KV head / query head of a lines_kernel launch
+    int win_heads;            // KV heads whose matrix the buffer takes (mode 1)
+    uint32_t* done;           // [BH] workgroups finished per head; zero between calls
 };
 
 constexpr int SELECT_HEAD_LINES = 1024;   // lines at the front of each sorted list whose weight and maximum are stored in order
@@ -150,7 +153,6 @@ hipError_t run_decode(const DecodeArgs& a, int d, hipStream_t st);
 size_t decode_smem_bytes(int d, int G, int nsplit);
 size_t decode_part_floats(int d);                                   // floats of one partial result
 void decode_split(int BK, int cap, int T, int* nsplit, int* chunk);   // chunk: 32-key tiles per workgroup
-size_t score_lines_smem(int w, int dtype, int d, int mode);
 // Union of two selections per head (the accumulated line set of Alg. 1): lists a and b in, ascending unique list out.
 struct MergeArgs {
     int64_t n;

@@ -1361,7 +1361,7 @@ hipError_t launch_plan(const PlanArgs& a, int BH, hipStream_t st) {
 }
 
 int prefill_block_rows() { return BM; }
-int prefill_split_slots(int64_t items) { return items > SPLIT_ITEMS ? 0 : items * 16 < SPLIT_SLOTS ? (int)items * 16 : SPLIT_SLOTS; }
+int prefill_split_slots(int64_t items) { return items > SPLIT_ITEMS ? 0 : items * 12 < SPLIT_SLOTS ? (int)items * 12 : SPLIT_SLOTS; }
 size_t prefill_slot_bytes(int d) { return (size_t)BM * d * 4 + BM * 2 * 4; }
 
 hipError_t launch_sched(const SchedArgs& a, hipStream_t st) {

@@ -10,345 +10,436 @@
 //   merge_kernel   per row: global max m and 1/l;
 //   lines_kernel   recomputes the logits, forms A = exp2(x - m) / l, and reduces it
 //                  - over rows, in registers, to column sums / maxima (written once, in order);
-//                  - over diagonals through an LDS copy of the 128-key slab of A, one thread per
-//                    diagonal adding the rows in fixed order; a diagonal crosses at most two key
-//                    blocks, whose two partial results finish_kernel adds.
+//                  - over diagonals through an LDS copy of 32 rows of the 128-key slab at a time, one
+//                    thread per diagonal adding the rows in fixed order; a diagonal crosses at most two
+//                    key blocks, whose two partial results finish_kernel adds.
+// With explicit scoring positions (q_pos given) the diagonals of a slab are not a contiguous range: the
+// matrix A is then written out, for as many KV heads at a time as the workspace takes, and
+// diagonals_kernel adds each diagonal's cells in row order.
 // Everything is summed in a fixed order, so results are bit-reproducible from run to run.
-// With explicit scoring positions (q_pos given) the diagonals of a slab are not a contiguous
-// range; that path uses fp32 atomics on zero-initialised outputs instead.
 //
-// Tile products run on 32x32 MFMA with K fragments held in registers (each wave owns 32 keys of
-// the block and re-uses them for every query head of the KV group and every 32-row group).
+// Tile products run on 32x32 MFMA with K fragments held in registers: each wave owns 32 keys of a block
+// and meets every query head of the KV group and every 32-row group with them.  Those chunks of 32 query rows
+// come through LDS by global -> LDS transfers, two buffers, one barrier per chunk.  K rows go through LDS on
+// their way to the registers as well: read straight from global memory a fragment load touches 32 rows with
+// 32 bytes each.  What bounds the passes is vector instruction issue (two thirds of all cycles at 131072 keys,
+// 4 cycles each, about 130 and 180 instructions per wave and chunk in stats and lines): what counts is few of
+// them (no masks where every row sees every key, no address arithmetic in the diagonal sums), and little enough
+// LDS (33 to 38 KB) for four workgroups per CU.  Whole windows of 64 rows in LDS (100 KB, one workgroup per CU),
+// as one step: 131072 keys 234 + 832 us, now 196 + 303; retention score, 16384 keys, B 4: 79 + 102 us, now 38 + 42.
+#include <type_traits>
+
 #include "ls_device.h"
 #include "ls_internal.h"
 
 namespace ls {
 
-constexpr int SB = 128;           // keys per workgroup
+constexpr int SB = 128;           // keys per block
 constexpr int SCORE_THREADS = 256;
+constexpr int SLAB = 33;          // floats per diagonal of the LDS slab: 32 rows, odd so that neighbouring diagonals lie in
+constexpr int SLAB_DIAGS = SB + 31;   // neighbouring banks; key k of row r lies on diagonal k - r + 31.  The cells no key falls into stay zero
+constexpr int SLAB_BYTES = (SLAB_DIAGS * SLAB * 4 + 15) / 16 * 16;
+constexpr int RED_CHUNKS = 8;     // chunks whose wave results stats_kernel keeps before merging them
 
+// 32 rows of T x D in LDS, row-major, the 8-element fragment units of a row XOR-swizzled with the row so that
+// the rows one fragment read touches fall into different banks; filled by transfers of 1 KB.
 template <typename T, int D>
-__device__ __forceinline__ void load_k_frags(Frag<T> (&kf)[D / 16], const T* Kg, int64_t key, int64_t n, int g) {
-    if (key < n) {
-#pragma unroll
-        for (int c = 0; c < D / 16; ++c) load_frag(kf[c], Kg + key * D + 16 * c + 8 * g);
-    } else {
-#pragma unroll
-        for (int c = 0; c < D / 16; ++c) zero_frag(kf[c]);
-    }
-}
-
-template <typename T, int D>
-__device__ __forceinline__ void load_q_frags(Frag<T> (&qf)[D / 16], const T* Qh, int row, int w, int g) {
-    if (row < w) {
-#pragma unroll
-        for (int c = 0; c < D / 16; ++c) load_frag(qf[c], Qh + (int64_t)row * D + 16 * c + 8 * g);
-    } else {
-#pragma unroll
-        for (int c = 0; c < D / 16; ++c) zero_frag(qf[c]);
-    }
-}
-
-// ---- the window's queries of one head, staged in LDS ---------------------------------------------
-// Every workgroup of a KV head needs the same few KB of Q for each of its G heads; read straight from
-// global memory by each wave (as the K fragments are) those reads all hit the same handful of L2 lines and
-// took half of both passes.  One copy per workgroup and head goes through LDS instead: row-major, the
-// 8-element fragment units of a row XOR-swizzled with the row so that the 16 rows one fragment read touches
-// fall into different banks.  The next head's units are fetched into registers while the current head is
-// multiplied.
-template <typename T, int D>
-struct QStage {
-    static constexpr int FB = 8 * Elem<T>::bytes;         // bytes of one fragment unit (8 elements)
+struct RowTile {
+    static constexpr int FB = 8 * Elem<T>::bytes;         // bytes of one fragment unit
     static constexpr int UPR = D / 8;                     // units per row
-    static constexpr int RBYTES = D * Elem<T>::bytes;
-    static constexpr int PF = 4;                          // units per thread held in registers
-    struct Unit { f32x4 v[FB / 16]; };
-    __device__ static void fetch(Unit (&u)[PF], const T* Qh, int w, int wpad, int tid) {
-#pragma unroll
-        for (int j = 0; j < PF; ++j) {
-            const int i = tid + SCORE_THREADS * j, row = i / UPR, uu = i % UPR;
-            const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int h = 0; h < FB / 16; ++h)
-                u[j].v[h] = (i < wpad * UPR && row < w) ? reinterpret_cast<const f32x4*>(Qh + (int64_t)row * D + 8 * uu)[h] : z;
+    static constexpr int RB = D * Elem<T>::bytes;         // bytes per row
+    static constexpr int BYTES = 32 * RB;
+    static constexpr int SPR = RB / 16;                   // 16-byte slots per row
+    static constexpr int RPI = 64 / SPR > 0 ? 64 / SPR : 1;   // rows per transfer
+    static constexpr int NI = BYTES / 1024;               // transfers
+    static_assert(SPR <= 64, "a row fits one transfer");
+    // transfers first, first + step, ... of the tile; row r of it comes from src + min(r, rows - 1) * RB
+    __device__ static void fetch(const unsigned char* src, int rows, uint32_t lds, int lane, int first, int step) {
+        const int tr = lane / SPR, sl = lane % SPR;
+        src = uniform_ptr(src);
+        lds = (uint32_t)__builtin_amdgcn_readfirstlane((int)lds);
+        for (int i = first; i < NI; i += step) {
+            const int row = RPI * i + tr;
+            const int u = FB == 16 ? sl ^ (row & (UPR - 1)) : 2 * ((sl >> 1) ^ (row & (UPR - 1))) + (sl & 1);
+            dma16(src, (uint32_t)((row < rows ? row : rows - 1) * RB + 16 * u), lds + (uint32_t)(i * 1024));
         }
     }
-    __device__ static unsigned char* slot(unsigned char* qs, int row, int uu) {
-        return qs + row * RBYTES + FB * (uu ^ (row & (UPR - 1)));
-    }
-    // registers -> LDS; rows beyond the register budget (long windows) are copied directly
-    __device__ static void commit(unsigned char* qs, const Unit (&u)[PF], const T* Qh, int w, int wpad, int tid) {
+    __device__ static void frags(Frag<T> (&f)[D / 16], const unsigned char* tile, int row, int g) {
 #pragma unroll
-        for (int j = 0; j < PF; ++j) {
-            const int i = tid + SCORE_THREADS * j, row = i / UPR, uu = i % UPR;
-            if (i < wpad * UPR) {
-#pragma unroll
-                for (int h = 0; h < FB / 16; ++h) reinterpret_cast<f32x4*>(slot(qs, row, uu))[h] = u[j].v[h];
-            }
-        }
-        for (int i = tid + SCORE_THREADS * PF; i < wpad * UPR; i += SCORE_THREADS) {
-            const int row = i / UPR, uu = i % UPR;
-            const f32x4 z = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int h = 0; h < FB / 16; ++h)
-                reinterpret_cast<f32x4*>(slot(qs, row, uu))[h] = row < w ? reinterpret_cast<const f32x4*>(Qh + (int64_t)row * D + 8 * uu)[h] : z;
-        }
-    }
-    __device__ static void frags(Frag<T> (&qf)[D / 16], const unsigned char* qs, int row, int g) {
-#pragma unroll
-        for (int c = 0; c < D / 16; ++c) load_frag(qf[c], qs + row * RBYTES + FB * ((2 * c + g) ^ (row & (UPR - 1))));
+        for (int c = 0; c < D / 16; ++c) load_frag(f[c], tile + row * RB + FB * ((2 * c + g) ^ (row & (UPR - 1))));
     }
 };
 
+__device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char*)p; }
+
+// The rows of a KV head's G windows in chunks of up to 32: chunk c covers the rows start .. start + cnt - 1 of the
+// G * w rows, which lie one after the other in memory.  A window whose length divides 32 shares a chunk with its
+// neighbours (`packed`); otherwise a chunk stays inside one head's window.
+struct Chunk { int start, cnt, t0; };         // t0: window row of the first one (row r of the chunk: (t0 + r) % w)
+struct Chunks {
+    int w, rows, rgs, count;
+    __device__ __forceinline__ Chunks(int w_, int G, bool packed) : w(w_), rows(G * w_), rgs(packed ? 0 : (w_ + 31) / 32), count(packed ? (G * w_ + 31) / 32 : G * ((w_ + 31) / 32)) {}
+    __device__ __forceinline__ Chunk at(int c) const {
+        if (rgs == 0) { const int s = 32 * c; return {s, rows - s < 32 ? rows - s : 32, 0}; }
+        const int h = c / rgs, r0 = 32 * (c - h * rgs);
+        return {h * w + r0, w - r0 < 32 ? w - r0 : 32, r0};
+    }
+};
+__host__ __device__ static bool packs(int w) { return w == 8 || w == 16; }
+
+// This wave's K fragments of 32 keys, through its own 32 rows of LDS (keys beyond the context repeat the last one; every
+// row's mask excludes them)
+template <typename T, int D>
+__device__ __forceinline__ void k_frags(Frag<T> (&kf)[D / 16], const T* Kg, int64_t key0, int64_t n, unsigned char* stage, int lane) {
+    using RT = RowTile<T, D>;
+    const int64_t left = n - key0;
+    const int64_t k0 = left > 0 ? key0 : n - 1;
+    RT::fetch(reinterpret_cast<const unsigned char*>(Kg + k0 * D), left > 32 ? 32 : left > 0 ? (int)left : 1, lds_address(stage), lane, 0, 1);
+    wait_transfers();
+    RT::frags(kf, stage, lane & 31, lane >> 5);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the stage may be filled again
+}
+
+// dynamic LDS ahead of the per-row arrays: the K stage, and what later takes its place
+template <typename T, int D>
+__host__ __device__ constexpr int stats_front() {
+    using RT = RowTile<T, D>;
+    return 4 * RT::BYTES > 2 * RT::BYTES + RED_CHUNKS * 1024 ? 4 * RT::BYTES : 2 * RT::BYTES + RED_CHUNKS * 1024;
+}
+template <typename T, int D>
+__host__ __device__ constexpr int lines_front(int mode) {
+    using RT = RowTile<T, D>;
+    return mode != 0 || 2 * RT::BYTES > SLAB_BYTES ? 4 * RT::BYTES : 2 * RT::BYTES + SLAB_BYTES;
+}
+// the larger / the sum of this lane's and lane ^ 32's value
+__device__ __forceinline__ float halves_max(float x) {
+    const auto b = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+    return fmaxf(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
+}
+__device__ __forceinline__ float halves_sum(float x) {
+    const auto b = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+    return __builtin_bit_cast(float, (uint32_t)b[0]) + __builtin_bit_cast(float, (uint32_t)b[1]);
+}
+
+// window row t's position in the context
+__device__ __forceinline__ int position_of(const ScoreArgs& a, int t) {
+    int64_t p = a.q_pos ? a.q_pos[t] : a.n - a.w + t;
+    if (p > a.n - 1) p = a.n - 1;                          // positions outside the context are clipped
+    return (int)(p < -1 ? -1 : p);
+}
+
 // ---- pass 1: per (row, key block) max and sum of exp2 -----------------------------------------
-// grid (nkb, B*Hkv), dynamic LDS: the staged Q of one head.  part[(bh*w + row)*nkb + kb] = {max, sum}.
+// grid (nkb, B*Hkv, shares of the G heads).  part[(bk * nkb + kb) * G w + row] = {max, sum} over the 128 keys of block kb.
 template <typename T, int D>
 __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void stats_kernel(ScoreArgs a) {
-    using QS = QStage<T, D>;
+    using RT = RowTile<T, D>;
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char* qs = smem;                              // [wpad][D] staged queries
-    __shared__ float red[2][4][32][2];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r32 = lane & 31, g = lane >> 5;
+    unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
+    unsigned char* qs = smem;                              // [2] chunks of queries and
+    float2 (*red)[4][32] = reinterpret_cast<float2 (*)[4][32]>(smem + 2 * RT::BYTES);   // [RED_CHUNKS] results of the waves
+    int32_t* pos = reinterpret_cast<int32_t*>(smem + stats_front<T, D>());              // [w]
+    const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = blockIdx.x, bk = blockIdx.y;
     const int b = bk / a.Hkv, kvh = bk % a.Hkv;
     const int64_t n = a.n;
     const T* Kg = reinterpret_cast<const T*>(a.k) + (int64_t)bk * n * D;
-    const int64_t key0 = (int64_t)kb * SB + 32 * wv;
-    const int wpad = ((a.w + 31) / 32) * 32;
-    const int rgs = wpad / 32;
-    const int bh0 = b * a.Hq + kvh * a.G;
-    const T* Q0 = reinterpret_cast<const T*>(a.q) + (int64_t)bh0 * a.w * D;
-    typename QS::Unit qu[QS::PF];
-    QS::fetch(qu, Q0, a.w, wpad, tid);
+    const unsigned char* Q0 = reinterpret_cast<const unsigned char*>(a.q) + (int64_t)(b * a.Hq + kvh * a.G) * a.w * RT::RB;
+    const Chunks ch(a.w, a.G, packs(a.w));
+    const int c0 = ch.count / (int)gridDim.z * (int)blockIdx.z, c1 = c0 + ch.count / (int)gridDim.z;
+    const uint32_t qs_lds = lds_address(qs);
+    auto fetch = [&](int c) {
+        const Chunk k = ch.at(c);
+        RT::fetch(Q0 + (int64_t)k.start * RT::RB, k.cnt, qs_lds + (uint32_t)((c & 1) * RT::BYTES), lane, wv, 4);
+    };
+    for (int t = tid; t < a.w; t += SCORE_THREADS) pos[t] = position_of(a, t);
     Frag<T> kf[D / 16];
-    load_k_frags<T, D>(kf, Kg, key0 + r32, n, g);
+    k_frags<T, D>(kf, Kg, (int64_t)kb * SB + 32 * wv, n, kst + wv * RT::BYTES, lane);
+    __syncthreads();
+    fetch(c0);
+    if (c0 + 1 < c1) fetch(c0 + 1);
     // every key of the block is visible to every row of a contiguous window: no masks (all but the last blocks)
-    const bool open = a.q_pos == nullptr && (int64_t)kb * SB + SB - 1 <= n - a.w;
-    int it = 0;
-    for (int gq = 0; gq < a.G; ++gq) {
-        const int bh = bh0 + gq;
-        const T* Qh = Q0 + (int64_t)gq * a.w * D;
-        lds_barrier();                                     // the previous head's fragments have been read
-        QS::commit(qs, qu, Qh, a.w, wpad, tid);
-        lds_barrier();
-        if (gq + 1 < a.G) QS::fetch(qu, Qh + (int64_t)a.w * D, a.w, wpad, tid);
-        for (int rg = 0; rg < rgs; ++rg, ++it) {
-            const int row = 32 * rg + r32;
+    const bool open = a.q_pos == nullptr && (int64_t)(kb + 1) * SB - 1 <= n - a.w;
+    const int rows = a.G * a.w;
+    wait_transfers();
+    __syncthreads();
+    int first = c0;                                        // first chunk whose wave results are still in `red`
+    for (int c = c0; c < c1; ++c) {
+        const Chunk k = ch.at(c);
+        f32x16 s;
+        {
             Frag<T> qf[D / 16];
-            QS::frags(qf, qs, row, g);
-            f32x16 s;
+            RT::frags(qf, qs + (c & 1) * RT::BYTES, r32, g);
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-            for (int c = 0; c < D / 16; ++c) mma(s, kf[c], qf[c]);   // s[r] = <k_{8(r/4)+4g+r%4}, q_row>
-            float mx = -INFINITY;
-            if (open && row < a.w) {
+            for (int cc = 0; cc < D / 16; ++cc) mma(s, kf[cc], qf[cc]);      // s[r] = <k_{8(r/4)+4g+r%4}, q_row>
+        }
+        float mx = -INFINITY;
+        if (open) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) { s[r] *= a.scale_log2e; mx = fmaxf(mx, s[r]); }
-            } else {
-                int64_t p = (row < a.w) ? (a.q_pos ? a.q_pos[row] : n - a.w + row) : -1;
-                if (p > n - 1) p = n - 1;                  // positions outside the context are clipped
-                int64_t lim64 = p - key0 - 4 * g;          // register r holds key key0 + 4g + 8(r/4) + r%4
-                const int lim = lim64 < -1 ? -1 : (lim64 > 64 ? 64 : (int)lim64);
+            for (int r = 0; r < 16; ++r) { s[r] *= a.scale_log2e; mx = fmaxf(mx, s[r]); }
+        } else {
+            int t = k.t0 + r32;
+            if (ch.rgs == 0) t &= a.w - 1;                 // packed windows: w is a power of two
+            const int p = t < a.w ? pos[t] : -1;
+            const int64_t lim64 = (int64_t)p - ((int64_t)kb * SB + 32 * wv) - 4 * g;      // register r holds key 4g + 8(r/4) + r%4
+            const int lim = lim64 < -1 ? -1 : (lim64 > 64 ? 64 : (int)lim64);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float x = (8 * (r >> 2) + (r & 3) <= lim) ? s[r] * a.scale_log2e : -INFINITY;
-                    s[r] = x;
-                    mx = fmaxf(mx, x);
-                }
+            for (int r = 0; r < 16; ++r) {
+                const float x = (8 * (r >> 2) + (r & 3) <= lim) ? s[r] * a.scale_log2e : -INFINITY;
+                s[r] = x;
+                mx = fmaxf(mx, x);
             }
-            mx = fmaxf(mx, xor32(mx));
-            const float ms = (mx == -INFINITY) ? 0.f : mx;
-            float sum = 0.f;
+        }
+        mx = halves_max(mx);
+        const float ms = (mx == -INFINITY) ? 0.f : mx;
+        float sum = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sum += fast_exp2(s[r] - ms);
-            sum += xor32(sum);
-            float (*rb)[32][2] = red[it & 1];              // two buffers: one barrier per iteration
-            if (g == 0) { rb[wv][r32][0] = mx; rb[wv][r32][1] = sum; }
-            lds_barrier();
-            if (wv == 0 && g == 0 && row < a.w) {
+        for (int r = 0; r < 16; ++r) sum += fast_exp2(s[r] - ms);
+        sum = halves_sum(sum);
+        if (g == 0) red[c - first][wv][r32] = make_float2(mx, sum);
+        wait_transfers();                                  // chunk c + 1
+        __syncthreads();
+        if (c + 2 < c1) fetch(c + 2);
+        if (c - first == RED_CHUNKS - 1 || c == c1 - 1) {
+            for (int i = tid; i < (c - first + 1) * 32; i += SCORE_THREADS) {
+                const int r = i & 31, cc = i >> 5;
+                const Chunk kk = ch.at(first + cc);
+                if (r >= kk.cnt) continue;
+                float2 v[4];
                 float M = -INFINITY;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) M = fmaxf(M, rb[i][r32][0]);
+                for (int w4 = 0; w4 < 4; ++w4) { v[w4] = red[cc][w4][r]; M = fmaxf(M, v[w4].x); }
                 const float Ms = (M == -INFINITY) ? 0.f : M;
                 float L = 0.f;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) L += rb[i][r32][1] * fast_exp2(rb[i][r32][0] - Ms);
-                float* dst = a.part + (((int64_t)bh * a.w + row) * a.nkb + kb) * 2;
-                dst[0] = M; dst[1] = L;
+                for (int w4 = 0; w4 < 4; ++w4) L += v[w4].y * fast_exp2(v[w4].x - Ms);
+                reinterpret_cast<float2*>(a.part)[((int64_t)bk * a.nkb + kb) * rows + kk.start + r] = make_float2(M, L);
             }
+            first = c + 1;
+            if (first < c1) __syncthreads();         // `red` is written again
         }
     }
 }
 
-// ---- merge: one wave per row; lanes stride over the key blocks, then a fixed butterfly ------------
-__global__ __launch_bounds__(256) void merge_kernel(ScoreArgs a, int rows) {
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= rows) return;
-    const float* p = a.part + (int64_t)row * a.nkb * 2;
-    float M = -INFINITY;
-    for (int kb = lane; kb < a.nkb; kb += 64) M = fmaxf(M, p[2 * kb]);
+// ---- merge: sixteen rows per workgroup; 64 threads of a row stride over the key blocks, then a fixed butterfly ----
+// grid (rows of a KV head / 16, B*Hkv).  Bound by the reads of `part`: the threads of sixteen neighbouring rows read 128
+// contiguous bytes (a wave per two rows, 16 bytes at a time: 25 us at 131072 keys).
+__global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
+    __shared__ float x[64][17];
+    const int rows = a.G * a.w, bk = blockIdx.y;
+    const int row = blockIdx.x * 16 + (threadIdx.x & 15), k0 = threadIdx.x >> 4;           // as a reader of `part`
+    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;                                // as a lane of row wv
+    const float2* p = reinterpret_cast<const float2*>(a.part) + (int64_t)bk * a.nkb * rows + (row < rows ? row : rows - 1);
+    constexpr int KEEP = 4;                                // values a thread keeps from the first look (contexts up to 32768)
+    float2 v[KEEP];
+    float M = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) {
+        const int kb = k0 + 64 * i;
+        v[i] = make_float2(-INFINITY, 0.f);
+        if (kb < a.nkb) v[i] = p[(int64_t)kb * rows];
+    }
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i) M = fmaxf(M, v[i].x);
+#pragma unroll 4
+    for (int kb = k0 + 64 * KEEP; kb < a.nkb; kb += 64) M = fmaxf(M, p[(int64_t)kb * rows].x);
+    x[k0][threadIdx.x & 15] = M;
+    __syncthreads();
+    M = x[lane][wv];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
-    float L = 0.f;
-    for (int kb = lane; kb < a.nkb; kb += 64) {
-        const float m = p[2 * kb];
-        if (m != -INFINITY) L += p[2 * kb + 1] * fast_exp2(m - M);
+    __syncthreads();
+    if (lane == 0) x[0][wv] = M;
+    __syncthreads();
+    const float Mr = x[0][threadIdx.x & 15];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < KEEP; ++i)
+        if (v[i].x != -INFINITY) L += v[i].y * fast_exp2(v[i].x - Mr);
+#pragma unroll 4
+    for (int kb = k0 + 64 * KEEP; kb < a.nkb; kb += 64) {
+        const float2 u = p[(int64_t)kb * rows];
+        if (u.x != -INFINITY) L += u.y * fast_exp2(u.x - Mr);
     }
+    x[k0][threadIdx.x & 15] = L;
+    __syncthreads();
+    L = x[lane][wv];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off, 64);
-    if (lane == 0) {
-        a.rowstat[2 * row] = M;
-        a.rowstat[2 * row + 1] = L > 0.f ? 1.0f / L : 0.f;
-    }
+    if (lane == 0 && blockIdx.x * 16 + wv < rows)
+        reinterpret_cast<float2*>(a.rowstat)[(int64_t)bk * rows + blockIdx.x * 16 + wv] = make_float2(M, L > 0.f ? 1.0f / L : 0.f);
 }
 
 // ---- pass 2: line sums ------------------------------------------------------------------------
-// grid (nkb, B*Hkv), dynamic LDS: A slab [wpad][SB + 1] floats + row stats [wpad][2] + row limits [wpad] +
-// the staged Q of one head.
+// grid (nkb, KV heads from a.bk0 on, shares of the G heads; one share in mode 2)
 // MODE 0: vert/vmax per head + diagonal partials (contiguous window, q_pos == NULL)
-// MODE 1: vert/vmax per head + diagonals through atomics (explicit q_pos)
+// MODE 1: vert/vmax per head + the matrix A of these KV heads, [heads][w][n], zero beyond each row's position
 // MODE 2: column sums only, summed over the G heads of the KV head (retention score)
-// MODE 3: no sums at all: the matrix A itself is written, [BH][w][n], zero beyond each row's position
+// MODE 3: the matrix A only
 template <typename T, int D, int MODE>
-__global__ __launch_bounds__(SCORE_THREADS) void lines_kernel(ScoreArgs a) {
-    using QS = QStage<T, D>;
+__global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void lines_kernel(ScoreArgs a) {
+    using RT = RowTile<T, D>;
     extern __shared__ __align__(16) unsigned char smem[];
-    const int wpad = ((a.w + 31) / 32) * 32;
-    float* slab = reinterpret_cast<float*>(smem);                  // [wpad][SB+1], MODE 0 only
-    float* rst = slab + (MODE == 0 ? (size_t)wpad * (SB + 1) : 0); // [wpad][2], 16-byte aligned (wpad % 32 == 0)
-    int32_t* ql = reinterpret_cast<int32_t*>(rst + 2 * wpad);      // [wpad] last visible key of a row, relative to the block
-    unsigned char* qs = reinterpret_cast<unsigned char*>(ql + wpad);   // [wpad][D] staged queries
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, r32 = lane & 31, g = lane >> 5;
-    const int kb = blockIdx.x, bk = blockIdx.y;
+    unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
+    float* slab = reinterpret_cast<float*>(smem);          // [SLAB_DIAGS][SLAB] A by diagonals (MODE 0) and
+    unsigned char* qs = smem + (MODE == 0 ? SLAB_BYTES : 0);           // [2] chunks of queries
+    float* rst = reinterpret_cast<float*>(smem + lines_front<T, D>(MODE));   // [2][32][2] max and 1 / sum of the chunks' rows
+    int32_t* ql = reinterpret_cast<int32_t*>(rst + 128);   // [w] last visible key of a row, relative to the block
+    const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kb = blockIdx.x, bk = a.bk0 + blockIdx.y;
     const int b = bk / a.Hkv, kvh = bk % a.Hkv;
     const int64_t n = a.n;
     const T* Kg = reinterpret_cast<const T*>(a.k) + (int64_t)bk * n * D;
     const int64_t blk0 = (int64_t)kb * SB;
-    const int64_t mykey = blk0 + 32 * wv + r32;
-    const int klocal = 32 * wv + r32;
+    const int klocal = 32 * wv + r32;                      // this lane's key in the block
+    const int64_t mykey = blk0 + klocal;
     const int bh0 = b * a.Hq + kvh * a.G;
-    const T* Q0 = reinterpret_cast<const T*>(a.q) + (int64_t)bh0 * a.w * D;
-    typename QS::Unit qu[QS::PF];
-    QS::fetch(qu, Q0, a.w, wpad, tid);
-    float rs_m = tid < a.w ? a.rowstat[2 * ((int64_t)bh0 * a.w + tid)] : 0.f;        // wpad <= 256 = one row per thread
-    float rs_il = tid < a.w ? a.rowstat[2 * ((int64_t)bh0 * a.w + tid) + 1] : 0.f;
-    Frag<T> kf[D / 16];
-    load_k_frags<T, D>(kf, Kg, mykey, n, g);
-    for (int i = tid; i < wpad; i += SCORE_THREADS) {
-        int64_t p = (i < a.w) ? (a.q_pos ? a.q_pos[i] : n - a.w + i) : -1;
-        if (p > n - 1) p = n - 1;                          // positions outside the context are clipped
-        const int64_t rel = p - blk0;                      // key klocal of the block is visible to row i iff klocal <= rel
-        ql[i] = rel < -1 ? -1 : (rel > SB ? SB : (int32_t)rel);
+    const unsigned char* Q0 = reinterpret_cast<const unsigned char*>(a.q) + (int64_t)bh0 * a.w * RT::RB;
+    const float* st0 = a.rowstat + 2 * (int64_t)bh0 * a.w;
+    const bool packed = MODE == 2 && packs(a.w);
+    const Chunks ch(a.w, a.G, packed);
+    const int c0 = ch.count / (int)gridDim.z * (int)blockIdx.z, c1 = c0 + ch.count / (int)gridDim.z;
+    const uint32_t qs_lds = lds_address(qs), rst_lds = lds_address(rst);
+    auto fetch = [&](int c) {
+        const Chunk k = ch.at(c);
+        RT::fetch(Q0 + (int64_t)k.start * RT::RB, k.cnt, qs_lds + (uint32_t)((c & 1) * RT::BYTES), lane, wv, 4);
+        if (wv == 3) dma4(uniform_ptr(st0), (uint32_t)(8 * (k.start + ((lane >> 1) < k.cnt ? lane >> 1 : k.cnt - 1)) + 4 * (lane & 1)), (uint32_t)__builtin_amdgcn_readfirstlane((int)(rst_lds + (uint32_t)((c & 1) * 256))));
+    };
+    for (int t = tid; t < a.w; t += SCORE_THREADS) {
+        const int64_t rel = position_of(a, t) - blk0;      // key klocal of the block is visible to row t iff klocal <= rel
+        ql[t] = rel < -1 ? -1 : (rel > SB ? SB : (int32_t)rel);
     }
+    Frag<T> kf[D / 16];
+    k_frags<T, D>(kf, Kg, blk0 + 32 * wv, n, kst + wv * RT::BYTES, lane);
+    __syncthreads();
+    fetch(c0);
+    if (c0 + 1 < c1) fetch(c0 + 1);
+    if (MODE == 0) for (int i = tid; i < SLAB_DIAGS * SLAB; i += SCORE_THREADS) slab[i] = 0.f;
     // every key of the block is visible to every row of a contiguous window (all but the last blocks)
     const bool open = a.q_pos == nullptr && blk0 + SB - 1 <= n - a.w;
-    const int rgs = wpad / 32;
-    float gsum = 0.f;                                              // MODE 2 accumulator over heads
-    for (int gq = 0; gq < a.G; ++gq) {
-        const int bh = bh0 + gq;
-        const T* Qh = Q0 + (int64_t)gq * a.w * D;
-        lds_barrier();                                             // slab / rst / staged Q free again
-        if (tid < wpad) { rst[2 * tid] = rs_m; rst[2 * tid + 1] = rs_il; }
-        QS::commit(qs, qu, Qh, a.w, wpad, tid);
-        lds_barrier();
-        // the next head's row statistics and queries are requested before this head's results are stored: a load
-        // issued after a store would not return before the store's round trip has ended (one in-order counter)
-        if (gq + 1 < a.G) {
-            rs_m = tid < a.w ? a.rowstat[2 * ((int64_t)(bh + 1) * a.w + tid)] : 0.f;
-            rs_il = tid < a.w ? a.rowstat[2 * ((int64_t)(bh + 1) * a.w + tid) + 1] : 0.f;
-            QS::fetch(qu, Qh + (int64_t)a.w * D, a.w, wpad, tid);
-        }
-        float vsum = 0.f, vmx = 0.f;
-        for (int rg = 0; rg < rgs; ++rg) {
+    const int64_t omin = n - a.w - (blk0 + SB - 1);        // MODE 0: this thread adds diagonal omin + tid of the slab (at most 255, w <= 128)
+    float gsum = 0.f, vsum = 0.f, vmx = 0.f, dsum = 0.f, dmax = 0.f;
+    wait_transfers();
+    __syncthreads();
+    for (int c = c0; c < c1; ++c) {
+        const Chunk k = ch.at(c);
+        const int bh = bh0 + k.start / a.w;                // head of the chunk (of its first row when packed)
+        const float* rs = rst + (c & 1) * 64;
+        f32x16 s;
+        {
             Frag<T> qf[D / 16];
-            QS::frags(qf, qs, 32 * rg + r32, g);
-            f32x16 s;
+            RT::frags(qf, qs + (c & 1) * RT::BYTES, r32, g);
 #pragma unroll
             for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-            for (int c = 0; c < D / 16; ++c) mma(s, qf[c], kf[c]);   // s[r] = <q_{8(r/4)+4g+r%4}, k_lane>
-            float ps = 0.f, pm = 0.f;
+            for (int cc = 0; cc < D / 16; ++cc) mma(s, qf[cc], kf[cc]);      // s[r] = <q_{8(r/4)+4g+r%4}, k_lane>
+        }
+        float ps = 0.f, pm = 0.f;
+        // MASKED: there are rows that do not exist (the last one is repeated) or keys that a row does not see
+        auto rows = [&](auto MASKED) {
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const int row0 = 32 * rg + 8 * q4 + 4 * g;         // registers 4*q4 .. 4*q4+3 hold rows row0 .. row0+3
-                const f32x4 st0 = reinterpret_cast<const f32x4*>(rst + 2 * row0)[0];     // m, 1/l of rows row0, row0+1
-                const f32x4 st1 = reinterpret_cast<const f32x4*>(rst + 2 * row0)[1];     // ... row0+2, row0+3
-                const float mm[4] = {st0.x, st0.z, st1.x, st1.z}, il[4] = {st0.y, st0.w, st1.y, st1.w};
-                int32_t lim[4] = {SB, SB, SB, SB};
-                if (!open) {
-                    typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
-                    const i32x4 l4 = *reinterpret_cast<const i32x4*>(ql + row0);
-                    lim[0] = l4.x; lim[1] = l4.y; lim[2] = l4.z; lim[3] = l4.w;
-                }
+                const int row0 = 8 * q4 + 4 * g;           // registers 4*q4 .. 4*q4+3 hold the chunk's rows row0 .. row0+3
+                const f32x4 sa = reinterpret_cast<const f32x4*>(rs + 2 * row0)[0];       // m, 1/l of rows row0, row0+1
+                const f32x4 sb = reinterpret_cast<const f32x4*>(rs + 2 * row0)[1];       // ... row0+2, row0+3
+                const float mm[4] = {sa.x, sa.z, sb.x, sb.z}, il[4] = {sa.y, sa.w, sb.y, sb.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int r = 4 * q4 + e, row = row0 + e;
-                    float p = fast_exp2(s[r] * a.scale_log2e - mm[e]) * il[e];
-                    if (!open) p = (klocal <= lim[e]) ? p : 0.f;
-                    ps += p;
-                    pm = fmaxf(pm, p);
-                    if (MODE == 0) slab[row * (SB + 1) + klocal] = p;
-                    if (MODE == 3 && row < a.w && mykey < n) a.a_win[((int64_t)bh * a.w + row) * n + mykey] = p;
-                    if (MODE == 1 && p > 0.f) {
-                        int64_t pr = a.q_pos ? a.q_pos[row] : n - a.w + row;
-                        if (pr > n - 1) pr = n - 1;
-                        const int64_t o = pr - mykey;
-                        atomicAdd(a.slash + (int64_t)bh * n + o, p);
-                        atomicMax(reinterpret_cast<unsigned int*>(a.smax + (int64_t)bh * n + o),
-                                  __builtin_bit_cast(unsigned int, p));
+                    const int row = row0 + e;
+                    float p = fast_exp2(s[4 * q4 + e] * a.scale_log2e - mm[e]) * il[e];
+                    if constexpr (decltype(MASKED)::value) {
+                        int t = k.t0 + row;
+                        if (MODE == 2 && packed) t &= a.w - 1;
+                        p = ((row < k.cnt) & (klocal <= ql[t < a.w ? t : a.w - 1])) ? p : 0.f;
                     }
+                    ps += p;
+                    if (MODE == 0 || MODE == 1) pm = fmaxf(pm, p);
+                    if (MODE == 0) slab[(klocal - row + 31) * SLAB + row] = p;
+                    if ((MODE == 1 || MODE == 3) && row < k.cnt && mykey < n)
+                        a.a_win[((int64_t)(bh - a.bh_first) * a.w + k.t0 + row) * n + mykey] = p;
+                }
+                if (MODE == 2 && packed && (8 * (q4 + 1)) % a.w == 0) {                  // the last rows of a head
+                    gsum += halves_sum(ps);                // (rows past the last head add zeros)
+                    ps = 0.f;
                 }
             }
-            ps += xor32(ps);
-            pm = fmaxf(pm, xor32(pm));
-            vsum += ps;
-            vmx = fmaxf(vmx, pm);
-        }
-        if (MODE == 2) gsum += vsum;
-        else if (MODE != 3 && g == 0 && mykey < n) {
-            a.vert[(int64_t)bh * n + mykey] = vsum;
-            a.vmax[(int64_t)bh * n + mykey] = vmx;
+        };
+        if (open && k.cnt == 32) rows(std::false_type{}); else rows(std::true_type{});
+        if (!(MODE == 2 && packed)) {
+            vsum += halves_sum(ps);
+            if (MODE == 0 || MODE == 1) vmx = fmaxf(vmx, halves_max(pm));
         }
         if (MODE == 0) {
-            lds_barrier();
-            // thread j owns diagonal o = omin + j of this slab; key_local = t + (SB-1) - j for row t
-            const int64_t omin = n - a.w - (blk0 + SB - 1);
-            for (int j = tid; j < SB - 1 + a.w; j += SCORE_THREADS) {
-                const int64_t o = omin + j;
-                if (o < 0) continue;
-                float ssum = 0.f, smx = 0.f;
-                const int t0 = j - (SB - 1) > 0 ? j - (SB - 1) : 0;
-                const int t1 = j < a.w - 1 ? j : a.w - 1;
-                // rows in ascending order, eight reads in flight; whole groups of eight need no range tests, the
-                // last, shorter group adds an exact zero for a row beyond t1
-                const float* dp = slab + (SB - 1) - j;             // row t of this diagonal sits at dp[t * (SB + 2)]
-                int tb = t0;
-                for (; tb + 7 <= t1; tb += 8) {
-                    float p8[8];
+            lds_barrier();                                 // the slab is whole
+            const int u = k.t0 + (SB - 1) - tid + 31;      // this thread's diagonal in the slab
+            if (tid < SB - 1 + a.w && u >= 0 && u < SLAB_DIAGS) {
+                int at = u * SLAB;
+                asm("" : "+v"(at));                        // (one address for all reads, constants in their offsets)
+                // rows in ascending order, sixteen reads in flight
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) p8[e] = dp[(tb + e) * (SB + 2)];
+                for (int rb = 0; rb < 32; rb += 16) {
+                    float p[16];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) { ssum += p8[e]; smx = fmaxf(smx, p8[e]); }
+                    for (int e = 0; e < 16; ++e) p[e] = slab[at + rb + e];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) { dsum += p[e]; dmax = fmaxf(dmax, p[e]); }
                 }
-                if (tb <= t1) {
-                    float p8[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) p8[e] = (tb + e <= t1) ? dp[(tb + e) * (SB + 2)] : 0.f;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) { ssum += p8[e]; smx = fmaxf(smx, p8[e]); }
-                }
-                float* dst = a.spart + (((int64_t)(kb & 1) * a.BH + bh) * n + o) * 2;
-                dst[0] = ssum; dst[1] = smx;
+            }
+        }
+        wait_transfers();                                  // chunk c + 1
+        __syncthreads();
+        if (c + 2 < c1) fetch(c + 2);
+        if (!(MODE == 2 && packed) && k.t0 + 32 >= a.w) {  // the head's last chunk
+            if (MODE == 2) gsum += vsum;
+            if ((MODE == 0 || MODE == 1) && g == 0 && mykey < n) {
+                a.vert[(int64_t)bh * n + mykey] = vsum;
+                a.vmax[(int64_t)bh * n + mykey] = vmx;
+            }
+            vsum = 0.f; vmx = 0.f;
+            if (MODE == 0) {
+                const int64_t o = omin + tid;
+                if (tid < SB - 1 + a.w && o >= 0)
+                    reinterpret_cast<float2*>(a.spart)[((int64_t)(kb & 1) * a.BH + bh) * n + o] = make_float2(dsum, dmax);
+                dsum = 0.f; dmax = 0.f;
             }
         }
     }
     if (MODE == 2 && g == 0 && mykey < n) a.gscore[(int64_t)bk * n + mykey] = gsum;
 }
 
+// ---- diagonals from the written matrix (explicit positions) ---------------------------------------
+// grid (n / 256, heads bh_first ..): thread o adds A[t][p_t - o] over the rows in order; neighbouring threads read
+// neighbouring cells.
+__global__ __launch_bounds__(256) void diagonals_kernel(ScoreArgs a) {
+    __shared__ int32_t pos[256];
+    if (threadIdx.x < (unsigned)a.w) pos[threadIdx.x] = position_of(a, threadIdx.x);
+    __syncthreads();
+    const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (o >= a.n) return;
+    const float* A = a.a_win + (int64_t)blockIdx.y * a.w * a.n;
+    float sum = 0.f, mx = 0.f;
+    for (int t0 = 0; t0 < a.w; t0 += 8) {
+        float p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int t = t0 + e < a.w ? t0 + e : a.w - 1;
+            const int64_t key = pos[t] - o;
+            p[e] = t0 + e < a.w && key >= 0 ? A[(int64_t)t * a.n + key] : 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { sum += p[e]; mx = fmaxf(mx, p[e]); }
+    }
+    a.slash[(int64_t)(a.bh_first + blockIdx.y) * a.n + o] = sum;
+    a.smax[(int64_t)(a.bh_first + blockIdx.y) * a.n + o] = mx;
+}
+
 // ---- finish: add the two diagonal partials, reduce the total ------------------------------------
-// grid (B*Hq).  Diagonal o is met by keys n-w-o .. n-1-o (clipped at 0), i.e. by key blocks
-// kA = max(0, n-w-o)/SB and kB = (n-1-o)/SB, which are equal or adjacent.
+// grid (B*Hq, FINISH_SPLIT).  Diagonal o is met by keys n-w-o .. n-1-o (clipped at 0), i.e. by key blocks
+// kA = max(0, n-w-o)/SB and kB = (n-1-o)/SB, which are equal or adjacent.  The last of a head's workgroups to get to its
+// end (a counter per head) adds their shares of the total, in a fixed tree order.
 constexpr int FINISH_SPLIT = 8;            // workgroups per head (a head alone is a string of load round trips)
 __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguous) {
     __shared__ float red[1024];
@@ -358,23 +449,22 @@ __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguou
     const int64_t beg = (int64_t)part * per, end = beg + per < n ? beg + per : n;
     if (contiguous) {
         for (int64_t o0 = beg + tid; o0 < end; o0 += 4 * 1024) {   // four diagonals per thread, all loads first
-            float sa[4], ma[4], sb[4], mb[4]; bool two[4];
+            float2 va[4], vb[4]; bool two[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int64_t o = o0 + j * 1024 < end ? o0 + j * 1024 : end - 1;
                 int64_t lo = n - a.w - o; if (lo < 0) lo = 0;
                 const int64_t kA = lo / SB, kB = (n - 1 - o) / SB;
-                const float* pa = a.spart + (((kA & 1) * a.BH + bh) * n + o) * 2;
-                const float* pb = a.spart + (((kB & 1) * a.BH + bh) * n + o) * 2;
                 two[j] = kB != kA;
-                sa[j] = pa[0]; ma[j] = pa[1]; sb[j] = pb[0]; mb[j] = pb[1];
+                va[j] = reinterpret_cast<const float2*>(a.spart)[((kA & 1) * a.BH + bh) * n + o];
+                vb[j] = reinterpret_cast<const float2*>(a.spart)[((kB & 1) * a.BH + bh) * n + o];
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int64_t o = o0 + j * 1024;
                 if (o < end) {
-                    a.slash[(int64_t)bh * n + o] = two[j] ? sa[j] + sb[j] : sa[j];      // lower key block first
-                    a.smax[(int64_t)bh * n + o] = two[j] ? fmaxf(ma[j], mb[j]) : ma[j];
+                    a.slash[(int64_t)bh * n + o] = two[j] ? va[j].x + vb[j].x : va[j].x;      // lower key block first
+                    a.smax[(int64_t)bh * n + o] = two[j] ? fmaxf(va[j].y, vb[j].y) : va[j].y;
                 }
             }
         }
@@ -390,51 +480,74 @@ __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguou
     }
     red[tid] = acc;
     __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
+    for (int s = 512; s >= 64; s >>= 1) {
         if (tid < s) red[tid] += red[tid + s];
         __syncthreads();
     }
-    if (tid == 0) a.part[(int64_t)bh * FINISH_SPLIT + part] = red[0];   // `part` is free again once merge_kernel has run
+    if (tid >= 64) return;
+    acc = red[tid];
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) acc += __shfl_down(acc, s, 64);
+    if (tid == 0) {
+        float* share = a.part + (int64_t)bh * FINISH_SPLIT;            // `part` is free again once merge_kernel has run
+        put_shared(share + part, acc);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (count_shared(a.done + bh) == FINISH_SPLIT - 1u) {
+            float p[FINISH_SPLIT];
+#pragma unroll
+            for (int i = 0; i < FINISH_SPLIT; ++i) p[i] = get_shared(share + i);
+            a.total[bh] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+            clear_shared(a.done + bh);                                 // for the next call
+        }
+    }
 }
 
-// total[bh] = the ranges' shares added in a fixed tree order
-__global__ void total_kernel(ScoreArgs a) {
-    const int bh = blockIdx.x * blockDim.x + threadIdx.x;
-    if (bh >= a.BH) return;
-    const float* p = a.part + (int64_t)bh * FINISH_SPLIT;
-    a.total[bh] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+// Workgroups that share a KV head's query heads over one key block.  A grid of less than four workgroups per CU
+// (what the LDS takes) leaves SIMDs with too few waves to cover the chunks' barriers: the heads are then shared
+// out, at the price of reading K once more per share, which the L2 mostly answers.  Two such rounds still gain
+// while a workgroup keeps four chunks (16384 keys, w = 128: lines 33.7 -> 31.4 us), with fewer they lose
+// (8192 keys, w = 64: 20.6 -> 22.6 us).  1024 fp32 keys, 4 -> 16 workgroups per key block: 15.1 -> 6.2 us.
+static int head_shares(const ScoreArgs& a, int kv_heads) {
+    const int64_t wgs = (int64_t)a.nkb * kv_heads;
+    const int chunks = a.G * ((a.w + 31) / 32);
+    int z = 1;
+    while (a.G % (2 * z) == 0 && wgs * 2 * z <= (chunks >= 8 * z ? 2048 : 1024)) z *= 2;
+    return z;
 }
-
-__global__ void fill_zero_kernel(float* p, int64_t count) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < count) p[i] = 0.f;
+template <typename T, int D>
+static void launch_stats(const ScoreArgs& a, hipStream_t st) {
+    const size_t smem = stats_front<T, D>() + (size_t)a.w * 4;
+    hipLaunchKernelGGL((stats_kernel<T, D>), dim3(a.nkb, a.B * a.Hkv, packs(a.w) ? 1 : head_shares(a, a.B * a.Hkv)), dim3(SCORE_THREADS), smem, st, a);
+}
+template <typename T, int D, int MODE>
+static void launch_lines(const ScoreArgs& a, int kv_heads, hipStream_t st) {
+    const size_t smem = lines_front<T, D>(MODE) + 512 + (size_t)a.w * 4;
+    hipLaunchKernelGGL((lines_kernel<T, D, MODE>), dim3(a.nkb, kv_heads, MODE == 2 ? 1 : head_shares(a, kv_heads)), dim3(SCORE_THREADS), smem, st, a);
 }
 
 template <typename T, int D>
-static hipError_t run_score_t(const ScoreArgs& a, int mode, hipStream_t st) {
-    const dim3 grid(a.nkb, a.B * a.Hkv);
-    const int wpad = ((a.w + 31) / 32) * 32;
-    const size_t qbytes = (size_t)wpad * D * Elem<T>::bytes;
-    hipLaunchKernelGGL((stats_kernel<T, D>), grid, dim3(SCORE_THREADS), qbytes, st, a);
-    const int rows = a.BH * a.w;
-    hipLaunchKernelGGL(merge_kernel, dim3((rows + 3) / 4), dim3(256), 0, st, a, rows);
-    const size_t smem = (mode == 0 ? (size_t)wpad * (SB + 1) * 4 : 0) + (size_t)wpad * 8 + (size_t)wpad * 4 + qbytes;
+static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
+    ScoreArgs a = a0;
+    const int BK = a.B * a.Hkv;
+    launch_stats<T, D>(a, st);
+    hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {
-        hipLaunchKernelGGL((lines_kernel<T, D, 0>), grid, dim3(SCORE_THREADS), smem, st, a);
+        launch_lines<T, D, 0>(a, BK, st);
     } else if (mode == 1) {
-        const int64_t cnt = (int64_t)a.BH * a.n;
-        hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, a.slash, cnt);
-        hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, st, a.smax, cnt);
-        hipLaunchKernelGGL((lines_kernel<T, D, 1>), grid, dim3(SCORE_THREADS), smem, st, a);
+        for (a.bk0 = 0; a.bk0 < BK; a.bk0 += a.win_heads) {            // as many KV heads as the matrix buffer takes
+            const int heads = BK - a.bk0 < a.win_heads ? BK - a.bk0 : a.win_heads;
+            a.bh_first = a.bk0 * a.G;
+            launch_lines<T, D, 1>(a, heads, st);
+            hipLaunchKernelGGL(diagonals_kernel, dim3((unsigned)((a.n + 255) / 256), heads * a.G), dim3(256), 0, st, a);
+        }
     } else if (mode == 3) {
-        hipLaunchKernelGGL((lines_kernel<T, D, 3>), grid, dim3(SCORE_THREADS), smem, st, a);
+        launch_lines<T, D, 3>(a, BK, st);
         return hipGetLastError();
     } else {
-        hipLaunchKernelGGL((lines_kernel<T, D, 2>), grid, dim3(SCORE_THREADS), smem, st, a);
+        launch_lines<T, D, 2>(a, BK, st);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(finish_kernel, dim3(a.BH, FINISH_SPLIT), dim3(1024), 0, st, a, mode == 0 ? 1 : 0);
-    hipLaunchKernelGGL(total_kernel, dim3((a.BH + 255) / 256), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -444,8 +557,8 @@ static hipError_t init_score_t() {
     if ((e = allow_full_lds(&stats_kernel<T, D>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 0>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 1>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&lines_kernel<T, D, 3>)) != hipSuccess) return e;
-    return allow_full_lds(&lines_kernel<T, D, 2>);
+    if ((e = allow_full_lds(&lines_kernel<T, D, 2>)) != hipSuccess) return e;
+    return allow_full_lds(&lines_kernel<T, D, 3>);
 }
 hipError_t init_score_kernels() {
     hipError_t e;
@@ -461,12 +574,6 @@ hipError_t run_score(const ScoreArgs& a, int dtype, int d, int mode, hipStream_t
     if (dtype == 1 && d == 128) return run_score_t<float, 128>(a, mode, st);
     if (dtype == 1 && d == 64) return run_score_t<float, 64>(a, mode, st);
     return hipErrorInvalidValue;
-}
-
-// dynamic LDS of lines_kernel (the larger of the two passes)
-size_t score_lines_smem(int w, int dtype, int d, int mode) {
-    const int wpad = ((w + 31) / 32) * 32;
-    return (mode == 0 ? (size_t)wpad * (SB + 1) * 4 : 0) + (size_t)wpad * 12 + (size_t)wpad * d * (dtype == 0 ? 2 : 4);
 }
 
 }  // namespace ls

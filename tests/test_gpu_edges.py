@@ -57,3 +57,66 @@ def test_prefill_parts_of_long_items(oracle, dtype, d, n, n_hat):
         alive = np.isfinite(ref_lse)
         np.testing.assert_array_equal(np.isfinite(l), alive)
         assert np.abs(l[alive] - ref_lse[alive]).max(initial=0) <= tol[2]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,w,d,dtype", [
+    (1, 8, 1, 127, 1, 128, "bf16"),        # one row, less than a key block; heads shared out over eight workgroups
+    (1, 6, 2, 128, 33, 64, "bf16"),        # exactly one key block; a chunk of one row; three heads a KV head: no sharing
+    (2, 8, 2, 257, 31, 128, "bf16"),       # one key in the last block; rows that do not exist in every chunk
+    (1, 12, 2, 385, 128, 64, "f32"),       # heads shared by two only (6 = 2 x 3); longest window with diagonals in LDS
+    (1, 2, 2, 640, 129, 128, "bf16"),      # shortest window whose diagonals come from the written matrix
+    (8, 16, 8, 3000, 16, 64, "bf16"),      # more than 1024 workgroups: no sharing
+    (1, 1, 1, 33000, 40, 64, "bf16"),      # more key blocks than a thread of the merge keeps
+])
+def test_score_chunks_and_shares(oracle, B, Hq, Hkv, n, w, d, dtype):
+    from tests.gpu_util import Pipeline, host
+    from tests.test_gpu_parity import _score_close
+    print(f"score edge B={B} Hq={Hq} Hkv={Hkv} n={n} w={w} d={d} {dtype}", flush=True)
+    q, k, v = inputs.make_plain(B, Hq, Hkv, n, w, d, dtype=dtype, seed=n + w, q_scale=2.0)
+    pipe = Pipeline(q, k, v, w, dtype)
+    _score_close(host(pipe.score()), oracle.score(q, k), w)
+
+
+@pytest.mark.parametrize("w,dtype", [(1, "bf16"), (40, "bf16"), (200, "f32")])
+def test_score_positions_in_head_groups(oracle, w, dtype):
+    """Scoring positions given: the window matrix passes through the workspace for as many KV heads as it takes."""
+    from tests.gpu_util import Pipeline, host
+    from tests.test_gpu_parity import _score_close
+    B, Hq, Hkv, n, d = 2, 6, 3, 700, 64
+    q, k, v = inputs.make_plain(B, Hq, Hkv, n, w, d, dtype=dtype, seed=w, q_scale=2.0)
+    pos = np.sort(np.random.default_rng(w).choice(n, size=w, replace=False))
+    ref = oracle.score(q, k, q_pos=pos)
+    pipe = Pipeline(q, k, v, w, dtype)
+    whole = host(pipe.score(q_pos=pos))
+    _score_close(whole, ref, w)
+    one = Hq // Hkv * w * n * 4
+    part = B * Hkv * ((n + 127) // 128) * (Hq // Hkv) * w * 8 + B * Hq * w * 8 + 4096
+    print(f"head groups w={w} matrix {one} bytes a KV head", flush=True)
+    pipe.ctx = binding.Context(workspace=part + 4 * one + one // 2)      # four of six KV heads at a time
+    some = host(pipe.score(q_pos=pos))
+    for name in whole:
+        np.testing.assert_array_equal(whole[name], some[name])
+
+
+@pytest.mark.parametrize("Hq,Hkv,ln,n_obs,d,dtype", [
+    (4, 4, 129, 8, 64, "bf16"),            # one head a KV head: a chunk of eight rows
+    (10, 2, 300, 8, 128, "bf16"),          # forty rows: a whole chunk and one of eight
+    (6, 2, 257, 16, 64, "f32"),            # forty-eight rows: a whole chunk and half of one
+    (16, 1, 1000, 16, 128, "bf16"),        # eight whole chunks
+    (4, 2, 200, 5, 64, "bf16"),            # no divisor of 32: a chunk per head
+    (4, 2, 500, 40, 128, "f32"),           # two chunks per head
+])
+def test_retention_score_chunks(oracle, Hq, Hkv, ln, n_obs, d, dtype):
+    from tests.gpu_util import Pipeline
+    print(f"retention edge Hq={Hq} Hkv={Hkv} len={ln} n_obs={n_obs} d={d} {dtype}", flush=True)
+    q, k, v = inputs.make_plain(1, Hq, Hkv, ln, n_obs, d, dtype=dtype, seed=ln, q_scale=2.0)
+    budget = 32
+    ref = oracle.compress(q, k, budget)
+    pipe = Pipeline(q, k, v, n_obs, dtype, budget=budget)
+    keep_idx = torch.full((1, Hkv, budget), -1, dtype=torch.int32, device="cuda")
+    keep_cnt = torch.zeros((1, Hkv), dtype=torch.int32, device="cuda")
+    k_out = torch.zeros((1, Hkv, budget, d), dtype=pipe.k.dtype, device="cuda")
+    pipe.ctx.ls_kv_compress(pipe.shape, budget, pipe.q, pipe.k, pipe.v, keep_idx, keep_cnt, k_out, torch.zeros_like(k_out))
+    score = torch.empty((1, Hkv, ln), dtype=torch.float32, device="cuda")
+    pipe.ctx.debug_compress_score(pipe.shape, score)
+    np.testing.assert_allclose(score.cpu().numpy(), ref["score"], rtol=1e-3, atol=1e-6 * n_obs)
