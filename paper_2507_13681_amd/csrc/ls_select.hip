@@ -273,6 +273,142 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_merge_kernel(SelectArgs a) 
     }
 }
 
+// ---- running sums in binary32, many additions at a time ------------------------------------------
+// s <- fl(s + g[i]) for one i after the other is a chain of dependent additions, but while s stays inside one binade
+// it is a chain of integer additions: with u the spacing of the binade and s = m u, fl(s + g) = u (m + floor(g / u) +
+// c) where c rounds the fraction of g / u to nearest, a tie to the even m + floor(g / u) + c.  Everything but the
+// tie is independent of m, and the tie depends on m's parity alone, so an entry is a pair of increments, one per
+// parity, and pairs compose: a scan over the lanes gives every partial sum of the chain, bit for bit.
+// Where the chain leaves the binade one entry is added the ordinary way; where the gains are not small against
+// the sum (its first entries), or negative, 64 entries are.
+
+// increments of a stretch of the chain that starts at an even (e) or odd (o) m
+struct ChainInc { int32_t e, o; };
+__device__ __forceinline__ ChainInc chain_then(ChainInc a, ChainInc b) {
+    return {a.e + ((a.e & 1) ? b.o : b.e), a.o + ((a.o & 1) ? b.e : b.o)};
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ ChainInc chain_dpp(ChainInc x) {        // lanes without a source receive the empty stretch
+    return {__builtin_amdgcn_update_dpp(0, x.e, CTRL, ROW_MASK, 0xF, false), __builtin_amdgcn_update_dpp(0, x.o, CTRL, ROW_MASK, 0xF, false)};
+}
+// of the lanes to the left, in order
+__device__ __forceinline__ ChainInc chain_before(ChainInc x) {
+    x = chain_then(chain_dpp<0x111, 0xF>(x), x);           // row_shr:1, 2, 4, 8
+    x = chain_then(chain_dpp<0x112, 0xF>(x), x);
+    x = chain_then(chain_dpp<0x114, 0xF>(x), x);
+    x = chain_then(chain_dpp<0x118, 0xF>(x), x);
+    x = chain_then(chain_dpp<0x142, 0xA>(x), x);           // row_bcast15 into rows 1 and 3
+    x = chain_then(chain_dpp<0x143, 0xC>(x), x);           // row_bcast31 into rows 2 and 3
+    return chain_dpp<0x138, 0xF>(x);                       // wave_shr:1
+}
+
+// index of the first entry any lane has found, entries in the order entry 0 of lane 0, entry 1 of lane 0, ... (64 E if
+// there is none); fe: the first of this lane's E entries (E: none)
+template <int E>
+__device__ __forceinline__ int first_entry(int fe) {
+    const uint64_t any = __ballot(fe < E);
+    if (any == 0ull) return 64 * E;
+    const int l = __ffsll((unsigned long long)any) - 1;
+    return E * l + __builtin_amdgcn_readlane(fe, l);
+}
+// entry i of the wave's 64 E (i uniform)
+template <int E, typename V>
+__device__ __forceinline__ V pick_entry(const V (&v)[E], int i) {
+    V x = v[0];
+#pragma unroll
+    for (int e = 1; e < E; ++e) x = (i % E) == e ? v[e] : x;
+    return __builtin_bit_cast(V, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i / E));
+}
+
+// Lane l holds the gains of the entries E l .. E l + E - 1 (0 from entry `limit` on).  Adds entries 0 .. `limit` - 1 to
+// `sum` (which is below `target`) in order until it reaches the target or they are used up; returns how many were
+// added.
+template <int E>
+__device__ __forceinline__ int chain_until(const float (&g)[E], int lane, int limit, float target, float& sum) {
+    constexpr float SMALL = 524288.f;                      // 2^19: 64 E of them stay below 2^30 for E <= 32
+    int at = 0;
+    bool plain = false;                                    // the next entries are not small against the sum
+    while (at < limit) {
+        const uint32_t sb = __builtin_bit_cast(uint32_t, sum);
+        const int ex = (int)(sb >> 23);
+        const int lo = at - E * lane;                      // this lane's entries from `lo` on are still to come
+        float h[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) h[e] = e >= lo ? g[e] : 0.f;
+        if (plain || ex < 64 || ex > 250) {                // (the first sum is 0)
+            // the lanes first .. first + 64 / E - 1, one after the other
+            const int first = at / E, lanes = 64 / E;
+            float x[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) x[e] = 0.f;
+            for (int p = 0; p < lanes; ++p) {
+                float left = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x[E - 1]), 0x138 /* wave_shr:1 */, 0xF, 0xF, true));
+                left = lane == first ? sum : left;
+                x[0] = __fadd_rn(left, h[0]);
+#pragma unroll
+                for (int e = 1; e < E; ++e) x[e] = __fadd_rn(x[e - 1], h[e]);
+            }
+            int fe = E;
+#pragma unroll
+            for (int e = E - 1; e >= 0; --e) fe = x[e] < target || e < lo ? fe : e;
+            const int j = first_entry<E>(lane >= first && lane < first + lanes ? fe : E);
+            if (j < limit) { sum = pick_entry(x, j); return j + 1; }
+            at = E * (first + lanes) < limit ? E * (first + lanes) : limit;
+            sum = pick_entry(x, at - 1);
+            plain = false;
+            continue;
+        }
+        const float per_u = __builtin_bit_cast(float, (uint32_t)(277 - ex) << 23);        // 1 / u = 2^(150 - ex)
+        const int m0 = (int)((sb & 0x7FFFFFu) | 0x800000u);
+        const float tf = target * per_u;
+        const int bound = tf < 16777216.f ? (int)ceilf(tf) : 1 << 24;  // first m that reaches the target, or has left the binade
+        int q[E];                                          // floor(g / u) * 4 + 2 (fraction > 1/2) + 1 (fraction = 1/2)
+        int big = E;                                       // first entry that is not small
+        int32_t me = 0, mo = 1;
+#pragma unroll
+        for (int e = E - 1; e >= 0; --e) {
+            float r = h[e] * per_u;
+            const bool small = r >= 0.f && r < SMALL;
+            big = small ? big : e;
+            r = small ? r : 0.f;
+            const float f = floorf(r), fr = r - f;
+            q[e] = 4 * (int)f + (fr > 0.5f ? 2 : fr == 0.5f ? 1 : 0);
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            me += q[e] >> 2; me += ((q[e] >> 1) & 1) + (me & q[e] & 1);
+            mo += q[e] >> 2; mo += ((q[e] >> 1) & 1) + (mo & q[e] & 1);
+        }
+        const ChainInc before = chain_before({me, mo - 1});
+        int m[E];
+        int32_t run = m0 + ((m0 & 1) ? before.o : before.e);
+        int fe = big;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            run += q[e] >> 2; run += ((q[e] >> 1) & 1) + (run & q[e] & 1);
+            m[e] = run;
+            fe = run >= bound && e < fe ? e : fe;
+        }
+        const int j0 = first_entry<E>(fe), j = j0 < limit ? j0 : limit;
+        if (j > at) sum = __builtin_bit_cast(float, ((uint32_t)ex << 23) | ((uint32_t)pick_entry(m, j - 1) & 0x7FFFFFu));
+        at = j;
+        if (j == limit) break;
+        if (__builtin_amdgcn_readlane(big, j / E) == j % E) { plain = true; continue; }
+        sum = __fadd_rn(sum, pick_entry(g, j));            // reaches the target, or the next binade
+        at = j + 1;
+        if (!(sum < target)) break;
+    }
+    return at;
+}
+// the same with the gains in LDS (64 E floats, 16-byte aligned)
+template <int E>
+__device__ __forceinline__ int chain_lds(const float* gains, int lane, int limit, float target, float& sum) {
+    float g[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) { g[e] = gains[E * lane + e]; g[e] = E * lane + e < limit ? g[e] : 0.f; }
+    return chain_until<E>(g, lane, limit, target, sum);
+}
+
 // ---- the greedy loop ----------------------------------------------------------------------------
 // One workgroup of six waves per head.  The loop of Alg. 2 is sequential, but three things about it are not:
 //   * ol_s after k slashes were taken is the left-to-right binary32 sum of the first k maxima of
@@ -759,23 +895,22 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
 // there is one, so
 //     overlap(slash o)  = sum over scored rows t with key c = p_t - o >= 0 and c taken  of A[t][c]
 //     overlap(column b) = sum over scored rows t with o = p_t - b >= 0 and o taken      of A[t][b]
-// "Taken" is a comparison of ranks: the lists are used up from the front, so column c is taken iff its position
-// in the sorted column list is below the number of columns taken so far.  A candidate therefore needs, once, the
-// w cells of its line and the ranks of the w lines it crosses; its overlap at any later moment is a masked sum of
-// those cells.  Everything else is the loop of walk_kernel (binary32, single roundings, cross-multiplied test).
+// Everything else is the loop of walk_kernel (binary32, single roundings, cross-multiplied test).
 //
-// rank_kernel: inverse of the sorted order, rank[list][bh][line] = position of the line in its sorted list.
-__global__ void rank_kernel(SelectArgs a) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t seg = ((int64_t)blockIdx.z * a.BH + blockIdx.y) * a.n;
-    if (i < a.n) a.sidx0[seg + a.sidx1[seg + i]] = (int32_t)i;
-}
-
-constexpr int XW_STAGERS = 3;                  // staging waves per list
-constexpr int XW_THREADS = 64 * (1 + 2 * XW_STAGERS);   // wave 0 walks, then XW_STAGERS waves per list stage its records
-constexpr int XW_CELLS = 4096;                 // cells of staged records per list: a ring of XW_CELLS / wpad records
-constexpr int XW_BATCH = 8;                    // records a stager fetches per round trip
-struct XwSync { int staged[2], head[2], done, err; };
+// One workgroup per head.  The loop takes long runs from one list (a few per walk, of hundreds to thousands of picks),
+// and during a run the other list's head and taken set stand still.  So a round looks at many candidates of one
+// list at once: 64 when the list has just changed, then up to 1024, one per thread.  It needs
+//   - what the other list's taken set covers of each candidate: a bitmap says which of its W cells count, and only
+//     those are read (they miss the L2, a microsecond each: sixteen threads share the rows of one of 64
+//     candidates, so that one load per thread and 64 rows is all; with more candidates a thread reads its own
+//     line's cells eight at a time, and keeps the sum while the other list stands still);
+//   - what of the other head is covered at each candidate: its W cells, each with the candidate that takes the line
+//     it lies on;
+//   - the first candidate that fails the test, and the gains before it added in order by one wave.
+// What bounds it is the latency of a round, 4 to 6 us (dependent loads, five barriers, one wave's chain), so the
+// head with most runs.  Taken pick by pick it was 0.37 us a pick: 8192 lines, 32 heads, up to 3074 picks or 14
+// runs a head, 1160 us; now 66.  All candidates brought up to date after every run, with bitmaps of the lines
+// taken since: 72 to 75 us.
 
 // Sum of a double over the 64 lanes, the same value in every lane.  Data-parallel-primitive moves on the two
 // halves of the value instead of cross-lane reads through LDS: a shuffle of a double is two LDS round trips, six
@@ -799,195 +934,207 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// grid (BH).  LDS: per list a ring of records (wpad cells + wpad ranks each) and per-record line index / weight.
-// NC: cells of a record per lane held in registers (1, 2 or 4; a window of w rows needs ceil(w / 64))
-template <int NC>
-__global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
-    extern __shared__ __align__(16) unsigned char xw_lds[];
-    const int W = a.w, wpad = (W + 63) / 64 * 64, CP = wpad / 64, ring = XW_CELLS / wpad;      // ring >= 16 (w <= 256)
-    float* cells = reinterpret_cast<float*>(xw_lds);                       // [2][ring][wpad]
-    int32_t* ranks = reinterpret_cast<int32_t*>(cells + 2 * XW_CELLS);     // [2][ring][wpad]
-    int32_t* ridx = ranks + 2 * XW_CELLS;                                  // [2][ring] line index of a record
-    float* rwt = reinterpret_cast<float*>(ridx + 2 * 256);                 // [2][ring] its weight
-    XwSync* sync = reinterpret_cast<XwSync*>(rwt + 2 * 256);
-    const int bh = blockIdx.x, lane = threadIdx.x & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n = (int)a.n;
-    const int spin_limit = a.spin_limit;
-    if (threadIdx.x == 0) { sync->staged[0] = sync->staged[1] = 0; sync->head[0] = sync->head[1] = 0; sync->done = 0; sync->err = 0; }
-    __syncthreads();
 
-    if (wv != 0) {
-        // ------------------------------------------------------------------ staging of one list
-        // XW_STAGERS waves per list take the batches of XW_BATCH records in turn (stager s: batches s, s + S, ...),
-        // so that the memory round trips of consecutive batches overlap; a batch is published in order, once the
-        // batch before it has been.
-        const int l = (wv - 1) / XW_STAGERS, sidx = (wv - 1) % XW_STAGERS; // list (0: slashes, 1: columns), stager
-        const int32_t* sorted = a.sidx1 + ((int64_t)l * a.BH + bh) * a.n;
-        const int32_t* rank_other = a.sidx0 + ((int64_t)(1 - l) * a.BH + bh) * a.n;
-        const float* wts = (l == 0 ? a.slash : a.vert) + (int64_t)bh * a.n;
-        const float* A = a.a_win + (int64_t)bh * W * a.n;
-        int pos[NC];                                                        // positions of this lane's rows t = lane + 64 c
+constexpr int XW_THREADS = 1024;
+constexpr int XW_ROWS = 256;                   // longest window
+constexpr int XW_FEW = 64;                     // candidates of the first round of a run
+static_assert(16 * XW_FEW == XW_THREADS, "sixteen threads a candidate");
+constexpr int XW_AGAIN = 768;                  // entries of a block of the sorted list behind the head before the next one is loaded
+
+// grid (BH).  Dynamic LDS: two bitmaps of n bits.
+__global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
+    extern __shared__ uint32_t xw_maps[];
+    __shared__ __align__(16) float gains[XW_THREADS];
+    __shared__ float cell[XW_ROWS];            // cells of the other head's line
+    __shared__ int32_t when[XW_ROWS];          // candidate whose line each lies on: -1 taken already, XW_NEVER none of this round
+    __shared__ int32_t pos[XW_ROWS];           // positions of the scored rows
+    __shared__ int32_t lines[XW_FEW];          // of the candidates
+    __shared__ int32_t head_line, run_end, taken_now;
+    __shared__ float head_weight, sum_now;
+    constexpr int32_t XW_NEVER = 0x7FFFFFFF;
+    const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = (int)a.n, W = a.w, words = (int)((a.n + 31) / 32);
+    uint32_t *const map_s = xw_maps, *const map_v = xw_maps + words;       // lines taken
+    for (int i = tid; i < 2 * words; i += XW_THREADS) xw_maps[i] = 0u;
+    const bool window = a.q_pos == nullptr;    // the scored rows are the last W positions
+    if (tid < W) {
+        const int64_t p = window ? (int64_t)n - W + tid : a.q_pos[tid];
+        pos[tid] = (int)(p > n - 1 ? n - 1 : p < -1 ? -1 : p);
+    }
+    const float target = a.alpha * a.total[bh], nh = (float)a.n_hat;
+    const float* A = a.a_win + (int64_t)bh * W * a.n;
+    auto length = [&](int line) { const float rest = (float)(n - line); return rest < nh ? rest : nh; };
+
+    // Of a list: its lines taken, and the thread's entry of the block of the sorted list loaded last: line, weight, and
+    // (valid) what the other list's lines taken so far cover of it.
+    struct List { int id, taken, base; bool valid; int32_t line; float weight, covered; };
+    auto load = [&](List& l) {
+        l.base = l.taken;
+        const int i = l.base + tid < n ? l.base + tid : n - 1;
+        l.line = a.sidx1[((int64_t)l.id * a.BH + bh) * a.n + i];
+        l.weight = ((l.id == 0 ? a.slash : a.vert) + (int64_t)bh * a.n)[l.line];
+        l.covered = 0.f;
+        l.valid = false;
+    };
+    List X, O;                                 // the list whose lines are the candidates, and the other one
+    X.id = X.taken = 0; O.id = 1; O.taken = 0;
+    load(X);
+    load(O);
+    float sum = 0.f;
+    int head_of = -1, head_at = -1;            // list and sorted position whose cells `cell` holds
+    int most = XW_FEW;                         // candidates of the next round
+    bool decided = false;                      // its first candidate is known to be the next pick
+    while (sum < target && (X.taken < n || O.taken < n)) {
+        bool change = false;                   // to the other list
+        if (X.taken == n) change = decided = true;
+        else {
+            uint32_t * const map_x = X.id == 0 ? map_s : map_v;
+            const uint32_t* const map_o = X.id == 0 ? map_v : map_s;
+            const bool has_o = O.taken < n, few = most == XW_FEW;
+            const int off = X.taken - X.base;  // the head's entry
+            const int C = XW_THREADS - off < most ? XW_THREADS - off : most;
+            const int j = tid - off;           // this thread's candidate
+            const bool cand = j >= 0 && j < C && X.base + tid < n;
+            const int j0 = 64 * wv - off;      // first candidate of this wave
+            const bool busy = j0 + 63 >= 0 && j0 < C;
+            const int32_t x = X.line;
+            if (has_o && tid == O.taken - O.base) { head_line = O.line; head_weight = O.weight; }
+            if (few && j >= 0 && j < C) lines[j] = x;
+            if (tid == 0) run_end = XW_NEVER;
+            __syncthreads();
+            const int32_t o = head_line;
+            // (the loads of this part are issued together: each takes a microsecond when it misses the L2)
+            float head_cell = 0.f;
+            bool head_moved = false;
+            if (has_o && tid < W) {
+                const int other = pos[tid] - o;            // the line of list X through this cell of the head
+                head_moved = head_of != O.id || head_at != O.taken;
+                if (head_moved) head_cell = A[other >= 0 ? (int64_t)tid * a.n + (O.id == 0 ? other : o) : 0];
+                head_cell = other >= 0 ? head_cell : 0.f;
+                when[tid] = other >= 0 && ((map_x[other >> 5] >> (other & 31)) & 1u) ? -1 : XW_NEVER;
+            }
+            head_of = O.id; head_at = O.taken;
+            if (few && O.taken > 0) {          // sixteen threads a candidate, every sixteenth row each
+                const int c = tid >> 4, x16 = lines[c];
+                double part = 0.0;
+                for (int t0 = 0; t0 < W; t0 += 64) {
+                    float v[4];
+                    bool on[4];
 #pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const int t = lane + 64 * c;
-            int64_t p = t < W ? (a.q_pos ? a.q_pos[t] : (int64_t)n - W + t) : -1;
-            if (p > n - 1) p = n - 1;
-            pos[c] = (int)p;
-        }
-        for (int j = sidx * XW_BATCH; j < n; j += XW_STAGERS * XW_BATCH) {
-            const int batch = n - j < XW_BATCH ? n - j : XW_BATCH;
-            // the loads do not depend on the ring: issued before waiting for room
-            int32_t idx[XW_BATCH];
+                    for (int u = 0; u < 4; ++u) {
+                        const int t = t0 + 16 * u + (tid & 15);
+                        const int other = c < C && t < W ? pos[t] - x16 : -1;
+                        on[u] = other >= 0 && ((map_o[other >> 5] >> (other & 31)) & 1u);
+                        v[u] = A[on[u] ? (int64_t)t * a.n + (X.id == 0 ? other : x16) : 0];
+                    }
 #pragma unroll
-            for (int r = 0; r < XW_BATCH; ++r) idx[r] = sorted[j + (r < batch ? r : 0)];
-            float wt[XW_BATCH], cell[XW_BATCH][NC];
-            int32_t rk[XW_BATCH][NC];
-#pragma unroll
-            for (int r = 0; r < XW_BATCH; ++r) {
-                wt[r] = wts[idx[r]];
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    cell[r][c] = 0.f; rk[r][c] = 0x7FFFFFFF;
-                    if (c < CP) {
-                        const int t = lane + 64 * c;
-                        const int other = pos[c] - idx[r];                 // the crossed line of the other kind (key, or diagonal)
-                        if (t < W && other >= 0) {
-                            const int key = l == 0 ? other : idx[r];
-                            cell[r][c] = A[(int64_t)t * a.n + key];
-                            rk[r][c] = rank_other[other];
+                    for (int u = 0; u < 4; ++u) part += on[u] ? (double)v[u] : 0.0;
+                }
+                part += dpp_f64<0xB1, 0xF>(part);          // over sixteen lanes, as in wave_sum_f64
+                part += dpp_f64<0x4E, 0xF>(part);
+                part += dpp_f64<0x141, 0xF>(part);
+                part += dpp_f64<0x140, 0xF>(part);
+                if ((tid & 15) == 0) gains[c] = (float)part;
+            } else if (!few && busy && !X.valid && O.taken > 0) {          // a thread a candidate
+                double part = 0.0;
+                auto word = [&](int wi) { return wi >= 0 && wi < words ? map_o[wi] : 0u; };
+                for (int t0 = 0; t0 < W; t0 += 64) {
+                    uint64_t on = 0ull;
+                    if (window) {
+                        const int b = n - W + t0 - x, wi = b >> 5, sh = b & 31;
+                        const uint64_t lo = ((uint64_t)word(wi + 1) << 32) | word(wi), hi = word(wi + 2);
+                        on = lo >> sh | (sh ? hi << (64 - sh) : 0ull);
+                        if (W - t0 < 64) on &= (1ull << (W - t0)) - 1ull;
+                    } else {
+                        for (int t = 0; t < 64 && t0 + t < W; ++t) {
+                            const int c = pos[t0 + t] - x;
+                            if (c >= 0) on |= (uint64_t)((word(c >> 5) >> (c & 31)) & 1u) << t;
                         }
                     }
-                }
-            }
-            // room for the whole batch: its last record may be written once record j + batch - 1 - ring has been left
-            bool stop = false;
-            for (int spins = 0; walk_ld(&sync->head[l]) + ring < j + batch; ) {
-                if (walk_ld(&sync->done) != 0) { stop = true; break; }
-                __builtin_amdgcn_s_sleep(2);
-                if (++spins > spin_limit) { walk_st(&sync->err, 1); stop = true; break; }
-            }
-            if (stop) break;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                    while (on) {               // eight cells in flight
+                        float v[8];
+                        uint64_t left = on;
 #pragma unroll
-            for (int r = 0; r < XW_BATCH; ++r) {
-                if (r < batch) {
-                    const int slot = (j + r) % ring;
-#pragma unroll
-                    for (int c = 0; c < NC; ++c)
-                        if (c < CP) {
-                            cells[(l * ring + slot) * wpad + lane + 64 * c] = cell[r][c];
-                            ranks[(l * ring + slot) * wpad + lane + 64 * c] = rk[r][c];
+                        for (int u = 0; u < 8; ++u) {
+                            const int t = t0 + (left ? __ffsll((unsigned long long)left) - 1 : 0);
+                            v[u] = A[left ? (int64_t)t * a.n + (X.id == 0 ? pos[t] - x : x) : 0];
+                            left &= left - 1ull;
                         }
-                    if (lane == 0) { ridx[l * 256 + slot] = idx[r]; rwt[l * 256 + slot] = wt[r]; }
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) { part += on ? (double)v[u] : 0.0; on &= on - 1ull; }
+                    }
+                }
+                X.covered = (float)part;
+                X.valid = true;
+            }
+            if (head_moved) cell[tid] = head_cell;
+            __syncthreads();
+            const float covered = O.taken == 0 ? 0.f : few ? gains[j >= 0 && j < XW_FEW ? j : 0] : X.covered;
+            const float gain = cand ? __fsub_rn(X.weight, covered) : 0.f;
+            if (has_o && cand) {               // does the candidate's line cross the other head's inside the window?
+                if (window) {
+                    const int t = x + o - (n - W);
+                    if (t >= 0 && t < W) when[t] = j;
+                } else {
+                    for (int t = 0; t < W; ++t) if (pos[t] == x + o) when[t] = j;
                 }
             }
-            // in-order publication: wait until every earlier batch is out
-            for (int spins = 0; walk_ld(&sync->staged[l]) != j; ) {
-                if (walk_ld(&sync->done) != 0) { stop = true; break; }
-                __builtin_amdgcn_s_sleep(1);
-                if (++spins > spin_limit) { walk_st(&sync->err, 1); stop = true; break; }
+            __syncthreads();
+            if (busy) {
+                bool stays = cand;
+                if (has_o) {
+                    // what of the other head is covered when the walk gets to this wave's candidates, and to each of them
+                    double part = 0.0;
+                    bool any = false;
+                    for (int t = lane; t < W; t += 64) {
+                        const int wh = when[t];
+                        const bool in = wh < j0 || wh == -1;
+                        any |= in;
+                        part += in ? (double)cell[t] : 0.0;
+                    }
+                    double head_covered = __ballot(any) == 0ull ? 0.0 : wave_sum_f64(part);
+                    for (int t0 = 0; t0 < W; t0 += 64) {
+                        const int wh = t0 + lane < W ? when[t0 + lane] : XW_NEVER;
+                        uint64_t mine = __ballot(wh >= 0 && wh >= j0 && wh < j0 + 64);
+                        while (mine) {
+                            const int t = __ffsll((unsigned long long)mine) - 1;
+                            mine &= mine - 1ull;
+                            head_covered += __builtin_amdgcn_readlane(wh, t) < j ? (double)cell[t0 + t] : 0.0;
+                        }
+                    }
+                    const float other_gain = __fsub_rn(head_weight, (float)head_covered);
+                    float cx = __fsub_rn(length(x), (float)O.taken); if (cx < 1.0f) cx = 1.0f;
+                    float co = __fsub_rn(length(o), (float)(X.taken + j)); if (co < 1.0f) co = 1.0f;
+                    const float mine = __fmul_rn(gain, co), other = __fmul_rn(other_gain, cx);
+                    stays = cand && ((X.id == 0 ? mine >= other : !(other >= mine)) || (j == 0 && decided));
+                }
+                const uint64_t leave = __ballot(j >= 0 && j < C && !stays);
+                if (leave != 0ull && lane == 0) atomicMin(&run_end, j0 + __ffsll((unsigned long long)leave) - 1);
+                if (j >= 0 && j < C) gains[j] = gain;
             }
-            if (stop) break;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            if (lane == 0) walk_st(&sync->staged[l], j + batch);
+            __syncthreads();
+            const int end = run_end, run = end < C ? end : C;
+            if (wv == 0) {
+                float s = sum;
+                const int got = run <= 64 ? chain_lds<1>(gains, lane, run, target, s) : chain_lds<16>(gains, lane, run, target, s);
+                if (lane == 0) { taken_now = got; sum_now = s; }
+            }
+            __syncthreads();
+            const int got = taken_now;
+            sum = sum_now;
+            if (j >= 0 && j < got) atomicOr(&map_x[x >> 5], 1u << (x & 31));
+            X.taken += got;
+            if (got > 0) O.valid = false;
+            if (got == run && X.taken < n && X.taken - X.base > XW_AGAIN) load(X);
+            change = decided = end < C;        // then the first pick of the other list has been decided
+            most = XW_THREADS;
         }
-        return;
+        if (change) { List t = X; X = O; O = t; most = XW_FEW; }
     }
-
-    // ---------------------------------------------------------------------- the walk (wave 0)
-    const float target = a.alpha * a.total[bh];
-    const float nh = (float)a.n_hat;
-    float sum = 0.f;
-    int is = 0, iv = 0;
-    bool failed = false;
-    // head record of each list, read again only when that head moves
-    float c_s[NC], c_v[NC], w_s = 0.f, w_v = 0.f, l_s = 1.f, l_v = 1.f;
-    int32_t r_s[NC], r_v[NC];
-    int seen[2] = {0, 0};                                  // records of each list known to be staged (the counter is re-read only past that)
-    auto wait_record = [&](int l, int want) {              // until record `want` of list l is staged
-        if (want < seen[l]) return;
-        int spins = 0, st;
-        while ((st = walk_ld(&sync->staged[l])) <= want) {
-            __builtin_amdgcn_s_sleep(1);
-            if (++spins > spin_limit || walk_ld(&sync->err)) { failed = true; break; }
-        }
-        seen[l] = st;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    };
-    auto read_record = [&](int l, int h, float (&c)[NC], int32_t (&r)[NC], float& wt, float& len) {
-        const int slot = h % ring;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-            c[q] = 0.f; r[q] = 0x7FFFFFFF;
-            if (q < CP) { c[q] = cells[(l * ring + slot) * wpad + lane + 64 * q]; r[q] = ranks[(l * ring + slot) * wpad + lane + 64 * q]; }
-        }
-        const int line = ridx[l * 256 + slot];
-        wt = rwt[l * 256 + slot];
-        const float rest = (float)(n - line);
-        len = rest < nh ? rest : nh;
-    };
-    auto overlap = [&](const float (&c)[NC], const int32_t (&r)[NC], int taken_other) -> float {
-        double x = 0.0;
-        bool any = false;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) { const bool in = r[q] < taken_other; any |= in; x += in ? (double)c[q] : 0.0; }
-        if (__ballot(any) == 0ull) return 0.f;             // no crossed line taken yet: nothing to add up
-        return (float)wave_sum_f64(x);
-    };
-    // the heads are published (slots handed back to the stagers) every eighth pick
-    if (n > 0) { wait_record(0, 0); wait_record(1, 0); }
-    if (!failed) { read_record(0, 0, c_s, r_s, w_s, l_s); read_record(1, 0, c_v, r_v, w_v, l_v); }
-    float ol_s = 0.f, ol_v = 0.f;
-    bool dirty_s = true, dirty_v = true;
-    auto crosses = [&](const int32_t (&r)[NC], int rank) -> bool {       // does the line of that rank cross this head's cells?
-        bool hit = false;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) hit |= r[q] == rank;
-        return __ballot(hit) != 0ull;
-    };
-    int picks = 0;
-    while (!failed && sum < target && (is < n || iv < n)) {
-        const bool has_s = is < n, has_v = iv < n;
-        // an overlap is summed again only when its set of taken crossed lines changed: a new list head, or the
-        // line just taken from the other list crosses this head inside the window
-        if (has_s && dirty_s) { ol_s = overlap(c_s, r_s, iv); dirty_s = false; }
-        if (has_v && dirty_v) { ol_v = overlap(c_v, r_v, is); dirty_v = false; }
-        const float ds = has_s ? __fsub_rn(w_s, ol_s) : 0.f;
-        const float dv = has_v ? __fsub_rn(w_v, ol_v) : 0.f;
-        bool take_s;
-        if (!has_v) take_s = true;
-        else if (!has_s) take_s = false;
-        else {
-            float cs = __fsub_rn(l_s, (float)iv); if (cs < 1.0f) cs = 1.0f;
-            float cv = __fsub_rn(l_v, (float)is); if (cv < 1.0f) cv = 1.0f;
-            take_s = __fmul_rn(ds, cv) >= __fmul_rn(dv, cs);
-        }
-        if (take_s) {
-            sum = __fadd_rn(sum, ds);
-            ++is;
-            dirty_s = true;
-            dirty_v = dirty_v || crosses(r_v, is - 1);
-            if (is < n && !(sum >= target)) { wait_record(0, is); if (!failed) read_record(0, is, c_s, r_s, w_s, l_s); }
-        } else {
-            sum = __fadd_rn(sum, dv);
-            ++iv;
-            dirty_v = true;
-            dirty_s = dirty_s || crosses(r_s, iv - 1);
-            if (iv < n && !(sum >= target)) { wait_record(1, iv); if (!failed) read_record(1, iv, c_v, r_v, w_v, l_v); }
-        }
-        if ((++picks & 7) == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // done reading the records left behind
-            if (lane == 0) { walk_st(&sync->head[0], is); walk_st(&sync->head[1], iv); }
-        }
-    }
-    if (lane == 0) {
-        if (failed) { walk_st(&sync->err, 1); atomicOr(a.status, STAT_WALK_TIMEOUT); }
-        walk_st(&sync->done, 1);
-        // a wait that ran into its bound reports every line selected (the coverage target still holds)
-        a.s_cnt[bh] = failed ? n : is;
-        a.v_cnt[bh] = failed ? n : iv;
+    if (tid == 0) {
+        a.s_cnt[bh] = X.id == 0 ? X.taken : O.taken;
+        a.v_cnt[bh] = X.id == 0 ? O.taken : X.taken;
         if (a.accounted) a.accounted[bh] = sum;
     }
 }
@@ -1329,9 +1476,7 @@ hipError_t init_select_kernels() {
     if ((e = allow_full_lds(&sort_merge_kernel<4096>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&sort_merge_kernel<SORT_SEG_MAX>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_kernel)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&walk_exact_kernel<1>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&walk_exact_kernel<2>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&walk_exact_kernel<4>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&walk_exact_kernel)) != hipSuccess) return e;
     if ((e = allow_full_lds(&merge_lines_kernel)) != hipSuccess) return e;
     return allow_full_lds(&emit_kernel);
 }
@@ -1356,12 +1501,8 @@ hipError_t run_select_exact(const SelectArgs& a, hipStream_t st) {
                  : want <= 4096         ? launch_sort<4096>(a, st)
                                         : launch_sort<SORT_SEG_MAX>(a, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(rank_kernel, dim3((unsigned)((a.n + 255) / 256), a.BH, 2), dim3(256), 0, st, a);
-    const size_t xw = 2 * XW_CELLS * 8 + 2 * 256 * 8 + sizeof(XwSync) + 16;
-    if (a.w <= 64) hipLaunchKernelGGL(walk_exact_kernel<1>, dim3(a.BH), dim3(XW_THREADS), xw, st, a);
-    else if (a.w <= 128) hipLaunchKernelGGL(walk_exact_kernel<2>, dim3(a.BH), dim3(XW_THREADS), xw, st, a);
-    else hipLaunchKernelGGL(walk_exact_kernel<4>, dim3(a.BH), dim3(XW_THREADS), xw, st, a);
     const size_t smem = (size_t)((a.n + 31) / 32) * 4;
+    hipLaunchKernelGGL(walk_exact_kernel, dim3(a.BH), dim3(XW_THREADS), 2 * smem, st, a);
     hipLaunchKernelGGL(emit_kernel, dim3(2, a.BH), dim3(1024), smem, st, a);
     return hipGetLastError();
 }

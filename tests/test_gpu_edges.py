@@ -120,3 +120,50 @@ def test_retention_score_chunks(oracle, Hq, Hkv, ln, n_obs, d, dtype):
     score = torch.empty((1, Hkv, ln), dtype=torch.float32, device="cuda")
     pipe.ctx.debug_compress_score(pipe.shape, score)
     np.testing.assert_allclose(score.cpu().numpy(), ref["score"], rtol=1e-3, atol=1e-6 * n_obs)
+
+
+@pytest.mark.parametrize("n,w,alpha,kind", [
+    (1, 1, 0.9, "spiky"),
+    (65, 64, 0.95, "spiky"),               # the window is almost the context
+    (1024, 33, 1.0, "flat"),               # one block of candidates, every line taken
+    (1025, 256, 0.95, "flat"),             # a block of one candidate; longest window
+    (3000, 97, 0.95, "spiky"),             # picks change lists all the time
+    (5000, 64, 0.98, "ties"),              # few distinct weights: sums with ties in rounding, long runs
+    (2500, 40, 0.9, "repeated"),           # scoring positions given, some of them twice
+    (262144, 2, 0.3, "flat"),              # longest context: largest bitmaps
+])
+def test_exact_walk_rounds(oracle, n, w, alpha, kind):
+    """ls_select_exact on synthetic window matrices against the oracle, to the last bit."""
+    from tests.gpu_util import host
+    from tests.test_gpu_configs import check_selection_exact
+    print(f"exact walk n={n} w={w} alpha={alpha} {kind}", flush=True)
+    rng = np.random.default_rng(n + w)
+    H = 2
+    pos = None
+    if kind == "repeated":
+        pos = np.sort(rng.integers(n // 2, n, w)); pos[1] = pos[0]
+    p = np.arange(n - w, n) if pos is None else pos
+    a = rng.exponential(size=(1, H, w, n)) ** (4 if kind == "spiky" else 1)
+    if kind == "ties":
+        a = np.round(a * 2) / 8 + 0.125
+    a[0, :, np.arange(n)[None, :] > p[:, None]] = 0
+    a = np.ascontiguousarray((a if kind == "ties" else a / a.sum(-1, keepdims=True)).astype(np.float32))
+    vert = a.sum(2, dtype=np.float64)
+    slash = np.zeros((1, H, n))
+    for t in range(w):
+        slash[0, :, :p[t] + 1] += a[0, :, t, p[t]::-1] if p[t] < n else 0
+    sc = dict(vert=vert.astype(np.float32), slash=slash.astype(np.float32), total=vert.sum(-1).astype(np.float32))
+    n_hat = max(w, n // 3)
+    ref = oracle.select_exact(a, sc, n_hat, alpha, q_pos=pos)
+    shape = binding.make_shape(1, H, 1, 64, n, n_hat, w, "f32", 0.0)
+    ctx = binding.Context(shape)
+    out = binding.alloc_select(shape, accounted=True)
+    dev = {k: torch.from_numpy(v).cuda() for k, v in sc.items()}
+    ctx.ls_select_exact(shape, alpha, torch.from_numpy(a).cuda(), dev["vert"], dev["slash"], dev["total"], out["v_idx"],
+                        out["v_cnt"], out["s_idx"], out["s_cnt"], out["accounted"],
+                        None if pos is None else torch.from_numpy(pos.astype(np.int64)).cuda())
+    assert ctx.ls_poll_status() == 0
+    gpu = host(out)
+    print("  picks", ref["v_cnt"].ravel().tolist(), ref["s_cnt"].ravel().tolist(), flush=True)
+    check_selection_exact(gpu, ref)
+    np.testing.assert_array_equal(gpu["accounted"], ref["accounted"])
