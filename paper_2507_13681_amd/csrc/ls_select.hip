@@ -274,13 +274,15 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_merge_kernel(SelectArgs a) 
 }
 
 // ---- running sums in binary32, many additions at a time ------------------------------------------
-// s <- fl(s + g[i]) for one i after the other is a chain of dependent additions, but while s stays inside one binade
-// it is a chain of integer additions: with u the spacing of the binade and s = m u, fl(s + g) = u (m + floor(g / u) +
-// c) where c rounds the fraction of g / u to nearest, a tie to the even m + floor(g / u) + c.  Everything but the
-// tie is independent of m, and the tie depends on m's parity alone, so an entry is a pair of increments, one per
-// parity, and pairs compose: a scan over the lanes gives every partial sum of the chain, bit for bit.
-// Where the chain leaves the binade one entry is added the ordinary way; where the gains are not small against
-// the sum (its first entries), or negative, 64 entries are.
+// s <- fl(s + g[i]) for one i after the other is a chain of dependent additions, 5 cycles each for a wave by itself.
+// But while s stays inside one binade, with u the spacing of its numbers and s = m u, what a stretch of additions
+// adds to m depends on m only through its parity (to which the ties round).  So each lane runs its stretch of
+// entries twice, from an even and an odd m in the middle of the binade, a scan over the lanes composes the pairs of
+// increments and gives every lane the exact sum it starts from, and the lane's entries are then added to that.  All of
+// it is valid up to the first lane that leaves the binade (itself included: its additions are ordinary ones), or
+// whose gains are not small against the sum or negative; the next step goes on behind that lane.  64 entries are added
+// the ordinary way where that is the first lane (the first entries of a chain: the sum is not yet large against
+// them).  16 entries a lane: 700 cycles a step, 1024 additions one by one 5700.
 
 // increments of a stretch of the chain that starts at an even (e) or odd (o) m
 struct ChainInc { int32_t e, o; };
@@ -293,6 +295,17 @@ __device__ __forceinline__ ChainInc chain_dpp(ChainInc x) {        // lanes with
 }
 // of the lanes to the left, in order
 __device__ __forceinline__ ChainInc chain_before(ChainInc x) {
+    if (__ballot(x.e != x.o) == 0ull) {                    // no tie anywhere: plain sums (most stretches of a long chain)
+        int32_t s = x.e;
+        s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);
+        s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);
+        s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);
+        s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);
+        s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xA, 0xF, false);
+        s += __builtin_amdgcn_update_dpp(0, s, 0x143, 0xC, 0xF, false);
+        s -= x.e;
+        return {s, s};
+    }
     x = chain_then(chain_dpp<0x111, 0xF>(x), x);           // row_shr:1, 2, 4, 8
     x = chain_then(chain_dpp<0x112, 0xF>(x), x);
     x = chain_then(chain_dpp<0x114, 0xF>(x), x);
@@ -320,85 +333,89 @@ __device__ __forceinline__ V pick_entry(const V (&v)[E], int i) {
     return __builtin_bit_cast(V, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i / E));
 }
 
-// Lane l holds the gains of the entries E l .. E l + E - 1 (0 from entry `limit` on).  Adds entries 0 .. `limit` - 1 to
-// `sum` (which is below `target`) in order until it reaches the target or they are used up; returns how many were
-// added.
+// Lane l holds the gains of the entries E l .. E l + E - 1.  x[e] = the sum behind entry e, starting from `sum` ahead of
+// lane `first`; valid in the lanes from `first` to the one returned.
+template <int E>
+__device__ __forceinline__ int chain_step(const float (&g)[E], int lane, int first, float sum, bool plain, float (&x)[E]) {
+    const uint32_t sb = __builtin_bit_cast(uint32_t, sum), binade = sb & 0x7F800000u;
+    if (plain || sb < (64u << 23) || sb > (250u << 23)) {  // (the first sum is 0, and gains may be negative in the end)
+#pragma unroll
+        for (int e = 0; e < E; ++e) x[e] = 0.f;
+        for (int p = 0; p < 64 / E; ++p) {                 // pass p settles lane first + p
+            float left = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x[E - 1]), 0x138 /* wave_shr:1 */, 0xF, 0xF, true));
+            left = lane == first ? sum : left;
+            x[0] = __fadd_rn(left, g[0]);
+#pragma unroll
+            for (int e = 1; e < E; ++e) x[e] = __fadd_rn(x[e - 1], g[e]);
+        }
+        return first + 64 / E < 64 ? first + 64 / E - 1 : 63;
+    }
+    const uint32_t even = binade | 0x400000u;              // 1.5 times the binade's first number, and the next one
+    float xe = __builtin_bit_cast(float, even), xo = __builtin_bit_cast(float, even + 1u), least = g[0];
+#pragma unroll
+    for (int e = 0; e < E; ++e) { xe = __fadd_rn(xe, g[e]); xo = __fadd_rn(xo, g[e]); least = fminf(least, g[e]); }
+    const bool idle = lane < first;
+    const bool small = xo < __builtin_bit_cast(float, binade + 0x800000u) && least >= 0.f;
+    ChainInc inc = {0, 0};
+    if (small && !idle) inc = {(int32_t)(__builtin_bit_cast(uint32_t, xe) - even), (int32_t)(__builtin_bit_cast(uint32_t, xo) - (even + 1u))};
+    const ChainInc before = chain_before(inc);
+    const int32_t m0 = (int32_t)(sb & 0x7FFFFFu);
+    const int32_t m = m0 + ((m0 & 1) ? before.o : before.e);               // less 2^23
+    const uint64_t leave = __ballot(!idle && (!small || m + ((m & 1) ? inc.o : inc.e) >= 1 << 23));
+    x[0] = __fadd_rn(__builtin_bit_cast(float, binade | ((uint32_t)m & 0x7FFFFFu)), g[0]);
+#pragma unroll
+    for (int e = 1; e < E; ++e) x[e] = __fadd_rn(x[e - 1], g[e]);
+    return leave != 0ull ? __ffsll((unsigned long long)leave) - 1 : 63;
+}
+// Adds entries 0 .. `limit` - 1 (the gains are 0 from there on) to `sum`, which is below `target`, in order until it
+// reaches the target or they are used up; returns how many were added.
 template <int E>
 __device__ __forceinline__ int chain_until(const float (&g)[E], int lane, int limit, float target, float& sum) {
-    constexpr float SMALL = 524288.f;                      // 2^19: 64 E of them stay below 2^30 for E <= 32
-    int at = 0;
-    bool plain = false;                                    // the next entries are not small against the sum
-    while (at < limit) {
-        const uint32_t sb = __builtin_bit_cast(uint32_t, sum);
-        const int ex = (int)(sb >> 23);
-        const int lo = at - E * lane;                      // this lane's entries from `lo` on are still to come
-        float h[E];
+    if (limit == 0) return 0;
+    int first = 0;
+    bool plain = false;
+    for (;;) {
+        float x[E];
+        const int last = chain_step<E>(g, lane, first, sum, plain, x);
+        int fe = E;
 #pragma unroll
-        for (int e = 0; e < E; ++e) h[e] = e >= lo ? g[e] : 0.f;
-        if (plain || ex < 64 || ex > 250) {                // (the first sum is 0)
-            // the lanes first .. first + 64 / E - 1, one after the other
-            const int first = at / E, lanes = 64 / E;
-            float x[E];
-#pragma unroll
-            for (int e = 0; e < E; ++e) x[e] = 0.f;
-            for (int p = 0; p < lanes; ++p) {
-                float left = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x[E - 1]), 0x138 /* wave_shr:1 */, 0xF, 0xF, true));
-                left = lane == first ? sum : left;
-                x[0] = __fadd_rn(left, h[0]);
-#pragma unroll
-                for (int e = 1; e < E; ++e) x[e] = __fadd_rn(x[e - 1], h[e]);
-            }
-            int fe = E;
-#pragma unroll
-            for (int e = E - 1; e >= 0; --e) fe = x[e] < target || e < lo ? fe : e;
-            const int j = first_entry<E>(lane >= first && lane < first + lanes ? fe : E);
-            if (j < limit) { sum = pick_entry(x, j); return j + 1; }
-            at = E * (first + lanes) < limit ? E * (first + lanes) : limit;
-            sum = pick_entry(x, at - 1);
-            plain = false;
-            continue;
-        }
-        const float per_u = __builtin_bit_cast(float, (uint32_t)(277 - ex) << 23);        // 1 / u = 2^(150 - ex)
-        const int m0 = (int)((sb & 0x7FFFFFu) | 0x800000u);
-        const float tf = target * per_u;
-        const int bound = tf < 16777216.f ? (int)ceilf(tf) : 1 << 24;  // first m that reaches the target, or has left the binade
-        int q[E];                                          // floor(g / u) * 4 + 2 (fraction > 1/2) + 1 (fraction = 1/2)
-        int big = E;                                       // first entry that is not small
-        int32_t me = 0, mo = 1;
-#pragma unroll
-        for (int e = E - 1; e >= 0; --e) {
-            float r = h[e] * per_u;
-            const bool small = r >= 0.f && r < SMALL;
-            big = small ? big : e;
-            r = small ? r : 0.f;
-            const float f = floorf(r), fr = r - f;
-            q[e] = 4 * (int)f + (fr > 0.5f ? 2 : fr == 0.5f ? 1 : 0);
-        }
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            me += q[e] >> 2; me += ((q[e] >> 1) & 1) + (me & q[e] & 1);
-            mo += q[e] >> 2; mo += ((q[e] >> 1) & 1) + (mo & q[e] & 1);
-        }
-        const ChainInc before = chain_before({me, mo - 1});
-        int m[E];
-        int32_t run = m0 + ((m0 & 1) ? before.o : before.e);
-        int fe = big;
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            run += q[e] >> 2; run += ((q[e] >> 1) & 1) + (run & q[e] & 1);
-            m[e] = run;
-            fe = run >= bound && e < fe ? e : fe;
-        }
-        const int j0 = first_entry<E>(fe), j = j0 < limit ? j0 : limit;
-        if (j > at) sum = __builtin_bit_cast(float, ((uint32_t)ex << 23) | ((uint32_t)pick_entry(m, j - 1) & 0x7FFFFFu));
-        at = j;
-        if (j == limit) break;
-        if (__builtin_amdgcn_readlane(big, j / E) == j % E) { plain = true; continue; }
-        sum = __fadd_rn(sum, pick_entry(g, j));            // reaches the target, or the next binade
-        at = j + 1;
-        if (!(sum < target)) break;
+        for (int e = E - 1; e >= 0; --e) fe = x[e] < target ? fe : e;
+        const int j = first_entry<E>(lane >= first && lane <= last ? fe : E);
+        if (j < limit) { sum = pick_entry(x, j); return j + 1; }
+        const bool end = E * (last + 1) >= limit;          // (the entries behind `limit` add 0)
+        sum = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[E - 1]), end ? (limit - 1) / E : last));
+        if (end) return limit;
+        plain = !plain && last == first;
+        first = last + 1;
     }
-    return at;
+}
+// Writes pre[i] = acc + (the entries before entry i, added left to right in binary32) for the 64 E entries, and returns
+// the sum behind the last one.  The first `again_end` of them (whole lanes) go to `again` as well.  E is even.
+template <int E>
+__device__ __forceinline__ float chain_prefix(const float (&g)[E], int lane, float acc, float* pre, float* again, int again_end) {
+    float x[E];                                            // the sum behind each entry
+    float sum = acc;
+    int first = 0;
+    bool plain = false;
+    while (first < 64) {
+        float y[E];
+        const int last = chain_step<E>(g, lane, first, sum, plain, y);
+#pragma unroll
+        for (int e = 0; e < E; ++e) x[e] = lane >= first ? y[e] : x[e];    // (behind `last` it is written again)
+        sum = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, y[E - 1]), last));
+        plain = !plain && last == first;
+        first = last + 1;
+    }
+    const float left = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x[E - 1]), 0x138 /* wave_shr:1 */, 0xF, 0xF, true));
+    auto put = [&](float* p) {
+        float2* dst = reinterpret_cast<float2*>(p + E * lane);
+        dst[0] = make_float2(lane == 0 ? acc : left, x[0]);
+#pragma unroll
+        for (int e = 2; e < E; e += 2) dst[e / 2] = make_float2(x[e - 1], x[e]);
+    };
+    put(pre);
+    if (E * lane < again_end) put(again);
+    return sum;
 }
 // the same with the gains in LDS (64 E floats, 16-byte aligned)
 template <int E>
@@ -423,10 +440,9 @@ __device__ __forceinline__ int chain_lds(const float* gains, int lane, int limit
 //     order) through a small ring in LDS, and whatever was decided beyond the pick that reaches the target
 //     is dropped.
 // What stays sequential are two chains of binary32 additions, one add per line each: the overlap prefix sums
-// and `sum` with its exit test after every pick.  Both are evaluated by a wave whose lanes hold consecutive
-// entries and pass the last partial sum to the right neighbour, one lane settling per pass, so every value is
-// the one the sequential loop would hold and each pick sees exactly the operands, operation order and
-// roundings of the definition.
+// and `sum` with its exit test after every pick.  Both are evaluated by the integer scan above, whose values are the
+// ones the sequential loop would hold: each pick sees exactly the operands, operation order and roundings of the
+// definition.
 constexpr int WALK_THREADS = 384;              // wave 0 decides the runs, wave 2 sums them; per list, waves 1 / 3 stage its
                                                // weights and lengths and waves 4 / 5 its overlap prefix sums
 constexpr int WALK_E = 8;                      // consecutive list entries a lane looks at: a run has up to 64 * E picks
@@ -437,8 +453,9 @@ constexpr int WALK_EB = WALK_BLK / 64;         // entries per lane when a block'
 static_assert(WALK_EB % 2 == 0 && WALK_RUN <= WALK_BLK, "a run never reaches beyond the block after the head's");
 
 // The resident part of one sorted list, indexed by sorted position modulo WALK_CAP: weights, line lengths, and
-// pre[p] = the overlap sum when the first p lines of the list have been taken.
-struct WalkList { float cw[WALK_CAP], cl[WALK_CAP], pre[WALK_CAP]; };
+// pre[p] = the overlap sum when the first p lines of the list have been taken.  The first WALK_RUN entries are
+// there a second time behind the last one, so that a run's entries are consecutive wherever it starts.
+struct WalkList { float cw[WALK_CAP + WALK_RUN], cl[WALK_CAP + WALK_RUN], pre[WALK_CAP + WALK_RUN]; };
 // One run of picks from one list: the gain of each pick, how many of them count, and whether the walk ends
 // after them because no line is left that adds anything.
 struct WalkRun { float g[WALK_RUN]; int which, limit, last, pad; };
@@ -449,35 +466,6 @@ constexpr size_t WALK_LDS_BYTES = 2 * sizeof(WalkList) + WALK_RING * sizeof(Walk
 
 __device__ __forceinline__ int walk_ld(const int* p) { return __builtin_amdgcn_readfirstlane(__atomic_load_n(p, __ATOMIC_RELAXED)); }
 __device__ __forceinline__ void walk_st(int* p, int v) { __atomic_store_n(p, v, __ATOMIC_RELAXED); }
-
-// Lane j holds the maxima m[0 .. E) of the list entries p0 + E j .. p0 + E j + E - 1.  Writes pre[i] = acc + (the
-// maxima of the entries before entry i of the block, added left to right in binary32) for the 64 E entries of
-// the block, pre pointing at the block's first entry, and returns the sum behind the last entry.  E is even.
-template <int E>
-__device__ __forceinline__ float walk_scan(const float (&m)[E], float* pre, float acc, int lane) {
-    float x[E];
-    // lane 0 has no left neighbour: the shift hands it 0, and its first addend is acc + m[0], so it holds exactly that
-    const float addend0 = lane == 0 ? __fadd_rn(acc, m[0]) : m[0];
-#pragma unroll
-    for (int e = 0; e < E; ++e) x[e] = 0.f;
-    for (int p = 0; p < 64; p += 2) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const float left = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-                0, __builtin_bit_cast(int, x[E - 1]), 0x138 /* wave_shr:1 */, 0xF, 0xF, true));
-            x[0] = __fadd_rn(left, addend0);
-#pragma unroll
-            for (int e = 1; e < E; ++e) x[e] = __fadd_rn(x[e - 1], m[e]);
-        }
-    }
-    const float left = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-        0, __builtin_bit_cast(int, x[E - 1]), 0x138 /* wave_shr:1 */, 0xF, 0xF, true));
-    float2* dst = reinterpret_cast<float2*>(pre + E * lane);
-    dst[0] = make_float2(lane == 0 ? acc : left, x[0]);
-#pragma unroll
-    for (int e = 2; e < E; e += 2) dst[e / 2] = make_float2(x[e - 1], x[e]);
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x[E - 1]), 63));
-}
 
 // ix[e] = the line at sorted position pos + e (the last line's index past the end of the list)
 template <int E>
@@ -507,16 +495,16 @@ __device__ __forceinline__ void walk_maxima(const float* m_l, const int32_t (&ix
     }
 }
 
-// Position of the first entry for which `p` holds, in the order entry 0 of lane 0, entry 1 of lane 0, ..., entry 0
-// of lane 1, ... (WALK_RUN if it holds nowhere): every lane finds its own first entry, one ballot finds the lane.
+// Position of the first entry for which `p` holds, in the order entry 0 of lane 0, entry 0 of lane 1, ..., entry 1 of
+// lane 0, ... (WALK_RUN if it holds nowhere)
 __device__ __forceinline__ int walk_first(const bool (&p)[WALK_E]) {
-    int fe = WALK_E;
+    int at = WALK_RUN;
 #pragma unroll
-    for (int e = WALK_E - 1; e >= 0; --e) fe = p[e] ? e : fe;
-    const uint64_t any = __ballot(fe < WALK_E);
-    if (any == 0ull) return WALK_RUN;
-    const int l = __ffsll((unsigned long long)any) - 1;
-    return WALK_E * l + __builtin_amdgcn_readlane(fe, l);
+    for (int e = WALK_E - 1; e >= 0; --e) {
+        const uint64_t any = __ballot(p[e]);
+        at = any != 0ull ? 64 * e + __ffsll((unsigned long long)any) - 1 : at;
+    }
+    return at;
 }
 
 // grid (BH).  Reads the sorted lists (weights, maxima, indices) and writes taken counts.
@@ -600,6 +588,7 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
                 const int len = n - fx[j] < nh32 ? n - fx[j] : nh32;       // line length in the n_hat x n block
                 L.cw[slot + i] = in ? fw[j] : 0.f;
                 L.cl[slot + i] = in ? (float)len : 1.f;
+                if (slot == 0 && 64 * j < WALK_RUN) { L.cw[WALK_CAP + i] = in ? fw[j] : 0.f; L.cl[WALK_CAP + i] = in ? (float)len : 1.f; }
             }
             fetch(b + 1);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -612,10 +601,7 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
 
     if (wv == 4 || wv == 5) {
         // ------------------------------------------------------------------ overlap prefix sums of one list
-        // One add after the other, in list order.  Lane j owns E consecutive entries; a pass is "take the last sum
-        // of the lane to the left, add my E maxima one after the other", and pass p settles lane p, so 64 passes
-        // leave every lane with the sums the sequential loop would hold (the lanes to the right of the settled
-        // ones compute values that the later passes replace).
+        // (one addition after the other took 5700 cycles a block)
         const int l = wv - 4;
         WalkList& L = lists[l];
         const int32_t* i_l = a.sidx1 + (l == 0 ? seg_s : seg_v);
@@ -641,7 +627,7 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
             walk_maxima<WALK_EB>(m_l, ix, (b + 1) * WALK_BLK + WALK_EB * lane, n, mn);
             walk_indices<WALK_EB>(i_l, (b + 2) * WALK_BLK + WALK_EB * lane, n, ix);
-            acc = walk_scan<WALK_EB>(m, L.pre + (b & (WALK_NBLK - 1)) * WALK_BLK, acc, lane);
+            acc = chain_prefix<WALK_EB>(m, lane, acc, L.pre + (b & (WALK_NBLK - 1)) * WALK_BLK, L.pre + WALK_CAP, (b & (WALK_NBLK - 1)) == 0 ? WALK_RUN : 0);
 #pragma unroll
             for (int e = 0; e < WALK_EB; ++e) m[e] = mn[e];
             if (b == nblk - 1 && lane == 0) sync->tot[l] = acc;
@@ -681,48 +667,19 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
             const int which = __builtin_amdgcn_readfirstlane(R.which);
             const int limit = __builtin_amdgcn_readfirstlane(R.limit);
             const int last = __builtin_amdgcn_readfirstlane(R.last);
-            float g[WALK_E], x[WALK_E];
+            float g[WALK_E];
 #pragma unroll
             for (int e = 0; e < WALK_E; e += 2) {
                 const float2 t = *reinterpret_cast<const float2*>(&R.g[WALK_E * lane + e]);
-                g[e] = t.x; g[e + 1] = t.y;
-            }
-            // Lane j ends up with the running sums after its E picks: x[0] = (x[E-1] of lane j-1) + g[0], x[e] =
-            // x[e-1] + g[e], lane 0 starting from `sum`.  One pass of "take the left neighbour's last sum, add my
-            // gains one after the other" over all lanes settles one more lane, in order, so ceil(limit / E) passes
-            // reproduce the pick-by-pick additions exactly; the first entry whose sum reaches the target is the
-            // pick the loop of the definition stops after.  (Lane 0 has no left neighbour: the shift hands it 0 and
-            // its first addend is sum + g[0], so it holds exactly that.)
-            const float addend0 = lane == 0 ? __fadd_rn(sum, g[0]) : g[0];
-#pragma unroll
-            for (int e = 0; e < WALK_E; ++e) x[e] = 0.f;
-            for (int p0 = 0; p0 < limit; p0 += 4 * WALK_E) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float left = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-                        0, __builtin_bit_cast(int, x[WALK_E - 1]), 0x138 /* wave_shr:1 */, 0xF, 0xF, true));
-                    x[0] = __fadd_rn(left, addend0);
-#pragma unroll
-                    for (int e = 1; e < WALK_E; ++e) x[e] = __fadd_rn(x[e - 1], g[e]);
-                }
+                g[e] = WALK_E * lane + e < limit ? t.x : 0.f; g[e + 1] = WALK_E * lane + e + 1 < limit ? t.y : 0.f;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // the slot may be written again
             ++k;
             if (lane == 0) walk_st(&sync->summed, k);
-            // entry e of lane j is pick E * j + e; only picks below `limit` count
-            bool hm[WALK_E];
-#pragma unroll
-            for (int e = 0; e < WALK_E; ++e) hm[e] = !(x[e] < target) && WALK_E * lane + e < limit;
-            const int hit = walk_first(hm);
-            const bool reached = hit < WALK_RUN;
-            const int taken = reached ? hit + 1 : limit;                    // picks applied
-            if (taken > 0) {
-                const int te = (taken - 1) % WALK_E;
-                float xs = x[0];
-#pragma unroll
-                for (int e = 1; e < WALK_E; ++e) xs = te == e ? x[e] : xs;
-                sum = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, xs), (taken - 1) / WALK_E));
-            }
+            // pick by pick, as the loop of the definition adds them; it stops after the pick that reaches the target
+            // (one addition after the other took 3900 cycles a run)
+            const int taken = chain_until<WALK_E>(g, lane, limit, target, sum);
+            const bool reached = !(sum < target);
             cnt_s += which == 0 ? taken : 0;
             cnt_v += which == 0 ? 0 : taken;
             if (!reached && last) { all = true; break; }  // the pick after the last one has no positive gain
@@ -763,26 +720,20 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
         return have;
     };
 
-    // What the lanes need of a list when its head is at `h`: lane l looks at the entries h + E l .. h + E l + E - 1
-    // (weight, overlap prefix, length), every lane at the head's own three values.  Re-read only when the head of
-    // that list moves.  (All of them lie in the head's block or the one after it.)
-    struct View { float cw[WALK_E], pre[WALK_E], cl[WALK_E], w0, l0, ol0; bool ok[WALK_E], has; };
+    // What the lanes need of a list when its head is at `h`: lane l looks at the entries h + l, h + 64 + l, ... (weight,
+    // overlap prefix, length; whatever lies there past the end of the list), every lane at the head's own three values.
+    // Re-read only when the head of that list moves.  (All of them lie in the head's block or the one after it.)
+    struct View { float cw[WALK_E], pre[WALK_E], cl[WALK_E], w0, l0, ol0; };
+    auto lane0 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x))); };
     auto view = [&](int l, int h) {
         const WalkList& L = lists[l];
         View r;
+        const int at = (h & (WALK_CAP - 1)) + lane;
 #pragma unroll
-        for (int e = 0; e < WALK_E; ++e) {
-            const int i = h + WALK_E * lane + e;
-            r.ok[e] = i < n;
-            const int ii = (i < n ? i : n - 1) & (WALK_CAP - 1);           // nothing is read from a block that never comes
-            r.cw[e] = L.cw[ii]; r.pre[e] = L.pre[ii]; r.cl[e] = L.cl[ii];
-        }
-        r.has = h < n;
-        const int hh = (r.has ? h : n - 1) & (WALK_CAP - 1);
-        r.w0 = r.has ? L.cw[hh] : 0.f;                     // an exhausted list: no weight, and its overlap sum
-        r.l0 = r.has ? L.cl[hh] : 1.f;                     // sits right behind its last line
-        r.ol0 = r.has ? L.pre[hh] : sync->tot[l];
-        return r;
+        for (int e = 0; e < WALK_E; ++e) { r.cw[e] = L.cw[at + 64 * e]; r.pre[e] = L.pre[at + 64 * e]; r.cl[e] = L.cl[at + 64 * e]; }
+        if (h < n) { r.w0 = lane0(r.cw[0]); r.l0 = lane0(r.cl[0]); r.ol0 = lane0(r.pre[0]); }
+        else { r.w0 = 0.f; r.l0 = 1.f; r.ol0 = lane0(sync->tot[l]); }      // an exhausted list: no weight, and its overlap sum
+        return r;                                                          // sits right behind its last line
     };
     // blocks a view at head h reads: through the block of entry h + RUN - 1, and pre[h] itself
     auto blocks_for = [&](int h) {
@@ -817,43 +768,47 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
             if (failed) break;
             V = view(1, iv);
         }
-        const bool s_has = S.has, v_has = V.has;
-        // entry e of lane j: the decision if the walk has taken E j + e more slashes (iv frozen)
+        // entry e of lane l: the decision if the walk has taken 64 e + l more slashes (iv frozen)
         float gain[WALK_E];
-        bool turn[WALK_E], dead[WALK_E];           // the pick goes to the other list; no gain is left
+        bool turn[WALK_E];                     // the pick goes to the other list
+        const float fs = (float)is, fv = (float)iv;
+        int run = 0, which = 0;
+        if (is < n) {
 #pragma unroll
-        for (int e = 0; e < WALK_E; ++e) {
-            const int i = is + WALK_E * lane + e;
-            const float ds = __fsub_rn(S.cw[e], V.ol0);
-            const float dv = __fsub_rn(V.w0, S.pre[e]);
-            float cs = __fsub_rn(S.cl[e], (float)iv); if (cs < 1.0f) cs = 1.0f;
-            float cv = __fsub_rn(V.l0, (float)i); if (cv < 1.0f) cv = 1.0f;
-            turn[e] = !(S.ok[e] && (!v_has || __fmul_rn(ds, cv) >= __fmul_rn(dv, cs)));
-            dead[e] = !(ds > 0.f) && (!v_has || !(dv > 0.f));
-            gain[e] = ds;
+            for (int e = 0; e < WALK_E; ++e) {
+                const float ds = __fsub_rn(S.cw[e], V.ol0), dv = __fsub_rn(V.w0, S.pre[e]);
+                const float cs = fmaxf(__fsub_rn(S.cl[e], fv), 1.0f), cv = fmaxf(__fsub_rn(V.l0, fs + (float)(64 * e + lane)), 1.0f);
+                turn[e] = !(__fmul_rn(ds, cv) >= __fmul_rn(dv, cs));
+                gain[e] = ds;
+            }
+            run = iv < n ? walk_first(turn) : WALK_RUN;
+            run = run < n - is ? run : n - is;
         }
-        int run = walk_first(turn);
-        int which = 0;
         if (run == 0) {
-            // the head pick is a vertical; entry e of lane j: the decision if E j + e more verticals are taken (is frozen)
+            // the head pick is a vertical; entry e of lane l: the decision if 64 e + l more verticals are taken (is frozen)
             which = 1;
 #pragma unroll
             for (int e = 0; e < WALK_E; ++e) {
-                const int i = iv + WALK_E * lane + e;
-                const float dv = __fsub_rn(V.cw[e], S.ol0);
-                const float ds = __fsub_rn(S.w0, V.pre[e]);
-                float cv = __fsub_rn(V.cl[e], (float)is); if (cv < 1.0f) cv = 1.0f;
-                float cs = __fsub_rn(S.l0, (float)i); if (cs < 1.0f) cs = 1.0f;
-                turn[e] = !(V.ok[e] && !(s_has && __fmul_rn(ds, cv) >= __fmul_rn(dv, cs)));           // true: not a vertical again
-                dead[e] = !(dv > 0.f) && (!s_has || !(ds > 0.f));
+                const float dv = __fsub_rn(V.cw[e], S.ol0), ds = __fsub_rn(S.w0, V.pre[e]);
+                const float cv = fmaxf(__fsub_rn(V.cl[e], fs), 1.0f), cs = fmaxf(__fsub_rn(S.l0, fv + (float)(64 * e + lane)), 1.0f);
+                turn[e] = __fmul_rn(ds, cv) >= __fmul_rn(dv, cs);          // not a vertical again
                 gain[e] = dv;
             }
-            run = walk_first(turn);
+            run = is < n ? walk_first(turn) : WALK_RUN;
+            run = run < n - iv ? run : n - iv;
         }
         if (run == 0) break;                   // cannot happen (entry 0 of lane 0 repeats the head's test); never spin
         // picks 0 .. run-1 come from list `which`; the walk ends early at a pick with no positive gain left
+        // (the gains of a run do not increase: none is 0 or less if the last entry's is not)
         int stop_dead = WALK_RUN;
-        if (early) stop_dead = walk_first(dead);
+        if (early && __ballot(!(gain[WALK_E - 1] > 0.f)) != 0ull) {
+            const bool has = which == 0 ? iv < n : is < n;
+            bool dead[WALK_E];                 // no gain is left in either list
+#pragma unroll
+            for (int e = 0; e < WALK_E; ++e)
+                dead[e] = !(gain[e] > 0.f) && (!has || !((which == 0 ? __fsub_rn(V.w0, S.pre[e]) : __fsub_rn(S.w0, V.pre[e])) > 0.f));
+            stop_dead = walk_first(dead);
+        }
         const int limit = run < stop_dead ? run : stop_dead;
         // the list's view after the run (read again above if it reaches into a block that is not resident yet)
         const View nxt = view(which, (which == 0 ? is : iv) + limit);
@@ -871,8 +826,7 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
         WalkRun& R = ring[published & (WALK_RING - 1)];
 #pragma unroll
-        for (int e = 0; e < WALK_E; e += 2)
-            *reinterpret_cast<float2*>(&R.g[WALK_E * lane + e]) = make_float2(gain[e], gain[e + 1]);
+        for (int e = 0; e < WALK_E; ++e) R.g[64 * e + lane] = gain[e];
         if (lane == 0) { R.which = which; R.limit = limit; R.last = stop_dead < run ? 1 : 0; }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         ++published;

@@ -167,3 +167,48 @@ def test_exact_walk_rounds(oracle, n, w, alpha, kind):
     print("  picks", ref["v_cnt"].ravel().tolist(), ref["s_cnt"].ravel().tolist(), flush=True)
     check_selection_exact(gpu, ref)
     np.testing.assert_array_equal(gpu["accounted"], ref["accounted"])
+
+
+@pytest.mark.parametrize("n,alpha,kind", [
+    (511, 1.0, "ties"), (513, 1.0, "ties"),      # a run of one entry less / more than the waves look at
+    (5000, 1.0, "ties"),                         # multiples of 1/8 on sums of 2^20 and more: every other addition is a tie
+    (4097, 1.0, "wide"),                         # weights over sixty binades: sums that leave theirs all the time
+    (9000, 1.0, "halves"),                       # long runs of equal gains that are half the spacing of the sum
+    (2100, 0.95, "alternate"),                   # picks that change lists all the time
+])
+def test_walk_sums(oracle, n, alpha, kind):
+    """ls_select on synthetic line weights against the oracle, to the last bit, with and without the sum."""
+    from tests.gpu_util import host
+    from tests.test_gpu_configs import check_selection_exact
+    print(f"walk sums n={n} alpha={alpha} {kind}", flush=True)
+    rng = np.random.default_rng(n)
+    H = 4
+    v, s = rng.exponential(size=(2, 1, H, n))
+    if kind == "ties":
+        v, s = v * 1e-6, np.round(s * 8) / 8 + 0.125         # (all picks are diagonals: their gains are the weights)
+        s[..., 0] = 2.0 ** 20 * (1 + np.arange(H))
+    elif kind == "wide":
+        v, s = np.exp2(60 * rng.random((2, 1, H, n)) - 50)
+    elif kind == "halves":
+        v, s = v * 1e-6, np.full((1, H, n), 2.0 ** -12); s[..., 0] = 2.0 ** 12 + 2.0 ** -11 * np.arange(H); s[..., 5] = 0.75
+    elif kind == "alternate":
+        v = np.arange(n, 0, -1)[None, None] + 0.25 * rng.random((1, H, n)); s = np.arange(n, 0, -1)[None, None] + 0.25 * rng.random((1, H, n))
+    m = 1e-3 if kind in ("halves", "alternate") else 0.05
+    sc = dict(vert=v, slash=s, vmax=v * m * rng.random((1, H, n)), smax=s * m * rng.random((1, H, n)), total=np.maximum(v.sum(-1), s.sum(-1)))
+    sc = {k: np.ascontiguousarray(x, dtype=np.float32) for k, x in sc.items()}
+    n_hat = n // 2
+    ref = oracle.select(sc, n_hat, alpha)
+    shape = binding.make_shape(1, H, 1, 64, n, n_hat, 1, "f32", 0.0)
+    ctx = binding.Context(shape)
+    dev = {k: torch.from_numpy(x).cuda() for k, x in sc.items()}
+    for accounted in (True, False):
+        out = binding.alloc_select(shape, accounted=accounted)
+        ctx.ls_select(shape, alpha, dev["vert"], dev["slash"], dev["vmax"], dev["smax"], dev["total"], out["v_idx"], out["v_cnt"],
+                      out["s_idx"], out["s_cnt"], out["accounted"])
+        assert ctx.ls_poll_status() == 0
+        print("  picks", ref["v_cnt"].ravel().tolist(), ref["s_cnt"].ravel().tolist(), flush=True)
+        gpu = {k: x for k, x in out.items() if x is not None}
+        gpu = host(gpu)
+        check_selection_exact(gpu, ref)
+        if accounted:
+            np.testing.assert_array_equal(gpu["accounted"], ref["accounted"])
