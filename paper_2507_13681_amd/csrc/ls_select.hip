@@ -42,11 +42,26 @@ constexpr int SORT_THREADS = 1024;
 constexpr int SORT_WAVES = 16;
 constexpr int SORT_SEG_MAX = 8192;             // most elements one workgroup sorts inside LDS
 constexpr int SORT_SEG_MIN = 2048;
-constexpr size_t sort_lds_bytes(int seg) { return (size_t)2 * seg * 4 + (size_t)2 * seg * 2 + SORT_WAVES * 256 * 4 + 256 * 4; }
+constexpr size_t sort_lds_bytes(int seg) { return (size_t)2 * seg * 4 + (size_t)2 * seg * 2 + 2 * SORT_WAVES * 256 * 4 + 256 * 4; }
+
+// sum over the lanes to the left and this one
+__device__ __forceinline__ uint32_t lanes_upto(uint32_t x) {
+    int32_t s = (int32_t)x;
+    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);       // row_shr:1, 2, 4, 8
+    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xA, 0xF, false);       // row_bcast15 into rows 1 and 3
+    s += __builtin_amdgcn_update_dpp(0, s, 0x143, 0xC, 0xF, false);       // row_bcast31 into rows 2 and 3
+    return (uint32_t)s;
+}
 
 // grid (segments, 2, BH): list 0 = diagonals (slash), 1 = columns (vert).  Sorts elements
 // [seg * SEG, +SEG) of one list entirely in LDS and writes the sorted keys (skey0) and their
-// line indices (sidx0) back to the same range.
+// line indices (sidx0) back to the same range; a list of one segment is finished here (sidx1, head_w, head_m).
+// What bounds it: vector instructions (the ballots of the ranks) where a wave has eight chunks to scatter, the five
+// barriers and the round trips between them where it has two.  So a pass reads the sixteen waves' counts of a digit at
+// once, scans the digits by lane shifts, and clears the other pass's counters on the side: @@.
 template <int SEG>
 __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
     constexpr int SLICE = SEG / SORT_WAVES;
@@ -55,8 +70,8 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
     uint32_t* kb1 = kb0 + SEG;
     uint16_t* ib0 = reinterpret_cast<uint16_t*>(kb1 + SEG);
     uint16_t* ib1 = ib0 + SEG;
-    uint32_t (*hist)[256] = reinterpret_cast<uint32_t (*)[256]>(ib1 + SEG);
-    uint32_t* dbase = &hist[SORT_WAVES][0];
+    uint32_t (*hists)[SORT_WAVES][256] = reinterpret_cast<uint32_t (*)[SORT_WAVES][256]>(ib1 + SEG);     // [2], by pass parity
+    uint32_t* dbase = &hists[1][SORT_WAVES - 1][0] + 256;
     const int seg = blockIdx.x, list = blockIdx.y, bh = blockIdx.z;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int64_t n = a.n;
@@ -66,23 +81,28 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
     const int64_t out0 = ((int64_t)list * a.BH + bh) * n + base0;
     // slots past the end of the list hold the largest key: they sort behind every element and, being
     // the highest local indices, turn behind equal keys as well
-    for (int i = tid; i < SEG; i += SORT_THREADS) {
-        kb0[i] = i < cnt ? desc_key(src[i]) : 0xFFFFFFFFu;
-        ib0[i] = (uint16_t)i;
-    }
     const int lo = wv * SLICE;
+    uint32_t keys[SLICE / 64]; uint16_t idxs[SLICE / 64];
+#pragma unroll
+    for (int c = 0; c < SLICE / 64; ++c) {
+        const int i = lo + 64 * c + lane;
+        keys[c] = i < cnt ? desc_key(src[i]) : 0xFFFFFFFFu;
+        idxs[c] = (uint16_t)i;
+    }
+    for (int i = tid; i < SORT_WAVES * 256; i += SORT_THREADS) (&hists[0][0][0])[i] = 0u;
+    __syncthreads();
+#pragma unroll
     for (int pass = 0; pass < 4; ++pass) {
         const int shift = 8 * pass;
-        const uint32_t* kin = (pass & 1) ? kb1 : kb0;
-        const uint16_t* iin = (pass & 1) ? ib1 : ib0;
+        uint32_t (*hist)[256] = hists[pass & 1];
         uint32_t* kout = (pass & 1) ? kb0 : kb1;
         uint16_t* iout = (pass & 1) ? ib0 : ib1;
-        for (int i = tid; i < SORT_WAVES * 256; i += SORT_THREADS) (&hist[0][0])[i] = 0u;
-        __syncthreads();
-        // this wave's slice, read once per pass and ahead of the counting (the compiler does not move reads across atomics)
-        uint32_t keys[SLICE / 64]; uint16_t idxs[SLICE / 64];
+        if (pass > 0) {                                    // this wave's slice
+            const uint32_t* kin = (pass & 1) ? kb1 : kb0;
+            const uint16_t* iin = (pass & 1) ? ib1 : ib0;
 #pragma unroll
-        for (int c = 0; c < SLICE / 64; ++c) { keys[c] = kin[lo + 64 * c + lane]; idxs[c] = iin[lo + 64 * c + lane]; }
+            for (int c = 0; c < SLICE / 64; ++c) { keys[c] = kin[lo + 64 * c + lane]; idxs[c] = iin[lo + 64 * c + lane]; }
+        }
         if (pass < 3) {
 #pragma unroll
             for (int c = 0; c < SLICE / 64; ++c) atomicAdd(&hist[wv][(keys[c] >> shift) & 255u], 1u);
@@ -108,27 +128,26 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
         }
         __syncthreads();
         // exclusive offsets in (digit, wave) order
+        uint32_t before[SORT_WAVES], total = 0u;
         if (tid < 256) {
-            uint32_t run = 0;
-            for (int w = 0; w < SORT_WAVES; ++w) { const uint32_t t = hist[w][tid]; hist[w][tid] = run; run += t; }
-            dbase[tid] = run;
-        }
-        __syncthreads();
-        if (tid < 64) {                                    // scan of 256 digit totals by one wave
-            uint32_t v[4], sm = 0;
+            uint32_t t[SORT_WAVES];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) { v[q] = dbase[4 * tid + q]; sm += v[q]; }
-            uint32_t inc = sm;
+            for (int w = 0; w < SORT_WAVES; ++w) t[w] = hist[w][tid];
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1) { const uint32_t t = __shfl_up(inc, off, 64); if (lane >= off) inc += t; }
-            uint32_t ex = inc - sm;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) { dbase[4 * tid + q] = ex; ex += v[q]; }
+            for (int w = 0; w < SORT_WAVES; ++w) { before[w] = total; total += t[w]; }
+            total = lanes_upto(total);                     // of this wave's 64 digits
+            if (lane == 63) dbase[wv] = total;
+        } else if (pass < 3) {                             // the other twelve waves clear the next pass's counters
+            uint32_t* next = &hists[(pass + 1) & 1][0][0];
+            for (int i = tid - 256; i < SORT_WAVES * 256; i += SORT_THREADS - 256) next[i] = 0u;
         }
         __syncthreads();
         if (tid < 256) {
-            const uint32_t bs = dbase[tid];
-            for (int w = 0; w < SORT_WAVES; ++w) hist[w][tid] += bs;
+            uint32_t base = total - (before[SORT_WAVES - 1] + hist[SORT_WAVES - 1][tid]);
+#pragma unroll
+            for (int w = 0; w < 3; ++w) base += w < wv ? dbase[w] : 0u;
+#pragma unroll
+            for (int w = 0; w < SORT_WAVES; ++w) hist[w][tid] = base + before[w];
         }
         __syncthreads();
         // in-order scatter of this wave's slice: inside a 64-element chunk the rank among equal digits
@@ -142,28 +161,37 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
             const uint16_t idx = idxs[c];
             const uint32_t dg = (key >> shift) & 255u;
             // lanes whose digit differs from mine in some bit: bit b of the lanes' digits as a wave mask, against
-            // my own bit b spread over a word
+            // my own bit b spread over a word; diff | (ballot ^ mine) is one instruction (truth table 0xF6)
             uint32_t diff_lo = 0u, diff_hi = 0u;
 #pragma unroll
             for (int bit = 0; bit < 8; ++bit) {
-                const int32_t m = (int32_t)(dg << (31 - bit)) >> 31;               // 0 or ~0
-                const uint64_t bal = __ballot(m != 0);
-                diff_lo |= (uint32_t)bal ^ (uint32_t)m;
-                diff_hi |= (uint32_t)(bal >> 32) ^ (uint32_t)m;
+                const uint32_t m = (uint32_t)((int32_t)(dg << (31 - bit)) >> 31);  // 0 or ~0
+                const uint64_t bal = __ballot(m != 0u);
+                diff_lo = __builtin_amdgcn_bitop3_b32(diff_lo, (uint32_t)bal, m, 0xF6);
+                diff_hi = __builtin_amdgcn_bitop3_b32(diff_hi, (uint32_t)(bal >> 32), m, 0xF6);
             }
             const uint64_t peers = ~(((uint64_t)diff_hi << 32) | diff_lo);
-            const uint64_t below = peers & ((1ull << lane) - 1ull);
-            const uint32_t rank = __popcll(below);
+            const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
             const uint32_t pos = __atomic_load_n(&myh[dg], __ATOMIC_RELAXED) + rank;
             __builtin_amdgcn_wave_barrier();
             kout[pos] = key;
             iout[pos] = idx;
-            if (below == 0ull) __atomic_store_n(&myh[dg], pos + (uint32_t)__popcll(peers), __ATOMIC_RELAXED);
+            if (rank == 0u) __atomic_store_n(&myh[dg], pos + (uint32_t)__popcll(peers), __ATOMIC_RELAXED);
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();                                   // every wave is done with the counters and the input buffer
     }
     // four passes: the result sits in buffer 0
+    if (gridDim.x == 1) {
+        const float* mx = (list == 0 ? a.smax : a.vmax) + (int64_t)bh * n;
+        const int64_t head = ((int64_t)list * a.BH + bh) * WALK_BLK;
+        for (int i = tid; i < cnt; i += SORT_THREADS) {
+            const int idx = ib0[i];
+            a.sidx1[out0 + i] = idx;
+            if (i < WALK_BLK) { a.head_w[head + i] = key_to_float(kb0[i]); a.head_m[head + i] = mx[idx]; }
+        }
+        return;
+    }
     for (int i = tid; i < cnt; i += SORT_THREADS) {
         a.skey0[out0 + i] = kb0[i];
         a.sidx0[out0 + i] = (int32_t)(base0 + ib0[i]);
@@ -1417,7 +1445,7 @@ template <int SEG>
 static hipError_t launch_sort(const SelectArgs& a, hipStream_t st) {
     const int nseg = (int)((a.n + SEG - 1) / SEG);
     hipLaunchKernelGGL(sort_seg_kernel<SEG>, dim3(nseg, 2, a.BH), dim3(SORT_THREADS), sort_lds_bytes(SEG), st, a);
-    hipLaunchKernelGGL(sort_merge_kernel<SEG>, dim3(nseg, 2, a.BH), dim3(SORT_THREADS), 2 * SEG * 4, st, a);
+    if (nseg > 1) hipLaunchKernelGGL(sort_merge_kernel<SEG>, dim3(nseg, 2, a.BH), dim3(SORT_THREADS), 2 * SEG * 4, st, a);
     return hipGetLastError();
 }
 
