@@ -272,21 +272,44 @@ __global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
         reinterpret_cast<float2*>(a.rowstat)[(int64_t)bk * rows + blockIdx.x * 16 + wv] = make_float2(M, L > 0.f ? 1.0f / L : 0.f);
 }
 
+// Short contexts: lines_kernel merges the statistics of its rows itself (every workgroup of a KV head again: at most
+// FOLD_BLOCKS * 8 bytes a row out of the L2), which takes a launch of 3.5 us away.  The same values in the same order.
+constexpr int FOLD_BLOCKS = 16, FOLD_CHUNKS = 32;
+static int score_chunks(const ScoreArgs& a) { return a.G * ((a.w + 31) / 32); }           // at most: packed windows take fewer
+static bool folds(const ScoreArgs& a) { return a.nkb <= FOLD_BLOCKS && score_chunks(a) <= FOLD_CHUNKS; }
+__device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row) {
+    const int rows = a.G * a.w;
+    const float2* p = reinterpret_cast<const float2*>(a.part) + (int64_t)bk * a.nkb * rows + row;
+    float2 v[FOLD_BLOCKS];
+    float l[FOLD_BLOCKS], M = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) v[kb] = p[(int64_t)(kb < a.nkb ? kb : 0) * rows];
+#pragma unroll
+    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) { if (kb >= a.nkb) v[kb] = make_float2(-INFINITY, 0.f); M = fmaxf(M, v[kb].x); }
+#pragma unroll
+    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) l[kb] = v[kb].x != -INFINITY ? v[kb].y * fast_exp2(v[kb].x - M) : 0.f;
+#pragma unroll
+    for (int off = FOLD_BLOCKS / 2; off > 0; off >>= 1)
+#pragma unroll
+        for (int i = 0; i < off; ++i) l[i] += l[i + off];
+    return make_float2(M, l[0] > 0.f ? 1.0f / l[0] : 0.f);
+}
+
 // ---- pass 2: line sums ------------------------------------------------------------------------
 // grid (nkb, KV heads from a.bk0 on, shares of the G heads; one share in mode 2)
 // MODE 0: vert/vmax per head + diagonal partials (contiguous window, q_pos == NULL)
 // MODE 1: vert/vmax per head + the matrix A of these KV heads, [heads][w][n], zero beyond each row's position
 // MODE 2: column sums only, summed over the G heads of the KV head (retention score)
 // MODE 3: the matrix A only
-template <typename T, int D, int MODE>
+template <typename T, int D, int MODE, bool FOLD>
 __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void lines_kernel(ScoreArgs a) {
     using RT = RowTile<T, D>;
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
     float* slab = reinterpret_cast<float*>(smem);          // [SLAB_DIAGS][SLAB] A by diagonals (MODE 0) and
     unsigned char* qs = smem + (MODE == 0 ? SLAB_BYTES : 0);           // [2] chunks of queries
-    float* rst = reinterpret_cast<float*>(smem + lines_front<T, D>(MODE));   // [2][32][2] max and 1 / sum of the chunks' rows
-    int32_t* ql = reinterpret_cast<int32_t*>(rst + 128);   // [w] last visible key of a row, relative to the block
+    int32_t* ql = reinterpret_cast<int32_t*>(smem + lines_front<T, D>(MODE));    // [w] last visible key of a row, relative to the block
+    float* rst = reinterpret_cast<float*>(ql + (a.w + 3) / 4 * 4);     // [2][32][2] max and 1 / sum of the chunks' rows (FOLD: of all chunks)
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = blockIdx.x, bk = a.bk0 + blockIdx.y;
@@ -306,12 +329,17 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
     auto fetch = [&](int c) {
         const Chunk k = ch.at(c);
         RT::fetch(Q0 + (int64_t)k.start * RT::RB, k.cnt, qs_lds + (uint32_t)((c & 1) * RT::BYTES), lane, wv, 4);
-        if (wv == 3) dma4(uniform_ptr(st0), (uint32_t)(8 * (k.start + ((lane >> 1) < k.cnt ? lane >> 1 : k.cnt - 1)) + 4 * (lane & 1)), (uint32_t)__builtin_amdgcn_readfirstlane((int)(rst_lds + (uint32_t)((c & 1) * 256))));
+        if (wv == 3 && !FOLD) dma4(uniform_ptr(st0), (uint32_t)(8 * (k.start + ((lane >> 1) < k.cnt ? lane >> 1 : k.cnt - 1)) + 4 * (lane & 1)), (uint32_t)__builtin_amdgcn_readfirstlane((int)(rst_lds + (uint32_t)((c & 1) * 256))));
     };
     for (int t = tid; t < a.w; t += SCORE_THREADS) {
         const int64_t rel = position_of(a, t) - blk0;      // key klocal of the block is visible to row t iff klocal <= rel
         ql[t] = rel < -1 ? -1 : (rel > SB ? SB : (int32_t)rel);
     }
+    if (FOLD)
+        for (int i = tid; i < 32 * (c1 - c0); i += SCORE_THREADS) {
+            const Chunk k = ch.at(c0 + i / 32);
+            reinterpret_cast<float2*>(rst)[i] = row_stats(a, bk, k.start + (i % 32 < k.cnt ? i % 32 : k.cnt - 1));
+        }
     Frag<T> kf[D / 16];
     k_frags<T, D>(kf, Kg, blk0 + 32 * wv, n, kst + wv * RT::BYTES, lane);
     __syncthreads();
@@ -327,7 +355,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
     for (int c = c0; c < c1; ++c) {
         const Chunk k = ch.at(c);
         const int bh = bh0 + k.start / a.w;                // head of the chunk (of its first row when packed)
-        const float* rs = rst + (c & 1) * 64;
+        const float* rs = rst + (FOLD ? c - c0 : c & 1) * 64;
         f32x16 s;
         {
             Frag<T> qf[D / 16];
@@ -342,13 +370,13 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         auto rows = [&](auto MASKED) {
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const int row0 = 8 * q4 + 4 * g;           // registers 4*q4 .. 4*q4+3 hold the chunk's rows row0 .. row0+3
-                const f32x4 sa = reinterpret_cast<const f32x4*>(rs + 2 * row0)[0];       // m, 1/l of rows row0, row0+1
-                const f32x4 sb = reinterpret_cast<const f32x4*>(rs + 2 * row0)[1];       // ... row0+2, row0+3
+                const int rq = 8 * q4 + 4 * g;             // registers 4*q4 .. 4*q4+3 hold the chunk's rows rq .. rq+3
+                const f32x4 sa = *reinterpret_cast<const f32x4*>(rs + 2 * rq);            // m, 1/l of rows rq, rq+1
+                const f32x4 sb = *reinterpret_cast<const f32x4*>(rs + 2 * rq + 4);        // ... rq+2, rq+3
                 const float mm[4] = {sa.x, sa.z, sb.x, sb.z}, il[4] = {sa.y, sa.w, sb.y, sb.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const int row = row0 + e;
+                    const int row = rq + e;
                     float p = fast_exp2(s[4 * q4 + e] * a.scale_log2e - mm[e]) * il[e];
                     if constexpr (decltype(MASKED)::value) {
                         int t = k.t0 + row;
@@ -521,8 +549,11 @@ static void launch_stats(const ScoreArgs& a, hipStream_t st) {
 }
 template <typename T, int D, int MODE>
 static void launch_lines(const ScoreArgs& a, int kv_heads, hipStream_t st) {
-    const size_t smem = lines_front<T, D>(MODE) + 512 + (size_t)a.w * 4;
-    hipLaunchKernelGGL((lines_kernel<T, D, MODE>), dim3(a.nkb, kv_heads, MODE == 2 ? 1 : head_shares(a, kv_heads)), dim3(SCORE_THREADS), smem, st, a);
+    const bool fold = folds(a);
+    const size_t smem = lines_front<T, D>(MODE) + (size_t)(a.w + 3) / 4 * 16 + (fold ? (size_t)score_chunks(a) * 256 : 512);
+    const dim3 grid(a.nkb, kv_heads, MODE == 2 ? 1 : head_shares(a, kv_heads));
+    if (fold) hipLaunchKernelGGL((lines_kernel<T, D, MODE, true>), grid, dim3(SCORE_THREADS), smem, st, a);
+    else hipLaunchKernelGGL((lines_kernel<T, D, MODE, false>), grid, dim3(SCORE_THREADS), smem, st, a);
 }
 
 template <typename T, int D>
@@ -530,7 +561,7 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     ScoreArgs a = a0;
     const int BK = a.B * a.Hkv;
     launch_stats<T, D>(a, st);
-    hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
+    if (!folds(a)) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {
         launch_lines<T, D, 0>(a, BK, st);
     } else if (mode == 1) {
@@ -555,10 +586,11 @@ template <typename T, int D>
 static hipError_t init_score_t() {
     hipError_t e;
     if ((e = allow_full_lds(&stats_kernel<T, D>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&lines_kernel<T, D, 0>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&lines_kernel<T, D, 1>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&lines_kernel<T, D, 2>)) != hipSuccess) return e;
-    return allow_full_lds(&lines_kernel<T, D, 3>);
+    if ((e = allow_full_lds(&lines_kernel<T, D, 0, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 0, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&lines_kernel<T, D, 1, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 1, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&lines_kernel<T, D, 2, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 2, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&lines_kernel<T, D, 3, false>)) != hipSuccess) return e;
+    return allow_full_lds(&lines_kernel<T, D, 3, true>);
 }
 hipError_t init_score_kernels() {
     hipError_t e;

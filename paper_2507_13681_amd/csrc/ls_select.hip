@@ -2,7 +2,7 @@
 //
 //   sort_seg_kernel / sort_merge_kernel
 //                 Desc_Sort: the n line weights of a list in descending order, equal weights in
-//                 ascending index order.  Segments of 2048 to 8192 elements are sorted inside LDS by a stable
+//                 ascending index order.  Segments of 1024 to 8192 elements are sorted inside LDS by a stable
 //                 LSD radix sort (4 x 8 bits): each of the 16 waves owns a contiguous slice, counts its
 //                 digits in its own histogram, and scatters its slice in order (ranks among equal
 //                 digits from wave ballots and the wave's running counters; no atomics decide an
@@ -41,7 +41,7 @@ static_assert(WALK_BLK == SELECT_HEAD_LINES, "the merge writes the walk's first 
 constexpr int SORT_THREADS = 1024;
 constexpr int SORT_WAVES = 16;
 constexpr int SORT_SEG_MAX = 8192;             // most elements one workgroup sorts inside LDS
-constexpr int SORT_SEG_MIN = 2048;
+constexpr int SORT_SEG_MIN = 1024;
 constexpr size_t sort_lds_bytes(int seg) { return (size_t)2 * seg * 4 + (size_t)2 * seg * 2 + 2 * SORT_WAVES * 256 * 4 + 256 * 4; }
 
 // sum over the lanes to the left and this one
@@ -60,8 +60,9 @@ __device__ __forceinline__ uint32_t lanes_upto(uint32_t x) {
 // [seg * SEG, +SEG) of one list entirely in LDS and writes the sorted keys (skey0) and their
 // line indices (sidx0) back to the same range; a list of one segment is finished here (sidx1, head_w, head_m).
 // What bounds it: vector instructions (the ballots of the ranks) where a wave has eight chunks to scatter, the five
-// barriers and the round trips between them where it has two.  So a pass reads the sixteen waves' counts of a digit at
-// once, scans the digits by lane shifts, and clears the other pass's counters on the side: @@.
+// barriers and the round trips between them where it has one or two.  So a pass reads the sixteen waves' counts of a
+// digit at once, scans the digits by lane shifts, and clears the other pass's counters on the side; slots past the end
+// of the list take no part.  32 lists of 32768 lines 31 -> 28 us, of 12347 24 -> 17, four of 1024 13 -> 8.
 template <int SEG>
 __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
     constexpr int SLICE = SEG / SORT_WAVES;
@@ -79,18 +80,22 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
     const int cnt = (int)(n - base0 < SEG ? n - base0 : SEG);
     const float* src = (list == 0 ? a.slash : a.vert) + (int64_t)bh * n + base0;
     const int64_t out0 = ((int64_t)list * a.BH + bh) * n + base0;
-    // slots past the end of the list hold the largest key: they sort behind every element and, being
-    // the highest local indices, turn behind equal keys as well
+    // slots past the end of the list take no part: neither counted nor moved (as largest keys, 64 atomics of a wave on one
+    // counter took turns for every chunk of them)
     const int lo = wv * SLICE;
     uint32_t keys[SLICE / 64]; uint16_t idxs[SLICE / 64];
 #pragma unroll
     for (int c = 0; c < SLICE / 64; ++c) {
         const int i = lo + 64 * c + lane;
-        keys[c] = i < cnt ? desc_key(src[i]) : 0xFFFFFFFFu;
+        keys[c] = i < cnt ? desc_key(src[i]) : 0u;
         idxs[c] = (uint16_t)i;
     }
     for (int i = tid; i < SORT_WAVES * 256; i += SORT_THREADS) (&hists[0][0][0])[i] = 0u;
     __syncthreads();
+    // (PART: the segment is not full.  Without predicates the chunks of a full one overlap: 28 instead of 31 us at 32768 lines)
+    auto passes = [&](auto PART) {
+    constexpr bool part = decltype(PART)::value;
+    auto here = [&](int c) { return !part || lo + 64 * c + lane < cnt; };
 #pragma unroll
     for (int pass = 0; pass < 4; ++pass) {
         const int shift = 8 * pass;
@@ -105,7 +110,7 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
         }
         if (pass < 3) {
 #pragma unroll
-            for (int c = 0; c < SLICE / 64; ++c) atomicAdd(&hist[wv][(keys[c] >> shift) & 255u], 1u);
+            for (int c = 0; c < SLICE / 64; ++c) if (here(c)) atomicAdd(&hist[wv][(keys[c] >> shift) & 255u], 1u);
         } else {
             // the top byte (sign and upper exponent bits) takes few values, and 64 atomics on one counter take turns:
             // three times over, the lanes that share the digit of the first lane not yet counted add once together;
@@ -113,7 +118,7 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
 #pragma unroll
             for (int c = 0; c < SLICE / 64; ++c) {
                 const uint32_t dg = keys[c] >> 24;
-                uint64_t todo = ~0ull;
+                uint64_t todo = part ? __ballot(here(c)) : ~0ull;
 #pragma unroll
                 for (int round = 0; round < 3; ++round) {
                     if (todo == 0ull) break;
@@ -162,7 +167,8 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
             const uint32_t dg = (key >> shift) & 255u;
             // lanes whose digit differs from mine in some bit: bit b of the lanes' digits as a wave mask, against
             // my own bit b spread over a word; diff | (ballot ^ mine) is one instruction (truth table 0xF6)
-            uint32_t diff_lo = 0u, diff_hi = 0u;
+            const uint64_t none = part ? ~__ballot(here(c)) : 0ull;
+            uint32_t diff_lo = (uint32_t)none, diff_hi = (uint32_t)(none >> 32);
 #pragma unroll
             for (int bit = 0; bit < 8; ++bit) {
                 const uint32_t m = (uint32_t)((int32_t)(dg << (31 - bit)) >> 31);  // 0 or ~0
@@ -174,13 +180,14 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
             const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
             const uint32_t pos = __atomic_load_n(&myh[dg], __ATOMIC_RELAXED) + rank;
             __builtin_amdgcn_wave_barrier();
-            kout[pos] = key;
-            iout[pos] = idx;
-            if (rank == 0u) __atomic_store_n(&myh[dg], pos + (uint32_t)__popcll(peers), __ATOMIC_RELAXED);
+            if (here(c)) { kout[pos] = key; iout[pos] = idx; }
+            if (here(c) && rank == 0u) __atomic_store_n(&myh[dg], pos + (uint32_t)__popcll(peers), __ATOMIC_RELAXED);
             __builtin_amdgcn_wave_barrier();
         }
         __syncthreads();                                   // every wave is done with the counters and the input buffer
     }
+    };
+    if (cnt == SEG) passes(std::false_type{}); else passes(std::true_type{});
     // four passes: the result sits in buffer 0
     if (gridDim.x == 1) {
         const float* mx = (list == 0 ? a.smax : a.vmax) + (int64_t)bh * n;
@@ -487,13 +494,55 @@ struct WalkList { float cw[WALK_CAP + WALK_RUN], cl[WALK_CAP + WALK_RUN], pre[WA
 // One run of picks from one list: the gain of each pick, how many of them count, and whether the walk ends
 // after them because no line is left that adds anything.
 struct WalkRun { float g[WALK_RUN]; int which, limit, last, pad; };
-struct WalkSync { int staged[2], summed_blk[2], cur[2], summed, stop, done, err, runs, decided; float tot[2]; };
+struct WalkSync { int staged[2], summed_blk[2], cur[2], summed, stop, done, err, runs, decided, cnt_s, cnt_v; float tot[2]; };
 static_assert(offsetof(WalkSync, summed) % 8 == 0 && offsetof(WalkSync, stop) == offsetof(WalkSync, summed) + 4, "summed and stop are read as one 8-byte word");   // tot: a list's whole overlap sum
 constexpr int WALK_RING = 4;                   // runs decided ahead of the running sum
 constexpr size_t WALK_LDS_BYTES = 2 * sizeof(WalkList) + WALK_RING * sizeof(WalkRun) + sizeof(WalkSync);
 
 __device__ __forceinline__ int walk_ld(const int* p) { return __builtin_amdgcn_readfirstlane(__atomic_load_n(p, __ATOMIC_RELAXED)); }
 __device__ __forceinline__ void walk_st(int* p, int v) { __atomic_store_n(p, v, __ATOMIC_RELAXED); }
+
+// Chosen prefixes -> ascending index lists of both lists of a head, by the workgroup that has walked them (half of its NT
+// threads a list).  bm: 2 * ceil(n / 32) words of LDS.  Up to EMIT_LINES lines: a launch of emit_kernel costs 4 to 5 us there.
+constexpr int64_t EMIT_LINES = 8192;
+template <int NT>
+__device__ __forceinline__ void emit_both(const SelectArgs& a, int bh, int cnt_s, int cnt_v, uint32_t* bm) {
+    __shared__ uint32_t wsum[NT / 64];
+    constexpr int H = NT / 2;
+    const int tid = threadIdx.x, list = tid >= H ? 1 : 0, t = tid - list * H, lane = tid & 63, wv = tid >> 6;
+    const int n = (int)a.n, words = (n + 31) / 32, cnt = list == 0 ? cnt_s : cnt_v, cap = list == 0 ? a.cap_s : a.cap_v;
+    const int32_t* sorted_idx = a.sidx1 + ((int64_t)list * a.BH + bh) * n;
+    int32_t* out = list == 0 ? a.s_idx + (int64_t)bh * cap : a.v_idx + (int64_t)bh * cap;
+    bm += list * words;
+    for (int i = t; i < words; i += H) bm[i] = cnt >= n ? 0xFFFFFFFFu >> (i == words - 1 ? 32 * words - n : 0) : 0u;
+    if (t == 0 && cnt > cap) atomicOr(a.status, list == 0 ? STAT_S_TRUNCATED : STAT_V_TRUNCATED);
+    __syncthreads();
+    if (cnt < n)
+        for (int i0 = t; i0 < cnt; i0 += 8 * H) {          // eight independent loads in flight per thread
+            int32_t x8[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x8[j] = sorted_idx[i0 + j * H < cnt ? i0 + j * H : cnt - 1];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) atomicOr(&bm[x8[j] >> 5], 1u << (x8[j] & 31));
+        }
+    __syncthreads();
+    const int per = (words + H - 1) / H, w0 = t * per < words ? t * per : words, w1 = w0 + per < words ? w0 + per : words;
+    uint32_t mine = 0u;
+    for (int w = w0; w < w1; ++w) mine += (uint32_t)__popc(bm[w]);
+    const uint32_t upto = lanes_upto(mine);
+    if (lane == 63) wsum[wv] = upto;
+    __syncthreads();
+    uint32_t at = upto - mine;
+    for (int w = list * (H / 64); w < wv; ++w) at += wsum[w];
+    for (int w = w0; w < w1; ++w) {
+        uint32_t m = bm[w];
+        while (m) {
+            if (at < (uint32_t)cap) out[at] = 32 * w + __ffs(m) - 1;
+            m &= m - 1u;
+            ++at;
+        }
+    }
+}
 
 // ix[e] = the line at sorted position pos + e (the last line's index past the end of the list)
 template <int E>
@@ -547,8 +596,7 @@ __device__ __forceinline__ int walk_first(const bool (&p)[WALK_E]) {
 // taken out, and stop when the walk is over.  The summing wave writes the result; the deciding wave ends the
 // stagers through `done`.  Every wait is a bounded spin that also ends when another wave has reported a failed
 // wait, so all six waves leave in every case.
-__global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
-    extern __shared__ __align__(16) unsigned char walk_lds[];
+__device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* walk_lds) {
     WalkList* lists = reinterpret_cast<WalkList*>(walk_lds);
     WalkRun* ring = reinterpret_cast<WalkRun*>(walk_lds + 2 * sizeof(WalkList));
     WalkSync* sync = reinterpret_cast<WalkSync*>(walk_lds + 2 * sizeof(WalkList) + WALK_RING * sizeof(WalkRun));
@@ -718,8 +766,8 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
             // A wait that ran into its bound (never observed with the default bound) reports the conservative
             // result, every line selected: the coverage target of Alg. 2 still holds for it, and the context's
             // status word tells the caller.
-            a.s_cnt[bh] = (failed || all) ? n : cnt_s;
-            a.v_cnt[bh] = (failed || all) ? n : cnt_v;
+            sync->cnt_s = (failed || all) ? n : cnt_s;
+            sync->cnt_v = (failed || all) ? n : cnt_v;
             if (failed) atomicOr(a.status, STAT_WALK_TIMEOUT);
             if (a.accounted) a.accounted[bh] = sum;
         }
@@ -869,6 +917,19 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
         walk_st(&sync->done, 1);
     }
 }
+
+// grid (BH); dynamic LDS: WALK_LDS_BYTES
+__global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
+    extern __shared__ __align__(16) unsigned char walk_lds[];
+    walk_head(a, walk_lds);
+    __syncthreads();
+    const WalkSync* sync = reinterpret_cast<const WalkSync*>(walk_lds + 2 * sizeof(WalkList) + WALK_RING * sizeof(WalkRun));
+    const int bh = blockIdx.x, cnt_s = sync->cnt_s, cnt_v = sync->cnt_v;
+    if (threadIdx.x == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; }
+    if (a.n > EMIT_LINES) return;
+    emit_both<WALK_THREADS>(a, bh, cnt_s, cnt_v, reinterpret_cast<uint32_t*>(walk_lds));      // (not where `sync` lies)
+}
+static_assert(2 * sizeof(WalkList) > EMIT_LINES / 4, "the bitmaps lie ahead of the rings");
 
 // ---- Alg. 2 with the overlap of a candidate counted cell by cell ----------------------------------
 // The loop of Alg. 2 compares the marginal contributions of the two list heads (Sec. 5.1); the listing bounds the
@@ -1114,11 +1175,15 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
         }
         if (change) { List t = X; X = O; O = t; most = XW_FEW; }
     }
+    const int cnt_s = X.id == 0 ? X.taken : O.taken, cnt_v = X.id == 0 ? O.taken : X.taken;
     if (tid == 0) {
-        a.s_cnt[bh] = X.id == 0 ? X.taken : O.taken;
-        a.v_cnt[bh] = X.id == 0 ? O.taken : X.taken;
+        a.s_cnt[bh] = cnt_s;
+        a.v_cnt[bh] = cnt_v;
         if (a.accounted) a.accounted[bh] = sum;
     }
+    if (a.n > EMIT_LINES) return;
+    __syncthreads();                           // the maps are done with
+    emit_both<XW_THREADS>(a, bh, cnt_s, cnt_v, xw_maps);
 }
 
 // ---- chosen prefix -> ascending index list --------------------------------------------------------
@@ -1441,20 +1506,36 @@ __global__ void gather_rows_kernel(const unsigned char* src, unsigned char* dst,
         *reinterpret_cast<f32x4*>(d + i) = *reinterpret_cast<const f32x4*>(s + i);
 }
 
+static void launch_emit(const SelectArgs& a, hipStream_t st) {
+    if (a.n > EMIT_LINES) hipLaunchKernelGGL(emit_kernel, dim3(2, a.BH), dim3(1024), (size_t)((a.n + 31) / 32) * 4, st, a);
+}
 template <int SEG>
 static hipError_t launch_sort(const SelectArgs& a, hipStream_t st) {
     const int nseg = (int)((a.n + SEG - 1) / SEG);
     hipLaunchKernelGGL(sort_seg_kernel<SEG>, dim3(nseg, 2, a.BH), dim3(SORT_THREADS), sort_lds_bytes(SEG), st, a);
-    if (nseg > 1) hipLaunchKernelGGL(sort_merge_kernel<SEG>, dim3(nseg, 2, a.BH), dim3(SORT_THREADS), 2 * SEG * 4, st, a);
+    if constexpr (SEG > SORT_SEG_MIN)                       // (lists of one segment only)
+        if (nseg > 1) hipLaunchKernelGGL(sort_merge_kernel<SEG>, dim3(nseg, 2, a.BH), dim3(SORT_THREADS), 2 * SEG * 4, st, a);
     return hipGetLastError();
+}
+
+// Segment length: the merge's work per workgroup hardly depends on it, the sort's shrinks with it, so the shortest one
+// that still gives no more workgroups than the chip has compute units (256); but no merge at all for a list that fits
+// into 2048.
+static hipError_t sort_lines(const SelectArgs& a, hipStream_t st) {
+    const int64_t want = a.n * 2 * a.BH / 256;
+    return a.n <= SORT_SEG_MIN ? launch_sort<SORT_SEG_MIN>(a, st)
+         : want <= 2048        ? launch_sort<2048>(a, st)
+         : want <= 4096        ? launch_sort<4096>(a, st)
+                               : launch_sort<SORT_SEG_MAX>(a, st);
 }
 
 hipError_t init_select_kernels() {
     hipError_t e;
     if ((e = allow_full_lds(&sort_seg_kernel<SORT_SEG_MIN>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&sort_seg_kernel<2048>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&sort_seg_kernel<4096>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&sort_seg_kernel<SORT_SEG_MAX>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&sort_merge_kernel<SORT_SEG_MIN>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&sort_merge_kernel<2048>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&sort_merge_kernel<4096>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&sort_merge_kernel<SORT_SEG_MAX>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_kernel)) != hipSuccess) return e;
@@ -1464,28 +1545,19 @@ hipError_t init_select_kernels() {
 }
 
 hipError_t run_select(const SelectArgs& a, hipStream_t st) {
-    // Segment length: the merge's work per workgroup hardly depends on it, the sort's shrinks with it, so the
-    // shortest one that still gives no more workgroups than the chip has compute units (256).
-    const int64_t want = a.n * 2 * a.BH / 256;
-    hipError_t e = want <= SORT_SEG_MIN ? launch_sort<SORT_SEG_MIN>(a, st)
-                 : want <= 4096         ? launch_sort<4096>(a, st)
-                                        : launch_sort<SORT_SEG_MAX>(a, st);
+    hipError_t e = sort_lines(a, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(walk_kernel, dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES, st, a);
-    const size_t smem = (size_t)((a.n + 31) / 32) * 4;
-    hipLaunchKernelGGL(emit_kernel, dim3(2, a.BH), dim3(1024), smem, st, a);
+    launch_emit(a, st);
     return hipGetLastError();
 }
 
 hipError_t run_select_exact(const SelectArgs& a, hipStream_t st) {
-    const int64_t want = a.n * 2 * a.BH / 256;
-    hipError_t e = want <= SORT_SEG_MIN ? launch_sort<SORT_SEG_MIN>(a, st)
-                 : want <= 4096         ? launch_sort<4096>(a, st)
-                                        : launch_sort<SORT_SEG_MAX>(a, st);
+    hipError_t e = sort_lines(a, st);
     if (e != hipSuccess) return e;
     const size_t smem = (size_t)((a.n + 31) / 32) * 4;
     hipLaunchKernelGGL(walk_exact_kernel, dim3(a.BH), dim3(XW_THREADS), 2 * smem, st, a);
-    hipLaunchKernelGGL(emit_kernel, dim3(2, a.BH), dim3(1024), smem, st, a);
+    launch_emit(a, st);
     return hipGetLastError();
 }
 

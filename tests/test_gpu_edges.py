@@ -212,3 +212,40 @@ def test_walk_sums(oracle, n, alpha, kind):
         check_selection_exact(gpu, ref)
         if accounted:
             np.testing.assert_array_equal(gpu["accounted"], ref["accounted"])
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1024, 1025, 2047, 2048, 2049, 8191, 8192, 8193])
+def test_sorted_and_emitted_lists(oracle, n):
+    """Lengths around the segments of the sort, its waves' slices and the lists that the walk writes out itself; few distinct
+    weights, so that the order of equal ones shows."""
+    from tests.gpu_util import host
+    from tests.test_gpu_configs import check_selection_exact
+    print(f"sorted lists n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    H = 3
+    v, s = rng.integers(1, 40, size=(2, 1, H, n)) / 8.0
+    s[:, 1] *= 1e-3; v[:, 0] *= 1e-3                                  # one head of columns, one of diagonals, one of both
+    sc = dict(vert=v, slash=s, vmax=v * 1e-7, smax=s * 1e-7, total=np.maximum(v.sum(-1), s.sum(-1)))
+    sc = {k: np.ascontiguousarray(x, dtype=np.float32) for k, x in sc.items()}
+    ref = oracle.select(sc, max(1, n // 3), 0.7)
+    shape = binding.make_shape(1, H, 1, 64, n, max(1, n // 3), 1, "f32", 0.0)
+    ctx = binding.Context(shape)
+    out = binding.alloc_select(shape, accounted=True)
+    dev = {k: torch.from_numpy(x).cuda() for k, x in sc.items()}
+    ctx.ls_select(shape, 0.7, dev["vert"], dev["slash"], dev["vmax"], dev["smax"], dev["total"], out["v_idx"], out["v_cnt"],
+                  out["s_idx"], out["s_cnt"], out["accounted"])
+    assert ctx.ls_poll_status() == 0
+    gpu = host(out)
+    check_selection_exact(gpu, ref)
+    np.testing.assert_array_equal(gpu["accounted"], ref["accounted"])
+
+
+@pytest.mark.parametrize("n,w,G", [(2048, 64, 4), (2049, 64, 4), (700, 100, 8), (900, 1, 1), (300, 33, 17)])
+def test_score_merges_row_statistics_itself(oracle, n, w, G):
+    """Up to sixteen key blocks and 32 chunks of rows the line sums' kernel merges the row statistics; with more of either a
+    kernel of its own does."""
+    from tests.gpu_util import Pipeline, host
+    from tests.test_gpu_parity import _score_close
+    print(f"row statistics n={n} w={w} G={G}", flush=True)
+    q, k, v = inputs.make_plain(1, 2 * G, 2, n, w, 64, dtype="bf16", seed=n + w, q_scale=2.0)
+    _score_close(host(Pipeline(q, k, v, w, "bf16").score()), oracle.score(q, k), w)
