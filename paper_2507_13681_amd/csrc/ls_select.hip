@@ -87,7 +87,7 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
 #pragma unroll
     for (int c = 0; c < SLICE / 64; ++c) {
         const int i = lo + 64 * c + lane;
-        keys[c] = i < cnt ? desc_key(src[i]) : 0u;
+        keys[c] = desc_key(src[i < cnt ? i : cnt - 1]);    // (no condition around the conversion: it would wait for each load)
         idxs[c] = (uint16_t)i;
     }
     for (int i = tid; i < SORT_WAVES * 256; i += SORT_THREADS) (&hists[0][0][0])[i] = 0u;
@@ -226,14 +226,17 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_merge_kernel(SelectArgs a) 
     const int64_t base0 = (int64_t)seg * SEG;
     const int cnt = (int)(n - base0 < SEG ? n - base0 : SEG);
     uint32_t key[PER], rank[PER], nxt[PER];
+    int32_t idx[PER];
     auto fetch = [&](int q) {                               // keys of segment q, padded with the largest key
         const int64_t qb = (int64_t)q * SEG;
         const int qc = (int)(n - qb < SEG ? n - qb : SEG);
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int i = tid + j * SORT_THREADS;
-            nxt[j] = i < qc ? a.skey0[lbase + qb + i] : 0xFFFFFFFFu;
+            nxt[j] = a.skey0[lbase + qb + (i < qc ? i : qc - 1)];
         }
+#pragma unroll
+        for (int j = 0; j < PER; ++j) nxt[j] = tid + j * SORT_THREADS < qc ? nxt[j] : 0xFFFFFFFFu;
     };
     auto stage = [&](int buf) {
 #pragma unroll
@@ -244,7 +247,8 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_merge_kernel(SelectArgs a) 
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         const int p = tid + j * SORT_THREADS;
-        key[j] = p < cnt ? a.skey0[lbase + base0 + p] : 0xFFFFFFFFu;
+        key[j] = a.skey0[lbase + base0 + (p < cnt ? p : cnt - 1)];
+        idx[j] = a.sidx0[lbase + base0 + (p < cnt ? p : cnt - 1)];
         rank[j] = (uint32_t)p;
     }
     if (q < nseg) stage(0);
@@ -292,19 +296,17 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_merge_kernel(SelectArgs a) 
         buf ^= 1;
         q = q2;
     }
-    // (the first WALK_BLK lines of the order also get their weight and maximum written, so that the walk can start
-    // without a second round trip through the indices)
-    const float* mx = (list == 0 ? a.smax : a.vmax) + (int64_t)bh * n;
-    float* hw = a.head_w + ((int64_t)list * a.BH + bh) * WALK_BLK;
-    float* hm = a.head_m + ((int64_t)list * a.BH + bh) * WALK_BLK;
+    // (stores only, the indices are there; a condition around load and store would wait for each of them in turn)
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int p = tid + j * SORT_THREADS;
-        if (p < cnt) {
-            const int32_t idx = a.sidx0[lbase + base0 + p];
-            a.sidx1[lbase + rank[j]] = idx;
-            if (rank[j] < (uint32_t)WALK_BLK) { hw[rank[j]] = key_to_float(key[j]); hm[rank[j]] = mx[idx]; }
-        }
+    for (int j = 0; j < PER; ++j)
+        if (tid + j * SORT_THREADS < cnt) a.sidx1[lbase + rank[j]] = idx[j];
+    // the first WALK_BLK lines of the order also get their weight and maximum written, so that the walk can start without
+    // a second round trip through the indices; they are among the first WALK_BLK of their segments
+    static_assert(WALK_BLK <= SORT_THREADS, "j = 0");
+    if (tid < cnt && rank[0] < (uint32_t)WALK_BLK) {
+        const int64_t head = ((int64_t)list * a.BH + bh) * WALK_BLK + rank[0];
+        a.head_w[head] = key_to_float(key[0]);
+        a.head_m[head] = ((list == 0 ? a.smax : a.vmax) + (int64_t)bh * n)[idx[0]];
     }
 }
 
