@@ -492,13 +492,12 @@ int kv_compress_on(const ErrSink& fail, const char* who, int device, unsigned ch
     e = ls::run_topb(t, BK, tb_scratch, st);
     if (e != hipSuccess) return fail(LS_EHIP, "%s(topb): %s", who, hipGetErrorString(e));
     const int row_bytes = s->d * (s->dtype == LS_BF16 ? 2 : 4);
-    if (k_out) {
-        e = ls::run_gather_rows(k, k_out, keep_idx, keep_cnt, BK, s->n, budget, row_bytes, st);
-        if (e != hipSuccess) return fail(LS_EHIP, "%s(gather k): %s", who, hipGetErrorString(e));
-    }
-    if (v_out) {
-        e = ls::run_gather_rows(v, v_out, keep_idx, keep_cnt, BK, s->n, budget, row_bytes, st);
-        if (e != hipSuccess) return fail(LS_EHIP, "%s(gather v): %s", who, hipGetErrorString(e));
+    const void* src[2]; void* dst[2]; int tensors = 0;
+    if (k_out) { src[tensors] = k; dst[tensors++] = k_out; }
+    if (v_out) { src[tensors] = v; dst[tensors++] = v_out; }
+    if (tensors) {
+        e = ls::run_gather_rows(src, dst, tensors, keep_idx, keep_cnt, BK, s->n, budget, row_bytes, st);
+        if (e != hipSuccess) return fail(LS_EHIP, "%s(gather): %s", who, hipGetErrorString(e));
     }
     return LS_OK;
 }

@@ -168,8 +168,8 @@ hipError_t run_select(const SelectArgs& a, hipStream_t st);
 hipError_t run_select_exact(const SelectArgs& a, hipStream_t st);   // a_win, q_pos, w set; vmax / smax unused
 hipError_t run_topb(const TopbArgs& a, int BK, uint32_t* scratch, hipStream_t st);   // scratch: topb_scratch_words(BK, len) words
 size_t topb_scratch_words(int BK, int64_t len);
-hipError_t run_gather_rows(const void* src, void* dst, const int32_t* keep_idx, const int32_t* keep_cnt,
-                           int BK, int64_t len, int budget, int row_bytes, hipStream_t st);
+hipError_t run_gather_rows(const void* const* src, void* const* dst, int tensors, const int32_t* keep_idx, const int32_t* keep_cnt,
+                           int BK, int64_t len, int budget, int row_bytes, hipStream_t st);      // one or two tensors
 hipError_t launch_plan(const PlanArgs& a, int BH, hipStream_t st);
 hipError_t launch_sched(const SchedArgs& a, hipStream_t st);
 // ev0 / ev1 (both or neither): events that receive the start and stop time of the attention kernel's own dispatch

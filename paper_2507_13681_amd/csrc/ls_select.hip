@@ -16,9 +16,9 @@
 //                 overlap prefix sums in LDS ahead of both.
 //   emit_kernel   one workgroup per (head, list): the chosen prefix of a sorted list becomes an
 //                 ascending index list (bitmap in LDS + prefix popcount).
-//   topb_*        Alg. 3: the `budget` largest scores per KV head by a three-digit radix select on the
-//                 float bit patterns, ties broken towards smaller indices, ascending output; a head's
-//                 scores are spread over many workgroups, one launch per step.
+//   topb_*        Alg. 3: the `budget` largest scores per KV head by a radix select on the float bit patterns,
+//                 ties broken towards smaller indices, ascending output; by one workgroup a head up to
+//                 TB_ONE_LEN scores, spread over many, one launch per step, beyond.
 #include "ls_device.h"
 #include "ls_internal.h"
 
@@ -1383,7 +1383,8 @@ __global__ __launch_bounds__(TB_THREADS) void topb_hist_kernel(TopbArgs a) {
 #pragma unroll
     for (int q = 0; q < TB_CHUNK / TB_THREADS; ++q) {
         const int64_t i = (int64_t)chunk * TB_CHUNK + q * TB_THREADS + tid;
-        kb[q] = i < len ? desc_key(sc[i]) : 0xFFFFFFFFu;
+        const uint32_t k = desc_key(sc[i < len ? i : len - 1]);
+        kb[q] = i < len ? k : 0xFFFFFFFFu;
     }
 #pragma unroll
     for (int q = 0; q < TB_CHUNK / TB_THREADS; ++q) {
@@ -1421,7 +1422,7 @@ __global__ __launch_bounds__(TB_THREADS) void topb_count_kernel(TopbArgs a) {
 #pragma unroll
     for (int q = 0; q < TB_CHUNK / TB_THREADS; ++q) {
         const int64_t i = (int64_t)chunk * TB_CHUNK + q * TB_THREADS + tid;
-        const uint32_t key = i < len ? desc_key(sc[i]) : 0xFFFFFFFFu;
+        const uint32_t key = desc_key(sc[i < len ? i : len - 1]);
         g += (uint32_t)__popcll(__ballot(i < len && key < kstar));
         e += (uint32_t)__popcll(__ballot(i < len && key == kstar));
     }
@@ -1467,7 +1468,8 @@ __global__ __launch_bounds__(TB_THREADS) void topb_write_kernel(TopbArgs a) {
 #pragma unroll
     for (int q = 0; q < TB_CHUNK / TB_THREADS; ++q) {
         const int64_t i = (int64_t)chunk * TB_CHUNK + q * TB_THREADS + tid;
-        kb[q] = i < len ? desc_key(sc[i]) : 0xFFFFFFFFu;
+        const uint32_t k = desc_key(sc[i < len ? i : len - 1]);
+        kb[q] = i < len ? k : 0xFFFFFFFFu;
         const uint64_t gm = __ballot(i < len && kb[q] < kstar), em = __ballot(i < len && kb[q] == kstar);
         if (lane == 0) { seg_g[q * 16 + wv] = (uint32_t)__popcll(gm); seg_e[q * 16 + wv] = (uint32_t)__popcll(em); }
     }
@@ -1496,16 +1498,121 @@ __global__ __launch_bounds__(TB_THREADS) void topb_write_kernel(TopbArgs a) {
     }
 }
 
-// gather kept rows: dst [BK][budget][row_bytes] <- src [BK][len][row_bytes]; grid (budget, BK)
-__global__ void gather_rows_kernel(const unsigned char* src, unsigned char* dst, const int32_t* keep_idx,
-                                   const int32_t* keep_cnt, int64_t len, int budget, int row_bytes) {
-    const int slot = blockIdx.x, bk = blockIdx.y;
-    if (slot >= keep_cnt[bk]) return;
-    const int64_t r = keep_idx[(int64_t)bk * budget + slot];
-    const unsigned char* s = src + ((int64_t)bk * len + r) * row_bytes;
-    unsigned char* d = dst + ((int64_t)bk * budget + slot) * row_bytes;
-    for (int i = threadIdx.x * 16; i < row_bytes; i += blockDim.x * 16)
-        *reinterpret_cast<f32x4*>(d + i) = *reinterpret_cast<const f32x4*>(s + i);
+// Caches of up to 1024 PER entries: one workgroup per KV head does all steps with the keys in registers, a wave holding
+// consecutive entries.  The threshold is narrowed by two bits a step, the counts of the four quarters in the bytes of a
+// register (a histogram in LDS of a head's scores, which crowd into few digits, took 16 us), until the few keys left are
+// ranked directly or wanted as a whole.  The five launches above cost 4.5 us each: 32 heads of 16384 entries 29 us, now 16.
+constexpr int TB_ONE_LEN = 32768, TB_RANKED = 256;
+template <int PER>
+__global__ __launch_bounds__(TB_THREADS) void topb_one_kernel(TopbArgs a) {
+    __shared__ uint2 counts[2][16];
+    __shared__ __align__(16) uint32_t left[TB_RANKED];
+    __shared__ uint32_t nleft, found[2], wg[16], we[16];
+    const int bk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int len = (int)a.len, keep = a.budget < len ? a.budget : len;
+    int32_t* out = a.keep_idx + (int64_t)bk * a.budget;
+    if (tid == 0) a.keep_cnt[bk] = keep;
+    if (keep == len) {
+        for (int i = tid; i < len; i += TB_THREADS) out[i] = i;
+        return;
+    }
+    const float* sc = a.score + (int64_t)bk * len;
+    const int first = wv * (64 * PER) + lane;              // entry j of this thread: first + 64 j
+    uint32_t key[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) key[j] = desc_key(sc[first + 64 * j < len ? first + 64 * j : len - 1]);      // (all loads in flight)
+#pragma unroll
+    for (int j = 0; j < PER; ++j) key[j] = first + 64 * j < len ? key[j] : 0xFFFFFFFFu;
+    if (tid == 0) nleft = 0u;
+    // the rem-th smallest key of those counted so far lies among the `within` keys of [lo, lo + 4 w), w = 2^bit
+    uint32_t lo = 0u, rem = (uint32_t)keep, within = 0xFFFFFFFFu;
+    int bit = 30;
+    for (int step = 0;; ++step) {
+        // how many of the lane's keys lie in each quarter: a byte each (what lies behind counts to the last one)
+        uint32_t mine = 0u;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const uint32_t q = (key[j] - lo) >> bit;
+            mine += 1u << (8u * (q < 3u ? q : 3u));
+        }
+        const uint32_t even = lanes_upto(mine & 0x00FF00FFu), odd = lanes_upto((mine >> 8) & 0x00FF00FFu);
+        if (lane == 63) counts[step & 1][wv] = make_uint2(even, odd);
+        __syncthreads();
+        const uint2 x = counts[step & 1][lane & 15];       // every row of sixteen lanes adds up the sixteen waves
+        const uint32_t e2 = (uint32_t)__builtin_amdgcn_readlane((int)lanes_upto(x.x), 15), o2 = (uint32_t)__builtin_amdgcn_readlane((int)lanes_upto(x.y), 15);
+        const uint32_t c0 = e2 & 0xFFFFu, c1 = c0 + (o2 & 0xFFFFu), c2 = c1 + (e2 >> 16), w = 1u << bit;
+        if (rem <= c0) within = c0;
+        else if (rem <= c1) { lo += w; rem -= c0; within = c1 - c0; }
+        else if (rem <= c2) { lo += 2u * w; rem -= c1; within = c2 - c1; }
+        else { lo += 3u * w; rem -= c2; within = within == 0xFFFFFFFFu ? within : within - c2; }
+        if (rem == within || within <= (uint32_t)TB_RANKED || bit == 0) break;
+        bit -= 2;
+    }
+    // every key below kstar is kept, and need_eq of those equal to it
+    uint32_t kstar = lo + (1u << bit) - 1u, need_eq = 0xFFFFFFFFu;
+    if (rem != within) {
+        if (within <= (uint32_t)TB_RANKED && bit > 0) {
+#pragma unroll
+            for (int j = 0; j < PER; ++j)
+                if (key[j] - lo < 1u << bit) { const uint32_t at = atomicAdd(&nleft, 1u); if (at < (uint32_t)TB_RANKED) left[at] = key[j]; }
+            __syncthreads();
+            if (tid < (int)within) {
+                const uint32_t k = left[tid];
+                uint32_t less = 0u, same = 0u;
+                for (uint32_t i = 0; i < within; ++i) { const uint32_t o = left[i]; less += o < k; same += o == k; }
+                if (less < rem && rem <= less + same) { found[0] = k; found[1] = rem - less; }       // (equal keys store the same)
+            }
+            __syncthreads();
+            kstar = found[0]; need_eq = found[1];
+        } else { kstar = lo; need_eq = rem; }
+    }
+    // places in index order: the waves before this one, the chunks before this one, the lanes before this one
+    uint32_t g = 0u, e = 0u;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const bool in = first + 64 * j < len;
+        g += (uint32_t)__popcll(__ballot(in && key[j] < kstar));
+        e += (uint32_t)__popcll(__ballot(in && key[j] == kstar));
+    }
+    if (lane == 0) { wg[wv] = g; we[wv] = e; }
+    __syncthreads();
+    const uint32_t ag = lanes_upto(wg[lane & 15]), ae = lanes_upto(we[lane & 15]);        // (row 0 holds the sums)
+    g = wv == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)ag, wv - 1);
+    e = wv == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)ae, wv - 1);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const bool in = first + 64 * j < len, gt = in && key[j] < kstar, eq = in && key[j] == kstar;
+        const uint64_t gm = __ballot(gt), em = __ballot(eq);
+        const uint32_t eb = e + __builtin_amdgcn_mbcnt_hi((uint32_t)(em >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)em, 0u));
+        const uint32_t at = g + __builtin_amdgcn_mbcnt_hi((uint32_t)(gm >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)gm, 0u)) + (eb < need_eq ? eb : need_eq);
+        if (gt || (eq && eb < need_eq)) out[at] = first + 64 * j;
+        g += (uint32_t)__popcll(gm);
+        e += (uint32_t)__popcll(em);
+    }
+}
+
+// gather kept rows of up to two tensors: dst [BK][budget][row_bytes] <- src [BK][len][row_bytes]; grid (slot blocks, BK, tensors).
+// 16 bytes a thread and row, four rows in flight: bound by HBM, 67 MB moved in 11 us (a row per 64-thread workgroup, a launch a
+// tensor: 33 us).
+constexpr int GATHER_THREADS = 256, GATHER_ROWS = 4;
+struct GatherArgs { const unsigned char* src[2]; unsigned char* dst[2]; };
+__global__ __launch_bounds__(GATHER_THREADS) void gather_rows_kernel(GatherArgs t, const int32_t* keep_idx, const int32_t* keep_cnt,
+                                                                     int64_t len, int budget, int row_bytes) {
+    const int lanes = row_bytes / 16, per = GATHER_THREADS / lanes;        // rows at a time (row_bytes: 128, 256 or 512)
+    const int bk = blockIdx.y, cnt = keep_cnt[bk];
+    const int slot = blockIdx.x * (GATHER_ROWS * per) + threadIdx.x / lanes, off = 16 * (threadIdx.x % lanes);
+    const unsigned char* s = t.src[blockIdx.z] + (int64_t)bk * len * row_bytes + off;
+    unsigned char* d = t.dst[blockIdx.z] + (int64_t)bk * budget * row_bytes + off;
+    if (slot >= cnt) return;
+    int32_t r[GATHER_ROWS];
+    f32x4 v[GATHER_ROWS];
+#pragma unroll
+    for (int u = 0; u < GATHER_ROWS; ++u) r[u] = keep_idx[(int64_t)bk * budget + (slot + u * per < cnt ? slot + u * per : slot)];
+#pragma unroll
+    for (int u = 0; u < GATHER_ROWS; ++u) v[u] = *reinterpret_cast<const f32x4*>(s + (int64_t)r[u] * row_bytes);
+#pragma unroll
+    for (int u = 0; u < GATHER_ROWS; ++u)
+        if (slot + u * per < cnt) *reinterpret_cast<f32x4*>(d + (int64_t)(slot + u * per) * row_bytes) = v[u];
 }
 
 static void launch_emit(const SelectArgs& a, hipStream_t st) {
@@ -1569,6 +1676,12 @@ size_t topb_scratch_words(int BK, int64_t len) { return (size_t)BK * (3 * TB_BIN
 hipError_t run_topb(const TopbArgs& a0, int BK, uint32_t* scratch, hipStream_t st) {
     if (a0.len < 1 || a0.len > TOPB_MAX_LEN || a0.budget < 1) return hipErrorInvalidValue;
     TopbArgs a = a0;
+    if (a.len <= TB_ONE_LEN) {
+        if (a.len <= 4096) hipLaunchKernelGGL(topb_one_kernel<4>, dim3(BK), dim3(TB_THREADS), 0, st, a);
+        else if (a.len <= 16384) hipLaunchKernelGGL(topb_one_kernel<16>, dim3(BK), dim3(TB_THREADS), 0, st, a);
+        else hipLaunchKernelGGL(topb_one_kernel<32>, dim3(BK), dim3(TB_THREADS), 0, st, a);
+        return hipGetLastError();
+    }
     a.chunks = topb_chunks(a.len);
     a.hist = scratch;
     a.state = a.hist + (size_t)BK * 3 * TB_BINS;
@@ -1584,11 +1697,13 @@ hipError_t run_topb(const TopbArgs& a0, int BK, uint32_t* scratch, hipStream_t s
     return hipGetLastError();
 }
 
-hipError_t run_gather_rows(const void* src, void* dst, const int32_t* keep_idx, const int32_t* keep_cnt,
+hipError_t run_gather_rows(const void* const* src, void* const* dst, int tensors, const int32_t* keep_idx, const int32_t* keep_cnt,
                            int BK, int64_t len, int budget, int row_bytes, hipStream_t st) {
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(budget, BK), dim3(64), 0, st,
-                       reinterpret_cast<const unsigned char*>(src), reinterpret_cast<unsigned char*>(dst),
-                       keep_idx, keep_cnt, len, budget, row_bytes);
+    GatherArgs t{};
+    for (int i = 0; i < tensors; ++i) { t.src[i] = static_cast<const unsigned char*>(src[i]); t.dst[i] = static_cast<unsigned char*>(dst[i]); }
+    const int rows = GATHER_ROWS * (GATHER_THREADS / (row_bytes / 16));
+    hipLaunchKernelGGL(gather_rows_kernel, dim3((budget + rows - 1) / rows, BK, tensors), dim3(GATHER_THREADS), 0, st,
+                       t, keep_idx, keep_cnt, len, budget, row_bytes);
     return hipGetLastError();
 }
 

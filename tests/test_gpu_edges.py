@@ -249,3 +249,32 @@ def test_score_merges_row_statistics_itself(oracle, n, w, G):
     print(f"row statistics n={n} w={w} G={G}", flush=True)
     q, k, v = inputs.make_plain(1, 2 * G, 2, n, w, 64, dtype="bf16", seed=n + w, q_scale=2.0)
     _score_close(host(Pipeline(q, k, v, w, "bf16").score()), oracle.score(q, k), w)
+
+
+@pytest.mark.parametrize("ln,budget,d,dtype", [
+    (4096, 1, 64, "bf16"), (4097, 4096, 64, "bf16"),                  # keys per thread: 4 -> 16; all but one kept
+    (16384, 700, 128, "f32"), (16385, 16001, 64, "bf16"),             # 16 -> 32
+    (32768, 65, 128, "bf16"), (32769, 2000, 64, "bf16"),              # one workgroup a head -> many
+    (50, 50, 64, "f32"),                                              # all kept
+])
+def test_retention_sizes(oracle, ln, budget, d, dtype):
+    """Lengths around the forms of the top-B selection, budgets around a workgroup's rows of the gather; repeated key rows, so
+    that the threshold falls among equal scores."""
+    from tests.gpu_util import Pipeline
+    print(f"retention sizes len={ln} budget={budget} d={d} {dtype}", flush=True)
+    q, k, v = inputs.make_plain(1, 4, 2, ln, 8, d, dtype=dtype, seed=ln, q_scale=2.0)
+    k = np.ascontiguousarray(k[:, :, np.arange(ln) % 97])
+    pipe = Pipeline(q, k, v, 8, dtype, budget=budget)
+    keep_idx = torch.full((1, 2, budget), -1, dtype=torch.int32, device="cuda")
+    keep_cnt = torch.zeros((1, 2), dtype=torch.int32, device="cuda")
+    k_out = torch.zeros((1, 2, budget, d), dtype=pipe.k.dtype, device="cuda")
+    v_out = torch.zeros_like(k_out)
+    pipe.ctx.ls_kv_compress(pipe.shape, budget, pipe.q, pipe.k, pipe.v, keep_idx, keep_cnt, k_out, v_out)
+    score = torch.empty((1, 2, ln), dtype=torch.float32, device="cuda")
+    pipe.ctx.debug_compress_score(pipe.shape, score)
+    assert keep_cnt.cpu().tolist() == [[min(budget, ln)] * 2]
+    for h in range(2):
+        got = keep_idx[0, h].cpu().numpy()
+        np.testing.assert_array_equal(got, oracle.topb(score[0, h].cpu().numpy(), budget))
+        at = torch.from_numpy(got.astype(np.int64)).cuda()
+        assert torch.equal(k_out[0, h], pipe.k[0, h, at]) and torch.equal(v_out[0, h], pipe.v[0, h, at])
