@@ -204,6 +204,9 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(DecodeArgs a) {
     }
 
     // ---- merge the waves through LDS: part[wv][head][PS]
+    // (the wait: a wave whose early request lies past the count has not waited for it, and neither the compiler nor the
+    // barrier does so; it could still be landing where other waves write their results)
+    wait_transfers();
     __syncthreads();                                                   // every wave is done with its V stage
     float* part = reinterpret_cast<float*>(dec_lds);
     constexpr int PS = C::PS;

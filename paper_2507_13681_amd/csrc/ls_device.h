@@ -111,8 +111,10 @@ __device__ __forceinline__ void wait_transfers() {
     __builtin_amdgcn_s_waitcnt(0x0F70);                    // vmcnt(0), the other counters unconstrained
 }
 
-// Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for the wave's outstanding global
-// loads and stores; a kernel whose waves exchange data through LDS alone need not stall on a store's round trip.
+// Workgroup barrier that orders LDS traffic only, and lets the wave's transfers and global accesses stay under way.
+// (Nor does __syncthreads() wait for those: on gfx950 neither the barrier nor the fences around it wait for vector memory,
+// apart from what the compiler puts there for its own loads, and it does not count the transfers.)  As an asm statement it
+// says so to the compiler too.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // LDS transpose read of a bf16 tile stored row-major: in a block of 16 lanes, lane s addresses 4

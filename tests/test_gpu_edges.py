@@ -22,6 +22,21 @@ def test_decode_tiles_and_splits(oracle, B, Hq, Hkv, cap, T, d, ragged):
     _check(oracle, _case(B, Hq, Hkv, cap, T, d, seed=3 * cap + T, ragged=ragged))
 
 
+@pytest.mark.parametrize("Hkv,cap", [(8, 2000), (2, 4000)])     # eight tiles a split, a wave each; five: waves without a tile
+@pytest.mark.parametrize("d,G", [(128, 4), (128, 17), (64, 3), (64, 24)])
+def test_decode_splits_past_the_count(oracle, d, G, Hkv, cap):
+    """Caches far from full: waves and whole splits whose first tile, asked for ahead of the count, lies past it.  The rows
+    there are poison."""
+    B, T = 4, 5
+    print(f"decode past the count d={d} G={G} Hkv={Hkv} cap={cap}", flush=True)
+    q, kc, vc, cnt, kt, vt = _case(B, G * Hkv, Hkv, cap, T, d, seed=d + G + cap)
+    cnt[:, 0::2] = [[1], [33], [0], [cap // 5]]
+    for b in range(B):
+        for g in range(Hkv):
+            kc[b, g, cnt[b, g]:] = float("nan"); vc[b, g, cnt[b, g]:] = float("nan")
+    _check(oracle, (q, kc, vc, cnt, kt, vt))
+
+
 @pytest.mark.parametrize("dtype,d,n,n_hat", [
     ("bf16", 128, 9001, 67),       # two row blocks, 141 key blocks: items in many parts
     ("bf16", 64, 6400, 128),       # one whole row block
