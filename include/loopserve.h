@@ -12,7 +12,11 @@
  *     no host synchronisation; outputs are valid once the stream reaches the end of the call.
  *     Counts (v_cnt, s_cnt, keep_cnt) stay on the device, so score -> select -> prefill chain without
  *     a host round trip.  Calls that share a context must be issued on one stream at a time (they
- *     share the workspace).
+ *     share the workspace, and counters through which the workgroups of a launch find out which of them
+ *     is the last).  Calls that overlap all the same spoil their own results, and may leave those
+ *     counters off for one or two later calls of ls_decode_attend on that context; the ones after
+ *     that are sound again.  A recorded call (HIP graph) always uses the same counters: replays that
+ *     overlapped leave it unsound until three other calls of ls_decode_attend have run.
  *   - Return value: LS_OK or a negative ls_status; ls_last_error(ctx) then describes the failure.
  *     Argument errors are detected on the host before anything is launched.
  *   - dtype is the storage type of q / k / v / out (bf16 or fp32); tile products accumulate in fp32

@@ -27,6 +27,12 @@ int ls_debug_copy_compress_score(ls_ctx* ctx, const ls_shape* shape, float* dst_
 int ls_debug_set_walk_spin_limit(ls_ctx* ctx, int32_t limit);
 
 /*
+ * Sets every counter through which workgroups of one launch find out which of them is the last to `value`
+ * (zero between calls).  The tests use it to see that calls recover from counters that are off.
+ */
+int ls_debug_set_counters(ls_ctx* ctx, int32_t value, void* hip_stream);
+
+/*
  * Copies to the host the work queues that the most recent ls_sparse_prefill call on this context built
  * (one queue per XCD; an item is one block of 128 query rows of one head): host_queue holds 8 arrays of
  * B * Hq * nqb words, (batch * Hq + head) << 16 | row block, of which the first host_qlen[x] are valid;

@@ -82,6 +82,8 @@ def load_library():
     lib.ls_poll_status.argtypes = [vp, C.POINTER(i32), vp]
     lib.ls_debug_set_walk_spin_limit.restype = C.c_int
     lib.ls_debug_set_walk_spin_limit.argtypes = [vp, i32]
+    lib.ls_debug_set_counters.restype = C.c_int
+    lib.ls_debug_set_counters.argtypes = [vp, i32, vp]
     lib.ls_debug_copy_prefill_queues.restype = C.c_int
     lib.ls_debug_copy_prefill_queues.argtypes = [vp, sp, vp, vp, C.POINTER(i32), vp]
     lib.ls_profile_enable.restype = C.c_int
@@ -212,6 +214,9 @@ class Context:
 
     def debug_set_walk_spin_limit(self, limit: int):
         self._check(self.lib.ls_debug_set_walk_spin_limit(self.h, limit))
+
+    def debug_set_counters(self, value: int):
+        self._check(self.lib.ls_debug_set_counters(self.h, value, _stream()))
 
     def debug_prefill_queues(self, shape):
         """Work queues of the last ls_sparse_prefill call: list of eight int arrays of item words."""

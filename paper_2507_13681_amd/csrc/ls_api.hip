@@ -25,7 +25,13 @@ struct ls_ctx {
     unsigned char* ws;
     size_t ws_bytes;
     int32_t* status;          // device status word (bits LS_STAT_*), OR-ed into by kernels, read and cleared by ls_poll_status
-    uint32_t* done;           // [MAX_KV_HEADS] workgroups finished per (batch, KV head) inside a launch; every launch leaves zeros
+    // [COUNTER_SETS][MAX_HEADS] workgroups finished per head or KV head inside a launch.  Set 0: ls_score, cleared by the call's
+    // first kernel.  The others take turns call by call in ls_decode_attend, one launch with nobody to clear a set ahead of it:
+    // a launch leaves zeros in its own and clears the one after the next.  So calls that overlapped against the rules, and left a
+    // set off, spoil the next user of that set and no more.
+    uint32_t* counters;
+    unsigned decode_calls;    // calls of ls_decode_attend that used a set
+    int decode_heads;         // most KV heads of such a call: the part of a set that is cleared
     int walk_spin_limit;      // bound of the waits inside walk_kernel (test hook)
     char err[256];
     // optional timing of the sparse attention kernel (ls_profile_*): event pairs on the call's stream
@@ -36,7 +42,10 @@ struct ls_ctx {
 namespace {
 
 constexpr size_t ALIGN = 256;
-constexpr size_t MAX_KV_HEADS = 65536;      // B * Hkv <= 65535 everywhere
+constexpr size_t MAX_HEADS = 65536;         // B * Hq (ls_score), B * Hkv (ls_decode_attend) <= 65535
+constexpr unsigned DECODE_SETS = 4, COUNTER_SETS = 1 + DECODE_SETS;
+constexpr size_t COUNTER_BYTES = COUNTER_SETS * MAX_HEADS * sizeof(uint32_t);
+inline uint32_t* decode_set(const ls_ctx* c, unsigned call) { return c->counters + (1 + call % DECODE_SETS) * MAX_HEADS; }
 inline size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 int fail(ls_ctx* c, int code, const char* fmt, ...) {
@@ -183,14 +192,19 @@ int ls_create(ls_ctx** out, int device, size_t workspace_bytes) {
     ls_ctx* c = new (std::nothrow) ls_ctx();
     if (!c) return LS_EINVAL;
     c->device = device; c->ws = nullptr; c->ws_bytes = workspace_bytes; c->err[0] = 0; c->profile = false;
-    c->status = nullptr; c->walk_spin_limit = ls::WALK_SPIN_DEFAULT;
+    c->status = nullptr; c->decode_calls = 0; c->decode_heads = 0; c->walk_spin_limit = ls::WALK_SPIN_DEFAULT;
     if (init_device_once(device) != hipSuccess) { delete c; return LS_EHIP; }
     {
         void* p = nullptr;
-        const size_t bytes = ALIGN + MAX_KV_HEADS * sizeof(uint32_t);
-        if (hipMalloc(&p, bytes) != hipSuccess || hipMemset(p, 0, bytes) != hipSuccess) { if (p) (void)hipFree(p); delete c; return LS_EWORKSPACE; }
+        const size_t bytes = ALIGN + COUNTER_BYTES;
+        // (calls may come on any stream: the zeros have to be there when this function returns)
+        if (hipMalloc(&p, bytes) != hipSuccess || hipMemset(p, 0, bytes) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
+            if (p) (void)hipFree(p);
+            delete c;
+            return LS_EWORKSPACE;
+        }
         c->status = static_cast<int32_t*>(p);
-        c->done = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(p) + ALIGN);
+        c->counters = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(p) + ALIGN);
     }
     if (workspace_bytes) {
         void* p = nullptr;
@@ -236,7 +250,7 @@ int ls_score(ls_ctx* c, const ls_shape* s, const void* q_win, const int64_t* q_p
         a.win_heads = (int)heads;
         a.a_win = reinterpret_cast<float*>(bp.base + bp.off);
     }
-    a.done = c->done;
+    a.done = c->counters;
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_score: workspace of %zu bytes is too small", c->ws_bytes);
     a.vert = vert; a.slash = slash; a.vmax = vmax; a.smax = smax; a.total = total; a.gscore = nullptr;
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_score: hipSetDevice failed");
@@ -550,13 +564,16 @@ int ls_decode_attend(ls_ctx* c, const ls_shape* s, int32_t cap, int32_t T, const
     a.B = s->B; a.Hq = s->Hq; a.Hkv = s->Hkv; a.G = s->Hq / s->Hkv; a.cap = cap; a.T = T;
     a.scale_log2e = scale_log2e(s);
     ls::decode_split(s->B * s->Hkv, cap, T, &a.nsplit, &a.chunk);
-    a.done = c->done;
+    a.done = decode_set(c, c->decode_calls);
+    a.done_clear = decode_set(c, c->decode_calls + 2);
+    a.clear_heads = c->decode_heads > s->B * s->Hkv ? c->decode_heads : s->B * s->Hkv;
     if (ls::decode_smem_bytes(s->d, a.G, a.nsplit) > 156 * 1024) return fail(c, LS_ESHAPE, "ls_decode_attend: group too large for LDS");
     Bump bp{c->ws, c->ws_bytes, 0};
     a.part = bp.take<float>((size_t)s->B * s->Hq * a.nsplit * ls::decode_part_floats(s->d));
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_decode_attend: workspace of %zu bytes is too small", c->ws_bytes);
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_decode_attend: hipSetDevice failed");
     hipError_t e = ls::run_decode(a, s->d, static_cast<hipStream_t>(stream));
+    if (a.nsplit > 1) { ++c->decode_calls; c->decode_heads = a.clear_heads; }
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_decode_attend: %s", hipGetErrorString(e));
     return LS_OK;
 }
@@ -601,6 +618,14 @@ int ls_poll_status(ls_ctx* c, int32_t* host_out, void* stream) {
 int ls_debug_set_walk_spin_limit(ls_ctx* c, int32_t limit) {
     if (!c) return LS_EINVAL;
     c->walk_spin_limit = limit < 0 ? ls::WALK_SPIN_DEFAULT : limit;
+    return LS_OK;
+}
+
+int ls_debug_set_counters(ls_ctx* c, int32_t value, void* stream) {
+    if (!c) return LS_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess ||
+        hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(c->counters), value, COUNTER_BYTES / 4, static_cast<hipStream_t>(stream)) != hipSuccess)
+        return fail(c, LS_EHIP, "ls_debug_set_counters: hipMemsetD32Async failed");
     return LS_OK;
 }
 

@@ -259,8 +259,10 @@ __global__ __launch_bounds__(DEC_THREADS) void decode_kernel(DecodeArgs a) {
     __syncthreads();
     if (tid == 0) {
         last_s = count_shared(a.done + bk) == (uint32_t)a.nsplit - 1u;
-        if (last_s) clear_shared(a.done + bk);                         // for the next call
+        if (last_s) clear_shared(a.done + bk);                         // for the call that uses these counters next
     }
+    if (split == 0)                                                    // whatever an earlier call has left there
+        for (int h = bk + tid * (int)gridDim.y; h < a.clear_heads; h += DEC_THREADS * (int)gridDim.y) clear_shared(a.done_clear + h);
     __syncthreads();
     if (!last_s) return;
     // A thread owns two elements of a head and every `subs`-th split; the subsets are added through LDS.

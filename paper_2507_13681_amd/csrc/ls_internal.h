@@ -21,7 +21,7 @@ struct ScoreArgs {
     float* a_win;             // [heads][w][n]    the window matrix (mode 3), or that of the heads from bh_first on (mode 1)
     int bk0, bh_first;        // first KV head / query head of a lines_kernel launch
     int win_heads;            // KV heads whose matrix the buffer takes (mode 1)
-    uint32_t* done;           // [BH] workgroups finished per head; zero between calls
+    uint32_t* done;           // [BH] workgroups of finish_kernel finished per head, cleared by stats_kernel (null: not used)
 };
 
 constexpr int SELECT_HEAD_LINES = 1024;   // lines at the front of each sorted list whose weight and maximum are stored in order
@@ -122,6 +122,8 @@ struct DecodeArgs {
     float* lse;               // [B][Hq] or NULL
     float* part;              // [B*Hkv][nsplit][G][d + 4] per-split output, reference, normaliser
     uint32_t* done;           // [B*Hkv] splits finished; zero between calls
+    uint32_t* done_clear;     // [clear_heads] the counters of the call after the next, cleared here; clear_heads >= B*Hkv
+    int clear_heads;
     int B, Hq, Hkv, G, cap, T, nsplit, chunk;
     float scale_log2e;
 };

@@ -161,6 +161,8 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
     // every key of the block is visible to every row of a contiguous window: no masks (all but the last blocks)
     const bool open = a.q_pos == nullptr && (int64_t)(kb + 1) * SB - 1 <= n - a.w;
     const int rows = a.G * a.w;
+    if (a.done && kb == 0 && blockIdx.z == 0)              // finish_kernel's counters
+        for (int h = tid; h < a.G; h += SCORE_THREADS) clear_shared(a.done + b * a.Hq + kvh * a.G + h);
     wait_transfers();
     __syncthreads();
     int first = c0;                                        // first chunk whose wave results are still in `red`
@@ -467,7 +469,7 @@ __global__ __launch_bounds__(256) void diagonals_kernel(ScoreArgs a) {
 // ---- finish: add the two diagonal partials, reduce the total ------------------------------------
 // grid (B*Hq, FINISH_SPLIT).  Diagonal o is met by keys n-w-o .. n-1-o (clipped at 0), i.e. by key blocks
 // kA = max(0, n-w-o)/SB and kB = (n-1-o)/SB, which are equal or adjacent.  The last of a head's workgroups to get to its
-// end (a counter per head) adds their shares of the total, in a fixed tree order.
+// end (a counter per head, which stats_kernel has cleared) adds their shares of the total, in a fixed tree order.
 constexpr int FINISH_SPLIT = 8;            // workgroups per head (a head alone is a string of load round trips)
 __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguous) {
     __shared__ float red[1024];
@@ -525,7 +527,6 @@ __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguou
 #pragma unroll
             for (int i = 0; i < FINISH_SPLIT; ++i) p[i] = get_shared(share + i);
             a.total[bh] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-            clear_shared(a.done + bh);                                 // for the next call
         }
     }
 }

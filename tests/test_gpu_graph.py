@@ -81,3 +81,35 @@ def test_hot_path_replays_in_a_graph():
         print(f"graph replay on new inputs {rep}", flush=True)
         graph.replay()
         same(snapshot(*g_bufs[1:]), ref2)
+
+
+def test_decode_replays_in_a_graph(oracle):
+    """ls_decode_attend over several splits, the results of which meet through counters in the context: two calls recorded,
+    replayed with eager calls of the same context in between, and followed by the replay when the inputs change in place."""
+    from tests.test_gpu_decode import _case
+    q, kc, vc, cnt, kt, vt = (torch.from_numpy(x).cuda() if isinstance(x, np.ndarray) else x.cuda()
+                              for x in _case(2, 32, 8, 3000, 9, 128, seed=11))
+    shape = binding.make_shape(2, 32, 8, 128, 3009, 1, 1, "bf16")
+    ctx = binding.Context(workspace=binding.decode_workspace_bytes(shape, 3000, 9))
+    new = lambda: (torch.empty_like(q), torch.empty(q.shape[:2], dtype=torch.float32, device="cuda"))
+    call = lambda o, l, qq: ctx.ls_decode_attend(shape, qq, kc, vc, cnt, kt, vt, o, l)
+    q2 = q.flip(1).contiguous()
+    eager, eager2, rec, rec2 = new(), new(), new(), new()
+    call(*eager, q); call(*eager2, q2)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(*rec, q); call(*rec2, q2)
+    for rep in range(7):
+        for t in (*rec, *rec2, *eager):
+            t.fill_(float("nan"))
+        if rep == 4:
+            kc.mul_(-0.5); call(*eager2, q2)
+        print(f"decode replay {rep}", flush=True)
+        graph.replay()
+        call(*eager, q)
+        torch.cuda.synchronize()
+        for got, want in zip((*rec, *rec2), (*eager, *eager2)):
+            assert torch.equal(got, want)
+    f = lambda t: t.float().cpu().numpy()
+    ref, _ = oracle.decode(f(q), f(kc), f(vc), cnt.cpu().numpy(), f(kt), f(vt))
+    assert np.abs(f(rec[0]) - ref).max() <= 2e-2

@@ -117,3 +117,38 @@ def test_out_of_range_diagonals_are_skipped_and_reported(oracle):
     assert pipe.ctx.ls_poll_status() == binding.LS_STAT_S_RANGE
     want, _ = oracle.attend(q, k, v, v_idx, v_cnt, s_idx, s_cnt, mode=0)
     assert np.abs(out.float().cpu().numpy().reshape(-1, d) - want).max() <= 2e-2
+
+
+def test_calls_recover_from_counters_that_are_off(oracle):
+    """One context through ls_score and ls_decode_attend (several splits, KV heads of different number) in turn.  Whatever is in
+    the counters through which their workgroups find the last one, ls_score is right at once and ls_decode_attend two calls
+    later."""
+    from tests.gpu_util import Pipeline, host
+    from tests.test_gpu_decode import _case
+    q, k, v = inputs.make_plain(1, 8, 2, 1500, 20, 64, dtype="bf16", seed=4, q_scale=2.0)
+    pipe = Pipeline(q, k, v, 20, "bf16")
+    want = host(pipe.score())
+    cases = []
+    for i, (B, Hkv) in enumerate([(2, 8), (1, 4)]):
+        dq, kc, vc, _, kt, vt = (None if t is None else t.cuda() for t in _case(B, 4 * Hkv, Hkv, 2500, 9, 64, seed=i, ragged=False))
+        shape = binding.make_shape(B, 4 * Hkv, Hkv, 64, 2509, 1, 1, "bf16")
+        assert binding.decode_workspace_bytes(shape, 2500, 9) <= pipe.ctx.workspace
+        cases.append((shape, dq, kc, vc, None, kt, vt))
+
+    def decode(case):
+        out = torch.full_like(case[1], float("nan"))
+        pipe.ctx.ls_decode_attend(*case, out, None)
+        return out
+
+    ref = [decode(c) for c in cases]
+    for c, r in zip(cases, ref):
+        f = lambda t: t.float().cpu().numpy()
+        assert np.abs(f(r) - oracle.decode(f(c[1]), f(c[2]), f(c[3]), None, f(c[5]), f(c[6]))[0]).max() <= 2e-2
+    for value in (1, 3, 1 << 20):
+        pipe.ctx.debug_set_counters(value)
+        print(f"counters at {value}", flush=True)
+        for name, x in host(pipe.score()).items():
+            np.testing.assert_array_equal(x, want[name])
+        decode(cases[1]); decode(cases[1])
+        for i in (1, 1, 0, 1, 1, 0, 0):
+            assert torch.equal(decode(cases[i]), ref[i]), (value, i)
