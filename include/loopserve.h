@@ -64,7 +64,10 @@ typedef struct {
     float scale;     /* logit scale; <= 0 means 1/sqrt(d) */
 } ls_shape;
 
-/* Bytes of workspace that every call on `shape` (and ls_kv_compress with `budget`) fits in.
+/* Bytes of workspace that every call on `shape` (and ls_kv_compress with `budget`) fits in: per query head and key
+ * 24 bytes, or 16 and w / 16 more where that is larger, and up to 66 MiB that ls_sparse_prefill uses for parts of long
+ * row blocks and ls_score for the rows of explicit positions.  Both calls run in less, and ls_score with explicit
+ * positions faster in more (up to B * Hq * w * n * 4 bytes on top).
  * Host-only, no GPU needed.  Returns 0 for an invalid shape. */
 size_t ls_workspace_bytes(const ls_shape* shape, int32_t budget);
 

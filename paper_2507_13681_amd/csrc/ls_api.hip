@@ -128,17 +128,17 @@ inline size_t part_floats(const ls_shape* s) {
     const size_t a = BH * s->w * nkb_of(s->n) * 2, b = BH * 8;
     return a > b ? a : b;
 }
-// Window matrix of explicit scoring positions: all heads at once up to 256 MB, at least one KV head's.
-inline size_t win_bytes_kv(const ls_shape* s) { return (size_t)(s->Hq / s->Hkv) * s->w * (size_t)s->n * 4; }
-inline size_t win_bytes(const ls_shape* s) {
-    const size_t one = win_bytes_kv(s), all = one * s->B * s->Hkv, most = 256u << 20;
-    return one > most ? one : all < most ? all : most;
-}
+// The window matrix of explicit scoring positions passes through what is left of the workspace, band by band.  The partial sums
+// of the diagonals, which that path does not need, leave room for four rows of every head, and any call gets by with those.
+// Asked for is room for the whole matrix up to WIN_BYTES, as much as the parts of long attention items take (ws_prefill).
+// ls_score, 32 / 8 heads of 128, 64 rows, 32768 keys: 331 us through 16 MiB, 192 through 64, 158 to 185 with the whole matrix (256);
+// 12347 keys: 103 us through 47 MiB, 97 through 64, 84 whole (92); 131072 keys, 128 rows: 1615 through 64, 1399 through 224.
+constexpr size_t WIN_BYTES = 64u << 20;
 size_t ws_score(const ls_shape* s, bool lines) {
     const size_t BH = (size_t)s->B * s->Hq;
     size_t b = up(part_floats(s) * 4) + up(BH * s->w * 2 * 4);
     if (lines) {
-        const size_t diag = 2 * BH * (size_t)s->n * 2 * 4, win = win_bytes(s);
+        const size_t diag = 2 * BH * (size_t)s->n * 2 * 4, all = BH * s->w * (size_t)s->n * 4, win = all < WIN_BYTES ? all : WIN_BYTES;
         b += up(diag > win ? diag : win);
     }
     return b;
@@ -244,10 +244,9 @@ int ls_score(ls_ctx* c, const ls_shape* s, const void* q_win, const int64_t* q_p
     if (mode == 0) {
         a.spart = bp.take<float>(2 * (size_t)a.BH * (size_t)a.n * 2);
     } else {
-        const size_t kv = win_bytes_kv(s), left = bp.ok() && bp.cap > bp.off ? bp.cap - bp.off : 0;
-        const size_t heads = left / kv < (size_t)s->B * s->Hkv ? left / kv : (size_t)s->B * s->Hkv;
-        if (heads == 0) return fail(c, LS_EWORKSPACE, "ls_score: workspace of %zu bytes is too small", c->ws_bytes);
-        a.win_heads = (int)heads;
+        const size_t row = (size_t)a.G * (size_t)a.n * 4;              // of a KV head's matrices
+        a.win_rows = bp.ok() ? (int64_t)((bp.cap - bp.off) / row) : 0;
+        if (a.win_rows == 0) return fail(c, LS_EWORKSPACE, "ls_score: workspace of %zu bytes is too small", c->ws_bytes);
         a.a_win = reinterpret_cast<float*>(bp.base + bp.off);
     }
     a.done = c->counters;

@@ -18,9 +18,12 @@ struct ScoreArgs {
     float* spart;             // [2][BH][n][2]    diagonal partial sum / max by key-block parity
     float *vert, *slash, *vmax, *smax, *total;
     float* gscore;            // [B*Hkv][n]       group-summed column sums (retention score)
-    float* a_win;             // [heads][w][n]    the window matrix (mode 3), or that of the heads from bh_first on (mode 1)
-    int bk0, bh_first;        // first KV head / query head of a lines_kernel launch
-    int win_heads;            // KV heads whose matrix the buffer takes (mode 1)
+    float* a_win;             // [BH][w][n]       the window matrix (mode 3), or [heads from bh_first on][t1 - t0][n] a band of it (mode 1)
+    int64_t win_rows;         // mode 1: how many rows of a KV head's G heads the buffer takes, at least one
+    // set by run_score for each launch
+    int bk0, bh_first;        // first KV head / query head
+    int t0, t1;               // window rows whose matrix is written out
+    int sums;                 // mode 1: the column sums of the chunks are added here (not on a chunk's later bands)
     uint32_t* done;           // [BH] workgroups of finish_kernel finished per head, cleared by stats_kernel (null: not used)
 };
 

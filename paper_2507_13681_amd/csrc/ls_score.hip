@@ -14,8 +14,8 @@
 //                    thread per diagonal adding the rows in fixed order; a diagonal crosses at most two
 //                    key blocks, whose two partial results finish_kernel adds.
 // With explicit scoring positions (q_pos given) the diagonals of a slab are not a contiguous range: the
-// matrix A is then written out, for as many KV heads at a time as the workspace takes, and
-// diagonals_kernel adds each diagonal's cells in row order.
+// matrix A is then written out, band by band of as many KV heads and rows as the workspace takes, and
+// diagonals_kernel adds each diagonal's cells in row order, on from where the band before it stopped.
 // Everything is summed in a fixed order, so results are bit-reproducible from run to run.
 //
 // Tile products run on 32x32 MFMA with K fragments held in registers: each wave owns 32 keys of a block
@@ -77,11 +77,13 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_
 // neighbours (`packed`); otherwise a chunk stays inside one head's window.
 struct Chunk { int start, cnt, t0; };         // t0: window row of the first one (row r of the chunk: (t0 + r) % w)
 struct Chunks {
-    int w, rows, rgs, count;
-    __device__ __forceinline__ Chunks(int w_, int G, bool packed) : w(w_), rows(G * w_), rgs(packed ? 0 : (w_ + 31) / 32), count(packed ? (G * w_ + 31) / 32 : G * ((w_ + 31) / 32)) {}
+    int w, rows, rgs, count, first, end;      // `first`: window row at which a head's chunks begin; they reach row end - 1
+    __device__ __forceinline__ Chunks(int w_, int G, bool packed) : w(w_), rows(G * w_), rgs(packed ? 0 : (w_ + 31) / 32), count(packed ? (G * w_ + 31) / 32 : G * ((w_ + 31) / 32)), first(0), end(w_) {}
+    // the chunks that hold window rows t0 .. t1 - 1
+    __device__ __forceinline__ Chunks(int w_, int G, int t0, int t1) : w(w_), rows(G * w_), rgs((t1 + 31) / 32 - t0 / 32), count(G * rgs), first(t0 & ~31), end(t1) {}
     __device__ __forceinline__ Chunk at(int c) const {
         if (rgs == 0) { const int s = 32 * c; return {s, rows - s < 32 ? rows - s : 32, 0}; }
-        const int h = c / rgs, r0 = 32 * (c - h * rgs);
+        const int h = c / rgs, r0 = first + 32 * (c - h * rgs);
         return {h * w + r0, w - r0 < 32 ? w - r0 : 32, r0};
     }
 };
@@ -300,7 +302,8 @@ __device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row)
 // ---- pass 2: line sums ------------------------------------------------------------------------
 // grid (nkb, KV heads from a.bk0 on, shares of the G heads; one share in mode 2)
 // MODE 0: vert/vmax per head + diagonal partials (contiguous window, q_pos == NULL)
-// MODE 1: vert/vmax per head + the matrix A of these KV heads, [heads][w][n], zero beyond each row's position
+// MODE 1: vert/vmax per head + a band of the matrix A of these KV heads, [heads][t1 - t0][n], zero beyond each row's position.
+//         The chunks that hold the band's rows are passed; their columns are added to those of the chunks before them.
 // MODE 2: column sums only, summed over the G heads of the KV head (retention score)
 // MODE 3: the matrix A only
 template <typename T, int D, int MODE, bool FOLD>
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
     const unsigned char* Q0 = reinterpret_cast<const unsigned char*>(a.q) + (int64_t)bh0 * a.w * RT::RB;
     const float* st0 = a.rowstat + 2 * (int64_t)bh0 * a.w;
     const bool packed = MODE == 2 && packs(a.w);
-    const Chunks ch(a.w, a.G, packed);
+    const Chunks ch = MODE == 1 ? Chunks(a.w, a.G, a.t0, a.t1) : Chunks(a.w, a.G, packed);
     const int c0 = ch.count / (int)gridDim.z * (int)blockIdx.z, c1 = c0 + ch.count / (int)gridDim.z;
     const uint32_t qs_lds = lds_address(qs), rst_lds = lds_address(rst);
     auto fetch = [&](int c) {
@@ -358,6 +361,10 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         const Chunk k = ch.at(c);
         const int bh = bh0 + k.start / a.w;                // head of the chunk (of its first row when packed)
         const float* rs = rst + (FOLD ? c - c0 : c & 1) * 64;
+        if (MODE == 1 && ch.first > 0 && k.t0 == ch.first && mykey < n) {
+            vsum = a.vert[(int64_t)bh * n + mykey];
+            vmx = a.vmax[(int64_t)bh * n + mykey];
+        }
         f32x16 s;
         {
             Frag<T> qf[D / 16];
@@ -368,6 +375,10 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
             for (int cc = 0; cc < D / 16; ++cc) mma(s, qf[cc], kf[cc]);      // s[r] = <q_{8(r/4)+4g+r%4}, k_lane>
         }
         float ps = 0.f, pm = 0.f;
+        // of the chunk's rows, lo .. lo + cells - 1 are written out; `cell`: this lane's key in row 4 g
+        const int lo = MODE == 1 && a.t0 > k.t0 ? a.t0 - k.t0 : 0;
+        const int cells = (MODE == 1 && a.t1 - k.t0 < k.cnt ? a.t1 - k.t0 : k.cnt) - lo;
+        float* cell = MODE == 1 || MODE == 3 ? a.a_win + ((int64_t)(bh - a.bh_first) * (a.t1 - a.t0) + k.t0 - a.t0 + 4 * g) * n + mykey : nullptr;
         // MASKED: there are rows that do not exist (the last one is repeated) or keys that a row does not see
         auto rows = [&](auto MASKED) {
 #pragma unroll
@@ -388,8 +399,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
                     ps += p;
                     if (MODE == 0 || MODE == 1) pm = fmaxf(pm, p);
                     if (MODE == 0) slab[(klocal - row + 31) * SLAB + row] = p;
-                    if ((MODE == 1 || MODE == 3) && row < k.cnt && mykey < n)
-                        a.a_win[((int64_t)(bh - a.bh_first) * a.w + k.t0 + row) * n + mykey] = p;
+                    if ((MODE == 1 || MODE == 3) && (unsigned)(row - lo) < (unsigned)cells && mykey < n) cell[(8 * q4 + e) * n] = p;
                 }
                 if (MODE == 2 && packed && (8 * (q4 + 1)) % a.w == 0) {                  // the last rows of a head
                     gsum += halves_sum(ps);                // (rows past the last head add zeros)
@@ -422,9 +432,9 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         wait_transfers();                                  // chunk c + 1
         __syncthreads();
         if (c + 2 < c1) fetch(c + 2);
-        if (!(MODE == 2 && packed) && k.t0 + 32 >= a.w) {  // the head's last chunk
+        if (!(MODE == 2 && packed) && k.t0 + 32 >= ch.end) {   // the head's last chunk
             if (MODE == 2) gsum += vsum;
-            if ((MODE == 0 || MODE == 1) && g == 0 && mykey < n) {
+            if ((MODE == 0 || (MODE == 1 && a.sums)) && g == 0 && mykey < n) {
                 a.vert[(int64_t)bh * n + mykey] = vsum;
                 a.vmax[(int64_t)bh * n + mykey] = vmx;
             }
@@ -441,29 +451,31 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
 }
 
 // ---- diagonals from the written matrix (explicit positions) ---------------------------------------
-// grid (n / 256, heads bh_first ..): thread o adds A[t][p_t - o] over the rows in order; neighbouring threads read
-// neighbouring cells.
+// grid (n / 256, heads bh_first ..): thread o adds A[t][p_t - o] over the band's rows in order, to what the bands before it
+// gave; neighbouring threads read neighbouring cells.
 __global__ __launch_bounds__(256) void diagonals_kernel(ScoreArgs a) {
     __shared__ int32_t pos[256];
     if (threadIdx.x < (unsigned)a.w) pos[threadIdx.x] = position_of(a, threadIdx.x);
     __syncthreads();
     const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (o >= a.n) return;
-    const float* A = a.a_win + (int64_t)blockIdx.y * a.w * a.n;
+    const float* A = a.a_win + ((int64_t)blockIdx.y * (a.t1 - a.t0) - a.t0) * a.n;
+    const int64_t at = (int64_t)(a.bh_first + blockIdx.y) * a.n + o;
     float sum = 0.f, mx = 0.f;
-    for (int t0 = 0; t0 < a.w; t0 += 8) {
+    if (a.t0 > 0) { sum = a.slash[at]; mx = a.smax[at]; }
+    for (int t0 = a.t0; t0 < a.t1; t0 += 8) {
         float p[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int t = t0 + e < a.w ? t0 + e : a.w - 1;
+            const int t = t0 + e < a.t1 ? t0 + e : a.t1 - 1;
             const int64_t key = pos[t] - o;
-            p[e] = t0 + e < a.w && key >= 0 ? A[(int64_t)t * a.n + key] : 0.f;
+            p[e] = t0 + e < a.t1 && key >= 0 ? A[(int64_t)t * a.n + key] : 0.f;
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) { sum += p[e]; mx = fmaxf(mx, p[e]); }
     }
-    a.slash[(int64_t)(a.bh_first + blockIdx.y) * a.n + o] = sum;
-    a.smax[(int64_t)(a.bh_first + blockIdx.y) * a.n + o] = mx;
+    a.slash[at] = sum;
+    a.smax[at] = mx;
 }
 
 // ---- finish: add the two diagonal partials, reduce the total ------------------------------------
@@ -557,20 +569,44 @@ static void launch_lines(const ScoreArgs& a, int kv_heads, hipStream_t st) {
     else hipLaunchKernelGGL((lines_kernel<T, D, MODE, false>), grid, dim3(SCORE_THREADS), smem, st, a);
 }
 
+// Explicit positions: how many KV heads and window rows a band of the matrix has, `fit` rows of one KV head at most.  Whole
+// chunks of 32 rows (or the whole window), so many of them that the bands are fewest, and of those the ones with most rows: K
+// is read once a band.  A buffer of less than a chunk takes parts of one, and the chunk is passed again for each.  A band costs
+// two launches that wait for each other: 32768 keys, two KV heads of four, 32 rows a band: 22 + 14 us for 34 MB written and read.
+static void window_bands(int64_t fit, int BK, int w, int* heads, int* rows) {
+    int64_t fewest = INT64_MAX;
+    *heads = 1;
+    *rows = (int)(fit < w ? fit : w);
+    for (int r = w; r > 0; r = (r - 1) / 32 * 32) {
+        if (fit < r) continue;
+        const int64_t h = fit / r < BK ? fit / r : BK, bands = ((BK + h - 1) / h) * ((w + r - 1) / r);
+        if (bands < fewest) { fewest = bands; *heads = (int)h; *rows = r; }
+    }
+}
+
 template <typename T, int D>
 static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     ScoreArgs a = a0;
     const int BK = a.B * a.Hkv;
+    a.t0 = 0; a.t1 = a.w;
     launch_stats<T, D>(a, st);
     if (!folds(a)) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {
         launch_lines<T, D, 0>(a, BK, st);
     } else if (mode == 1) {
-        for (a.bk0 = 0; a.bk0 < BK; a.bk0 += a.win_heads) {            // as many KV heads as the matrix buffer takes
-            const int heads = BK - a.bk0 < a.win_heads ? BK - a.bk0 : a.win_heads;
+        int most, rows;
+        window_bands(a.win_rows, BK, a.w, &most, &rows);
+        for (a.bk0 = 0; a.bk0 < BK; a.bk0 += most) {
+            const int heads = BK - a.bk0 < most ? BK - a.bk0 : most;
             a.bh_first = a.bk0 * a.G;
-            launch_lines<T, D, 1>(a, heads, st);
-            hipLaunchKernelGGL(diagonals_kernel, dim3((unsigned)((a.n + 255) / 256), heads * a.G), dim3(256), 0, st, a);
+            for (a.t0 = 0; a.t0 < a.w; a.t0 = a.t1) {
+                const int chunk_end = rows < 32 ? (a.t0 / 32 + 1) * 32 : a.w;      // a band of less than a chunk lies inside one
+                a.t1 = a.t0 + rows < a.w ? a.t0 + rows : a.w;
+                if (a.t1 > chunk_end) a.t1 = chunk_end;
+                a.sums = a.t0 % 32 == 0;
+                launch_lines<T, D, 1>(a, heads, st);
+                hipLaunchKernelGGL(diagonals_kernel, dim3((unsigned)((a.n + 255) / 256), heads * a.G), dim3(256), 0, st, a);
+            }
         }
     } else if (mode == 3) {
         launch_lines<T, D, 3>(a, BK, st);

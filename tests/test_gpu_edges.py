@@ -113,6 +113,40 @@ def test_score_positions_in_head_groups(oracle, w, dtype):
         np.testing.assert_array_equal(whole[name], some[name])
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,n,w,rows,given", [
+    (1, 2, 1, 700, 40, 1, True),           # a row at a time: every chunk passed once for each of its rows
+    (1, 2, 1, 700, 40, 4, True),           # what the diagonals of the last rows take at one KV head
+    (2, 6, 3, 700, 100, 33, True),         # one chunk of one KV head at a time
+    (1, 6, 2, 900, 100, 70, True),         # one of them in two bands, rather than both chunk by chunk
+    (1, 8, 4, 385, 70, 100, True),         # three KV heads chunk by chunk, then one
+    (1, 4, 2, 600, 256, 31, True),         # parts of chunks that differ in length
+    (2, 4, 2, 640, 129, 64, False),        # the last 129 rows: two chunks a band, the last of one row
+])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_score_matrix_in_bands(oracle, B, Hq, Hkv, n, w, rows, given, dtype):
+    """The window matrix passes through the workspace in bands of as many rows of KV heads as it takes, with the same sums."""
+    from tests.gpu_util import Pipeline, host
+    from tests.test_gpu_parity import _score_close
+    print(f"bands B={B} Hq={Hq} Hkv={Hkv} n={n} w={w} rows={rows} {dtype}", flush=True)
+    d = 64
+    q, k, v = inputs.make_plain(B, Hq, Hkv, n, w, d, dtype=dtype, seed=w + n, q_scale=2.0)
+    pos = np.sort(np.random.default_rng(w).choice(n, size=w, replace=False)) if given else None
+    pipe = Pipeline(q, k, v, w, dtype)
+    up = lambda x: (x + 255) // 256 * 256
+    front = up(B * Hq * w * ((n + 127) // 128) * 8) + up(B * Hq * w * 8)
+    row = Hq // Hkv * n * 4
+    pipe.ctx = binding.Context(workspace=front + B * Hkv * w * row)
+    whole = host(pipe.score(q_pos=pos))
+    _score_close(whole, oracle.score(q, k, q_pos=pos), w)
+    pipe.ctx = binding.Context(workspace=front + rows * row)
+    bands = host(pipe.score(q_pos=pos))
+    for name in whole:
+        np.testing.assert_array_equal(whole[name], bands[name])
+    pipe.ctx = binding.Context(workspace=front + row - 1)
+    with pytest.raises(binding.LoopServeError):
+        pipe.score(q_pos=pos)
+
+
 @pytest.mark.parametrize("Hq,Hkv,ln,n_obs,d,dtype", [
     (4, 4, 129, 8, 64, "bf16"),            # one head a KV head: a chunk of eight rows
     (10, 2, 300, 8, 128, "bf16"),          # forty rows: a whole chunk and one of eight

@@ -48,6 +48,18 @@ def test_workspace_bytes_is_host_only(lib):
     assert binding.workspace_bytes(bad) == 0
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,d,n,n_hat,w", [
+    (1, 32, 8, 128, 32768, 10923, 64), (1, 32, 8, 128, 12347, 61, 61), (1, 16, 4, 64, 5003, 1777, 48),
+    (1, 32, 8, 128, 131072, 16384, 128), (1, 64, 8, 128, 262144, 16384, 256), (1, 64, 1, 128, 1048576, 1, 256)])
+def test_workspace_grows_as_the_lists_do(lib, B, Hq, Hkv, d, n, n_hat, w):
+    """Per query head and key 24 bytes of sorted lists, or 16 of diagonal sums beside 8 per row and 128 keys, and at most 66 MiB
+    for the parts of long attention items: no window matrix [Hq, w, n], which is a fraction of the workspace at a time."""
+    b = binding.workspace_bytes(binding.make_shape(B, Hq, Hkv, d, n, n_hat, w, "bf16"), 2048)
+    heads = B * Hq
+    lists = heads * max(24 * n + 16384, 16 * n + 8 * w * ((n + 127) // 128) + 8 * w)
+    assert lists <= b <= lists + (66 << 20) + 8192, (b / 2 ** 20, lists / 2 ** 20)
+
+
 def test_struct_layout_matches_header():
     assert ctypes.sizeof(binding.LsShape) == 48
     assert binding.LsShape.n.offset == 16 and binding.LsShape.w.offset == 32 and binding.LsShape.scale.offset == 40
