@@ -160,7 +160,7 @@ size_t ws_prefill(const ls_shape* s) {
     const size_t items = BH * (size_t)row_blocks(s->n, n_hat);   // (head, row block) work items
     const size_t slots = (size_t)ls::prefill_split_slots((int64_t)items);
     return up(BH * (size_t)(words_of(s->n) + 4) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(items * 4) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
-           up(8 * (items + slots) * 16) + 2 * up(8 * 4) + up(slots * 8) + up(8) + up(slots * ls::prefill_slot_bytes(s->d)) + ALIGN;
+           up((items + slots) * 16) + up(26 * 4) + up(slots * 8) + up(slots * ls::prefill_slot_bytes(s->d)) + ALIGN;
 }
 size_t ws_compress(const ls_shape* s) {
     return ws_score(s, false) + up((size_t)s->B * s->Hkv * (size_t)s->n * 4) +
@@ -362,9 +362,9 @@ namespace {
 // Where ls_sparse_prefill keeps its per-call state in the workspace (one place, so that the test hook that
 // reads the work queues back finds them where the call put them).
 struct PrefillCarve {
-    uint32_t* obits; uint32_t* ncol; uint32_t* cost; uint16_t* pref; uint4* queue; int32_t* qlen; int32_t* qhead; uint8_t* tab;
+    uint32_t* obits; uint32_t* ncol; uint32_t* cost; uint16_t* pref; uint4* queue; int32_t* qlen; int32_t* qhead; int32_t* qbase; uint8_t* tab;
     uint2* split; int32_t* split_count; float* part_o; float* part_ml;
-    int nqb, qcap, slots; int64_t pos0; int code;
+    int nqb, slots; int64_t pos0; int code;
 };
 const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     const int BH = s->B * s->Hq;
@@ -380,9 +380,8 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     if (w.nqb > 65535) return "too many row blocks";
     if (BH > 8192) return "B * Hq exceeds 8192";
     w.ncol = bp.take<uint32_t>((size_t)BH * w.nqb);
-    w.qlen = bp.take<int32_t>(8);
-    w.qhead = bp.take<int32_t>(8);
-    w.split_count = bp.take<int32_t>(2);
+    w.qlen = bp.take<int32_t>(8 + 8 + 8 + 2);
+    w.qhead = w.qlen + 8; w.qbase = w.qlen + 16; w.split_count = w.qlen + 24;
     w.tab = bp.take<uint8_t>((size_t)BH * tab_len);
     // long items are split as far as the workspace has room for their parts' results (sized for it by
     // ls_workspace_bytes; a smaller workspace that holds the rest still works)
@@ -393,8 +392,7 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     const Bump mark = bp;
     for (;;) {
         bp = mark;
-        w.qcap = (int)items + w.slots;
-        w.queue = bp.take<uint4>(8 * (size_t)w.qcap);
+        w.queue = bp.take<uint4>(items + w.slots);
         w.split = w.slots ? bp.take<uint2>((size_t)w.slots) : nullptr;
         w.part_o = w.slots ? bp.take<float>((size_t)w.slots * 128 * s->d) : nullptr;
         w.part_ml = w.slots ? bp.take<float>((size_t)w.slots * 128 * 2) : nullptr;
@@ -436,7 +434,7 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(plan): %s", hipGetErrorString(e));
     ls::SchedArgs sa{};
     sa.BH = BH; sa.G = s->Hq / s->Hkv; sa.Hq = s->Hq; sa.Hkv = s->Hkv; sa.nqb = nqb; sa.cost = cost;
-    sa.queue = w.queue; sa.qcap = w.qcap; sa.qlen = qlen; sa.qhead = qhead;
+    sa.queue = w.queue; sa.qlen = qlen; sa.qbase = w.qbase; sa.qhead = qhead;
     sa.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)BH * nqb, w.slots);
     sa.slots = w.slots; sa.split = w.split; sa.split_count = w.split_count;
     sa.pref = pref; sa.ncol = w.ncol; sa.tab_len = tab_len; sa.n = s->n; sa.pos0 = pos0;
@@ -444,7 +442,7 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(sched): %s", hipGetErrorString(e));
     ls::PrefillArgs a{};
     a.q = q; a.k = k; a.v = v; a.out = out; a.lse = lse; a.n = s->n; a.n_hat = s->n_hat;
-    a.queue = w.queue; a.qlen = qlen; a.qhead = qhead; a.qcap = w.qcap; a.grid = sa.grid;
+    a.queue = w.queue; a.qlen = qlen; a.qbase = w.qbase; a.qhead = qhead; a.grid = sa.grid;
     a.slots = w.slots; a.split = w.split; a.split_count = w.split_count; a.part_o = w.part_o; a.part_ml = w.part_ml;
     a.pos0 = pos0;
     a.Hq = s->Hq; a.Hkv = s->Hkv; a.G = s->Hq / s->Hkv; a.BH = BH;
@@ -541,7 +539,7 @@ int ls_kv_compress_static(int device, const ls_shape* s, int32_t budget, const v
 size_t ls_decode_workspace_bytes(const ls_shape* s, int32_t cap, int32_t T) {
     if (!s || s->B <= 0 || s->Hq <= 0 || s->Hkv <= 0 || s->Hq % s->Hkv || (s->d != 64 && s->d != 128) || cap < 1 || T < 0) return 0;
     int nsplit, chunk;
-    ls::decode_split(s->B * s->Hkv, cap, T, &nsplit, &chunk);
+    ls::decode_split(s->B * s->Hkv, cap, T, ls::DECODE_MAX_SPLITS, &nsplit, &chunk);
     return up((size_t)s->B * s->Hq * nsplit * ls::decode_part_floats(s->d) * 4) + ALIGN;
 }
 
@@ -562,13 +560,19 @@ int ls_decode_attend(ls_ctx* c, const ls_shape* s, int32_t cap, int32_t T, const
     a.q = q; a.kc = k_c; a.vc = v_c; a.kt = k_t; a.vt = v_t; a.cnt = cnt; a.out = out; a.lse = lse;
     a.B = s->B; a.Hq = s->Hq; a.Hkv = s->Hkv; a.G = s->Hq / s->Hkv; a.cap = cap; a.T = T;
     a.scale_log2e = scale_log2e(s);
-    ls::decode_split(s->B * s->Hkv, cap, T, &a.nsplit, &a.chunk);
     a.done = decode_set(c, c->decode_calls);
     a.done_clear = decode_set(c, c->decode_calls + 2);
     a.clear_heads = c->decode_heads > s->B * s->Hkv ? c->decode_heads : s->B * s->Hkv;
+    // as many splits as the workspace has room for.  (The result of one split goes to `out`; a workspace that would not hold it is
+    // refused all the same.)
+    Bump bp{nullptr, 0, 0};
+    for (int limit = ls::DECODE_MAX_SPLITS; limit > 0; limit = a.nsplit - 1) {
+        ls::decode_split(s->B * s->Hkv, cap, T, limit, &a.nsplit, &a.chunk);
+        bp = Bump{c->ws, c->ws_bytes, 0};
+        a.part = bp.take<float>((size_t)s->B * s->Hq * a.nsplit * (a.nsplit > 1 ? ls::decode_part_floats(s->d) : (size_t)s->d + 2));
+        if (bp.ok()) break;
+    }
     if (ls::decode_smem_bytes(s->d, a.G, a.nsplit) > 156 * 1024) return fail(c, LS_ESHAPE, "ls_decode_attend: group too large for LDS");
-    Bump bp{c->ws, c->ws_bytes, 0};
-    a.part = bp.take<float>((size_t)s->B * s->Hq * a.nsplit * ls::decode_part_floats(s->d));
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_decode_attend: workspace of %zu bytes is too small", c->ws_bytes);
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_decode_attend: hipSetDevice failed");
     hipError_t e = ls::run_decode(a, s->d, static_cast<hipStream_t>(stream));
@@ -637,16 +641,17 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
     if (carve_prefill(c, s, w)) return w.code;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t items = (size_t)s->B * s->Hq * w.nqb;
-    std::vector<uint4> q(8 * (size_t)w.qcap);
-    int32_t len[8];
+    std::vector<uint4> q(items + w.slots);
+    int32_t len[8], base[8];
     if (hipSetDevice(c->device) != hipSuccess) return LS_EHIP;
     if (hipMemcpyAsync(q.data(), w.queue, q.size() * sizeof(uint4), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
     if (hipMemcpyAsync(len, w.qlen, sizeof(len), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
+    if (hipMemcpyAsync(base, w.qbase, sizeof(base), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
     if (hipStreamSynchronize(st) != hipSuccess) return LS_EHIP;
     for (int x = 0; x < 8; ++x) {                          // an item in parts is listed once, by its first part
         host_qlen[x] = 0;
-        for (int i = 0; i < len[x] && i < w.qcap; ++i) {
-            const uint4 e = q[(size_t)x * w.qcap + i];
+        for (int i = 0; i < len[x] && (size_t)base[x] + i < q.size(); ++i) {
+            const uint4 e = q[(size_t)base[x] + i];
             if ((e.y & 0xFF) == 0 && (size_t)host_qlen[x] < items) host_queue[x * items + host_qlen[x]++] = e.x;
         }
     }

@@ -332,12 +332,12 @@ size_t decode_part_floats(int d) { return (size_t)d + 4; }
 // but at least four tiles in each, and no split at all while the waves of one workgroup get through with two or three
 // tiles each (measured at 8 KV heads of 128: 17 tiles 8.0 us in one workgroup, 8.2 us in four, 7.9 us in eight; 32
 // tiles 10.7 / 8.3 / 8.2 us; 512 workgroups instead of 256 cost 10 to 50 % on large caches).
-void decode_split(int BK, int cap, int T, int* nsplit, int* chunk) {
+void decode_split(int BK, int cap, int T, int limit, int* nsplit, int* chunk) {
     const int tiles = (cap + DEC_TILE - 1) / DEC_TILE + (T + DEC_TILE - 1) / DEC_TILE;
     int want = 256 / BK;
     const int most = tiles <= 2 * DEC_WAVES + 2 ? 1 : tiles / 4;
     if (want > most) want = most;
-    if (want > 128) want = 128;
+    if (want > limit) want = limit;
     if (want < 1) want = 1;
     *chunk = (tiles + want - 1) / want;
     *nsplit = (tiles + *chunk - 1) / *chunk;

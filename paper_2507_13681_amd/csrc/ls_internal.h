@@ -84,9 +84,9 @@ struct SchedArgs {
     const uint32_t* ncol;     // [BH][nqb]
     int tab_len;
     int64_t n, pos0;
-    uint4* queue;             // [8][qcap] entries: {bh << 16 | qb, part | parts << 8 | first slot << 16, key blocks, columns}
-    int qcap;
+    uint4* queue;             // [items + slots] entries, one queue behind the other: {bh << 16 | qb, part | parts << 8 | first slot << 16, key blocks, columns}
     int32_t* qlen;            // [8]
+    int32_t* qbase;           // [8] first entry of each queue
     int32_t* qhead;           // [8] next entry to hand out (the first ones go by workgroup number)
     int grid;                 // workgroups of the attention kernel
     int slots;                // results of parts that the workspace holds (0: no item is split)
@@ -106,9 +106,8 @@ struct PrefillArgs {
     const int32_t* v_idx;
     int cap_v;
     const uint4* queue;       // work queues built by sched_kernel
-    const int32_t* qlen;
+    const int32_t *qlen, *qbase;
     int32_t* qhead;
-    int qcap;                 // entries per queue
     int grid;
     int slots;
     const uint2* split;
@@ -157,7 +156,8 @@ hipError_t run_score(const ScoreArgs& a, int dtype, int d, int mode, hipStream_t
 hipError_t run_decode(const DecodeArgs& a, int d, hipStream_t st);
 size_t decode_smem_bytes(int d, int G, int nsplit);
 size_t decode_part_floats(int d);                                   // floats of one partial result
-void decode_split(int BK, int cap, int T, int* nsplit, int* chunk);   // chunk: 32-key tiles per workgroup
+void decode_split(int BK, int cap, int T, int limit, int* nsplit, int* chunk);   // at most `limit` splits; chunk: 32-key tiles per workgroup
+constexpr int DECODE_MAX_SPLITS = 128;
 // Union of two selections per head (the accumulated line set of Alg. 1): lists a and b in, ascending unique list out.
 struct MergeArgs {
     int64_t n;

@@ -267,7 +267,7 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     __shared__ uint16_t heads[SCHED_MAX_HEADS];
     __shared__ uint16_t cost_s[SPLIT_ITEMS];              // costs of all items, where they are few
     __shared__ int nheads;
-    __shared__ uint32_t wsum[16];
+    __shared__ uint32_t wsum[16], base;                    // base: entries of the queues before this one, which lie ahead of it
     const int tid = threadIdx.x;
     const int groups = a.BH / a.G;
     const bool sorted = groups <= SCHED_MAX_GROUPS;
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     if (cached)
         for (uint32_t it = tid; it < all_items; it += SCHED_THREADS) cost_s[it] = (uint16_t)item_cost((int)(it / nqb), (int)(it % nqb));
     for (int i = tid; i < 4097; i += SCHED_THREADS) hist[i] = 0u;
-    if (tid == 0) nheads = 0;
+    if (tid == 0) { nheads = 0; base = 0u; }
     if (sorted) {                                          // every block repeats this small computation
         for (int gi = tid; gi < groups; gi += SCHED_THREADS) {
             const int b = gi / a.Hkv, kvh = gi % a.Hkv;
@@ -320,9 +320,12 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
         }
     }
     __syncthreads();
+    uint8_t* head_bin = reinterpret_cast<uint8_t*>(gcost);  // (the costs of the groups have been used; at most 8192 heads)
+    static_assert(SCHED_MAX_HEADS <= sizeof(gcost), "a byte for every head");
     for (int bh = tid; bh < a.BH; bh += SCHED_THREADS) {   // heads of this bin (order inside the list is free)
         const int b = bh / a.Hq, h = bh % a.Hq, gi = b * a.Hkv + h / a.G;
         const int bin = sorted ? (int)bin_of[gi] : (gi & 7);
+        head_bin[bh] = (uint8_t)bin;
         if (bin == x) { const int i = atomicAdd(&nheads, 1); if (i < SCHED_MAX_HEADS) heads[i] = (uint16_t)bh; }
     }
     // longest part: the same in every block, from the costs of all items
@@ -358,6 +361,15 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
         return p < 1 ? 1 : p > SPLIT_MAX_PARTS ? SPLIT_MAX_PARTS : p;
     };
     __syncthreads();
+    uint32_t ahead = 0;
+    if (lmax < 4096) {
+        for (uint32_t it = tid; it < all_items; it += SCHED_THREADS) if (head_bin[it / nqb] < x) ahead += (uint32_t)parts_of(cost_s[it]);
+    } else {
+        for (int bh = tid; bh < a.BH; bh += SCHED_THREADS) if (head_bin[bh] < x) ahead += nqb;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) ahead += __shfl_xor(ahead, off, 64);
+    if ((tid & 63) == 0 && ahead) atomicAdd(&base, ahead);
     const int nh_ = nheads < SCHED_MAX_HEADS ? nheads : SCHED_MAX_HEADS;
     const uint32_t items = (uint32_t)nh_ * nqb;
     for (uint32_t it = tid; it < items; it += SCHED_THREADS) {
@@ -386,11 +398,11 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
             slot0 = (uint32_t)atomicAdd(&a.split_count[0], p);
             a.split[atomicAdd(&a.split_count[1], 1)] = make_uint2(item, (uint32_t)p | (slot0 << 16));
         }
-        uint4* q = a.queue + (int64_t)x * a.qcap + posn;
+        uint4* q = a.queue + base + posn;
         const uint32_t bkv = (uint32_t)(bh / a.Hq * a.Hkv + bh % a.Hq / a.G);
         for (int e = 0; e < p; ++e) q[e] = make_uint4(item, (uint32_t)e | ((uint32_t)p << 8) | (slot0 << 16), n1 | (bkv << 16), nv);
     }
-    if (tid == 0) { a.qlen[x] = (int)entries; a.qhead[x] = (a.grid - x + 7) / 8; }
+    if (tid == 0) { a.qlen[x] = (int)entries; a.qbase[x] = (int)base; a.qhead[x] = (a.grid - x + 7) / 8; }
 }
 
 // Persistent launch: the workgroups that are resident at once (256 CUs x per_cu); any number drains the queues, but a
@@ -407,11 +419,11 @@ int prefill_grid(int dtype, int d, int64_t items, int slots) {
 // the end every workgroup would update it once for nothing, and updates of one counter take turns.  item = ~0 when every
 // queue is drained (each queue hands out each entry once and never refills, so the search ends).
 struct EntrySource {
-    int own, x, len;                          // lane l < 8: queue (own + l) % 8 and its length
+    int own, x, len, base;                    // lane l < 8: queue (own + l) % 8, its length and first entry
     int at;                                   // place taken in the own queue, -1: none
     bool plenty;
     __device__ __forceinline__ void init(const PrefillArgs& a, int lane) {
-        own = blockIdx.x & 7; x = (own + lane) & 7; len = lane < 8 ? a.qlen[x] : 0;
+        own = blockIdx.x & 7; x = (own + lane) & 7; len = lane < 8 ? a.qlen[x] : 0; base = a.qbase[x];
         at = (int)(blockIdx.x >> 3); plenty = true;
     }
     __device__ __forceinline__ void ahead(const PrefillArgs& a, int lane) {
@@ -426,7 +438,7 @@ struct EntrySource {
             const int i = at;
             at = -1;
             plenty = own_len - i > 128;
-            return a.queue[(int64_t)own * a.qcap + i];
+            return a.queue[__builtin_amdgcn_readfirstlane(base) + i];
         }
         plenty = false;
         for (;;) {
@@ -437,8 +449,8 @@ struct EntrySource {
             int i = 0;
             if (lane == src) i = atomicAdd(&a.qhead[x], 1);
             i = __builtin_amdgcn_readlane(i, src);
-            const int xs = __builtin_amdgcn_readlane(x, src), ls = __builtin_amdgcn_readlane(len, src);
-            if (i < ls) return a.queue[(int64_t)xs * a.qcap + i];
+            const int ls = __builtin_amdgcn_readlane(len, src);
+            if (i < ls) return a.queue[__builtin_amdgcn_readlane(base, src) + i];
         }
     }
 };

@@ -44,8 +44,8 @@ def test_decode_splits_past_the_count(oracle, d, G, Hkv, cap):
     ("f32", 128, 2049, 1),         # one row
 ])
 def test_prefill_parts_of_long_items(oracle, dtype, d, n, n_hat):
-    """Few row blocks over a long context: items are cut into parts and put together again; in a workspace without room
-    for parts they are not, with the same result."""
+    """Few row blocks over a long context: items are cut into parts and put together again; into fewer in a workspace with
+    less room for them, into none in one without, with the same result."""
     from tests.gpu_util import Pipeline, dev_lists
     from tests.test_gpu_random_shapes import _selection
     print(f"parts {dtype} d={d} n={n} n_hat={n_hat}", flush=True)
@@ -57,9 +57,10 @@ def test_prefill_parts_of_long_items(oracle, dtype, d, n, n_hat):
     rows = np.unique(rng.integers(0, Hq * n_hat, 60))
     ref, ref_lse = oracle.attend(q, k, v, v_idx, v_cnt, s_idx, s_cnt, rows=rows, mode=1)
     pipe = Pipeline(q, k, v, 1, dtype)
-    small = binding.Context(workspace=2 << 20)
+    # the parts' results take (4 d + 8) * 128 bytes each, at least a dozen at a time; everything else less than 64 KB
+    some, none = binding.Context(workspace=2 << 20), binding.Context(workspace=1 << 18)
     tol = (2e-2, 5e-3, 2e-3) if dtype == "bf16" else (1e-4, 1e-5, 1e-4)
-    for ctx in (pipe.ctx, small):
+    for ctx in (pipe.ctx, some, none):
         pipe.ctx = ctx
         out, lse = pipe.prefill(dev_lists(v_idx, v_cnt, s_idx, s_cnt), sentinel=True)
         torch.cuda.synchronize()
@@ -72,6 +73,50 @@ def test_prefill_parts_of_long_items(oracle, dtype, d, n, n_hat):
         alive = np.isfinite(ref_lse)
         np.testing.assert_array_equal(np.isfinite(l), alive)
         assert np.abs(l[alive] - ref_lse[alive]).max(initial=0) <= tol[2]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat", [(1, 1, 1, 1, 1), (2, 8, 2, 900, 900), (1, 40, 5, 300, 129), (1, 24, 8, 2000, 1)])
+def test_prefill_in_the_smallest_workspace(oracle, B, Hq, Hkv, n, n_hat):
+    """The eight work queues lie one behind the other: the call needs 20 bytes per item (row block of a head) beside the
+    bitmap and tables of each head, and says so where they are not there."""
+    from tests.gpu_util import Pipeline, dev_lists
+    from tests.test_gpu_random_shapes import _selection
+    print(f"smallest workspace B={B} Hq={Hq} Hkv={Hkv} n={n} n_hat={n_hat}", flush=True)
+    q, k, v = inputs.make_plain(B, Hq, Hkv, n, n_hat, 64, dtype="bf16", seed=n, q_scale=1.5)
+    lists = _selection(np.random.default_rng(n), B, Hq, n)
+    ref, _ = oracle.attend(q, k, v, *lists)
+    pipe = Pipeline(q, k, v, 1, "bf16")
+    up = lambda x: (x + 255) // 256 * 256
+    heads, blocks = B * Hq, (n - (n - n_hat) // 128 * 128 + 127) // 128
+    table = n // 64 + 4
+    need = up(heads * ((n + 31) // 32 + 12) * 4) + up(heads * 4) + up(heads * (table + 1) * 2) + up(heads * blocks * 4) + 256 + up(heads * table) + up(heads * blocks * 16)
+    pipe.ctx = binding.Context(workspace=need)
+    out, _ = pipe.prefill(dev_lists(*lists), sentinel=True)
+    queues, nqb = pipe.ctx.debug_prefill_queues(pipe.shape)
+    assert nqb == blocks
+    items = np.sort(np.concatenate(queues))
+    np.testing.assert_array_equal(items, np.sort([h << 16 | b for h in range(heads) for b in range(blocks)]))
+    err = np.abs(out.float().cpu().numpy().reshape(-1, 64) - ref)
+    assert err.max() <= 2e-2 and err.mean() <= 5e-3
+    pipe.ctx = binding.Context(workspace=need - 256)
+    with pytest.raises(binding.LoopServeError):
+        pipe.prefill(dev_lists(*lists))
+
+
+@pytest.mark.parametrize("d,splits", [(128, 7), (64, 2), (128, 1)])
+def test_decode_with_room_for_fewer_splits(oracle, d, splits):
+    """ls_decode_attend cuts the keys into as many splits as the workspace has room for."""
+    B, Hkv, G, cap, T = 1, 4, 4, 3000, 9
+    print(f"decode splits d={d} splits={splits}", flush=True)
+    q, kc, vc, cnt, kt, vt = _case(B, G * Hkv, Hkv, cap, T, d, seed=splits)
+    shape = binding.make_shape(B, G * Hkv, Hkv, d, cap + T, 1, 1, "bf16")
+    room = B * G * Hkv * splits * (d + 4) * 4
+    assert room + 256 < binding.decode_workspace_bytes(shape, cap, T)
+    ctx = binding.Context(workspace=room)
+    out = torch.full((B, G * Hkv, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    ctx.ls_decode_attend(shape, q.cuda(), kc.cuda(), vc.cuda(), torch.from_numpy(cnt).cuda(), kt.cuda(), vt.cuda(), out, None)
+    ref, _ = oracle.decode(q.float().numpy(), kc.float().numpy(), vc.float().numpy(), cnt, kt.float().numpy(), vt.float().numpy())
+    assert np.abs(out.float().cpu().numpy() - ref).max() <= 2e-2
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,n,w,d,dtype", [
