@@ -361,13 +361,18 @@ __device__ __forceinline__ int first_entry(int fe) {
     const int l = __ffsll((unsigned long long)any) - 1;
     return E * l + __builtin_amdgcn_readlane(fe, l);
 }
-// entry i of the wave's 64 E (i uniform)
-template <int E, typename V>
-__device__ __forceinline__ V pick_entry(const V (&v)[E], int i) {
-    V x = v[0];
+// entry i of the wave's 64 E (i uniform).  The lane's registers are read first and the choice is among scalars: a choice among
+// the registers becomes an array in scratch memory, E stores and a load in the chain of every run.
+template <int E>
+__device__ __forceinline__ float pick_entry(const float (&v)[E], int i) {
+    const int l = i / E;
+    int x = __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[0]), l);
 #pragma unroll
-    for (int e = 1; e < E; ++e) x = (i % E) == e ? v[e] : x;
-    return __builtin_bit_cast(V, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), i / E));
+    for (int e = 1; e < E; ++e) {
+        const int y = __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[e]), l);
+        x = (i % E) == e ? y : x;
+    }
+    return __builtin_bit_cast(float, x);
 }
 
 // Lane l holds the gains of the entries E l .. E l + E - 1.  x[e] = the sum behind entry e, starting from `sum` ahead of
@@ -1013,14 +1018,15 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
 
     // Of a list: its lines taken, and the thread's entry of the block of the sorted list loaded last: line, weight, and
     // (valid) what the other list's lines taken so far cover of it.
-    struct List { int id, taken, base; bool valid; int32_t line; float weight, covered; };
+    // (`valid` is an int: the padding behind a bool would be swapped through scratch memory)
+    struct List { int id, taken, base, valid; int32_t line; float weight, covered; };
     auto load = [&](List& l) {
         l.base = l.taken;
         const int i = l.base + tid < n ? l.base + tid : n - 1;
         l.line = a.sidx1[((int64_t)l.id * a.BH + bh) * a.n + i];
         l.weight = ((l.id == 0 ? a.slash : a.vert) + (int64_t)bh * a.n)[l.line];
         l.covered = 0.f;
-        l.valid = false;
+        l.valid = 0;
     };
     List X, O;                                 // the list whose lines are the candidates, and the other one
     X.id = X.taken = 0; O.id = 1; O.taken = 0;
@@ -1111,7 +1117,7 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
                     }
                 }
                 X.covered = (float)part;
-                X.valid = true;
+                X.valid = 1;
             }
             if (head_moved) cell[tid] = head_cell;
             __syncthreads();
@@ -1170,7 +1176,7 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
             sum = sum_now;
             if (j >= 0 && j < got) atomicOr(&map_x[x >> 5], 1u << (x & 31));
             X.taken += got;
-            if (got > 0) O.valid = false;
+            if (got > 0) O.valid = 0;
             if (got == run && X.taken < n && X.taken - X.base > XW_AGAIN) load(X);
             change = decided = end < C;        // then the first pick of the other list has been decided
             most = XW_THREADS;
