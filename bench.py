@@ -110,9 +110,9 @@ def main():
         print(json.dumps({"metric": "decode step over the compressed cache, algorithmic bytes per second", "value": round(nbytes / (ms * 1e-3) / 1e9, 2),
                           "unit": "GB/s", "ms_per_call": round(ms, 5), "steps": args.steps, "warmup": args.warmup, "dtype": "bf16", "data": "synthetic",
                           "config": {"workload": "llama70b_16k_b4 decode", "B": B, "Hq": Hq, "Hkv": Hkv, "d": d, "retained": cap, "since": T},
-                          "roofline": {"kernel": "decode_partial_kernel", "bound": "hbm", "achieved": round(nbytes / (ms * 1e-3) / 1e9, 2), "peak": 8000.0,
+                          "roofline": {"kernel": "decode_kernel", "bound": "hbm", "achieved": round(nbytes / (ms * 1e-3) / 1e9, 2), "peak": 8000.0,
                                        "unit": "GB/s", "frac": round(nbytes / (ms * 1e-3) / 8e12, 4), "bytes": nbytes,
-                                       "note": "per call (two kernels), launch gaps included"}}))
+                                       "note": "per call (one kernel), launch gaps included"}}))
         return
 
     cfg = inputs.CONFIGS[args.workload]
@@ -167,8 +167,8 @@ def main():
 
     def step():
         # compress is issued once the scoring kernels (which fill the chip themselves) are queued, so that it runs
-        # beside the selection kernels; measured: beside score + select 2.80 ms per step, after everything 2.86,
-        # beside select only 2.73, beside the attention kernel 3.40
+        # beside the selection kernels; measured: beside select 2.23-2.24 ms per step, beside the attention kernel 2.24,
+        # beside score + select 2.24-2.32, after everything 2.27 (the step without it: 2.20-2.21)
         main = torch.cuda.current_stream()
         f_score()
         side.wait_stream(main)
@@ -250,7 +250,7 @@ def main():
         "by_head_kind": by_kind,
         "ms_per_call": {a: round(b, 4) for a, b in br.items()},
         "wall_s": round(wall, 3),
-        "roofline": {"kernel": "prefill_bf16_kernel" if cfg.dtype == "bf16" else "prefill_kernel", "bound": "mfma", "achieved": round(achieved, 3), "peak": peak,
+        "roofline": {"kernel": ("prefill_bf16_kernel" if cfg.dtype == "bf16" else "prefill_kernel") + " + combine_kernel", "bound": "mfma", "achieved": round(achieved, 3), "peak": peak,
                      "unit": "TFLOP/s", "frac": round(achieved / peak, 4), "traffic": args.traffic_bytes,
                      "kernel_ms": round(kern_ms, 4), "launches": launches},
         "paper_context": "no speed-up printed in the paper's text; its machine: 1x H100 80GB + 8-core Xeon Gold 6542Y",

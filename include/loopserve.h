@@ -248,13 +248,14 @@ int ls_decode_attend(ls_ctx* ctx, const ls_shape* shape, int32_t cap, int32_t T,
 size_t ls_decode_workspace_bytes(const ls_shape* shape, int32_t cap, int32_t T);
 
 /*
- * Timing of the sparse attention kernel itself (the dominant kernel of ls_sparse_prefill), for
- * roofline reports.  After ls_profile_enable(ctx, 1) every ls_sparse_prefill call attaches a pair
- * of HIP events to that one kernel launch on the call's stream: they receive the start and stop
- * time of the dispatch itself, and no marker is put into the stream (this creates two events per
- * call, so leave it off in allocation-free loops).  ls_profile_prefill_kernel_ms waits for the recorded
- * events and returns the mean kernel duration in milliseconds and the number of launches seen since
- * profiling was enabled.  ls_profile_enable(ctx, 0) stops recording and drops the events.
+ * Timing of the sparse attention itself (the dominant part of ls_sparse_prefill), for roofline
+ * reports.  After ls_profile_enable(ctx, 1) every ls_sparse_prefill call attaches a pair of HIP
+ * events to the launch of the attention kernel and, where long row blocks may have been cut into
+ * parts, another to the launch that puts the parts' results together: they receive the start and
+ * stop time of the dispatches themselves, and no marker is put into the stream (this creates events
+ * on every call, so leave it off in allocation-free loops).  ls_profile_prefill_kernel_ms waits for the
+ * recorded events and returns the mean of a call's kernel time (the sum of the two) in milliseconds
+ * and the number of calls seen since profiling was enabled.  ls_profile_enable(ctx, 0) stops recording and drops the events.
  */
 int ls_profile_enable(ls_ctx* ctx, int on);
 int ls_profile_prefill_kernel_ms(ls_ctx* ctx, double* mean_ms, int32_t* launches);

@@ -4,11 +4,10 @@
 #include <stdio.h>
 #include <string.h>
 
-#include <new>
-#include <utility>
-#include <vector>
-
+#include <array>
 #include <mutex>
+#include <new>
+#include <vector>
 
 #include "../../include/loopserve.h"
 #include "../../include/loopserve_test_hooks.h"
@@ -34,9 +33,10 @@ struct ls_ctx {
     int decode_heads;         // most KV heads of such a call: the part of a set that is cleared
     int walk_spin_limit;      // bound of the waits inside walk_kernel (test hook)
     char err[256];
-    // optional timing of the sparse attention kernel (ls_profile_*): event pairs on the call's stream
+    // optional timing of the sparse attention (ls_profile_*), per call: start and stop of the attention kernel, and of the launch
+    // that puts parts together (null where there is none)
     bool profile;
-    std::vector<std::pair<hipEvent_t, hipEvent_t>> events;
+    std::vector<std::array<hipEvent_t, 4>> events;
 };
 
 namespace {
@@ -56,6 +56,12 @@ int fail(ls_ctx* c, int code, const char* fmt, ...) {
         va_end(ap);
     }
     return code;
+}
+
+void drop_events(ls_ctx* c) {
+    for (auto& call : c->events)
+        for (hipEvent_t e : call) if (e) (void)hipEventDestroy(e);
+    c->events.clear();
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -218,7 +224,7 @@ int ls_create(ls_ctx** out, int device, size_t workspace_bytes) {
 void ls_destroy(ls_ctx* c) {
     if (!c) return;
     (void)hipSetDevice(c->device);
-    for (auto& e : c->events) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
+    drop_events(c);
     if (c->ws) (void)hipFree(c->ws);
     if (c->status) (void)hipFree(c->status);
     delete c;
@@ -449,13 +455,15 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
     a.nqb = nqb;
     a.words = words; a.tab_len = tab_len; a.scale_log2e = scale_log2e(s);
     a.obits = obits; a.tab = tab; a.v_idx = v_idx; a.cap_v = cap_v;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (c->profile) {
-        if (hipEventCreate(&e0) != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill: hipEventCreate failed");
-        if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return fail(c, LS_EHIP, "ls_sparse_prefill: hipEventCreate failed"); }
-    }
-    e = ls::launch_prefill(a, s->dtype, s->d, static_cast<hipStream_t>(stream), e0, e1);
-    if (c->profile) c->events.emplace_back(e0, e1);
+    std::array<hipEvent_t, 4> ev{};
+    if (c->profile)
+        for (size_t i = 0; i < (w.slots > 0 ? 4u : 2u); ++i)
+            if (hipEventCreate(&ev[i]) != hipSuccess) {
+                for (size_t j = 0; j < i; ++j) (void)hipEventDestroy(ev[j]);
+                return fail(c, LS_EHIP, "ls_sparse_prefill: hipEventCreate failed");
+            }
+    e = ls::launch_prefill(a, s->dtype, s->d, static_cast<hipStream_t>(stream), c->profile ? ev.data() : nullptr);
+    if (c->profile) c->events.push_back(ev);
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill: %s", hipGetErrorString(e));
     return LS_OK;
 }
@@ -584,8 +592,7 @@ int ls_decode_attend(ls_ctx* c, const ls_shape* s, int32_t cap, int32_t T, const
 int ls_profile_enable(ls_ctx* c, int on) {
     if (!c) return LS_EINVAL;
     (void)hipSetDevice(c->device);
-    for (auto& e : c->events) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
-    c->events.clear();
+    drop_events(c);
     c->profile = on != 0;
     return LS_OK;
 }
@@ -595,10 +602,13 @@ int ls_profile_prefill_kernel_ms(ls_ctx* c, double* mean_ms, int32_t* launches) 
     double tot = 0.0;
     int cnt = 0;
     for (auto& e : c->events) {
-        if (hipEventSynchronize(e.second) != hipSuccess) return fail(c, LS_EHIP, "ls_profile: hipEventSynchronize failed");
-        float ms = 0.f;
-        if (hipEventElapsedTime(&ms, e.first, e.second) != hipSuccess) return fail(c, LS_EHIP, "ls_profile: hipEventElapsedTime failed");
-        tot += ms; ++cnt;
+        for (int k = 0; k < 4 && e[k]; k += 2) {
+            if (hipEventSynchronize(e[k + 1]) != hipSuccess) return fail(c, LS_EHIP, "ls_profile: hipEventSynchronize failed");
+            float ms = 0.f;
+            if (hipEventElapsedTime(&ms, e[k], e[k + 1]) != hipSuccess) return fail(c, LS_EHIP, "ls_profile: hipEventElapsedTime failed");
+            tot += ms;
+        }
+        ++cnt;
     }
     *mean_ms = cnt ? tot / cnt : 0.0;
     *launches = cnt;

@@ -177,8 +177,8 @@ hipError_t run_gather_rows(const void* const* src, void* const* dst, int tensors
                            int BK, int64_t len, int budget, int row_bytes, hipStream_t st);      // one or two tensors
 hipError_t launch_plan(const PlanArgs& a, int BH, hipStream_t st);
 hipError_t launch_sched(const SchedArgs& a, hipStream_t st);
-// ev0 / ev1 (both or neither): events that receive the start and stop time of the attention kernel's own dispatch
-hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// ev (null or four events): the start and stop time of the attention kernel's own dispatch, and, where a.slots > 0, of combine_kernel's
+hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st, const hipEvent_t* ev = nullptr);
 size_t prefill_smem_bytes(int dtype, int d, int tab_len);
 int prefill_block_rows();
 int prefill_grid(int dtype, int d, int64_t items, int slots);

@@ -1316,8 +1316,11 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
 }
 
 template <typename T, int D>
-static void launch_combine(const PrefillArgs& a, hipStream_t st) {
-    if (a.slots > 0) hipLaunchKernelGGL((combine_kernel<T, D>), dim3(a.slots < 256 ? 2 * a.slots : 512), dim3(256), 0, st, a);
+static void launch_combine(const PrefillArgs& a, hipStream_t st, const hipEvent_t* ev) {
+    const dim3 grid(a.slots < 256 ? 2 * a.slots : 512);
+    if (a.slots == 0) return;
+    if (ev) hipExtLaunchKernelGGL((combine_kernel<T, D>), grid, dim3(256), 0, st, ev[2], ev[3], 0, a);
+    else hipLaunchKernelGGL((combine_kernel<T, D>), grid, dim3(256), 0, st, a);
 }
 
 template <int D>
@@ -1326,12 +1329,12 @@ static size_t prefill_bf16_smem(int tab_len) {
 }
 
 template <int D>
-static hipError_t launch_prefill_bf16(const PrefillArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+static hipError_t launch_prefill_bf16(const PrefillArgs& a, hipStream_t st, const hipEvent_t* ev) {
     const size_t smem = prefill_bf16_smem<D>(a.tab_len);
     // with events: they take the start and stop time stamps of this dispatch itself, no marker goes into the stream
-    if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
+    if (ev) hipExtLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev[0], ev[1], 0, a);
     else hipLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
-    launch_combine<bf16_t, D>(a, st);
+    launch_combine<bf16_t, D>(a, st, ev);
     return hipGetLastError();
 }
 
@@ -1342,11 +1345,11 @@ static size_t prefill_smem_t(int tab_len) {
 }
 
 template <typename T, int D>
-static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t st, const hipEvent_t* ev) {
     const size_t smem = prefill_smem_t<T, D>(a.tab_len);
-    if (ev0 && ev1) hipExtLaunchKernelGGL((prefill_kernel<T, D>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev0, ev1, 0, a);
+    if (ev) hipExtLaunchKernelGGL((prefill_kernel<T, D>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev[0], ev[1], 0, a);
     else hipLaunchKernelGGL((prefill_kernel<T, D>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
-    launch_combine<T, D>(a, st);
+    launch_combine<T, D>(a, st, ev);
     return hipGetLastError();
 }
 
@@ -1381,11 +1384,11 @@ hipError_t launch_sched(const SchedArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    if (dtype == 0 && d == 128) return launch_prefill_bf16<128>(a, st, ev0, ev1);
-    if (dtype == 0 && d == 64) return launch_prefill_bf16<64>(a, st, ev0, ev1);
-    if (dtype == 1 && d == 128) return launch_prefill_t<float, 128>(a, st, ev0, ev1);
-    if (dtype == 1 && d == 64) return launch_prefill_t<float, 64>(a, st, ev0, ev1);
+hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st, const hipEvent_t* ev) {
+    if (dtype == 0 && d == 128) return launch_prefill_bf16<128>(a, st, ev);
+    if (dtype == 0 && d == 64) return launch_prefill_bf16<64>(a, st, ev);
+    if (dtype == 1 && d == 128) return launch_prefill_t<float, 128>(a, st, ev);
+    if (dtype == 1 && d == 64) return launch_prefill_t<float, 64>(a, st, ev);
     return hipErrorInvalidValue;
 }
 

@@ -372,3 +372,30 @@ def test_retention_sizes(oracle, ln, budget, d, dtype):
         np.testing.assert_array_equal(got, oracle.topb(score[0, h].cpu().numpy(), budget))
         at = torch.from_numpy(got.astype(np.int64)).cuda()
         assert torch.equal(k_out[0, h], pipe.k[0, h, at]) and torch.equal(v_out[0, h], pipe.v[0, h, at])
+
+
+def test_profile_covers_the_parts():
+    """ls_profile_* with and without room for parts: every call counted, the time of its kernels below the calls' own."""
+    from tests.gpu_util import Pipeline, dev_lists
+    n, n_hat, H = 9000, 100, 8
+    q, k, v = inputs.make_plain(1, H, 2, n, n_hat, 128, dtype="bf16", seed=1)
+    every = np.broadcast_to(np.arange(n, dtype=np.int32), (1, H, n))
+    lists = dev_lists(every, np.full((1, H), n), every, np.full((1, H), n))       # dense heads: 141 tiles an item
+    pipe = Pipeline(q, k, v, 1, "bf16")
+    times = []
+    for ctx in (pipe.ctx, binding.Context(workspace=1 << 18)):
+        pipe.ctx = ctx
+        pipe.prefill(lists)
+        ctx.profile_enable(True)
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(10):
+            pipe.prefill(lists)
+        e1.record()
+        torch.cuda.synchronize()
+        ms, calls = ctx.profile_prefill_kernel_ms()
+        ctx.profile_enable(False)
+        assert calls == 10 and 0 < ms < e0.elapsed_time(e1) / 10
+        times.append(ms)
+    print("attention kernels in parts and whole, ms:", times, flush=True)
+    assert times[0] < times[1]                             # sixteen items on 256 compute units: parts win, combining included
