@@ -17,8 +17,8 @@
 //   emit_kernel   one workgroup per (head, list): the chosen prefix of a sorted list becomes an
 //                 ascending index list (bitmap in LDS + prefix popcount).
 //   topb_*        Alg. 3: the `budget` largest scores per KV head by a radix select on the float bit patterns,
-//                 ties broken towards smaller indices, ascending output; by one workgroup a head up to
-//                 TB_ONE_LEN scores, spread over many, one launch per step, beyond.
+//                 ties broken towards smaller indices, ascending output; by one workgroup a head up to TB_FEW_LEN
+//                 scores (TB_ONE_LEN where there are heads enough), spread over many, one launch per step, beyond.
 #include "ls_device.h"
 #include "ls_internal.h"
 
@@ -1504,11 +1504,15 @@ __global__ __launch_bounds__(TB_THREADS) void topb_write_kernel(TopbArgs a) {
     }
 }
 
-// Caches of up to 1024 PER entries: one workgroup per KV head does all steps with the keys in registers, a wave holding
+// One workgroup per KV head, up to 1024 PER entries, does all steps with the keys in registers, a wave holding
 // consecutive entries.  The threshold is narrowed by two bits a step, the counts of the four quarters in the bytes of a
 // register (a histogram in LDS of a head's scores, which crowd into few digits, took 16 us), until the few keys left are
-// ranked directly or wanted as a whole.  The five launches above cost 4.5 us each: 32 heads of 16384 entries 29 us, now 16.
-constexpr int TB_ONE_LEN = 32768, TB_RANKED = 256;
+// ranked directly or wanted as a whole.  The launches above cost 4.5 us each: 32 heads of 16384 entries 29 us, now 16.
+// Beyond 16 keys a thread (TB_FEW_LEN) one workgroup takes longer than the launches spread over the chip, unless there are
+// heads enough to fill it: the whole of ls_kv_compress (d 64, 8 rows), spread / one workgroup a head, us: 16384 entries 33.8 / 29.1
+// (8 heads), 57.2 / 52.2 (32); 17000 entries 35.1 / 38.4 (8), 51.7 / 56.0 (24), 62.3 / 61.4 (32), 95.0 / 86.0 (64); 32768 entries
+// 40.4 / 44.8 (8), 57.1 / 62.3 (16), 84.5 / 84.7 (32), 149 / 132 (64).
+constexpr int TB_FEW_LEN = 16384, TB_ONE_LEN = 32768, TB_ONE_HEADS = 32, TB_RANKED = 256;
 template <int PER>
 __global__ __launch_bounds__(TB_THREADS) void topb_one_kernel(TopbArgs a) {
     __shared__ uint2 counts[2][16];
@@ -1682,9 +1686,9 @@ size_t topb_scratch_words(int BK, int64_t len) { return (size_t)BK * (3 * TB_BIN
 hipError_t run_topb(const TopbArgs& a0, int BK, uint32_t* scratch, hipStream_t st) {
     if (a0.len < 1 || a0.len > TOPB_MAX_LEN || a0.budget < 1) return hipErrorInvalidValue;
     TopbArgs a = a0;
-    if (a.len <= TB_ONE_LEN) {
+    if (a.len <= (BK >= TB_ONE_HEADS ? TB_ONE_LEN : TB_FEW_LEN)) {
         if (a.len <= 4096) hipLaunchKernelGGL(topb_one_kernel<4>, dim3(BK), dim3(TB_THREADS), 0, st, a);
-        else if (a.len <= 16384) hipLaunchKernelGGL(topb_one_kernel<16>, dim3(BK), dim3(TB_THREADS), 0, st, a);
+        else if (a.len <= TB_FEW_LEN) hipLaunchKernelGGL(topb_one_kernel<16>, dim3(BK), dim3(TB_THREADS), 0, st, a);
         else hipLaunchKernelGGL(topb_one_kernel<32>, dim3(BK), dim3(TB_THREADS), 0, st, a);
         return hipGetLastError();
     }

@@ -374,6 +374,29 @@ def test_retention_sizes(oracle, ln, budget, d, dtype):
         assert torch.equal(k_out[0, h], pipe.k[0, h, at]) and torch.equal(v_out[0, h], pipe.v[0, h, at])
 
 
+@pytest.mark.parametrize("B,Hkv,ln,budget", [
+    (4, 8, 16385, 16384), (4, 8, 32768, 300),                         # heads enough for one workgroup each, 32 keys a thread
+    (4, 8, 32769, 300), (31, 1, 32768, 5000),                         # too long for one; a head too few
+])
+def test_retention_of_many_heads(oracle, B, Hkv, ln, budget):
+    """Where one workgroup per head ends and the launches spread over the chip begin, by length and by heads."""
+    print(f"retention of many heads B={B} Hkv={Hkv} len={ln} budget={budget}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(ln)
+    k = torch.randn(B, Hkv, 97, 64, device="cuda", generator=g).to(torch.bfloat16)[:, :, torch.arange(ln, device="cuda") % 97].contiguous()
+    q = torch.randn(B, Hkv, 8, 64, device="cuda", generator=g).to(torch.bfloat16)
+    shape = binding.make_shape(B, Hkv, Hkv, 64, ln, 1, 8, "bf16")
+    ctx = binding.Context(shape, budget)
+    keep_idx = torch.full((B, Hkv, budget), -1, dtype=torch.int32, device="cuda")
+    keep_cnt = torch.zeros((B, Hkv), dtype=torch.int32, device="cuda")
+    ctx.ls_kv_compress(shape, budget, q, k, None, keep_idx, keep_cnt)
+    score = torch.empty((B, Hkv, ln), dtype=torch.float32, device="cuda")
+    ctx.debug_compress_score(shape, score)
+    assert (keep_cnt == budget).all()
+    for b in range(B):
+        for h in range(Hkv):
+            np.testing.assert_array_equal(keep_idx[b, h].cpu().numpy(), oracle.topb(score[b, h].cpu().numpy(), budget))
+
+
 def test_profile_covers_the_parts():
     """ls_profile_* with and without room for parts: every call counted, the time of its kernels below the calls' own."""
     from tests.gpu_util import Pipeline, dev_lists
