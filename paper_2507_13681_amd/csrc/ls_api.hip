@@ -203,12 +203,7 @@ int ls_create(ls_ctx** out, int device, size_t workspace_bytes) {
     {
         void* p = nullptr;
         const size_t bytes = ALIGN + COUNTER_BYTES;
-        // (calls may come on any stream: the zeros have to be there when this function returns)
-        if (hipMalloc(&p, bytes) != hipSuccess || hipMemset(p, 0, bytes) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
-            if (p) (void)hipFree(p);
-            delete c;
-            return LS_EWORKSPACE;
-        }
+        if (hipMalloc(&p, bytes) != hipSuccess || hipMemset(p, 0, bytes) != hipSuccess) { if (p) (void)hipFree(p); delete c; return LS_EWORKSPACE; }
         c->status = static_cast<int32_t*>(p);
         c->counters = reinterpret_cast<uint32_t*>(static_cast<unsigned char*>(p) + ALIGN);
     }
@@ -217,6 +212,8 @@ int ls_create(ls_ctx** out, int device, size_t workspace_bytes) {
         if (hipMalloc(&p, workspace_bytes) != hipSuccess) { (void)hipFree(c->status); delete c; return LS_EWORKSPACE; }
         c->ws = static_cast<unsigned char*>(p);
     }
+    // (hipMemset returns at once, and calls may come on a stream that does not wait for the default one)
+    if (hipStreamSynchronize(nullptr) != hipSuccess) { ls_destroy(c); return LS_EHIP; }
     *out = c;
     return LS_OK;
 }
