@@ -329,9 +329,11 @@ size_t decode_smem_bytes(int d, int G, int nsplit) {
 size_t decode_part_floats(int d) { return (size_t)d + 4; }
 
 // Split of the key axis: `chunk` tiles of a KV head per workgroup.  As many workgroups as the chip has compute units,
-// but at least four tiles in each, and no split at all while the waves of one workgroup get through with two or three
-// tiles each (measured at 8 KV heads of 128: 17 tiles 8.0 us in one workgroup, 8.2 us in four, 7.9 us in eight; 32
-// tiles 10.7 / 8.3 / 8.2 us; 512 workgroups instead of 256 cost 10 to 50 % on large caches).
+// but at least four tiles in each (512 workgroups instead of 256 cost 10 to 50 % on large caches), and no split at all while
+// the waves of one workgroup get through with two tiles each or little more.  Measured, one workgroup / splits of four tiles,
+// us: 8 KV heads, full caches of 14 tiles 7.7 / 7.9, 16 tiles 8.1 / 7.6, 18 tiles 8.6 / 8.0, 22 tiles 10.0 / 8.1, 34 tiles 12.8 /
+// 8.4; caches filled to three quarters 15 tiles 7.7 / 8.1, 16 tiles 7.8 / 7.8, 18 tiles 8.3 / 8.1; 64 KV heads, full 16 tiles 8.2 /
+// 8.7, 18 tiles 8.7 / 8.8.  The count is on the device: the line lies between what full and what partly filled caches ask for.
 void decode_split(int BK, int cap, int T, int limit, int* nsplit, int* chunk) {
     const int tiles = (cap + DEC_TILE - 1) / DEC_TILE + (T + DEC_TILE - 1) / DEC_TILE;
     int want = 256 / BK;

@@ -249,15 +249,20 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // results go to `slots` of the workspace and combine_kernel puts them together.  lmax is the mean number of tiles per
 // resident workgroup over SPLIT_SHARE, so the longest entry is a fraction of the run, but at least SPLIT_MIN: a part costs a
 // 64 KB result written and read (3-4 us of one CU's share of the memory bandwidth) against about 2 us per tile.
+// SPLIT_WGS is the resident workgroups of d = 128 for all types and dimensions.  Attention with 256 / 512 / 768, us: first turn of
+// 8192 rows 211 / 230 / 230 (d 64: 131 / 147 / 148), 10923 rows of 32768 1596 / 1543 / 1529, 5000 of 16384 at d 64 342 / 350 / 350, 1777
+// of 5003 at d 64 108 / 112 / 113, fp32 1024 of 4096 64 / 64 / 64: fewer, longer parts suit short contexts, more the long ones.
+// SPLIT_ITEMS is what a copy of all costs in LDS holds.  With 8192 instead, 131072 keys (4128 items) 12145 -> 12101 us, first turn of
+// 20000 rows (5024 items) 1114 -> 1096, B 2, 64 heads, 7000 of 16384 rows (7040 items) 1687 -> 1696: so many items balance by themselves.
 // ---------------------------------------------------------------------------------------------
 constexpr int SCHED_MAX_GROUPS = 2048;
 constexpr int SCHED_MAX_HEADS = 8192;      // heads one XCD's queue can take
 constexpr int SCHED_THREADS = 1024;
-constexpr int SPLIT_ITEMS = 4096;          // most items for which splitting is considered (more of them balance by themselves)
+constexpr int SPLIT_ITEMS = 4096;          // most items for which splitting is considered
 constexpr int SPLIT_SLOTS = 1024;          // most parts of split items
 constexpr int SPLIT_MIN = 4;               // tiles
 constexpr int SPLIT_SHARE = 2;
-constexpr int SPLIT_WGS = 512;             // workgroups resident on the chip (d = 128)
+constexpr int SPLIT_WGS = 512;
 constexpr int SPLIT_MAX_PARTS = 64;
 __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     __shared__ uint32_t gcost[SCHED_MAX_GROUPS];

@@ -510,7 +510,9 @@ __device__ __forceinline__ int walk_ld(const int* p) { return __builtin_amdgcn_r
 __device__ __forceinline__ void walk_st(int* p, int v) { __atomic_store_n(p, v, __ATOMIC_RELAXED); }
 
 // Chosen prefixes -> ascending index lists of both lists of a head, by the workgroup that has walked them (half of its NT
-// threads a list).  bm: 2 * ceil(n / 32) words of LDS.  Up to EMIT_LINES lines: a launch of emit_kernel costs 4 to 5 us there.
+// threads a list).  bm: 2 * ceil(n / 32) words of LDS.  Up to EMIT_LINES lines; beyond, the 192 threads a list take longer than
+// emit_kernel's 1024 and its launch.  ls_select, 32 heads, launch / here, us: 1024 lines 24.9 / 22.1, 4096 28.9 / 27.8, 8192 38.0 /
+// 38.3, 12288 50.6 / 50.3, 16384 55.1 / 57.1, 32768 84.0 / 93.5; with exact overlaps 1024 86.2 / 84.8, 8192 93.4 / 93.2.
 constexpr int64_t EMIT_LINES = 8192;
 template <int NT>
 __device__ __forceinline__ void emit_both(const SelectArgs& a, int bh, int cnt_s, int cnt_v, uint32_t* bm) {
