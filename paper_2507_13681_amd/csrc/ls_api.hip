@@ -81,7 +81,9 @@ hipError_t init_device_once(int device) {
     static std::mutex mu;
     static std::vector<char> done;
     std::lock_guard<std::mutex> lock(mu);
-    if ((int)done.size() <= device) { done.resize(device + 1, 0); scratch_on.resize(device + 1, nullptr); }
+    try {                                    // (no exception may leave through the C entry points)
+        if ((int)done.size() <= device) { scratch_on.resize(device + 1, nullptr); done.resize(device + 1, 0); }
+    } catch (...) { return hipErrorOutOfMemory; }
     if (done[device]) return hipSuccess;
     hipError_t e;
     unsigned char* sp = nullptr;
@@ -453,12 +455,14 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
     a.words = words; a.tab_len = tab_len; a.scale_log2e = scale_log2e(s);
     a.obits = obits; a.tab = tab; a.v_idx = v_idx; a.cap_v = cap_v;
     std::array<hipEvent_t, 4> ev{};
-    if (c->profile)
+    if (c->profile) {
+        try { c->events.reserve(c->events.size() + 1); } catch (...) { return fail(c, LS_EHIP, "ls_sparse_prefill: out of memory for events"); }
         for (size_t i = 0; i < (w.slots > 0 ? 4u : 2u); ++i)
             if (hipEventCreate(&ev[i]) != hipSuccess) {
                 for (size_t j = 0; j < i; ++j) (void)hipEventDestroy(ev[j]);
                 return fail(c, LS_EHIP, "ls_sparse_prefill: hipEventCreate failed");
             }
+    }
     e = ls::launch_prefill(a, s->dtype, s->d, static_cast<hipStream_t>(stream), c->profile ? ev.data() : nullptr);
     if (c->profile) c->events.push_back(ev);
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill: %s", hipGetErrorString(e));
@@ -648,7 +652,8 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
     if (carve_prefill(c, s, w)) return w.code;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t items = (size_t)s->B * s->Hq * w.nqb;
-    std::vector<uint4> q(items + w.slots);
+    std::vector<uint4> q;
+    try { q.resize(items + w.slots); } catch (...) { return fail(c, LS_EHIP, "ls_debug_copy_prefill_queues: out of memory"); }
     int32_t len[8], base[8];
     if (hipSetDevice(c->device) != hipSuccess) return LS_EHIP;
     if (hipMemcpyAsync(q.data(), w.queue, q.size() * sizeof(uint4), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;

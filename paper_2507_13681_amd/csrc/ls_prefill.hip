@@ -252,7 +252,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // SPLIT_WGS is the resident workgroups of d = 128 for all types and dimensions.  Attention with 256 / 512 / 768, us: first turn of
 // 8192 rows 211 / 230 / 230 (d 64: 131 / 147 / 148), 10923 rows of 32768 1596 / 1543 / 1529, 5000 of 16384 at d 64 342 / 350 / 350, 1777
 // of 5003 at d 64 108 / 112 / 113, fp32 1024 of 4096 64 / 64 / 64: fewer, longer parts suit short contexts, more the long ones.
-// SPLIT_ITEMS is what a copy of all costs in LDS holds.  With 8192 instead, 131072 keys (4128 items) 12145 -> 12101 us, first turn of
+// SPLIT_ITEMS is what a copy of all costs in LDS holds.  With 8192 instead: 24000 of 32768 rows (6016 items) 2993 -> 2961 us, first turn of
 // 20000 rows (5024 items) 1114 -> 1096, B 2, 64 heads, 7000 of 16384 rows (7040 items) 1687 -> 1696: so many items balance by themselves.
 // ---------------------------------------------------------------------------------------------
 constexpr int SCHED_MAX_GROUPS = 2048;

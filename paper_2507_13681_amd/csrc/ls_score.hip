@@ -26,7 +26,7 @@
 // 4 cycles each, about 130 and 180 instructions per wave and chunk in stats and lines): what counts is few of
 // them (no masks where every row sees every key, no address arithmetic in the diagonal sums), and little enough
 // LDS (33 to 38 KB) for four workgroups per CU.  Whole windows of 64 rows in LDS (100 KB, one workgroup per CU),
-// as one step: 131072 keys 234 + 832 us, now 196 + 303; retention score, 16384 keys, B 4: 79 + 102 us, now 38 + 42.
+// as one step: 131072 keys 234 + 832 us, now 202 + 310; retention score, 16384 keys, B 4: 79 + 102 us, now 38 + 43.
 #include <type_traits>
 
 #include "ls_device.h"

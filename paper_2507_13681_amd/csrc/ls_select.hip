@@ -62,7 +62,7 @@ __device__ __forceinline__ uint32_t lanes_upto(uint32_t x) {
 // What bounds it: vector instructions (the ballots of the ranks) where a wave has eight chunks to scatter, the five
 // barriers and the round trips between them where it has one or two.  So a pass reads the sixteen waves' counts of a
 // digit at once, scans the digits by lane shifts, and clears the other pass's counters on the side; slots past the end
-// of the list take no part.  32 lists of 32768 lines 31 -> 28 us, of 12347 24 -> 17, four of 1024 13 -> 8.
+// of the list take no part.  64 lists of 32768 lines 31 -> 27 us, of 12347 24 -> 15, eight of 1024 13 -> 7.
 template <int SEG>
 __global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
     constexpr int SLICE = SEG / SORT_WAVES;
@@ -362,7 +362,8 @@ __device__ __forceinline__ int first_entry(int fe) {
     return E * l + __builtin_amdgcn_readlane(fe, l);
 }
 // entry i of the wave's 64 E (i uniform).  The lane's registers are read first and the choice is among scalars: a choice among
-// the registers becomes an array in scratch memory, E stores and a load in the chain of every run.
+// the registers becomes an array in scratch memory, E stores and a load in the chain of every run.  (walk_exact_kernel, which
+// waits for that chain, 54.7 -> 49.7 us at 8192 lines; walk_kernel, whose other waves go on meanwhile, 13.2 us both at 12347.)
 template <int E>
 __device__ __forceinline__ float pick_entry(const float (&v)[E], int i) {
     const int l = i / E;
@@ -961,8 +962,8 @@ static_assert(2 * sizeof(WalkList) > EMIT_LINES / 4, "the bitmaps lie ahead of t
 //   - the first candidate that fails the test, and the gains before it added in order by one wave.
 // What bounds it is the latency of a round, 4 to 6 us (dependent loads, five barriers, one wave's chain), so the
 // head with most runs.  Taken pick by pick it was 0.37 us a pick: 8192 lines, 32 heads, up to 3074 picks or 14
-// runs a head, 1160 us; now 66.  All candidates brought up to date after every run, with bitmaps of the lines
-// taken since: 72 to 75 us.
+// runs a head, 1160 us; then 66, and with no registers in scratch memory (pick_entry) a tenth less: 54.7 -> 49.7 on another
+// input of that size.  All candidates brought up to date after every run, with bitmaps of the lines taken since: 72 to 75 us.
 
 // Sum of a double over the 64 lanes, the same value in every lane.  Data-parallel-primitive moves on the two
 // halves of the value instead of cross-lane reads through LDS: a shuffle of a double is two LDS round trips, six
@@ -1509,7 +1510,7 @@ __global__ __launch_bounds__(TB_THREADS) void topb_write_kernel(TopbArgs a) {
 // One workgroup per KV head, up to 1024 PER entries, does all steps with the keys in registers, a wave holding
 // consecutive entries.  The threshold is narrowed by two bits a step, the counts of the four quarters in the bytes of a
 // register (a histogram in LDS of a head's scores, which crowd into few digits, took 16 us), until the few keys left are
-// ranked directly or wanted as a whole.  The launches above cost 4.5 us each: 32 heads of 16384 entries 29 us, now 16.
+// ranked directly or wanted as a whole.  The launches above cost 4.5 us each: 32 heads of 16384 entries 29 us, now 17.
 // Beyond 16 keys a thread (TB_FEW_LEN) one workgroup takes longer than the launches spread over the chip, unless there are
 // heads enough to fill it: the whole of ls_kv_compress (d 64, 8 rows), spread / one workgroup a head, us: 16384 entries 33.8 / 29.1
 // (8 heads), 57.2 / 52.2 (32); 17000 entries 35.1 / 38.4 (8), 51.7 / 56.0 (24), 62.3 / 61.4 (32), 95.0 / 86.0 (64); 32768 entries
@@ -1604,7 +1605,7 @@ __global__ __launch_bounds__(TB_THREADS) void topb_one_kernel(TopbArgs a) {
 }
 
 // gather kept rows of up to two tensors: dst [BK][budget][row_bytes] <- src [BK][len][row_bytes]; grid (slot blocks, BK, tensors).
-// 16 bytes a thread and row, four rows in flight: bound by HBM, 67 MB moved in 11 us (a row per 64-thread workgroup, a launch a
+// 16 bytes a thread and row, four rows in flight: bound by HBM, 67 MB moved in 12 us (a row per 64-thread workgroup, a launch a
 // tensor: 33 us).
 constexpr int GATHER_THREADS = 256, GATHER_ROWS = 4;
 struct GatherArgs { const unsigned char* src[2]; unsigned char* dst[2]; };
