@@ -1,7 +1,8 @@
-"""Thin ctypes binding of libloopserve (see include/loopserve.h, include/loopserve_test_hooks.h).
+"""Thin binding of libloopserve (see include/loopserve.h, include/loopserve_test_hooks.h).
 
-Argument marshalling only: every step of the path runs in the HIP kernels of the library.
-PyTorch supplies device memory and the current stream.  The library must have been built
+Argument marshalling only (natively, by csrc/ls_py.c, for the calls of a serving loop; through ctypes for
+the rest): every step of the path runs in the HIP kernels of the library.  PyTorch supplies device memory and
+the current stream.  The library must have been built
 (`python -m paper_2507_13681_amd.build` or `__graft_entry__.build()`); loading fails loudly
 otherwise -- there is no CPU fallback.
 """

@@ -22,8 +22,8 @@
 // and meets every query head of the KV group and every 32-row group with them.  Those chunks of 32 query rows
 // come through LDS by global -> LDS transfers, two buffers, one barrier per chunk.  K rows go through LDS on
 // their way to the registers as well: read straight from global memory a fragment load touches 32 rows with
-// 32 bytes each.  What bounds the passes is vector instruction issue (two thirds of all cycles at 131072 keys,
-// 4 cycles each, about 130 and 180 instructions per wave and chunk in stats and lines): what counts is few of
+// 32 bytes each.  What bounds the passes is vector instruction issue (71 and 52 % of all SIMD cycles in stats and
+// lines at 131072 keys, 4 cycles each, about 130 and 200 instructions per wave and chunk): what counts is few of
 // them (no masks where every row sees every key, no address arithmetic in the diagonal sums), and little enough
 // LDS (33 to 38 KB) for four workgroups per CU.  Whole windows of 64 rows in LDS (100 KB, one workgroup per CU),
 // as one step: 131072 keys 234 + 832 us, now 202 + 310; retention score, 16384 keys, B 4: 79 + 102 us, now 38 + 43.
