@@ -58,8 +58,8 @@ def _barriers_with_a_transfer_in_flight(lines):
     return len(bad)
 
 
-def test_checker_sees_a_missing_wait():
-    """The checker itself: a transfer on one of two paths, with and without a wait behind it."""
+def test_path_search_sees_a_missing_wait():
+    """The search itself: a transfer on one of two paths, with and without a wait behind it."""
     code = ["s_cbranch_scc1 .L1", "global_load_lds_dwordx4 v[0:1], off", ".L1:", "s_waitcnt lgkmcnt(0)", "s_barrier", "s_endpgm"]
     assert _barriers_with_a_transfer_in_flight(code) == 1
     assert _barriers_with_a_transfer_in_flight(code[:3] + ["s_waitcnt vmcnt(0)"] + code[3:]) == 0
