@@ -36,6 +36,9 @@ namespace ls {
 constexpr int BM = 128;   // query rows per workgroup
 constexpr int BN = 64;    // keys per tile
 constexpr int PREFILL_THREADS = 256;
+// A half's probabilities (relative to the running reference) may sum to this in a lane before the reference moves: bf16 and fp32
+// are as exact up there as around one, and the 2^18 keys of a row stay far from the end of either's range.
+constexpr float SOFT_LIMIT = 65536.f;
 
 // ---------------------------------------------------------------------------------------------
 // plan: per (batch, head) bitmap of the selected diagonals, the per-j activity table, a head flag.
@@ -527,7 +530,6 @@ __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
     constexpr int DBLK = D / 32;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r32 = lane & 31, g = lane >> 5;
     const int units = a.split_count[1] * 4;
-    const float sc2 = a.scale_log2e;
     for (int u = blockIdx.x; u < units; u += gridDim.x) {
         const uint2 e = a.split[u >> 2];
         const int wv = u & 3, bh = e.x >> 16, qb = e.x & 0xFFFF, parts = e.y & 0xFFFF, slot0 = e.y >> 16;
@@ -551,14 +553,14 @@ __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
                 for (int k = 0; k < DBLK; ++k) x[e][k] = *reinterpret_cast<const f32x4*>(o + (int64_t)p * (BM * D) + (w + 4 * k) * 256);
             }
             const float m_new = fmaxf(fmaxf(fmaxf(m, t[0].x), fmaxf(t[1].x, t[2].x)), t[3].x);
-            const float corr = m > -INFINITY ? fast_exp2((m - m_new) * sc2) : 0.f;
+            const float corr = m > -INFINITY ? fast_exp2(m - m_new) : 0.f;
             m = m_new;
             l *= corr;
 #pragma unroll
             for (int k = 0; k < DBLK; ++k) acc[k] *= corr;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const float wgt = t[e].x > -INFINITY ? fast_exp2((t[e].x - m) * sc2) : 0.f;
+                const float wgt = t[e].x > -INFINITY ? fast_exp2(t[e].x - m) : 0.f;
                 l += t[e].y * wgt;
 #pragma unroll
                 for (int k = 0; k < DBLK; ++k) acc[k] += x[e][k] * wgt;
@@ -572,7 +574,7 @@ __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
             store_out4(orow + d0, acc[k].x * inv, acc[k].y * inv, acc[k].z * inv, acc[k].w * inv);
         }
         if (a.lse && g == 0 && w == 0)
-            a.lse[(int64_t)bh * a.n_hat + (pos - row0)] = l > 0.f ? (m * sc2 + log2f(l)) * 0.69314718055994531f : -INFINITY;
+            a.lse[(int64_t)bh * a.n_hat + (pos - row0)] = l > 0.f ? (m + log2f(l)) * 0.69314718055994531f : -INFINITY;
     }
 }
 
@@ -605,16 +607,24 @@ __device__ __forceinline__ TileMask diag_mask(const DiagWords& w, int r32, int g
 }
 // 32 x 32 bit transpose inside each half of the wave: bit c of lane r <- bit r of lane c
 __device__ __forceinline__ uint32_t transpose32(uint32_t x, int lane) {
-#define LS_STEP(j, m, moved)                                                                          \
-    { const uint32_t p = (uint32_t)(moved); x = (lane & (j)) ? (((p >> (j)) & (m)) | (x & ~(m))) : ((x & (m)) | ((p & (m)) << (j))); }
-    LS_STEP(16, 0x0000FFFFu, __builtin_amdgcn_ds_swizzle((int)x, 0x401F))                              // lane ^ 16
-    LS_STEP(8, 0x00FF00FFu, __builtin_amdgcn_update_dpp(0, (int)x, 0x128 /* row_ror:8 */, 0xF, 0xF, false))
-    LS_STEP(4, 0x0F0F0F0Fu, __builtin_amdgcn_ds_swizzle((int)x, 0x101F))                               // lane ^ 4
-    LS_STEP(2, 0x33333333u, __builtin_amdgcn_update_dpp(0, (int)x, 0x4E /* quad_perm 2,3,0,1 */, 0xF, 0xF, false))
-    LS_STEP(1, 0x55555555u, __builtin_amdgcn_update_dpp(0, (int)x, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, false))
+    // (written without a choice between two expressions: the compiler made branches of those)
+#define LS_STEP(b, m, moved)                                                                          \
+    { const uint32_t p = (uint32_t)(moved), hi = (uint32_t)__builtin_amdgcn_sbfe(lane, b, 1), mk = (m) ^ ~hi;   \
+      const uint32_t y = ((p >> (1 << (b))) & hi) | ((p << (1 << (b))) & ~hi); x = (y & mk) | (x & ~mk); }
+    LS_STEP(4, 0x0000FFFFu, __builtin_amdgcn_ds_swizzle((int)x, 0x401F))                              // lane ^ 16
+    LS_STEP(3, 0x00FF00FFu, __builtin_amdgcn_update_dpp(0, (int)x, 0x128 /* row_ror:8 */, 0xF, 0xF, false))
+    LS_STEP(2, 0x0F0F0F0Fu, __builtin_amdgcn_ds_swizzle((int)x, 0x101F))                               // lane ^ 4
+    LS_STEP(1, 0x33333333u, __builtin_amdgcn_update_dpp(0, (int)x, 0x4E /* quad_perm 2,3,0,1 */, 0xF, 0xF, false))
+    LS_STEP(0, 0x55555555u, __builtin_amdgcn_update_dpp(0, (int)x, 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, false))
 #undef LS_STEP
     return x;
 }
+// The same in pieces: what a lane sees of a half whose words are hi and lo, and whether the half has an allowed cell (1) and nothing else (4)
+__device__ __forceinline__ uint32_t diag_cells(uint32_t hi, uint32_t lo, int r32, int g) {
+    const uint64_t w = (((uint64_t)hi << 32) | lo) >> 1;   // (uniform)
+    return __brev(__builtin_amdgcn_alignbit((uint32_t)(w >> 32), (uint32_t)w, (uint32_t)r32)) >> (4 * g);
+}
+__device__ __forceinline__ int diag_half(uint32_t hi, uint32_t lo) { return (((lo & ~1u) | hi) != 0u ? 1 : 0) | ((hi & (lo | 1u)) == 0xFFFFFFFFu ? 4 : 0); }
 // Packed columns: lane l answers for column `col` (slot l of the tile; -1: none) and all 32 rows of the wave at once,
 // 32 bits of the bitmap in two words, and one bit transpose hands the rows their columns.  (Each lane testing the
 // columns of its row one after the other was a chain of up to 64 LDS reads per tile.)  A cell whose diagonal is selected
@@ -894,7 +904,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     const float l_tot = l_run + xor32(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
     if (parts > 1) {
-        store_part<C::DBLK>(a, (int)(info >> 16) + part, wv, lane, oacc, m_run, l_tot);
+        store_part<C::DBLK>(a, (int)(info >> 16) + part, wv, lane, oacc, m_run * sc2, l_tot);
     } else if (row_ok) {
         T* orow = reinterpret_cast<T*>(a.out) + ((int64_t)bh * a.n_hat + (pos - row0)) * D;
 #pragma unroll
@@ -941,7 +951,7 @@ struct DirectCfg {
     static constexpr int K_ISTR = D == 128 ? 1088 : 1024; // LDS bytes from one K transfer to the next
     static constexpr int V_ISTR = 1024;
     static constexpr int K_BYTES = NI * K_ISTR, V_BYTES = NI * V_ISTR, TILE_BYTES = K_BYTES + V_BYTES;
-    static constexpr int STEP = 4 * RPI * RB;             // global bytes between a wave's consecutive transfers
+    static constexpr int K_LAG = K_ISTR - RPI * RB;       // bytes by which the K rows in LDS move ahead of those in memory, per transfer
     static constexpr int KSTEPS = D / 16, DBLK = D / 32;
     static constexpr int KA = D == 128 ? 2 : 4;           // K fragment address registers
     // slot swizzles (XOR on the 16-byte slot index inside a row); both are unchanged by adding a
@@ -967,13 +977,13 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     const uint32_t colring_lds = tiles_lds + 2u * C::TILE_BYTES, colbits_lds = colring_lds + 1024u + (uint32_t)wv * 512u;
     const int r32 = lane & 31, g = lane >> 5;
 
-    // ---- per-lane constants of the transfers: this lane fills slot sl of row rowlane (+ 4*RPI per
-    // further instruction of the wave) and fetches the chunk the swizzle assigns to that slot
-    const int rowlane = C::RPI * wv + lane / C::DS;
+    // ---- per-lane constants of the transfers: this lane fills slot sl of row rowlane (+ RPI per further instruction of
+    // the wave) and fetches the chunk the swizzle assigns to that slot
+    const int rowlane = 16 * wv + lane / C::DS;
     const int sl = lane % C::DS;
-    const uint32_t kcpart = 16u * (uint32_t)(sl ^ C::kswz(rowlane));
-    const uint32_t vcpart = 16u * (uint32_t)(sl ^ C::vswz(rowlane));
-    const uint32_t kvoff0 = (uint32_t)rowlane * C::RB + kcpart, vvoff0 = (uint32_t)rowlane * C::RB + vcpart;
+    const uint32_t kcpart0 = 16u * (uint32_t)(sl ^ C::kswz(rowlane)), vcpart = 16u * (uint32_t)(sl ^ C::vswz(rowlane));
+    // (of the wave's instruction i: the swizzle of d = 64 has a bit of the row's multiple of eight)
+    auto kcpart = [&](int i) -> uint32_t { return D == 128 ? kcpart0 : kcpart0 ^ (uint32_t)(64 * (i & 1)); };
     // ---- K fragment reads: row r32 (+32), chunk 2c+g sits in slot (2c+g) ^ kswz
     int kaddr[C::KA];
     {
@@ -1060,161 +1070,265 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     for (int i = 0; i < C::DBLK; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;                  // m_run in raw logit units
+    // mneg: the softmax reference of this lane's row in base 2, negated (+inf: no cell seen yet).  It moves only when a probability
+    // might exceed SOFT_LIMIT, so that most tiles need no rescaling of the accumulators (nor is a larger one less precise).
     const float sc2 = a.scale_log2e;
-    // The running reference m_run follows the row maximum lazily: it moves only when a tile exceeds it
-    // by more than 2^8 in the exponent, so probabilities stay below 256 (exact in fp32 and bf16 alike)
-    // and most tiles need no rescaling of the accumulators.
-    const float lazy = 8.0f / sc2;
+    float mneg = INFINITY, l_run = 0.f;
 
-    // ---- staging.  Wave wv issues transfer instructions wv, wv+4, ... of each operand; instruction q
-    // carries tile rows RPI*q .. RPI*q+RPI-1.  A row beyond the context re-loads the last row, a missing
+    // ---- staging.  Wave wv fetches rows 16 wv .. 16 wv + 15 of each operand, IPW instructions of RPI rows, which share one M0:
+    // an instruction's offset moves its source and its target alike, and where the target moves further (K_LAG) the
+    // per-lane offsets take that back.  A row beyond the context re-loads the last row, a missing
     // column re-loads row 0: every slot is always written with finite data and needs no exec masking.
-    // (Measured: spreading the transfers over the products of the previous tile instead of issuing
-    // them together is slower; a transfer stalls the wave that issues it for as long as the vector
-    // memory pipeline is busy, which then also stalls its matrix pipeline.)
-    const uint32_t kdst0 = tiles_lds + (uint32_t)(wv * C::K_ISTR), vdst0 = tiles_lds + (uint32_t)(C::K_BYTES + wv * C::V_ISTR);
-    auto issue_block = [&](int kb, int t) {                // key block kb -> LDS buffer t & 1
-        const uint32_t bo = (uint32_t)((t & 1) * C::TILE_BYTES);
+    const uint32_t kdst0 = tiles_lds + (uint32_t)(wv * C::IPW * C::K_ISTR), vdst0 = tiles_lds + (uint32_t)(C::K_BYTES + wv * C::IPW * C::V_ISTR);
+    auto issue_k = [&](int kb, int t) {                    // K of key block kb -> LDS buffer t & 1
+        const uint32_t dst = kdst0 + (uint32_t)((t & 1) * C::TILE_BYTES);
         const int64_t key0 = (int64_t)kb * BN;
         const unsigned char* kb_ = Kg + key0 * C::RB;
-        const unsigned char* vb_ = Vg + key0 * C::RB;
         if (key0 + BN <= n) {
+            uint32_t off[C::IPW];
 #pragma unroll
-            for (int i = 0; i < C::IPW; ++i) dma16(kb_ + i * C::STEP, kvoff0, kdst0 + bo + (uint32_t)(4 * i * C::K_ISTR));
-#pragma unroll
-            for (int i = 0; i < C::IPW; ++i) dma16(vb_ + i * C::STEP, vvoff0, vdst0 + bo + (uint32_t)(4 * i * C::V_ISTR));
-        } else {                                           // last key block of the context: clamp the rows
+            for (int i = 0; i < C::IPW; ++i) off[i] = (uint32_t)rowlane * C::RB + kcpart(i) + (uint32_t)((C::IPW - 1 - i) * C::K_LAG);
+            dma16_rows<C::IPW, C::K_ISTR>(kb_ - (C::IPW - 1) * C::K_LAG, off, dst);
+        }
+        else {                                             // last key block of the context: clamp the rows
             const int last = (int)(n - 1 - key0);
 #pragma unroll
             for (int i = 0; i < C::IPW; ++i) {
-                const int row = rowlane + 4 * C::RPI * i;
-                const uint32_t ro = (uint32_t)(row <= last ? row : last) * C::RB;
-                dma16(kb_, ro + kcpart, kdst0 + bo + (uint32_t)(4 * i * C::K_ISTR));
-                dma16(vb_, ro + vcpart, vdst0 + bo + (uint32_t)(4 * i * C::V_ISTR));
+                const int row = rowlane + C::RPI * i;
+                dma16(kb_, (uint32_t)(row <= last ? row : last) * C::RB + kcpart(i), dst + (uint32_t)(i * C::K_ISTR));
+            }
+        }
+    };
+    auto issue_v = [&](int kb, int t) {
+        const uint32_t dst = vdst0 + (uint32_t)((t & 1) * C::TILE_BYTES);
+        const int64_t key0 = (int64_t)kb * BN;
+        const unsigned char* vb_ = Vg + key0 * C::RB;
+        if (key0 + BN <= n) {
+            uint32_t off[C::IPW];
+#pragma unroll
+            for (int i = 0; i < C::IPW; ++i) off[i] = (uint32_t)rowlane * C::RB + vcpart;
+            dma16_rows<C::IPW, C::V_ISTR>(vb_, off, dst);
+        } else {
+            const int last = (int)(n - 1 - key0);
+#pragma unroll
+            for (int i = 0; i < C::IPW; ++i) {
+                const int row = rowlane + C::RPI * i;
+                dma16(vb_, (uint32_t)(row <= last ? row : last) * C::RB + vcpart, dst + (uint32_t)(i * C::V_ISTR));
             }
         }
     };
     auto issue_cols = [&](int t) {                         // the columns of packed tile t -> LDS buffer t & 1
         const uint32_t bo = (uint32_t)((t & 1) * C::TILE_BYTES);
         const int32_t* cols = colring + (t & 3) * BN;
+        uint32_t ro[C::IPW];
 #pragma unroll
-        for (int i = 0; i < C::IPW; ++i) {
-            const uint32_t ro = (uint32_t)cols[rowlane + 4 * C::RPI * i] * C::RB;
-            dma16(Kg, ro + kcpart, kdst0 + bo + (uint32_t)(4 * i * C::K_ISTR));
-            dma16(Vg, ro + vcpart, vdst0 + bo + (uint32_t)(4 * i * C::V_ISTR));
-        }
+        for (int i = 0; i < C::IPW; ++i) ro[i] = (uint32_t)cols[rowlane + C::RPI * i] * C::RB;
+#pragma unroll
+        for (int i = 0; i < C::IPW; ++i) dma16(Kg, ro[i] + kcpart(i), kdst0 + bo + (uint32_t)(i * C::K_ISTR));
+#pragma unroll
+        for (int i = 0; i < C::IPW; ++i) dma16(Vg, ro[i] + vcpart, vdst0 + bo + (uint32_t)(i * C::V_ISTR));
     };
 
-    // One tile: S^T = K Q^T, online softmax, O^T += V^T P^T.  The products run in a pinned order
-    // (a scheduling barrier after each) with the LDS fragment reads a fixed number of products ahead.
-    auto process = [&](int tileoff, const TileMask& tm) {
-        const unsigned char* tile = tiles + tileoff;
-        f32x16 s[2];
-        if (!tm.act[0] && !tm.act[1]) return;              // none of this wave's rows has an allowed cell here
-        const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        constexpr int SUB = (32 / C::RPI) * C::K_ISTR;     // LDS bytes from key r to key r + 32
-        if (tm.act[0] && tm.act[1]) {
-            // 2 * KSTEPS products in a fixed order; K fragments are read RING_S products ahead of their use
-            constexpr int NP = 2 * C::KSTEPS, R = LS_RING_S;
-            Frag<T> kf[NP];
-            auto kload = [&](int i) {
-                const int c = i >> 1;
-                load_frag(kf[i], tile + kaddr[c & (C::KA - 1)] + (i & 1) * SUB + 32 * (c & ~(C::KA - 1)));
-            };
-#pragma unroll
-            for (int i = 0; i < R; ++i) kload(i);
-            __builtin_amdgcn_sched_barrier(0);
-            s[0] = zero16; s[1] = zero16;
-#pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                mma(s[i & 1], kf[i], qf[i >> 1]);          // s[r] = <k_{8(r/4)+4g+r%4}, q_row>
-                if (i + R < NP) kload(i + R);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-            // one 32-key half: KSTEPS products on one accumulator, same ring
-            auto half = [&](auto subc) {
-                constexpr int sub = decltype(subc)::value;
-                constexpr int R = LS_RING_S < C::KSTEPS ? LS_RING_S : C::KSTEPS;
-                Frag<T> kf[C::KSTEPS];
-                auto kload = [&](int c) { load_frag(kf[c], tile + kaddr[c & (C::KA - 1)] + sub * SUB + 32 * (c & ~(C::KA - 1))); };
-#pragma unroll
-                for (int c = 0; c < R; ++c) kload(c);
-                __builtin_amdgcn_sched_barrier(0);
-                s[sub] = zero16;
-#pragma unroll
-                for (int c = 0; c < C::KSTEPS; ++c) {
-                    mma(s[sub], kf[c], qf[c]);
-                    if (c + R < C::KSTEPS) kload(c + R);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            };
-            if (tm.act[0]) half(std::integral_constant<int, 0>{}); else half(std::integral_constant<int, 1>{});
+    // ---- masks.  halves: of the tile at hand, 1, 2 = the half has an allowed cell (for this wave), 4, 8 = all of it is allowed.
+    // The bitmap words of contiguous tiles come out of a register: lane l keeps word wq - l, good for some 30 neighbouring
+    // tiles, and a tile's three words are three lane reads.  (Scalar loads ahead of the tile's transfers, waited for
+    // there, were 200 cycles a tile.)
+    const int rows_mask = rows_here ? 15 : 0;
+    uint32_t am[2] = {0u, 0u};
+    int halves = 0, kb_next = 0;                           // kb_next: key block of the tile after the one at hand (phase 1)
+    uint32_t wc = 0u;
+    int wq = -1000000;
+    auto keep_words = [&](int kb) {                        // with no transfer of this wave under way
+        const int q = (posw - kb * BN) >> 5;               // >= -2
+        if ((uint32_t)(wq - q) > 61u) {
+            const int at = q - lane + OB_PAD;              // (below the bitmap: zero words)
+            wc = obg[at < 0 ? 0 : at];
+            wq = q;
+            wait_transfers();
         }
-        float mx = -INFINITY;
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            if (tm.act[sub]) {
-                if (!tm.full[sub]) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) s[sub][r] = masked(s[sub][r], tm.am[sub], r);
-                }
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[sub][r]);
-            }
-        }
-        mx = max32(mx);
-        const float m_new = (mx > m_run + lazy) ? mx : m_run;            // -inf + lazy = -inf: the first finite tile always moves it
-        const float m_safe = (m_new == -INFINITY) ? 0.f : m_new;
-        const float corr = fast_exp2((m_run - m_safe) * sc2);
-        const float mneg = -m_safe * sc2;
-        m_run = m_new;
-        if (__ballot(corr != 1.0f) != 0ull) {
-            l_run *= corr;
-#pragma unroll
-            for (int i = 0; i < C::DBLK; ++i)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) oacc[i][r] *= corr;
-        }
-        auto vt_frag = [&](Frag<T>& vf, int q4, int i) {     // V^T fragment: keys 16*q4.., output block i
-            const unsigned char* va = tile + vaddr[i] + 16 * q4 * C::RB;
-            load_frag_tr(vf, va, va + 8 * C::RB);
+    };
+    uint32_t x0 = 0u, x1 = 0u, x2 = 0u;
+    auto mask_step = [&](int k) {                          // masks of contiguous tile kb_next, in four steps
+        if (k == 0) {
+            const int l = wq - ((posw - kb_next * BN) >> 5);
+            x2 = (uint32_t)__builtin_amdgcn_readlane((int)wc, l);
+            x1 = (uint32_t)__builtin_amdgcn_readlane((int)wc, l + 1);
+            x0 = (uint32_t)__builtin_amdgcn_readlane((int)wc, l + 2);
+        } else if (k == 1) am[0] = diag_cells(x2, x1, r32, g);
+        else if (k == 2) am[1] = diag_cells(x1, x0, r32, g);
+        else halves = (diag_half(x2, x1) | diag_half(x1, x0) << 1) & rows_mask;
+    };
+    // One tile: S^T = K Q^T, softmax, O^T += V^T P^T, by halves of 32 keys; halves without an allowed cell are passed by.  With
+    // two halves the vector work of one runs beside the products of the other: S(1) beside the softmax of 0, P V of 0 beside
+    // the softmax of 1.  Order is pinned (a scheduling barrier after each product), the LDS fragment reads run a fixed number
+    // of products ahead, and a product is followed by its share of the other half's 16 registers (a product takes its wave 33
+    // cycles, a masked register 27, an unmasked one 18).
+    // No maximum is looked for on the way: the exponentials are taken with the reference as it stands, and where a lane's
+    // sum says that one of them may exceed SOFT_LIMIT (or is no number, as with the first cells of a row: -mneg = -inf), the half is
+    // done again with a new reference.  s keeps the logits for that.
+    // Cycles of a workgroup over the 32768-key turn 3.52 -> 3.34 million; the clock falls with the better use of the matrix pipeline
+    // (2.29 -> 2.23 GHz, dense heads 2.05 -> 1.98: the card's power is what bounds them), so that 1723 us became 1665.  Going on to
+    // overlap P V, the products of the next tile and a softmax between them all had 1780: it works on halves that nobody sees.
+    constexpr int SUB = (32 / C::RPI) * C::K_ISTR;         // LDS bytes from key r to key r + 32
+    constexpr int NS = C::KSTEPS, NV = 2 * C::DBLK;        // products of a half
+    constexpr int ES = 16 / NS, EV = 16 / NV;              // registers of the other half's softmax per product
+    constexpr int RS = LS_RING_S < NS ? LS_RING_S : NS, RV = LS_RING_P < NV ? LS_RING_P : NV;
+    const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto apart = [](int x) { asm volatile("" : "+v"(x)); return __builtin_amdgcn_readfirstlane(x); };      // a condition that is not joined with others
+    struct Soft { uint32_t p[8]; float sum[2]; };          // packed probabilities and their sums
+    auto process = [&](int tileoff) {
+        f32x16 sa, sb;
+        Soft pa, pb;
+        auto kload = [&](Frag<T>& f, const unsigned char* base, int c) { load_frag(f, base + kaddr[c & (C::KA - 1)] + 32 * (c & ~(C::KA - 1))); };
+        auto vload = [&](Frag<T>& f, const unsigned char* base, int k) {     // keys 16 (k / DBLK).., output block k % DBLK
+            const unsigned char* va = base + vaddr[k % C::DBLK] + 16 * (k / C::DBLK) * C::RB;
+            load_frag_tr(f, va, va + 8 * C::RB);
         };
-        // P*V: per 32-key half, 2 * DBLK products in a fixed order (16-key chunk q4, output block i); V^T
-        // fragments are read RING_P products ahead
-        float ps4[4] = {0.f, 0.f, 0.f, 0.f};               // four short add chains instead of one long one
+        auto pack2 = [&](float lo, float hi) {
+            typedef __attribute__((ext_vector_type(2))) float f32x2;
+            typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+            uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));   // v_cvt_pk_bf16_f32, round to nearest even
+            asm volatile("" : "+v"(u));                    // here, and not where it is used
+            return u;
+        };
+        // registers r .. r + E - 1 of a half, in step k of 16 / E; x: their exponents, one step ahead
+        auto exponents = [&](auto MASKED, auto EC, float (&x)[4], f32x16& s, uint32_t am, int k) {
+            constexpr int E = decltype(EC)::value;
 #pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-            if (tm.act[sub]) {
-                constexpr int NPV = 2 * C::DBLK, R = LS_RING_P < NPV ? LS_RING_P : NPV;
+            for (int e = 0; e < E; ++e) {
+                const int r = E * k + e;
+                if constexpr (decltype(MASKED)::value) s[r] = masked(s[r], am, r);
+                x[e] = __builtin_fmaf(s[r], sc2, mneg);
+            }
+        };
+        auto soft_step = [&](auto MASKED, auto EC, float (&x)[4], f32x16& s, uint32_t am, Soft& o, int k) {
+            constexpr int E = decltype(EC)::value;
+            float p[E];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float p = fast_exp2(__builtin_fmaf(s[sub][r], sc2, mneg));
-                    s[sub][r] = p;
-                    ps4[r & 3] += p;
-                }
-                Frag<T> pf[2];
+            for (int e = 0; e < E; ++e) p[e] = fast_exp2(x[e]);
+            if (k + 1 < 16 / E) exponents(MASKED, EC, x, s, am, k + 1);
 #pragma unroll
-                for (int h2 = 0; h2 < 2; ++h2) {
-                    float pv[8];
+            for (int e = 0; e < E; ++e) { if (E * k + e < 2) o.sum[e] = p[e]; else o.sum[e & 1] += p[e]; }
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) pv[e] = s[sub][8 * h2 + e];
-                    pack_frag(pf[h2], pv);
-                }
-                Frag<T> vf[NPV];
+            for (int e = 0; e < E; e += 2) o.p[(E * k + e) / 2] = pack2(p[e], p[e + 1]);
+        };
+        auto settle = [&](f32x16& s, Soft& o) {            // the sums in, or the half once more with a new reference
+            float sum = o.sum[0] + o.sum[1];
+            if (__ballot(!(sum <= SOFT_LIMIT)) != 0ull) {
+                float mx = -INFINITY;
 #pragma unroll
-                for (int k = 0; k < R; ++k) vt_frag(vf[k], 2 * sub + k / C::DBLK, k % C::DBLK);
+                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
+                mx = max32(mx) * sc2;
+                const float m_new = fmaxf(mx, -mneg);      // in base 2
+                const float corr = m_new > -INFINITY ? fast_exp2(-mneg - m_new) : 1.f;
+                mneg = -m_new;
+                const float safe = m_new > -INFINITY ? mneg : 0.f;
+                l_run *= corr;
+#pragma unroll
+                for (int i = 0; i < C::DBLK; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) oacc[i][r] *= corr;
+                sum = 0.f;
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int k = 0; k < NPV; ++k) {
-                    mma(oacc[k % C::DBLK], vf[k], pf[k / C::DBLK]);
-                    if (k + R < NPV) vt_frag(vf[k + R], 2 * sub + (k + R) / C::DBLK, (k + R) % C::DBLK);
+                for (int r = 0; r < 16; r += 4) {
+                    float p[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { p[e] = fast_exp2(__builtin_fmaf(s[r + e], sc2, safe)); sum += p[e]; }
+                    o.p[r / 2] = pack2(p[0], p[1]);
+                    o.p[r / 2 + 1] = pack2(p[2], p[3]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
+            l_run += sum;
+        };
+        auto pfrag = [&](const Soft& o, int h) {
+            struct U { uint32_t w[4]; } u = {o.p[4 * h], o.p[4 * h + 1], o.p[4 * h + 2], o.p[4 * h + 3]};
+            Frag<T> f;
+            f.v = __builtin_bit_cast(bf16x8, u);
+            return f;
+        };
+        using std::integral_constant;
+        auto scores = [&](f32x16& x, const unsigned char* base) {              // S of a half
+            Frag<T> kf[NS];
+#pragma unroll
+            for (int c = 0; c < RS; ++c) kload(kf[c], base, c);
+            __builtin_amdgcn_sched_barrier(0);
+            x = zero16;
+#pragma unroll
+            for (int c = 0; c < NS; ++c) {
+                mma(x, kf[c], qf[c]);                      // x[r] = <k_{8(r/4)+4g+r%4}, q_row>
+                if (c + RS < NS) kload(kf[c + RS], base, c + RS);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        auto values = [&](const Soft& p, const unsigned char* base) {          // P V of a half, beside it the masks of the next tile
+            Frag<T> vf[NV];
+#pragma unroll
+            for (int k = 0; k < RV; ++k) vload(vf[k], base, k);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                mma(oacc[k % C::DBLK], vf[k], pfrag(p, k / C::DBLK));
+                if (k + RV < NV) vload(vf[k + RV], base, k + RV);
+                if (k < 4) mask_step(k);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        // (The accumulators change in straight code and under conditions without an else only: where both sides of a choice
+        // changed them, the compiler, which gives every choice the form of two guarded parts, kept them twice and moved them.)
+        const unsigned char* t0 = tiles + tileoff;
+        const int two = (halves & 3) == 3, h0 = (halves & 3) == 2;
+        const uint32_t am0 = h0 ? am[1] : am[0];
+        scores(sa, t0 + h0 * SUB);
+        if (two) {
+            auto first = [&](auto MASKED) {                // S of the second half beside the softmax of the first
+                Frag<T> kf[NS];
+                float x[4];
+#pragma unroll
+                for (int c = 0; c < RS; ++c) kload(kf[c], t0 + SUB, c);
+                __builtin_amdgcn_sched_barrier(0);
+                sb = zero16;
+#pragma unroll
+                for (int c = 0; c < NS; ++c) {
+                    mma(sb, kf[c], qf[c]);
+                    if (c + RS < NS) kload(kf[c + RS], t0 + SUB, c + RS);
+                    if (c == 0) exponents(MASKED, integral_constant<int, ES>{}, x, sa, am0, 0);
+                    else soft_step(MASKED, integral_constant<int, ES>{}, x, sa, am0, pa, c - 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                soft_step(MASKED, integral_constant<int, ES>{}, x, sa, am0, pa, NS - 1);
+            };
+            if (halves & 4) first(std::false_type{}); else first(std::true_type{});
+        } else {
+            float x[4];
+            exponents(std::true_type{}, integral_constant<int, 4>{}, x, sa, am0, 0);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) soft_step(std::true_type{}, integral_constant<int, 4>{}, x, sa, am0, pa, k);
         }
-        l_run += (ps4[0] + ps4[1]) + (ps4[2] + ps4[3]);
+        settle(sa, pa);
+        pb = pa;
+        if (apart(two)) {
+            auto second = [&](auto MASKED) {               // P V of the first half beside the softmax of the second
+                Frag<T> vf[NV];
+                float x[4];
+#pragma unroll
+                for (int k = 0; k < RV; ++k) vload(vf[k], t0, k);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int k = 0; k < NV; ++k) {
+                    mma(oacc[k % C::DBLK], vf[k], pfrag(pa, k / C::DBLK));
+                    if (k + RV < NV) vload(vf[k + RV], t0, k + RV);
+                    if (k == 0) exponents(MASKED, integral_constant<int, EV>{}, x, sb, am[1], 0);
+                    else soft_step(MASKED, integral_constant<int, EV>{}, x, sb, am[1], pb, k - 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                soft_step(MASKED, integral_constant<int, EV>{}, x, sb, am[1], pb, NV - 1);
+            };
+            second(std::true_type{});
+            settle(sb, pb);
+        }
+        values(pb, t0 + ((halves & 2) ? 32 * C::RB : 0));
     };
 
     // What a packed tile needs besides its rows goes through LDS by transfers of its own: the ids of its columns two
@@ -1229,30 +1343,22 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         }
     };
     auto block_at = [&](int t) -> int { return __builtin_amdgcn_readfirstlane((int)kbl[t]); };
-    // what the masks of tile t are made of
-    DiagWords dw = {0u, 0u, 0u};
     int32_t mycol = -1;
-    TileMask tm;
-    auto mask_words = [&](int t, int kb) {                 // ahead of the transfers of tile t
-        if (t < n1) dw = diag_words((const_words)obg, posw, kb * BN);
-        else {
-            mycol = (t - n1) * BN + lane < nv ? colring[(t & 3) * BN + lane] : -1;
-            if (n1 > 0) {
-                const uint32_t off = (uint32_t)((col_offset(posw, mycol < 0 ? 0 : mycol) >> 5) + OB_PAD) * 4u;
-                dma4(obg, off, colbits_lds);
-                dma4(obg, off + 4u, colbits_lds + 256u);
-            }
+    auto col_words_of = [&](int t) {                       // what the masks of packed tile t are made of, ahead of its transfers
+        const int32_t col = colring[(t & 3) * BN + lane];
+        mycol = (t - n1) * BN + lane < nv ? col : -1;
+        if (n1 > 0) {
+            const uint32_t off = (uint32_t)((col_offset(posw, mycol < 0 ? 0 : mycol) >> 5) + OB_PAD) * 4u;
+            dma4(obg, off, colbits_lds);
+            dma4(obg, off + 4u, colbits_lds + 256u);
         }
     };
     auto masks_cols = [&]() {                              // once the transfers have landed
         ColWords cw = {0u, 0u};
         if (n1 > 0) { cw.lo = colbits[wv * 128 + lane]; cw.hi = colbits[wv * 128 + 64 + lane]; }
-        tm = col_mask(cw, posw, mycol, lane);
-        if (!rows_here) tm.act[0] = tm.act[1] = false;
-    };
-    auto masks_block = [&]() {
-        tm = diag_mask(dw, r32, g);
-        if (!rows_here) tm.act[0] = tm.act[1] = false;
+        const TileMask tm = col_mask(cw, posw, mycol, lane);
+        am[0] = tm.am[0]; am[1] = tm.am[1];
+        halves = ((tm.act[0] ? 1 : 0) | (tm.act[1] ? 2 : 0)) & rows_mask;
     };
 
     if (ntiles > n1 && tbeg < ntiles && tbeg + 1 >= n1) {  // a packed tile among the first two
@@ -1261,37 +1367,46 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         wait_transfers();
     }
     __syncthreads();                                       // kbl and the first column ids are visible
-    int kb_next = 0;                                       // key block of tile t + 1 (phase 1)
-    if (tbeg < ntiles) {
-        kb_next = tbeg < n1 ? block_at(tbeg) : 0;
-        mask_words(tbeg, kb_next);
-        if (tbeg < n1) issue_block(kb_next, tbeg); else issue_cols(tbeg);
-        kb_next = tbeg + 1 < n1 ? block_at(tbeg + 1) : 0;
+    if (tbeg < n1) {
+        kb_next = block_at(tbeg);
+        keep_words(kb_next);
+        issue_k(kb_next, tbeg); issue_v(kb_next, tbeg);
+        for (int k = 0; k < 4; ++k) mask_step(k);
+        wait_transfers();
+    } else if (tbeg < ntiles) {
+        col_words_of(tbeg);
+        issue_cols(tbeg);
+        wait_transfers();
+        masks_cols();
     }
-    wait_transfers();
-    if (tbeg < ntiles) { if (tbeg < n1) masks_block(); else masks_cols(); }
+    kb_next = tbeg + 1 < n1 ? block_at(tbeg + 1) : 0;
     __syncthreads();
 
     for (int t = tbeg; t < ntiles; ++t) {
+        const bool next = t + 1 < ntiles;
+        if (next && t + 1 < n1) keep_words(kb_next);
         if (t + 2 >= n1 && t + 2 < ntiles) request_cols(t + 2);
-        if (t + 1 < ntiles) {
-            mask_words(t + 1, kb_next);
-            if (t + 1 < n1) issue_block(kb_next, t + 1); else issue_cols(t + 1);
-        }
+        if (next && t + 1 >= n1) { col_words_of(t + 1); issue_cols(t + 1); }
+        if (next && t + 1 < n1) { issue_k(kb_next, t + 1); issue_v(kb_next, t + 1); }
         const int kb_after = t + 2 < n1 ? (int)kbl[t + 2] : 0;
-        process((t & 1) * C::TILE_BYTES, tm);
+        const int active = halves & 3;
+        if (active) process((t & 1) * C::TILE_BYTES);  // some of this wave's rows have an allowed cell here
+        if (apart(active) == 0) for (int k = 0; k < 4; ++k) mask_step(k);
         kb_next = __builtin_amdgcn_readfirstlane(kb_after);
-        if (t + 1 < n1) masks_block();
         wait_transfers();                                  // this wave's transfers of tile t+1 have landed
-        if (t + 1 >= n1 && t + 1 < ntiles) masks_cols();
+        if (next && t + 1 >= n1) masks_cols();
         __syncthreads();
     }
 
     if (wv == 0) src.ahead(a, lane);                       // the next entry's place in the queue, under the stores below
     const float l_tot = l_run + xor32(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    // (the lane once more: addresses made of it are not to be kept in registers, or spilled, from one entry to the next)
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int rl = ln & 31, gl = ln >> 5;
     if (parts > 1) {
-        store_part<C::DBLK>(a, (int)(info >> 16) + part, wv, lane, oacc, m_run, l_tot);
+        store_part<C::DBLK>(a, (int)(info >> 16) + part, wv, ln, oacc, -mneg, l_tot);
     } else if (rows_here) {
         // A lane holds four neighbouring values of its row at a time; through LDS (32 rows of this wave in the tile
         // buffers, which nobody reads any more) they become whole rows, 1 KB a store.  (Stored as they are, 8 bytes a
@@ -1302,20 +1417,20 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         for (int i = 0; i < C::DBLK; ++i)
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq)
-                store_out4(reinterpret_cast<T*>(ow + r32 * OS) + 32 * i + 8 * rq + 4 * g, oacc[i][4 * rq] * inv, oacc[i][4 * rq + 1] * inv,
+                store_out4(reinterpret_cast<T*>(ow + rl * OS) + 32 * i + 8 * rq + 4 * gl, oacc[i][4 * rq] * inv, oacc[i][4 * rq + 1] * inv,
                            oacc[i][4 * rq + 2] * inv, oacc[i][4 * rq + 3] * inv);
         __builtin_amdgcn_wave_barrier();
         unsigned char* og = reinterpret_cast<unsigned char*>(a.out) + ((int64_t)bh * a.n_hat + (posw - row0)) * C::RB;   // row posw may lie before the turn
-        const int cr = lane / C::DS, cs = lane % C::DS;
+        const int cr = ln / C::DS, cs = ln % C::DS;
 #pragma unroll
         for (int j = 0; j < 32 / C::RPI; ++j) {
             const int r = C::RPI * j + cr;
             const f32x4 v = *reinterpret_cast<const f32x4*>(ow + r * OS + 16 * cs);
             if (posw + r >= row0 && posw + r < n) *reinterpret_cast<f32x4*>(og + (int64_t)r * C::RB + 16 * cs) = v;
         }
-        if (a.lse && row_ok && g == 0)
-            a.lse[(int64_t)bh * a.n_hat + (pos - row0)] =
-                l_tot > 0.f ? (m_run * sc2 + log2f(l_tot)) * 0.69314718055994531f : -INFINITY;
+        if (a.lse && gl == 0 && posw + rl >= row0 && posw + rl < n)
+            a.lse[(int64_t)bh * a.n_hat + (posw + rl - row0)] =
+                l_tot > 0.f ? (log2f(l_tot) - mneg) * 0.69314718055994531f : -INFINITY;
     }
   }                                                        // next item
 }
