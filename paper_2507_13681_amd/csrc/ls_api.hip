@@ -166,9 +166,11 @@ size_t ws_prefill(const ls_shape* s) {
     const size_t BH = (size_t)s->B * s->Hq;
     const int64_t n_hat = s->n_hat > 0 && s->n_hat <= s->n ? s->n_hat : s->n;
     const size_t items = BH * (size_t)row_blocks(s->n, n_hat);   // (head, row block) work items
-    const size_t slots = (size_t)ls::prefill_split_slots((int64_t)items);
+    const bool pieces = ls::prefill_in_pieces((int)BH, s->n, (int)row_blocks(s->n, n_hat));
+    const int grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, pieces);
+    const size_t slots = (size_t)ls::prefill_split_slots((int64_t)items, grid, pieces);
     return up(BH * (size_t)(words_of(s->n) + 4) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(items * 4) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
-           up((items + slots) * 16) + up(26 * 4) + up(slots * 8) + up(slots * ls::prefill_slot_bytes(s->d)) + ALIGN;
+           up(26 * 4) + up((items + slots) * 16) + up(pieces ? ((size_t)grid + 1) * 8 : slots * 8) + up(slots * ls::prefill_slot_bytes(s->d)) + ALIGN;
 }
 size_t ws_compress(const ls_shape* s) {
     return ws_score(s, false) + up((size_t)s->B * s->Hkv * (size_t)s->n * 4) +
@@ -367,38 +369,43 @@ namespace {
 // Where ls_sparse_prefill keeps its per-call state in the workspace (one place, so that the test hook that
 // reads the work queues back finds them where the call put them).
 struct PrefillCarve {
-    uint32_t* obits; uint32_t* ncol; uint32_t* cost; uint16_t* pref; uint4* queue; int32_t* qlen; int32_t* qhead; int32_t* qbase; uint8_t* tab;
-    uint2* split; int32_t* split_count; float* part_o; float* part_ml;
-    int nqb, slots; int64_t pos0; int code;
+    uint32_t* obits; uint32_t* upto; uint32_t* head_work; uint16_t* elist; uint8_t* tab; int32_t* misc;
+    uint32_t* rec; uint4* queue; uint2* split; int2* cuts; float* part_o; float* part_ml;
+    bool pieces;
+    int nqb, grid, slots; int64_t pos0; int code;
 };
 const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     const int BH = s->B * s->Hq;
     const int words = words_of(s->n), tab_len = tab_len_of(s->n);
     Bump bp{c->ws, c->ws_bytes, 0};
     w.obits = bp.take<uint32_t>((size_t)BH * (words + 4));
-    w.cost = bp.take<uint32_t>((size_t)BH);
-    w.pref = bp.take<uint16_t>((size_t)BH * (tab_len + 1));
+    w.head_work = bp.take<uint32_t>((size_t)BH);
+    w.elist = bp.take<uint16_t>((size_t)BH * (tab_len + 1));
     const int bm = ls::prefill_block_rows();
     w.pos0 = (s->n - s->n_hat) / bm * bm;
     w.nqb = (int)row_blocks(s->n, s->n_hat);
     w.code = LS_ESHAPE;
     if (w.nqb > 65535) return "too many row blocks";
     if (BH > 8192) return "B * Hq exceeds 8192";
-    w.ncol = bp.take<uint32_t>((size_t)BH * w.nqb);
-    w.qlen = bp.take<int32_t>(8 + 8 + 8 + 2);
-    w.qhead = w.qlen + 8; w.qbase = w.qlen + 16; w.split_count = w.qlen + 24;
+    const size_t items = (size_t)BH * w.nqb;
+    uint32_t* per_item = bp.take<uint32_t>(items);         // pieces: `upto`, the records lie where the queues would; queues: the records
     w.tab = bp.take<uint8_t>((size_t)BH * tab_len);
+    w.misc = bp.take<int32_t>(26);                         // of the queues: lengths, heads, first entries, slots in use and split items
     // long items are split as far as the workspace has room for their parts' results (sized for it by
     // ls_workspace_bytes; a smaller workspace that holds the rest still works)
-    const size_t items = (size_t)BH * w.nqb;
-    w.slots = ls::prefill_split_slots((int64_t)items);
+    w.pieces = ls::prefill_in_pieces(BH, s->n, w.nqb);
+    w.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, w.pieces);
+    w.slots = ls::prefill_split_slots((int64_t)items, w.grid, w.pieces);
     w.code = LS_EWORKSPACE;
     if (!bp.ok()) return "workspace is too small";
     const Bump mark = bp;
     for (;;) {
         bp = mark;
         w.queue = bp.take<uint4>(items + w.slots);
-        w.split = w.slots ? bp.take<uint2>((size_t)w.slots) : nullptr;
+        w.rec = w.pieces ? reinterpret_cast<uint32_t*>(w.queue) : per_item;
+        w.upto = w.pieces ? per_item : nullptr;
+        w.cuts = w.slots && w.pieces ? bp.take<int2>((size_t)w.grid + 1) : nullptr;
+        w.split = w.slots && !w.pieces ? bp.take<uint2>((size_t)w.slots) : nullptr;
         w.part_o = w.slots ? bp.take<float>((size_t)w.slots * 128 * s->d) : nullptr;
         w.part_ml = w.slots ? bp.take<float>((size_t)w.slots * 128 * 2) : nullptr;
         if (bp.ok()) break;
@@ -427,33 +434,33 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
         return fail(c, LS_ESHAPE, "ls_sparse_prefill: n too large for the LDS bitmaps");
     PrefillCarve w;
     if (const char* m = carve_prefill(c, s, w)) return fail(c, w.code, "ls_sparse_prefill: %s", m);
-    uint32_t* obits = w.obits; uint32_t* cost = w.cost; uint16_t* pref = w.pref;
-    int32_t* qlen = w.qlen; int32_t* qhead = w.qhead; uint8_t* tab = w.tab;
     const int nqb = w.nqb; const int64_t pos0 = w.pos0;
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill: hipSetDevice failed");
     ls::PlanArgs p{};
     p.n = s->n; p.words = words; p.tab_len = tab_len; p.v_idx = v_idx; p.v_cnt = v_cnt; p.s_idx = s_idx; p.s_cnt = s_cnt;
-    p.cap_v = cap_v; p.cap_s = cap_s; p.obits = obits; p.tab = tab; p.nqb = nqb; p.pos0 = pos0; p.ncol = w.ncol; p.cost = cost; p.pref = pref;
-    p.status = c->status; p.split_count = w.split_count;
+    p.cap_v = cap_v; p.cap_s = cap_s; p.obits = w.obits; p.tab = w.tab; p.nqb = nqb; p.pos0 = pos0; p.dtype = s->dtype;
+    p.elist = w.elist; p.rec = w.rec; p.upto = w.upto; p.head_work = w.head_work; p.split_count = w.misc + 24; p.status = c->status;
     hipError_t e = ls::launch_plan(p, BH, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(plan): %s", hipGetErrorString(e));
-    ls::SchedArgs sa{};
-    sa.BH = BH; sa.G = s->Hq / s->Hkv; sa.Hq = s->Hq; sa.Hkv = s->Hkv; sa.nqb = nqb; sa.cost = cost;
-    sa.queue = w.queue; sa.qlen = qlen; sa.qbase = w.qbase; sa.qhead = qhead;
-    sa.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)BH * nqb, w.slots);
-    sa.slots = w.slots; sa.split = w.split; sa.split_count = w.split_count;
-    sa.pref = pref; sa.ncol = w.ncol; sa.tab_len = tab_len; sa.n = s->n; sa.pos0 = pos0;
-    e = ls::launch_sched(sa, static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(sched): %s", hipGetErrorString(e));
+    if (!w.pieces) {
+        ls::SchedArgs sa{};
+        sa.BH = BH; sa.G = s->Hq / s->Hkv; sa.Hq = s->Hq; sa.Hkv = s->Hkv; sa.nqb = nqb; sa.rec = w.rec; sa.head_work = w.head_work;
+        sa.queue = w.queue; sa.qlen = w.misc; sa.qhead = w.misc + 8; sa.qbase = w.misc + 16;
+        sa.grid = w.grid; sa.slots = w.slots; sa.split = w.split; sa.split_count = w.misc + 24;
+        e = ls::launch_sched(sa, static_cast<hipStream_t>(stream));
+        if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(sched): %s", hipGetErrorString(e));
+    }
     ls::PrefillArgs a{};
     a.q = q; a.k = k; a.v = v; a.out = out; a.lse = lse; a.n = s->n; a.n_hat = s->n_hat;
-    a.queue = w.queue; a.qlen = qlen; a.qbase = w.qbase; a.qhead = qhead; a.grid = sa.grid;
-    a.slots = w.slots; a.split = w.split; a.split_count = w.split_count; a.part_o = w.part_o; a.part_ml = w.part_ml;
+    a.elist = w.elist; a.rec = w.rec; a.upto = w.upto; a.head_work = w.head_work;
+    a.queue = w.pieces ? nullptr : w.queue; a.qlen = w.misc; a.qhead = w.misc + 8; a.qbase = w.misc + 16;
+    a.split = w.split; a.split_count = w.misc + 24;
+    a.grid = w.grid; a.slots = w.slots; a.cuts = w.cuts; a.part_o = w.part_o; a.part_ml = w.part_ml;
     a.pos0 = pos0;
     a.Hq = s->Hq; a.Hkv = s->Hkv; a.G = s->Hq / s->Hkv; a.BH = BH;
-    a.nqb = nqb;
+    a.nqb = nqb; a.dtype = s->dtype;
     a.words = words; a.tab_len = tab_len; a.scale_log2e = scale_log2e(s);
-    a.obits = obits; a.tab = tab; a.v_idx = v_idx; a.cap_v = cap_v;
+    a.obits = w.obits; a.tab = w.tab; a.v_idx = v_idx; a.cap_v = cap_v;
     std::array<hipEvent_t, 4> ev{};
     if (c->profile) {
         try { c->events.reserve(c->events.size() + 1); } catch (...) { return fail(c, LS_EHIP, "ls_sparse_prefill: out of memory for events"); }
@@ -643,7 +650,7 @@ int ls_debug_set_counters(ls_ctx* c, int32_t value, void* stream) {
     return LS_OK;
 }
 
-/* Debug / test hook: the eight work queues the last ls_sparse_prefill call on this context built
+/* Debug / test hook: the items that the last ls_sparse_prefill call on this context gave to each XCD
  * (host_queue: [8][B*Hq*nqb] item words = (head << 16) | row block, host_qlen: [8]); synchronises the stream. */
 int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_queue, int32_t* host_qlen, int32_t* nqb_out, void* stream) {
     if (!c || !s || !host_queue || !host_qlen || !nqb_out) return LS_EINVAL;
@@ -652,20 +659,31 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
     if (carve_prefill(c, s, w)) return w.code;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t items = (size_t)s->B * s->Hq * w.nqb;
-    std::vector<uint4> q;
-    try { q.resize(items + w.slots); } catch (...) { return fail(c, LS_EHIP, "ls_debug_copy_prefill_queues: out of memory"); }
-    int32_t len[8], base[8];
+    const size_t BH = (size_t)s->B * s->Hq;
+    std::vector<uint4> q;                                  // queues, or records
+    std::vector<uint32_t> upto, head;
+    std::vector<int> xcd;
+    try { q.resize(items + w.slots); upto.resize(items); head.resize(BH); xcd.resize(items); } catch (...) { return fail(c, LS_EHIP, "ls_debug_copy_prefill_queues: out of memory"); }
+    int32_t misc[24];
     if (hipSetDevice(c->device) != hipSuccess) return LS_EHIP;
     if (hipMemcpyAsync(q.data(), w.queue, q.size() * sizeof(uint4), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
-    if (hipMemcpyAsync(len, w.qlen, sizeof(len), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
-    if (hipMemcpyAsync(base, w.qbase, sizeof(base), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
+    if (w.pieces && hipMemcpyAsync(upto.data(), w.upto, items * 4, hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
+    if (hipMemcpyAsync(head.data(), w.head_work, BH * 4, hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
+    if (hipMemcpyAsync(misc, w.misc, sizeof(misc), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
     if (hipStreamSynchronize(st) != hipSuccess) return LS_EHIP;
-    for (int x = 0; x < 8; ++x) {                          // an item in parts is listed once, by its first part
-        host_qlen[x] = 0;
-        for (int i = 0; i < len[x] && (size_t)base[x] + i < q.size(); ++i) {
-            const uint4 e = q[(size_t)base[x] + i];
-            if ((e.y & 0xFF) == 0 && (size_t)host_qlen[x] < items) host_queue[x * items + host_qlen[x]++] = e.x;
-        }
+    // an item in parts is listed once, by its first part
+    auto word = [&](size_t i) { return (uint32_t)(i / w.nqb) << 16 | (uint32_t)(i % w.nqb); };
+    for (int x = 0; x < 8; ++x) host_qlen[x] = 0;
+    if (w.pieces) {
+        ls::prefill_pieces(s->dtype, reinterpret_cast<const uint32_t*>(q.data()), upto.data(), head.data(), (int)BH, w.nqb, w.grid, w.slots, xcd.data());
+        for (size_t i = 0; i < items; ++i)
+            if (xcd[i] >= 0) host_queue[xcd[i] * items + host_qlen[xcd[i]]++] = word(i);
+    } else {
+        for (int x = 0; x < 8; ++x)
+            for (int i = 0; i < misc[x] && (size_t)misc[16 + x] + i < q.size(); ++i) {
+                const uint4 e = q[(size_t)misc[16 + x] + i];
+                if ((e.y & 0xFF) == 0 && (size_t)host_qlen[x] < items) host_queue[x * items + host_qlen[x]++] = word(e.x);
+            }
     }
     *nqb_out = w.nqb;
     return LS_OK;

@@ -69,9 +69,11 @@ struct PlanArgs {
     uint8_t* tab;             // [BH][tab_len]
     int nqb;                  // row blocks of the turn
     int64_t pos0;             // position of the first
-    uint32_t* ncol;           // [BH][nqb] selected columns each row block gathers
-    uint32_t* cost;           // [BH] estimated tiles per row block (for the work queues)
-    uint16_t* pref;           // [BH][tab_len + 1] prefix counts of table entries with a selected diagonal
+    int dtype;
+    uint16_t* elist;          // [BH][tab_len + 1] the table entries with a selected diagonal, ascending
+    uint32_t* rec;            // [BH][nqb] of each row block: key blocks it visits | columns it gathers << 13
+    uint32_t* upto;           // [BH][nqb] work of the head's row blocks up to and including this one (null: not wanted)
+    uint32_t* head_work;      // [BH] work of all of them
     int32_t* split_count;     // [2] cleared here for sched_kernel
     int32_t* status;          // device status word of the context (bits LS_STAT_*), OR-ed into
 };
@@ -79,19 +81,16 @@ struct PlanArgs {
 // Work queues of the sparse attention kernel: one list per XCD of (head, row block) items or parts of them.
 struct SchedArgs {
     int BH, G, Hq, Hkv, nqb;
-    const uint32_t* cost;     // [BH]
-    const uint16_t* pref;     // [BH][tab_len + 1]
-    const uint32_t* ncol;     // [BH][nqb]
-    int tab_len;
-    int64_t n, pos0;
-    uint4* queue;             // [items + slots] entries, one queue behind the other: {bh << 16 | qb, part | parts << 8 | first slot << 16, key blocks, columns}
+    const uint32_t* rec;      // [BH][nqb], as plan_kernel left them
+    const uint32_t* head_work;
+    uint4* queue;             // [items + slots] entries, one queue behind the other: {item, part | parts << 8 | first slot << 16, key blocks, columns}
     int32_t* qlen;            // [8]
     int32_t* qbase;           // [8] first entry of each queue
     int32_t* qhead;           // [8] next entry to hand out (the first ones go by workgroup number)
     int grid;                 // workgroups of the attention kernel
     int slots;                // results of parts that the workspace holds (0: no item is split)
-    uint2* split;             // [slots] split items: {bh << 16 | qb, parts | first slot << 16}
-    int32_t* split_count;     // [2] slots in use, split items
+    uint2* split;             // [slots] split items: {item, parts | first slot << 16}
+    int32_t* split_count;     // [2] slots in use, split items; cleared by plan_kernel
 };
 
 struct PrefillArgs {
@@ -99,17 +98,23 @@ struct PrefillArgs {
     void* out;
     float* lse;
     int64_t n, n_hat, pos0;
-    int Hq, Hkv, G, BH, nqb, words, tab_len;
+    int Hq, Hkv, G, BH, nqb, words, tab_len, dtype;
     float scale_log2e;
     const uint32_t* obits;
     const uint8_t* tab;
     const int32_t* v_idx;
     int cap_v;
-    const uint4* queue;       // work queues built by sched_kernel
+    const uint16_t* elist;    // as plan_kernel left them
+    int grid;                 // workgroups
+    int slots;                // results of parts that the workspace holds
+    // pieces (ls_prefill.hip): at most `grid`
+    const uint32_t* rec;
+    const uint32_t *upto, *head_work;
+    int2* cuts;               // [grid + 1] where each piece begins {item, tile}; behind them their number (where slots > 0)
+    // or work queues built by sched_kernel
+    const uint4* queue;       // null: pieces
     const int32_t *qlen, *qbase;
     int32_t* qhead;
-    int grid;
-    int slots;
     const uint2* split;
     const int32_t* split_count;
     float *part_o, *part_ml;  // [slots][128][d] accumulators in lane order, [slots][128][2] reference and normaliser
@@ -181,8 +186,11 @@ hipError_t launch_sched(const SchedArgs& a, hipStream_t st);
 hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st, const hipEvent_t* ev = nullptr);
 size_t prefill_smem_bytes(int dtype, int d, int tab_len);
 int prefill_block_rows();
-int prefill_grid(int dtype, int d, int64_t items, int slots);
-int prefill_split_slots(int64_t items);       // parts of split items that a call with so many (head, row block) items may use
+bool prefill_in_pieces(int BH, int64_t n, int nqb);                 // the work is shared out in pieces, or by queues
+int prefill_grid(int dtype, int d, int64_t items, bool pieces);
+int prefill_split_slots(int64_t items, int grid, bool pieces);      // parts' results that a call with so many (head, row block) items may use
 size_t prefill_slot_bytes(int d);
+// What the workgroups work out for themselves, on the host: the XCD on whose piece each item begins
+void prefill_pieces(int dtype, const uint32_t* rec, const uint32_t* upto, const uint32_t* head_work, int BH, int nqb, int grid, int slots, int* xcd_of_item);
 
 }  // namespace ls

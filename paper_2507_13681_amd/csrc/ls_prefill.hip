@@ -36,6 +36,16 @@ namespace ls {
 constexpr int BM = 128;   // query rows per workgroup
 constexpr int BN = 64;    // keys per tile
 constexpr int PREFILL_THREADS = 256;
+
+// Work is counted in eighths of a contiguous tile: a packed tile takes longer (its rows are gathered), and an item takes as long as
+// four tiles beside its own (queries, lists, the first tile's way from memory, the results; one tile in fp32, whose tiles take long).
+constexpr uint32_t WORK_TILE = 8, WORK_COLS = 9;
+// What an item is: the contiguous tiles (at most 4097) and the columns (at most 262144) of a row block.
+__host__ __device__ __forceinline__ uint32_t pack_item(uint32_t n1, uint32_t cols) { return n1 | cols << 13; }
+__host__ __device__ __forceinline__ int item_blocks(uint32_t r) { return (int)(r & 0x1FFFu); }
+__host__ __device__ __forceinline__ int item_cols(uint32_t r) { return (int)(r >> 13); }
+__host__ __device__ __forceinline__ uint32_t work_base(int dtype) { return dtype == 0 ? 32 : 8; }
+__host__ __device__ __forceinline__ uint32_t item_work(uint32_t base, uint32_t n1, uint32_t n2) { return base + n1 * WORK_TILE + n2 * WORK_COLS; }
 // A half's probabilities (relative to the running reference) may sum to this in a lane before the reference moves: bf16 and fp32
 // are as exact up there as around one, and the 2^18 keys of a row stay far from the end of either's range.
 constexpr float SOFT_LIMIT = 65536.f;
@@ -45,8 +55,10 @@ constexpr float SOFT_LIMIT = 65536.f;
 //   obits : [BH][4 + words] uint32: four zero words, then bit o in word 4 + o/32; words = n/32 rounded up + 8 zero words
 //   tab   : [BH][tab_len] bytes, entry j+1 for j = -1 .. ; bit0 = some diagonal of
 //           [64j-63, 64j+127] is selected, bit1 = all of them are (and none is cut off at 0 or n-1)
-//   ncol  : [BH][nqb] columns that a row block gathers (none if every diagonal is selected: the mask is plain causal
-//           then, or if the column list is not strictly ascending inside [0, n): its columns are ignored)
+//   elist : [BH][tab_len + 1] the entries of tab with bit0, ascending: a row block's key blocks are a run of them
+//   rec   : [BH][nqb] of each row block the length of that run and the columns it gathers (none if every diagonal is
+//           selected: the mask is plain causal then, or if the column list is not strictly ascending inside [0, n): its columns
+//           are ignored); upto, head_work: running sums of the work that is
 // ---------------------------------------------------------------------------------------------
 // Exclusive prefix sum over the 1024 threads of a workgroup (wave shuffles + one LDS round).
 // `wsum` must hold 16 words; returns the sum of `v` over the threads before this one and, in
@@ -202,45 +214,196 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
         tabs[e] = f;                                       // LDS copy for the counts below
     }
     __syncthreads();
-    // prefix counts of active entries: pref[e] = number of active entries below e
+    // the active entries in ascending order, and in LDS how many lie below each entry
     const int chunk = (a.tab_len + (int)blockDim.x - 1) / (int)blockDim.x;
     const int e0 = tid * chunk < a.tab_len ? tid * chunk : a.tab_len, e1 = (e0 + chunk < a.tab_len) ? e0 + chunk : a.tab_len;
     int mine2 = 0;
     for (int e = e0; e < e1; ++e) mine2 += tabs[e] & 1;
     uint32_t active_entries;
     uint32_t run = block_scan_1024((uint32_t)mine2, wsum, active_entries);
-    uint16_t* pref = a.pref + (int64_t)bh * (a.tab_len + 1);
-    for (int e = e0; e < e1; ++e) { pref[e] = (uint16_t)run; run += tabs[e] & 1; }
-    if (e1 == a.tab_len && e0 < a.tab_len) pref[a.tab_len] = (uint16_t)run;
-    // columns each row block gathers: those up to its last row (none where every diagonal is selected, phase 1 covers
-    // all cells then, or where the list is unusable)
+    uint16_t* el = a.elist + (int64_t)bh * (a.tab_len + 1);
+    uint16_t* below = reinterpret_cast<uint16_t*>(sm);     // [tab_len + 1]; the bitmap has been written out (the scan's barriers lie between)
+    for (int e = e0; e < e1; ++e) {
+        below[e] = (uint16_t)run;
+        if (tabs[e] & 1) el[run++] = (uint16_t)e;
+    }
+    if (tid == 0) below[a.tab_len] = (uint16_t)active_entries;
+    // what each row block visits and gathers: the columns up to its last row (none where every diagonal is selected, phase 1 covers
+    // all cells then, or where the list is unusable), and the work that is
     {
         const bool none = total_bits == (int)n || v_bad;
         const int per = (a.nqb + (int)blockDim.x - 1) / (int)blockDim.x;
         const int q0 = tid * per < a.nqb ? tid * per : a.nqb, q1 = q0 + per < a.nqb ? q0 + per : a.nqb;
         uint32_t top = 0;                                  // positions grow with the block: a running maximum fills the gaps
         for (int q = q0; q < q1; ++q) top = top > colh[q] ? top : colh[q];
-        uint32_t before = block_max_1024(top, wsum);
+        const uint32_t before = block_max_1024(top, wsum);             // (its barriers publish `below`)
+        const uint32_t base = work_base(a.dtype);
+        uint32_t work = 0, all;
+        auto visit = [&](int q, uint32_t& cols) -> uint2 {                       // {key blocks, columns}
+            const int64_t blockpos = a.pos0 + (int64_t)q * BM;
+            const int64_t posmax = (blockpos + BM - 1 < n - 1) ? blockpos + BM - 1 : n - 1;
+            const int jb = (int)(blockpos / BN), kb_hi = (int)(posmax / BN);
+            cols = cols > colh[q] ? cols : colh[q];
+            return make_uint2(below[jb + 2] - below[jb - kb_hi + 1], none ? 0u : cols);             // entries jb-kb_hi+1 .. jb+1
+        };
+        uint32_t cols = before;
+        for (int q = q0; q < q1; ++q) { const uint2 r = visit(q, cols); work += item_work(base, r.x, (r.y + BN - 1) / BN); }
+        uint32_t pre = block_scan_1024(work, wsum, all);
+        cols = before;
         for (int q = q0; q < q1; ++q) {
-            before = before > colh[q] ? before : colh[q];
-            a.ncol[(int64_t)bh * a.nqb + q] = none ? 0u : before;
+            const uint2 r = visit(q, cols);
+            pre += item_work(base, r.x, (r.y + BN - 1) / BN);
+            a.rec[(int64_t)bh * a.nqb + q] = pack_item(r.x, r.y);
+            if (a.upto) a.upto[(int64_t)bh * a.nqb + q] = pre;
         }
+        if (tid == 0) a.head_work[bh] = all;
     }
-    // head flag and cost estimate: table entries with a selected diagonal (key blocks a late row block
-    // visits) plus packed column tiles
     s_bad = __syncthreads_or(s_bad);
     if (bh == 0 && tid < 2) a.split_count[tid] = 0;
     if (tid == 0) {
         if (v_bad) atomicOr(a.status, STAT_V_INVALID);
         if (s_bad) atomicOr(a.status, STAT_S_RANGE);
-        int nv = a.v_cnt[bh]; if (nv > a.cap_v) nv = a.cap_v; if (nv < 0) nv = 0;
-        if (total_bits == (int)n || v_bad) nv = 0;
-        a.cost[bh] = (uint32_t)((int)active_entries + (nv + 63) / 64 + 1);
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// sched: builds the 8 work queues.  The query heads of one KV head stay together (they share K/V
+// pieces: which part of the work each workgroup of the attention kernel takes, up to PIECES_TILES.
+//
+// The items (row blocks of heads) lie in one row, head by head, and the row is cut into as many pieces of equal work as
+// there are workgroups.  Every workgroup finds its own piece from the running sums that plan_kernel left behind: a scan over
+// the heads, a look through one head's row blocks.  Neighbouring pieces go to the same XCD, so that the query heads that
+// share K and V meet in one L2.  An item that a cut goes through is done in parts, whose unnormalised results go to slots of the
+// workspace and which combine_kernel puts together; a cut that would leave a few tiles on one side is moved to the
+// end of the item, and so are all cuts where the workspace has no room for the parts.
+//
+// Against the work queues of sched_kernel (which serve what is larger) this saves a launch of one workgroup per XCD, a look at the
+// queues per item, and the wait for the longest item, which a short turn feels most.  The whole call, bf16, 32 heads of d = 128, queues -> pieces,
+// us: 2048 rows, all new, 92 -> 68; 1024 new of 8192 152 -> 124; 300 of 16384 89 -> 70; 100 of 131072 254 -> 230; 61 of 12347
+// 32.7 -> 30.3; 4 heads fp32, 256 of 1024 44 -> 38, 2048 all new 65 -> 37.
+// The line.  Of equal pieces the two workgroups of a CU get unequal speed (10-15 %; the older one's waves go first) and nothing
+// evens that out, and the row spreads the heads of a moment wider than the queues do: the longer the run, the more both cost.
+// Tiles here are those that dense heads would have.  262144: 2048 of 32768 rows 507 -> 477, 8192 rows all new 300 -> 290, B 4, 64 heads,
+// 2048 of 4096 389 -> 397; 400000 to 570000: 10000 rows 378 -> 361, 12000 rows 553 -> 581, B 2, 6000 of 9000 502 -> 505; 720000 and more: 9000 of
+// 20000 814 -> 844, 10923 of 32768 1661 -> 1870 and more.
+// ---------------------------------------------------------------------------------------------
+constexpr int64_t PIECES_TILES = 262144;
+constexpr int CUT_TILES = 2;                               // fewest tiles on either side of a cut (a part costs its result written and read: the time of two)
+__host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : base + 8; }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
+
+struct Cut { int item, tile; };                            // a piece begins at this tile of this item
+// The cut `u` into an item of n1 contiguous and n2 packed tiles.
+__host__ __device__ __forceinline__ Cut cut_item(uint32_t base, uint32_t u, int item, int n1, int n2, bool split) {
+    const int tiles = n1 + n2;
+    int t;
+    if (!split) t = 2 * u < item_work(base, n1, n2) ? 0 : tiles;
+    else if (u < base + CUT_TILES * WORK_TILE) t = 0;
+    else {
+        const uint32_t v = u - base;
+        t = v < n1 * WORK_TILE ? (int)(v / WORK_TILE) : n1 + (int)((v - n1 * WORK_TILE) / WORK_COLS);
+        if (t + CUT_TILES > tiles) t = tiles;
+    }
+    return t > 0 && t >= tiles ? Cut{item + 1, 0} : Cut{item, t};
+}
+// Pieces of which no more than `grid` may be made, and `slots` results of parts kept: one for each piece that begins inside an
+// item, one for each item (or piece) that is left unfinished.
+__host__ __device__ __forceinline__ int begin_slots(int64_t items, int pieces) { return items < pieces ? (int)items : pieces; }
+__host__ __device__ __forceinline__ bool cuts_items(int64_t items, int grid, int slots) {
+    return slots >= grid + begin_slots(items, grid) || slots > 2 * items;
+}
+__host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work, int64_t items, int grid, int slots) {
+    if (!cuts_items(items, grid, slots)) return items < grid ? (int)items : grid;
+    const uint32_t most = slots >= grid + begin_slots(items, grid) ? grid : slots - (int)items;
+    uint32_t pieces = work / piece_work(base), least = items < most ? (uint32_t)items : most;
+    pieces = pieces > most ? most : pieces < least ? least : pieces;
+    // (at least two tiles a piece: no two cuts fall into one tile)
+    return pieces <= work / (2 * WORK_TILE) ? (int)pieces : work >= 2 * WORK_TILE ? (int)(work / (2 * WORK_TILE)) : 1;
+}
+// where piece p begins
+__host__ __device__ __forceinline__ uint32_t cut_at(uint32_t total, int p, int pieces) {
+    const uint32_t q = total / (uint32_t)pieces, r = total % (uint32_t)pieces;
+    return q * (uint32_t)p + ((uint32_t)p < r ? (uint32_t)p : r);
+}
+// piece of workgroup `id`, or -1
+__host__ __device__ __forceinline__ int piece_of(int id, int pieces) {
+    const int x = id & 7, j = id >> 3, q = pieces / 8, r = pieces % 8;
+    return j < q + (x < r ? 1 : 0) ? x * q + (x < r ? x : r) + j : -1;
+}
+
+struct Span { int piece, pieces; Cut from, to; uint32_t rec; };          // from `from` up to, not including, `to`; rec: of from.item where known (else 0)
+// The span of this workgroup (all of its 256 threads call; the result is uniform).  piece -1: none.  Two round trips to memory.
+__device__ __forceinline__ Span my_span(const PrefillArgs& a, uint32_t* sh) {              // sh: 8 words of LDS
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int per = (a.BH + 255) / 256, h0 = tid * per < a.BH ? tid * per : a.BH, h1 = h0 + per < a.BH ? h0 + per : a.BH;
+    uint32_t mine = 0;                                     // (all work there is: less than 2^25, prefill_in_pieces)
+    for (int h = h0; h < h1; ++h) mine += a.head_work[h];
+    uint32_t inc = mine;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) { const uint32_t t = __shfl_up(inc, off, 64); if (lane >= off) inc += t; }
+    if (lane == 63) sh[wv] = inc;
+    __syncthreads();
+    uint32_t before = inc - mine, total = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) { const uint32_t t = sh[w]; if (w < wv) before += t; total += t; }
+    total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
+    const int items = a.BH * a.nqb;
+    const uint32_t base = work_base(a.dtype);
+    const bool split = cuts_items(items, a.grid, a.slots);
+    Span s;
+    s.pieces = piece_count(base, total, items, a.grid, a.slots);
+    s.piece = piece_of((int)blockIdx.x, s.pieces);
+    s.from = s.to = Cut{items, 0};
+    s.rec = 0u;
+    if (s.piece < 0) return s;
+    const uint32_t x0 = cut_at(total, s.piece, s.pieces), x1 = cut_at(total, s.piece + 1, s.pieces);
+    if (x0 < before + mine && x1 >= before) {
+        uint32_t at = before;
+        for (int h = h0; h < h1; ++h) {
+            const uint32_t next = at + a.head_work[h];
+            if (x0 >= at && x0 < next) { sh[4] = (uint32_t)h; sh[5] = x0 - at; }
+            if (x1 >= at && x1 < next) { sh[6] = (uint32_t)h; sh[7] = x1 - at; }
+            at = next;
+        }
+    }
+    __syncthreads();
+    // every wave looks for both ends in the sums of their heads, with the records beside them
+    const bool more = s.piece + 1 < s.pieces;
+    const int hb = __builtin_amdgcn_readfirstlane((int)sh[4]), he = more ? __builtin_amdgcn_readfirstlane((int)sh[6]) : hb;
+    const uint32_t rb = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh[5]), re = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh[7]);
+    const uint32_t *ub = a.upto + (int64_t)hb * a.nqb, *ue = a.upto + (int64_t)he * a.nqb;
+    const uint32_t *cb = a.rec + (int64_t)hb * a.nqb, *ce = a.rec + (int64_t)he * a.nqb;
+    const int l = lane < a.nqb ? lane : a.nqb - 1;
+    uint32_t u0 = ub[l], c0 = cb[l], u1 = ue[l], c1 = ce[l];
+    auto find = [&](const uint32_t* upto, const uint32_t* recs, uint32_t u, uint32_t c, int h, uint32_t r, uint32_t* rec) -> Cut {
+        uint32_t at = 0;                                   // work of the row blocks before q
+        for (int q = 0;;) {
+            const int n = __popcll(__ballot(q + lane < a.nqb && u <= r));
+            if (n > 0) at = (uint32_t)__builtin_amdgcn_readlane((int)u, n - 1);
+            if (n < 64) {
+                const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)c, n);
+                const Cut k = cut_item(base, r - at, h * a.nqb + q + n, item_blocks(e), (item_cols(e) + BN - 1) / BN, split);
+                if (rec && k.item == h * a.nqb + q + n) *rec = e;
+                return k;
+            }
+            q += 64;
+            const int i = q + lane < a.nqb ? q + lane : a.nqb - 1;
+            u = upto[i]; c = recs[i];
+        }
+    };
+    uint32_t rec = 0xFFFFFFFFu;
+    s.from = find(ub, cb, u0, c0, hb, rb, &rec);
+    if (more) s.to = find(ue, ce, u1, c1, he, re, nullptr);
+    s.rec = rec != 0xFFFFFFFFu || s.from.item >= items ? rec : a.rec[s.from.item];      // (a cut moved to the next item: its record)
+    if (a.slots > 0 && tid == 0) {                         // for combine_kernel
+        a.cuts[s.piece] = make_int2(s.from.item, s.from.tile);
+        if (s.piece == 0) a.cuts[a.grid] = make_int2(s.pieces, 0);
+    }
+    return s;
+}
+// Slot of the part with which an item begins on piece p; one that takes an item up goes to the slot of its piece.
+__host__ __device__ __forceinline__ int begin_slot(int item, int p, int64_t items, int pieces) { return pieces + (items < pieces ? item : p); }
+
+// ---------------------------------------------------------------------------------------------
+// sched: builds the 8 work queues of turns beyond PIECES_TILES.  The query heads of one KV head stay together (they share K/V
 // tiles in one L2); KV groups are dealt to the XCDs heaviest first, each to the XCD with the least
 // work so far.
 // One workgroup per queue; groups beyond SCHED_MAX_GROUPS fall back to round-robin dealing.  Inside a
@@ -280,30 +443,22 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     const int groups = a.BH / a.G;
     const bool sorted = groups <= SCHED_MAX_GROUPS;
     const int x = blockIdx.x;
-    // Item cost = key blocks with a selected diagonal that the row block visits (from the prefix counts) + packed
-    // column tiles.
-    auto blocks_of = [&](int bh, int qb) -> int {
-        const int64_t blockpos = a.pos0 + (int64_t)qb * BM;
-        const int64_t posmax = (blockpos + BM - 1 < a.n - 1) ? blockpos + BM - 1 : a.n - 1;
-        const int jb = (int)(blockpos / BN), kb_hi = (int)(posmax / BN);
-        const uint16_t* pref = a.pref + (int64_t)bh * (a.tab_len + 1);
-        return pref[jb + 2] - pref[jb - kb_hi + 1];       // entries jb-kb_hi+1 .. jb+1
-    };
-    auto item_cost = [&](int bh, int qb) -> int {
-        const int c = blocks_of(bh, qb) + (int)(a.ncol[(int64_t)bh * a.nqb + qb] + 63) / 64;
+    auto item_cost = [&](uint32_t it) -> int {             // tiles
+        const uint32_t r = a.rec[it];
+        const int c = item_blocks(r) + (item_cols(r) + BN - 1) / BN;
         return c > 4095 ? 4095 : c;
     };
     const uint32_t all_items = (uint32_t)a.BH * (uint32_t)a.nqb, nqb = (uint32_t)a.nqb;      // at most 8192 * 2050
     const bool cached = all_items <= SPLIT_ITEMS;
     if (cached)
-        for (uint32_t it = tid; it < all_items; it += SCHED_THREADS) cost_s[it] = (uint16_t)item_cost((int)(it / nqb), (int)(it % nqb));
+        for (uint32_t it = tid; it < all_items; it += SCHED_THREADS) cost_s[it] = (uint16_t)item_cost(it);
     for (int i = tid; i < 4097; i += SCHED_THREADS) hist[i] = 0u;
     if (tid == 0) { nheads = 0; base = 0u; }
     if (sorted) {                                          // every block repeats this small computation
         for (int gi = tid; gi < groups; gi += SCHED_THREADS) {
             const int b = gi / a.Hkv, kvh = gi % a.Hkv;
             uint32_t c = 0;
-            for (int g = 0; g < a.G; ++g) c += a.cost[b * a.Hq + kvh * a.G + g];
+            for (int g = 0; g < a.G; ++g) c += a.head_work[b * a.Hq + kvh * a.G + g] / (WORK_TILE * 8);
             gcost[gi] = c;
         }
         __syncthreads();
@@ -315,7 +470,7 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
         }
         __syncthreads();
         if (tid < 64) {                                    // one wave deals them out; lane l < 8 holds bin l's load
-            uint32_t load = 0;                             // (a group's cost is at most G * 4 * 4096 tiles)
+            uint32_t load = 0;                             // (eights of tiles: all heads together have less than 2^28)
             for (int r = 0; r < groups; ++r) {
                 const int gi = order[r];
                 uint32_t best = tid < 8 ? (load << 3 | tid) : 0xFFFFFFFFu;           // least load, then least index
@@ -336,11 +491,11 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
         head_bin[bh] = (uint8_t)bin;
         if (bin == x) { const int i = atomicAdd(&nheads, 1); if (i < SCHED_MAX_HEADS) heads[i] = (uint16_t)bh; }
     }
-    // longest part: the same in every block, from the costs of all items
+    // what is cut into parts: the same in every block, from the costs of all items
     int lmax = 1 << 30;
-    if (a.slots > 0 && cached) {
+    if (cached) {
         int c4[SPLIT_ITEMS / SCHED_THREADS];
-        uint32_t mine = 0, total, used;
+        uint32_t mine = 0, total, used = 0;
 #pragma unroll
         for (int j = 0; j < SPLIT_ITEMS / SCHED_THREADS; ++j) {
             const int it = tid + j * SCHED_THREADS;
@@ -348,29 +503,32 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
             mine += (uint32_t)c4[j];
         }
         (void)block_scan_1024(mine, wsum, total);
-        lmax = (int)(total / (SPLIT_WGS * SPLIT_SHARE));
-        if (lmax < SPLIT_MIN) lmax = SPLIT_MIN;
-        for (;;) {                                         // until the parts fit the slots (lmax >= 4096: nothing is split)
-            mine = 0;
+        if (a.slots > 0) {
+            lmax = (int)(total / (SPLIT_WGS * SPLIT_SHARE));
+            if (lmax < SPLIT_MIN) lmax = SPLIT_MIN;
+            for (;;) {                                     // until the parts fit the slots (lmax >= 4096: nothing is split)
+                mine = 0;
 #pragma unroll
-            for (int j = 0; j < SPLIT_ITEMS / SCHED_THREADS; ++j) {
-                int parts = (c4[j] + lmax - 1) / lmax;
-                if (parts > SPLIT_MAX_PARTS) parts = SPLIT_MAX_PARTS;
-                mine += parts > 1 ? (uint32_t)parts : 0u;
+                for (int j = 0; j < SPLIT_ITEMS / SCHED_THREADS; ++j) {
+                    int parts = (c4[j] + lmax - 1) / lmax;
+                    if (parts > SPLIT_MAX_PARTS) parts = SPLIT_MAX_PARTS;
+                    mine += parts > 1 ? (uint32_t)parts : 0u;
+                }
+                (void)block_scan_1024(mine, wsum, used);
+                if (used <= (uint32_t)a.slots || lmax >= 4096) break;
+                lmax += (lmax + 1) / 2;
             }
-            (void)block_scan_1024(mine, wsum, used);
-            if (used <= (uint32_t)a.slots || lmax >= 4096) break;
-            lmax += (lmax + 1) / 2;
+            if (used > (uint32_t)a.slots) lmax = 1 << 30;
         }
-        if (used > (uint32_t)a.slots) lmax = 1 << 30;
     }
+    const bool splits = lmax < 4096;
     auto parts_of = [&](int c) -> int {
-        const int p = lmax >= 4096 ? 1 : (c + lmax - 1) / lmax;
+        const int p = splits ? (c + lmax - 1) / lmax : 1;
         return p < 1 ? 1 : p > SPLIT_MAX_PARTS ? SPLIT_MAX_PARTS : p;
     };
     __syncthreads();
     uint32_t ahead = 0;
-    if (lmax < 4096) {
+    if (splits) {
         for (uint32_t it = tid; it < all_items; it += SCHED_THREADS) if (head_bin[it / nqb] < x) ahead += (uint32_t)parts_of(cost_s[it]);
     } else {
         for (int bh = tid; bh < a.BH; bh += SCHED_THREADS) if (head_bin[bh] < x) ahead += nqb;
@@ -380,9 +538,9 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     if ((tid & 63) == 0 && ahead) atomicAdd(&base, ahead);
     const int nh_ = nheads < SCHED_MAX_HEADS ? nheads : SCHED_MAX_HEADS;
     const uint32_t items = (uint32_t)nh_ * nqb;
-    for (uint32_t it = tid; it < items; it += SCHED_THREADS) {
-        const int bh = heads[it / nqb], qb = (int)(it % nqb);
-        const int c = cached ? cost_s[bh * a.nqb + qb] : item_cost(bh, qb), p = parts_of(c);
+    for (uint32_t i = tid; i < items; i += SCHED_THREADS) {
+        const uint32_t it = heads[i / nqb] * nqb + i % nqb;
+        const int c = cached ? cost_s[it] : item_cost(it), p = parts_of(c);
         atomicAdd(&hist[4095 - (c + p - 1) / p], (uint32_t)p);
     }
     __syncthreads();
@@ -396,28 +554,57 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
         for (int q = 0; q < 4; ++q) { hist[4 * tid + q] = run; run += h4[q]; }
     }
     __syncthreads();
-    for (uint32_t it = tid; it < items; it += SCHED_THREADS) {
-        const int bh = heads[it / nqb], qb = (int)(it % nqb);
-        const uint32_t n1 = (uint32_t)blocks_of(bh, qb), nv = a.ncol[(int64_t)bh * a.nqb + qb];
-        const int c = cached ? cost_s[bh * a.nqb + qb] : item_cost(bh, qb), p = parts_of(c);
-        const uint32_t item = ((uint32_t)bh << 16) | (uint32_t)qb;
-        uint32_t posn = atomicAdd(&hist[4095 - (c + p - 1) / p], (uint32_t)p), slot0 = 0;
+    for (uint32_t i = tid; i < items; i += SCHED_THREADS) {
+        const uint32_t it = heads[i / nqb] * nqb + i % nqb;
+        const int c = cached ? cost_s[it] : item_cost(it), p = parts_of(c);
+        const uint32_t posn = atomicAdd(&hist[4095 - (c + p - 1) / p], (uint32_t)p);
+        uint32_t slot0 = 0;
         if (p > 1) {                                       // slots and the list of split items are shared by the 8 blocks
             slot0 = (uint32_t)atomicAdd(&a.split_count[0], p);
-            a.split[atomicAdd(&a.split_count[1], 1)] = make_uint2(item, (uint32_t)p | (slot0 << 16));
+            a.split[atomicAdd(&a.split_count[1], 1)] = make_uint2(it, (uint32_t)p | (slot0 << 16));
         }
+        const uint32_t r = a.rec[it];
         uint4* q = a.queue + base + posn;
-        const uint32_t bkv = (uint32_t)(bh / a.Hq * a.Hkv + bh % a.Hq / a.G);
-        for (int e = 0; e < p; ++e) q[e] = make_uint4(item, (uint32_t)e | ((uint32_t)p << 8) | (slot0 << 16), n1 | (bkv << 16), nv);
+        for (int e = 0; e < p; ++e) q[e] = make_uint4(it, (uint32_t)e | ((uint32_t)p << 8) | (slot0 << 16), (uint32_t)item_blocks(r), (uint32_t)item_cols(r));
     }
     if (tid == 0) { a.qlen[x] = (int)entries; a.qbase[x] = (int)base; a.qhead[x] = (a.grid - x + 7) / 8; }
 }
 
-// Persistent launch: the workgroups that are resident at once (256 CUs x per_cu); any number drains the queues, but a
-// surplus one only starts when another ends and lengthens the run by its look at the queues.
-int prefill_grid(int dtype, int d, int64_t items, int slots) {
+// Launch of the attention kernel: the workgroups that are resident at once (256 CUs x per_cu); any number drains the queues, but a
+// surplus one only starts when another ends and lengthens the run by its look at the queues.  Pieces: of few items a dozen each.
+constexpr int ITEM_PARTS = 12;
+int prefill_grid(int dtype, int d, int64_t items, bool pieces) {
     const int per_cu = dtype == 0 ? (d == 128 ? 2 : 3) : (d == 128 ? 1 : 2);
-    return (int)(items + slots < 256 * per_cu ? items + slots : 256 * per_cu);
+    const int64_t most = pieces ? items * ITEM_PARTS : items + prefill_split_slots(items, 0, false);
+    return (int)(most < 256 * per_cu ? most : 256 * per_cu);
+}
+int prefill_split_slots(int64_t items, int grid, bool pieces) {
+    if (pieces) return grid + begin_slots(items, grid);
+    return items > SPLIT_ITEMS ? 0 : items * ITEM_PARTS < SPLIT_SLOTS ? (int)items * ITEM_PARTS : SPLIT_SLOTS;
+}
+bool prefill_in_pieces(int BH, int64_t n, int nqb) { return (int64_t)BH * nqb * ((n + BN - 1) / BN) <= PIECES_TILES; }
+
+void prefill_pieces(int dtype, const uint32_t* rec, const uint32_t* upto, const uint32_t* head_work, int BH, int nqb, int grid, int slots, int* xcd_of_item) {
+    const int64_t all = (int64_t)BH * nqb;
+    uint32_t total = 0;
+    for (int h = 0; h < BH; ++h) total += head_work[h];
+    const int pieces = piece_count(work_base(dtype), total, all, grid, slots);
+    const bool split = cuts_items(all, grid, slots);
+    for (int64_t i = 0; i < all; ++i) xcd_of_item[i] = -1;
+    for (int id = 0; id < grid; ++id) {
+        const int p = piece_of(id, pieces);
+        if (p < 0) continue;
+        Cut c[2] = {{(int)all, 0}, {(int)all, 0}};
+        for (int e = 0; e < 2 && p + e < pieces; ++e) {
+            uint32_t x = cut_at(total, p + e, pieces);
+            int h = 0, q = 0;
+            while (x >= head_work[h]) x -= head_work[h++];
+            while (upto[(int64_t)h * nqb + q] <= x) ++q;
+            const int64_t it = (int64_t)h * nqb + q;
+            c[e] = cut_item(work_base(dtype), x - (q ? upto[it - 1] : 0u), (int)it, item_blocks(rec[it]), (item_cols(rec[it]) + BN - 1) / BN, split);
+        }
+        for (int it = c[0].item + (c[0].tile > 0 ? 1 : 0); it < c[1].item + (c[1].tile > 0 ? 1 : 0); ++it) xcd_of_item[it] = id & 7;
+    }
 }
 
 // Queue entries for this workgroup, called by one whole wave.  The first entry is the workgroup's own place in its
@@ -426,8 +613,8 @@ int prefill_grid(int dtype, int d, int64_t items, int slots) {
 // its end the counter is updated without a look, and beside the other waves' stores of the last results (`ahead`); near
 // the end every workgroup would update it once for nothing, and updates of one counter take turns.  item = ~0 when every
 // queue is drained (each queue hands out each entry once and never refills, so the search ends).
-struct EntrySource {
-    int own, x, len, base;                    // lane l < 8: queue (own + l) % 8, its length and first entry
+struct QueueSource {
+    int own, x, len, base;                    // lane l < 8: queue (own + l) % 8, its length, its first entry
     int at;                                   // place taken in the own queue, -1: none
     bool plenty;
     __device__ __forceinline__ void init(const PrefillArgs& a, int lane) {
@@ -448,6 +635,7 @@ struct EntrySource {
             plenty = own_len - i > 128;
             return a.queue[__builtin_amdgcn_readfirstlane(base) + i];
         }
+        at = -1;
         plenty = false;
         for (;;) {
             const bool some = lane < 8 && __atomic_load_n(&a.qhead[x], __ATOMIC_RELAXED) < len;
@@ -457,9 +645,60 @@ struct EntrySource {
             int i = 0;
             if (lane == src) i = atomicAdd(&a.qhead[x], 1);
             i = __builtin_amdgcn_readlane(i, src);
-            const int ls = __builtin_amdgcn_readlane(len, src);
-            if (i < ls) return a.queue[__builtin_amdgcn_readlane(base, src) + i];
+            if (i < __builtin_amdgcn_readlane(len, src)) {
+                plenty = src == 0 && own_len - i > 128;
+                return a.queue[__builtin_amdgcn_readlane(base, src) + i];
+            }
         }
+    }
+};
+
+// What a workgroup does next: an item, or a part of one.
+struct Entry {
+    int item, blocks, cols;                   // the item's contiguous tiles and columns
+    int lo, hi;                               // queues: part lo of hi; pieces: from tile lo on, up to tile hi (-1: the last)
+    int slot0, slot1;                         // queues: -1, slot of the part; pieces: slots for the part that begins and for the one that goes on
+    __device__ __forceinline__ int begin(int tiles) const { return slot0 < 0 ? tiles * lo / hi : lo; }
+    __device__ __forceinline__ int end(int tiles) const { return slot0 < 0 ? tiles * (lo + 1) / hi : hi < 0 ? tiles : hi; }
+    __device__ __forceinline__ bool in_parts(int tiles) const { return slot0 < 0 ? hi > 1 : lo > 0 || (hi >= 0 && hi < tiles); }
+    __device__ __forceinline__ int slot() const { return slot0 < 0 || lo > 0 ? slot1 : slot0; }
+};
+template <bool QUEUES> struct Entries;
+template <> struct Entries<true> {
+    QueueSource src;
+    __device__ __forceinline__ void init(const PrefillArgs& a, int lane) { src.init(a, lane); }
+    __device__ __forceinline__ void ahead(const PrefillArgs& a, int lane, int wv) { if (wv == 0) src.ahead(a, lane); }
+    __device__ __forceinline__ bool next(const PrefillArgs& a, int lane, int wv, Entry& e) {
+        __shared__ uint4 entry_s;
+        if (wv == 0) {                        // (the other waves have read the last entry: barriers came after it)
+            const uint4 t = src.next(a, lane);
+            if (lane == 0) entry_s = t;
+        }
+        __syncthreads();
+        const uint32_t item = (uint32_t)__builtin_amdgcn_readfirstlane((int)entry_s.x), info = (uint32_t)__builtin_amdgcn_readfirstlane((int)entry_s.y);
+        e.blocks = __builtin_amdgcn_readfirstlane((int)entry_s.z); e.cols = __builtin_amdgcn_readfirstlane((int)entry_s.w);
+        e.item = (int)item; e.lo = info & 0xFF; e.hi = (info >> 8) & 0xFF; e.slot0 = -1; e.slot1 = (int)(info >> 16) + e.lo;
+        return item != 0xFFFFFFFFu;
+    }
+};
+template <> struct Entries<false> {
+    Span s;
+    int at, last;
+    uint32_t rec;                             // of item `at`
+    __device__ __forceinline__ void init(const PrefillArgs& a, int lane) {
+        __shared__ uint32_t span_s[8];
+        s = my_span(a, span_s);
+        at = s.from.item;
+        last = s.to.item - (s.to.tile > 0 ? 0 : 1);
+        rec = s.rec;
+    }
+    __device__ __forceinline__ void ahead(const PrefillArgs& a, int, int) { if (at <= last) rec = a.rec[at]; }
+    __device__ __forceinline__ bool next(const PrefillArgs& a, int, int, Entry& e) {
+        const uint32_t r = (uint32_t)__builtin_amdgcn_readfirstlane((int)rec);
+        e.item = at; e.blocks = item_blocks(r); e.cols = item_cols(r); e.slot0 = begin_slot(at, s.piece, (int64_t)a.BH * a.nqb, s.pieces); e.slot1 = s.piece;
+        e.lo = at == s.from.item ? s.from.tile : 0;
+        e.hi = at == s.to.item ? s.to.tile : -1;
+        return at++ <= last;
     }
 };
 
@@ -523,20 +762,44 @@ __device__ __forceinline__ void store_out4(float* p, float a, float b, float c, 
     *reinterpret_cast<f32x4*>(p) = v;
 }
 
-// Puts the parts of the split items together.  A unit is one wave's 32 rows of a split item, taken by one workgroup in
-// the layout store_part wrote: wave w adds the groups w, w + 4, ... of 16 bytes a lane.  grid-stride over the units.
-template <typename T, int D>
+// Puts the parts of the split items together.  Queues: `split` lists them.  Pieces: the cuts tell; the part that begins an item
+// lies in the slot of the item (or of its piece, where there are more items than pieces) behind those of the pieces, the
+// others in the slots of theirs.  A unit is one wave's 32 rows of a split item, taken by one workgroup in the layout store_part
+// wrote: wave w adds the groups w, w + 4, ... of 16 bytes a lane.  grid-stride over the units (pieces: four per cut).
+template <typename T, int D, bool QUEUES>
 __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
     constexpr int DBLK = D / 32;
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r32 = lane & 31, g = lane >> 5;
-    const int units = a.split_count[1] * 4;
+    const int units = QUEUES ? a.split_count[1] * 4 : (a.grid - 1) * 4;
     for (int u = blockIdx.x; u < units; u += gridDim.x) {
-        const uint2 e = a.split[u >> 2];
-        const int wv = u & 3, bh = e.x >> 16, qb = e.x & 0xFFFF, parts = e.y & 0xFFFF, slot0 = e.y >> 16;
+        const int wv = u & 3;
+        int item, parts, begin, rest;                      // begin: slot of part 0; rest + p: slot of part p > 0
+        if constexpr (QUEUES) {
+            const uint2 e = a.split[u >> 2];
+            item = (int)e.x; parts = (int)(e.y & 0xFFFF); begin = rest = (int)(e.y >> 16);
+        } else {
+            const int first = u >> 2, p = first + 1 + lane;              // the item's first piece, if the next begins inside it
+            const int pieces = a.cuts[a.grid].x;
+            const int2 c0 = a.cuts[first], c1 = a.cuts[first + 1];
+            int2 c = a.cuts[p < a.grid ? p : a.grid - 1];                // (asked for at once; those of no piece are not looked at)
+            if (first + 1 >= pieces || c1.y == 0 || (c0.x == c1.x && c0.y > 0)) continue;       // no cut through an item, or not its first
+            item = c1.x; parts = 1;                        // the first, and one for every piece that begins inside the item
+            for (;;) {
+                const uint64_t no = ~__ballot(first + parts + lane < pieces && c.x == item);
+                const int more = no ? __ffsll((unsigned long long)no) - 1 : 64;
+                parts += more;
+                if (more < 64) break;
+                const int q = first + parts + lane;
+                c = a.cuts[q < a.grid ? q : a.grid - 1];
+            }
+            begin = begin_slot(item, first, a.BH * (int64_t)a.nqb, pieces); rest = first;
+        }
+        const int bh = item / a.nqb, qb = item % a.nqb;
         const int64_t row0 = a.n - a.n_hat, pos = a.pos0 + (int64_t)qb * BM + 32 * wv + r32;
         if (pos < row0 || pos >= a.n) continue;
-        const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + (int64_t)slot0 * BM + 32 * wv + r32;
-        const float* o = a.part_o + (int64_t)slot0 * (BM * D) + wv * (DBLK * 4 * 256) + lane * 4;
+        auto slot_of = [&](int p) -> int64_t { return p == 0 ? begin : rest + p; };
+        const float2* ml = reinterpret_cast<const float2*>(a.part_ml) + 32 * wv + r32;
+        const float* o = a.part_o + wv * (DBLK * 4 * 256) + lane * 4;
         f32x4 acc[DBLK];
 #pragma unroll
         for (int k = 0; k < DBLK; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -547,10 +810,10 @@ __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const int p = p0 + e < parts ? p0 + e : parts - 1;
-                t[e] = ml[(int64_t)p * BM];
+                t[e] = ml[slot_of(p) * BM];
                 if (p0 + e >= parts) t[e].x = -INFINITY;
 #pragma unroll
-                for (int k = 0; k < DBLK; ++k) x[e][k] = *reinterpret_cast<const f32x4*>(o + (int64_t)p * (BM * D) + (w + 4 * k) * 256);
+                for (int k = 0; k < DBLK; ++k) x[e][k] = *reinterpret_cast<const f32x4*>(o + slot_of(p) * (BM * D) + (w + 4 * k) * 256);
             }
             const float m_new = fmaxf(fmaxf(fmaxf(m, t[0].x), fmaxf(t[1].x, t[2].x)), t[3].x);
             const float corr = m > -INFINITY ? fast_exp2(m - m_new) : 0.f;
@@ -666,7 +929,7 @@ __device__ __forceinline__ float max32(float x) {                           // t
 // Tile sequence of one workgroup: first the n1 key blocks crossed by a selected diagonal (ascending),
 // then n2 packed tiles of 64 selected columns each.  K/V rows of tile t+1 are fetched into registers
 // while tile t is multiplied out of LDS buffer t&1, then written to buffer (t+1)&1; one barrier per tile.
-template <typename T, int D>
+template <typename T, int D, bool QUEUES>
 __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs a) {
     using C = TileCfg<T, D>;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -680,22 +943,14 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, g = lane >> 5;
 
-    __shared__ uint4 entry_s;
-    EntrySource src;
-    src.init(a, lane);
-  for (;;) {                                               // persistent: one queue entry per trip
+    Entries<QUEUES> entries;
+    entries.init(a, lane);
+    Entry en;
+    while (entries.next(a, lane, wv, en)) {
     __syncthreads();                                       // everyone is done with the previous entry's LDS
-    if (wv == 0) {
-        const uint4 e = src.next(a, lane);
-        if (lane == 0) entry_s = e;
-    }
-    __syncthreads();
-    const uint32_t item = __builtin_amdgcn_readfirstlane(entry_s.x), info = __builtin_amdgcn_readfirstlane(entry_s.y);
-    const int bkv = (int)(__builtin_amdgcn_readfirstlane(entry_s.z) >> 16);
-    const int nv = __builtin_amdgcn_readfirstlane(entry_s.w);           // columns phase 2 gathers (those up to the block's last row)
-    if (item == 0xFFFFFFFFu) break;
-    const int bh = item >> 16, qb = item & 0xFFFF;
-    const int part = info & 0xFF, parts = (info >> 8) & 0xFF;           // this entry's share of the item's tiles
+    const int item = en.item, bh = item / a.nqb, qb = item % a.nqb;
+    const int bkv = bh / a.Hq * a.Hkv + bh % a.Hq / a.G;
+    const int nv = en.cols;                                // columns phase 2 gathers (those up to the block's last row)
     const int64_t n = a.n, row0 = n - a.n_hat;
     const int64_t blockpos = a.pos0 + (int64_t)qb * BM;                  // multiple of 128
     const int64_t posmax = (blockpos + BM - 1 < n - 1) ? blockpos + BM - 1 : n - 1;
@@ -740,7 +995,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     }
     const int32_t* vi = a.v_idx + (int64_t)bh * a.cap_v;
     const int n2 = (nv + BN - 1) / BN;
-    const int tbeg = (n1 + n2) * part / parts, ntiles = (n1 + n2) * (part + 1) / parts;   // tiles tbeg .. ntiles - 1
+    const int tbeg = en.begin(n1 + n2), ntiles = en.end(n1 + n2);        // tiles tbeg .. ntiles - 1
 
     f32x16 oacc[C::DBLK];
 #pragma unroll
@@ -903,8 +1158,9 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     // ================= epilogue =================
     const float l_tot = l_run + xor32(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-    if (parts > 1) {
-        store_part<C::DBLK>(a, (int)(info >> 16) + part, wv, lane, oacc, m_run * sc2, l_tot);
+    entries.ahead(a, lane, wv);
+    if (en.in_parts(n1 + n2)) {
+        store_part<C::DBLK>(a, en.slot(), wv, lane, oacc, m_run * sc2, l_tot);
     } else if (row_ok) {
         T* orow = reinterpret_cast<T*>(a.out) + ((int64_t)bh * a.n_hat + (pos - row0)) * D;
 #pragma unroll
@@ -919,7 +1175,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
             a.lse[(int64_t)bh * a.n_hat + (pos - row0)] =
                 l_tot > 0.f ? (m_run * sc2 + log2f(l_tot)) * 0.69314718055994531f : -INFINITY;
     }
-  }                                                        // next item
+    }                                                      // next entry
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -960,7 +1216,7 @@ struct DirectCfg {
     __device__ static constexpr int vswz(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
 };
 
-template <int D>
+template <int D, bool QUEUES>
 __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf16_kernel(PrefillArgs a) {
     using C = DirectCfg<D>;
     using T = bf16_t;
@@ -1002,38 +1258,32 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         for (int i = 0; i < C::DBLK; ++i) vaddr[i] = C::K_BYTES + lrow * C::RB + 64 * (i ^ y) + 32 * beta + 8 * (L16 & 3);
     }
 
-    __shared__ uint4 entry_s;
-    EntrySource src;
-    src.init(a, lane);
-  for (;;) {                                               // persistent: one queue entry per trip
-    if (wv == 0) {                                         // (the other waves have read the last entry: barriers came after it)
-        const uint4 e = src.next(a, lane); // taken only when needed: entries are coarse, reserving early hurts the tail
-        if (lane == 0) entry_s = e;
-    }
-    __syncthreads();
-    const uint32_t item = __builtin_amdgcn_readfirstlane(entry_s.x), info = __builtin_amdgcn_readfirstlane(entry_s.y);
-    const int n1 = (int)(__builtin_amdgcn_readfirstlane(entry_s.z) & 0xFFFF);   // key blocks phase 1 visits
-    const int bkv = (int)(__builtin_amdgcn_readfirstlane(entry_s.z) >> 16);
-    const int nv = __builtin_amdgcn_readfirstlane(entry_s.w);           // columns phase 2 gathers (those up to the block's last row)
-    if (item == 0xFFFFFFFFu) break;
-    const int bh = item >> 16, qb = item & 0xFFFF;
-    const int part = info & 0xFF, parts = (info >> 8) & 0xFF;           // this entry's share of the item's tiles
+    Entries<QUEUES> entries;
+    entries.init(a, lane);
+    Entry en;
+    while (entries.next(a, lane, wv, en)) {
+    const int item = en.item, bh = item / a.nqb, qb = item % a.nqb;
+    const int n1 = en.blocks, nv = en.cols;                // key blocks phase 1 visits, columns phase 2 gathers (those up to the block's last row)
+    const int bkv = bh / a.Hq * a.Hkv + bh % a.Hq / a.G;
+    const int n2 = (nv + BN - 1) / BN;
+    const int tbeg = en.begin(n1 + n2), ntiles = en.end(n1 + n2);        // tiles tbeg .. ntiles - 1
     const int64_t n = a.n, row0 = n - a.n_hat;
     const int64_t blockpos = a.pos0 + (int64_t)qb * BM;                  // multiple of 128
-    const int64_t posmax = (blockpos + BM - 1 < n - 1) ? blockpos + BM - 1 : n - 1;
     const unsigned char* Kg = reinterpret_cast<const unsigned char*>(a.k) + (int64_t)bkv * n * C::RB;
     const unsigned char* Vg = reinterpret_cast<const unsigned char*>(a.v) + (int64_t)bkv * n * C::RB;
     const T* Qg = reinterpret_cast<const T*>(a.q) + (int64_t)bh * a.n_hat * D;
-    const uint8_t* tabg = a.tab + (int64_t)bh * a.tab_len;
 
     const uint32_t* obg = a.obits + (int64_t)bh * (OB_PAD + a.words);     // zero words + bitmap of this head
     const int64_t pos = blockpos + 32 * wv + r32;
     const int posw = (int)blockpos + 32 * wv;              // the wave's first row
     const bool row_ok = (pos >= row0) && (pos < n);        // a row that does not exist has zeros: finite results, not stored
     const bool rows_here = posw < n && posw + 31 >= row0;
-    // the first table entries are asked for ahead of the queries: the list below waits for them only
-    const int jb = (int)(blockpos / BN), kb_hi = (int)(posmax / BN);    // jb is even
-    uint8_t tab0 = n1 > 0 && tid <= kb_hi ? tabg[jb - tid + 1] : (uint8_t)0;
+    // the first entries of the head's list are asked for ahead of the queries: the key blocks below wait for them only
+    const int jb = (int)(blockpos / BN);
+    const uint16_t* el = a.elist + (int64_t)bh * (a.tab_len + 1) + n1 - 1 - tbeg;         // of tile tbeg, the others below it
+    if (n - 1 < blockpos + BN && n1 > 0 && a.elist[(int64_t)bh * (a.tab_len + 1)] == 0) ++el;       // half a row block: entry 0 belongs to key blocks beyond it
+    const int blocks = (ntiles < n1 ? ntiles : n1) - tbeg;               // contiguous tiles of this part, none if not positive
+    const uint16_t el0 = tid < blocks ? el[-tid] : (uint16_t)0;
     asm volatile("" ::: "memory");
     Frag<T> qf[C::KSTEPS];
     if (row_ok) {
@@ -1045,25 +1295,9 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         for (int c = 0; c < C::KSTEPS; ++c) zero_frag(qf[c]);
     }
 
-    // ---- ordered list of the key blocks phase 1 visits
-    if (n1 > 0) {
-        int done = 0;
-        for (int base = 0; base <= kb_hi; base += PREFILL_THREADS) {
-            const int kb = base + tid;
-            const bool act = kb <= kb_hi && ((base == 0 ? tab0 : tabg[jb - kb + 1]) & 1);
-            const uint64_t bal = __ballot(act);
-            if (lane == 0) wcnt[wv] = __popcll(bal);
-            __syncthreads();
-            int off = done;
-            for (int w2 = 0; w2 < wv; ++w2) off += wcnt[w2];
-            if (act) kbl[off + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)kb;
-            done += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
-            __syncthreads();
-        }
-    }
+    // ---- key blocks of the contiguous tiles, ascending: the table entry of block kb is jb - kb + 1
+    for (int i = tid; i < blocks; i += PREFILL_THREADS) kbl[i] = (uint16_t)(jb + 1 - (int)(i == tid ? el0 : el[-i]));
     const int32_t* vi = a.v_idx + (int64_t)bh * a.cap_v;
-    const int n2 = (nv + BN - 1) / BN;
-    const int tbeg = (n1 + n2) * part / parts, ntiles = (n1 + n2) * (part + 1) / parts;   // tiles tbeg .. ntiles - 1
 
     f32x16 oacc[C::DBLK];
 #pragma unroll
@@ -1342,7 +1576,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
             dma4(vi, (uint32_t)i * 4u, colring_lds + (uint32_t)((t & 3) * BN * 4));
         }
     };
-    auto block_at = [&](int t) -> int { return __builtin_amdgcn_readfirstlane((int)kbl[t]); };
+    auto block_at = [&](int t) -> int { return __builtin_amdgcn_readfirstlane((int)kbl[t - tbeg]); };
     int32_t mycol = -1;
     auto col_words_of = [&](int t) {                       // what the masks of packed tile t are made of, ahead of its transfers
         const int32_t col = colring[(t & 3) * BN + lane];
@@ -1379,7 +1613,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         wait_transfers();
         masks_cols();
     }
-    kb_next = tbeg + 1 < n1 ? block_at(tbeg + 1) : 0;
+    kb_next = tbeg + 1 < n1 && tbeg + 1 < ntiles ? block_at(tbeg + 1) : 0;
     __syncthreads();
 
     for (int t = tbeg; t < ntiles; ++t) {
@@ -1388,7 +1622,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         if (t + 2 >= n1 && t + 2 < ntiles) request_cols(t + 2);
         if (next && t + 1 >= n1) { col_words_of(t + 1); issue_cols(t + 1); }
         if (next && t + 1 < n1) { issue_k(kb_next, t + 1); issue_v(kb_next, t + 1); }
-        const int kb_after = t + 2 < n1 ? (int)kbl[t + 2] : 0;
+        const int kb_after = t + 2 < n1 && t + 2 < ntiles ? (int)kbl[t + 2 - tbeg] : 0;
         const int active = halves & 3;
         if (active) process((t & 1) * C::TILE_BYTES);  // some of this wave's rows have an allowed cell here
         if (apart(active) == 0) for (int k = 0; k < 4; ++k) mask_step(k);
@@ -1398,15 +1632,15 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         __syncthreads();
     }
 
-    if (wv == 0) src.ahead(a, lane);                       // the next entry's place in the queue, under the stores below
     const float l_tot = l_run + xor32(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    entries.ahead(a, lane, wv);                            // the next entry's place in the queue, under the stores below
     // (the lane once more: addresses made of it are not to be kept in registers, or spilled, from one entry to the next)
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int rl = ln & 31, gl = ln >> 5;
-    if (parts > 1) {
-        store_part<C::DBLK>(a, (int)(info >> 16) + part, wv, ln, oacc, -mneg, l_tot);
+    if (en.in_parts(n1 + n2)) {
+        store_part<C::DBLK>(a, en.slot(), wv, ln, oacc, -mneg, l_tot);
     } else if (rows_here) {
         // A lane holds four neighbouring values of its row at a time; through LDS (32 rows of this wave in the tile
         // buffers, which nobody reads any more) they become whole rows, 1 KB a store.  (Stored as they are, 8 bytes a
@@ -1432,53 +1666,57 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
             a.lse[(int64_t)bh * a.n_hat + (posw + rl - row0)] =
                 l_tot > 0.f ? (log2f(l_tot) - mneg) * 0.69314718055994531f : -INFINITY;
     }
-  }                                                        // next item
+    }                                                      // next entry
 }
 
-template <typename T, int D>
+template <typename T, int D, bool QUEUES>
 static void launch_combine(const PrefillArgs& a, hipStream_t st, const hipEvent_t* ev) {
-    const dim3 grid(a.slots < 256 ? 2 * a.slots : 512);
-    if (a.slots == 0) return;
-    if (ev) hipExtLaunchKernelGGL((combine_kernel<T, D>), grid, dim3(256), 0, st, ev[2], ev[3], 0, a);
-    else hipLaunchKernelGGL((combine_kernel<T, D>), grid, dim3(256), 0, st, a);
+    const dim3 grid(QUEUES ? (a.slots < 256 ? 2 * a.slots : 512) : (a.grid < 128 ? 4 * a.grid : 512));
+    if (QUEUES ? a.slots == 0 : !cuts_items((int64_t)a.BH * a.nqb, a.grid, a.slots)) return;
+    if (ev) hipExtLaunchKernelGGL((combine_kernel<T, D, QUEUES>), grid, dim3(256), 0, st, ev[2], ev[3], 0, a);
+    else hipLaunchKernelGGL((combine_kernel<T, D, QUEUES>), grid, dim3(256), 0, st, a);
 }
 
 template <int D>
 static size_t prefill_bf16_smem(int tab_len) {
     return 2 * (size_t)DirectCfg<D>::TILE_BYTES + 256 * 4 + 512 * 4 + 8 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
 }
-
-template <int D>
-static hipError_t launch_prefill_bf16(const PrefillArgs& a, hipStream_t st, const hipEvent_t* ev) {
-    const size_t smem = prefill_bf16_smem<D>(a.tab_len);
-    // with events: they take the start and stop time stamps of this dispatch itself, no marker goes into the stream
-    if (ev) hipExtLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev[0], ev[1], 0, a);
-    else hipLaunchKernelGGL((prefill_bf16_kernel<D>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
-    launch_combine<bf16_t, D>(a, st, ev);
-    return hipGetLastError();
-}
-
 template <typename T, int D>
 static size_t prefill_smem_t(int tab_len) {
     using C = TileCfg<T, D>;
     return 2 * (size_t)C::K_BYTES + 2 * (size_t)C::VT_BYTES + 128 * 4 + 8 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
 }
 
-template <typename T, int D>
+template <typename T, int D, bool QUEUES>
 static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t st, const hipEvent_t* ev) {
-    const size_t smem = prefill_smem_t<T, D>(a.tab_len);
-    if (ev) hipExtLaunchKernelGGL((prefill_kernel<T, D>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev[0], ev[1], 0, a);
-    else hipLaunchKernelGGL((prefill_kernel<T, D>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
-    launch_combine<T, D>(a, st, ev);
+    // with events: they take the start and stop time stamps of this dispatch itself, no marker goes into the stream
+    if constexpr (std::is_same<T, float>::value) {
+        const size_t smem = prefill_smem_t<T, D>(a.tab_len);
+        if (ev) hipExtLaunchKernelGGL((prefill_kernel<T, D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev[0], ev[1], 0, a);
+        else hipLaunchKernelGGL((prefill_kernel<T, D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
+    } else {
+        const size_t smem = prefill_bf16_smem<D>(a.tab_len);
+        if (ev) hipExtLaunchKernelGGL((prefill_bf16_kernel<D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev[0], ev[1], 0, a);
+        else hipLaunchKernelGGL((prefill_bf16_kernel<D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
+    }
+    launch_combine<T, D, QUEUES>(a, st, ev);
     return hipGetLastError();
+}
+template <typename T, int D>
+static hipError_t launch_prefill_d(const PrefillArgs& a, hipStream_t st, const hipEvent_t* ev) {
+    return a.queue ? launch_prefill_t<T, D, true>(a, st, ev) : launch_prefill_t<T, D, false>(a, st, ev);
 }
 
 hipError_t init_prefill_kernels() {
     hipError_t e;
-    if ((e = allow_full_lds(&prefill_bf16_kernel<128>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&prefill_bf16_kernel<64>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&prefill_kernel<float, 128>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&prefill_kernel<float, 64>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_bf16_kernel<128, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_bf16_kernel<128, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_bf16_kernel<64, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_bf16_kernel<64, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_kernel<float, 128, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_kernel<float, 128, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_kernel<float, 64, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&prefill_kernel<float, 64, false>)) != hipSuccess) return e;
     return allow_full_lds(&plan_kernel);
 }
 
@@ -1496,7 +1734,7 @@ hipError_t launch_plan(const PlanArgs& a, int BH, hipStream_t st) {
 }
 
 int prefill_block_rows() { return BM; }
-int prefill_split_slots(int64_t items) { return items > SPLIT_ITEMS ? 0 : items * 12 < SPLIT_SLOTS ? (int)items * 12 : SPLIT_SLOTS; }
+
 size_t prefill_slot_bytes(int d) { return (size_t)BM * d * 4 + BM * 2 * 4; }
 
 hipError_t launch_sched(const SchedArgs& a, hipStream_t st) {
@@ -1505,10 +1743,10 @@ hipError_t launch_sched(const SchedArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st, const hipEvent_t* ev) {
-    if (dtype == 0 && d == 128) return launch_prefill_bf16<128>(a, st, ev);
-    if (dtype == 0 && d == 64) return launch_prefill_bf16<64>(a, st, ev);
-    if (dtype == 1 && d == 128) return launch_prefill_t<float, 128>(a, st, ev);
-    if (dtype == 1 && d == 64) return launch_prefill_t<float, 64>(a, st, ev);
+    if (dtype == 0 && d == 128) return launch_prefill_d<bf16_t, 128>(a, st, ev);
+    if (dtype == 0 && d == 64) return launch_prefill_d<bf16_t, 64>(a, st, ev);
+    if (dtype == 1 && d == 128) return launch_prefill_d<float, 128>(a, st, ev);
+    if (dtype == 1 && d == 64) return launch_prefill_d<float, 64>(a, st, ev);
     return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,57 @@
+"""How ls_sparse_prefill shares its work among the workgroups: in pieces of equal work up to 262144 tiles of 64 keys (counted
+as if every head were dense), by work queues above.  One call over a batch that lies above that line is compared with calls
+over its parts, which lie below: the same cells summed in another order of tiles and parts."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_13681_amd import inputs
+
+LINE = 262144
+
+
+def _tiles(B, Hq, n, n_hat):
+    return B * Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128) * ((n + 63) // 64)
+
+
+def _lists(rng, B, H, n):
+    """Heads of very unequal work: every diagonal; none; a few; the newest alone with many columns; random ones."""
+    v, s = [], []
+    for i in range(B * H):
+        kind = i % 5
+        s.append(np.arange(n) if kind == 0 else np.zeros(0, int) if kind == 1 else np.unique(rng.integers(0, n, 3)) if kind == 2
+                 else np.zeros(1, int) if kind == 3 else np.flatnonzero(rng.random(n) < rng.choice([0.01, 0.2])))
+        v.append(np.zeros(0, int) if kind == 0 and i % 2 else np.flatnonzero(rng.random(n) < (0.3 if kind == 3 else 0.02)))
+    def pack(x):
+        out = np.zeros((B * H, n), np.int32)
+        for i, e in enumerate(x):
+            out[i, :len(e)] = e
+        return out.reshape(B, H, n), np.array([len(e) for e in x], np.int32).reshape(B, H)
+    vi, vc = pack(v)
+    si, sc = pack(s)
+    return vi, vc, si, sc
+
+
+# the turn is the end of the context or all of it; n and n_hat have no relation to any tile size
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d,dtype", [
+    (11, 16, 4, 3999, 3000, 128, "bf16"), (11, 16, 2, 3999, 3999, 64, "bf16"), (5, 4, 1, 20001, 6500, 128, "bf16"),
+    (11, 16, 4, 3999, 3000, 64, "f32"), (11, 16, 4, 4003, 2900, 128, "f32")])
+def test_queues_and_pieces_agree(B, Hq, Hkv, n, n_hat, d, dtype):
+    from tests.gpu_util import Pipeline, dev_lists
+    print(f"queues and pieces B={B} Hq={Hq} n={n} n_hat={n_hat} d={d} {dtype}", flush=True)
+    cut = B // 2 + 1
+    assert _tiles(B, Hq, n, n_hat) > LINE >= _tiles(cut, Hq, n, n_hat)
+    q, k, v = inputs.make_plain(B, Hq, Hkv, n, n_hat, d, dtype=dtype, seed=n, q_scale=1.5)
+    lists = _lists(np.random.default_rng(n), B, Hq, n)
+    out, lse = Pipeline(q, k, v, 1, dtype).prefill(dev_lists(*lists), sentinel=True)
+    # In bf16 each side rounds every probability (2^-9 relative, against references that differ) and the result: 4 * 2^-9 of
+    # the largest value.  fp32: sums of at most n terms in another order, sqrt(n) * 2^-24 * 8 and room for exp's argument.
+    tol = (4 * 2.0 ** -9 if dtype == "bf16" else 1e-5) * float(np.abs(v).max())
+    for b in (slice(0, cut), slice(cut, B)):
+        part, plse = Pipeline(q[b], k[b], v[b], 1, dtype).prefill(dev_lists(*(x[b] for x in lists)), sentinel=True)
+        assert not torch.isnan(out[b]).any() and not torch.isnan(part).any()
+        assert (out[b].float() - part.float()).abs().max().item() <= tol
+        some = torch.isfinite(plse)
+        assert torch.equal(torch.isfinite(lse[b]), some)
+        assert (lse[b][some] - plse[some]).abs().max().item() <= 1e-4
