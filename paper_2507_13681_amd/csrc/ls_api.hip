@@ -151,6 +151,8 @@ size_t ws_score(const ls_shape* s, bool lines) {
     }
     return b;
 }
+// (The selection itself takes 8 bytes per head and line beside its heads' first lines; the workspace that a shape is stated to
+// need has 24, as it always had.)
 size_t ws_select(const ls_shape* s) {
     const size_t BH = (size_t)s->B * s->Hq;
     return 3 * up(2 * BH * (size_t)s->n * 4) + 2 * up(2 * BH * ls::SELECT_HEAD_LINES * 4);
@@ -302,8 +304,7 @@ int ls_select_exact(ls_ctx* c, const ls_shape* s, float alpha, const float* a_wi
     a.vert = vert; a.slash = slash; a.vmax = vert; a.smax = slash; a.total = total;   // the maxima are not used: any readable array
     Bump bp{c->ws, c->ws_bytes, 0};
     const size_t cnt = 2 * (size_t)a.BH * (size_t)a.n;
-    a.skey0 = bp.take<uint32_t>(cnt);
-    a.sidx0 = bp.take<int32_t>(cnt); a.sidx1 = bp.take<int32_t>(cnt);
+    a.sidx = bp.take<int32_t>(cnt);
     a.head_w = bp.take<float>(2 * (size_t)a.BH * ls::SELECT_HEAD_LINES); a.head_m = bp.take<float>(2 * (size_t)a.BH * ls::SELECT_HEAD_LINES);
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_select_exact: workspace of %zu bytes is too small", c->ws_bytes);
     a.v_idx = v_idx; a.v_cnt = v_cnt; a.s_idx = s_idx; a.s_cnt = s_cnt; a.cap_v = cap_v; a.cap_s = cap_s;
@@ -330,8 +331,7 @@ int ls_select(ls_ctx* c, const ls_shape* s, float alpha,
     a.vert = vert; a.slash = slash; a.vmax = vmax; a.smax = smax; a.total = total;
     Bump bp{c->ws, c->ws_bytes, 0};
     const size_t cnt = 2 * (size_t)a.BH * (size_t)a.n;
-    a.skey0 = bp.take<uint32_t>(cnt);
-    a.sidx0 = bp.take<int32_t>(cnt); a.sidx1 = bp.take<int32_t>(cnt);
+    a.sidx = bp.take<int32_t>(cnt);
     a.head_w = bp.take<float>(2 * (size_t)a.BH * ls::SELECT_HEAD_LINES); a.head_m = bp.take<float>(2 * (size_t)a.BH * ls::SELECT_HEAD_LINES);
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_select: workspace of %zu bytes is too small", c->ws_bytes);
     a.v_idx = v_idx; a.v_cnt = v_cnt; a.s_idx = s_idx; a.s_cnt = s_cnt; a.cap_v = cap_v; a.cap_s = cap_s;

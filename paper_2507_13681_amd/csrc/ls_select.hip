@@ -1,14 +1,8 @@
 // Per-head line selection (Alg. 2 from Desc_Sort on) and top-B retention (Alg. 3), gfx950.
 //
-//   sort_seg_kernel / sort_merge_kernel
-//                 Desc_Sort: the n line weights of a list in descending order, equal weights in
-//                 ascending index order.  Segments of 1024 to 8192 elements are sorted inside LDS by a stable
-//                 LSD radix sort (4 x 8 bits): each of the 16 waves owns a contiguous slice, counts its
-//                 digits in its own histogram, and scatters its slice in order (ranks among equal
-//                 digits from wave ballots and the wave's running counters; no atomics decide an
-//                 output position).  The sorted segments are then merged by rank: every element's
-//                 final position is its position in its segment plus, by bisection, the number of
-//                 elements of the other segments that precede it.
+//   order_kernel  Desc_Sort: the n line weights of a list in descending order, equal weights in ascending index order.
+//                 The weights' range is cut into ranges of about as many lines each, a workgroup per range: it picks its
+//                 lines out of the list and ranks them inside LDS, so nothing is left to merge.
 //   walk_kernel   one workgroup of six waves per head: the greedy loop of Alg. 2 in binary32 with the operands
 //                 and operation order of the definition.  One wave decides runs of up to 512 picks from one
 //                 list with its lanes, one accumulates the running sum pick by pick behind it and finds
@@ -38,11 +32,15 @@ __device__ __forceinline__ float key_to_float(uint32_t key) {
 
 constexpr int WALK_BLK = 1024;                 // entries of a sorted list the walk stages at a time
 static_assert(WALK_BLK == SELECT_HEAD_LINES, "the merge writes the walk's first block in order");
-constexpr int SORT_THREADS = 1024;
-constexpr int SORT_WAVES = 16;
-constexpr int SORT_SEG_MAX = 8192;             // most elements one workgroup sorts inside LDS
-constexpr int SORT_SEG_MIN = 1024;
-constexpr size_t sort_lds_bytes(int seg) { return (size_t)2 * seg * 4 + (size_t)2 * seg * 2 + 2 * SORT_WAVES * 256 * 4 + 256 * 4; }
+constexpr int ORDER_THREADS = 1024;
+constexpr int ORDER_WAVES = 16;
+constexpr int ORDER_CHUNKS = 10;               // most chunks of 64 lines a wave sorts: 10240 lines a workgroup
+constexpr int ORDER_ONE = 4096;                // longest list that one workgroup puts in order
+constexpr int ORDER_FINE = 16384;              // fine bins
+constexpr int ORDER_FULL = 32;                 // lines of the fullest bin that are still ranked against each other
+constexpr int ORDER_FRONT = ORDER_FINE * 2 + 16 + 1024 * 4;
+static_assert(ORDER_FINE * 2 >= ORDER_WAVES * 1024 * 2 && ORDER_FINE >= 1024 * ORDER_CHUNKS, "room for the waves' digit counters, a bin per line");
+constexpr size_t order_lds_bytes(int cap) { return (size_t)ORDER_FRONT + (size_t)cap * 10; }
 
 // sum over the lanes to the left and this one
 __device__ __forceinline__ uint32_t lanes_upto(uint32_t x) {
@@ -56,257 +54,396 @@ __device__ __forceinline__ uint32_t lanes_upto(uint32_t x) {
     return (uint32_t)s;
 }
 
-// grid (segments, 2, BH): list 0 = diagonals (slash), 1 = columns (vert).  Sorts elements
-// [seg * SEG, +SEG) of one list entirely in LDS and writes the sorted keys (skey0) and their
-// line indices (sidx0) back to the same range; a list of one segment is finished here (sidx1, head_w, head_m).
-// What bounds it: vector instructions (the ballots of the ranks) where a wave has eight chunks to scatter, the five
-// barriers and the round trips between them where it has one or two.  So a pass reads the sixteen waves' counts of a
-// digit at once, scans the digits by lane shifts, and clears the other pass's counters on the side; slots past the end
-// of the list take no part.  64 lists of 32768 lines 31 -> 27 us, of 12347 24 -> 15, eight of 1024 13 -> 7.
-template <int SEG>
-__global__ __launch_bounds__(SORT_THREADS) void sort_seg_kernel(SelectArgs a) {
-    constexpr int SLICE = SEG / SORT_WAVES;
-    extern __shared__ __align__(16) unsigned char sort_lds[];
-    uint32_t* kb0 = reinterpret_cast<uint32_t*>(sort_lds);
-    uint32_t* kb1 = kb0 + SEG;
-    uint16_t* ib0 = reinterpret_cast<uint16_t*>(kb1 + SEG);
-    uint16_t* ib1 = ib0 + SEG;
-    uint32_t (*hists)[SORT_WAVES][256] = reinterpret_cast<uint32_t (*)[SORT_WAVES][256]>(ib1 + SEG);     // [2], by pass parity
-    uint32_t* dbase = &hists[1][SORT_WAVES - 1][0] + 256;
-    const int seg = blockIdx.x, list = blockIdx.y, bh = blockIdx.z;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int64_t n = a.n;
-    const int64_t base0 = (int64_t)seg * SEG;
-    const int cnt = (int)(n - base0 < SEG ? n - base0 : SEG);
-    const float* src = (list == 0 ? a.slash : a.vert) + (int64_t)bh * n + base0;
-    const int64_t out0 = ((int64_t)list * a.BH + bh) * n + base0;
-    // slots past the end of the list take no part: neither counted nor moved (as largest keys, 64 atomics of a wave on one
-    // counter took turns for every chunk of them)
-    const int lo = wv * SLICE;
-    uint32_t keys[SLICE / 64]; uint16_t idxs[SLICE / 64];
-#pragma unroll
-    for (int c = 0; c < SLICE / 64; ++c) {
-        const int i = lo + 64 * c + lane;
-        keys[c] = desc_key(src[i < cnt ? i : cnt - 1]);    // (no condition around the conversion: it would wait for each load)
-        idxs[c] = (uint16_t)i;
-    }
-    for (int i = tid; i < SORT_WAVES * 256; i += SORT_THREADS) (&hists[0][0][0])[i] = 0u;
+// smallest / largest of the wave's, in lane 63
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp_min(uint32_t x) { const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, ROWS, 0xF, false); return o < x ? o : x; }
+__device__ __forceinline__ uint32_t lanes_min(uint32_t x) {
+    x = dpp_min<0x111, 0xF>(x); x = dpp_min<0x112, 0xF>(x); x = dpp_min<0x114, 0xF>(x); x = dpp_min<0x118, 0xF>(x);       // row_shr:1, 2, 4, 8
+    x = dpp_min<0x142, 0xA>(x);                            // row_bcast15 into rows 1 and 3
+    return dpp_min<0x143, 0xC>(x);                         // row_bcast31 into rows 2 and 3
+}
+__device__ __forceinline__ uint32_t lanes_max(uint32_t x) { return ~lanes_min(~x); }
+// digits of 10 bits at most that hold a number below 2^width
+__device__ __forceinline__ int width_of(uint32_t x) { return x == 0u ? 0 : 32 - __builtin_clz(x); }
+
+// What the workgroup keeps beside the keys: `red` for sums over the waves (two rounds that follow each other use different halves).
+struct OrderSync { uint32_t red[2][ORDER_WAVES], bin[2], rest[2]; };
+
+// Sum of `x` over the threads before this one, and over all of them.  One barrier; `red` must not be in use.
+__device__ __forceinline__ uint32_t order_scan(uint32_t x, uint32_t* red, int lane, int wv, uint32_t& total) {
+    const uint32_t upto = lanes_upto(x);
+    if (lane == 63) red[wv] = upto;
     __syncthreads();
-    // (PART: the segment is not full.  Without predicates the chunks of a full one overlap: 28 instead of 31 us at 32768 lines)
-    auto passes = [&](auto PART) {
-    constexpr bool part = decltype(PART)::value;
-    auto here = [&](int c) { return !part || lo + 64 * c + lane < cnt; };
+    uint32_t before = 0u, all = 0u;
 #pragma unroll
-    for (int pass = 0; pass < 4; ++pass) {
-        const int shift = 8 * pass;
-        uint32_t (*hist)[256] = hists[pass & 1];
-        uint32_t* kout = (pass & 1) ? kb0 : kb1;
-        uint16_t* iout = (pass & 1) ? ib0 : ib1;
-        if (pass > 0) {                                    // this wave's slice
-            const uint32_t* kin = (pass & 1) ? kb1 : kb0;
-            const uint16_t* iin = (pass & 1) ? ib1 : ib0;
-#pragma unroll
-            for (int c = 0; c < SLICE / 64; ++c) { keys[c] = kin[lo + 64 * c + lane]; idxs[c] = iin[lo + 64 * c + lane]; }
-        }
-        if (pass < 3) {
-#pragma unroll
-            for (int c = 0; c < SLICE / 64; ++c) if (here(c)) atomicAdd(&hist[wv][(keys[c] >> shift) & 255u], 1u);
-        } else {
-            // the top byte (sign and upper exponent bits) takes few values, and 64 atomics on one counter take turns:
-            // three times over, the lanes that share the digit of the first lane not yet counted add once together;
-            // what is left adds one by one
-#pragma unroll
-            for (int c = 0; c < SLICE / 64; ++c) {
-                const uint32_t dg = keys[c] >> 24;
-                uint64_t todo = part ? __ballot(here(c)) : ~0ull;
-#pragma unroll
-                for (int round = 0; round < 3; ++round) {
-                    if (todo == 0ull) break;
-                    const int first = __ffsll((unsigned long long)todo) - 1;
-                    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)dg, first);
-                    const uint64_t same = __ballot(dg == d0) & todo;
-                    if (lane == first) atomicAdd(&hist[wv][d0], (uint32_t)__popcll(same));
-                    todo &= ~same;
-                }
-                if ((todo >> lane) & 1ull) atomicAdd(&hist[wv][dg], 1u);
-            }
-        }
-        __syncthreads();
-        // exclusive offsets in (digit, wave) order
-        uint32_t before[SORT_WAVES], total = 0u;
-        if (tid < 256) {
-            uint32_t t[SORT_WAVES];
-#pragma unroll
-            for (int w = 0; w < SORT_WAVES; ++w) t[w] = hist[w][tid];
-#pragma unroll
-            for (int w = 0; w < SORT_WAVES; ++w) { before[w] = total; total += t[w]; }
-            total = lanes_upto(total);                     // of this wave's 64 digits
-            if (lane == 63) dbase[wv] = total;
-        } else if (pass < 3) {                             // the other twelve waves clear the next pass's counters
-            uint32_t* next = &hists[(pass + 1) & 1][0][0];
-            for (int i = tid - 256; i < SORT_WAVES * 256; i += SORT_THREADS - 256) next[i] = 0u;
-        }
-        __syncthreads();
-        if (tid < 256) {
-            uint32_t base = total - (before[SORT_WAVES - 1] + hist[SORT_WAVES - 1][tid]);
-#pragma unroll
-            for (int w = 0; w < 3; ++w) base += w < wv ? dbase[w] : 0u;
-#pragma unroll
-            for (int w = 0; w < SORT_WAVES; ++w) hist[w][tid] = base + before[w];
-        }
-        __syncthreads();
-        // in-order scatter of this wave's slice: inside a 64-element chunk the rank among equal digits
-        // comes from wave ballots, across chunks from the wave's running counters
-        // (the wave's counters are read and written with relaxed atomics: plain LDS accesses that the compiler keeps
-        // in program order around the wave barriers; a volatile pointer would turn them into flat accesses)
-        uint32_t* myh = hist[wv];
-#pragma unroll
-        for (int c = 0; c < SLICE / 64; ++c) {
-            const uint32_t key = keys[c];
-            const uint16_t idx = idxs[c];
-            const uint32_t dg = (key >> shift) & 255u;
-            // lanes whose digit differs from mine in some bit: bit b of the lanes' digits as a wave mask, against
-            // my own bit b spread over a word; diff | (ballot ^ mine) is one instruction (truth table 0xF6)
-            const uint64_t none = part ? ~__ballot(here(c)) : 0ull;
-            uint32_t diff_lo = (uint32_t)none, diff_hi = (uint32_t)(none >> 32);
-#pragma unroll
-            for (int bit = 0; bit < 8; ++bit) {
-                const uint32_t m = (uint32_t)((int32_t)(dg << (31 - bit)) >> 31);  // 0 or ~0
-                const uint64_t bal = __ballot(m != 0u);
-                diff_lo = __builtin_amdgcn_bitop3_b32(diff_lo, (uint32_t)bal, m, 0xF6);
-                diff_hi = __builtin_amdgcn_bitop3_b32(diff_hi, (uint32_t)(bal >> 32), m, 0xF6);
-            }
-            const uint64_t peers = ~(((uint64_t)diff_hi << 32) | diff_lo);
-            const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
-            const uint32_t pos = __atomic_load_n(&myh[dg], __ATOMIC_RELAXED) + rank;
-            __builtin_amdgcn_wave_barrier();
-            if (here(c)) { kout[pos] = key; iout[pos] = idx; }
-            if (here(c) && rank == 0u) __atomic_store_n(&myh[dg], pos + (uint32_t)__popcll(peers), __ATOMIC_RELAXED);
-            __builtin_amdgcn_wave_barrier();
-        }
-        __syncthreads();                                   // every wave is done with the counters and the input buffer
-    }
-    };
-    if (cnt == SEG) passes(std::false_type{}); else passes(std::true_type{});
-    // four passes: the result sits in buffer 0
-    if (gridDim.x == 1) {
-        const float* mx = (list == 0 ? a.smax : a.vmax) + (int64_t)bh * n;
-        const int64_t head = ((int64_t)list * a.BH + bh) * WALK_BLK;
-        for (int i = tid; i < cnt; i += SORT_THREADS) {
-            const int idx = ib0[i];
-            a.sidx1[out0 + i] = idx;
-            if (i < WALK_BLK) { a.head_w[head + i] = key_to_float(kb0[i]); a.head_m[head + i] = mx[idx]; }
-        }
-        return;
-    }
-    for (int i = tid; i < cnt; i += SORT_THREADS) {
-        a.skey0[out0 + i] = kb0[i];
-        a.sidx0[out0 + i] = (int32_t)(base0 + ib0[i]);
-    }
+    for (int w = 0; w < ORDER_WAVES; ++w) { const uint32_t t = red[w]; before += w < wv ? t : 0u; all += t; }
+    total = all;
+    return before + upto - x;
 }
 
-// grid (segments, 2, BH).  Final position of an element of segment q = its position inside q + the
-// number of elements of every other segment that go before it: smaller key, or equal key in a segment
-// of smaller line indices (the order stays stable).  The other segments' sorted keys are staged in
-// LDS one at a time (two buffers: the next segment is loaded while the current one is searched) and
-// searched by bisection.  Writes the line indices in sorted order (sidx1): a scattered store per line, which is
-// why the weights and maxima are not written beside them; the walk fetches those through the indices, and only
-// for the part of the order it gets to.
-// Dynamic LDS: 2 * SEG keys.
-template <int SEG>
-__global__ __launch_bounds__(SORT_THREADS) void sort_merge_kernel(SelectArgs a) {
-    constexpr int PER = SEG / SORT_THREADS;
-    extern __shared__ __align__(16) unsigned char merge_lds[];
-    uint32_t (*other)[SEG] = reinterpret_cast<uint32_t (*)[SEG]>(merge_lds);
-    const int seg = blockIdx.x, list = blockIdx.y, bh = blockIdx.z;
-    const int tid = threadIdx.x;
-    const int64_t n = a.n;
-    const int nseg = (int)((n + SEG - 1) / SEG);
-    const int64_t lbase = ((int64_t)list * a.BH + bh) * n;
-    const int64_t base0 = (int64_t)seg * SEG;
-    const int cnt = (int)(n - base0 < SEG ? n - base0 : SEG);
-    uint32_t key[PER], rank[PER], nxt[PER];
-    int32_t idx[PER];
-    auto fetch = [&](int q) {                               // keys of segment q, padded with the largest key
-        const int64_t qb = (int64_t)q * SEG;
-        const int qc = (int)(n - qb < SEG ? n - qb : SEG);
+// The keys that bound range `b` of `nb`: those of rank b S / nb and (b + 1) S / nb among S = 2048 samples, two a thread, to 20
+// bits of the samples' span.  The same numbers in every workgroup of the list.  hist: 2 * 1024 words of LDS.
+__device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], int b, int nb, uint32_t* hist, OrderSync& sync, uint32_t& k0, uint32_t& k1) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    constexpr int PER = 2, S = PER * ORDER_THREADS;
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+    hist[tid] = 0u; hist[1024 + tid] = 0u;
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int i = tid + j * SORT_THREADS;
-            nxt[j] = a.skey0[lbase + qb + (i < qc ? i : qc - 1)];
-        }
+    for (int j = 0; j < PER; ++j) { lo = key[j] < lo ? key[j] : lo; hi = key[j] > hi ? key[j] : hi; }
+    lo = lanes_min(lo); hi = lanes_max(hi);
+    if (lane == 63) { sync.red[0][wv] = lo; sync.red[1][wv] = hi; }
+    __syncthreads();
+    lo = sync.red[0][0]; hi = sync.red[1][0];
 #pragma unroll
-        for (int j = 0; j < PER; ++j) nxt[j] = tid + j * SORT_THREADS < qc ? nxt[j] : 0xFFFFFFFFu;
-    };
-    auto stage = [&](int buf) {
+    for (int w = 1; w < ORDER_WAVES; ++w) { const uint32_t t = sync.red[0][w], u = sync.red[1][w]; lo = t < lo ? t : lo; hi = u > hi ? u : hi; }
+    const int width = width_of(hi - lo), sh = width > 20 ? width - 20 : 0;
+    uint32_t at[PER];
 #pragma unroll
-        for (int j = 0; j < PER; ++j) other[buf][tid + j * SORT_THREADS] = nxt[j];
-    };
-    int q = seg == 0 ? 1 : 0;
-    if (q < nseg) fetch(q);
+    for (int j = 0; j < PER; ++j) { at[j] = (key[j] - lo) >> sh; atomicAdd(&hist[at[j] >> 10], 1u); }
+    __syncthreads();
+    // bins of the two ranks, then the bins inside those (of both at once, in the halves of a word)
+    const uint32_t t0 = (uint32_t)(b * S / nb), t1 = (uint32_t)((b + 1) * S / nb);
+    uint32_t all;
+    uint32_t v = hist[tid], e = order_scan(v, sync.red[0], lane, wv, all);
+    if (t0 >= e && t0 < e + v) { sync.bin[0] = (uint32_t)tid; sync.rest[0] = t0 - e; }
+    if (t1 >= e && t1 < e + v) { sync.bin[1] = (uint32_t)tid; sync.rest[1] = t1 - e; }
+    if (b == nb - 1 && tid == 0) { sync.bin[1] = 1023u; sync.rest[1] = 0u; }             // (no bound: not looked at)
+    __syncthreads();
+    const uint32_t bin0 = sync.bin[0], bin1 = sync.bin[1], rest0 = sync.rest[0], rest1 = sync.rest[1];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int p = tid + j * SORT_THREADS;
-        key[j] = a.skey0[lbase + base0 + (p < cnt ? p : cnt - 1)];
-        idx[j] = a.sidx0[lbase + base0 + (p < cnt ? p : cnt - 1)];
-        rank[j] = (uint32_t)p;
+        const uint32_t add = ((at[j] >> 10) == bin0 ? 1u : 0u) | ((at[j] >> 10) == bin1 ? 0x10000u : 0u);
+        if (add) atomicAdd(&hist[1024 + (at[j] & 1023u)], add);
     }
-    if (q < nseg) stage(0);
     __syncthreads();
-    int buf = 0;
-    while (q < nseg) {
-        const int q2 = q + 1 == seg ? q + 2 : q + 1;
-        if (q2 < nseg) fetch(q2);
-        const int64_t qb = (int64_t)q * SEG;
-        const int qc = (int)(n - qb < SEG ? n - qb : SEG);
-        // number of i in [0, qc) with other[i] before key: other[i] < key, or <= key when the other segment is an
-        // earlier one (its equal keys go first).  The segment is padded to its full power-of-two length with the
-        // largest key, so the search has a fixed number of steps and the PER searches of a thread advance together:
-        // their LDS reads are in flight at the same time (plain 32-bit compares: a 64-bit "key + 1" compare made the
-        // compiler funnel all reads through one register pair, one wait each).
-        // (positions are kept as LDS byte addresses: a probe then needs no address arithmetic beyond the
-        // instruction's own offset)
-        typedef const __attribute__((address_space(3))) uint32_t* lds_u32;
-        const uint32_t base = (uint32_t)(uintptr_t)(lds_u32)other[buf];
-        uint32_t la[PER];
+    v = hist[1024 + tid]; e = order_scan(v, sync.red[1], lane, wv, all);
+    if (rest0 >= (e & 0xFFFFu) && rest0 < (e & 0xFFFFu) + (v & 0xFFFFu)) sync.bin[0] = (uint32_t)tid;
+    if (rest1 >= (e >> 16) && rest1 < (e >> 16) + (v >> 16)) sync.bin[1] = (uint32_t)tid;
+    __syncthreads();
+    k0 = lo + ((bin0 << 10 | sync.bin[0]) << sh);
+    k1 = lo + ((bin1 << 10 | sync.bin[1]) << sh);
+}
+
+// Desc_Sort.  grid (lists, nb); list 2 bh + 0 = diagonals (slash), + 1 = columns (vert) of a head.  (Workgroups of a list are
+// `lists` apart: with a multiple of eight lists in one XCD, whose L2 then fetches the list once.)
+// Workgroup b puts the b-th of nb ranges of weights in order (WHOLE: the list, of up to 1024 MAXC lines).  It
+//   - finds the range's bounds from 2048 samples of the list, so that each range has about as many lines;
+//   - counts the range's lines and those before it, and takes the former into LDS, in index order;
+//   - spreads them over bins, about one line each (below), and ranks the few lines of a bin against each other, by weight
+//     and then by index: no pass over digits, no chain of ranks from one 64 lines to the next;
+//   - writes their indices (sidx) where they belong, one behind the other; the first WALK_BLK lines of the order get their
+//     weight and maximum written as well (head_w, head_m), so that the walk can start without a second round trip.
+// A range of more than `cap` lines is halved until it fits, one of equal weights is written as it comes.  Lines that crowd
+// into a bin all the same (many equal weights, or one far away from all others) are sorted digit by digit, stably.
+//
+// What bounds it: latencies, one workgroup of sixteen waves per CU: 32768 lines, cycles of one of 4 workgroups: bounds 10000, count
+// 7000, lines into LDS 5700, their span 9500 (the barrier waits for the wave with most of them), bins 10000, ranks 8000,
+// results 11000.  Beyond 65536 lines it is the look through the whole list, which every range repeats.  Against segments
+// sorted by four passes over digits and merged by bisection, two launches, ls_select of 32 heads, us: 4096 lines 26.8 -> 25.0,
+// 12347 45.0 -> 40.2, 24000 76.0 -> 62.6, 32768 86.5 -> 71.5, 65536 176 -> 140, 131072 455 -> 388; 256 heads of 16384 162.5 -> 149.
+// Weights that crowd pay for both ways: all but ten of 32768 lines within 2^12 numbers 76 -> 149, two thirds of one weight 191 -> 228.
+template <int MAXC, bool WHOLE>
+__global__ __launch_bounds__(ORDER_THREADS) void order_kernel(SelectArgs a, int nb, int cap) {
+    constexpr int FINE = MAXC == ORDER_CHUNKS ? ORDER_FINE : 2048 * MAXC, PT = FINE / 2 / ORDER_THREADS;
+    extern __shared__ __align__(16) unsigned char order_lds[];
+    __shared__ OrderSync sync;
+    uint16_t (*hist)[1024] = reinterpret_cast<uint16_t (*)[1024]>(order_lds);            // [16 waves]
+    uint16_t* fine = reinterpret_cast<uint16_t*>(order_lds);                             // [ORDER_FINE + 1], in the same place
+    uint32_t* words = reinterpret_cast<uint32_t*>(order_lds);                            // either's counters in pairs
+    uint32_t* coarse = reinterpret_cast<uint32_t*>(order_lds + ORDER_FINE * 2 + 16);     // [1024]
+    uint32_t* keys = reinterpret_cast<uint32_t*>(order_lds + ORDER_FRONT);               // [cap]
+    int32_t* line = reinterpret_cast<int32_t*>(keys + cap);                              // [cap] the lines, in index order
+    uint16_t* ids = reinterpret_cast<uint16_t*>(line + cap);                             // [cap] places in `line`, in the order so far
+    const int list = blockIdx.x & 1, bh = blockIdx.x >> 1, b = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = (int)a.n;
+    const float* src = (list == 0 ? a.slash : a.vert) + (int64_t)bh * n;
+    const float* mx = (list == 0 ? a.smax : a.vmax) + (int64_t)bh * n;
+    int32_t* out = a.sidx + ((int64_t)list * a.BH + bh) * n;
+    const int64_t head = ((int64_t)list * a.BH + bh) * WALK_BLK;
+    const int per = (n + ORDER_THREADS - 1) / ORDER_THREADS * 64;
+    const int w0 = wv * per < n ? wv * per : n, w1 = w0 + per < n ? w0 + per : n;         // this wave's lines
+    // f(line, key, whether there is such a line) for the wave's lines, 64 at a time
+    auto read = [&](auto f) {
+        for (int i0 = w0; i0 < w1; i0 += 64 * 8) {
+            float x[8];
 #pragma unroll
-        for (int j = 0; j < PER; ++j) la[j] = base;
-        auto search = [&](auto earlier) {
-            constexpr bool le = decltype(earlier)::value;
+            for (int j = 0; j < 8; ++j) { const int i = i0 + 64 * j + lane; x[j] = src[i < n ? i : n - 1]; }
 #pragma unroll
-            for (int step = SEG / 2; step >= 1; step >>= 1) {
-                uint32_t o[PER];
+            for (int j = 0; j < 8; ++j) { const int i = i0 + 64 * j + lane; f(i, desc_key(x[j]), i < w1); }
+        }
+    };
+    uint32_t lo = 0u, end = 0xFFFFFFFFu;
+    if (!WHOLE && nb > 1) {
+        uint32_t sample[2], k0, k1;
 #pragma unroll
-                for (int j = 0; j < PER; ++j) o[j] = *(lds_u32)(uintptr_t)(la[j] + 4u * (uint32_t)(step - 1));
-#pragma unroll
-                for (int j = 0; j < PER; ++j) if (le ? o[j] <= key[j] : o[j] < key[j]) la[j] += 4u * (uint32_t)step;
-            }
-            uint32_t o[PER];
-#pragma unroll
-            for (int j = 0; j < PER; ++j) o[j] = *(lds_u32)(uintptr_t)la[j];
-#pragma unroll
-            for (int j = 0; j < PER; ++j) {
-                const int r = (int)((la[j] - base) >> 2) + ((le ? o[j] <= key[j] : o[j] < key[j]) ? 1 : 0);
-                rank[j] += (uint32_t)(r < qc ? r : qc);
-            }
-        };
-        if (q < seg) search(std::true_type{}); else search(std::false_type{});
-        if (q2 < nseg) stage(buf ^ 1);
-        __syncthreads();                                   // this buffer is free again, the other one is filled
-        buf ^= 1;
-        q = q2;
+        for (int j = 0; j < 2; ++j) {                      // somewhere in the i-th 2048th of the list, so that no period of it is met
+            const int i = tid + j * ORDER_THREADS, len = n / (2 * ORDER_THREADS);
+            sample[j] = desc_key(src[(int)((int64_t)i * n / (2 * ORDER_THREADS)) + (int)((((uint32_t)i * 0x9E3779B1u) >> 16) * (uint32_t)len >> 16)]);
+        }
+        order_bounds(sample, b, nb, reinterpret_cast<uint32_t*>(order_lds), sync, k0, k1);
+        if (b > 0) lo = k0;
+        if (b < nb - 1) {
+            if (k1 <= lo) return;                          // (all of them: the bounds are the same for every thread)
+            end = k1 - 1u;
+        }
     }
-    // (stores only, the indices are there; a condition around load and store would wait for each of them in turn)
+    auto put = [&](int at, int i, uint32_t k) {            // line i is the `at`-th of the order
+        out[at] = i;
+        if (at < WALK_BLK) { a.head_w[head + at] = key_to_float(k); a.head_m[head + at] = mx[i]; }
+    };
+    uint32_t hi = end;
+    int base = nb > 1 ? -1 : 0;                            // lines before the range
+    for (;;) {
+        const uint32_t span = hi - lo;
+        int before = w0, m = n;                            // lines of the range in the waves before, and in all (a list in one range: all lines)
+        if (!WHOLE && nb > 1) {
+            uint32_t here = 0u, below = 0u;
+            auto count = [&](uint32_t k, bool any) { here += any && k - lo <= span ? 1u : 0u; below += any && k < lo ? 1u : 0u; };
+            {                                              // (their order does not matter here: 16 bytes a lane)
+                typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+                int i = w0 + 4 * lane;
+                for (; i - 4 * lane + 1024 <= w1; i += 1024) {
+                    f32x4u x[4];
 #pragma unroll
-    for (int j = 0; j < PER; ++j)
-        if (tid + j * SORT_THREADS < cnt) a.sidx1[lbase + rank[j]] = idx[j];
-    // the first WALK_BLK lines of the order also get their weight and maximum written, so that the walk can start without
-    // a second round trip through the indices; they are among the first WALK_BLK of their segments
-    static_assert(WALK_BLK <= SORT_THREADS, "j = 0");
-    if (tid < cnt && rank[0] < (uint32_t)WALK_BLK) {
-        const int64_t head = ((int64_t)list * a.BH + bh) * WALK_BLK + rank[0];
-        a.head_w[head] = key_to_float(key[0]);
-        a.head_m[head] = ((list == 0 ? a.smax : a.vmax) + (int64_t)bh * n)[idx[0]];
+                    for (int j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const f32x4u*>(src + i + 256 * j);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) count(desc_key(x[j][e]), true);
+                }
+                for (i += lane - 4 * lane; i - lane < w1; i += 64 * 4) {
+                    float x[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) x[j] = src[i + 64 * j < n ? i + 64 * j : n - 1];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) count(desc_key(x[j]), i + 64 * j < w1);
+                }
+            }
+            here = lanes_upto(here); below = lanes_upto(below);
+            __syncthreads();                               // `red` and the last range's lines are free again
+            if (lane == 63) { sync.red[0][wv] = here; sync.red[1][wv] = below; }
+            __syncthreads();
+            int ahead = 0;
+            before = 0; m = 0;
+#pragma unroll
+            for (int w = 0; w < ORDER_WAVES; ++w) { const int t = (int)sync.red[0][w]; before += w < wv ? t : 0; m += t; ahead += (int)sync.red[1][w]; }
+            if (base < 0) base = ahead;
+            m = __builtin_amdgcn_readfirstlane(m);
+        }
+        if (!WHOLE && m > cap && lo < hi) {                // the lower half of the span that its weights have (nothing lies before it)
+            uint32_t least = 0xFFFFFFFFu, most = 0u;
+            read([&](int, uint32_t k, bool any) {
+                const bool in = any && k - lo <= span;
+                least = in && k < least ? k : least; most = in && k > most ? k : most;
+            });
+            least = lanes_min(least); most = lanes_max(most);
+            __syncthreads();                               // `red` has been read
+            if (lane == 63) { sync.red[0][wv] = least; sync.red[1][wv] = most; }
+            __syncthreads();
+            least = sync.red[0][0]; most = sync.red[1][0];
+#pragma unroll
+            for (int w = 1; w < ORDER_WAVES; ++w) { const uint32_t t = sync.red[0][w], u = sync.red[1][w]; least = t < least ? t : least; most = u > most ? u : most; }
+            lo = least; hi = least + (most - least) / 2;
+            continue;
+        }
+        const uint64_t left = (1ull << lane) - 1ull;
+        if (!WHOLE && m > cap) {                           // equal weights: the order is there
+            read([&](int i, uint32_t k, bool any) {
+                const bool in = any && k - lo <= span;
+                const uint64_t who = __ballot(in);
+                if (in) put(base + before + __popcll(who & left), i, k);
+                before += __popcll(who);
+            });
+        } else if (m > 0) {
+            const int nc = (m + ORDER_THREADS - 1) / ORDER_THREADS, first = wv * 64 * nc + lane;    // this wave's slice: nc chunks of 64
+            uint32_t key[MAXC], least = 0xFFFFFFFFu, most = 0u;
+            if (WHOLE) {
+#pragma unroll
+                for (int c = 0; c < MAXC; ++c) {
+                    const int p = first + 64 * c;
+                    if (c < nc) key[c] = desc_key(src[p < m ? p : m - 1]);
+                }
+#pragma unroll
+                for (int c = 0; c < MAXC; ++c) {
+                    const int p = first + 64 * c;
+                    if (c < nc && p < m) { keys[p] = key[c]; line[p] = p; }
+                }
+            } else {
+                read([&](int i, uint32_t k, bool any) {
+                    const bool in = any && k - lo <= span;
+                    const uint64_t who = __ballot(in);
+                    const int at = before + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
+                    if (in) { keys[at] = k; line[at] = i; }
+                    before += __popcll(who);
+                });
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < MAXC; ++c)
+                    if (c < nc) { const int p = first + 64 * c; key[c] = keys[p < m ? p : m - 1]; }
+            }
+#pragma unroll
+            for (int c = 0; c < MAXC; ++c)
+                if (c < nc) { least = key[c] < least ? key[c] : least; most = key[c] > most ? key[c] : most; }
+            least = lanes_min(least); most = lanes_max(most);
+            if (lane == 63) { sync.red[0][wv] = least; sync.red[1][wv] = most; }
+            for (int i = tid; i < FINE / 2; i += ORDER_THREADS) words[i] = 0u;
+            coarse[tid] = 0u;
+            __syncthreads();
+            least = sync.red[0][0]; most = sync.red[1][0];
+#pragma unroll
+            for (int w = 1; w < ORDER_WAVES; ++w) { const uint32_t t = sync.red[0][w], u = sync.red[1][w]; least = t < least ? t : least; most = u > most ? u : most; }
+            const int width = __builtin_amdgcn_readfirstlane(width_of(most - least));
+            bool sorted = width == 0;                      // equal weights: the order is there
+            if (!sorted) {
+                // 1024 coarse bins of equal span, and of each as many fine bins of equal span as it has lines (or a few times
+                // that): a fine bin then has about one line wherever the weights crowd
+                const int sh = width > 10 ? width - 10 : 0, times = FINE / m;
+                uint32_t bin[MAXC];                        // fine bin | lines met there before << 16
+#pragma unroll
+                for (int c = 0; c < MAXC; ++c)
+                    if (c < nc && first + 64 * c < m) atomicAdd(&coarse[(key[c] - least) >> sh], 1u);
+                __syncthreads();
+                uint32_t all;
+                const uint32_t mine = coarse[tid], ahead_of = order_scan(mine, sync.red[0], lane, wv, all);
+                coarse[tid] = ahead_of * (uint32_t)times | (mine * (uint32_t)times) << 16;      // (at most 16384: first bin below it or no line, number)
+                __syncthreads();
+#pragma unroll
+                for (int c = 0; c < MAXC; ++c)
+                    if (c < nc && first + 64 * c < m) {
+                        const uint32_t d = key[c] - least, w = coarse[d >> sh];
+                        const uint32_t f = (w & 0xFFFFu) + (sh ? __umulhi(d << (32 - sh), w >> 16) : 0u);
+                        const uint32_t old = atomicAdd(&words[f >> 1], 1u << (16 * (f & 1u)));
+                        bin[c] = f | ((old >> (16 * (f & 1u))) & 0xFFFFu) << 16;
+                    }
+                __syncthreads();
+                {                                          // where each fine bin begins
+                    uint32_t t[PT], sum = 0u, fullest = 0u;
+#pragma unroll
+                    for (int j = 0; j < PT; ++j) t[j] = words[PT * tid + j];
+#pragma unroll
+                    for (int j = 0; j < PT; ++j) {
+                        const uint32_t x = t[j] & 0xFFFFu, y = t[j] >> 16;
+                        sum += x + y; fullest = x > fullest ? x : fullest; fullest = y > fullest ? y : fullest;
+                    }
+                    uint32_t at = order_scan(sum, sync.red[1], lane, wv, all);
+#pragma unroll
+                    for (int j = 0; j < PT; ++j) {
+                        words[PT * tid + j] = at | (at + (t[j] & 0xFFFFu)) << 16;
+                        at += (t[j] & 0xFFFFu) + (t[j] >> 16);
+                    }
+                    if (tid == ORDER_THREADS - 1) fine[FINE] = (uint16_t)m;
+                    sorted = !__syncthreads_or(fullest > (uint32_t)ORDER_FULL);
+                }
+                if (sorted) {
+#pragma unroll
+                    for (int c = 0; c < MAXC; ++c)
+                        if (c < nc && first + 64 * c < m) {
+                            const uint32_t at = (uint32_t)fine[bin[c] & 0xFFFFu] + (bin[c] >> 16);
+                            keys[at] = key[c]; ids[at] = (uint16_t)(first + 64 * c);
+                        }
+                    __syncthreads();
+                    // a line's place in its bin: the lines of it that go before (four at once; the places behind the bin are other
+                    // lines', or behind all keys other words of LDS, and do not count)
+#pragma unroll
+                    for (int c = 0; c < MAXC; ++c)
+                        if (c < nc && first + 64 * c < m) {
+                            const uint32_t f = bin[c] & 0xFFFFu, from = fine[f], to = fine[f + 1];
+                            uint32_t at = from;
+                            for (uint32_t q = from; q < to; q += 4) {
+                                uint32_t k[4];
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) k[e] = keys[q + e];
+                                bool equal = false;
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) { at += q + e < to && k[e] < key[c] ? 1u : 0u; equal = equal || (q + e < to && k[e] == key[c] && q + e != from + (bin[c] >> 16)); }
+                                if (equal)
+                                    for (uint32_t e = q; e < q + 4 && e < to; ++e) at += keys[e] == key[c] && (int)ids[e] < first + 64 * c ? 1u : 0u;
+                            }
+                            bin[c] = at;
+                        }
+                    int own[MAXC];
+#pragma unroll
+                    for (int c = 0; c < MAXC; ++c) if (c < nc && first + 64 * c < m) own[c] = line[first + 64 * c];
+                    __syncthreads();
+#pragma unroll
+                    for (int c = 0; c < MAXC; ++c)
+                        if (c < nc && first + 64 * c < m) { keys[bin[c]] = key[c]; line[bin[c]] = own[c]; }
+                } else {
+                    for (int i = tid; i < ORDER_FINE / 2; i += ORDER_THREADS) words[i] = 0u;
+                    __syncthreads();
+                }
+            }
+            // many equal weights, or weights that crowd beyond that: digit by digit
+            const int passes = sorted ? 0 : (width + 9) / 10, bits = passes ? (width + passes - 1) / passes : 0;
+            const uint32_t mask = (1u << bits) - 1u;
+            uint16_t id[MAXC];
+#pragma unroll
+            for (int c = 0; c < MAXC; ++c) id[c] = (uint16_t)(first + 64 * c);
+            for (int p = 0; p < passes; ++p) {
+                const int shift = p * bits;
+                if (p > 0) {
+                    __syncthreads();                       // the order so far is whole
+                    for (int i = tid; i < ORDER_WAVES * 512; i += ORDER_THREADS) words[i] = 0u;
+#pragma unroll
+                    for (int c = 0; c < MAXC; ++c)
+                        if (c < nc) { const int q = first + 64 * c < m ? first + 64 * c : m - 1; key[c] = keys[q]; id[c] = ids[q]; }
+                    __syncthreads();
+                }
+#pragma unroll
+                for (int c = 0; c < MAXC; ++c)
+                    if (c < nc && first + 64 * c < m) {
+                        const uint32_t dg = ((key[c] - least) >> shift) & mask;
+                        atomicAdd(&words[wv * 512 + (dg >> 1)], 1u << (16 * (dg & 1u)));
+                    }
+                __syncthreads();
+                {                                          // first place of every wave's lines of digit tid
+                    uint32_t cnt[ORDER_WAVES], sum = 0u, all;
+#pragma unroll
+                    for (int w = 0; w < ORDER_WAVES; ++w) cnt[w] = hist[w][tid];
+#pragma unroll
+                    for (int w = 0; w < ORDER_WAVES; ++w) sum += cnt[w];
+                    uint32_t at = order_scan(sum, sync.red[p & 1], lane, wv, all);
+#pragma unroll
+                    for (int w = 0; w < ORDER_WAVES; ++w) { hist[w][tid] = (uint16_t)at; at += cnt[w]; }
+                }
+                __syncthreads();
+                // (the wave's counters are read and written with relaxed atomics: plain LDS accesses that the compiler keeps
+                // in program order around the wave barriers)
+                uint16_t* mine = hist[wv];
+#pragma unroll
+                for (int c = 0; c < MAXC; ++c) {
+                    if (c >= nc) break;
+                    const bool in = first + 64 * c < m;
+                    const uint32_t dg = ((key[c] - least) >> shift) & mask;
+                    // lanes whose digit differs from mine in some bit: bit b of the lanes' digits as a wave mask, against
+                    // my own bit b spread over a word; diff | (ballot ^ mine) is one instruction (truth table 0xF6)
+                    const uint64_t none = ~__ballot(in);
+                    uint32_t diff_lo = (uint32_t)none, diff_hi = (uint32_t)(none >> 32);
+                    auto bit = [&](int q) {
+                        const uint32_t t = (uint32_t)((int32_t)(dg << (31 - q)) >> 31);  // 0 or ~0
+                        const uint64_t bal = __ballot(t != 0u);
+                        diff_lo = __builtin_amdgcn_bitop3_b32(diff_lo, (uint32_t)bal, t, 0xF6);
+                        diff_hi = __builtin_amdgcn_bitop3_b32(diff_hi, (uint32_t)(bal >> 32), t, 0xF6);
+                    };
+#pragma unroll
+                    for (int q = 0; q < 7; ++q) bit(q);
+                    if (bits > 7) { bit(7); if (bits > 8) { bit(8); if (bits > 9) bit(9); } }
+                    const uint64_t peers = ~(((uint64_t)diff_hi << 32) | diff_lo);
+                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
+                    const uint32_t pos = (uint32_t)__atomic_load_n(&mine[dg], __ATOMIC_RELAXED) + rank;
+                    __builtin_amdgcn_wave_barrier();
+                    if (in) { keys[pos] = key[c]; ids[pos] = id[c]; }
+                    if (in && rank == 0u) __atomic_store_n(&mine[dg], (uint16_t)(pos + (uint32_t)__popcll(peers)), __ATOMIC_RELAXED);
+                    __builtin_amdgcn_wave_barrier();
+                }
+            }
+            __syncthreads();
+            for (int i = tid; i < m; i += ORDER_THREADS) put(base + i, line[passes ? (int)ids[i] : i], keys[i]);
+        }
+        base += m;
+        if (hi == end) break;
+        lo = hi + 1u; hi = end;
     }
 }
 
@@ -521,7 +658,7 @@ __device__ __forceinline__ void emit_both(const SelectArgs& a, int bh, int cnt_s
     constexpr int H = NT / 2;
     const int tid = threadIdx.x, list = tid >= H ? 1 : 0, t = tid - list * H, lane = tid & 63, wv = tid >> 6;
     const int n = (int)a.n, words = (n + 31) / 32, cnt = list == 0 ? cnt_s : cnt_v, cap = list == 0 ? a.cap_s : a.cap_v;
-    const int32_t* sorted_idx = a.sidx1 + ((int64_t)list * a.BH + bh) * n;
+    const int32_t* sorted_idx = a.sidx + ((int64_t)list * a.BH + bh) * n;
     int32_t* out = list == 0 ? a.s_idx + (int64_t)bh * cap : a.v_idx + (int64_t)bh * cap;
     bm += list * words;
     for (int i = t; i < words; i += H) bm[i] = cnt >= n ? 0xFFFFFFFFu >> (i == words - 1 ? 32 * words - n : 0) : 0u;
@@ -631,7 +768,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
         WalkList& L = lists[l];
         const int64_t seg = l == 0 ? seg_s : seg_v;
         const float* w_l = (l == 0 ? a.slash : a.vert) + (int64_t)bh * a.n;   // weights by line index
-        const int32_t* i_l = a.sidx1 + seg;
+        const int32_t* i_l = a.sidx + seg;
         const int nh32 = (int)nh;
         constexpr int PER = WALK_BLK / 64;
         // the block after the last one written to LDS (indices and weights), and the indices of the one after it:
@@ -690,7 +827,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
         // (one addition after the other took 5700 cycles a block)
         const int l = wv - 4;
         WalkList& L = lists[l];
-        const int32_t* i_l = a.sidx1 + (l == 0 ? seg_s : seg_v);
+        const int32_t* i_l = a.sidx + (l == 0 ? seg_s : seg_v);
         const float* m_l = (l == 0 ? a.smax : a.vmax) + (int64_t)bh * a.n;     // maxima by line index
         float m[WALK_EB], mn[WALK_EB];
         int32_t ix[WALK_EB];                   // line indices of the block after the next one's maxima
@@ -1026,7 +1163,7 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
     auto load = [&](List& l) {
         l.base = l.taken;
         const int i = l.base + tid < n ? l.base + tid : n - 1;
-        l.line = a.sidx1[((int64_t)l.id * a.BH + bh) * a.n + i];
+        l.line = a.sidx[((int64_t)l.id * a.BH + bh) * a.n + i];
         l.weight = ((l.id == 0 ? a.slash : a.vert) + (int64_t)bh * a.n)[l.line];
         l.covered = 0.f;
         l.valid = 0;
@@ -1207,7 +1344,7 @@ __global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
     const int64_t n = a.n;
     const int words = (int)((n + 31) / 32);
     const int64_t seg = ((int64_t)list * a.BH + bh) * n;
-    const int32_t* sorted_idx = a.sidx1 + seg;
+    const int32_t* sorted_idx = a.sidx + seg;
     const int cnt = list == 0 ? a.s_cnt[bh] : a.v_cnt[bh];
     int32_t* out = list == 0 ? a.s_idx + (int64_t)bh * a.cap_s : a.v_idx + (int64_t)bh * a.cap_v;
     const int cap = list == 0 ? a.cap_s : a.cap_v;
@@ -1631,35 +1768,36 @@ __global__ __launch_bounds__(GATHER_THREADS) void gather_rows_kernel(GatherArgs 
 static void launch_emit(const SelectArgs& a, hipStream_t st) {
     if (a.n > EMIT_LINES) hipLaunchKernelGGL(emit_kernel, dim3(2, a.BH), dim3(1024), (size_t)((a.n + 31) / 32) * 4, st, a);
 }
-template <int SEG>
-static hipError_t launch_sort(const SelectArgs& a, hipStream_t st) {
-    const int nseg = (int)((a.n + SEG - 1) / SEG);
-    hipLaunchKernelGGL(sort_seg_kernel<SEG>, dim3(nseg, 2, a.BH), dim3(SORT_THREADS), sort_lds_bytes(SEG), st, a);
-    if constexpr (SEG > SORT_SEG_MIN)                       // (lists of one segment only)
-        if (nseg > 1) hipLaunchKernelGGL(sort_merge_kernel<SEG>, dim3(nseg, 2, a.BH), dim3(SORT_THREADS), 2 * SEG * 4, st, a);
-    return hipGetLastError();
-}
-
-// Segment length: the merge's work per workgroup hardly depends on it, the sort's shrinks with it, so the shortest one
-// that still gives no more workgroups than the chip has compute units (256); but no merge at all for a list that fits
-// into 2048.
+// Ranges of 8192 lines, a fifth less than a workgroup takes (the samples miss by 4 % at most; beyond 65536 lines by more, and a halved
+// range counts again), and more of them, down to 512 lines, as long as there are compute units for one each: 16 heads of
+// 5003 lines 29.8 us in 8 ranges, 33.2 in one; 512 workgroups instead of 256 take turns: 32 heads of 32768 lines 71.4 -> 88.3.
+// One range up to 4096 lines saves the look for its bounds: 32 heads of 4096 lines 26.1 -> 25.0, of 8192 36.9 -> 41.9.
 static hipError_t sort_lines(const SelectArgs& a, hipStream_t st) {
-    const int64_t want = a.n * 2 * a.BH / 256;
-    return a.n <= SORT_SEG_MIN ? launch_sort<SORT_SEG_MIN>(a, st)
-         : want <= 2048        ? launch_sort<2048>(a, st)
-         : want <= 4096        ? launch_sort<4096>(a, st)
-                               : launch_sort<SORT_SEG_MAX>(a, st);
+    int64_t nb = 1;
+    if (a.n > ORDER_ONE) {
+        nb = a.n > 65536 ? (a.n + 6553) / 6554 : (a.n + 8191) / 8192;
+        const int64_t fill = 256 / (2 * (int64_t)a.BH), most = (a.n + 511) / 512;
+        const int64_t more = fill < most ? fill : most;
+        if (nb < more) nb = more;
+    }
+    int64_t chunks = nb == 1 ? (a.n + 1023) / 1024 : (a.n * 5 / (4 * nb) + 256 + 1023) / 1024;
+    if (chunks > ORDER_CHUNKS) chunks = ORDER_CHUNKS;
+    const int cap = (int)chunks * 1024;
+    const dim3 grid(2 * (unsigned)a.BH, (unsigned)nb);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(ORDER_THREADS), order_lds_bytes(cap), st, a, (int)nb, cap); };
+    if (a.n <= 1024) launch(&order_kernel<1, true>);
+    else if (a.n <= ORDER_ONE) launch(&order_kernel<4, true>);
+    else if (cap <= 4096) launch(&order_kernel<4, false>);
+    else launch(&order_kernel<ORDER_CHUNKS, false>);
+    return hipGetLastError();
 }
 
 hipError_t init_select_kernels() {
     hipError_t e;
-    if ((e = allow_full_lds(&sort_seg_kernel<SORT_SEG_MIN>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&sort_seg_kernel<2048>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&sort_seg_kernel<4096>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&sort_seg_kernel<SORT_SEG_MAX>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&sort_merge_kernel<2048>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&sort_merge_kernel<4096>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&sort_merge_kernel<SORT_SEG_MAX>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<1, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<4, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<4, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<ORDER_CHUNKS, false>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_kernel)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_exact_kernel)) != hipSuccess) return e;
     if ((e = allow_full_lds(&merge_lines_kernel)) != hipSuccess) return e;

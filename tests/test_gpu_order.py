@@ -1,0 +1,54 @@
+"""Desc_Sort inside ls_select, where a list is put in order in several ranges of weights: the lengths at which their number
+changes, and weights that miss the ranges' usual course.  The oracle's selection exactly; `accounted` is a running sum
+over the picks, so it shows their order."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_13681_amd import binding
+
+
+def _sampled(n):
+    """The lines from which the ranges' bounds are taken."""
+    i = np.arange(2048)
+    return i * n // 2048 + ((i * 0x9E3779B1 % 2 ** 32 >> 16) * (n // 2048) >> 16)
+
+
+KINDS = {
+    # distinct weights over ten binades
+    "spread": lambda rng, n: np.exp2(rng.uniform(-10, 0, n)),
+    # two thirds of one weight, more than a workgroup holds; the others few-valued
+    "equal": lambda rng, n: np.where(rng.random(n) < 0.67, 0.25, rng.integers(1, 60, n) / 64.0),
+    # all but a handful within 2^12 numbers: the bins of the outliers' ranges hold hundreds of lines each
+    "crowd": lambda rng, n: np.where(rng.random(n) < 10 / n, np.exp2(rng.uniform(-60, 20, n)), 0.5 + rng.integers(0, 4096, n) * 2.0 ** -24),
+    # every sampled line far above the others: the ranges found for them hold nearly nothing or nearly everything
+    "unseen": lambda rng, n: np.where(np.isin(np.arange(n), _sampled(n)), rng.uniform(1, 2, n), rng.uniform(0.01, 0.02, n)),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,kind", [(4096, "crowd"), (4096, "spread"), (4097, "spread"), (4097, "crowd"), (8193, "equal"), (30011, "spread"),
+                                    (30011, "equal"), (30011, "crowd"), (65536, "spread"), (65537, "unseen"), (65537, "spread"), (20000, "unseen")])
+def test_lists_in_ranges(oracle, n, kind):
+    from tests.gpu_util import host
+    from tests.test_gpu_configs import check_selection_exact
+    print(f"lists in ranges n={n} {kind}", flush=True)
+    rng = np.random.default_rng(n)
+    H = 3
+    v, s = (np.stack([KINDS[kind](rng, n) for _ in range(H)])[None] for _ in range(2))
+    v = v.copy(); s = s.copy()
+    s[:, 1] *= 1e-3; v[:, 0] *= 1e-3                                  # one head of columns, one of diagonals, one of both
+    sc = dict(vert=v, slash=s, vmax=v * 1e-7, smax=s * 1e-7, total=np.maximum(v.sum(-1), s.sum(-1)))
+    sc = {k: np.ascontiguousarray(x, dtype=np.float32) for k, x in sc.items()}
+    for alpha in (0.3, 0.97):
+        ref = oracle.select(sc, max(1, n // 3), alpha)
+        shape = binding.make_shape(1, H, 1, 64, n, max(1, n // 3), 1, "f32", 0.0)
+        ctx = binding.Context(shape)
+        out = binding.alloc_select(shape, accounted=True)
+        dev = {k: torch.from_numpy(x).cuda() for k, x in sc.items()}
+        ctx.ls_select(shape, alpha, dev["vert"], dev["slash"], dev["vmax"], dev["smax"], dev["total"], out["v_idx"], out["v_cnt"],
+                      out["s_idx"], out["s_cnt"], out["accounted"])
+        assert ctx.ls_poll_status() == 0
+        gpu = host(out)
+        check_selection_exact(gpu, ref)
+        np.testing.assert_array_equal(gpu["accounted"], ref["accounted"])
