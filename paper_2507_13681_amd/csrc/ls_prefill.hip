@@ -95,6 +95,9 @@ __device__ __forceinline__ uint32_t block_max_1024(uint32_t v, uint32_t* wsum) {
     return ex;
 }
 
+// grid (BH).  Bound by the round trips of one workgroup through the lists of its head: so many loads of 16 bytes are in flight as
+// there are registers for without losing a wave, and the bitmap is put together from neighbouring entries (one entry a lane, eight
+// loads of 4 bytes in flight: 131072 rows 81 us, now 52; 32768 26 -> 19.5, B 4, 64 heads of 16384 17.1 -> 14.7).
 constexpr int LS_MAX_BLOCKS = 262144 / 128 + 2;   // row blocks at the largest supported context
 constexpr int LS_MAX_TAB = 262144 / 64 + 8;  // table entries at the largest supported context
 __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
@@ -126,15 +129,28 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     };
     if ((reinterpret_cast<uintptr_t>(vl) & 15) == 0 && a.cap_v % 4 == 0) {     // four entries per load (and the one before them)
         typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
-        for (int i0 = 4 * tid; i0 < nvl; i0 += 4 * (int)blockDim.x) {
-            const i32x4 c4 = *reinterpret_cast<const i32x4*>(vl + i0);     // entries past nvl (inside the capacity, a multiple of 4 here) are not looked at
-            int32_t prev = i0 > 0 ? vl[i0 - 1] : -1;
-            const int32_t next = i0 + 4 < nvl ? vl[i0 + 4] : 0;
-            const int32_t c[4] = {c4.x, c4.y, c4.z, c4.w};
+        constexpr int AT_ONCE = 4;                         // loads of a thread in flight, 4096 entries apart
+        for (int b0 = 4 * tid; b0 < nvl; b0 += AT_ONCE * 4 * (int)blockDim.x) {
+            i32x4 c4[AT_ONCE];
+            int32_t before[AT_ONCE], next[AT_ONCE];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (i0 + e < nvl) { v_bad = v_bad || c[e] <= prev || c[e] >= n; prev = c[e]; }
-                if (i0 + e < nvl) mark_col(i0 + e, c[e], e < 3 ? c[(e + 1) & 3] : next, i0 + e == nvl - 1);
+            for (int u = 0; u < AT_ONCE; ++u) {
+                const int i0 = b0 + u * 4 * (int)blockDim.x, at = i0 < nvl ? i0 : b0;
+                c4[u] = *reinterpret_cast<const i32x4*>(vl + at);      // entries past nvl (inside the capacity, a multiple of 4 here) are not looked at
+                before[u] = vl[at > 0 ? at - 1 : 0];
+                next[u] = vl[at + 4 < nvl ? at + 4 : at];
+            }
+#pragma unroll
+            for (int u = 0; u < AT_ONCE; ++u) {
+                const int i0 = b0 + u * 4 * (int)blockDim.x;
+                if (i0 >= nvl) break;
+                int32_t prev = i0 > 0 ? before[u] : -1;
+                const int32_t c[4] = {c4[u].x, c4[u].y, c4[u].z, c4[u].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (i0 + e < nvl) { v_bad = v_bad || c[e] <= prev || c[e] >= n; prev = c[e]; }
+                    if (i0 + e < nvl) mark_col(i0 + e, c[e], e < 3 ? c[(e + 1) & 3] : next[u], i0 + e == nvl - 1);
+                }
             }
         }
     } else {
@@ -146,41 +162,49 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     }
     v_bad = __syncthreads_or(v_bad);
     // every diagonal selected (a head the walk gave up sparsifying): the list is 0 .. n-1, checked while it is read
-    bool ident = ns == (int)n;
+    typedef int32_t i32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    bool ident = ns == (int)n && ns >= 4;
     if (ident) {
-        for (int i0 = tid; i0 < ns; i0 += 8 * 1024) {
-            int32_t o8[8];
+        for (int i0 = 4 * tid; i0 < ns; i0 += 4 * 4 * 1024) {
+            i32x4u x[4];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) { const int i = i0 + j * 1024; o8[j] = i < ns ? si[i] : i; }
+            for (int j = 0; j < 4; ++j) { const int i = i0 + j * 4096; x[j] = *reinterpret_cast<const i32x4u*>(si + (i + 4 <= ns ? i : ns - 4)); }
 #pragma unroll
-            for (int j = 0; j < 8; ++j) ident = ident && o8[j] == i0 + j * 1024;
+            for (int j = 0; j < 4; ++j) {
+                const int i = i0 + j * 4096, at = i + 4 <= ns ? i : ns - 4;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) ident = ident && x[j][e] == at + e;
+            }
         }
         ident = __syncthreads_and(ident);
         if (ident) for (int i = tid; i < (int)((n + 31) / 32); i += blockDim.x) sm[i] = (i == (int)(n / 32)) ? ((1u << (n & 31)) - 1u) : 0xFFFFFFFFu;
     }
-    for (int i0 = tid; i0 < (ident ? 0 : ns); i0 += 8 * 1024) {          // eight independent loads in flight per thread
-        int32_t o8[8];
+    // sixteen entries that follow each other per thread; the list is ascending, so most of them fall into few words of the bitmap,
+    // and a word's bits are collected first.  (Correct for any order of the list.)
+    for (int i0 = 16 * tid; i0 < (ident ? 0 : ns); i0 += 16 * 1024) {
+        int32_t o[16];
+        if (i0 + 16 <= ns) {
+            i32x4u x[4];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) { const int i = i0 + j * 1024; o8[j] = i < ns ? si[i] : -1; }
+            for (int j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const i32x4u*>(si + i0 + 4 * j);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            // The list is ascending, so neighbouring lanes mostly hit the same bitmap word: their bits are OR-ed
-            // across each run of equal words inside a row of 16 lanes first (four doubling steps of row shifts,
-            // plain vector moves) and the run's first lane, and every 16th lane, does the one atomic.  Correct for
-            // any order of the list.
-            const bool ok = o8[j] >= 0 && o8[j] < n;
-            s_bad = s_bad || (!ok && i0 + j * 1024 < ns);
-            const int wd = ok ? o8[j] >> 5 : -1 - (tid & 63);
-            uint32_t m = ok ? 1u << (o8[j] & 31) : 0u;
-            // value of the lane `off` to the right inside the row (lanes shifted in from outside a row read -2 / 0)
-#define LS_ROW_SHL(x, off, fill) __builtin_amdgcn_update_dpp((int)(fill), (int)(x), 0x100 + (off), 0xF, 0xF, false)
-#define LS_OR_STEP(off) { const uint32_t tm = (uint32_t)LS_ROW_SHL(m, off, 0); const int tw = LS_ROW_SHL(wd, off, -2); if (tw == wd) m |= tm; }
-            LS_OR_STEP(1) LS_OR_STEP(2) LS_OR_STEP(4) LS_OR_STEP(8)
-            const int pw = __builtin_amdgcn_update_dpp(-2, wd, 0x110 + 1 /* row_shr:1 */, 0xF, 0xF, false);
-#undef LS_OR_STEP
-#undef LS_ROW_SHL
-            if (ok && pw != wd) atomicOr(&sm[wd], m);
+            for (int j = 0; j < 16; ++j) o[j] = x[j >> 2][j & 3];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) o[j] = si[i0 + j < ns ? i0 + j : i0];
         }
+        int word = -1;
+        uint32_t m = 0u;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const bool ok = o[j] >= 0 && o[j] < n;
+            s_bad = s_bad || !ok;
+            const int wd = ok ? o[j] >> 5 : word;
+            if (wd != word && word >= 0) { atomicOr(&sm[word], m); m = 0u; }
+            word = wd;
+            m |= ok ? 1u << (o[j] & 31) : 0u;
+        }
+        if (word >= 0) atomicOr(&sm[word], m);
     }
     __syncthreads();
     int mine = 0;

@@ -141,8 +141,10 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], int b, in
 // sorted by four passes over digits and merged by bisection, two launches, ls_select of 32 heads, us: 4096 lines 26.8 -> 25.0,
 // 12347 45.0 -> 40.2, 24000 76.0 -> 62.6, 32768 86.5 -> 71.5, 65536 176 -> 140, 131072 455 -> 388; 256 heads of 16384 162.5 -> 149.
 // Weights that crowd pay for both ways: all but ten of 32768 lines within 2^12 numbers 76 -> 149, two thirds of one weight 191 -> 228.
+// (WHOLE: two workgroups per CU, 256 heads of 1500 lines 36.0 -> 31.4 us; 64 registers do not do for the others, 16 heads of 5003 lines
+// 29.0 -> 37.8.)
 template <int MAXC, bool WHOLE>
-__global__ __launch_bounds__(ORDER_THREADS) void order_kernel(SelectArgs a, int nb, int cap) {
+__global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(SelectArgs a, int nb, int cap) {
     constexpr int FINE = MAXC == ORDER_CHUNKS ? ORDER_FINE : 2048 * MAXC, PT = FINE / 2 / ORDER_THREADS;
     extern __shared__ __align__(16) unsigned char order_lds[];
     __shared__ OrderSync sync;
