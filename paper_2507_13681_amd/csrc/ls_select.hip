@@ -11,8 +11,8 @@
 //   emit_kernel   one workgroup per (head, list): the chosen prefix of a sorted list becomes an
 //                 ascending index list (bitmap in LDS + prefix popcount).
 //   topb_*        Alg. 3: the `budget` largest scores per KV head by a radix select on the float bit patterns,
-//                 ties broken towards smaller indices, ascending output; by one workgroup a head up to TB_FEW_LEN
-//                 scores (TB_ONE_LEN where there are heads enough), spread over many, one launch per step, beyond.
+//                 ties broken towards smaller indices, ascending output; by one workgroup a head up to TB_ONE_LEN
+//                 scores, spread over many, one launch per step, beyond.
 #include "ls_device.h"
 #include "ls_internal.h"
 
@@ -1647,19 +1647,17 @@ __global__ __launch_bounds__(TB_THREADS) void topb_write_kernel(TopbArgs a) {
 }
 
 // One workgroup per KV head, up to 1024 PER entries, does all steps with the keys in registers, a wave holding
-// consecutive entries.  The threshold is narrowed by two bits a step, the counts of the four quarters in the bytes of a
-// register (a histogram in LDS of a head's scores, which crowd into few digits, took 16 us), until the few keys left are
-// ranked directly or wanted as a whole.  The launches above cost 4.5 us each: 32 heads of 16384 entries 29 us, now 17.
-// Beyond 16 keys a thread (TB_FEW_LEN) one workgroup takes longer than the launches spread over the chip, unless there are
-// heads enough to fill it: the whole of ls_kv_compress (d 64, 8 rows), spread / one workgroup a head, us: 16384 entries 33.8 / 29.1
-// (8 heads), 57.2 / 52.2 (32); 17000 entries 35.1 / 38.4 (8), 51.7 / 56.0 (24), 62.3 / 61.4 (32), 95.0 / 86.0 (64); 32768 entries
-// 40.4 / 44.8 (8), 57.1 / 62.3 (16), 84.5 / 84.7 (32), 149 / 132 (64).
-constexpr int TB_FEW_LEN = 16384, TB_ONE_LEN = 32768, TB_ONE_HEADS = 32, TB_RANKED = 256;
+// consecutive entries.  The threshold lies in one of 1024 bins of equal span between the smallest and the largest key, and so
+// on inside that bin, until the few keys left are ranked directly or wanted as a whole: mostly one round, a few hundred keys
+// at most sharing a bin.  (Digits of the keys as bins, into few of which a head's scores crowd, took 16 us of LDS atomics that take
+// turns; two bits a step, counted in registers, 8 to 10 steps, 15.9 for 32 heads of 16384 entries, now 9.9.)
+// Beyond 32 keys a thread the launches below, 4.5 us each, are spread over the chip; 64 keys do not stay in registers.  The whole of
+// ls_kv_compress (d 64, 8 rows), spread / one workgroup a head, us: 16500 entries 35.5 / 28.9 (8 heads), 93.5 / 73.8 (64); 32768
+// entries 40.5 / 35.8 (8), 84.2 / 75.5 (32), 148 / 122 (64); 33000 entries 41.8 / 75.5 (8), 157 / 179 (64).
+constexpr int TB_ONE_LEN = 32768, TB_RANKED = 256;
 template <int PER>
 __global__ __launch_bounds__(TB_THREADS) void topb_one_kernel(TopbArgs a) {
-    __shared__ uint2 counts[2][16];
-    __shared__ __align__(16) uint32_t left[TB_RANKED];
-    __shared__ uint32_t nleft, found[2], wg[16], we[16];
+    __shared__ uint32_t bins[TB_THREADS], left[TB_RANKED], most[2][16], place[3], nleft, found[2], wg[16], we[16];
     const int bk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int len = (int)a.len, keep = a.budget < len ? a.budget : len;
     int32_t* out = a.keep_idx + (int64_t)bk * a.budget;
@@ -1673,32 +1671,36 @@ __global__ __launch_bounds__(TB_THREADS) void topb_one_kernel(TopbArgs a) {
     uint32_t key[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) key[j] = desc_key(sc[first + 64 * j < len ? first + 64 * j : len - 1]);      // (all loads in flight)
-#pragma unroll
-    for (int j = 0; j < PER; ++j) key[j] = first + 64 * j < len ? key[j] : 0xFFFFFFFFu;
     if (tid == 0) nleft = 0u;
-    // the rem-th smallest key of those counted so far lies among the `within` keys of [lo, lo + 4 w), w = 2^bit
-    uint32_t lo = 0u, rem = (uint32_t)keep, within = 0xFFFFFFFFu;
-    int bit = 30;
-    for (int step = 0;; ++step) {
-        // how many of the lane's keys lie in each quarter: a byte each (what lies behind counts to the last one)
-        uint32_t mine = 0u;
+    bins[tid] = 0u;
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;                    // (entries behind the last one repeat it)
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const uint32_t q = (key[j] - lo) >> bit;
-            mine += 1u << (8u * (q < 3u ? q : 3u));
-        }
-        const uint32_t even = lanes_upto(mine & 0x00FF00FFu), odd = lanes_upto((mine >> 8) & 0x00FF00FFu);
-        if (lane == 63) counts[step & 1][wv] = make_uint2(even, odd);
+    for (int j = 0; j < PER; ++j) { lo = key[j] < lo ? key[j] : lo; hi = key[j] > hi ? key[j] : hi; }
+    lo = lanes_min(lo); hi = lanes_max(hi);
+    if (lane == 63) { most[0][wv] = lo; most[1][wv] = hi; }
+    __syncthreads();
+    lo = (uint32_t)__builtin_amdgcn_readlane((int)lanes_min(most[0][lane & 15]), 63);
+    hi = (uint32_t)__builtin_amdgcn_readlane((int)lanes_max(most[1][lane & 15]), 63);
+    // the rem-th smallest key of those not below lo lies among the `within` keys of [lo, lo + 2^bit)
+    uint32_t rem = (uint32_t)keep, within;
+    int bit;
+    for (;;) {
+        const int width = width_of(hi - lo);
+        bit = width > 10 ? width - 10 : 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (first + 64 * j < len && key[j] - lo <= hi - lo) atomicAdd(&bins[(key[j] - lo) >> bit], 1u);
         __syncthreads();
-        const uint2 x = counts[step & 1][lane & 15];       // every row of sixteen lanes adds up the sixteen waves
-        const uint32_t e2 = (uint32_t)__builtin_amdgcn_readlane((int)lanes_upto(x.x), 15), o2 = (uint32_t)__builtin_amdgcn_readlane((int)lanes_upto(x.y), 15);
-        const uint32_t c0 = e2 & 0xFFFFu, c1 = c0 + (o2 & 0xFFFFu), c2 = c1 + (e2 >> 16), w = 1u << bit;
-        if (rem <= c0) within = c0;
-        else if (rem <= c1) { lo += w; rem -= c0; within = c1 - c0; }
-        else if (rem <= c2) { lo += 2u * w; rem -= c1; within = c2 - c1; }
-        else { lo += 3u * w; rem -= c2; within = within == 0xFFFFFFFFu ? within : within - c2; }
+        const uint32_t mine = bins[tid], upto = lanes_upto(mine);
+        if (lane == 63) wg[wv] = upto;
+        __syncthreads();
+        const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)lanes_upto(lane < wv ? wg[lane & 15] : 0u), 63) + upto - mine;
+        if (rem > before && rem <= before + mine) { place[0] = (uint32_t)tid; place[1] = before; place[2] = mine; }
+        bins[tid] = 0u;
+        __syncthreads();
+        lo += place[0] << bit; rem -= place[1]; within = place[2];
         if (rem == within || within <= (uint32_t)TB_RANKED || bit == 0) break;
-        bit -= 2;
+        hi = lo + ((1u << bit) - 1u);
     }
     // every key below kstar is kept, and need_eq of those equal to it
     uint32_t kstar = lo + (1u << bit) - 1u, need_eq = 0xFFFFFFFFu;
@@ -1706,13 +1708,17 @@ __global__ __launch_bounds__(TB_THREADS) void topb_one_kernel(TopbArgs a) {
         if (within <= (uint32_t)TB_RANKED && bit > 0) {
 #pragma unroll
             for (int j = 0; j < PER; ++j)
-                if (key[j] - lo < 1u << bit) { const uint32_t at = atomicAdd(&nleft, 1u); if (at < (uint32_t)TB_RANKED) left[at] = key[j]; }
+                if (first + 64 * j < len && key[j] - lo < 1u << bit) { const uint32_t at = atomicAdd(&nleft, 1u); if (at < (uint32_t)TB_RANKED) left[at] = key[j]; }
             __syncthreads();
-            if (tid < (int)within) {
-                const uint32_t k = left[tid];
+            {                                              // four threads a key
+                const uint32_t k = left[tid >> 2];
                 uint32_t less = 0u, same = 0u;
-                for (uint32_t i = 0; i < within; ++i) { const uint32_t o = left[i]; less += o < k; same += o == k; }
-                if (less < rem && rem <= less + same) { found[0] = k; found[1] = rem - less; }       // (equal keys store the same)
+                for (uint32_t i = tid & 3; i < within; i += 4) { const uint32_t o = left[i]; less += o < k; same += o == k; }
+                less += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)less, 0xB1, 0xF, 0xF, false);        // quad_perm [1,0,3,2], [2,3,0,1]
+                less += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)less, 0x4E, 0xF, 0xF, false);
+                same += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)same, 0xB1, 0xF, 0xF, false);
+                same += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)same, 0x4E, 0xF, 0xF, false);
+                if (tid >> 2 < (int)within && less < rem && rem <= less + same) { found[0] = k; found[1] = rem - less; }       // (equal keys store the same)
             }
             __syncthreads();
             kstar = found[0]; need_eq = found[1];
@@ -1829,9 +1835,9 @@ size_t topb_scratch_words(int BK, int64_t len) { return (size_t)BK * (3 * TB_BIN
 hipError_t run_topb(const TopbArgs& a0, int BK, uint32_t* scratch, hipStream_t st) {
     if (a0.len < 1 || a0.len > TOPB_MAX_LEN || a0.budget < 1) return hipErrorInvalidValue;
     TopbArgs a = a0;
-    if (a.len <= (BK >= TB_ONE_HEADS ? TB_ONE_LEN : TB_FEW_LEN)) {
+    if (a.len <= TB_ONE_LEN) {
         if (a.len <= 4096) hipLaunchKernelGGL(topb_one_kernel<4>, dim3(BK), dim3(TB_THREADS), 0, st, a);
-        else if (a.len <= TB_FEW_LEN) hipLaunchKernelGGL(topb_one_kernel<16>, dim3(BK), dim3(TB_THREADS), 0, st, a);
+        else if (a.len <= 16384) hipLaunchKernelGGL(topb_one_kernel<16>, dim3(BK), dim3(TB_THREADS), 0, st, a);
         else hipLaunchKernelGGL(topb_one_kernel<32>, dim3(BK), dim3(TB_THREADS), 0, st, a);
         return hipGetLastError();
     }
