@@ -293,8 +293,8 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // ---------------------------------------------------------------------------------------------
 // pieces: which part of the work each workgroup of the attention kernel takes, up to PIECES_TILES.
 //
-// The items (row blocks of heads) lie in one row, head by head, and the row is cut into as many pieces of equal work as
-// there are workgroups.  Every workgroup finds its own piece from the running sums that plan_kernel left behind: a scan over
+// The items (row blocks of heads) lie in one row, head by head, and the row is cut into as many pieces of about equal work
+// as there are workgroups.  Every workgroup finds its own piece from the running sums that plan_kernel left behind: a scan over
 // the heads, a look through one head's row blocks.  Neighbouring pieces go to the same XCD, so that the query heads that
 // share K and V meet in one L2.  An item that a cut goes through is done in parts, whose unnormalised results go to slots of the
 // workspace and which combine_kernel puts together; a cut that would leave a few tiles on one side is moved to the
@@ -304,13 +304,15 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // queues per item, and the wait for the longest item, which a short turn feels most.  The whole call, bf16, 32 heads of d = 128, queues -> pieces,
 // us: 2048 rows, all new, 92 -> 68; 1024 new of 8192 152 -> 124; 300 of 16384 89 -> 70; 100 of 131072 254 -> 230; 61 of 12347
 // 32.7 -> 30.3; 4 heads fp32, 256 of 1024 44 -> 38, 2048 all new 65 -> 37.
-// The line.  Of equal pieces the two workgroups of a CU get unequal speed (10-15 %; the older one's waves go first) and nothing
-// evens that out, and the row spreads the heads of a moment wider than the queues do: the longer the run, the more both cost.
-// Tiles here are those that dense heads would have.  262144: 2048 of 32768 rows 507 -> 477, 8192 rows all new 300 -> 290, B 4, 64 heads,
-// 2048 of 4096 389 -> 397; 400000 to 570000: 10000 rows 378 -> 361, 12000 rows 553 -> 581, B 2, 6000 of 9000 502 -> 505; 720000 and more: 9000 of
-// 20000 814 -> 844, 10923 of 32768 1661 -> 1870 and more.
+// The line.  What the pieces' estimates miss nothing evens out, and the row spreads the heads of a moment wider than the queues
+// do: the longer the run, the more both cost.
+// Tiles here are those that dense heads would have, and a tile of d = 64 counts half.  Queues / pieces, the whole call, us:
+// 262144: 2048 of 32768 rows 507 / 460, 8192 rows all new 300 / 290; 400000 to 520000: 10000 rows 374 / 346, 6000 of 9000, B 2, 490 / 479,
+// 1000 of 131072 840 / 788; 570000 to 660000: 12000 rows 562 / 543, 5000 of 32768 1022 / 989, 2500 of 65536 927 / 944; 720000 and
+// more: 9000 of 20000 819 / 851, 14000 rows 511 / 528, 2000 of 131072 1769 / 1883, 10923 of 32768 1709 / 1816.  d = 64, 16 heads: 16384 rows
+// (526304) 163 / 124, 12000 of 30000 (714000) 375 / 347, 24000 rows (1130961) 367 / 307.
 // ---------------------------------------------------------------------------------------------
-constexpr int64_t PIECES_TILES = 262144;
+constexpr int64_t PIECES_TILES = 524288;
 constexpr int CUT_TILES = 2;                               // fewest tiles on either side of a cut (a part costs its result written and read: the time of two)
 __host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : base + 8; }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
 
@@ -343,7 +345,21 @@ __host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work
     return pieces <= work / (2 * WORK_TILE) ? (int)pieces : work >= 2 * WORK_TILE ? (int)(work / (2 * WORK_TILE)) : 1;
 }
 // where piece p begins
+//
+// Of the workgroups of a CU the one that came first is served first: of equal pieces, one per place, those of workgroups 0 to 255
+// took 220 us, 256 to 511 262 (first turn of 8192 rows), at d = 64 41, 50 and 60 us (5003 rows carried), and a CU left to its last
+// workgroup is not busy.  So where every place is taken the pieces of a place are that much larger or smaller.  Shares of
+// 64 / 64, 67 / 61, 70 / 58, 73 / 55, 76 / 52, the whole call, us: 8192 rows, all new, 300 / 296 / 291 / 290 / 297, 2048 of 32768 481 / 473 / 465 /
+// 460 / 475; at d = 64 64, 69, 74, 79, 84 for the first of three 90 / 88 / 88 / 88 / 87, 5003 rows, all new, 73 / 71 / 71 / 71 / 70.
+constexpr uint32_t FIRST_OF_2 = 72, FIRST_OF_3 = 80;       // of 128, of 192 (the second of three: 64)
 __host__ __device__ __forceinline__ uint32_t cut_at(uint32_t total, int p, int pieces) {
+    if (pieces == 512 || pieces == 768) {                  // 32 CUs an XCD, whose workgroups take neighbouring pieces
+        const uint32_t places = pieces / 256, xcd = (uint32_t)p / (32 * places), j = (uint32_t)p % (32 * places);
+        const uint32_t w0 = places == 2 ? FIRST_OF_2 : FIRST_OF_3, w1 = places == 2 ? 128 - FIRST_OF_2 : 64, w2 = 192 - w0 - w1;
+        const uint32_t at = xcd * 32 * 64 * places + (j < 32 ? j * w0 : j < 64 ? 32 * w0 + (j - 32) * w1 : 32 * (w0 + w1) + (j - 64) * w2);
+        const uint32_t all = 256 * 64 * places;            // (total % all * at: less than 2^32)
+        return total / all * at + total % all * at / all;
+    }
     const uint32_t q = total / (uint32_t)pieces, r = total % (uint32_t)pieces;
     return q * (uint32_t)p + ((uint32_t)p < r ? (uint32_t)p : r);
 }
@@ -606,7 +622,7 @@ int prefill_split_slots(int64_t items, int grid, bool pieces) {
     if (pieces) return grid + begin_slots(items, grid);
     return items > SPLIT_ITEMS ? 0 : items * ITEM_PARTS < SPLIT_SLOTS ? (int)items * ITEM_PARTS : SPLIT_SLOTS;
 }
-bool prefill_in_pieces(int BH, int64_t n, int nqb) { return (int64_t)BH * nqb * ((n + BN - 1) / BN) <= PIECES_TILES; }
+bool prefill_in_pieces(int BH, int64_t n, int nqb, int d) { return (int64_t)BH * nqb * ((n + BN - 1) / BN) * d <= PIECES_TILES * 128; }
 
 void prefill_pieces(int dtype, const uint32_t* rec, const uint32_t* upto, const uint32_t* head_work, int BH, int nqb, int grid, int slots, int* xcd_of_item) {
     const int64_t all = (int64_t)BH * nqb;

@@ -1,5 +1,5 @@
-"""How ls_sparse_prefill shares its work among the workgroups: in pieces of equal work up to 262144 tiles of 64 keys (counted
-as if every head were dense), by work queues above.  One call over a batch that lies above that line is compared with calls
+"""How ls_sparse_prefill shares its work among the workgroups: in pieces of about equal work up to 524288 tiles of 64 keys
+(counted as if every head were dense, half at d = 64), by work queues above.  One call over a batch that lies above that line is compared with calls
 over its parts, which lie below: the same cells summed in another order of tiles and parts."""
 import numpy as np
 import pytest
@@ -7,11 +7,11 @@ import torch
 
 from paper_2507_13681_amd import inputs
 
-LINE = 262144
+LINE = 524288 * 128
 
 
-def _tiles(B, Hq, n, n_hat):
-    return B * Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128) * ((n + 63) // 64)
+def _tiles(B, Hq, n, n_hat, d):
+    return d * B * Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128) * ((n + 63) // 64)
 
 
 def _lists(rng, B, H, n):
@@ -35,13 +35,13 @@ def _lists(rng, B, H, n):
 # the turn is the end of the context or all of it; n and n_hat have no relation to any tile size
 @pytest.mark.gpu
 @pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d,dtype", [
-    (11, 16, 4, 3999, 3000, 128, "bf16"), (11, 16, 2, 3999, 3999, 64, "bf16"), (5, 4, 1, 20001, 6500, 128, "bf16"),
-    (11, 16, 4, 3999, 3000, 64, "f32"), (11, 16, 4, 4003, 2900, 128, "f32")])
+    (22, 16, 4, 3999, 3000, 128, "bf16"), (5, 4, 2, 21001, 21001, 64, "bf16"), (5, 4, 1, 20001, 12000, 128, "bf16"),
+    (5, 4, 1, 21001, 21001, 64, "f32"), (5, 4, 2, 20003, 12001, 128, "f32")])
 def test_queues_and_pieces_agree(B, Hq, Hkv, n, n_hat, d, dtype):
     from tests.gpu_util import Pipeline, dev_lists
     print(f"queues and pieces B={B} Hq={Hq} n={n} n_hat={n_hat} d={d} {dtype}", flush=True)
     cut = B // 2 + 1
-    assert _tiles(B, Hq, n, n_hat) > LINE >= _tiles(cut, Hq, n, n_hat)
+    assert _tiles(B, Hq, n, n_hat, d) > LINE >= _tiles(cut, Hq, n, n_hat, d)
     q, k, v = inputs.make_plain(B, Hq, Hkv, n, n_hat, d, dtype=dtype, seed=n, q_scale=1.5)
     lists = _lists(np.random.default_rng(n), B, Hq, n)
     out, lse = Pipeline(q, k, v, 1, dtype).prefill(dev_lists(*lists), sentinel=True)
