@@ -805,7 +805,9 @@ __device__ __forceinline__ void store_out4(float* p, float a, float b, float c, 
 // Puts the parts of the split items together.  Queues: `split` lists them.  Pieces: the cuts tell; the part that begins an item
 // lies in the slot of the item (or of its piece, where there are more items than pieces) behind those of the pieces, the
 // others in the slots of theirs.  A unit is one wave's 32 rows of a split item, taken by one workgroup in the layout store_part
-// wrote: wave w adds the groups w, w + 4, ... of 16 bytes a lane.  grid-stride over the units (pieces: four per cut).
+// wrote: wave w adds the groups w, w + 4, ... of 16 bytes a lane.  Queues: grid-stride over the units.  Pieces: four units a cut, a
+// workgroup each (512 workgroups in all: 5003 rows carried, d = 64, 13.4 us instead of 10.3, first turn of 8192 rows 17.6 instead of 15.7,
+// which is 65 MB read at 4.2 TB/s).
 template <typename T, int D, bool QUEUES>
 __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
     constexpr int DBLK = D / 32;
@@ -1711,7 +1713,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
 
 template <typename T, int D, bool QUEUES>
 static void launch_combine(const PrefillArgs& a, hipStream_t st, const hipEvent_t* ev) {
-    const dim3 grid(QUEUES ? (a.slots < 256 ? 2 * a.slots : 512) : (a.grid < 128 ? 4 * a.grid : 512));
+    const dim3 grid(QUEUES ? (a.slots < 256 ? 2 * a.slots : 512) : 4 * a.grid);
     if (QUEUES ? a.slots == 0 : !cuts_items((int64_t)a.BH * a.nqb, a.grid, a.slots)) return;
     if (ev) hipExtLaunchKernelGGL((combine_kernel<T, D, QUEUES>), grid, dim3(256), 0, st, ev[2], ev[3], 0, a);
     else hipLaunchKernelGGL((combine_kernel<T, D, QUEUES>), grid, dim3(256), 0, st, a);
