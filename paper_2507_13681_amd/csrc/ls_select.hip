@@ -4,7 +4,7 @@
 //                 The weights' range is cut into ranges of about as many lines each, a workgroup per range: it picks its
 //                 lines out of the list and ranks them inside LDS, so nothing is left to merge.
 //   walk_kernel   one workgroup of six waves per head: the greedy loop of Alg. 2 in binary32 with the operands
-//                 and operation order of the definition.  One wave decides runs of up to 512 picks from one
+//                 and operation order of the definition.  One wave decides runs of up to 1024 picks from one
 //                 list with its lanes, one accumulates the running sum pick by pick behind it and finds
 //                 the pick that reaches the target, and two waves per list stage the sorted list and its
 //                 overlap prefix sums in LDS ahead of both.
@@ -627,24 +627,26 @@ __device__ __forceinline__ int chain_lds(const float* gains, int lane, int limit
 // definition.
 constexpr int WALK_THREADS = 384;              // wave 0 decides the runs, wave 2 sums them; per list, waves 1 / 3 stage its
                                                // weights and lengths and waves 4 / 5 its overlap prefix sums
-constexpr int WALK_E = 8;                      // consecutive list entries a lane looks at: a run has up to 64 * E picks
-constexpr int WALK_RUN = 64 * WALK_E;
+// A lane looks at E list entries: a run has up to 64 E picks.  Short lists have short runs, long ones long: 4 / 8 / 16, ls_select of
+// 32 heads, us: 2048 lines 22.9 / 25.1 / 29.5, 4096 25.0 / 24.6 / 26.2, 12347 39.3 / 39.8 / 40.7, 16384 60.3 / 52.3 / 50.3, 32768 81.3 / 71.2 / 67.6,
+// 65536 164 / 141 / 134; 256 heads of 1500 lines 29.6 / 31.7 / 37.2.
+constexpr int64_t WALK_SHORT = 2048, WALK_LONG = 16384;        // up to: 4; from: 16
 constexpr int WALK_NBLK = 4;                   // blocks of a list resident in LDS (a ring over sorted positions)
 constexpr int WALK_CAP = WALK_BLK * WALK_NBLK;
 constexpr int WALK_EB = WALK_BLK / 64;         // entries per lane when a block's prefix sums are added
-static_assert(WALK_EB % 2 == 0 && WALK_RUN <= WALK_BLK, "a run never reaches beyond the block after the head's");
+static_assert(WALK_EB % 2 == 0 && 64 * 16 <= WALK_BLK, "a run never reaches beyond the block after the head's");
 
 // The resident part of one sorted list, indexed by sorted position modulo WALK_CAP: weights, line lengths, and
-// pre[p] = the overlap sum when the first p lines of the list have been taken.  The first WALK_RUN entries are
+// pre[p] = the overlap sum when the first p lines of the list have been taken.  The first 64 E entries are
 // there a second time behind the last one, so that a run's entries are consecutive wherever it starts.
-struct WalkList { float cw[WALK_CAP + WALK_RUN], cl[WALK_CAP + WALK_RUN], pre[WALK_CAP + WALK_RUN]; };
+template <int E> struct WalkList { float cw[WALK_CAP + 64 * E], cl[WALK_CAP + 64 * E], pre[WALK_CAP + 64 * E]; };
 // One run of picks from one list: the gain of each pick, how many of them count, and whether the walk ends
 // after them because no line is left that adds anything.
-struct WalkRun { float g[WALK_RUN]; int which, limit, last, pad; };
+template <int E> struct WalkRun { float g[64 * E]; int which, limit, last, pad; };
 struct WalkSync { int staged[2], summed_blk[2], cur[2], summed, stop, done, err, runs, decided, cnt_s, cnt_v; float tot[2]; };
 static_assert(offsetof(WalkSync, summed) % 8 == 0 && offsetof(WalkSync, stop) == offsetof(WalkSync, summed) + 4, "summed and stop are read as one 8-byte word");   // tot: a list's whole overlap sum
 constexpr int WALK_RING = 4;                   // runs decided ahead of the running sum
-constexpr size_t WALK_LDS_BYTES = 2 * sizeof(WalkList) + WALK_RING * sizeof(WalkRun) + sizeof(WalkSync);
+template <int E> constexpr size_t WALK_LDS_BYTES = 2 * sizeof(WalkList<E>) + WALK_RING * sizeof(WalkRun<E>) + sizeof(WalkSync);
 
 __device__ __forceinline__ int walk_ld(const int* p) { return __builtin_amdgcn_readfirstlane(__atomic_load_n(p, __ATOMIC_RELAXED)); }
 __device__ __forceinline__ void walk_st(int* p, int v) { __atomic_store_n(p, v, __ATOMIC_RELAXED); }
@@ -722,11 +724,12 @@ __device__ __forceinline__ void walk_maxima(const float* m_l, const int32_t (&ix
 }
 
 // Position of the first entry for which `p` holds, in the order entry 0 of lane 0, entry 0 of lane 1, ..., entry 1 of
-// lane 0, ... (WALK_RUN if it holds nowhere)
-__device__ __forceinline__ int walk_first(const bool (&p)[WALK_E]) {
-    int at = WALK_RUN;
+// lane 0, ... (64 E if it holds nowhere)
+template <int E>
+__device__ __forceinline__ int walk_first(const bool (&p)[E]) {
+    int at = 64 * E;
 #pragma unroll
-    for (int e = WALK_E - 1; e >= 0; --e) {
+    for (int e = E - 1; e >= 0; --e) {
         const uint64_t any = __ballot(p[e]);
         at = any != 0ull ? 64 * e + __ffsll((unsigned long long)any) - 1 : at;
     }
@@ -745,10 +748,14 @@ __device__ __forceinline__ int walk_first(const bool (&p)[WALK_E]) {
 // taken out, and stop when the walk is over.  The summing wave writes the result; the deciding wave ends the
 // stagers through `done`.  Every wait is a bounded spin that also ends when another wave has reported a failed
 // wait, so all six waves leave in every case.
+template <int E>
 __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* walk_lds) {
-    WalkList* lists = reinterpret_cast<WalkList*>(walk_lds);
-    WalkRun* ring = reinterpret_cast<WalkRun*>(walk_lds + 2 * sizeof(WalkList));
-    WalkSync* sync = reinterpret_cast<WalkSync*>(walk_lds + 2 * sizeof(WalkList) + WALK_RING * sizeof(WalkRun));
+    using List = WalkList<E>;
+    using Run = WalkRun<E>;
+    constexpr int RUN = 64 * E;
+    List* lists = reinterpret_cast<List*>(walk_lds);
+    Run* ring = reinterpret_cast<Run*>(walk_lds + 2 * sizeof(List));
+    WalkSync* sync = reinterpret_cast<WalkSync*>(walk_lds + 2 * sizeof(List) + WALK_RING * sizeof(Run));
     const int bh = blockIdx.x, lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = (int)a.n;
@@ -767,7 +774,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
     if (wv == 1 || wv == 3) {
         // ------------------------------------------------------------------ weights and lengths of one list
         const int l = wv == 1 ? 0 : 1;
-        WalkList& L = lists[l];
+        List& L = lists[l];
         const int64_t seg = l == 0 ? seg_s : seg_v;
         const float* w_l = (l == 0 ? a.slash : a.vert) + (int64_t)bh * a.n;   // weights by line index
         const int32_t* i_l = a.sidx + seg;
@@ -813,7 +820,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
                 const int len = n - fx[j] < nh32 ? n - fx[j] : nh32;       // line length in the n_hat x n block
                 L.cw[slot + i] = in ? fw[j] : 0.f;
                 L.cl[slot + i] = in ? (float)len : 1.f;
-                if (slot == 0 && 64 * j < WALK_RUN) { L.cw[WALK_CAP + i] = in ? fw[j] : 0.f; L.cl[WALK_CAP + i] = in ? (float)len : 1.f; }
+                if (slot == 0 && 64 * j < RUN) { L.cw[WALK_CAP + i] = in ? fw[j] : 0.f; L.cl[WALK_CAP + i] = in ? (float)len : 1.f; }
             }
             fetch(b + 1);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -828,7 +835,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
         // ------------------------------------------------------------------ overlap prefix sums of one list
         // (one addition after the other took 5700 cycles a block)
         const int l = wv - 4;
-        WalkList& L = lists[l];
+        List& L = lists[l];
         const int32_t* i_l = a.sidx + (l == 0 ? seg_s : seg_v);
         const float* m_l = (l == 0 ? a.smax : a.vmax) + (int64_t)bh * a.n;     // maxima by line index
         float m[WALK_EB], mn[WALK_EB];
@@ -852,7 +859,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
             walk_maxima<WALK_EB>(m_l, ix, (b + 1) * WALK_BLK + WALK_EB * lane, n, mn);
             walk_indices<WALK_EB>(i_l, (b + 2) * WALK_BLK + WALK_EB * lane, n, ix);
-            acc = chain_prefix<WALK_EB>(m, lane, acc, L.pre + (b & (WALK_NBLK - 1)) * WALK_BLK, L.pre + WALK_CAP, (b & (WALK_NBLK - 1)) == 0 ? WALK_RUN : 0);
+            acc = chain_prefix<WALK_EB>(m, lane, acc, L.pre + (b & (WALK_NBLK - 1)) * WALK_BLK, L.pre + WALK_CAP, (b & (WALK_NBLK - 1)) == 0 ? RUN : 0);
 #pragma unroll
             for (int e = 0; e < WALK_EB; ++e) m[e] = mn[e];
             if (b == nblk - 1 && lane == 0) sync->tot[l] = acc;
@@ -888,22 +895,22 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             }
             if (!have) break;                  // both lists were used up (or a wait ran into its bound)
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            const WalkRun& R = ring[k & (WALK_RING - 1)];
+            const Run& R = ring[k & (WALK_RING - 1)];
             const int which = __builtin_amdgcn_readfirstlane(R.which);
             const int limit = __builtin_amdgcn_readfirstlane(R.limit);
             const int last = __builtin_amdgcn_readfirstlane(R.last);
-            float g[WALK_E];
+            float g[E];
 #pragma unroll
-            for (int e = 0; e < WALK_E; e += 2) {
-                const float2 t = *reinterpret_cast<const float2*>(&R.g[WALK_E * lane + e]);
-                g[e] = WALK_E * lane + e < limit ? t.x : 0.f; g[e + 1] = WALK_E * lane + e + 1 < limit ? t.y : 0.f;
+            for (int e = 0; e < E; e += 2) {
+                const float2 t = *reinterpret_cast<const float2*>(&R.g[E * lane + e]);
+                g[e] = E * lane + e < limit ? t.x : 0.f; g[e + 1] = E * lane + e + 1 < limit ? t.y : 0.f;
             }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // the slot may be written again
             ++k;
             if (lane == 0) walk_st(&sync->summed, k);
             // pick by pick, as the loop of the definition adds them; it stops after the pick that reaches the target
             // (one addition after the other took 3900 cycles a run)
-            const int taken = chain_until<WALK_E>(g, lane, limit, target, sum);
+            const int taken = chain_until<E>(g, lane, limit, target, sum);
             const bool reached = !(sum < target);
             cnt_s += which == 0 ? taken : 0;
             cnt_v += which == 0 ? 0 : taken;
@@ -948,21 +955,21 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
     // What the lanes need of a list when its head is at `h`: lane l looks at the entries h + l, h + 64 + l, ... (weight,
     // overlap prefix, length; whatever lies there past the end of the list), every lane at the head's own three values.
     // Re-read only when the head of that list moves.  (All of them lie in the head's block or the one after it.)
-    struct View { float cw[WALK_E], pre[WALK_E], cl[WALK_E], w0, l0, ol0; };
+    struct View { float cw[E], pre[E], cl[E], w0, l0, ol0; };
     auto lane0 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x))); };
     auto view = [&](int l, int h) {
-        const WalkList& L = lists[l];
+        const List& L = lists[l];
         View r;
         const int at = (h & (WALK_CAP - 1)) + lane;
 #pragma unroll
-        for (int e = 0; e < WALK_E; ++e) { r.cw[e] = L.cw[at + 64 * e]; r.pre[e] = L.pre[at + 64 * e]; r.cl[e] = L.cl[at + 64 * e]; }
+        for (int e = 0; e < E; ++e) { r.cw[e] = L.cw[at + 64 * e]; r.pre[e] = L.pre[at + 64 * e]; r.cl[e] = L.cl[at + 64 * e]; }
         if (h < n) { r.w0 = lane0(r.cw[0]); r.l0 = lane0(r.cl[0]); r.ol0 = lane0(r.pre[0]); }
         else { r.w0 = 0.f; r.l0 = 1.f; r.ol0 = lane0(sync->tot[l]); }      // an exhausted list: no weight, and its overlap sum
         return r;                                                          // sits right behind its last line
     };
     // blocks a view at head h reads: through the block of entry h + RUN - 1, and pre[h] itself
     auto blocks_for = [&](int h) {
-        const int want = (h + WALK_RUN - 1) / WALK_BLK + 1;
+        const int want = (h + RUN - 1) / WALK_BLK + 1;
         return want < nblk ? want : nblk;
     };
     have_s = wait_blocks(0, blocks_for(0));
@@ -994,43 +1001,43 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             V = view(1, iv);
         }
         // entry e of lane l: the decision if the walk has taken 64 e + l more slashes (iv frozen)
-        float gain[WALK_E];
-        bool turn[WALK_E];                     // the pick goes to the other list
+        float gain[E];
+        bool turn[E];                     // the pick goes to the other list
         const float fs = (float)is, fv = (float)iv;
         int run = 0, which = 0;
         if (is < n) {
 #pragma unroll
-            for (int e = 0; e < WALK_E; ++e) {
+            for (int e = 0; e < E; ++e) {
                 const float ds = __fsub_rn(S.cw[e], V.ol0), dv = __fsub_rn(V.w0, S.pre[e]);
                 const float cs = fmaxf(__fsub_rn(S.cl[e], fv), 1.0f), cv = fmaxf(__fsub_rn(V.l0, fs + (float)(64 * e + lane)), 1.0f);
                 turn[e] = !(__fmul_rn(ds, cv) >= __fmul_rn(dv, cs));
                 gain[e] = ds;
             }
-            run = iv < n ? walk_first(turn) : WALK_RUN;
+            run = iv < n ? walk_first(turn) : RUN;
             run = run < n - is ? run : n - is;
         }
         if (run == 0) {
             // the head pick is a vertical; entry e of lane l: the decision if 64 e + l more verticals are taken (is frozen)
             which = 1;
 #pragma unroll
-            for (int e = 0; e < WALK_E; ++e) {
+            for (int e = 0; e < E; ++e) {
                 const float dv = __fsub_rn(V.cw[e], S.ol0), ds = __fsub_rn(S.w0, V.pre[e]);
                 const float cv = fmaxf(__fsub_rn(V.cl[e], fs), 1.0f), cs = fmaxf(__fsub_rn(S.l0, fv + (float)(64 * e + lane)), 1.0f);
                 turn[e] = __fmul_rn(ds, cv) >= __fmul_rn(dv, cs);          // not a vertical again
                 gain[e] = dv;
             }
-            run = is < n ? walk_first(turn) : WALK_RUN;
+            run = is < n ? walk_first(turn) : RUN;
             run = run < n - iv ? run : n - iv;
         }
         if (run == 0) break;                   // cannot happen (entry 0 of lane 0 repeats the head's test); never spin
         // picks 0 .. run-1 come from list `which`; the walk ends early at a pick with no positive gain left
         // (the gains of a run do not increase: none is 0 or less if the last entry's is not)
-        int stop_dead = WALK_RUN;
-        if (early && __ballot(!(gain[WALK_E - 1] > 0.f)) != 0ull) {
+        int stop_dead = RUN;
+        if (early && __ballot(!(gain[E - 1] > 0.f)) != 0ull) {
             const bool has = which == 0 ? iv < n : is < n;
-            bool dead[WALK_E];                 // no gain is left in either list
+            bool dead[E];                 // no gain is left in either list
 #pragma unroll
-            for (int e = 0; e < WALK_E; ++e)
+            for (int e = 0; e < E; ++e)
                 dead[e] = !(gain[e] > 0.f) && (!has || !((which == 0 ? __fsub_rn(V.w0, S.pre[e]) : __fsub_rn(S.w0, V.pre[e])) > 0.f));
             stop_dead = walk_first(dead);
         }
@@ -1049,9 +1056,9 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
         }
         if (stopped || failed) break;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        WalkRun& R = ring[published & (WALK_RING - 1)];
+        Run& R = ring[published & (WALK_RING - 1)];
 #pragma unroll
-        for (int e = 0; e < WALK_E; ++e) R.g[64 * e + lane] = gain[e];
+        for (int e = 0; e < E; ++e) R.g[64 * e + lane] = gain[e];
         if (lane == 0) { R.which = which; R.limit = limit; R.last = stop_dead < run ? 1 : 0; }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         ++published;
@@ -1067,18 +1074,19 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
     }
 }
 
-// grid (BH); dynamic LDS: WALK_LDS_BYTES
+// grid (BH); dynamic LDS: WALK_LDS_BYTES<E>
+template <int E>
 __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
     extern __shared__ __align__(16) unsigned char walk_lds[];
-    walk_head(a, walk_lds);
+    walk_head<E>(a, walk_lds);
     __syncthreads();
-    const WalkSync* sync = reinterpret_cast<const WalkSync*>(walk_lds + 2 * sizeof(WalkList) + WALK_RING * sizeof(WalkRun));
+    const WalkSync* sync = reinterpret_cast<const WalkSync*>(walk_lds + 2 * sizeof(WalkList<E>) + WALK_RING * sizeof(WalkRun<E>));
     const int bh = blockIdx.x, cnt_s = sync->cnt_s, cnt_v = sync->cnt_v;
     if (threadIdx.x == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; }
     if (a.n > EMIT_LINES) return;
     emit_both<WALK_THREADS>(a, bh, cnt_s, cnt_v, reinterpret_cast<uint32_t*>(walk_lds));      // (not where `sync` lies)
 }
-static_assert(2 * sizeof(WalkList) > EMIT_LINES / 4, "the bitmaps lie ahead of the rings");
+static_assert(2 * sizeof(WalkList<4>) > EMIT_LINES / 4, "the bitmaps lie ahead of the rings");
 
 // ---- Alg. 2 with the overlap of a candidate counted cell by cell ----------------------------------
 // The loop of Alg. 2 compares the marginal contributions of the two list heads (Sec. 5.1); the listing bounds the
@@ -1806,7 +1814,9 @@ hipError_t init_select_kernels() {
     if ((e = allow_full_lds(&order_kernel<4, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&order_kernel<4, false>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&order_kernel<ORDER_CHUNKS, false>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&walk_kernel)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&walk_kernel<4>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&walk_kernel<8>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&walk_kernel<16>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_exact_kernel)) != hipSuccess) return e;
     if ((e = allow_full_lds(&merge_lines_kernel)) != hipSuccess) return e;
     return allow_full_lds(&emit_kernel);
@@ -1815,7 +1825,9 @@ hipError_t init_select_kernels() {
 hipError_t run_select(const SelectArgs& a, hipStream_t st) {
     hipError_t e = sort_lines(a, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(walk_kernel, dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES, st, a);
+    if (a.n <= WALK_SHORT) hipLaunchKernelGGL(walk_kernel<4>, dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES<4>, st, a);
+    else if (a.n < WALK_LONG) hipLaunchKernelGGL(walk_kernel<8>, dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES<8>, st, a);
+    else hipLaunchKernelGGL(walk_kernel<16>, dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES<16>, st, a);
     launch_emit(a, st);
     return hipGetLastError();
 }

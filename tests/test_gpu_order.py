@@ -28,7 +28,8 @@ KINDS = {
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,kind", [(4096, "crowd"), (4096, "spread"), (4097, "spread"), (4097, "crowd"), (8193, "equal"), (30011, "spread"),
-                                    (30011, "equal"), (30011, "crowd"), (65536, "spread"), (65537, "unseen"), (65537, "spread"), (20000, "unseen")])
+                                    (30011, "equal"), (30011, "crowd"), (65536, "spread"), (65537, "unseen"), (65537, "spread"), (20000, "unseen"),
+                                    (2049, "spread"), (16383, "spread"), (16384, "equal")])
 def test_lists_in_ranges(oracle, n, kind):
     from tests.gpu_util import host
     from tests.test_gpu_configs import check_selection_exact
