@@ -46,9 +46,14 @@ __host__ __device__ __forceinline__ int item_blocks(uint32_t r) { return (int)(r
 __host__ __device__ __forceinline__ int item_cols(uint32_t r) { return (int)(r >> 13); }
 __host__ __device__ __forceinline__ uint32_t work_base(int dtype) { return dtype == 0 ? 32 : 8; }
 __host__ __device__ __forceinline__ uint32_t item_work(uint32_t base, uint32_t n1, uint32_t n2) { return base + n1 * WORK_TILE + n2 * WORK_COLS; }
-// A half's probabilities (relative to the running reference) may sum to this in a lane before the reference moves: bf16 and fp32
-// are as exact up there as around one, and the 2^18 keys of a row stay far from the end of either's range.
-constexpr float SOFT_LIMIT = 65536.f;
+// A half's probabilities (relative to the running reference) may sum to this in a lane before the reference moves to the half's maximum;
+// in an item's first tiles to less (4, 8, 16: twice as much every tile).  bf16 is as exact up there as around one, but the probability
+// that is the reference is one, without rounding, and a row's largest cells mostly come early (the band beside the
+// diagonal).  Error of the output against 64 bits, rms relative to it, 1e-3, with 65536 throughout / 16 / this / a maximum per tile and
+// moves beyond 2^8, as it was: 3000 of 6000 rows 2.05 / 1.97 / 1.98 / 1.99, 61 of 12347 2.09 / 1.92 / 1.87 / 1.92, 8192 rows, all new, 2.14 / 1.89 /
+// 1.91 / 2.06, 2000 of 30000 2.10 / 1.95 / 1.96 / 2.04, d = 64, 1777 of 5003 2.02 / 1.89 / 1.90 / 1.92.  It costs 0.5 % of the attention of
+// a long turn, 4 % of one of 61 rows.
+constexpr float SOFT_LIMIT = 32.f, SOFT_FIRST = 2.f;
 
 // ---------------------------------------------------------------------------------------------
 // plan: per (batch, head) bitmap of the selected diagonals, the per-j activity table, a head flag.
@@ -1347,9 +1352,9 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[i][r] = 0.f;
     // mneg: the softmax reference of this lane's row in base 2, negated (+inf: no cell seen yet).  It moves only when a probability
-    // might exceed SOFT_LIMIT, so that most tiles need no rescaling of the accumulators (nor is a larger one less precise).
+    // might exceed the limit, so that most tiles need no rescaling of the accumulators.
     const float sc2 = a.scale_log2e;
-    float mneg = INFINITY, l_run = 0.f;
+    float mneg = INFINITY, l_run = 0.f, limit = SOFT_FIRST;
 
     // ---- staging.  Wave wv fetches rows 16 wv .. 16 wv + 15 of each operand, IPW instructions of RPI rows, which share one M0:
     // an instruction's offset moves its source and its target alike, and where the target moves further (K_LAG) the
@@ -1440,7 +1445,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     // of products ahead, and a product is followed by its share of the other half's 16 registers (a product takes its wave 33
     // cycles, a masked register 27, an unmasked one 18).
     // No maximum is looked for on the way: the exponentials are taken with the reference as it stands, and where a lane's
-    // sum says that one of them may exceed SOFT_LIMIT (or is no number, as with the first cells of a row: -mneg = -inf), the half is
+    // sum says that one of them may exceed the limit (or is no number, as with the first cells of a row: -mneg = -inf), the half is
     // done again with a new reference.  s keeps the logits for that.
     // Cycles of a workgroup over the 32768-key turn 3.52 -> 3.34 million; the clock falls with the better use of the matrix pipeline
     // (2.29 -> 2.23 GHz, dense heads 2.05 -> 1.98: the card's power is what bounds them), so that 1723 us became 1665.  Going on to
@@ -1455,6 +1460,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     auto process = [&](int tileoff) {
         f32x16 sa, sb;
         Soft pa, pb;
+        limit = fminf(limit * 2.f, SOFT_LIMIT);
         auto kload = [&](Frag<T>& f, const unsigned char* base, int c) { load_frag(f, base + kaddr[c & (C::KA - 1)] + 32 * (c & ~(C::KA - 1))); };
         auto vload = [&](Frag<T>& f, const unsigned char* base, int k) {     // keys 16 (k / DBLK).., output block k % DBLK
             const unsigned char* va = base + vaddr[k % C::DBLK] + 16 * (k / C::DBLK) * C::RB;
@@ -1490,7 +1496,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         };
         auto settle = [&](f32x16& s, Soft& o) {            // the sums in, or the half once more with a new reference
             float sum = o.sum[0] + o.sum[1];
-            if (__ballot(!(sum <= SOFT_LIMIT)) != 0ull) {
+            if (__ballot(!(sum <= limit)) != 0ull) {
                 float mx = -INFINITY;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
