@@ -31,7 +31,7 @@ __device__ __forceinline__ float key_to_float(uint32_t key) {
 }
 
 constexpr int WALK_BLK = 1024;                 // entries of a sorted list the walk stages at a time
-static_assert(WALK_BLK == SELECT_HEAD_LINES, "the merge writes the walk's first block in order");
+static_assert(WALK_BLK == SELECT_HEAD_LINES, "order_kernel writes the walk's first block in order");
 constexpr int ORDER_THREADS = 1024;
 constexpr int ORDER_WAVES = 16;
 constexpr int ORDER_CHUNKS = 10;               // most chunks of 64 lines a wave sorts: 10240 lines a workgroup
