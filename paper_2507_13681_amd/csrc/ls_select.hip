@@ -13,6 +13,7 @@
 //   topb_*        Alg. 3: the `budget` largest scores per KV head by a radix select on the float bit patterns,
 //                 ties broken towards smaller indices, ascending output; by one workgroup a head up to TB_ONE_LEN
 //                 scores, spread over many, one launch per step, beyond.
+#include <type_traits>
 #include "ls_device.h"
 #include "ls_internal.h"
 
@@ -34,13 +35,14 @@ constexpr int WALK_BLK = 1024;                 // entries of a sorted list the w
 static_assert(WALK_BLK == SELECT_HEAD_LINES, "order_kernel writes the walk's first block in order");
 constexpr int ORDER_THREADS = 1024;
 constexpr int ORDER_WAVES = 16;
-constexpr int ORDER_CHUNKS = 10;               // most chunks of 64 lines a wave sorts: 10240 lines a workgroup
+constexpr int ORDER_CHUNKS = 10;               // most lines of a workgroup, in 1024
 constexpr int ORDER_ONE = 4096;                // longest list that one workgroup puts in order
-constexpr int ORDER_FINE = 16384;              // fine bins
 constexpr int ORDER_FULL = 32;                 // lines of the fullest bin that are still ranked against each other
-constexpr int ORDER_FRONT = ORDER_FINE * 2 + 16 + 1024 * 4;
-static_assert(ORDER_FINE * 2 >= ORDER_WAVES * 1024 * 2 && ORDER_FINE >= 1024 * ORDER_CHUNKS, "room for the waves' digit counters, a bin per line");
-constexpr size_t order_lds_bytes(int cap) { return (size_t)ORDER_FRONT + (size_t)cap * 10; }
+constexpr int order_fine(int pt) { return pt * 2 * ORDER_THREADS; }        // fine bins, where a thread has `pt` words of them
+constexpr size_t order_lds_bytes(int pt, int cap) { return (size_t)order_fine(pt) * 2 + 16 + 1024 * 4 + (size_t)cap * 12; }
+static_assert(order_fine(4) * 2 >= 4096 * 4 && order_fine(8) >= 1024 * ORDER_CHUNKS, "room for order_bounds, a bin per line");
+constexpr int ORDER_SEGS = 320;                // most bins with more lines than that
+static_assert(1024 * ORDER_CHUNKS / (ORDER_FULL + 1) < ORDER_SEGS && 2 * ORDER_SEGS <= 1024 && 1024 * ORDER_CHUNKS <= 1 << 14, "words for each of them, places 14 bits");
 
 // sum over the lanes to the left and this one
 __device__ __forceinline__ uint32_t lanes_upto(uint32_t x) {
@@ -66,23 +68,44 @@ __device__ __forceinline__ uint32_t lanes_max(uint32_t x) { return ~lanes_min(~x
 __device__ __forceinline__ int width_of(uint32_t x) { return x == 0u ? 0 : 32 - __builtin_clz(x); }
 
 // What the workgroup keeps beside the keys: `red` for sums over the waves (two rounds that follow each other use different halves).
-struct OrderSync { uint32_t red[2][ORDER_WAVES], bin[2], rest[2]; };
+struct OrderSync { uint32_t red[4][ORDER_WAVES], bin[2], rest[2], many[2]; int32_t cross[4]; uint16_t lines[ORDER_SEGS]; };
+
+// Sums over the waves before this one, and over all, of what each left in `red` (the sixteen in a row of lanes: a tenth of the
+// instructions that a loop over them takes, which a kernel that runs through its code once has to fetch)
+__device__ __forceinline__ uint32_t waves_before(const uint32_t* red, int lane, int wv, uint32_t& total) {
+    static_assert(ORDER_WAVES == 16, "a row of lanes");
+    int32_t s = (int32_t)red[lane & 15];
+    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);       // row_shr:1, 2, 4, 8
+    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);
+    total = (uint32_t)__builtin_amdgcn_readlane(s, 15);
+    return wv > 0 ? (uint32_t)__builtin_amdgcn_readlane(s, wv - 1) : 0u;
+}
+// Smallest and largest over the waves, of what each left in the two halves of `red`
+__device__ __forceinline__ void waves_extremes(const uint32_t (*red)[ORDER_WAVES], int lane, uint32_t& least, uint32_t& most) {
+    least = (uint32_t)__builtin_amdgcn_readlane((int)lanes_min(red[0][lane & 15]), 63);
+    most = (uint32_t)__builtin_amdgcn_readlane((int)lanes_max(red[1][lane & 15]), 63);
+}
 
 // Sum of `x` over the threads before this one, and over all of them.  One barrier; `red` must not be in use.
 __device__ __forceinline__ uint32_t order_scan(uint32_t x, uint32_t* red, int lane, int wv, uint32_t& total) {
     const uint32_t upto = lanes_upto(x);
     if (lane == 63) red[wv] = upto;
     __syncthreads();
-    uint32_t before = 0u, all = 0u;
-#pragma unroll
-    for (int w = 0; w < ORDER_WAVES; ++w) { const uint32_t t = red[w]; before += w < wv ? t : 0u; all += t; }
-    total = all;
-    return before + upto - x;
+    return waves_before(red, lane, wv, total) + upto - x;
 }
 
-// The keys that bound range `b` of `nb`: those of rank b S / nb and (b + 1) S / nb among S = 2048 samples, two a thread, to 20
-// bits of the samples' span.  The same numbers in every workgroup of the list.  hist: 2 * 1024 words of LDS.
-__device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], int b, int nb, uint32_t* hist, OrderSync& sync, uint32_t& k0, uint32_t& k1) {
+// Where a range begins: lines of a lighter weight come behind it, and lines of its weight from `line` on.  -1: all of them.
+// earlier, later: the bound before or behind it lies among the lines of the same weight as well.
+struct OrderBound { uint32_t key; int32_t line; bool earlier, later; };
+
+// The bounds of range `b` of `nb`: the samples of rank b S / nb and (b + 1) S / nb among S = 2048 of them, two a thread (sample i before
+// sample i + 1 in the list).  The key is found to 20 bits of the samples' span, and to the last bit where more than a sixteenth of
+// a range's share of samples lies in one such step; the line is given where as many samples have one weight: its lines then fall
+// to several ranges.  The same numbers in every workgroup of the list: a bound depends on its rank alone.
+// hist: 4096 words of LDS.
+__device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int32_t (&pos)[2], int b, int nb, uint32_t* hist, OrderSync& sync, OrderBound& from, OrderBound& to) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     constexpr int PER = 2, S = PER * ORDER_THREADS;
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
@@ -92,9 +115,7 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], int b, in
     lo = lanes_min(lo); hi = lanes_max(hi);
     if (lane == 63) { sync.red[0][wv] = lo; sync.red[1][wv] = hi; }
     __syncthreads();
-    lo = sync.red[0][0]; hi = sync.red[1][0];
-#pragma unroll
-    for (int w = 1; w < ORDER_WAVES; ++w) { const uint32_t t = sync.red[0][w], u = sync.red[1][w]; lo = t < lo ? t : lo; hi = u > hi ? u : hi; }
+    waves_extremes(sync.red, lane, lo, hi);
     const int width = width_of(hi - lo), sh = width > 20 ? width - 20 : 0;
     uint32_t at[PER];
 #pragma unroll
@@ -108,7 +129,8 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], int b, in
     if (t1 >= e && t1 < e + v) { sync.bin[1] = (uint32_t)tid; sync.rest[1] = t1 - e; }
     if (b == nb - 1 && tid == 0) { sync.bin[1] = 1023u; sync.rest[1] = 0u; }             // (no bound: not looked at)
     __syncthreads();
-    const uint32_t bin0 = sync.bin[0], bin1 = sync.bin[1], rest0 = sync.rest[0], rest1 = sync.rest[1];
+    const uint32_t bin0 = sync.bin[0], bin1 = sync.bin[1];
+    uint32_t rest0 = sync.rest[0], rest1 = sync.rest[1];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         const uint32_t add = ((at[j] >> 10) == bin0 ? 1u : 0u) | ((at[j] >> 10) == bin1 ? 0x10000u : 0u);
@@ -116,45 +138,103 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], int b, in
     }
     __syncthreads();
     v = hist[1024 + tid]; e = order_scan(v, sync.red[1], lane, wv, all);
-    if (rest0 >= (e & 0xFFFFu) && rest0 < (e & 0xFFFFu) + (v & 0xFFFFu)) sync.bin[0] = (uint32_t)tid;
-    if (rest1 >= (e >> 16) && rest1 < (e >> 16) + (v >> 16)) sync.bin[1] = (uint32_t)tid;
+    if (rest0 >= (e & 0xFFFFu) && rest0 < (e & 0xFFFFu) + (v & 0xFFFFu)) { sync.bin[0] = (uint32_t)tid; sync.rest[0] = rest0 - (e & 0xFFFFu); sync.many[0] = v & 0xFFFFu; }
+    if (b < nb - 1 && rest1 >= (e >> 16) && rest1 < (e >> 16) + (v >> 16)) { sync.bin[1] = (uint32_t)tid; sync.rest[1] = rest1 - (e >> 16); sync.many[1] = v >> 16; }
     __syncthreads();
-    k0 = lo + ((bin0 << 10 | sync.bin[0]) << sh);
-    k1 = lo + ((bin1 << 10 | sync.bin[1]) << sh);
+    uint32_t f0 = bin0 << 10 | sync.bin[0], f1 = bin1 << 10 | sync.bin[1];
+    uint32_t many0 = b > 0 ? sync.many[0] : 0u, many1 = b < nb - 1 ? sync.many[1] : 0u;
+    rest0 = sync.rest[0]; rest1 = sync.rest[1];
+    from = OrderBound{lo + (f0 << sh), -1, false, false};
+    to = OrderBound{lo + (f1 << sh), -1, false, false};
+    const uint32_t few = (uint32_t)(S / (16 * nb));
+    if (many0 <= few && many1 <= few) return;              // (uniform, as all of this)
+    if (sh > 0) {                                          // the last bits, at most 12
+#pragma unroll
+        for (int j = 0; j < 4; ++j) hist[4 * tid + j] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const uint32_t add = (at[j] == f0 ? 1u : 0u) | (at[j] == f1 ? 0x10000u : 0u);
+            if (add) atomicAdd(&hist[(key[j] - lo) & ((1u << sh) - 1u)], add);
+        }
+        __syncthreads();
+        uint32_t h[4], sum = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { h[j] = hist[4 * tid + j]; sum += h[j]; }
+        e = order_scan(sum, sync.red[0], lane, wv, all);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t x = h[j] & 0xFFFFu, y = h[j] >> 16, ex = e & 0xFFFFu, ey = e >> 16;
+            if (rest0 >= ex && rest0 < ex + x) { sync.bin[0] = (uint32_t)(4 * tid + j); sync.rest[0] = rest0 - ex; sync.many[0] = x; }
+            if (rest1 >= ey && rest1 < ey + y) { sync.bin[1] = (uint32_t)(4 * tid + j); sync.rest[1] = rest1 - ey; sync.many[1] = y; }
+            e += h[j];
+        }
+        __syncthreads();
+        f0 = f0 << sh | sync.bin[0]; f1 = f1 << sh | sync.bin[1];
+        rest0 = sync.rest[0]; rest1 = sync.rest[1];
+        if (many0 > few) { from.key = lo + f0; many0 = sync.many[0]; }
+        if (many1 > few) { to.key = lo + f1; many1 = sync.many[1]; }
+        if (many0 <= few && many1 <= few) return;
+    }
+    // samples of the bound's weight, in the list's order
+    uint32_t upto = 0u;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const bool is0 = many0 > few && key[j] == from.key, is1 = many1 > few && key[j] == to.key;
+        const uint32_t n = upto + order_scan((is0 ? 1u : 0u) | (is1 ? 0x10000u : 0u), sync.red[j ^ 1], lane, wv, all);
+        if (is0 && (n & 0xFFFFu) == rest0) sync.bin[0] = (uint32_t)pos[j];
+        if (is1 && (n >> 16) == rest1) sync.bin[1] = (uint32_t)pos[j];
+        upto += all;
+    }
+    __syncthreads();
+    auto rank = [&](int r) -> int { return r * S / nb; };
+    auto finish = [&](OrderBound& x, int r, uint32_t bin, uint32_t rest, uint32_t many) {      // r: the range that it begins
+        x.line = (int32_t)bin;
+        const int first = rank(r) - (int)rest;
+        x.earlier = r > 1 && rank(r - 1) >= first;
+        x.later = r + 1 < nb && rank(r + 1) < first + (int)many;
+    };
+    if (many0 > few) finish(from, b, sync.bin[0], rest0, many0);
+    if (many1 > few) finish(to, b + 1, sync.bin[1], rest1, many1);
 }
 
 // Desc_Sort.  grid (lists, nb); list 2 bh + 0 = diagonals (slash), + 1 = columns (vert) of a head.  (Workgroups of a list are
 // `lists` apart: with a multiple of eight lists in one XCD, whose L2 then fetches the list once.)
-// Workgroup b puts the b-th of nb ranges of weights in order (WHOLE: the list, of up to 1024 MAXC lines).  It
+// Workgroup b puts the b-th of nb ranges of weights in order (WHOLE: the list, of up to `cap` lines).  It
 //   - finds the range's bounds from 2048 samples of the list, so that each range has about as many lines;
 //   - counts the range's lines and those before it, and takes the former into LDS, in index order;
 //   - spreads them over bins, about one line each (below), and ranks the few lines of a bin against each other, by weight
-//     and then by index: no pass over digits, no chain of ranks from one 64 lines to the next;
-//   - writes their indices (sidx) where they belong, one behind the other; the first WALK_BLK lines of the order get their
-//     weight and maximum written as well (head_w, head_m), so that the walk can start without a second round trip.
-// A range of more than `cap` lines is halved until it fits, one of equal weights is written as it comes.  Lines that crowd
-// into a bin all the same (many equal weights, or one far away from all others) are sorted digit by digit, stably.
+//     and then by index; bins with too many lines are spread again, each over as many bins as it has lines;
+//   - writes their indices (sidx) where they belong; the first WALK_BLK lines of the order get their weight and maximum written as
+//     well (head_w, head_m), so that the walk can start without a second round trip.
+// The lines of a weight that has ranges to itself are written as they come, by one workgroup, and so is a range's share of a weight that
+// two ranges meet in.  A range of more than `cap` lines all the same (the samples missed them) is halved until it fits.
 //
-// What bounds it: latencies, one workgroup of sixteen waves per CU: 32768 lines, cycles of one of 4 workgroups: bounds 10000, count
-// 7000, lines into LDS 5700, their span 9500 (the barrier waits for the wave with most of them), bins 10000, ranks 8000,
-// results 11000.  Beyond 65536 lines it is the look through the whole list, which every range repeats.  Against segments
-// sorted by four passes over digits and merged by bisection, two launches, ls_select of 32 heads, us: 4096 lines 26.8 -> 25.0,
-// 12347 45.0 -> 40.2, 24000 76.0 -> 62.6, 32768 86.5 -> 71.5, 65536 176 -> 140, 131072 455 -> 388; 256 heads of 16384 162.5 -> 149.
-// Weights that crowd pay for both ways: all but ten of 32768 lines within 2^12 numbers 76 -> 149, two thirds of one weight 191 -> 228.
-// (WHOLE: two workgroups per CU, 256 heads of 1500 lines 36.0 -> 31.4 us; 64 registers do not do for the others, 16 heads of 5003 lines
-// 29.0 -> 37.8.)
-template <int MAXC, bool WHOLE>
+// What bounds it: latencies, one workgroup of sixteen waves per CU: 32768 lines, cycles of one of 4 workgroups: bounds and count 14800, lines
+// into LDS 14300, their span 1600, bins 14600, ranks and results 10200.  Beyond 65536 lines it is the look through the whole
+// list, which every range repeats.  A workgroup runs through its code once and has to fetch it: everything lies in LDS and the loops are
+// not unrolled over it.  (Keys and bins in registers, ten lines a thread, ranks by indirection and many equal weights
+// by digits, 30 KB of code and 88 bytes of scratch: 32 heads of 32768 lines 35 us, now 30; 256 heads of 16384 111 -> 96; 4096 10.8 -> 10.2;
+// 131072 243 both.  The kernel alone.)
+// Lists that crowd, 32 heads, the kernel alone, us, by digits / now / segments of 8192 sorted by digits and merged:
+// all but ten lines within 2^12 numbers 1024 lines 13.6 / 10.7 / 7.7, 4096 27.9 / 17.1 / 14.4, 32768 122 / 48 / 54, 131072 320 / 354 / 323; two thirds of one
+// weight, the others of 59 4096 31.9 / 21.6 / 17.7, 32768 96 / 47 / 59, 131072 300 / 238 / 326; two fifths zero 4096 25.6 / 18.3 / 15.0, 32768 34 / 33 / 53,
+// 131072 233 / 219 / 317; 59 weights 4096 26.6 / 16.9 / 17.0, 32768 69 / 57 / 56, 131072 408 / 454 / 314 (there every range ends inside a
+// weight on both sides, and its two looks through the list take half as long again).
+// (WHOLE: two workgroups per CU; 256 heads of 1500 lines, the whole ls_select, 29.4 -> 27.9.)
+template <int PT, bool WHOLE>
 __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(SelectArgs a, int nb, int cap) {
-    constexpr int FINE = MAXC == ORDER_CHUNKS ? ORDER_FINE : 2048 * MAXC, PT = FINE / 2 / ORDER_THREADS;
+    constexpr int FINE = order_fine(PT);
     extern __shared__ __align__(16) unsigned char order_lds[];
     __shared__ OrderSync sync;
-    uint16_t (*hist)[1024] = reinterpret_cast<uint16_t (*)[1024]>(order_lds);            // [16 waves]
-    uint16_t* fine = reinterpret_cast<uint16_t*>(order_lds);                             // [ORDER_FINE + 1], in the same place
-    uint32_t* words = reinterpret_cast<uint32_t*>(order_lds);                            // either's counters in pairs
-    uint32_t* coarse = reinterpret_cast<uint32_t*>(order_lds + ORDER_FINE * 2 + 16);     // [1024]
-    uint32_t* keys = reinterpret_cast<uint32_t*>(order_lds + ORDER_FRONT);               // [cap]
-    int32_t* line = reinterpret_cast<int32_t*>(keys + cap);                              // [cap] the lines, in index order
-    uint16_t* ids = reinterpret_cast<uint16_t*>(line + cap);                             // [cap] places in `line`, in the order so far
+    uint32_t* words = reinterpret_cast<uint32_t*>(order_lds);                            // of the fine bins: lines, then places, in pairs
+    uint16_t* fine = reinterpret_cast<uint16_t*>(order_lds);                             // [FINE + 1] bin f's at f + 1; in the end bin f has the places from fine[f] up to fine[f + 1]
+    uint32_t* coarse = reinterpret_cast<uint32_t*>(order_lds + FINE * 2 + 16);           // [1024]; later least and largest key of the bins that are too full
+    uint32_t* keys = coarse + 1024;                                                      // [cap] of the range's lines, in index order
+    uint32_t* spread = keys + cap;                                                       // [cap] by fine bin: how far into the bin << 14 | place in `keys`
+    uint16_t* line = reinterpret_cast<uint16_t*>(spread + cap);                          // [cap] index, low half
+    uint16_t* bins = line + cap;                                                         // [cap] fine bin | DONE | EQUAL; between two spreads, place in the order | DONE or first place of its bin
+    constexpr uint32_t PLACE = 0x3FFFu, DONE = 0x4000u, EQUAL = 0x8000u;
     const int list = blockIdx.x & 1, bh = blockIdx.x >> 1, b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -175,34 +255,77 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
             for (int j = 0; j < 8; ++j) { const int i = i0 + 64 * j + lane; f(i, desc_key(x[j]), i < w1); }
         }
     };
-    uint32_t lo = 0u, end = 0xFFFFFFFFu;
-    if (!WHOLE && nb > 1) {
-        uint32_t sample[2], k0, k1;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {                      // somewhere in the i-th 2048th of the list, so that no period of it is met
-            const int i = tid + j * ORDER_THREADS, len = n / (2 * ORDER_THREADS);
-            sample[j] = desc_key(src[(int)((int64_t)i * n / (2 * ORDER_THREADS)) + (int)((((uint32_t)i * 0x9E3779B1u) >> 16) * (uint32_t)len >> 16)]);
-        }
-        order_bounds(sample, b, nb, reinterpret_cast<uint32_t*>(order_lds), sync, k0, k1);
-        if (b > 0) lo = k0;
-        if (b < nb - 1) {
-            if (k1 <= lo) return;                          // (all of them: the bounds are the same for every thread)
-            end = k1 - 1u;
-        }
-    }
     auto put = [&](int at, int i, uint32_t k) {            // line i is the `at`-th of the order
         out[at] = i;
         if (at < WALK_BLK) { a.head_w[head + at] = key_to_float(k); a.head_m[head + at] = mx[i]; }
     };
+    auto lanes_before = [](uint64_t who) -> int { return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u)); };
+    // The range: the weights from `lo` to `end`.  With `ends` it begins or ends among lines of one weight, has all lines from key << 32 | index of
+    // `lo_line` to that of `end_line`, and `lo` to `end` are the weights between `front` and `back`, its first and the first behind it.
+    uint32_t lo = 0u, end = 0xFFFFFFFFu, front = 0u, back = 0u;
+    uint64_t lo_line = 0u, end_line = ~0ull;
+    bool ends = false, alone = false;                      // alone: `front` is its only weight
+    if (!WHOLE && nb > 1) {
+        uint32_t sample[2];
+        int32_t where[2];
+        OrderBound from, to;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {                      // somewhere in the i-th 2048th of the list, so that no period of it is met
+            const int i = tid + j * ORDER_THREADS, len = n / (2 * ORDER_THREADS);
+            where[j] = (int)((int64_t)i * n / (2 * ORDER_THREADS)) + (int)((((uint32_t)i * 0x9E3779B1u) >> 16) * (uint32_t)len >> 16);
+            sample[j] = desc_key(src[where[j]]);
+        }
+        order_bounds(sample, where, b, nb, words, sync, from, to);
+        const bool last = b == nb - 1;
+        if (b == 0) from = OrderBound{0u, -1, false, false};
+        // A weight that has ranges to itself: the first of them takes all its lines, those at its ends none
+        if (!last && to.line >= 0 && (to.earlier || to.later)) {
+            if (from.line >= 0 && from.key == to.key) {
+                if (from.earlier) return;
+                from.line = 0; to.line = 0x7FFFFFFF;
+            } else {
+                to.line = -1;
+            }
+        }
+        if (from.line >= 0 && (from.earlier || from.later) && (last || from.key != to.key)) {
+            if (from.key == 0xFFFFFFFFu) return;
+            from.line = -1; ++from.key;
+        }
+        lo_line = (uint64_t)from.key << 32 | (uint32_t)(from.line > 0 ? from.line : 0);
+        lo = from.key;
+        if (!last) {
+            const uint64_t behind = (uint64_t)to.key << 32 | (uint32_t)(to.line > 0 ? to.line : 0);
+            if (behind <= lo_line) return;                 // nothing (the bounds are the same for every thread)
+            end_line = behind - 1u;
+            end = to.key - 1u;
+        }
+        if (from.line >= 0 || (!last && to.line >= 0)) {
+            ends = true;
+            alone = !last && to.key == from.key;
+            front = lo++; back = last ? front : to.key;
+        }
+    }
     uint32_t hi = end;
-    int base = nb > 1 ? -1 : 0;                            // lines before the range
+    int base = nb > 1 ? -1 : 0;                            // place of the range's first line in the order
+    if (!WHOLE && tid < 4) sync.cross[tid] = 0x7FFFFFFF;
     for (;;) {
-        const uint32_t span = hi - lo;
         int before = w0, m = n;                            // lines of the range in the waves before, and in all (a list in one range: all lines)
+        const uint32_t span = hi - lo;
         if (!WHOLE && nb > 1) {
-            uint32_t here = 0u, below = 0u;
-            auto count = [&](uint32_t k, bool any) { here += any && k - lo <= span ? 1u : 0u; below += any && k < lo ? 1u : 0u; };
-            {                                              // (their order does not matter here: 16 bytes a lane)
+            uint32_t here = 0u, below = 0u, fronts = 0u, backs = 0u;
+            auto counts = [&](auto ENDS) {
+                auto count = [&](int i, uint32_t k, bool any) {
+                    if (decltype(ENDS)::value) {
+                        const uint64_t x = (uint64_t)k << 32 | (uint32_t)i;
+                        const bool in = any && x - lo_line <= end_line - lo_line, f = in && k == front, r = in && k == back && !f;
+                        fronts += f ? 1u : 0u; backs += r ? 1u : 0u; here += in ? 1u : 0u;
+                        below += any && x < lo_line ? 1u : 0u;
+                    } else {
+                        here += any && k - lo <= span ? 1u : 0u;
+                        below += any && k < lo ? 1u : 0u;
+                    }
+                };
+                // (their order does not matter here: 16 bytes a lane)
                 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
                 int i = w0 + 4 * lane;
                 for (; i - 4 * lane + 1024 <= w1; i += 1024) {
@@ -212,240 +335,243 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) count(desc_key(x[j][e]), true);
+                        for (int e = 0; e < 4; ++e) count(i + 256 * j + e, desc_key(x[j][e]), true);
                 }
                 for (i += lane - 4 * lane; i - lane < w1; i += 64 * 4) {
                     float x[4];
 #pragma unroll
                     for (int j = 0; j < 4; ++j) x[j] = src[i + 64 * j < n ? i + 64 * j : n - 1];
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) count(desc_key(x[j]), i + 64 * j < w1);
+                    for (int j = 0; j < 4; ++j) count(i + 64 * j, desc_key(x[j]), i + 64 * j < w1);
                 }
-            }
+            };
+            if (ends) counts(std::true_type{}); else counts(std::false_type{});
             here = lanes_upto(here); below = lanes_upto(below);
             __syncthreads();                               // `red` and the last range's lines are free again
+            if (ends) {
+                fronts = lanes_upto(fronts); backs = lanes_upto(backs);
+                here -= fronts + backs;
+                if (lane == 63) { sync.red[2][wv] = fronts; sync.red[3][wv] = backs; }
+            }
             if (lane == 63) { sync.red[0][wv] = here; sync.red[1][wv] = below; }
             __syncthreads();
-            int ahead = 0;
-            before = 0; m = 0;
-#pragma unroll
-            for (int w = 0; w < ORDER_WAVES; ++w) { const int t = (int)sync.red[0][w]; before += w < wv ? t : 0; m += t; ahead += (int)sync.red[1][w]; }
-            if (base < 0) base = ahead;
-            m = __builtin_amdgcn_readfirstlane(m);
+            uint32_t all, ahead;
+            before = (int)waves_before(sync.red[0], lane, wv, all);
+            (void)waves_before(sync.red[1], lane, wv, ahead);
+            m = (int)all;
+            if (base < 0) base = (int)ahead;
+            if (ends) {                                    // the order of the lines at the ends is there; the others are picked on the way
+                uint32_t f_all, r_all;
+                int f_at = base + (int)waves_before(sync.red[2], lane, wv, f_all), r_at = (int)waves_before(sync.red[3], lane, wv, r_all);
+                base += (int)f_all;
+                r_at += base + m;
+                int at = before;
+                const bool take = m <= cap;
+                if (!alone || (w1 > (int)(uint32_t)lo_line && w0 <= (int)(uint32_t)end_line)) read([&](int i, uint32_t k, bool any) {
+                    const uint64_t x = (uint64_t)k << 32 | (uint32_t)i;
+                    const bool in = any && x - lo_line <= end_line - lo_line, f = in && k == front, r = in && k == back && !f, mid = in && !f && !r;
+                    const uint64_t fs = __ballot(f), rs = __ballot(r), who = __ballot(mid);
+                    if ((i & 0xFFFF) == 0 && any) sync.cross[i >> 16] = at;
+                    if (mid && take) { const int p = at + lanes_before(who); keys[p] = k; line[p] = (uint16_t)i; }
+                    if (f || r) put((f ? f_at : r_at) + lanes_before(f ? fs : rs), i, k);
+                    f_at += __popcll(fs); r_at += __popcll(rs); at += __popcll(who);
+                });
+            }
         }
-        if (!WHOLE && m > cap && lo < hi) {                // the lower half of the span that its weights have (nothing lies before it)
-            uint32_t least = 0xFFFFFFFFu, most = 0u;
-            read([&](int, uint32_t k, bool any) {
-                const bool in = any && k - lo <= span;
-                least = in && k < least ? k : least; most = in && k > most ? k : most;
-            });
+        uint32_t least = 0xFFFFFFFFu, most = 0u;
+        auto extremes = [&](uint32_t k, bool in) { least = in && k < least ? k : least; most = in && k > most ? k : most; };
+        auto agree = [&]() {                               // (all threads; `red` must have been read)
             least = lanes_min(least); most = lanes_max(most);
-            __syncthreads();                               // `red` has been read
             if (lane == 63) { sync.red[0][wv] = least; sync.red[1][wv] = most; }
             __syncthreads();
-            least = sync.red[0][0]; most = sync.red[1][0];
-#pragma unroll
-            for (int w = 1; w < ORDER_WAVES; ++w) { const uint32_t t = sync.red[0][w], u = sync.red[1][w]; least = t < least ? t : least; most = u > most ? u : most; }
-            lo = least; hi = least + (most - least) / 2;
-            continue;
-        }
-        const uint64_t left = (1ull << lane) - 1ull;
-        if (!WHOLE && m > cap) {                           // equal weights: the order is there
-            read([&](int i, uint32_t k, bool any) {
-                const bool in = any && k - lo <= span;
+            waves_extremes(sync.red, lane, least, most);
+        };
+        if (!WHOLE && m > cap) {                           // more than expected (the samples missed them)
+            read([&](int, uint32_t k, bool any) { extremes(k, any && k - lo <= span); });
+            __syncthreads();
+            agree();
+            if (least < most) { lo = least; hi = least + (most - least) / 2; ends = false; continue; }           // the lower half of the span that its weights have
+            read([&](int i, uint32_t k, bool any) {        // equal weights: the order is there
+                const bool in = any && k == least;
                 const uint64_t who = __ballot(in);
-                if (in) put(base + before + __popcll(who & left), i, k);
+                if (in) put(base + before + lanes_before(who), i, k);
                 before += __popcll(who);
             });
         } else if (m > 0) {
-            const int nc = (m + ORDER_THREADS - 1) / ORDER_THREADS, first = wv * 64 * nc + lane;    // this wave's slice: nc chunks of 64
-            uint32_t key[MAXC], least = 0xFFFFFFFFu, most = 0u;
-            if (WHOLE) {
-#pragma unroll
-                for (int c = 0; c < MAXC; ++c) {
-                    const int p = first + 64 * c;
-                    if (c < nc) key[c] = desc_key(src[p < m ? p : m - 1]);
-                }
-#pragma unroll
-                for (int c = 0; c < MAXC; ++c) {
-                    const int p = first + 64 * c;
-                    if (c < nc && p < m) { keys[p] = key[c]; line[p] = p; }
-                }
-            } else {
-                read([&](int i, uint32_t k, bool any) {
-                    const bool in = any && k - lo <= span;
-                    const uint64_t who = __ballot(in);
-                    const int at = before + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u));
-                    if (in) { keys[at] = k; line[at] = i; }
-                    before += __popcll(who);
-                });
-                __syncthreads();
-#pragma unroll
-                for (int c = 0; c < MAXC; ++c)
-                    if (c < nc) { const int p = first + 64 * c; key[c] = keys[p < m ? p : m - 1]; }
-            }
-#pragma unroll
-            for (int c = 0; c < MAXC; ++c)
-                if (c < nc) { least = key[c] < least ? key[c] : least; most = key[c] > most ? key[c] : most; }
-            least = lanes_min(least); most = lanes_max(most);
-            if (lane == 63) { sync.red[0][wv] = least; sync.red[1][wv] = most; }
-            for (int i = tid; i < FINE / 2; i += ORDER_THREADS) words[i] = 0u;
+            for (int i = tid; i <= FINE / 2; i += ORDER_THREADS) words[i] = 0u;
             coarse[tid] = 0u;
-            __syncthreads();
-            least = sync.red[0][0]; most = sync.red[1][0];
-#pragma unroll
-            for (int w = 1; w < ORDER_WAVES; ++w) { const uint32_t t = sync.red[0][w], u = sync.red[1][w]; least = t < least ? t : least; most = u > most ? u : most; }
+            if (WHOLE) {
+                for (int p = tid; p < m; p += ORDER_THREADS) { const uint32_t k = desc_key(src[p]); keys[p] = k; extremes(k, true); }
+            } else {
+                if (!ends)
+                    read([&](int i, uint32_t k, bool any) {
+                        const bool in = any && k - lo <= span;
+                        const uint64_t who = __ballot(in);
+                        const int at = before + lanes_before(who);
+                        if (in) { keys[at] = k; line[at] = (uint16_t)i; }
+                        if ((i & 0xFFFF) == 0 && any) sync.cross[i >> 16] = before;
+                        before += __popcll(who);
+                    });
+                __syncthreads();
+                for (int p = tid; p < m; p += ORDER_THREADS) extremes(keys[p], true);
+            }
+            agree();
+            const int c1 = sync.cross[1], c2 = sync.cross[2], c3 = sync.cross[3];
+            auto line_at = [&](int p) -> int {             // (index of the p-th line of the range)
+                if (WHOLE) return p;
+                return (int)line[p] + (n > 65536 ? (p >= c1 ? 65536 : 0) + (p >= c2 ? 65536 : 0) + (p >= c3 ? 65536 : 0) : 0);
+            };
             const int width = __builtin_amdgcn_readfirstlane(width_of(most - least));
-            bool sorted = width == 0;                      // equal weights: the order is there
-            if (!sorted) {
+            if (width == 0) {                              // equal weights: the order is there
+                for (int p = tid; p < m; p += ORDER_THREADS) put(base + p, line_at(p), least);
+            } else {
                 // 1024 coarse bins of equal span, and of each as many fine bins of equal span as it has lines (or a few times
                 // that): a fine bin then has about one line wherever the weights crowd
-                const int sh = width > 10 ? width - 10 : 0, times = FINE / m;
-                uint32_t bin[MAXC];                        // fine bin | lines met there before << 16
-#pragma unroll
-                for (int c = 0; c < MAXC; ++c)
-                    if (c < nc && first + 64 * c < m) atomicAdd(&coarse[(key[c] - least) >> sh], 1u);
+                const int sh = width > 10 ? width - 10 : 0, place_sh = 32 - width_of((uint32_t)m - 1u);
+                const uint32_t times = (uint32_t)(FINE / m);
+                for (int p = tid; p < m; p += ORDER_THREADS) {                  // (lines of the first lane's bin at once: all may be in one)
+                    const uint32_t c = (keys[p] - least) >> sh;
+                    const bool same = c == (uint32_t)__builtin_amdgcn_readfirstlane((int)c);
+                    const uint64_t who = __ballot(same);
+                    if (!same || lanes_before(who) == 0) atomicAdd(&coarse[c], same ? (uint32_t)__popcll(who) : 1u);
+                }
                 __syncthreads();
                 uint32_t all;
-                const uint32_t mine = coarse[tid], ahead_of = order_scan(mine, sync.red[0], lane, wv, all);
-                coarse[tid] = ahead_of * (uint32_t)times | (mine * (uint32_t)times) << 16;      // (at most 16384: first bin below it or no line, number)
+                const uint32_t mine = coarse[tid], ahead_of = order_scan(mine, sync.red[2], lane, wv, all);
+                coarse[tid] = ahead_of * times | (mine * times) << 16;      // (at most 16384: first bin below it or no line, number)
                 __syncthreads();
-#pragma unroll
-                for (int c = 0; c < MAXC; ++c)
-                    if (c < nc && first + 64 * c < m) {
-                        const uint32_t d = key[c] - least, w = coarse[d >> sh];
-                        const uint32_t f = (w & 0xFFFFu) + (sh ? __umulhi(d << (32 - sh), w >> 16) : 0u);
-                        const uint32_t old = atomicAdd(&words[f >> 1], 1u << (16 * (f & 1u)));
-                        bin[c] = f | ((old >> (16 * (f & 1u))) & 0xFFFFu) << 16;
-                    }
-                __syncthreads();
-                {                                          // where each fine bin begins
-                    uint32_t t[PT], sum = 0u, fullest = 0u;
-#pragma unroll
-                    for (int j = 0; j < PT; ++j) t[j] = words[PT * tid + j];
-#pragma unroll
-                    for (int j = 0; j < PT; ++j) {
-                        const uint32_t x = t[j] & 0xFFFFu, y = t[j] >> 16;
-                        sum += x + y; fullest = x > fullest ? x : fullest; fullest = y > fullest ? y : fullest;
-                    }
-                    uint32_t at = order_scan(sum, sync.red[1], lane, wv, all);
-#pragma unroll
-                    for (int j = 0; j < PT; ++j) {
-                        words[PT * tid + j] = at | (at + (t[j] & 0xFFFFu)) << 16;
-                        at += (t[j] & 0xFFFFu) + (t[j] >> 16);
-                    }
-                    if (tid == ORDER_THREADS - 1) fine[FINE] = (uint16_t)m;
-                    sorted = !__syncthreads_or(fullest > (uint32_t)ORDER_FULL);
-                }
-                if (sorted) {
-#pragma unroll
-                    for (int c = 0; c < MAXC; ++c)
-                        if (c < nc && first + 64 * c < m) {
-                            const uint32_t at = (uint32_t)fine[bin[c] & 0xFFFFu] + (bin[c] >> 16);
-                            keys[at] = key[c]; ids[at] = (uint16_t)(first + 64 * c);
+                // The 18 bits tell all keys of a bin apart where its coarse bin has so many fine ones, and always in later spreads, whose
+                // bins span less than 2^18 numbers.
+                const uint32_t tell = sh > 18 ? 1u << (sh - 18) : 0u;
+                for (bool again = false;; again = true) {
+                    // fine bin of line p | DONE | EQUAL, and how far into the bin it lies, in 2^-32 of it
+                    auto locate = [&](int p, uint32_t& into) -> uint32_t {
+                        uint32_t first, lines, step, flags = 0u;
+                        if (!again) {
+                            const uint32_t d = keys[p] - least, w = coarse[d >> sh];
+                            first = w & 0xFFFFu; lines = w >> 16; step = sh ? d << (32 - sh) : 0u;
+                        } else {
+                            const uint32_t x = bins[p], at = x & PLACE, s = at / (ORDER_FULL + 1);
+                            first = at * times; into = 0u;
+                            if (x & DONE) return first | DONE;
+                            const uint32_t low = coarse[s], wide = coarse[ORDER_SEGS + s] - low;
+                            lines = sync.lines[s] * times;
+                            step = wide ? (keys[p] - low) << (32 - width_of(wide)) : (uint32_t)p << place_sh;
+                            flags = wide ? 0u : EQUAL;
                         }
-                    __syncthreads();
-                    // a line's place in its bin: the lines of it that go before (four at once; the places behind the bin are other
-                    // lines', or behind all keys other words of LDS, and do not count)
-#pragma unroll
-                    for (int c = 0; c < MAXC; ++c)
-                        if (c < nc && first + 64 * c < m) {
-                            const uint32_t f = bin[c] & 0xFFFFu, from = fine[f], to = fine[f + 1];
-                            uint32_t at = from;
-                            for (uint32_t q = from; q < to; q += 4) {
-                                uint32_t k[4];
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) k[e] = keys[q + e];
-                                bool equal = false;
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) { at += q + e < to && k[e] < key[c] ? 1u : 0u; equal = equal || (q + e < to && k[e] == key[c] && q + e != from + (bin[c] >> 16)); }
-                                if (equal)
-                                    for (uint32_t e = q; e < q + 4 && e < to; ++e) at += keys[e] == key[c] && (int)ids[e] < first + 64 * c ? 1u : 0u;
-                            }
-                            bin[c] = at;
-                        }
-                    int own[MAXC];
-#pragma unroll
-                    for (int c = 0; c < MAXC; ++c) if (c < nc && first + 64 * c < m) own[c] = line[first + 64 * c];
-                    __syncthreads();
-#pragma unroll
-                    for (int c = 0; c < MAXC; ++c)
-                        if (c < nc && first + 64 * c < m) { keys[bin[c]] = key[c]; line[bin[c]] = own[c]; }
-                } else {
-                    for (int i = tid; i < ORDER_FINE / 2; i += ORDER_THREADS) words[i] = 0u;
-                    __syncthreads();
-                }
-            }
-            // many equal weights, or weights that crowd beyond that: digit by digit
-            const int passes = sorted ? 0 : (width + 9) / 10, bits = passes ? (width + passes - 1) / passes : 0;
-            const uint32_t mask = (1u << bits) - 1u;
-            uint16_t id[MAXC];
-#pragma unroll
-            for (int c = 0; c < MAXC; ++c) id[c] = (uint16_t)(first + 64 * c);
-            for (int p = 0; p < passes; ++p) {
-                const int shift = p * bits;
-                if (p > 0) {
-                    __syncthreads();                       // the order so far is whole
-                    for (int i = tid; i < ORDER_WAVES * 512; i += ORDER_THREADS) words[i] = 0u;
-#pragma unroll
-                    for (int c = 0; c < MAXC; ++c)
-                        if (c < nc) { const int q = first + 64 * c < m ? first + 64 * c : m - 1; key[c] = keys[q]; id[c] = ids[q]; }
-                    __syncthreads();
-                }
-#pragma unroll
-                for (int c = 0; c < MAXC; ++c)
-                    if (c < nc && first + 64 * c < m) {
-                        const uint32_t dg = ((key[c] - least) >> shift) & mask;
-                        atomicAdd(&words[wv * 512 + (dg >> 1)], 1u << (16 * (dg & 1u)));
-                    }
-                __syncthreads();
-                {                                          // first place of every wave's lines of digit tid
-                    uint32_t cnt[ORDER_WAVES], sum = 0u, all;
-#pragma unroll
-                    for (int w = 0; w < ORDER_WAVES; ++w) cnt[w] = hist[w][tid];
-#pragma unroll
-                    for (int w = 0; w < ORDER_WAVES; ++w) sum += cnt[w];
-                    uint32_t at = order_scan(sum, sync.red[p & 1], lane, wv, all);
-#pragma unroll
-                    for (int w = 0; w < ORDER_WAVES; ++w) { hist[w][tid] = (uint16_t)at; at += cnt[w]; }
-                }
-                __syncthreads();
-                // (the wave's counters are read and written with relaxed atomics: plain LDS accesses that the compiler keeps
-                // in program order around the wave barriers)
-                uint16_t* mine = hist[wv];
-#pragma unroll
-                for (int c = 0; c < MAXC; ++c) {
-                    if (c >= nc) break;
-                    const bool in = first + 64 * c < m;
-                    const uint32_t dg = ((key[c] - least) >> shift) & mask;
-                    // lanes whose digit differs from mine in some bit: bit b of the lanes' digits as a wave mask, against
-                    // my own bit b spread over a word; diff | (ballot ^ mine) is one instruction (truth table 0xF6)
-                    const uint64_t none = ~__ballot(in);
-                    uint32_t diff_lo = (uint32_t)none, diff_hi = (uint32_t)(none >> 32);
-                    auto bit = [&](int q) {
-                        const uint32_t t = (uint32_t)((int32_t)(dg << (31 - q)) >> 31);  // 0 or ~0
-                        const uint64_t bal = __ballot(t != 0u);
-                        diff_lo = __builtin_amdgcn_bitop3_b32(diff_lo, (uint32_t)bal, t, 0xF6);
-                        diff_hi = __builtin_amdgcn_bitop3_b32(diff_hi, (uint32_t)(bal >> 32), t, 0xF6);
+                        const uint64_t x = (uint64_t)step * lines;
+                        into = (uint32_t)x;
+                        return (first + (uint32_t)(x >> 32)) | flags;
                     };
+                    auto meet = [&](uint32_t f) -> uint32_t {                  // its count goes up by one
+                        const uint32_t h = (f & PLACE) + 1u;
+                        return atomicAdd(&words[h >> 1], 1u << (16 * (h & 1u))) >> (16 * (h & 1u)) & 0xFFFFu;
+                    };
+                    for (int p = tid; p < m; p += ORDER_THREADS) { uint32_t into; meet(locate(p, into)); }
+                    __syncthreads();
+                    bool full;
+                    {                                      // where each fine bin begins
+                        uint32_t t[PT], sum = 0u, fullest = 0u;
 #pragma unroll
-                    for (int q = 0; q < 7; ++q) bit(q);
-                    if (bits > 7) { bit(7); if (bits > 8) { bit(8); if (bits > 9) bit(9); } }
-                    const uint64_t peers = ~(((uint64_t)diff_hi << 32) | diff_lo);
-                    const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(peers >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)peers, 0u));
-                    const uint32_t pos = (uint32_t)__atomic_load_n(&mine[dg], __ATOMIC_RELAXED) + rank;
-                    __builtin_amdgcn_wave_barrier();
-                    if (in) { keys[pos] = key[c]; ids[pos] = id[c]; }
-                    if (in && rank == 0u) __atomic_store_n(&mine[dg], (uint16_t)(pos + (uint32_t)__popcll(peers)), __ATOMIC_RELAXED);
-                    __builtin_amdgcn_wave_barrier();
+                        for (int j = 0; j < PT; ++j) t[j] = words[PT * tid + j];
+                        const uint32_t very_last = words[FINE / 2];
+#pragma unroll
+                        for (int j = 0; j < PT; ++j) {
+                            const uint32_t x = t[j] & 0xFFFFu, y = t[j] >> 16;
+                            sum += x + y; fullest = x > fullest ? x : fullest; fullest = y > fullest ? y : fullest;
+                        }
+                        fullest = very_last > fullest ? very_last : fullest;
+                        // (with it, above the lines, how many threads saw too full a bin)
+                        uint32_t at = order_scan(sum | (fullest > (uint32_t)ORDER_FULL ? 0x10000u : 0u), sync.red[again ? 0 : 1], lane, wv, all) & 0xFFFFu;
+                        full = all >> 16 != 0u;
+#pragma unroll
+                        for (int j = 0; j < PT; ++j) {
+                            words[PT * tid + j] = at | (at + (t[j] & 0xFFFFu)) << 16;
+                            at += (t[j] & 0xFFFFu) + (t[j] >> 16);
+                        }
+                        if (tid == ORDER_THREADS - 1) words[FINE / 2] = at;
+                        __syncthreads();
+                    }
+                    for (int p = tid; p < m; p += ORDER_THREADS) {
+                        uint32_t into;
+                        const uint32_t f = locate(p, into);
+                        spread[meet(f)] = (into & ~PLACE) | (uint32_t)p;
+                        bins[p] = (uint16_t)f;
+                    }
+                    __syncthreads();
+                    // a line's place in its bin: the lines of it that go before, four at once.  Their keys are looked at only where they are
+                    // as far into it to 18 bits.
+                    bool more = false;
+                    for (int q = tid; q < m; q += ORDER_THREADS) {
+                        const uint32_t self = spread[q], p = self & PLACE, x = bins[p], f = x & PLACE;
+                        const uint32_t from = fine[f], to = fine[f + 1];
+                        if (x & DONE) { bins[p] = (uint16_t)(from | DONE); continue; }
+                        if (to - from > (uint32_t)ORDER_FULL && !(x & EQUAL)) {
+                            bins[p] = (uint16_t)from;
+                            sync.lines[from / (ORDER_FULL + 1)] = (uint16_t)(to - from);
+                            more = true;
+                            continue;
+                        }
+                        uint32_t at = from;
+                        if (to - from > 1u) {
+                            uint32_t nearest = 0xFFFFFFFFu;            // least difference, but one, to another line: below PLACE if the 18 bits are the same
+                            uint32_t o[4], r = from;
+                            auto tally = [&]() {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    at += o[e] < self ? 1u : 0u;
+                                    const uint32_t z = (o[e] ^ self) - 1u;
+                                    nearest = z < nearest ? z : nearest;
+                                }
+                            };
+                            for (; r + 4u <= to; r += 4u) {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) o[e] = spread[r + e];
+                                tally();
+                            }
+                            if (r < to) {
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) { const uint32_t y = spread[r + e]; o[e] = r + e < to ? y : self; }
+                                tally();
+                            }
+                            const uint32_t k = keys[p];
+                            if (nearest < PLACE && !again && coarse[(k - least) >> sh] >> 16 < tell) {
+                                for (r = from; r < to; ++r) {
+                                    const uint32_t y = spread[r];
+                                    if ((y ^ self) - 1u >= PLACE) continue;
+                                    const uint32_t j = keys[y & PLACE];
+                                    at += j == k ? 0u : (j < k ? 1u : 0u) - (y < self ? 1u : 0u);
+                                }
+                            }
+                        }
+                        if (full) bins[p] = (uint16_t)(at | DONE);
+                        put(base + (int)at, line_at((int)p), keys[p]);
+                    }
+                    if (!full || !__syncthreads_or(more)) break;           // (too full a bin may have been one of equal keys)
+                    // Bins with more lines than are ranked against each other: each is spread once more over as many bins as it has
+                    // lines (or a few times that), by equal steps from its least key to its largest, or if all its keys are equal, by
+                    // place.  (Each time the least and the largest part, so it ends; of equal keys no bin gets many more than the root of
+                    // `cap`.)  Such bins begin more than ORDER_FULL places apart, which numbers them.
+                    for (int i = tid; i <= FINE / 2; i += ORDER_THREADS) words[i] = 0u;
+                    for (int p = tid; p < m; p += ORDER_THREADS) {
+                        const uint32_t x = bins[p], s = x / (ORDER_FULL + 1);
+                        if (!(x & DONE)) { coarse[s] = keys[p]; coarse[ORDER_SEGS + s] = keys[p]; }
+                    }
+                    __syncthreads();
+                    for (int p = tid; p < m; p += ORDER_THREADS) {
+                        const uint32_t x = bins[p], s = x / (ORDER_FULL + 1), k = keys[p];
+                        if (!(x & DONE)) {
+                            if (k < __atomic_load_n(&coarse[s], __ATOMIC_RELAXED)) atomicMin(&coarse[s], k);
+                            if (k > __atomic_load_n(&coarse[ORDER_SEGS + s], __ATOMIC_RELAXED)) atomicMax(&coarse[ORDER_SEGS + s], k);
+                        }
+                    }
+                    __syncthreads();
                 }
             }
-            __syncthreads();
-            for (int i = tid; i < m; i += ORDER_THREADS) put(base + i, line[passes ? (int)ids[i] : i], keys[i]);
         }
         base += m;
         if (hi == end) break;
-        lo = hi + 1u; hi = end;
+        lo = hi + 1u; hi = end; ends = false;
     }
 }
 
@@ -1785,9 +1911,9 @@ static void launch_emit(const SelectArgs& a, hipStream_t st) {
     if (a.n > EMIT_LINES) hipLaunchKernelGGL(emit_kernel, dim3(2, a.BH), dim3(1024), (size_t)((a.n + 31) / 32) * 4, st, a);
 }
 // Ranges of 8192 lines, a fifth less than a workgroup takes (the samples miss by 4 % at most; beyond 65536 lines by more, and a halved
-// range counts again), and more of them, down to 512 lines, as long as there are compute units for one each: 16 heads of
-// 5003 lines 29.8 us in 8 ranges, 33.2 in one; 512 workgroups instead of 256 take turns: 32 heads of 32768 lines 71.4 -> 88.3.
-// One range up to 4096 lines saves the look for its bounds: 32 heads of 4096 lines 26.1 -> 25.0, of 8192 36.9 -> 41.9.
+// range counts again), and more of them, down to 512 lines, as long as there are compute units for one each: 8 heads of 8192 lines
+// 33.2 us in 16 ranges, 36.7 in one; 512 workgroups instead of 256 take turns: 32 heads of 32768 lines 63.0 -> 75.5, of 8192 36.6 -> 45.8.
+// One range up to 4096 lines saves the look for its bounds: 32 heads of 4096 lines 25.7 -> 24.1, of 8192 36.6 -> 38.5.
 static hipError_t sort_lines(const SelectArgs& a, hipStream_t st) {
     int64_t nb = 1;
     if (a.n > ORDER_ONE) {
@@ -1800,11 +1926,11 @@ static hipError_t sort_lines(const SelectArgs& a, hipStream_t st) {
     if (chunks > ORDER_CHUNKS) chunks = ORDER_CHUNKS;
     const int cap = (int)chunks * 1024;
     const dim3 grid(2 * (unsigned)a.BH, (unsigned)nb);
-    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(ORDER_THREADS), order_lds_bytes(cap), st, a, (int)nb, cap); };
-    if (a.n <= 1024) launch(&order_kernel<1, true>);
-    else if (a.n <= ORDER_ONE) launch(&order_kernel<4, true>);
-    else if (cap <= 4096) launch(&order_kernel<4, false>);
-    else launch(&order_kernel<ORDER_CHUNKS, false>);
+    auto launch = [&](auto kernel, int pt) { hipLaunchKernelGGL(kernel, grid, dim3(ORDER_THREADS), order_lds_bytes(pt, cap), st, a, (int)nb, cap); };
+    if (a.n <= 1024) launch(&order_kernel<1, true>, 1);
+    else if (a.n <= ORDER_ONE) launch(&order_kernel<4, true>, 4);
+    else if (cap <= 4096) launch(&order_kernel<4, false>, 4);
+    else launch(&order_kernel<8, false>, 8);
     return hipGetLastError();
 }
 
@@ -1813,7 +1939,7 @@ hipError_t init_select_kernels() {
     if ((e = allow_full_lds(&order_kernel<1, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&order_kernel<4, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&order_kernel<4, false>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&order_kernel<ORDER_CHUNKS, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<8, false>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_kernel<4>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_kernel<8>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_kernel<16>)) != hipSuccess) return e;

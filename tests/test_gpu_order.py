@@ -1,5 +1,5 @@
 """Desc_Sort inside ls_select, where a list is put in order in several ranges of weights: the lengths at which their number
-changes, and weights that miss the ranges' usual course.  The oracle's selection exactly; `accounted` is a running sum
+changes, and weights that miss the ranges' usual course or fill single bins.  The oracle's selection exactly; `accounted` is a running sum
 over the picks, so it shows their order."""
 import numpy as np
 import pytest
@@ -21,6 +21,15 @@ KINDS = {
     "equal": lambda rng, n: np.where(rng.random(n) < 0.67, 0.25, rng.integers(1, 60, n) / 64.0),
     # all but a handful within 2^12 numbers: the bins of the outliers' ranges hold hundreds of lines each
     "crowd": lambda rng, n: np.where(rng.random(n) < 10 / n, np.exp2(rng.uniform(-60, 20, n)), 0.5 + rng.integers(0, 4096, n) * 2.0 ** -24),
+    # few weights, each of hundreds of lines and more; two fifths of the lines at zero, in runs
+    "few": lambda rng, n: rng.integers(1, 60, n) / 64.0,
+    "zeros": lambda rng, n: np.where(np.arange(n) // 997 % 5 < 2, 0.0, np.exp2(rng.uniform(-20, 0, n))),
+    # clusters inside clusters: each eighth of the lines lies within a 2^-6 of the span that is left
+    "nested": lambda rng, n: 0.5 + np.ldexp(rng.integers(1, 1 << 6, n).astype(float), -np.minimum(6 * (1 + rng.geometric(0.4, n) % 4), 24)),
+    # one weight; two; one beside a single other
+    "one": lambda rng, n: np.full(n, 0.125),
+    "two": lambda rng, n: np.where(rng.random(n) < 0.5, 0.125, 0.25),
+    "but_one": lambda rng, n: np.where(np.arange(n) == n // 2, 3.0, 0.125),
     # every sampled line far above the others: the ranges found for them hold nearly nothing or nearly everything
     "unseen": lambda rng, n: np.where(np.isin(np.arange(n), _sampled(n)), rng.uniform(1, 2, n), rng.uniform(0.01, 0.02, n)),
 }
@@ -29,13 +38,16 @@ KINDS = {
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,kind", [(4096, "crowd"), (4096, "spread"), (4097, "spread"), (4097, "crowd"), (8193, "equal"), (30011, "spread"),
                                     (30011, "equal"), (30011, "crowd"), (65536, "spread"), (65537, "unseen"), (65537, "spread"), (20000, "unseen"),
-                                    (2049, "spread"), (16383, "spread"), (16384, "equal")])
-def test_lists_in_ranges(oracle, n, kind):
+                                    (2049, "spread"), (16383, "spread"), (16384, "equal"),
+                                    (33, "one"), (700, "crowd"), (1024, "few"), (1000, "two"), (1024, "nested"), (4096, "few"), (4096, "zeros"), (4095, "but_one"),
+                                    (4096, "nested"), (8192, "zeros"), (8192, "few"), (8191, "two"), (10240, "nested"), (30011, "few"), (30011, "zeros"),
+                                    (30011, "two"), (30011, "one"), (30011, "but_one"), (30011, "nested"), (131071, "few"), (131071, "equal"),
+                                    (65537, "zeros"), (65537, "crowd")])
+def test_lists_in_ranges(oracle, n, kind, H=3):
     from tests.gpu_util import host
     from tests.test_gpu_configs import check_selection_exact
     print(f"lists in ranges n={n} {kind}", flush=True)
     rng = np.random.default_rng(n)
-    H = 3
     v, s = (np.stack([KINDS[kind](rng, n) for _ in range(H)])[None] for _ in range(2))
     v = v.copy(); s = s.copy()
     s[:, 1] *= 1e-3; v[:, 0] *= 1e-3                                  # one head of columns, one of diagonals, one of both
@@ -53,3 +65,10 @@ def test_lists_in_ranges(oracle, n, kind):
         gpu = host(out)
         check_selection_exact(gpu, ref)
         np.testing.assert_array_equal(gpu["accounted"], ref["accounted"])
+
+
+# so many heads that there is one range a list, beyond the length that always is
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,kind", [(4097, "spread"), (5003, "few"), (6000, "zeros"), (8192, "crowd"), (8192, "equal")])
+def test_long_lists_of_many_heads(oracle, n, kind):
+    test_lists_in_ranges(oracle, n, kind, H=130)
