@@ -754,9 +754,14 @@ __device__ __forceinline__ int chain_lds(const float* gains, int lane, int limit
 constexpr int WALK_THREADS = 384;              // wave 0 decides the runs, wave 2 sums them; per list, waves 1 / 3 stage its
                                                // weights and lengths and waves 4 / 5 its overlap prefix sums
 // A lane looks at E list entries: a run has up to 64 E picks.  Short lists have short runs, long ones long: 4 / 8 / 16, ls_select of
-// 32 heads, us: 2048 lines 22.9 / 25.1 / 29.5, 4096 25.0 / 24.6 / 26.2, 12347 39.3 / 39.8 / 40.7, 16384 60.3 / 52.3 / 50.3, 32768 81.3 / 71.2 / 67.6,
-// 65536 164 / 141 / 134; 256 heads of 1500 lines 29.6 / 31.7 / 37.2.
+// 32 heads, us: 2048 lines 22.0 / 23.1 / 24.3, 4096 24.2 / 24.0 / 25.3, 12347 34.9 / 35.5 / 36.4, 16384 56.2 / 49.3 / 45.7, 32768 76.8 / 67.2 / 63.1,
+// 65536 157 / 137 / 128; 256 heads of 1500 lines 27.5 / 29.0 / 29.9.
 constexpr int64_t WALK_SHORT = 2048, WALK_LONG = 16384;        // up to: 4; from: 16
+// Where the picks go back and forth between the lists a run is one or a few, and its price is that of looking at all E entries: the
+// waves then look at these few only, from a run of up to half of what they hold until one fills them.  The walk alone with E entries
+// throughout / now, 32 heads of 32768 lines, us: runs of one to five picks 76.5 / 52.2, of one 489 / 308, one run to the end 18.8 / 17.9; 8192
+// lines 24.9 / 23.5, 95.8 / 83.9, 10.9 / 11.1.  (Eight entries a lane throughout: 55.5, 346, 15.6.)
+constexpr int WALK_NARROW = 4;
 constexpr int WALK_NBLK = 4;                   // blocks of a list resident in LDS (a ring over sorted positions)
 constexpr int WALK_CAP = WALK_BLK * WALK_NBLK;
 constexpr int WALK_EB = WALK_BLK / 64;         // entries per lane when a block's prefix sums are added
@@ -769,6 +774,10 @@ template <int E> struct WalkList { float cw[WALK_CAP + 64 * E], cl[WALK_CAP + 64
 // One run of picks from one list: the gain of each pick, how many of them count, and whether the walk ends
 // after them because no line is left that adds anything.
 template <int E> struct WalkRun { float g[64 * E]; int which, limit, last, pad; };
+// What the lanes need of a list when its head is at `h`: lane l looks at the entries h + l, h + 64 + l, ... (weight,
+// overlap prefix, length; whatever lies there past the end of the list), every lane at the head's own three values.
+// Re-read only when the head of that list moves.  (All of them lie in the head's block or the one after it.)
+template <int N> struct WalkView { float cw[N], pre[N], cl[N], w0, l0, ol0; };
 struct WalkSync { int staged[2], summed_blk[2], cur[2], summed, stop, done, err, runs, decided, cnt_s, cnt_v; float tot[2]; };
 static_assert(offsetof(WalkSync, summed) % 8 == 0 && offsetof(WalkSync, stop) == offsetof(WalkSync, summed) + 4, "summed and stop are read as one 8-byte word");   // tot: a list's whole overlap sum
 constexpr int WALK_RING = 4;                   // runs decided ahead of the running sum
@@ -1025,18 +1034,24 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             const int which = __builtin_amdgcn_readfirstlane(R.which);
             const int limit = __builtin_amdgcn_readfirstlane(R.limit);
             const int last = __builtin_amdgcn_readfirstlane(R.last);
-            float g[E];
-#pragma unroll
-            for (int e = 0; e < E; e += 2) {
-                const float2 t = *reinterpret_cast<const float2*>(&R.g[E * lane + e]);
-                g[e] = E * lane + e < limit ? t.x : 0.f; g[e + 1] = E * lane + e + 1 < limit ? t.y : 0.f;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // the slot may be written again
-            ++k;
-            if (lane == 0) walk_st(&sync->summed, k);
             // pick by pick, as the loop of the definition adds them; it stops after the pick that reaches the target
             // (one addition after the other took 3900 cycles a run)
-            const int taken = chain_until<E>(g, lane, limit, target, sum);
+            int taken;
+            auto add = [&](auto ENTRIES) {
+                constexpr int N = decltype(ENTRIES)::value;
+                float g[N];
+#pragma unroll
+                for (int e = 0; e < N; e += 2) {
+                    const float2 t = *reinterpret_cast<const float2*>(&R.g[N * lane + e]);
+                    g[e] = N * lane + e < limit ? t.x : 0.f; g[e + 1] = N * lane + e + 1 < limit ? t.y : 0.f;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");     // the slot may be written again
+                ++k;
+                if (lane == 0) walk_st(&sync->summed, k);
+                taken = chain_until<N>(g, lane, limit, target, sum);
+            };
+            if (E > WALK_NARROW && limit <= 64 * WALK_NARROW) add(std::integral_constant<int, WALK_NARROW>{});
+            else add(std::integral_constant<int, E>{});
             const bool reached = !(sum < target);
             cnt_s += which == 0 ? taken : 0;
             cnt_v += which == 0 ? 0 : taken;
@@ -1078,21 +1093,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
         return have;
     };
 
-    // What the lanes need of a list when its head is at `h`: lane l looks at the entries h + l, h + 64 + l, ... (weight,
-    // overlap prefix, length; whatever lies there past the end of the list), every lane at the head's own three values.
-    // Re-read only when the head of that list moves.  (All of them lie in the head's block or the one after it.)
-    struct View { float cw[E], pre[E], cl[E], w0, l0, ol0; };
     auto lane0 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x))); };
-    auto view = [&](int l, int h) {
-        const List& L = lists[l];
-        View r;
-        const int at = (h & (WALK_CAP - 1)) + lane;
-#pragma unroll
-        for (int e = 0; e < E; ++e) { r.cw[e] = L.cw[at + 64 * e]; r.pre[e] = L.pre[at + 64 * e]; r.cl[e] = L.cl[at + 64 * e]; }
-        if (h < n) { r.w0 = lane0(r.cw[0]); r.l0 = lane0(r.cl[0]); r.ol0 = lane0(r.pre[0]); }
-        else { r.w0 = 0.f; r.l0 = 1.f; r.ol0 = lane0(sync->tot[l]); }      // an exhausted list: no weight, and its overlap sum
-        return r;                                                          // sits right behind its last line
-    };
     // blocks a view at head h reads: through the block of entry h + RUN - 1, and pre[h] itself
     auto blocks_for = [&](int h) {
         const int want = (h + RUN - 1) / WALK_BLK + 1;
@@ -1100,98 +1101,117 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
     };
     have_s = wait_blocks(0, blocks_for(0));
     have_v = wait_blocks(1, blocks_for(0));
-    View S = view(0, 0), V = view(1, 0);
 
-    while (!failed) {
-        if (is >= n && iv >= n) break;
-        // a head that has entered a new block frees the blocks behind it; a view that reaches into a block not
-        // known to be resident yet is read again once that block is
-        if (is / WALK_BLK != blk_s && is < n) {
-            blk_s = is / WALK_BLK;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // done reading the blocks left behind
-            if (lane == 0) walk_st(&sync->cur[0], blk_s);
-        }
-        if (iv / WALK_BLK != blk_v && iv < n) {
-            blk_v = iv / WALK_BLK;
+    // Decides run after run with N entries a lane, until the walk is over (false) or runs of another length would suit N better.
+    auto decide = [&](auto ENTRIES) -> bool {
+        constexpr int N = decltype(ENTRIES)::value;
+        using View = WalkView<N>;
+        auto view = [&](int l, int h) {
+            const List& L = lists[l];
+            View r;
+            const int at = (h & (WALK_CAP - 1)) + lane;
+#pragma unroll
+            for (int e = 0; e < N; ++e) { r.cw[e] = L.cw[at + 64 * e]; r.pre[e] = L.pre[at + 64 * e]; r.cl[e] = L.cl[at + 64 * e]; }
+            if (h < n) { r.w0 = lane0(r.cw[0]); r.l0 = lane0(r.cl[0]); r.ol0 = lane0(r.pre[0]); }
+            else { r.w0 = 0.f; r.l0 = 1.f; r.ol0 = lane0(sync->tot[l]); }  // an exhausted list: no weight, and its overlap sum
+            return r;                                                      // sits right behind its last line
+        };
+        View S = view(0, is), V = view(1, iv);
+        while (!failed) {
+            if (is >= n && iv >= n) break;
+            // a head that has entered a new block frees the blocks behind it; a view that reaches into a block not
+            // known to be resident yet is read again once that block is
+            if (is / WALK_BLK != blk_s && is < n) {
+                blk_s = is / WALK_BLK;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");     // done reading the blocks left behind
+                if (lane == 0) walk_st(&sync->cur[0], blk_s);
+            }
+            if (iv / WALK_BLK != blk_v && iv < n) {
+                blk_v = iv / WALK_BLK;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                if (lane == 0) walk_st(&sync->cur[1], blk_v);
+            }
+            if (is < n && have_s < blocks_for(is)) {
+                have_s = wait_blocks(0, blocks_for(is));
+                if (failed) break;
+                S = view(0, is);
+            }
+            if (iv < n && have_v < blocks_for(iv)) {
+                have_v = wait_blocks(1, blocks_for(iv));
+                if (failed) break;
+                V = view(1, iv);
+            }
+            // entry e of lane l: the decision if the walk has taken 64 e + l more slashes (iv frozen)
+            float gain[N];
+            bool turn[N];                     // the pick goes to the other list
+            const float fs = (float)is, fv = (float)iv;
+            int run = 0, which = 0;
+            if (is < n) {
+#pragma unroll
+                for (int e = 0; e < N; ++e) {
+                    const float ds = __fsub_rn(S.cw[e], V.ol0), dv = __fsub_rn(V.w0, S.pre[e]);
+                    const float cs = fmaxf(__fsub_rn(S.cl[e], fv), 1.0f), cv = fmaxf(__fsub_rn(V.l0, fs + (float)(64 * e + lane)), 1.0f);
+                    turn[e] = !(__fmul_rn(ds, cv) >= __fmul_rn(dv, cs));
+                    gain[e] = ds;
+                }
+                run = iv < n ? walk_first(turn) : 64 * N;
+                run = run < n - is ? run : n - is;
+            }
+            if (run == 0) {
+                // the head pick is a vertical; entry e of lane l: the decision if 64 e + l more verticals are taken (is frozen)
+                which = 1;
+#pragma unroll
+                for (int e = 0; e < N; ++e) {
+                    const float dv = __fsub_rn(V.cw[e], S.ol0), ds = __fsub_rn(S.w0, V.pre[e]);
+                    const float cv = fmaxf(__fsub_rn(V.cl[e], fs), 1.0f), cs = fmaxf(__fsub_rn(S.l0, fv + (float)(64 * e + lane)), 1.0f);
+                    turn[e] = __fmul_rn(ds, cv) >= __fmul_rn(dv, cs);      // not a vertical again
+                    gain[e] = dv;
+                }
+                run = is < n ? walk_first(turn) : 64 * N;
+                run = run < n - iv ? run : n - iv;
+            }
+            if (run == 0) break;                   // cannot happen (entry 0 of lane 0 repeats the head's test); never spin
+            // picks 0 .. run-1 come from list `which`; the walk ends early at a pick with no positive gain left
+            // (the gains of a run do not increase: none is 0 or less if the last entry's is not)
+            int stop_dead = 64 * N;
+            if (early && __ballot(!(gain[N - 1] > 0.f)) != 0ull) {
+                const bool has = which == 0 ? iv < n : is < n;
+                bool dead[N];                 // no gain is left in either list
+#pragma unroll
+                for (int e = 0; e < N; ++e)
+                    dead[e] = !(gain[e] > 0.f) && (!has || !((which == 0 ? __fsub_rn(V.w0, S.pre[e]) : __fsub_rn(S.w0, V.pre[e])) > 0.f));
+                stop_dead = walk_first(dead);
+            }
+            const int limit = run < stop_dead ? run : stop_dead;
+            // the list's view after the run (read again above if it reaches into a block that is not resident yet)
+            const View nxt = view(which, (which == 0 ? is : iv) + limit);
+            // hand the run over: a free slot of the ring, the gains, then the count of published runs
+            bool stopped = false;
+            int spins = 0;
+            for (;;) {                             // one read: runs taken out of the ring, and whether the walk is over
+                const unsigned long long ss = __atomic_load_n(static_cast<const unsigned long long*>(__builtin_assume_aligned(&sync->summed, 8)), __ATOMIC_RELAXED);
+                if (__builtin_amdgcn_readfirstlane((int)(ss >> 32))) { stopped = true; break; }
+                if (published - __builtin_amdgcn_readfirstlane((int)ss) < WALK_RING) break;
+                __builtin_amdgcn_s_sleep(1);
+                if (++spins > spin_limit || walk_ld(&sync->err)) { failed = true; break; }
+            }
+            if (stopped || failed) break;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            Run& R = ring[published & (WALK_RING - 1)];
+#pragma unroll
+            for (int e = 0; e < N; ++e) R.g[64 * e + lane] = gain[e];
+            if (lane == 0) { R.which = which; R.limit = limit; R.last = stop_dead < run ? 1 : 0; }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            if (lane == 0) walk_st(&sync->cur[1], blk_v);
+            ++published;
+            if (lane == 0) walk_st(&sync->runs, published);
+            if (stop_dead < run) break;            // nothing after this run can add to the sum
+            if (which == 0) { is += limit; S = nxt; } else { iv += limit; V = nxt; }
+            if (E > WALK_NARROW && (N == E ? limit <= 32 * WALK_NARROW : limit == 64 * WALK_NARROW)) return true;
         }
-        if (is < n && have_s < blocks_for(is)) {
-            have_s = wait_blocks(0, blocks_for(is));
-            if (failed) break;
-            S = view(0, is);
-        }
-        if (iv < n && have_v < blocks_for(iv)) {
-            have_v = wait_blocks(1, blocks_for(iv));
-            if (failed) break;
-            V = view(1, iv);
-        }
-        // entry e of lane l: the decision if the walk has taken 64 e + l more slashes (iv frozen)
-        float gain[E];
-        bool turn[E];                     // the pick goes to the other list
-        const float fs = (float)is, fv = (float)iv;
-        int run = 0, which = 0;
-        if (is < n) {
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const float ds = __fsub_rn(S.cw[e], V.ol0), dv = __fsub_rn(V.w0, S.pre[e]);
-                const float cs = fmaxf(__fsub_rn(S.cl[e], fv), 1.0f), cv = fmaxf(__fsub_rn(V.l0, fs + (float)(64 * e + lane)), 1.0f);
-                turn[e] = !(__fmul_rn(ds, cv) >= __fmul_rn(dv, cs));
-                gain[e] = ds;
-            }
-            run = iv < n ? walk_first(turn) : RUN;
-            run = run < n - is ? run : n - is;
-        }
-        if (run == 0) {
-            // the head pick is a vertical; entry e of lane l: the decision if 64 e + l more verticals are taken (is frozen)
-            which = 1;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const float dv = __fsub_rn(V.cw[e], S.ol0), ds = __fsub_rn(S.w0, V.pre[e]);
-                const float cv = fmaxf(__fsub_rn(V.cl[e], fs), 1.0f), cs = fmaxf(__fsub_rn(S.l0, fv + (float)(64 * e + lane)), 1.0f);
-                turn[e] = __fmul_rn(ds, cv) >= __fmul_rn(dv, cs);          // not a vertical again
-                gain[e] = dv;
-            }
-            run = is < n ? walk_first(turn) : RUN;
-            run = run < n - iv ? run : n - iv;
-        }
-        if (run == 0) break;                   // cannot happen (entry 0 of lane 0 repeats the head's test); never spin
-        // picks 0 .. run-1 come from list `which`; the walk ends early at a pick with no positive gain left
-        // (the gains of a run do not increase: none is 0 or less if the last entry's is not)
-        int stop_dead = RUN;
-        if (early && __ballot(!(gain[E - 1] > 0.f)) != 0ull) {
-            const bool has = which == 0 ? iv < n : is < n;
-            bool dead[E];                 // no gain is left in either list
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                dead[e] = !(gain[e] > 0.f) && (!has || !((which == 0 ? __fsub_rn(V.w0, S.pre[e]) : __fsub_rn(S.w0, V.pre[e])) > 0.f));
-            stop_dead = walk_first(dead);
-        }
-        const int limit = run < stop_dead ? run : stop_dead;
-        // the list's view after the run (read again above if it reaches into a block that is not resident yet)
-        const View nxt = view(which, (which == 0 ? is : iv) + limit);
-        // hand the run over: a free slot of the ring, the gains, then the count of published runs
-        bool stopped = false;
-        int spins = 0;
-        for (;;) {                             // one read: runs taken out of the ring, and whether the walk is over
-            const unsigned long long ss = __atomic_load_n(static_cast<const unsigned long long*>(__builtin_assume_aligned(&sync->summed, 8)), __ATOMIC_RELAXED);
-            if (__builtin_amdgcn_readfirstlane((int)(ss >> 32))) { stopped = true; break; }
-            if (published - __builtin_amdgcn_readfirstlane((int)ss) < WALK_RING) break;
-            __builtin_amdgcn_s_sleep(1);
-            if (++spins > spin_limit || walk_ld(&sync->err)) { failed = true; break; }
-        }
-        if (stopped || failed) break;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        Run& R = ring[published & (WALK_RING - 1)];
-#pragma unroll
-        for (int e = 0; e < E; ++e) R.g[64 * e + lane] = gain[e];
-        if (lane == 0) { R.which = which; R.limit = limit; R.last = stop_dead < run ? 1 : 0; }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        ++published;
-        if (lane == 0) walk_st(&sync->runs, published);
-        if (stop_dead < run) break;            // nothing after this run can add to the sum
-        if (which == 0) { is += limit; S = nxt; } else { iv += limit; V = nxt; }
-    }
+        return false;
+    };
+    bool wide = true;
+    while (wide ? decide(std::integral_constant<int, E>{}) : decide(std::integral_constant<int, (E < WALK_NARROW ? E : WALK_NARROW)>{})) wide = !wide;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (lane == 0) {
         if (failed) walk_st(&sync->err, 1);
