@@ -33,14 +33,15 @@ int ls_debug_set_walk_spin_limit(ls_ctx* ctx, int32_t limit);
 int ls_debug_set_counters(ls_ctx* ctx, int32_t value, void* hip_stream);
 
 /*
- * Copies to the host how the most recent ls_sparse_prefill call on this context shared its items among the XCDs:
- * its work queues, or in a call that needs none the items that begin on each XCD's workgroups (an item is one block of 128 query rows of one head): host_queue holds 8 arrays of
- * B * Hq * nqb words, (batch * Hq + head) << 16 | row block, of which the first host_qlen[x] are valid;
- * *nqb_out receives the number of row blocks per head.  `shape` must be that call's shape.  Waits for the
- * stream.  The tests use it to check that every item is there exactly once.
+ * Copies to the host how the most recent ls_sparse_prefill call on this context shared its items among the XCDs, as its kernels
+ * left it in the workspace: its work queues, or in a call that needs none the items that begin on each XCD's workgroups (an item is one
+ * block of 128 query rows of one head).  host_queue holds 8 arrays of B * Hq * nqb words, (batch * Hq + head) << 16 | row block, of
+ * which the first host_qlen[x] are valid; *nqb_out receives the number of row blocks per head, *cuts_out how many cuts go through items.
+ * `shape` must be that call's shape.  Waits for the stream.  The tests use it to check that every item is there exactly once, and
+ * that items are cut where the workspace has room for their parts.
  */
 int ls_debug_copy_prefill_queues(ls_ctx* ctx, const ls_shape* shape, uint32_t* host_queue, int32_t* host_qlen,
-                                 int32_t* nqb_out, void* hip_stream);
+                                 int32_t* nqb_out, int32_t* cuts_out, void* hip_stream);
 
 #ifdef __cplusplus
 }

@@ -404,7 +404,8 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
         w.queue = bp.take<uint4>(items + w.slots);
         w.rec = w.pieces ? reinterpret_cast<uint32_t*>(w.queue) : per_item;
         w.upto = w.pieces ? per_item : nullptr;
-        w.cuts = w.slots && w.pieces ? bp.take<int2>((size_t)w.grid + 1) : nullptr;
+        // (without slots there are no more pieces than items, and their cuts lie behind the records)
+        w.cuts = !w.pieces ? nullptr : w.slots ? bp.take<int2>((size_t)w.grid + 1) : reinterpret_cast<int2*>(w.rec + ((items + 1) & ~(size_t)1));
         w.split = w.slots && !w.pieces ? bp.take<uint2>((size_t)w.slots) : nullptr;
         w.part_o = w.slots ? bp.take<float>((size_t)w.slots * 128 * s->d) : nullptr;
         w.part_ml = w.slots ? bp.take<float>((size_t)w.slots * 128 * 2) : nullptr;
@@ -651,37 +652,47 @@ int ls_debug_set_counters(ls_ctx* c, int32_t value, void* stream) {
 }
 
 /* Debug / test hook: the items that the last ls_sparse_prefill call on this context gave to each XCD
- * (host_queue: [8][B*Hq*nqb] item words = (head << 16) | row block, host_qlen: [8]); synchronises the stream. */
-int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_queue, int32_t* host_qlen, int32_t* nqb_out, void* stream) {
-    if (!c || !s || !host_queue || !host_qlen || !nqb_out) return LS_EINVAL;
+ * (host_queue: [8][B*Hq*nqb] item words = (head << 16) | row block, host_qlen: [8]) and how often it cut one, as its kernels left
+ * them in the workspace; synchronises the stream. */
+int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_queue, int32_t* host_qlen, int32_t* nqb_out, int32_t* cuts_out, void* stream) {
+    if (!c || !s || !host_queue || !host_qlen || !nqb_out || !cuts_out) return LS_EINVAL;
     if (check_shape(s, true, false, true)) return LS_ESHAPE;
     PrefillCarve w;
     if (carve_prefill(c, s, w)) return w.code;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const size_t items = (size_t)s->B * s->Hq * w.nqb;
-    const size_t BH = (size_t)s->B * s->Hq;
-    std::vector<uint4> q;                                  // queues, or records
-    std::vector<uint32_t> upto, head;
-    std::vector<int> xcd;
-    try { q.resize(items + w.slots); upto.resize(items); head.resize(BH); xcd.resize(items); } catch (...) { return fail(c, LS_EHIP, "ls_debug_copy_prefill_queues: out of memory"); }
+    std::vector<uint4> q;
+    std::vector<int2> cuts;
+    try { q.resize(items + w.slots); cuts.resize((size_t)w.grid + 1); } catch (...) { return fail(c, LS_EHIP, "ls_debug_copy_prefill_queues: out of memory"); }
     int32_t misc[24];
     if (hipSetDevice(c->device) != hipSuccess) return LS_EHIP;
-    if (hipMemcpyAsync(q.data(), w.queue, q.size() * sizeof(uint4), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
-    if (w.pieces && hipMemcpyAsync(upto.data(), w.upto, items * 4, hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
-    if (hipMemcpyAsync(head.data(), w.head_work, BH * 4, hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
-    if (hipMemcpyAsync(misc, w.misc, sizeof(misc), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
-    if (hipStreamSynchronize(st) != hipSuccess) return LS_EHIP;
-    // an item in parts is listed once, by its first part
     auto word = [&](size_t i) { return (uint32_t)(i / w.nqb) << 16 | (uint32_t)(i % w.nqb); };
     for (int x = 0; x < 8; ++x) host_qlen[x] = 0;
+    *cuts_out = 0;
     if (w.pieces) {
-        ls::prefill_pieces(s->dtype, reinterpret_cast<const uint32_t*>(q.data()), upto.data(), head.data(), (int)BH, w.nqb, w.grid, w.slots, xcd.data());
-        for (size_t i = 0; i < items; ++i)
-            if (xcd[i] >= 0) host_queue[xcd[i] * items + host_qlen[xcd[i]]++] = word(i);
+        auto read = [&](int2* to, const int2* from, size_t count) {
+            return hipMemcpyAsync(to, from, count * sizeof(int2), hipMemcpyDeviceToHost, st) == hipSuccess && hipStreamSynchronize(st) == hipSuccess;
+        };
+        if (!read(cuts.data(), w.cuts, 1)) return LS_EHIP;
+        const int pieces = cuts[0].x;
+        if (pieces < 1 || pieces > w.grid) return fail(c, LS_EHIP, "ls_debug_copy_prefill_queues: no call of this shape came before");
+        if (!read(cuts.data(), w.cuts, 1 + (size_t)pieces)) return LS_EHIP;
+        // an item belongs to the piece on which it begins
+        for (int p = 0; p < pieces; ++p) {
+            const int x = ls::prefill_piece_xcd(p, pieces);
+            *cuts_out += cuts[1 + p].y > 0 ? 1 : 0;
+            const int2 from = cuts[1 + p], to = p + 1 < pieces ? cuts[2 + p] : make_int2((int)items, 0);
+            for (int64_t i = from.x + (from.y > 0 ? 1 : 0); i < to.x + (to.y > 0 ? 1 : 0); ++i)
+                if (i >= 0 && (size_t)i < items && (size_t)host_qlen[x] < items) host_queue[x * items + host_qlen[x]++] = word((size_t)i);
+        }
     } else {
-        for (int x = 0; x < 8; ++x)
+        if (hipMemcpyAsync(q.data(), w.queue, q.size() * sizeof(uint4), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
+        if (hipMemcpyAsync(misc, w.misc, sizeof(misc), hipMemcpyDeviceToHost, st) != hipSuccess) return LS_EHIP;
+        if (hipStreamSynchronize(st) != hipSuccess) return LS_EHIP;
+        for (int x = 0; x < 8; ++x)                        // an item in parts is listed once, by its first part
             for (int i = 0; i < misc[x] && (size_t)misc[16 + x] + i < q.size(); ++i) {
                 const uint4 e = q[(size_t)misc[16 + x] + i];
+                *cuts_out += (e.y & 0xFF) != 0 ? 1 : 0;
                 if ((e.y & 0xFF) == 0 && (size_t)host_qlen[x] < items) host_queue[x * items + host_qlen[x]++] = word(e.x);
             }
     }

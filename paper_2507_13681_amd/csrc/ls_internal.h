@@ -111,7 +111,7 @@ struct PrefillArgs {
     // pieces (ls_prefill.hip): at most `grid`
     const uint32_t* rec;
     const uint32_t *upto, *head_work;
-    int2* cuts;               // [grid + 1] where each piece begins {item, tile}; behind them their number (where slots > 0)
+    int2* cuts;               // [1 + pieces] their number, and where each piece begins {item, tile}
     // or work queues built by sched_kernel
     const uint4* queue;       // null: pieces
     const int32_t *qlen, *qbase;
@@ -191,7 +191,6 @@ bool prefill_in_pieces(int BH, int64_t n, int nqb, int d);               // the 
 int prefill_grid(int dtype, int d, int64_t items, bool pieces);
 int prefill_split_slots(int64_t items, int grid, bool pieces);      // parts' results that a call with so many (head, row block) items may use
 size_t prefill_slot_bytes(int d);
-// What the workgroups work out for themselves, on the host: the XCD on whose piece each item begins
-void prefill_pieces(int dtype, const uint32_t* rec, const uint32_t* upto, const uint32_t* head_work, int BH, int nqb, int grid, int slots, int* xcd_of_item);
+int prefill_piece_xcd(int p, int pieces);                                // XCD whose workgroup takes piece p
 
 }  // namespace ls

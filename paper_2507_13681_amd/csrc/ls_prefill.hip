@@ -438,9 +438,9 @@ __device__ __forceinline__ Span my_span(const PrefillArgs& a, uint32_t* sh) {   
     s.from = find(ub, cb, u0, c0, hb, rb, &rec);
     if (more) s.to = find(ue, ce, u1, c1, he, re, nullptr);
     s.rec = rec != 0xFFFFFFFFu || s.from.item >= items ? rec : a.rec[s.from.item];      // (a cut moved to the next item: its record)
-    if (a.slots > 0 && tid == 0) {                         // for combine_kernel
-        a.cuts[s.piece] = make_int2(s.from.item, s.from.tile);
-        if (s.piece == 0) a.cuts[a.grid] = make_int2(s.pieces, 0);
+    if (tid == 0) {                                        // for combine_kernel
+        a.cuts[1 + s.piece] = make_int2(s.from.item, s.from.tile);
+        if (s.piece == 0) a.cuts[0] = make_int2(s.pieces, 0);
     }
     return s;
 }
@@ -629,27 +629,10 @@ int prefill_split_slots(int64_t items, int grid, bool pieces) {
 }
 bool prefill_in_pieces(int BH, int64_t n, int nqb, int d) { return (int64_t)BH * nqb * ((n + BN - 1) / BN) * d <= PIECES_TILES * 128; }
 
-void prefill_pieces(int dtype, const uint32_t* rec, const uint32_t* upto, const uint32_t* head_work, int BH, int nqb, int grid, int slots, int* xcd_of_item) {
-    const int64_t all = (int64_t)BH * nqb;
-    uint32_t total = 0;
-    for (int h = 0; h < BH; ++h) total += head_work[h];
-    const int pieces = piece_count(work_base(dtype), total, all, grid, slots);
-    const bool split = cuts_items(all, grid, slots);
-    for (int64_t i = 0; i < all; ++i) xcd_of_item[i] = -1;
-    for (int id = 0; id < grid; ++id) {
-        const int p = piece_of(id, pieces);
-        if (p < 0) continue;
-        Cut c[2] = {{(int)all, 0}, {(int)all, 0}};
-        for (int e = 0; e < 2 && p + e < pieces; ++e) {
-            uint32_t x = cut_at(total, p + e, pieces);
-            int h = 0, q = 0;
-            while (x >= head_work[h]) x -= head_work[h++];
-            while (upto[(int64_t)h * nqb + q] <= x) ++q;
-            const int64_t it = (int64_t)h * nqb + q;
-            c[e] = cut_item(work_base(dtype), x - (q ? upto[it - 1] : 0u), (int)it, item_blocks(rec[it]), (item_cols(rec[it]) + BN - 1) / BN, split);
-        }
-        for (int it = c[0].item + (c[0].tile > 0 ? 1 : 0); it < c[1].item + (c[1].tile > 0 ? 1 : 0); ++it) xcd_of_item[it] = id & 7;
-    }
+int prefill_piece_xcd(int p, int pieces) {
+    for (int id = 0; id < 8; ++id)
+        for (int j = id; piece_of(j, pieces) >= 0; j += 8) if (piece_of(j, pieces) == p) return id;
+    return -1;
 }
 
 // Queue entries for this workgroup, called by one whole wave.  The first entry is the workgroup's own place in its
@@ -826,9 +809,10 @@ __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
             item = (int)e.x; parts = (int)(e.y & 0xFFFF); begin = rest = (int)(e.y >> 16);
         } else {
             const int first = u >> 2, p = first + 1 + lane;              // the item's first piece, if the next begins inside it
-            const int pieces = a.cuts[a.grid].x;
-            const int2 c0 = a.cuts[first], c1 = a.cuts[first + 1];
-            int2 c = a.cuts[p < a.grid ? p : a.grid - 1];                // (asked for at once; those of no piece are not looked at)
+            const int2* cuts = a.cuts + 1;
+            const int pieces = a.cuts[0].x;
+            const int2 c0 = cuts[first], c1 = cuts[first + 1];
+            int2 c = cuts[p < a.grid ? p : a.grid - 1];                  // (asked for at once; those of no piece are not looked at)
             if (first + 1 >= pieces || c1.y == 0 || (c0.x == c1.x && c0.y > 0)) continue;       // no cut through an item, or not its first
             item = c1.x; parts = 1;                        // the first, and one for every piece that begins inside the item
             for (;;) {
@@ -837,7 +821,7 @@ __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
                 parts += more;
                 if (more < 64) break;
                 const int q = first + parts + lane;
-                c = a.cuts[q < a.grid ? q : a.grid - 1];
+                c = cuts[q < a.grid ? q : a.grid - 1];
             }
             begin = begin_slot(item, first, a.BH * (int64_t)a.nqb, pieces); rest = first;
         }

@@ -154,7 +154,7 @@ def block_rows(cfg, sel, rng, heads_per_kind=2, random_blocks=8):
 
 def check_queues(pipe):
     """The work queues of the attention kernel hold every (head, 128-row block) item exactly once."""
-    queues, nqb = pipe.ctx.debug_prefill_queues(pipe.shape)
+    queues, nqb, _ = pipe.ctx.debug_prefill_queues(pipe.shape)
     items = np.concatenate(queues).astype(np.int64)
     BH = pipe.shape.B * pipe.shape.Hq
     expect = (np.arange(BH, dtype=np.int64)[:, None] << 16 | np.arange(nqb, dtype=np.int64)[None, :]).ravel()

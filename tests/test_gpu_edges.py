@@ -92,8 +92,8 @@ def test_prefill_in_the_smallest_workspace(oracle, B, Hq, Hkv, n, n_hat):
     need = up(heads * ((n + 31) // 32 + 12) * 4) + up(heads * 4) + up(heads * (table + 1) * 2) + up(heads * blocks * 4) + 256 + up(heads * table) + up(heads * blocks * 16)
     pipe.ctx = binding.Context(workspace=need)
     out, _ = pipe.prefill(dev_lists(*lists), sentinel=True)
-    queues, nqb = pipe.ctx.debug_prefill_queues(pipe.shape)
-    assert nqb == blocks
+    queues, nqb, cuts = pipe.ctx.debug_prefill_queues(pipe.shape)
+    assert nqb == blocks and cuts == 0
     items = np.sort(np.concatenate(queues))
     np.testing.assert_array_equal(items, np.sort([h << 16 | b for h in range(heads) for b in range(blocks)]))
     err = np.abs(out.float().cpu().numpy().reshape(-1, 64) - ref)

@@ -55,3 +55,26 @@ def test_queues_and_pieces_agree(B, Hq, Hkv, n, n_hat, d, dtype):
         some = torch.isfinite(plse)
         assert torch.equal(torch.isfinite(lse[b]), some)
         assert (lse[b][some] - plse[some]).abs().max().item() <= 1e-4
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d", [(1, 1, 1, 5000, 100, 128), (1, 4, 2, 3001, 3001, 64), (5, 4, 1, 20001, 12000, 128)])
+def test_items_are_shared_as_the_device_says(B, Hq, Hkv, n, n_hat, d):
+    """Pieces and queues as the kernels left them: every item once, items of the one dense head cut; no cut without room for parts."""
+    from tests.gpu_util import Pipeline, dev_lists
+    from paper_2507_13681_amd import binding
+    print(f"items as shared B={B} Hq={Hq} n={n} n_hat={n_hat} d={d}", flush=True)
+    q, k, v = inputs.make_plain(B, Hq, Hkv, n, n_hat, d, dtype="bf16", seed=n)
+    every = np.broadcast_to(np.arange(n, dtype=np.int32), (B, Hq, n)).copy()
+    lists = np.zeros((B, Hq, n), np.int32), np.zeros((B, Hq), np.int32), every, np.full((B, Hq), 5, np.int32)
+    lists[3][0, 0] = n
+    pipe = Pipeline(q, k, v, 1, "bf16")
+    blocks = (n - (n - n_hat) // 128 * 128 + 127) // 128
+    want = np.sort([h << 16 | b for h in range(B * Hq) for b in range(blocks)])
+    tables = B * Hq * ((n + 31) // 32 * 4 + 64 + (n // 64 + 5) * 3) + B * Hq * blocks * 20 + 4096
+    for ctx, cut in ((pipe.ctx, True), (binding.Context(workspace=tables), False)):
+        pipe.ctx = ctx
+        pipe.prefill(dev_lists(*lists), sentinel=True)
+        queues, nqb, cuts = ctx.debug_prefill_queues(pipe.shape)
+        assert nqb == blocks and (cuts > 0) == cut, cuts
+        np.testing.assert_array_equal(np.sort(np.concatenate(queues)), want)
