@@ -391,27 +391,40 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
     uint32_t* per_item = bp.take<uint32_t>(items);         // pieces: `upto`, the records lie where the queues would; queues: the records
     w.tab = bp.take<uint8_t>((size_t)BH * tab_len);
     w.misc = bp.take<int32_t>(26);                         // of the queues: lengths, heads, first entries, slots in use and split items
-    // long items are split as far as the workspace has room for their parts' results (sized for it by
-    // ls_workspace_bytes; a smaller workspace that holds the rest still works)
-    w.pieces = ls::prefill_in_pieces(BH, s->n, w.nqb, s->d);
-    w.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, w.pieces);
-    w.slots = ls::prefill_split_slots((int64_t)items, w.grid, w.pieces);
     w.code = LS_EWORKSPACE;
     if (!bp.ok()) return "workspace is too small";
+    // long items are cut as far as the workspace has room for their parts' results (sized for it by ls_workspace_bytes; a smaller
+    // workspace that holds the rest still works)
     const Bump mark = bp;
-    for (;;) {
+    auto take = [&](int slots) {
         bp = mark;
-        w.queue = bp.take<uint4>(items + w.slots);
+        w.slots = slots;
+        w.queue = bp.take<uint4>(items + slots);
         w.rec = w.pieces ? reinterpret_cast<uint32_t*>(w.queue) : per_item;
         w.upto = w.pieces ? per_item : nullptr;
-        // (without slots there are no more pieces than items, and their cuts lie behind the records)
-        w.cuts = !w.pieces ? nullptr : w.slots ? bp.take<int2>((size_t)w.grid + 1) : reinterpret_cast<int2*>(w.rec + ((items + 1) & ~(size_t)1));
-        w.split = w.slots && !w.pieces ? bp.take<uint2>((size_t)w.slots) : nullptr;
-        w.part_o = w.slots ? bp.take<float>((size_t)w.slots * 128 * s->d) : nullptr;
-        w.part_ml = w.slots ? bp.take<float>((size_t)w.slots * 128 * 2) : nullptr;
-        if (bp.ok()) break;
-        if (w.slots == 0) return "workspace is too small";
-        w.slots = w.slots > 16 ? w.slots / 2 : 0;
+        w.cuts = w.pieces ? bp.take<int2>((size_t)w.grid + 1) : nullptr;
+        w.split = slots && !w.pieces ? bp.take<uint2>((size_t)slots) : nullptr;
+        w.part_o = slots ? bp.take<float>((size_t)slots * 128 * s->d) : nullptr;
+        w.part_ml = slots ? bp.take<float>((size_t)slots * 128 * 2) : nullptr;
+        return bp.ok();
+    };
+    auto most_slots = [&]() {                              // of those wanted, as many as fit
+        int slots = ls::prefill_split_slots((int64_t)items, w.grid, w.pieces);
+        const size_t queues = up(items * 16), room = mark.cap - mark.off > queues ? mark.cap - mark.off - queues : 0;
+        if ((size_t)slots > room / ls::prefill_slot_bytes(s->d)) slots = (int)(room / ls::prefill_slot_bytes(s->d));
+        while (slots > 0 && !take(slots)) --slots;         // (a slot has a few more bytes than its results, rounded up together)
+        return slots;
+    };
+    w.pieces = ls::prefill_in_pieces(BH, s->n, w.nqb, s->d);
+    w.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, w.pieces);
+    if (w.pieces) {
+        w.grid = ls::prefill_pieces_for((int64_t)items, w.grid, most_slots());
+        w.pieces = w.grid > 0;
+        if (w.pieces && !take(ls::prefill_split_slots((int64_t)items, w.grid, true))) return "workspace is too small";
+    }
+    if (!w.pieces) {
+        w.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, false);
+        if (!take(most_slots())) return "workspace is too small";
     }
     w.code = LS_OK;
     return nullptr;

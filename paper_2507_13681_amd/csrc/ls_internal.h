@@ -107,7 +107,7 @@ struct PrefillArgs {
     int cap_v;
     const uint16_t* elist;    // as plan_kernel left them
     int grid;                 // workgroups
-    int slots;                // results of parts that the workspace holds
+    int slots;                // results of parts that may be kept
     // pieces (ls_prefill.hip): at most `grid`
     const uint32_t* rec;
     const uint32_t *upto, *head_work;
@@ -191,6 +191,7 @@ bool prefill_in_pieces(int BH, int64_t n, int nqb, int d);               // the 
 int prefill_grid(int dtype, int d, int64_t items, bool pieces);
 int prefill_split_slots(int64_t items, int grid, bool pieces);      // parts' results that a call with so many (head, row block) items may use
 size_t prefill_slot_bytes(int d);
+int prefill_pieces_for(int64_t items, int grid, int slots);              // workgroups of a call in pieces with room for so many parts' results (0: queues)
 int prefill_piece_xcd(int p, int pieces);                                // XCD whose workgroup takes piece p
 
 }  // namespace ls

@@ -303,7 +303,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // the heads, a look through one head's row blocks.  Neighbouring pieces go to the same XCD, so that the query heads that
 // share K and V meet in one L2.  An item that a cut goes through is done in parts, whose unnormalised results go to slots of the
 // workspace and which combine_kernel puts together; a cut that would leave a few tiles on one side is moved to the
-// end of the item, and so are all cuts where the workspace has no room for the parts.
+// end of the item.  A workspace that does not hold all parts gets fewer pieces, or queues (prefill_pieces_for).
 //
 // Against the work queues of sched_kernel (which serve what is larger) this saves a launch of one workgroup per XCD, a look at the
 // queues per item, and the wait for the longest item, which a short turn feels most.  The whole call, bf16, 32 heads of d = 128, queues -> pieces,
@@ -323,27 +323,21 @@ __host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return 
 
 struct Cut { int item, tile; };                            // a piece begins at this tile of this item
 // The cut `u` into an item of n1 contiguous and n2 packed tiles.
-__host__ __device__ __forceinline__ Cut cut_item(uint32_t base, uint32_t u, int item, int n1, int n2, bool split) {
+__host__ __device__ __forceinline__ Cut cut_item(uint32_t base, uint32_t u, int item, int n1, int n2) {
     const int tiles = n1 + n2;
-    int t;
-    if (!split) t = 2 * u < item_work(base, n1, n2) ? 0 : tiles;
-    else if (u < base + CUT_TILES * WORK_TILE) t = 0;
-    else {
+    int t = 0;
+    if (u >= base + CUT_TILES * WORK_TILE) {
         const uint32_t v = u - base;
         t = v < n1 * WORK_TILE ? (int)(v / WORK_TILE) : n1 + (int)((v - n1 * WORK_TILE) / WORK_COLS);
         if (t + CUT_TILES > tiles) t = tiles;
     }
     return t > 0 && t >= tiles ? Cut{item + 1, 0} : Cut{item, t};
 }
-// Pieces of which no more than `grid` may be made, and `slots` results of parts kept: one for each piece that begins inside an
-// item, one for each item (or piece) that is left unfinished.
-__host__ __device__ __forceinline__ int begin_slots(int64_t items, int pieces) { return items < pieces ? (int)items : pieces; }
-__host__ __device__ __forceinline__ bool cuts_items(int64_t items, int grid, int slots) {
-    return slots >= grid + begin_slots(items, grid) || slots > 2 * items;
-}
-__host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work, int64_t items, int grid, int slots) {
-    if (!cuts_items(items, grid, slots)) return items < grid ? (int)items : grid;
-    const uint32_t most = slots >= grid + begin_slots(items, grid) ? grid : slots - (int)items;
+// Results of parts that so many pieces may have to keep: one for each that begins inside an item, and one for what was left unfinished
+// before it (by item or by piece, whichever are fewer).
+__host__ __device__ __forceinline__ int part_slots(int64_t items, int pieces) { return pieces - 1 + (items < pieces ? (int)items : pieces - 1); }
+// Number of pieces, no more than `most`, and no more than the workgroups of the launch
+__host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work, int64_t items, uint32_t most) {
     uint32_t pieces = work / piece_work(base), least = items < most ? (uint32_t)items : most;
     pieces = pieces > most ? most : pieces < least ? least : pieces;
     // (at least two tiles a piece: no two cuts fall into one tile)
@@ -392,9 +386,8 @@ __device__ __forceinline__ Span my_span(const PrefillArgs& a, uint32_t* sh) {   
     total = (uint32_t)__builtin_amdgcn_readfirstlane((int)total);
     const int items = a.BH * a.nqb;
     const uint32_t base = work_base(a.dtype);
-    const bool split = cuts_items(items, a.grid, a.slots);
     Span s;
-    s.pieces = piece_count(base, total, items, a.grid, a.slots);
+    s.pieces = piece_count(base, total, items, (uint32_t)a.grid);
     s.piece = piece_of((int)blockIdx.x, s.pieces);
     s.from = s.to = Cut{items, 0};
     s.rec = 0u;
@@ -425,7 +418,7 @@ __device__ __forceinline__ Span my_span(const PrefillArgs& a, uint32_t* sh) {   
             if (n > 0) at = (uint32_t)__builtin_amdgcn_readlane((int)u, n - 1);
             if (n < 64) {
                 const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)c, n);
-                const Cut k = cut_item(base, r - at, h * a.nqb + q + n, item_blocks(e), (item_cols(e) + BN - 1) / BN, split);
+                const Cut k = cut_item(base, r - at, h * a.nqb + q + n, item_blocks(e), (item_cols(e) + BN - 1) / BN);
                 if (rec && k.item == h * a.nqb + q + n) *rec = e;
                 return k;
             }
@@ -444,8 +437,8 @@ __device__ __forceinline__ Span my_span(const PrefillArgs& a, uint32_t* sh) {   
     }
     return s;
 }
-// Slot of the part with which an item begins on piece p; one that takes an item up goes to the slot of its piece.
-__host__ __device__ __forceinline__ int begin_slot(int item, int p, int64_t items, int pieces) { return pieces + (items < pieces ? item : p); }
+// Slot of the part with which an item begins on piece p; the one that takes an item up on piece p goes to slot p - 1.
+__host__ __device__ __forceinline__ int begin_slot(int item, int p, int64_t items, int pieces) { return pieces - 1 + (items < pieces ? item : p); }
 
 // ---------------------------------------------------------------------------------------------
 // sched: builds the 8 work queues of turns beyond PIECES_TILES.  The query heads of one KV head stay together (they share K/V
@@ -624,11 +617,23 @@ int prefill_grid(int dtype, int d, int64_t items, bool pieces) {
     return (int)(most < 256 * per_cu ? most : 256 * per_cu);
 }
 int prefill_split_slots(int64_t items, int grid, bool pieces) {
-    if (pieces) return grid + begin_slots(items, grid);
+    if (pieces) return part_slots(items, grid);
     return items > SPLIT_ITEMS ? 0 : items * ITEM_PARTS < SPLIT_SLOTS ? (int)items * ITEM_PARTS : SPLIT_SLOTS;
 }
 bool prefill_in_pieces(int BH, int64_t n, int nqb, int d) { return (int64_t)BH * nqb * ((n + BN - 1) / BN) * d <= PIECES_TILES * 128; }
 
+// Pieces, of up to `grid`, whose parts `slots` hold; 0: the queues serve the call better.  Fewer pieces than workgroups make the run about
+// grid / pieces as long (of three places a CU only 5 % where two are filled), queues about a quarter of grid / items longer.  The whole
+// call with all slots / 90, 75, 67, 50, 40, 25 % of them, us, pieces; and queues:
+// 8192 rows, all new, 32 heads of 128 (4 items a workgroup) 274 / 295 337 371 396 484 736; 294 to 307. 16 heads of 64 (1.3) 75 / 79 85 76 94 110 131;
+// 96 to 115.  6000 of 9000, 32 heads (3) 242 / 265 305 337 349 423 649; 259 to 268.  4096, all new, 8 heads of 128 (0.5) 62 / 64 70 68 78 86 117;
+// 72 to 94.  300 of 16384, 32 heads (0.2) 62 / 62 62 64 67 79 122; 76 to 94.  1777 of 5003, 16 heads of 64 (0.3) 50 / 53 53 53 61 63 84; 74 to 104.
+int prefill_pieces_for(int64_t items, int grid, int slots) {
+    if (slots >= part_slots(items, grid)) return grid;
+    const int64_t pieces = 1 + (slots > 2 * items ? slots - items : slots / 2);
+    if (grid > 512 && pieces >= 512) return items <= 5 * (int64_t)grid ? 512 : 0;
+    return pieces > 1 && 4 * items * (grid - pieces) <= grid * pieces ? (int)pieces : 0;
+}
 int prefill_piece_xcd(int p, int pieces) {
     for (int id = 0; id < 8; ++id)
         for (int j = id; piece_of(j, pieces) >= 0; j += 8) if (piece_of(j, pieces) == p) return id;
@@ -723,7 +728,7 @@ template <> struct Entries<false> {
     __device__ __forceinline__ void ahead(const PrefillArgs& a, int, int) { if (at <= last) rec = a.rec[at]; }
     __device__ __forceinline__ bool next(const PrefillArgs& a, int, int, Entry& e) {
         const uint32_t r = (uint32_t)__builtin_amdgcn_readfirstlane((int)rec);
-        e.item = at; e.blocks = item_blocks(r); e.cols = item_cols(r); e.slot0 = begin_slot(at, s.piece, (int64_t)a.BH * a.nqb, s.pieces); e.slot1 = s.piece;
+        e.item = at; e.blocks = item_blocks(r); e.cols = item_cols(r); e.slot0 = begin_slot(at, s.piece, (int64_t)a.BH * a.nqb, s.pieces); e.slot1 = s.piece - 1;
         e.lo = at == s.from.item ? s.from.tile : 0;
         e.hi = at == s.to.item ? s.to.tile : -1;
         return at++ <= last;
@@ -791,7 +796,7 @@ __device__ __forceinline__ void store_out4(float* p, float a, float b, float c, 
 }
 
 // Puts the parts of the split items together.  Queues: `split` lists them.  Pieces: the cuts tell; the part that begins an item
-// lies in the slot of the item (or of its piece, where there are more items than pieces) behind those of the pieces, the
+// lies in the slot of the item (or of its piece, where there are more items than pieces) behind those of the cuts, the
 // others in the slots of theirs.  A unit is one wave's 32 rows of a split item, taken by one workgroup in the layout store_part
 // wrote: wave w adds the groups w, w + 4, ... of 16 bytes a lane.  Queues: grid-stride over the units.  Pieces: four units a cut, a
 // workgroup each (512 workgroups in all: 5003 rows carried, d = 64, 13.4 us instead of 10.3, first turn of 8192 rows 17.6 instead of 15.7,
@@ -823,7 +828,7 @@ __global__ __launch_bounds__(256) void combine_kernel(PrefillArgs a) {
                 const int q = first + parts + lane;
                 c = cuts[q < a.grid ? q : a.grid - 1];
             }
-            begin = begin_slot(item, first, a.BH * (int64_t)a.nqb, pieces); rest = first;
+            begin = begin_slot(item, first, a.BH * (int64_t)a.nqb, pieces); rest = first - 1;
         }
         const int bh = item / a.nqb, qb = item % a.nqb;
         const int64_t row0 = a.n - a.n_hat, pos = a.pos0 + (int64_t)qb * BM + 32 * wv + r32;
@@ -1703,8 +1708,8 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
 
 template <typename T, int D, bool QUEUES>
 static void launch_combine(const PrefillArgs& a, hipStream_t st, const hipEvent_t* ev) {
+    if (a.slots == 0) return;
     const dim3 grid(QUEUES ? (a.slots < 256 ? 2 * a.slots : 512) : 4 * a.grid);
-    if (QUEUES ? a.slots == 0 : !cuts_items((int64_t)a.BH * a.nqb, a.grid, a.slots)) return;
     if (ev) hipExtLaunchKernelGGL((combine_kernel<T, D, QUEUES>), grid, dim3(256), 0, st, ev[2], ev[3], 0, a);
     else hipLaunchKernelGGL((combine_kernel<T, D, QUEUES>), grid, dim3(256), 0, st, a);
 }

@@ -78,3 +78,34 @@ def test_items_are_shared_as_the_device_says(B, Hq, Hkv, n, n_hat, d):
         queues, nqb, cuts = ctx.debug_prefill_queues(pipe.shape)
         assert nqb == blocks and (cuts > 0) == cut, cuts
         np.testing.assert_array_equal(np.sort(np.concatenate(queues)), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("Hq,Hkv,n,n_hat,d", [(16, 4, 3001, 3001, 64), (8, 2, 4096, 4096, 128), (32, 8, 5003, 300, 128), (32, 8, 4099, 4099, 128)])
+def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
+    """A workspace with room for some of the parts: items are still cut, in fewer pieces or by the queues, to the same result."""
+    from tests.gpu_util import Pipeline, dev_lists
+    from paper_2507_13681_amd import binding
+    print(f"room for some parts Hq={Hq} n={n} n_hat={n_hat} d={d}", flush=True)
+    q, k, v = inputs.make_plain(1, Hq, Hkv, n, n_hat, d, dtype="bf16", seed=n, q_scale=1.5)
+    lists = dev_lists(*_lists(np.random.default_rng(n), 1, Hq, n))
+    pipe = Pipeline(q, k, v, 1, "bf16")
+    ref, rlse = pipe.prefill(lists, sentinel=True)
+    items = Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128)
+    places = 512 if d == 128 else 768
+    slots = places - 1 + min(items, places - 1)
+    tables = Hq * ((n + 31) // 32 * 4 + 64 + (n // 64 + 5) * 3) + items * 20 + 16384
+    tol = 4 * 2.0 ** -9 * float(np.abs(v).max())                      # as between queues and pieces
+    for share in (1.0, 0.99, 0.9, 0.7, 0.667, 0.5, 0.3, 0.1, 0.02):
+        ctx = pipe.ctx = binding.Context(workspace=tables + int(share * slots) * (128 * d * 4 + 1024 + 24))
+        ctx.profile_enable(True)
+        out, lse = pipe.prefill(lists, sentinel=True)
+        torch.cuda.synchronize()
+        assert ctx.profile_prefill_kernel_ms()[1] == 1
+        queues, _, cuts = ctx.debug_prefill_queues(pipe.shape)
+        assert (cuts > 0 or share < 0.3) and len(np.unique(np.concatenate(queues))) == sum(map(len, queues)) == items, (share, cuts)
+        assert not torch.isnan(out).any()
+        assert (out.float() - ref.float()).abs().max().item() <= tol
+        some = torch.isfinite(rlse)
+        assert torch.equal(torch.isfinite(lse), some)
+        assert (lse[some] - rlse[some]).abs().max().item() <= 1e-4
