@@ -1,4 +1,4 @@
-"""The decode kernel waits for its global -> LDS transfers before every barrier, on every path of the built code.
+"""The kernels wait for their global -> LDS transfers before every barrier that publishes them, on every path of the built code.
 
 The transfers are asm statements, which the compiler does not count among the memory operations it waits for, and a
 barrier of gfx950 does not wait for vector memory by itself: a transfer still in flight there could land in LDS that other
@@ -7,6 +7,8 @@ waves have taken for something else.  Which waits the compiler happens to put el
 import os
 import re
 import subprocess
+
+import pytest
 
 from paper_2507_13681_amd import build
 
@@ -67,21 +69,37 @@ def test_path_search_sees_a_missing_wait():
     assert _barriers_with_a_transfer_in_flight(loop) == 1
 
 
-def test_decode_kernel_waits_before_its_barriers(tmp_path):
-    out = tmp_path / "decode.s"
+# source: kernels, by the beginning of their names, their instances, and barriers that leave the next chunk of query rows under way
+# on purpose: they order LDS that no transfer fills (the slab of diagonals, the rows' reduction)
+KERNELS = {
+    "ls_decode.hip": [("decode_kernelI", 4, 0)],
+    "ls_prefill.hip": [("prefill_bf16_kernelI", 4, 0)],
+    "ls_score.hip": [("stats_kernelI", 4, 1), (r"lines_kernelI\w+Li0ELb", 8, 1), (r"lines_kernelI\w+Li[123]ELb", 24, 0)],
+}
+
+
+@pytest.mark.parametrize("source", KERNELS)
+def test_kernels_wait_before_their_barriers(tmp_path, source):
+    out = tmp_path / "source.s"
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    subprocess.run([hipcc, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "ls_decode.hip"), "-o", str(out)],
+    subprocess.run([hipcc, *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", str(out)],
                    check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
-    kernels = {}
+    kernels, current = {}, []
     for line in out.read_text().splitlines():
-        start = re.match(r"(_ZN2ls13decode_kernel\w+):", line)
+        start = re.match(r"(_ZN2ls\w+):", line)
         if start:
             kernels[start[1]] = current = []
         elif line.startswith(".Lfunc_end"):
             current = []
-        elif kernels:
+        else:
             current.append(line)
-    assert len(kernels) == 4
-    for name, lines in kernels.items():
-        assert sum("_load_lds_" in x for x in lines) and sum("s_barrier" in x for x in lines), name
-        assert _barriers_with_a_transfer_in_flight(lines) == 0, name
+    seen = set()
+    for name, instances, in_flight in KERNELS[source]:
+        found = {k: v for k, v in kernels.items() if re.match(rf"_ZN2ls\d+{name}", k)}
+        assert len(found) == instances, (name, list(found))
+        for k, lines in found.items():
+            assert any("_load_lds_" in x for x in lines) and any("s_barrier" in x for x in lines), k
+            assert _barriers_with_a_transfer_in_flight(lines) == in_flight, k
+        seen |= set(found)
+    # no other kernel of the source has transfers
+    assert not [k for k, lines in kernels.items() if k not in seen and any("_load_lds_" in x for x in lines)]
