@@ -1319,7 +1319,9 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     const uint16_t* el = a.elist + (int64_t)bh * (a.tab_len + 1) + n1 - 1 - tbeg;         // of tile tbeg, the others below it
     if (n - 1 < blockpos + BN && n1 > 0 && a.elist[(int64_t)bh * (a.tab_len + 1)] == 0) ++el;       // half a row block: entry 0 belongs to key blocks beyond it
     const int blocks = (ntiles < n1 ? ntiles : n1) - tbeg;               // contiguous tiles of this part, none if not positive
-    const uint16_t el0 = tid < blocks ? el[-tid] : (uint16_t)0;
+    int tl = tid;                                          // (made new here: addresses made of it would be kept, or spilled, from one entry to the next)
+    asm volatile("" : "+v"(tl));
+    const uint16_t el0 = tl < blocks ? el[-tl] : (uint16_t)0;
     asm volatile("" ::: "memory");
     Frag<T> qf[C::KSTEPS];
     if (row_ok) {
@@ -1332,7 +1334,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     }
 
     // ---- key blocks of the contiguous tiles, ascending: the table entry of block kb is jb - kb + 1
-    for (int i = tid; i < blocks; i += PREFILL_THREADS) kbl[i] = (uint16_t)(jb + 1 - (int)(i == tid ? el0 : el[-i]));
+    for (int i = tl; i < blocks; i += PREFILL_THREADS) kbl[i] = (uint16_t)(jb + 1 - (int)(i == tl ? el0 : el[-i]));
     const int32_t* vi = a.v_idx + (int64_t)bh * a.cap_v;
 
     f32x16 oacc[C::DBLK];

@@ -9,6 +9,8 @@ from paper_2507_13681_amd import build
 
 # the kernels of a source, by the beginning of their names, that must do without scratch memory
 NO_SCRATCH = {
+    "ls_decode.hip": ["decode_kernel"],
+    "ls_prefill.hip": ["plan_kernel", "sched_kernel", "prefill_bf16_kernel", "combine_kernel"],
     "ls_select.hip": ["order_kernel", "walk_kernel", "walk_exact_kernel", "emit_kernel", "merge_lines_kernel", "topb_one_kernel"],
 }
 
