@@ -205,9 +205,9 @@ def main():
     sel_h = {a: b.cpu().numpy() for a, b in sel.items() if b is not None}
     cells = metrics.selection_cells(cfg.n, cfg.n_hat, sel_h)
 
-    # What each kind of head costs the attention kernel.  The kernel's time per visited tile hardly depends on the tile
-    # (its four waves move from barrier to barrier together), so the measured kernel time is split between the kinds in proportion to the 128 x 64 tiles
-    # their heads make the kernel visit (counted on the host from the index sets, as the kernel's own plan does).
+    # What each kind of head costs the attention kernel: it is run once more with every head's lists replaced by those of the heads of
+    # one kind, in turn, and that time is scaled by the 128 x 64 tiles that the kind's own heads make it visit (counted on the host
+    # from the index sets, as the kernel's own plan does).
     nvh, nsh = sel_h["v_cnt"], sel_h["s_cnt"]
     kind_masks = {"exhausted": (nvh >= cfg.n) & (nsh >= cfg.n), "slash_only": (nvh == 0) & (nsh > 0),
                   "vertical_only": (nsh == 0) & (nvh > 0)}
@@ -222,10 +222,20 @@ def main():
         if int(m.sum()) == 0:
             continue
         kc, kt = int(cells[m].sum()), int(tiles[m].sum())
-        ms_k = kern_ms * kt / max(int(tiles.sum()), 1)
+        pick = np.flatnonzero(m.ravel())[np.arange(m.size) % int(m.sum())]
+        like = {a: x.reshape(m.size, -1)[torch.from_numpy(pick).to(x.device)].reshape(x.shape).contiguous() for a, x in sel.items() if x is not None}
+        f_kind = lambda: ctx.ls_sparse_prefill(shape, qd, kd, vd, like["v_idx"], like["v_cnt"], like["s_idx"], like["s_cnt"], out, lse)
+        f_kind()
+        ctx.profile_enable(True)
+        for _ in range(8):
+            f_kind()
+        torch.cuda.synchronize()
+        ms_all, _ = ctx.profile_prefill_kernel_ms()
+        ctx.profile_enable(False)
         by_kind[kname] = {"heads": int(m.sum()), "selected_cells": kc, "visited_tiles": kt,
-                          "cells_per_tile_cell": round(kc / max(kt * 128 * 64, 1), 4), "kernel_ms_share": round(ms_k, 4),
-                          "effective_tflops": round(4.0 * cfg.d * kc / max(ms_k * 1e-3, 1e-12) / 1e12, 1)}
+                          "cells_per_tile_cell": round(kc / max(kt * 128 * 64, 1), 4),
+                          "kernel_ms_share": round(ms_all * kt / int(tiles.ravel()[pick].sum()), 4),
+                          "effective_tflops": round(4.0 * cfg.d * int(cells.ravel()[pick].sum()) / (ms_all * 1e-3) / 1e12, 1)}
     total_cells = int(cells.sum())
     dense_cells = cfg.B * cfg.Hq * metrics.causal_cells(cfg.n, cfg.n_hat)
     flops = 4.0 * cfg.d * total_cells                     # 2 d for q.k and 2 d for p.v per allowed cell

@@ -38,7 +38,7 @@ def visited_tiles(n: int, n_hat: int, v_idx, s_idx, rows: int = 128, keys: int =
     """Number of (rows x keys) tiles the sparse attention kernel visits for one head: per block of `rows` query rows
     (aligned to absolute positions that are multiples of `rows`), the key blocks of `keys` keys that hold a cell on a
     selected diagonal, plus the packed tiles of `keys` gathered columns each (none when every diagonal is selected).
-    Reports split the kernel's time between heads in proportion to this count."""
+    Reports scale the kernel's time for one kind of head by this count."""
     v = np.unique(np.asarray(v_idx, dtype=np.int64))
     s = np.unique(np.asarray(s_idx, dtype=np.int64))
     bm = np.zeros(n + 1, np.int64)
