@@ -757,10 +757,12 @@ constexpr int WALK_THREADS = 384;              // wave 0 decides the runs, wave 
 // 32 heads, us: 2048 lines 22.0 / 23.1 / 24.3, 4096 24.2 / 24.0 / 25.3, 12347 34.9 / 35.5 / 36.4, 16384 56.2 / 49.3 / 45.7, 32768 76.8 / 67.2 / 63.1,
 // 65536 157 / 137 / 128; 256 heads of 1500 lines 27.5 / 29.0 / 29.9.
 constexpr int64_t WALK_SHORT = 2048, WALK_LONG = 16384;        // up to: 4; from: 16
-// Where the picks go back and forth between the lists a run is one or a few, and its price is that of looking at all E entries: the
-// waves then look at these few only, from a run of up to half of what they hold until one fills them.  The walk alone with E entries
-// throughout / now, 32 heads of 32768 lines, us: runs of one to five picks 76.5 / 52.2, of one 489 / 308, one run to the end 18.8 / 17.9; 8192
-// lines 24.9 / 23.5, 95.8 / 83.9, 10.9 / 11.1.  (Eight entries a lane throughout: 55.5, 346, 15.6.)
+// Where the picks go back and forth between the lists a run is one or a few, and its price is that of looking at all E entries.  Of
+// sixteen the deciding wave then looks at these few only, from a run of up to half of what they hold until one fills them.  The walk alone
+// with sixteen throughout / now, 32 heads of 32768 lines, us: runs of one to five picks 76.5 / 54.7, of one 489 / 320, one run to the end 18.8 / 18.3;
+// 131072 lines of a long turn 123 / 120.  (Eight throughout: 55.5, 346, 15.6; 131.  Beginning with the few: 32k turn 25.4 -> 27.1.  With the
+// sums over four entries a lane as well: 52.2, 308, 17.9; 130.  The same with eight entries instead of sixteen: 8192 lines of single picks
+// 95.8 -> 83.9, of a first turn 21.6 -> 23.0.)
 constexpr int WALK_NARROW = 4;
 constexpr int WALK_NBLK = 4;                   // blocks of a list resident in LDS (a ring over sorted positions)
 constexpr int WALK_CAP = WALK_BLK * WALK_NBLK;
@@ -1034,24 +1036,18 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             const int which = __builtin_amdgcn_readfirstlane(R.which);
             const int limit = __builtin_amdgcn_readfirstlane(R.limit);
             const int last = __builtin_amdgcn_readfirstlane(R.last);
+            float g[E];
+#pragma unroll
+            for (int e = 0; e < E; e += 2) {
+                const float2 t = *reinterpret_cast<const float2*>(&R.g[E * lane + e]);
+                g[e] = E * lane + e < limit ? t.x : 0.f; g[e + 1] = E * lane + e + 1 < limit ? t.y : 0.f;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // the slot may be written again
+            ++k;
+            if (lane == 0) walk_st(&sync->summed, k);
             // pick by pick, as the loop of the definition adds them; it stops after the pick that reaches the target
             // (one addition after the other took 3900 cycles a run)
-            int taken;
-            auto add = [&](auto ENTRIES) {
-                constexpr int N = decltype(ENTRIES)::value;
-                float g[N];
-#pragma unroll
-                for (int e = 0; e < N; e += 2) {
-                    const float2 t = *reinterpret_cast<const float2*>(&R.g[N * lane + e]);
-                    g[e] = N * lane + e < limit ? t.x : 0.f; g[e + 1] = N * lane + e + 1 < limit ? t.y : 0.f;
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");     // the slot may be written again
-                ++k;
-                if (lane == 0) walk_st(&sync->summed, k);
-                taken = chain_until<N>(g, lane, limit, target, sum);
-            };
-            if (E > WALK_NARROW && limit <= 64 * WALK_NARROW) add(std::integral_constant<int, WALK_NARROW>{});
-            else add(std::integral_constant<int, E>{});
+            const int taken = chain_until<E>(g, lane, limit, target, sum);
             const bool reached = !(sum < target);
             cnt_s += which == 0 ? taken : 0;
             cnt_v += which == 0 ? 0 : taken;
@@ -1206,12 +1202,12 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             if (lane == 0) walk_st(&sync->runs, published);
             if (stop_dead < run) break;            // nothing after this run can add to the sum
             if (which == 0) { is += limit; S = nxt; } else { iv += limit; V = nxt; }
-            if (E > WALK_NARROW && (N == E ? limit <= 32 * WALK_NARROW : limit == 64 * WALK_NARROW)) return true;
+            if (E == 16 && (N == E ? limit <= 32 * WALK_NARROW : limit == 64 * WALK_NARROW)) return true;
         }
         return false;
     };
     bool wide = true;
-    while (wide ? decide(std::integral_constant<int, E>{}) : decide(std::integral_constant<int, (E < WALK_NARROW ? E : WALK_NARROW)>{})) wide = !wide;
+    while (wide ? decide(std::integral_constant<int, E>{}) : decide(std::integral_constant<int, (E == 16 ? WALK_NARROW : E)>{})) wide = !wide;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (lane == 0) {
         if (failed) walk_st(&sync->err, 1);
