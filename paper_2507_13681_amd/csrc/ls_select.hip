@@ -1801,13 +1801,17 @@ __global__ __launch_bounds__(TB_THREADS) void topb_write_kernel(TopbArgs a) {
 // on inside that bin, until the few keys left are ranked directly or wanted as a whole: mostly one round, a few hundred keys
 // at most sharing a bin.  (Digits of the keys as bins, into few of which a head's scores crowd, took 16 us of LDS atomics that take
 // turns; two bits a step, counted in registers, 8 to 10 steps, 15.9 for 32 heads of 16384 entries, now 9.9.)
+// Lanes that add to one word take turns, four cycles each: a bin has a word for every eighth lane.  ls_kv_compress, 32 heads, one word a
+// bin / eight / two bits a step: 16384 entries of which 90 % weigh nothing 131 / 92 / 96 us, all but equal 122 / 89 / 95; 32768 77 / 56 / 57,
+// 130 / 59 / 57; scores as they mostly are 93 / 93 / 98, 55 / 55 / 58.
 // Beyond 32 keys a thread the launches below, 4.5 us each, are spread over the chip; 64 keys do not stay in registers.  The whole of
 // ls_kv_compress (d 64, 8 rows), spread / one workgroup a head, us: 16500 entries 35.5 / 28.9 (8 heads), 93.5 / 73.8 (64); 32768
 // entries 40.5 / 35.8 (8), 84.2 / 75.5 (32), 148 / 122 (64); 33000 entries 41.8 / 75.5 (8), 157 / 179 (64).
-constexpr int TB_ONE_LEN = 32768, TB_RANKED = 256;
+constexpr int TB_ONE_LEN = 32768, TB_RANKED = 256, TB_COPIES = 8;
 template <int PER>
 __global__ __launch_bounds__(TB_THREADS) void topb_one_kernel(TopbArgs a) {
-    __shared__ uint32_t bins[TB_THREADS], left[TB_RANKED], most[2][16], place[3], nleft, found[2], wg[16], we[16];
+    __shared__ uint4 bins[TB_THREADS][TB_COPIES / 4];
+    __shared__ uint32_t left[TB_RANKED], most[2][16], place[3], nleft, found[2], wg[16], we[16];
     const int bk = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int len = (int)a.len, keep = a.budget < len ? a.budget : len;
     int32_t* out = a.keep_idx + (int64_t)bk * a.budget;
@@ -1822,7 +1826,12 @@ __global__ __launch_bounds__(TB_THREADS) void topb_one_kernel(TopbArgs a) {
 #pragma unroll
     for (int j = 0; j < PER; ++j) key[j] = desc_key(sc[first + 64 * j < len ? first + 64 * j : len - 1]);      // (all loads in flight)
     if (tid == 0) nleft = 0u;
-    bins[tid] = 0u;
+    auto clear = [&]() {
+#pragma unroll
+        for (int c = 0; c < TB_COPIES / 4; ++c) bins[tid][c] = make_uint4(0u, 0u, 0u, 0u);
+    };
+    clear();
+    uint32_t* const copy = reinterpret_cast<uint32_t*>(bins) + (lane & (TB_COPIES - 1));
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;                    // (entries behind the last one repeat it)
 #pragma unroll
     for (int j = 0; j < PER; ++j) { lo = key[j] < lo ? key[j] : lo; hi = key[j] > hi ? key[j] : hi; }
@@ -1839,14 +1848,17 @@ __global__ __launch_bounds__(TB_THREADS) void topb_one_kernel(TopbArgs a) {
         bit = width > 10 ? width - 10 : 0;
 #pragma unroll
         for (int j = 0; j < PER; ++j)
-            if (first + 64 * j < len && key[j] - lo <= hi - lo) atomicAdd(&bins[(key[j] - lo) >> bit], 1u);
+            if (first + 64 * j < len && key[j] - lo <= hi - lo) atomicAdd(copy + ((key[j] - lo) >> bit) * TB_COPIES, 1u);
         __syncthreads();
-        const uint32_t mine = bins[tid], upto = lanes_upto(mine);
+        uint32_t mine = 0u;
+#pragma unroll
+        for (int c = 0; c < TB_COPIES / 4; ++c) { const uint4 b = bins[tid][c]; mine += b.x + b.y + b.z + b.w; }
+        const uint32_t upto = lanes_upto(mine);
         if (lane == 63) wg[wv] = upto;
         __syncthreads();
         const uint32_t before = (uint32_t)__builtin_amdgcn_readlane((int)lanes_upto(lane < wv ? wg[lane & 15] : 0u), 63) + upto - mine;
         if (rem > before && rem <= before + mine) { place[0] = (uint32_t)tid; place[1] = before; place[2] = mine; }
-        bins[tid] = 0u;
+        clear();
         __syncthreads();
         lo += place[0] << bit; rem -= place[1]; within = place[2];
         if (rem == within || within <= (uint32_t)TB_RANKED || bit == 0) break;

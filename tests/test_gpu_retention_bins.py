@@ -9,7 +9,7 @@ from paper_2507_13681_amd import binding
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("ln", [300, 4097, 32768])
-@pytest.mark.parametrize("kind", ["equal", "outlier", "close"])
+@pytest.mark.parametrize("kind", ["equal", "outlier", "close", "zeros"])
 def test_retention_of_crowded_scores(oracle, ln, kind):
     print(f"retention of crowded scores len={ln} {kind}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(ln)
@@ -20,6 +20,10 @@ def test_retention_of_crowded_scores(oracle, ln, kind):
     if kind == "outlier":                                  # three keys far above the rest
         k[:, :, [7, ln // 2, ln - 1]] *= 6.0
     q = 2.0 * torch.randn(1, H, 8, d, device="cuda", generator=g)
+    if kind == "zeros":                                    # a tenth of the keys so far above the rest that those weigh exactly nothing
+        k += torch.randn(1, H, ln, d, device="cuda", generator=g)
+        k[..., 0], q[..., 0] = -30.0, 40.0
+        k[:, :, ::10, 0] = 30.0
     shape = binding.make_shape(1, H, H, d, ln, 1, 8, "f32")
     ctx = binding.Context(shape, budget)
     keep_idx = torch.full((1, H, budget), -1, dtype=torch.int32, device="cuda")
@@ -27,6 +31,6 @@ def test_retention_of_crowded_scores(oracle, ln, kind):
     ctx.ls_kv_compress(shape, budget, q, k, None, keep_idx, keep_cnt)
     score = torch.empty((1, H, ln), dtype=torch.float32, device="cuda")
     ctx.debug_compress_score(shape, score)
-    assert (keep_cnt == budget).all()
+    assert (keep_cnt == budget).all() and (kind != "zeros" or (score == 0).float().mean() > 0.85)
     for h in range(H):
         np.testing.assert_array_equal(keep_idx[0, h].cpu().numpy(), oracle.topb(score[0, h].cpu().numpy(), budget))
