@@ -151,8 +151,9 @@ size_t ws_score(const ls_shape* s, bool lines) {
     }
     return b;
 }
-// (The selection itself takes 8 bytes per head and line beside its heads' first lines; the workspace that a shape is stated to
-// need has 24, as it always had.)
+// (The selection itself takes 8 bytes per head and line beside its heads' first lines.  The 24 that a shape is stated to need are what
+// contexts have had from the start, and what the parts of attention items and the bands of the window matrix then find free in
+// a context sized for another turn: stating less would give such a program a smaller workspace than it has now.)
 size_t ws_select(const ls_shape* s) {
     const size_t BH = (size_t)s->B * s->Hq;
     return 3 * up(2 * BH * (size_t)s->n * 4) + 2 * up(2 * BH * ls::SELECT_HEAD_LINES * 4);

@@ -18,8 +18,10 @@
 // So every allowed cell is visited exactly once.  Each wave owns 32 rows and skips the 32 x 32
 // sub-tiles in which none of its rows has an allowed cell.
 //
-// Tile products: S^T = K_tile * Q^T and O^T += V_tile^T * P^T on 32x32 MFMA, fp32 accumulation,
-// online softmax in the base-2 domain.  K is staged row-major in LDS, V transposed (see vt_col).
+// Tile products: S^T = K_tile * Q^T and O^T += V_tile^T * P^T on 32x32 MFMA, fp32 accumulation, softmax
+// in the base-2 domain.  bf16 (prefill_bf16_kernel): K and V rows go to LDS as they are, V is read back transposed, and the softmax
+// reference moves only where a sum of probabilities exceeds a limit.  fp32 (prefill_kernel): online softmax with the tile's maximum,
+// K staged row-major in LDS, V transposed (see vt_col).
 #include <type_traits>
 #include <hip/hip_ext.h>
 #include "ls_device.h"
@@ -1260,8 +1262,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     unsigned char* tiles = smem;                                         // [2][TILE_BYTES]
     int32_t* colring = reinterpret_cast<int32_t*>(smem + 2 * C::TILE_BYTES);   // [4][64] column ids of packed tiles
     uint32_t* colbits = reinterpret_cast<uint32_t*>(colring + 256);      // [4 waves][2][64] bitmap words for the masks of a packed tile
-    int32_t* wcnt = reinterpret_cast<int32_t*>(colbits + 512);           // [8]
-    uint16_t* kbl = reinterpret_cast<uint16_t*>(wcnt + 8);               // [tab_len] active key blocks
+    uint16_t* kbl = reinterpret_cast<uint16_t*>(colbits + 512);          // [tab_len] active key blocks
     const uint32_t tiles_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)tiles;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1718,7 +1719,7 @@ static void launch_combine(const PrefillArgs& a, hipStream_t st, const hipEvent_
 
 template <int D>
 static size_t prefill_bf16_smem(int tab_len) {
-    return 2 * (size_t)DirectCfg<D>::TILE_BYTES + 256 * 4 + 512 * 4 + 8 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
+    return 2 * (size_t)DirectCfg<D>::TILE_BYTES + 256 * 4 + 512 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
 }
 template <typename T, int D>
 static size_t prefill_smem_t(int tab_len) {

@@ -10,9 +10,9 @@
 //                 overlap prefix sums in LDS ahead of both.
 //   emit_kernel   one workgroup per (head, list): the chosen prefix of a sorted list becomes an
 //                 ascending index list (bitmap in LDS + prefix popcount).
-//   topb_*        Alg. 3: the `budget` largest scores per KV head by a radix select on the float bit patterns,
-//                 ties broken towards smaller indices, ascending output; by one workgroup a head up to TB_ONE_LEN
-//                 scores, spread over many, one launch per step, beyond.
+//   topb_*        Alg. 3: the `budget` largest scores per KV head, ties broken towards smaller indices, ascending output.
+//                 Up to TB_ONE_LEN scores one workgroup a head narrows the threshold by bins of equal span; beyond, a radix
+//                 select on the float bit patterns is spread over many, one launch per step.
 #include <type_traits>
 #include "ls_device.h"
 #include "ls_internal.h"
@@ -64,7 +64,7 @@ __device__ __forceinline__ uint32_t lanes_min(uint32_t x) {
     return dpp_min<0x143, 0xC>(x);                         // row_bcast31 into rows 2 and 3
 }
 __device__ __forceinline__ uint32_t lanes_max(uint32_t x) { return ~lanes_min(~x); }
-// digits of 10 bits at most that hold a number below 2^width
+// bits of a number
 __device__ __forceinline__ int width_of(uint32_t x) { return x == 0u ? 0 : 32 - __builtin_clz(x); }
 
 // What the workgroup keeps beside the keys: `red` for sums over the waves (two rounds that follow each other use different halves).
@@ -932,7 +932,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             for (int j = 0; j < PER; ++j) { fx[j] = fxn[j]; fw[j] = w_l[fx[j]]; }
             fetch_idx(b + 1, fxn);
         };
-        {                                                  // block 0: its weights were written in order by the merge
+        {                                                  // block 0: its weights were written in order by order_kernel
             const float* hw = a.head_w + ((int64_t)l * a.BH + bh) * WALK_BLK;
             fetch_idx(0, fx);
 #pragma unroll
@@ -977,7 +977,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
         const float* m_l = (l == 0 ? a.smax : a.vmax) + (int64_t)bh * a.n;     // maxima by line index
         float m[WALK_EB], mn[WALK_EB];
         int32_t ix[WALK_EB];                   // line indices of the block after the next one's maxima
-        {                                      // block 0: its maxima were written in order by the merge
+        {                                      // block 0: its maxima were written in order by order_kernel
             const float* hm = a.head_m + ((int64_t)l * a.BH + bh) * WALK_BLK;
 #pragma unroll
             for (int e = 0; e < WALK_EB; ++e) { const int i = WALK_EB * lane + e; const float t = hm[i < n ? i : n - 1]; m[e] = i < n ? t : 0.f; }
