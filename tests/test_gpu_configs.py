@@ -268,7 +268,7 @@ def test_config5_llama70b_decode_compress(oracle):
 
 
 def test_maximum_context_length(oracle):
-    """n = LS_MAX_N (262144): 32 sort segments, the largest diagonal bitmap and activity table, a short newest turn
+    """n = LS_MAX_N (262144): lists put in order in 64 ranges, the largest diagonal bitmap and activity table, a short newest turn
     so that the oracle stays quick.  Structured inputs (sinks, heavy columns, a local band) as in the workloads."""
     cfg = inputs.scaled(inputs.CONFIGS["llama8b_8k"], n=262144, Hq=2, Hkv=1, turns=256, name="max_n")
     assert cfg.n_hat == 1024

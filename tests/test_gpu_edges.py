@@ -310,7 +310,7 @@ def test_walk_sums(oracle, n, alpha, kind):
 
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1024, 1025, 2047, 2048, 2049, 8191, 8192, 8193])
 def test_sorted_and_emitted_lists(oracle, n):
-    """Lengths around the segments of the sort, its waves' slices and the lists that the walk writes out itself; few distinct
+    """Lengths around the waves' shares of a list, the lists in one range and those that the walk writes out itself; few distinct
     weights, so that the order of equal ones shows."""
     from tests.gpu_util import host
     from tests.test_gpu_configs import check_selection_exact

@@ -113,8 +113,8 @@ def test_select_ties_and_capacity(oracle):
 
 @pytest.mark.parametrize("heads", [2, 16, 24])
 def test_select_ties_across_sort_segments(oracle, heads):
-    """Equal weights spread over several sort segments (the last one ragged): the order of equal weights is by
-    index, whichever segment they sit in.  The segment length follows n * heads (2048, 4096 and 8192 here)."""
+    """Equal weights by the thousand, in lists that are put in order in several ranges of weights: the order of equal weights is by
+    index, wherever a range begins or ends among them.  The number of ranges follows n and the heads (50, 8 and 5 here)."""
     n, n_hat = 3 * 8192 + 517, 4000
     rng = np.random.default_rng(11)
     sc = dict(vert=rng.integers(0, 6, (1, heads, n)).astype(np.float32) / 8192,

@@ -81,7 +81,8 @@ def test_items_are_shared_as_the_device_says(B, Hq, Hkv, n, n_hat, d):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("Hq,Hkv,n,n_hat,d", [(16, 4, 3001, 3001, 64), (8, 2, 4096, 4096, 128), (32, 8, 5003, 300, 128), (32, 8, 4099, 4099, 128)])
+@pytest.mark.parametrize("Hq,Hkv,n,n_hat,d", [(16, 4, 3001, 3001, 64), (8, 2, 4096, 4096, 128), (32, 8, 5003, 300, 128), (32, 8, 4099, 4099, 128),
+                                                (20, 4, 21001, 21001, 64)])      # queues whatever the room: beyond the line
 def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
     """A workspace with room for some of the parts: items are still cut, in fewer pieces or by the queues, to the same result."""
     from tests.gpu_util import Pipeline, dev_lists
@@ -93,7 +94,7 @@ def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
     ref, rlse = pipe.prefill(lists, sentinel=True)
     items = Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128)
     places = 512 if d == 128 else 768
-    slots = places - 1 + min(items, places - 1)
+    slots = places - 1 + min(items, places - 1) if _tiles(1, Hq, n, n_hat, d) <= LINE else 1024
     tables = Hq * ((n + 31) // 32 * 4 + 64 + (n // 64 + 5) * 3) + items * 20 + 16384
     tol = 4 * 2.0 ** -9 * float(np.abs(v).max())                      # as between queues and pieces
     for share in (1.0, 0.99, 0.9, 0.7, 0.667, 0.5, 0.3, 0.1, 0.02):
