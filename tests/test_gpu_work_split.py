@@ -82,7 +82,7 @@ def test_items_are_shared_as_the_device_says(B, Hq, Hkv, n, n_hat, d):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv,n,n_hat,d", [(16, 4, 3001, 3001, 64), (8, 2, 4096, 4096, 128), (32, 8, 5003, 300, 128), (32, 8, 4099, 4099, 128),
-                                                (20, 4, 21001, 21001, 64)])      # queues whatever the room: beyond the line
+                                                (20, 4, 130001, 3300, 64)])      # queues whatever the room: beyond the line
 def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
     """A workspace with room for some of the parts: items are still cut, in fewer pieces or by the queues, to the same result."""
     from tests.gpu_util import Pipeline, dev_lists
@@ -94,7 +94,9 @@ def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
     ref, rlse = pipe.prefill(lists, sentinel=True)
     items = Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128)
     places = 512 if d == 128 else 768
-    slots = places - 1 + min(items, places - 1) if _tiles(1, Hq, n, n_hat, d) <= LINE else 1024
+    slots, fewest = places - 1 + min(items, places - 1), 0.3          # fewest: share of them with which items are still cut
+    if _tiles(1, Hq, n, n_hat, d) > LINE:                             # (the longest part grows by half until all parts fit)
+        slots, fewest = 1024, 0.5
     tables = Hq * ((n + 31) // 32 * 4 + 64 + (n // 64 + 5) * 3) + items * 20 + 16384
     tol = 4 * 2.0 ** -9 * float(np.abs(v).max())                      # as between queues and pieces
     for share in (1.0, 0.99, 0.9, 0.7, 0.667, 0.5, 0.3, 0.1, 0.02):
@@ -104,7 +106,7 @@ def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
         torch.cuda.synchronize()
         assert ctx.profile_prefill_kernel_ms()[1] == 1
         queues, _, cuts = ctx.debug_prefill_queues(pipe.shape)
-        assert (cuts > 0 or share < 0.3) and len(np.unique(np.concatenate(queues))) == sum(map(len, queues)) == items, (share, cuts)
+        assert (cuts > 0 or share < fewest) and len(np.unique(np.concatenate(queues))) == sum(map(len, queues)) == items, (share, cuts)
         assert not torch.isnan(out).any()
         assert (out.float() - ref.float()).abs().max().item() <= tol
         some = torch.isfinite(rlse)
