@@ -56,6 +56,16 @@ __host__ __device__ __forceinline__ uint32_t item_work(uint32_t base, uint32_t n
 // 1.91 / 2.06, 2000 of 30000 2.10 / 1.95 / 1.96 / 2.04, d = 64, 1777 of 5003 2.02 / 1.89 / 1.90 / 1.92.  It costs 0.5 % of the attention of
 // a long turn, 4 % of one of 61 rows.
 constexpr float SOFT_LIMIT = 32.f, SOFT_FIRST = 2.f;
+// Where a row's logits rise along the keys (heads that look at the newest keys most), nearly every half would be done again.  A wave whose
+// halves exceed the limit that often (SOFT_OFTEN: 4 for each, less 1 a tile) sets its references 2^32 above the maxima from then on, until
+// the last two contiguous tiles, where such rows have their largest cells: those are done with the maxima as the references again.
+// (In between, what values of V below 2^-94 add is too small for fp32.)
+// 4096 of 16384 rows, 8 dense heads whose logits rise by 0 / 1 / 4 / 16 / 32 (base 2) in 64 keys, us: without 326 / 363 / 387 / 402 / 396, with
+// 316 / 342 / 325 / 328 / 354 (a maximum per tile 361 / 365 / 344 / 341 / 340); d = 64 196 / 221 / 264 / 259 / 258, with 194 / 210 / 208 / 205 / 229.
+// Error against 64 bits 2.32 / 2.27 / 2.11 / 1.90 / 1.83e-3, with 2.32 / 2.17 / 2.01 / 1.90 / 1.84e-3 (without the last two tiles' part
+// 2.32 / 2.34 / 2.30 / 2.21 / 2.09e-3).  Other rows pay 0.1 to 0.5 % of the attention for the count.
+constexpr int SOFT_OFTEN = 40, SOFT_RISING = 1 << 29;      // (what the count is from then on)
+constexpr float SOFT_AHEAD = 32.f;
 
 // ---------------------------------------------------------------------------------------------
 // plan: per (batch, head) bitmap of the selected diagonals, the per-j activity table, a head flag.
@@ -1347,6 +1357,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     // might exceed the limit, so that most tiles need no rescaling of the accumulators.
     const float sc2 = a.scale_log2e;
     float mneg = INFINITY, l_run = 0.f, limit = SOFT_FIRST;
+    int often = 0;                                         // how often halves exceed the limit (uniform)
 
     // ---- staging.  Wave wv fetches rows 16 wv .. 16 wv + 15 of each operand, IPW instructions of RPI rows, which share one M0:
     // an instruction's offset moves its source and its target alike, and where the target moves further (K_LAG) the
@@ -1449,7 +1460,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     auto apart = [](int x) { asm volatile("" : "+v"(x)); return __builtin_amdgcn_readfirstlane(x); };      // a condition that is not joined with others
     struct Soft { uint32_t p[8]; float sum[2]; };          // packed probabilities and their sums
-    auto process = [&](int tileoff) {
+    auto process = [&](int t) {
         f32x16 sa, sb;
         Soft pa, pb;
         limit = fminf(limit * 2.f, SOFT_LIMIT);
@@ -1493,7 +1504,18 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
 #pragma unroll
                 for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
                 mx = max32(mx) * sc2;
-                const float m_new = fmaxf(mx, -mneg);      // in base 2
+                float m_new = fmaxf(mx, -mneg);            // in base 2
+                often = (often > t ? often : t) + 4;
+                if (often - t > SOFT_OFTEN) {
+                    asm volatile("");                      // (rare: a branch, no selects)
+                    often = SOFT_RISING;
+                    if (limit < 0.f) {                     // back to the maxima, once
+                        if (limit == -2.f) m_new = fmaxf(mx, -mneg - SOFT_AHEAD);
+                        limit = t < n1 ? -4.f : SOFT_LIMIT;
+                    } else if (t + 2 < n1) {
+                        m_new = mx > -mneg ? mx + SOFT_AHEAD : -mneg;
+                    }
+                }
                 const float corr = m_new > -INFINITY ? fast_exp2(-mneg - m_new) : 1.f;
                 mneg = -m_new;
                 const float safe = m_new > -INFINITY ? mneg : 0.f;
@@ -1551,7 +1573,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         };
         // (The accumulators change in straight code and under conditions without an else only: where both sides of a choice
         // changed them, the compiler, which gives every choice the form of two guarded parts, kept them twice and moved them.)
-        const unsigned char* t0 = tiles + tileoff;
+        const unsigned char* t0 = tiles + (t & 1) * C::TILE_BYTES;
         const int two = (halves & 3) == 3, h0 = (halves & 3) == 2;
         const uint32_t am0 = h0 ? am[1] : am[0];
         scores(sa, t0 + h0 * SUB);
@@ -1659,12 +1681,15 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     for (int t = tbeg; t < ntiles; ++t) {
         const bool next = t + 1 < ntiles;
         if (next && t + 1 < n1) keep_words(kb_next);
-        if (t + 2 >= n1 && t + 2 < ntiles) request_cols(t + 2);
+        if (t + 2 >= n1) {
+            if (t + 2 < ntiles) request_cols(t + 2);
+            if (t + 2 == n1 && often == SOFT_RISING) limit = -1.f;       // (no sum is less: every half from here on)
+        }
         if (next && t + 1 >= n1) { col_words_of(t + 1); issue_cols(t + 1); }
         if (next && t + 1 < n1) { issue_k(kb_next, t + 1); issue_v(kb_next, t + 1); }
         const int kb_after = t + 2 < n1 && t + 2 < ntiles ? (int)kbl[t + 2 - tbeg] : 0;
         const int active = halves & 3;
-        if (active) process((t & 1) * C::TILE_BYTES);  // some of this wave's rows have an allowed cell here
+        if (active) process(t);                        // some of this wave's rows have an allowed cell here
         if (apart(active) == 0) for (int k = 0; k < 4; ++k) mask_step(k);
         kb_next = __builtin_amdgcn_readfirstlane(kb_after);
         wait_transfers();                                  // this wave's transfers of tile t+1 have landed
