@@ -37,6 +37,8 @@ constexpr int ORDER_THREADS = 1024;
 constexpr int ORDER_WAVES = 16;
 constexpr int ORDER_CHUNKS = 10;               // most lines of a workgroup, in 1024
 constexpr int ORDER_ONE = 4096;                // longest list that one workgroup puts in order
+constexpr int ORDER_SAMPLES = 2048;            // of a list, for the bounds of its ranges
+constexpr int ORDER_WIDE = 65536;              // lists beyond: shorter ranges, with more room
 constexpr int ORDER_FULL = 32;                 // lines of the fullest bin that are still ranked against each other
 constexpr int order_fine(int pt) { return pt * 2 * ORDER_THREADS; }        // fine bins, where a thread has `pt` words of them
 constexpr size_t order_lds_bytes(int pt, int cap) { return (size_t)order_fine(pt) * 2 + 16 + 1024 * 4 + (size_t)cap * 12; }
@@ -101,13 +103,14 @@ __device__ __forceinline__ uint32_t order_scan(uint32_t x, uint32_t* red, int la
 struct OrderBound { uint32_t key; int32_t line; bool earlier, later; };
 
 // The bounds of range `b` of `nb`: the samples of rank b S / nb and (b + 1) S / nb among S = 2048 of them, two a thread (sample i before
-// sample i + 1 in the list).  The key is found to 20 bits of the samples' span, and to the last bit where more than a sixteenth of
-// a range's share of samples lies in one such step; the line is given where as many samples have one weight: its lines then fall
+// sample i + 1 in the list).  The key is found to 20 bits of the samples' span, and to the last bit where more than `few`
+// samples lie in one such step; the line is given where as many samples have one weight: its lines then fall
 // to several ranges.  The same numbers in every workgroup of the list: a bound depends on its rank alone.
 // hist: 4096 words of LDS.
-__device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int32_t (&pos)[2], int b, int nb, uint32_t* hist, OrderSync& sync, OrderBound& from, OrderBound& to) {
+__device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int32_t (&pos)[2], int b, int nb, uint32_t few, uint32_t* hist, OrderSync& sync, OrderBound& from, OrderBound& to) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    constexpr int PER = 2, S = PER * ORDER_THREADS;
+    constexpr int PER = 2, S = ORDER_SAMPLES;
+    static_assert(S == PER * ORDER_THREADS, "two a thread");
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
     hist[tid] = 0u; hist[1024 + tid] = 0u;
 #pragma unroll
@@ -146,7 +149,6 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int
     rest0 = sync.rest[0]; rest1 = sync.rest[1];
     from = OrderBound{lo + (f0 << sh), -1, false, false};
     to = OrderBound{lo + (f1 << sh), -1, false, false};
-    const uint32_t few = (uint32_t)(S / (16 * nb));
     if (many0 <= few && many1 <= few) return;              // (uniform, as all of this)
     if (sh > 0) {                                          // the last bits, at most 12
 #pragma unroll
@@ -207,7 +209,7 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int
 //     and then by index; bins with too many lines are spread again, each over as many bins as it has lines;
 //   - writes their indices (sidx) where they belong; the first WALK_BLK lines of the order get their weight and maximum written as
 //     well (head_w, head_m), so that the walk can start without a second round trip.
-// The lines of a weight that has ranges to itself are written as they come, by one workgroup, and so is a range's share of a weight that
+// The lines of a weight that has ranges to itself are written as they come, by one workgroup, and so are many lines of weights that
 // two ranges meet in.  A range of more than `cap` lines all the same (the samples missed them) is halved until it fits.
 //
 // What bounds it: latencies, one workgroup of sixteen waves per CU: 32768 lines, cycles of one of 4 workgroups: bounds and count 14800, lines
@@ -219,8 +221,12 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int
 // Lists that crowd, 32 heads, the kernel alone, us, by digits / now / segments of 8192 sorted by digits and merged:
 // all but ten lines within 2^12 numbers 1024 lines 13.6 / 10.7 / 7.7, 4096 27.9 / 17.1 / 14.4, 32768 122 / 48 / 54, 131072 320 / 354 / 323; two thirds of one
 // weight, the others of 59 4096 31.9 / 21.6 / 17.7, 32768 96 / 47 / 59, 131072 300 / 238 / 326; two fifths zero 4096 25.6 / 18.3 / 15.0, 32768 34 / 33 / 53,
-// 131072 233 / 219 / 317; 59 weights 4096 26.6 / 16.9 / 17.0, 32768 69 / 57 / 56, 131072 408 / 454 / 314 (there every range ends inside a
-// weight on both sides, and its two looks through the list take half as long again).
+// 131072 233 / 219 / 317; 59 weights 4096 26.6 / 16.9 / 17.0, 32768 69 / 57 / 56.
+// Where a range begins or ends inside a weight its looks through the list take longer.  So weights of less than two fifths of a range are left whole
+// beyond ORDER_WIDE lines, where there is room for them, and lines at the ends are ranked with the others unless they are more than
+// half.  ls_select that ends after its first pick, by digits / every weight shared that has a sixteenth, its lines written apart / now / segments:
+// 59 weights 80862 lines 332 / 284 / 217 / 199, 131072 432 / 466 / 387 / 309, 262144 1020 / 1300 / 1240 / 880 (there each has two thirds of a range);
+// 300 weights 131072 406 / 462 / 329 / 315; two thirds of one weight 131072 356 / 281 / 215 / 328; within 2^12 numbers 262144 1745 / 1230 / 934 / 946.
 // (WHOLE: two workgroups per CU; 256 heads of 1500 lines, the whole ls_select, 29.4 -> 27.9.)
 template <int PT, bool WHOLE>
 __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(SelectArgs a, int nb, int cap) {
@@ -275,7 +281,10 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
             where[j] = (int)((int64_t)i * n / (2 * ORDER_THREADS)) + (int)((((uint32_t)i * 0x9E3779B1u) >> 16) * (uint32_t)len >> 16);
             sample[j] = desc_key(src[where[j]]);
         }
-        order_bounds(sample, where, b, nb, words, sync, from, to);
+        // weights of so many samples are shared: two fifths of a range where it has room for that beside its own, a sixteenth where they would leave the
+        // ranges unequal
+        const uint32_t few = (uint32_t)(n > ORDER_WIDE ? 2 * ORDER_SAMPLES / (5 * nb) : ORDER_SAMPLES / (16 * nb));
+        order_bounds(sample, where, b, nb, few, words, sync, from, to);
         const bool last = b == nb - 1;
         if (b == 0) from = OrderBound{0u, -1, false, false};
         // A weight that has ranges to itself: the first of them takes all its lines, those at its ends none
@@ -310,6 +319,7 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
     if (!WHOLE && tid < 4) sync.cross[tid] = 0x7FFFFFFF;
     for (;;) {
         int before = w0, m = n;                            // lines of the range in the waves before, and in all (a list in one range: all lines)
+        bool picked = false;
         const uint32_t span = hi - lo;
         if (!WHOLE && nb > 1) {
             uint32_t here = 0u, below = 0u, fronts = 0u, backs = 0u;
@@ -317,8 +327,8 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
                 auto count = [&](int i, uint32_t k, bool any) {
                     if (decltype(ENDS)::value) {
                         const uint64_t x = (uint64_t)k << 32 | (uint32_t)i;
-                        const bool in = any && x - lo_line <= end_line - lo_line, f = in && k == front, r = in && k == back && !f;
-                        fronts += f ? 1u : 0u; backs += r ? 1u : 0u; here += in ? 1u : 0u;
+                        const bool in = any && x - lo_line <= end_line - lo_line;
+                        here += in ? 1u : 0u; fronts += in && k == front ? 1u : 0u; backs += in && k == back ? 1u : 0u;
                         below += any && x < lo_line ? 1u : 0u;
                     } else {
                         here += any && k - lo <= span ? 1u : 0u;
@@ -349,8 +359,7 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
             here = lanes_upto(here); below = lanes_upto(below);
             __syncthreads();                               // `red` and the last range's lines are free again
             if (ends) {
-                fronts = lanes_upto(fronts); backs = lanes_upto(backs);
-                here -= fronts + backs;
+                fronts = lanes_upto(fronts); backs = front == back ? 0u : lanes_upto(backs);
                 if (lane == 63) { sync.red[2][wv] = fronts; sync.red[3][wv] = backs; }
             }
             if (lane == 63) { sync.red[0][wv] = here; sync.red[1][wv] = below; }
@@ -360,22 +369,26 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
             (void)waves_before(sync.red[1], lane, wv, ahead);
             m = (int)all;
             if (base < 0) base = (int)ahead;
-            if (ends) {                                    // the order of the lines at the ends is there; the others are picked on the way
+            if (ends) {
                 uint32_t f_all, r_all;
-                int f_at = base + (int)waves_before(sync.red[2], lane, wv, f_all), r_at = (int)waves_before(sync.red[3], lane, wv, r_all);
-                base += (int)f_all;
-                r_at += base + m;
-                int at = before;
-                const bool take = m <= cap;
-                if (!alone || (w1 > (int)(uint32_t)lo_line && w0 <= (int)(uint32_t)end_line)) read([&](int i, uint32_t k, bool any) {
-                    const uint64_t x = (uint64_t)k << 32 | (uint32_t)i;
-                    const bool in = any && x - lo_line <= end_line - lo_line, f = in && k == front, r = in && k == back && !f, mid = in && !f && !r;
-                    const uint64_t fs = __ballot(f), rs = __ballot(r), who = __ballot(mid);
-                    if ((i & 0xFFFF) == 0 && any) sync.cross[i >> 16] = at;
-                    if (mid && take) { const int p = at + lanes_before(who); keys[p] = k; line[p] = (uint16_t)i; }
-                    if (f || r) put((f ? f_at : r_at) + lanes_before(f ? fs : rs), i, k);
-                    f_at += __popcll(fs); r_at += __popcll(rs); at += __popcll(who);
-                });
+                const int f_before = (int)waves_before(sync.red[2], lane, wv, f_all), r_before = (int)waves_before(sync.red[3], lane, wv, r_all);
+                if (m > cap || 2 * (int)(f_all + r_all) > m) {               // the order of the lines at the ends is there: they are written now, the others picked on the way
+                    before -= f_before + r_before; m -= (int)(f_all + r_all);
+                    int f_at = base + f_before, at = before;
+                    base += (int)f_all;
+                    int r_at = base + m + r_before;
+                    picked = m <= cap;
+                    if (!alone || (w1 > (int)(uint32_t)lo_line && w0 <= (int)(uint32_t)end_line)) read([&](int i, uint32_t k, bool any) {
+                        const uint64_t x = (uint64_t)k << 32 | (uint32_t)i;
+                        const bool in = any && x - lo_line <= end_line - lo_line, f = in && k == front, r = in && k == back && !f, mid = in && !f && !r;
+                        const uint64_t fs = __ballot(f), rs = __ballot(r), who = __ballot(mid);
+                        if ((i & 0xFFFF) == 0 && any) sync.cross[i >> 16] = at;
+                        if (mid && picked) { const int p = at + lanes_before(who); keys[p] = k; line[p] = (uint16_t)i; }
+                        if (f || r) put((f ? f_at : r_at) + lanes_before(f ? fs : rs), i, k);
+                        f_at += __popcll(fs); r_at += __popcll(rs); at += __popcll(who);
+                    });
+                    ends = false;
+                }
             }
         }
         uint32_t least = 0xFFFFFFFFu, most = 0u;
@@ -390,7 +403,7 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
             read([&](int, uint32_t k, bool any) { extremes(k, any && k - lo <= span); });
             __syncthreads();
             agree();
-            if (least < most) { lo = least; hi = least + (most - least) / 2; ends = false; continue; }           // the lower half of the span that its weights have
+            if (least < most) { lo = least; hi = least + (most - least) / 2; continue; }           // the lower half of the span that its weights have
             read([&](int i, uint32_t k, bool any) {        // equal weights: the order is there
                 const bool in = any && k == least;
                 const uint64_t who = __ballot(in);
@@ -403,15 +416,17 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
             if (WHOLE) {
                 for (int p = tid; p < m; p += ORDER_THREADS) { const uint32_t k = desc_key(src[p]); keys[p] = k; extremes(k, true); }
             } else {
-                if (!ends)
+                auto pick = [&](auto ENDS) {
                     read([&](int i, uint32_t k, bool any) {
-                        const bool in = any && k - lo <= span;
+                        const bool in = any && (decltype(ENDS)::value ? ((uint64_t)k << 32 | (uint32_t)i) - lo_line <= end_line - lo_line : k - lo <= span);
                         const uint64_t who = __ballot(in);
                         const int at = before + lanes_before(who);
                         if (in) { keys[at] = k; line[at] = (uint16_t)i; }
                         if ((i & 0xFFFF) == 0 && any) sync.cross[i >> 16] = before;
                         before += __popcll(who);
                     });
+                };
+                if (ends) pick(std::true_type{}); else if (!picked) pick(std::false_type{});
                 __syncthreads();
                 for (int p = tid; p < m; p += ORDER_THREADS) extremes(keys[p], true);
             }
@@ -571,7 +586,7 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
         }
         base += m;
         if (hi == end) break;
-        lo = hi + 1u; hi = end; ends = false;
+        lo = hi + 1u; hi = end;
     }
 }
 
@@ -1945,13 +1960,13 @@ static void launch_emit(const SelectArgs& a, hipStream_t st) {
 static hipError_t sort_lines(const SelectArgs& a, hipStream_t st) {
     int64_t nb = 1;
     if (a.n > ORDER_ONE) {
-        nb = a.n > 65536 ? (a.n + 6553) / 6554 : (a.n + 8191) / 8192;
+        nb = a.n > ORDER_WIDE ? (a.n + 6553) / 6554 : (a.n + 8191) / 8192;
         const int64_t fill = 256 / (2 * (int64_t)a.BH), most = (a.n + 511) / 512;
         const int64_t more = fill < most ? fill : most;
         if (nb < more) nb = more;
     }
     int64_t chunks = nb == 1 ? (a.n + 1023) / 1024 : (a.n * 5 / (4 * nb) + 256 + 1023) / 1024;
-    if (chunks > ORDER_CHUNKS) chunks = ORDER_CHUNKS;
+    if (chunks > ORDER_CHUNKS || a.n > ORDER_WIDE) chunks = ORDER_CHUNKS;
     const int cap = (int)chunks * 1024;
     const dim3 grid(2 * (unsigned)a.BH, (unsigned)nb);
     auto launch = [&](auto kernel, int pt) { hipLaunchKernelGGL(kernel, grid, dim3(ORDER_THREADS), order_lds_bytes(pt, cap), st, a, (int)nb, cap); };

@@ -42,7 +42,8 @@ KINDS = {
                                     (33, "one"), (700, "crowd"), (1024, "few"), (1000, "two"), (1024, "nested"), (4096, "few"), (4096, "zeros"), (4095, "but_one"),
                                     (4096, "nested"), (8192, "zeros"), (8192, "few"), (8191, "two"), (10240, "nested"), (30011, "few"), (30011, "zeros"),
                                     (30011, "two"), (30011, "one"), (30011, "but_one"), (30011, "nested"), (131071, "few"), (131071, "equal"),
-                                    (65537, "zeros"), (65537, "crowd")])
+                                    (65537, "zeros"), (65537, "crowd"),
+                                    (80862, "few"), (131072, "two"), (262144, "few"), (262143, "crowd"), (200001, "nested")])
 def test_lists_in_ranges(oracle, n, kind, H=3):
     from tests.gpu_util import host
     from tests.test_gpu_configs import check_selection_exact
