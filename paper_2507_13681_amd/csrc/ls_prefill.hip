@@ -362,9 +362,15 @@ __host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work
 // workgroup is not busy.  So where every place is taken the pieces of a place are that much larger or smaller.  Shares of
 // 64 / 64, 67 / 61, 70 / 58, 73 / 55, 76 / 52, the whole call, us: 8192 rows, all new, 300 / 296 / 291 / 290 / 297, 2048 of 32768 481 / 473 / 465 /
 // 460 / 475; at d = 64 64, 69, 74, 79, 84 for the first of three 90 / 88 / 88 / 88 / 87, 5003 rows, all new, 73 / 71 / 71 / 71 / 70.
+//
+// But not where items of alike work come out in whole pieces, or pieces in whole items (few row blocks a head, `equal` in my_span): then equal
+// pieces leave most items uncut, and the query heads of a group, cut at the same tiles, meet at the same keys in the L2.  By place / equal,
+// us: 8 dialogues, 8 heads of 128, 2 rows of 98648 keys 551 / 326; 4, 64 heads, 4 rows of 11569, every diagonal, 237 / 164; 4, 32 heads of 64, columns, 331
+// rows of 9141 28 / 24; the other way 4, 32 heads, 84 rows of 1435 53 / 57, 2, 64 heads, one of them dense, 3 rows of 116925 115 / 124.  (Short turns of 10 to 130000
+// keys, 1 to 64 dialogues: of 108 that are so 27 gain more than 3 %, 7 lose more; of 51 that are not, 12 and 10.  fp32, whose tiles wait for no memory: 52 / 56.)
 constexpr uint32_t FIRST_OF_2 = 72, FIRST_OF_3 = 80;       // of 128, of 192 (the second of three: 64)
-__host__ __device__ __forceinline__ uint32_t cut_at(uint32_t total, int p, int pieces) {
-    if (pieces == 512 || pieces == 768) {                  // 32 CUs an XCD, whose workgroups take neighbouring pieces
+__host__ __device__ __forceinline__ uint32_t cut_at(uint32_t total, int p, int pieces, bool equal) {
+    if (!equal && (pieces == 512 || pieces == 768)) {                  // 32 CUs an XCD, whose workgroups take neighbouring pieces
         const uint32_t places = pieces / 256, xcd = (uint32_t)p / (32 * places), j = (uint32_t)p % (32 * places);
         const uint32_t w0 = places == 2 ? FIRST_OF_2 : FIRST_OF_3, w1 = places == 2 ? 128 - FIRST_OF_2 : 64, w2 = 192 - w0 - w1;
         const uint32_t at = xcd * 32 * 64 * places + (j < 32 ? j * w0 : j < 64 ? 32 * w0 + (j - 32) * w1 : 32 * (w0 + w1) + (j - 64) * w2);
@@ -404,7 +410,8 @@ __device__ __forceinline__ Span my_span(const PrefillArgs& a, uint32_t* sh) {   
     s.from = s.to = Cut{items, 0};
     s.rec = 0u;
     if (s.piece < 0) return s;
-    const uint32_t x0 = cut_at(total, s.piece, s.pieces), x1 = cut_at(total, s.piece + 1, s.pieces);
+    const bool equal = a.nqb <= 2 && a.dtype == 0 && (s.pieces % items == 0 || items % s.pieces == 0);
+    const uint32_t x0 = cut_at(total, s.piece, s.pieces, equal), x1 = cut_at(total, s.piece + 1, s.pieces, equal);
     if (x0 < before + mine && x1 >= before) {
         uint32_t at = before;
         for (int h = h0; h < h1; ++h) {

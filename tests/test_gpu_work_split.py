@@ -112,3 +112,30 @@ def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
         some = torch.isfinite(rlse)
         assert torch.equal(torch.isfinite(lse), some)
         assert (lse[some] - rlse[some]).abs().max().item() <= 1e-4
+
+
+# row blocks a head, and heads, at which pieces and items come out in each other (512 and 768 pieces) or just do not
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d", [(2, 32, 8, 6001, 3, 128), (4, 64, 8, 1200, 130, 128), (2, 64, 8, 3001, 5, 64), (3, 64, 8, 2999, 129, 64),
+                                               (2, 33, 3, 3001, 1, 128), (4, 64, 8, 1200, 300, 128)])
+def test_short_turns_of_many_heads(B, Hq, Hkv, n, n_hat, d):
+    """Against the same call without room for parts: queues of whole items."""
+    from tests.gpu_util import Pipeline, dev_lists
+    from paper_2507_13681_amd import binding
+    print(f"short turns of many heads B={B} Hq={Hq} n={n} n_hat={n_hat} d={d}", flush=True)
+    q, k, v = inputs.make_plain(B, Hq, Hkv, n, n_hat, d, dtype="bf16", seed=n, q_scale=1.5)
+    lists = dev_lists(*_lists(np.random.default_rng(n), B, Hq, n))
+    pipe = Pipeline(q, k, v, 1, "bf16")
+    out, lse = pipe.prefill(lists, sentinel=True)
+    queues, blocks, _ = pipe.ctx.debug_prefill_queues(pipe.shape)
+    items = B * Hq * blocks
+    assert len(np.unique(np.concatenate(queues))) == sum(map(len, queues)) == items
+    pipe.ctx = binding.Context(workspace=B * Hq * ((n + 31) // 32 * 4 + 64 + (n // 64 + 5) * 3) + items * 20 + 4096)
+    ref, rlse = pipe.prefill(lists, sentinel=True)
+    assert pipe.ctx.debug_prefill_queues(pipe.shape)[2] == 0
+    assert not torch.isnan(out).any()
+    tol = 4 * 2.0 ** -9 * float(np.abs(v).max())                      # as between queues and pieces
+    assert (out.float() - ref.float()).abs().max().item() <= tol
+    some = torch.isfinite(rlse)
+    assert torch.equal(torch.isfinite(lse), some)
+    assert (lse[some] - rlse[some]).abs().max().item() <= 1e-4
