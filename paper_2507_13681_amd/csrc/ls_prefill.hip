@@ -54,7 +54,9 @@ __host__ __device__ __forceinline__ uint32_t item_work(uint32_t base, uint32_t n
 // diagonal).  Error of the output against 64 bits, rms relative to it, 1e-3, with 65536 throughout / 16 / this / a maximum per tile and
 // moves beyond 2^8, as it was: 3000 of 6000 rows 2.05 / 1.97 / 1.98 / 1.99, 61 of 12347 2.09 / 1.92 / 1.87 / 1.92, 8192 rows, all new, 2.14 / 1.89 /
 // 1.91 / 2.06, 2000 of 30000 2.10 / 1.95 / 1.96 / 2.04, d = 64, 1777 of 5003 2.02 / 1.89 / 1.90 / 1.92.  It costs 0.5 % of the attention of
-// a long turn, 4 % of one of 61 rows.
+// a long turn, 4 % of one of 61 rows, and most where items have a handful of tiles: the 300 newest diagonals, 4402 rows of 13466, B 16, 16 heads 410 us,
+// at 16 from the second tile on 398, with a maximum per tile 382; d = 64, 7390 of 9251 rows 410, 390, 363.  (The first reference over both halves of
+// the first tile: nothing.  Errors at 16 from the second tile on 2.041, 1.983, 2.036e-3 instead of 2.037, 1.973, 2.035: not taken.)
 constexpr float SOFT_LIMIT = 32.f, SOFT_FIRST = 2.f;
 // Where a row's logits rise along the keys (heads that look at the newest keys most), nearly every half would be done again.  A wave whose
 // halves exceed the limit that often (SOFT_OFTEN: 4 for each, less 1 a tile) sets its references 2^32 above the maxima from then on, until
