@@ -169,7 +169,7 @@ size_t ws_prefill(const ls_shape* s) {
     const size_t BH = (size_t)s->B * s->Hq;
     const int64_t n_hat = s->n_hat > 0 && s->n_hat <= s->n ? s->n_hat : s->n;
     const size_t items = BH * (size_t)row_blocks(s->n, n_hat);   // (head, row block) work items
-    const bool pieces = ls::prefill_in_pieces((int)BH, s->n, (int)row_blocks(s->n, n_hat), s->d);
+    const bool pieces = ls::prefill_in_pieces((int)BH, s->n, (int)row_blocks(s->n, n_hat), s->dtype, s->d);
     const int grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, pieces);
     const size_t slots = (size_t)ls::prefill_split_slots((int64_t)items, grid, pieces);
     return up(BH * (size_t)(words_of(s->n) + 4) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(items * 4) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
@@ -416,7 +416,7 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
         while (slots > 0 && !take(slots)) --slots;         // (a slot has a few more bytes than its results, rounded up together)
         return slots;
     };
-    w.pieces = ls::prefill_in_pieces(BH, s->n, w.nqb, s->d);
+    w.pieces = ls::prefill_in_pieces(BH, s->n, w.nqb, s->dtype, s->d);
     w.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, w.pieces);
     if (w.pieces) {
         w.grid = ls::prefill_pieces_for((int64_t)items, w.grid, most_slots());

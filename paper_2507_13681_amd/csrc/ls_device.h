@@ -93,19 +93,6 @@ __device__ __forceinline__ void dma16(const unsigned char* gbase, uint32_t voff,
 __device__ __forceinline__ void dma16(const unsigned char* gptr, uint32_t lds) {                    // per-lane address
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(gptr) : "memory", "m0");
 }
-// N transfers (at most 4) whose targets lie STEP bytes apart, through one M0: transfer i fetches gbase + i * STEP + voff[i] to lds + i * STEP + 16 * l.
-template <int N, int STEP>
-__device__ __forceinline__ void dma16_rows(const unsigned char* gbase, const uint32_t (&voff)[N], uint32_t lds) {
-    static_assert(N == 2 || N == 4, "transfers");
-    static_assert((N - 1) * STEP < 4096, "instruction offset");
-    if constexpr (N == 4)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %5 offset:%6\n\t"
-                     "global_load_lds_dwordx4 %3, %5 offset:%7\n\tglobal_load_lds_dwordx4 %4, %5 offset:%8"
-                     ::"s"(lds), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(gbase), "n"(STEP), "n"(2 * STEP), "n"(3 * STEP) : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:%4"
-                     ::"s"(lds), "v"(voff[0]), "v"(voff[1]), "s"(gbase), "n"(STEP) : "memory", "m0");
-}
 // A wave-uniform address, told so to the compiler (which may compute it in vector registers all the same).
 __device__ __forceinline__ const unsigned char* uniform_ptr(const void* p) {
     const uint64_t u = reinterpret_cast<uint64_t>(p);

@@ -35,6 +35,9 @@ namespace ls {
 #ifndef LS_RING_P
 #define LS_RING_P 3       // V^T fragments in flight ahead of the P*V products
 #endif
+#ifndef LS_RING_PH
+#define LS_RING_PH 2      // ... with queues, where there are fewer registers
+#endif
 constexpr int BM = 128;   // query rows per workgroup
 constexpr int BN = 64;    // keys per tile
 constexpr int PREFILL_THREADS = 256;
@@ -324,14 +327,15 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // us: 2048 rows, all new, 92 -> 68; 1024 new of 8192 152 -> 124; 300 of 16384 89 -> 70; 100 of 131072 254 -> 230; 61 of 12347
 // 32.7 -> 30.3; 4 heads fp32, 256 of 1024 44 -> 38, 2048 all new 65 -> 37.
 // The line.  What the pieces' estimates miss nothing evens out, and the row spreads the heads of a moment wider than the queues
-// do: the longer the run, the more both cost.
-// Tiles here are those that dense heads would have, and a tile of d = 64 counts half.  Queues / pieces, the whole call, us:
-// 262144: 2048 of 32768 rows 507 / 460, 8192 rows all new 300 / 290; 400000 to 520000: 10000 rows 374 / 346, 6000 of 9000, B 2, 490 / 479,
-// 1000 of 131072 840 / 788; 570000 to 660000: 12000 rows 562 / 543, 5000 of 32768 1022 / 989, 2500 of 65536 927 / 944; 720000 and
-// more: 9000 of 20000 819 / 851, 14000 rows 511 / 528, 2000 of 131072 1769 / 1883, 10923 of 32768 1709 / 1816.  d = 64, 16 heads: 16384 rows
-// (526304) 163 / 124, 12000 of 30000 (714000) 375 / 347, 24000 rows (1130961) 367 / 307.
+// do: the longer the run, the more both cost.  In bf16 the queues' kernel also has a workgroup more per CU (prefill_bf16_kernel).
+// Tiles here are those that dense heads would have, and a tile of d = 64 counts half.  Pieces / queues, the whole call, us, d = 128:
+// 65536: 4096 rows, all new, 114 / 150; 129696: 2500 of 12347 253 / 285; 225216: 1000 of 50000 494 / 447; 262144: 8192, all new, 271 / 291,
+// 2048 of 32768 479 / 462; 282752: 64 heads, 6000, all new, 280 / 308; 396896 and more: 10000, all new, 353 / 350, 6000 of 9000, B 2, 508 / 477, 1000 of 131072
+// 785 / 679, 4096 of 8192, B 4, 605 / 538, 10923 of 32768 1957 / 1527.  d = 64: 524288: 16384 rows, 16 heads, 112 / 167, 8000 of 65536, 8 heads, 634 / 789;
+// 577536: 4000 of 9000, B 4, 500 / 505; 641024: 8000 of 20000 297 / 298; 704512 and more: 5462 of 16384, B 2, 682 / 635, 10923 of 32768 986 / 858 (but 20000,
+// all new, 417 / 487).  fp32, whose kernel is the same for both: 524288.
 // ---------------------------------------------------------------------------------------------
-constexpr int64_t PIECES_TILES = 524288;
+constexpr int64_t PIECES_TILES = 262144, PIECES_TILES_F32 = 524288;
 constexpr int CUT_TILES = 2;                               // fewest tiles on either side of a cut (a part costs its result written and read: the time of two)
 __host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : base + 8; }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
 
@@ -629,11 +633,11 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
     if (tid == 0) { a.qlen[x] = (int)entries; a.qbase[x] = (int)base; a.qhead[x] = (a.grid - x + 7) / 8; }
 }
 
-// Launch of the attention kernel: the workgroups that are resident at once (256 CUs x per_cu); any number drains the queues, but a
-// surplus one only starts when another ends and lengthens the run by its look at the queues.  Pieces: of few items a dozen each.
+// Launch of the attention kernel: the workgroups that are resident at once (256 CUs x per_cu, see prefill_bf16_kernel); any number drains the
+// queues, but a surplus one only starts when another ends and lengthens the run by its look at the queues.  Pieces: of few items a dozen each.
 constexpr int ITEM_PARTS = 12;
 int prefill_grid(int dtype, int d, int64_t items, bool pieces) {
-    const int per_cu = dtype == 0 ? (d == 128 ? 2 : 3) : (d == 128 ? 1 : 2);
+    const int per_cu = dtype == 0 ? (d == 128 ? 2 : 3) + (pieces ? 0 : 1) : (d == 128 ? 1 : 2);
     const int64_t most = pieces ? items * ITEM_PARTS : items + prefill_split_slots(items, 0, false);
     return (int)(most < 256 * per_cu ? most : 256 * per_cu);
 }
@@ -641,7 +645,7 @@ int prefill_split_slots(int64_t items, int grid, bool pieces) {
     if (pieces) return part_slots(items, grid);
     return items > SPLIT_ITEMS ? 0 : items * ITEM_PARTS < SPLIT_SLOTS ? (int)items * ITEM_PARTS : SPLIT_SLOTS;
 }
-bool prefill_in_pieces(int BH, int64_t n, int nqb, int d) { return (int64_t)BH * nqb * ((n + BN - 1) / BN) * d <= PIECES_TILES * 128; }
+bool prefill_in_pieces(int BH, int64_t n, int nqb, int dtype, int d) { return (int64_t)BH * nqb * ((n + BN - 1) / BN) * d <= (dtype == 0 ? PIECES_TILES : PIECES_TILES_F32) * 128; }
 
 // Pieces, of up to `grid`, whose parts `slots` hold; 0: the queues serve the call better.  Fewer pieces than workgroups make the run about
 // grid / pieces as long (of three places a CU only 5 % where two are filled), queues about a quarter of grid / items longer.  The whole
@@ -668,12 +672,14 @@ int prefill_piece_xcd(int p, int pieces) {
 // the end every workgroup would update it once for nothing, and updates of one counter take turns.  item = ~0 when every
 // queue is drained (each queue hands out each entry once and never refills, so the search ends).
 struct QueueSource {
-    int own, x, len, base;                    // lane l < 8: queue (own + l) % 8, its length, its first entry
+    int own;
     int at;                                   // place taken in the own queue, -1: none
     bool plenty;
-    __device__ __forceinline__ void init(const PrefillArgs& a, int lane) {
-        own = blockIdx.x & 7; x = (own + lane) & 7; len = lane < 8 ? a.qlen[x] : 0; base = a.qbase[x];
-        at = (int)(blockIdx.x >> 3); plenty = true;
+    // [8] lengths, [8] first entries of the queues (in LDS: one wave looks at them once an entry)
+    __device__ __forceinline__ static int* queues() { __shared__ int q[16]; return q; }
+    __device__ __forceinline__ void init(const PrefillArgs& a, int) {
+        own = blockIdx.x & 7; at = (int)(blockIdx.x >> 3); plenty = true;
+        if (threadIdx.x < 16) queues()[threadIdx.x] = threadIdx.x < 8 ? a.qlen[threadIdx.x] : a.qbase[threadIdx.x - 8];      // (read by the same wave)
     }
     __device__ __forceinline__ void ahead(const PrefillArgs& a, int lane) {
         if (!plenty) return;
@@ -682,6 +688,8 @@ struct QueueSource {
         at = __builtin_amdgcn_readfirstlane(i);
     }
     __device__ __forceinline__ uint4 next(const PrefillArgs& a, int lane) {
+        asm volatile("" : "+v"(lane));      // (addresses made of it are not to be kept through an entry)
+        const int x = (own + lane) & 7, len = lane < 8 ? queues()[x] : 0, base = queues()[8 + x];      // lane l < 8: queue (own + l) % 8
         const int own_len = __builtin_amdgcn_readfirstlane(len);
         if (at >= 0 && at < own_len) {
             const int i = at;
@@ -944,7 +952,12 @@ __device__ __forceinline__ uint32_t diag_cells(uint32_t hi, uint32_t lo, int r32
     const uint64_t w = (((uint64_t)hi << 32) | lo) >> 1;   // (uniform)
     return __brev(__builtin_amdgcn_alignbit((uint32_t)(w >> 32), (uint32_t)w, (uint32_t)r32)) >> (4 * g);
 }
-__device__ __forceinline__ int diag_half(uint32_t hi, uint32_t lo) { return (((lo & ~1u) | hi) != 0u ? 1 : 0) | ((hi & (lo | 1u)) == 0xFFFFFFFFu ? 4 : 0); }
+__device__ __forceinline__ int diag_half(uint32_t hi, uint32_t lo) {      // (as asm statements it stays in scalar registers)
+    uint32_t any, out;
+    asm("s_min_u32 %0, %1, 1" : "=s"(any) : "s"((lo & ~1u) | hi) : "scc");
+    asm("s_min_u32 %0, %1, 1" : "=s"(out) : "s"(~(hi & (lo | 1u))) : "scc");
+    return (int)(any | (out ^ 1u) << 2);
+}
 // Packed columns: lane l answers for column `col` (slot l of the tile; -1: none) and all 32 rows of the wave at once,
 // 32 bits of the bitmap in two words, and one bit transpose hands the rows their columns.  (Each lane testing the
 // columns of its row one after the other was a chain of up to 64 LDS reads per tile.)  A cell whose diagonal is selected
@@ -981,6 +994,11 @@ __device__ __forceinline__ float masked(float x, uint32_t am, int r) {      // x
 __device__ __forceinline__ float max32(float x) {                           // the larger of this lane's and lane ^ 32's value
     const auto b = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
     return fmaxf(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
+}
+
+__device__ __forceinline__ float sum32(float x) {                           // the sum of this lane's and lane ^ 32's value
+    const auto b = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+    return __builtin_bit_cast(float, (uint32_t)b[0]) + __builtin_bit_cast(float, (uint32_t)b[1]);
 }
 
 // Tile sequence of one workgroup: first the n1 key blocks crossed by a selected diagonal (ascending),
@@ -1243,7 +1261,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
 //     lane's bytes land is fixed; which bytes it fetches is free, so slot s of row r receives chunk
 //     s ^ swizzle(r) of that row.  The swizzles (kswz, vswz) are chosen so that the fragment reads
 //     below touch every LDS bank once per pass; for d = 128 the K transfers are also spaced 64 bytes
-//     apart.  All transfers of a wave then differ only in a uniform base address: one per-lane
+//     apart.  All transfers of a wave then differ only in uniform addresses: one per-lane
 //     offset register per operand serves the whole kernel.
 //   * V stays row-major; the V^T fragments of the P*V product come from the LDS transpose read
 //     ds_read_b64_tr_b16: in a block of 16 lanes, lane s addresses 4 consecutive 16-bit values and
@@ -1252,6 +1270,18 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
 //     eight keys of a fragment.
 // Rows that do not exist (tail of the context or of the column list) re-load an existing row; their
 // keys are masked, so only finiteness of the staged values matters.
+//
+// Two ways through the tiles.  What bounds the kernel is instruction issue, and the card's power: of the cycles of a SIMD the products
+// take half, and the clock falls as they take more.
+//   Queues (long runs): half a tile, 32 keys, from barrier to barrier, and nothing of a half overlaps in its own wave: that takes 166 registers and
+//   37 KB of LDS, so that three workgroups share a CU (four at d = 64) and one wave's softmax runs beside another's products.
+//   Pieces (short runs): a whole tile from barrier to barrier, by halves, the softmax of one beside the products of the other: two workgroups
+//   a CU (three at d = 64), but a wave that has the SIMD to itself, as where a workgroup has a handful of tiles, is faster: 61 rows of 12347
+//   30.5 us a call against 32.0 by halves, d = 64, 1777 of 5003 rows, carried lines, 83.6 against 87.2.
+// A tile of the 32768 keys' turn, three quarters diagonals, took a SIMD 2060 cycles with two halves and their transfers in one burst, 1830 with the
+// transfers in between the products and fewer scalar instructions, 1600 by halves.  The whole call, us (as it was / tiles / halves): 10923 of 32768 rows 1700 / 1615 /
+// 1580, all heads dense 4840 / 4750 / 4240, diagonals only 2055 / 1890 / 1850; 16384 of 131072 14670 / 13660 / 13600, B 4, 64 heads, 5462 of 16384 4120 / 3900 / 3660;
+// 8192 rows, all new (pieces) 275 / 266.  (What the clock gives back: 2.24 GHz as it was, 2.0 by halves.)
 // ---------------------------------------------------------------------------------------------
 template <int D>
 struct DirectCfg {
@@ -1259,44 +1289,52 @@ struct DirectCfg {
     static constexpr int RB = D * 2;                      // bytes per row
     static constexpr int DS = RB / 16;                    // 16-byte slots per row
     static constexpr int RPI = 64 / DS;                   // rows per transfer instruction
-    static constexpr int NI = BN / RPI;                   // transfer instructions per operand tile
+    static constexpr int HB = BN / 2;                     // keys of a half, which is what a buffer holds
+    static constexpr int NI = HB / RPI;                   // transfer instructions per operand and half
     static constexpr int IPW = NI / 4;                    // ... per wave
     static constexpr int K_ISTR = D == 128 ? 1088 : 1024; // LDS bytes from one K transfer to the next
     static constexpr int V_ISTR = 1024;
-    static constexpr int K_BYTES = NI * K_ISTR, V_BYTES = NI * V_ISTR, TILE_BYTES = K_BYTES + V_BYTES;
-    static constexpr int K_LAG = K_ISTR - RPI * RB;       // bytes by which the K rows in LDS move ahead of those in memory, per transfer
+    static constexpr int K_BYTES = NI * K_ISTR, V_BYTES = NI * V_ISTR, HALF_BYTES = K_BYTES + V_BYTES;
+    static constexpr int FRONT = (128 + 512) * 4;         // LDS ahead of the buffers
+    static constexpr int OUT_ROW = RB + 16;               // results on their way out: LDS bytes from row to row
+    static constexpr int lds(bool queues) {
+        const int halves = (queues ? 2 : 4) * HALF_BYTES;
+        return FRONT + (halves > BM * OUT_ROW ? halves : BM * OUT_ROW);
+    }
     static constexpr int KSTEPS = D / 16, DBLK = D / 32;
     static constexpr int KA = D == 128 ? 2 : 4;           // K fragment address registers
-    // slot swizzles (XOR on the 16-byte slot index inside a row); both are unchanged by adding a
-    // multiple of 16 (d = 128) or 32 (d = 64) to the row
+    // slot swizzles (XOR on the 16-byte slot index inside a row)
     __device__ static constexpr int kswz(int row) { return D == 128 ? (row & 3) : (((row >> 1) & 3) | (((row >> 3) & 1) << 2)); }
     __device__ static constexpr int vswz(int row) { return D == 128 ? ((row & 3) << 2) : (((row >> 1) & 1) << 2); }
 };
 
 template <int D, bool QUEUES>
-__global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf16_kernel(PrefillArgs a) {
+__global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2) + (QUEUES ? 1 : 0)) void prefill_bf16_kernel(PrefillArgs a) {
     using C = DirectCfg<D>;
     using T = bf16_t;
+    using std::integral_constant;
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char* tiles = smem;                                         // [2][TILE_BYTES]
-    int32_t* colring = reinterpret_cast<int32_t*>(smem + 2 * C::TILE_BYTES);   // [4][64] column ids of packed tiles
-    uint32_t* colbits = reinterpret_cast<uint32_t*>(colring + 256);      // [4 waves][2][64] bitmap words for the masks of a packed tile
-    uint16_t* kbl = reinterpret_cast<uint16_t*>(colbits + 512);          // [tab_len] active key blocks
+    int32_t* colring = reinterpret_cast<int32_t*>(smem);                 // [2][64] column ids of packed tiles
+    uint32_t* colbits = reinterpret_cast<uint32_t*>(colring + 128);      // [4 waves][2][64] bitmap words for the masks of a packed tile
+    unsigned char* tiles = smem + C::FRONT;                              // [2 halves, or two tiles of 2][HALF_BYTES]: K rows, V rows
     const uint32_t tiles_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)tiles;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t colring_lds = tiles_lds + 2u * C::TILE_BYTES, colbits_lds = colring_lds + 1024u + (uint32_t)wv * 512u;
+    const uint32_t colring_lds = tiles_lds - (uint32_t)C::FRONT, colbits_lds = colring_lds + 512u + (uint32_t)wv * 512u;
     const int r32 = lane & 31, g = lane >> 5;
+    auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    // a value made anew: addresses and masks computed from it are needed now and then, and would otherwise be kept in registers (20 of them)
+    auto again = [](int x) { asm volatile("" : "+v"(x)); return x; };
+    auto apart = [](int x) { asm volatile("" : "+v"(x)); return __builtin_amdgcn_readfirstlane(x); };      // a condition that is not joined with others
 
-    // ---- per-lane constants of the transfers: this lane fills slot sl of row rowlane (+ RPI per further instruction of
-    // the wave) and fetches the chunk the swizzle assigns to that slot
-    const int rowlane = 16 * wv + lane / C::DS;
+    // ---- per-lane constants of the transfers: this lane fills slot sl of row rowlane (+ RPI for the wave's second instruction)
+    // of a half and fetches the chunk the swizzle assigns to that slot
+    const int rowlane = C::IPW * C::RPI * wv + lane / C::DS;
     const int sl = lane % C::DS;
-    const uint32_t kcpart0 = 16u * (uint32_t)(sl ^ C::kswz(rowlane)), vcpart = 16u * (uint32_t)(sl ^ C::vswz(rowlane));
-    // (of the wave's instruction i: the swizzle of d = 64 has a bit of the row's multiple of eight)
-    auto kcpart = [&](int i) -> uint32_t { return D == 128 ? kcpart0 : kcpart0 ^ (uint32_t)(64 * (i & 1)); };
-    // ---- K fragment reads: row r32 (+32), chunk 2c+g sits in slot (2c+g) ^ kswz
+    const uint32_t kcpart = 16u * (uint32_t)(sl ^ C::kswz(rowlane)), vcpart = 16u * (uint32_t)(sl ^ C::vswz(rowlane));
+    static_assert(C::IPW == 1 || (C::kswz(C::RPI) == 0 && C::vswz(C::RPI) == 0), "a wave's instructions share their swizzles");
+    // ---- K fragment reads: row r32, chunk 2c+g sits in slot (2c+g) ^ kswz
     int kaddr[C::KA];
     {
         const int x = C::kswz(r32);
@@ -1318,11 +1356,11 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     entries.init(a, lane);
     Entry en;
     while (entries.next(a, lane, wv, en)) {
-    const int item = en.item, bh = item / a.nqb, qb = item % a.nqb;
+    const int item = uniform(en.item), bh = item / a.nqb, qb = item % a.nqb;
     const int n1 = en.blocks, nv = en.cols;                // key blocks phase 1 visits, columns phase 2 gathers (those up to the block's last row)
     const int bkv = bh / a.Hq * a.Hkv + bh % a.Hq / a.G;
     const int n2 = (nv + BN - 1) / BN;
-    const int tbeg = en.begin(n1 + n2), ntiles = en.end(n1 + n2);        // tiles tbeg .. ntiles - 1
+    const int tbeg = uniform(en.begin(n1 + n2)), ntiles = uniform(en.end(n1 + n2));      // tiles tbeg .. ntiles - 1
     const int64_t n = a.n, row0 = n - a.n_hat;
     const int64_t blockpos = a.pos0 + (int64_t)qb * BM;                  // multiple of 128
     const unsigned char* Kg = reinterpret_cast<const unsigned char*>(a.k) + (int64_t)bkv * n * C::RB;
@@ -1330,31 +1368,37 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     const T* Qg = reinterpret_cast<const T*>(a.q) + (int64_t)bh * a.n_hat * D;
 
     const uint32_t* obg = a.obits + (int64_t)bh * (OB_PAD + a.words);     // zero words + bitmap of this head
-    const int64_t pos = blockpos + 32 * wv + r32;
     const int posw = (int)blockpos + 32 * wv;              // the wave's first row
-    const bool row_ok = (pos >= row0) && (pos < n);        // a row that does not exist has zeros: finite results, not stored
     const bool rows_here = posw < n && posw + 31 >= row0;
-    // the first entries of the head's list are asked for ahead of the queries: the key blocks below wait for them only
+    // ---- key blocks of the contiguous tiles, ascending: a run of the head's list of active table entries, backwards; entry e is key block
+    // jb + 1 - e.  Lane l keeps that of tile tile0 + l.  The first are asked for ahead of the queries.
     const int jb = (int)(blockpos / BN);
-    const uint16_t* el = a.elist + (int64_t)bh * (a.tab_len + 1) + n1 - 1 - tbeg;         // of tile tbeg, the others below it
-    if (n - 1 < blockpos + BN && n1 > 0 && a.elist[(int64_t)bh * (a.tab_len + 1)] == 0) ++el;       // half a row block: entry 0 belongs to key blocks beyond it
-    const int blocks = (ntiles < n1 ? ntiles : n1) - tbeg;               // contiguous tiles of this part, none if not positive
-    int tl = tid;                                          // (made new here: addresses made of it would be kept, or spilled, from one entry to the next)
-    asm volatile("" : "+v"(tl));
-    const uint16_t el0 = tl < blocks ? el[-tl] : (uint16_t)0;
+    const uint16_t* el = a.elist + (int64_t)bh * (a.tab_len + 1) + n1 - 1;         // of tile 0, the others below it
+    if (n - 1 < blockpos + BN && n1 > 0 && uniform((int)a.elist[(int64_t)bh * (a.tab_len + 1)]) == 0) ++el;      // half a row block: entry 0 belongs to key blocks beyond it
+    const int blocks = ntiles < n1 ? ntiles : n1;                        // contiguous tiles of this part end here
+    int kbv = 0, tile0 = tbeg;
+    auto ask_blocks = [&]() { const int i = tile0 + lane < blocks ? tile0 + lane : blocks - 1; kbv = jb + 1 - (int)el[-i]; };
+    auto keep_blocks = [&](int t) {                        // tile t among them
+        if (t - tile0 < 64) return;
+        tile0 = t;
+        ask_blocks();
+        wait_transfers();
+    };
+    auto block_at = [&](int t) -> int { return __builtin_amdgcn_readlane(kbv, t - tile0); };
+    if (tbeg < blocks) ask_blocks();
     asm volatile("" ::: "memory");
     Frag<T> qf[C::KSTEPS];
-    if (row_ok) {
-        const T* qrow = Qg + (pos - row0) * D;
+    {
+        const int64_t pos = posw + again(r32);
+        if (pos >= row0 && pos < n) {                      // a row that does not exist has zeros: finite results, not stored
+            const T* qrow = Qg + (pos - row0) * D;
 #pragma unroll
-        for (int c = 0; c < C::KSTEPS; ++c) load_frag(qf[c], qrow + 16 * c + 8 * g);
-    } else {
+            for (int c = 0; c < C::KSTEPS; ++c) load_frag(qf[c], qrow + 16 * c + 8 * g);
+        } else {
 #pragma unroll
-        for (int c = 0; c < C::KSTEPS; ++c) zero_frag(qf[c]);
+            for (int c = 0; c < C::KSTEPS; ++c) zero_frag(qf[c]);
+        }
     }
-
-    // ---- key blocks of the contiguous tiles, ascending: the table entry of block kb is jb - kb + 1
-    for (int i = tl; i < blocks; i += PREFILL_THREADS) kbl[i] = (uint16_t)(jb + 1 - (int)(i == tl ? el0 : el[-i]));
     const int32_t* vi = a.v_idx + (int64_t)bh * a.cap_v;
 
     f32x16 oacc[C::DBLK];
@@ -1366,74 +1410,46 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     // might exceed the limit, so that most tiles need no rescaling of the accumulators.
     const float sc2 = a.scale_log2e;
     float mneg = INFINITY, l_run = 0.f, limit = SOFT_FIRST;
-    int often = 0;                                         // how often halves exceed the limit (uniform)
+    int often = 0, doubled = -1;                           // how often halves exceed the limit; the tile for which the limit was doubled last (uniform)
 
-    // ---- staging.  Wave wv fetches rows 16 wv .. 16 wv + 15 of each operand, IPW instructions of RPI rows, which share one M0:
-    // an instruction's offset moves its source and its target alike, and where the target moves further (K_LAG) the
-    // per-lane offsets take that back.  A row beyond the context re-loads the last row, a missing
-    // column re-loads row 0: every slot is always written with finite data and needs no exec masking.
+    // ---- staging.  Of a half's K and V wave wv fetches rows 8 wv .. 8 wv + 7, IPW instructions of RPI rows each.  A row beyond the context
+    // re-loads the last row, a missing column the last column: every slot is always written with finite data and needs no exec masking.
     const uint32_t kdst0 = tiles_lds + (uint32_t)(wv * C::IPW * C::K_ISTR), vdst0 = tiles_lds + (uint32_t)(C::K_BYTES + wv * C::IPW * C::V_ISTR);
-    auto issue_k = [&](int kb, int t) {                    // K of key block kb -> LDS buffer t & 1
-        const uint32_t dst = kdst0 + (uint32_t)((t & 1) * C::TILE_BYTES);
-        const int64_t key0 = (int64_t)kb * BN;
-        const unsigned char* kb_ = Kg + key0 * C::RB;
-        if (key0 + BN <= n) {
-            uint32_t off[C::IPW];
+    auto buffer = [](int s) -> uint32_t { return (uint32_t)(s & (QUEUES ? 1 : 3)) * (uint32_t)C::HALF_BYTES; };       // of half s, counted through the tiles
+    auto issue_half = [&](int kh, int s) {                 // keys 32 kh ..
+        const int64_t left = n - (int64_t)kh * C::HB;      // none left: the last key throughout
+        const int64_t key0 = left > 0 ? (int64_t)kh * C::HB : n - 1;
+        const int last = left > C::HB ? C::HB - 1 : left > 0 ? (int)left - 1 : 0, r0 = again(rowlane);
 #pragma unroll
-            for (int i = 0; i < C::IPW; ++i) off[i] = (uint32_t)rowlane * C::RB + kcpart(i) + (uint32_t)((C::IPW - 1 - i) * C::K_LAG);
-            dma16_rows<C::IPW, C::K_ISTR>(kb_ - (C::IPW - 1) * C::K_LAG, off, dst);
-        }
-        else {                                             // last key block of the context: clamp the rows
-            const int last = (int)(n - 1 - key0);
-#pragma unroll
-            for (int i = 0; i < C::IPW; ++i) {
-                const int row = rowlane + C::RPI * i;
-                dma16(kb_, (uint32_t)(row <= last ? row : last) * C::RB + kcpart(i), dst + (uint32_t)(i * C::K_ISTR));
-            }
+        for (int i = 0; i < C::IPW; ++i) {
+            const int row = r0 + C::RPI * i;
+            const uint32_t at = (uint32_t)(row <= last ? row : last) * C::RB;
+            dma16(Kg + key0 * C::RB, at + kcpart, kdst0 + buffer(s) + (uint32_t)(i * C::K_ISTR));
+            dma16(Vg + key0 * C::RB, at + vcpart, vdst0 + buffer(s) + (uint32_t)(i * C::V_ISTR));
         }
     };
-    auto issue_v = [&](int kb, int t) {
-        const uint32_t dst = vdst0 + (uint32_t)((t & 1) * C::TILE_BYTES);
-        const int64_t key0 = (int64_t)kb * BN;
-        const unsigned char* vb_ = Vg + key0 * C::RB;
-        if (key0 + BN <= n) {
-            uint32_t off[C::IPW];
+    auto issue_cols = [&](int s) {                         // the columns of half s & 1 of packed tile s / 2
+        const int32_t* cols = colring + (s >> 1 & 1) * BN + (s & 1) * C::HB + again(rowlane);
 #pragma unroll
-            for (int i = 0; i < C::IPW; ++i) off[i] = (uint32_t)rowlane * C::RB + vcpart;
-            dma16_rows<C::IPW, C::V_ISTR>(vb_, off, dst);
-        } else {
-            const int last = (int)(n - 1 - key0);
-#pragma unroll
-            for (int i = 0; i < C::IPW; ++i) {
-                const int row = rowlane + C::RPI * i;
-                dma16(vb_, (uint32_t)(row <= last ? row : last) * C::RB + vcpart, dst + (uint32_t)(i * C::V_ISTR));
-            }
+        for (int i = 0; i < C::IPW; ++i) {
+            const uint32_t at = (uint32_t)cols[C::RPI * i] * C::RB;
+            dma16(Kg, at + kcpart, kdst0 + buffer(s) + (uint32_t)(i * C::K_ISTR));
+            dma16(Vg, at + vcpart, vdst0 + buffer(s) + (uint32_t)(i * C::V_ISTR));
         }
-    };
-    auto issue_cols = [&](int t) {                         // the columns of packed tile t -> LDS buffer t & 1
-        const uint32_t bo = (uint32_t)((t & 1) * C::TILE_BYTES);
-        const int32_t* cols = colring + (t & 3) * BN;
-        uint32_t ro[C::IPW];
-#pragma unroll
-        for (int i = 0; i < C::IPW; ++i) ro[i] = (uint32_t)cols[rowlane + C::RPI * i] * C::RB;
-#pragma unroll
-        for (int i = 0; i < C::IPW; ++i) dma16(Kg, ro[i] + kcpart(i), kdst0 + bo + (uint32_t)(i * C::K_ISTR));
-#pragma unroll
-        for (int i = 0; i < C::IPW; ++i) dma16(Vg, ro[i] + vcpart, vdst0 + bo + (uint32_t)(i * C::V_ISTR));
     };
 
-    // ---- masks.  halves: of the tile at hand, 1, 2 = the half has an allowed cell (for this wave), 4, 8 = all of it is allowed.
-    // The bitmap words of contiguous tiles come out of a register: lane l keeps word wq - l, good for some 30 neighbouring
-    // tiles, and a tile's three words are three lane reads.  (Scalar loads ahead of the tile's transfers, waited for
-    // there, were 200 cycles a tile.)
-    const int rows_mask = rows_here ? 15 : 0;
+    // ---- masks.  halves: of the tile at hand, 1, 2 = the half has an allowed cell (for this wave), 4, 8 = all of it is allowed; am: which.
+    // (Queues, contiguous tiles: of the half at hand, in the first place.)
+    // The bitmap words of contiguous tiles come out of a register: lane l keeps word wq - l, good for some 60 neighbouring
+    // halves, and a half's words are lane reads.  (Scalar loads ahead of the tile's transfers, waited for there, were 200 cycles a tile.)
+    const int rows_mask = rows_here ? 15 : 0, pw = posw / 32;
     uint32_t am[2] = {0u, 0u};
-    int halves = 0, kb_next = 0;                           // kb_next: key block of the tile after the one at hand (phase 1)
+    int halves = 0, kh_next = 0;                           // kh_next: the keys (in 32s) of the half (pieces: the tile) after the one at hand (phase 1)
     uint32_t wc = 0u;
     int wq = -1000000;
-    auto keep_words = [&](int kb) {                        // with no transfer of this wave under way
-        const int q = (posw - kb * BN) >> 5;               // >= -2
-        if ((uint32_t)(wq - q) > 61u) {
+    auto keep_words = [&](int kh) {
+        const int q = pw - kh;                             // >= -3
+        if ((uint32_t)(wq - q) > (QUEUES ? 62u : 61u)) {
             const int at = q - lane + OB_PAD;              // (below the bitmap: zero words)
             wc = obg[at < 0 ? 0 : at];
             wq = q;
@@ -1441,163 +1457,192 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
         }
     };
     uint32_t x0 = 0u, x1 = 0u, x2 = 0u;
-    auto mask_step = [&](int k) {                          // masks of contiguous tile kb_next, in four steps
+    auto mask_step = [&](int k) {                          // masks of the contiguous half or tile kh_next, in four steps
         if (k == 0) {
-            const int l = wq - ((posw - kb_next * BN) >> 5);
+            const int l = wq - pw + kh_next;
             x2 = (uint32_t)__builtin_amdgcn_readlane((int)wc, l);
             x1 = (uint32_t)__builtin_amdgcn_readlane((int)wc, l + 1);
-            x0 = (uint32_t)__builtin_amdgcn_readlane((int)wc, l + 2);
+            if (!QUEUES) x0 = (uint32_t)__builtin_amdgcn_readlane((int)wc, l + 2);
         } else if (k == 1) am[0] = diag_cells(x2, x1, r32, g);
-        else if (k == 2) am[1] = diag_cells(x1, x0, r32, g);
-        else halves = (diag_half(x2, x1) | diag_half(x1, x0) << 1) & rows_mask;
+        else if (k == 2) { if (!QUEUES) am[1] = diag_cells(x1, x0, r32, g); }
+        else halves = (diag_half(x2, x1) | (QUEUES ? 0 : diag_half(x1, x0) << 1)) & rows_mask;
     };
-    // One tile: S^T = K Q^T, softmax, O^T += V^T P^T, by halves of 32 keys; halves without an allowed cell are passed by.  With
-    // two halves the vector work of one runs beside the products of the other: S(1) beside the softmax of 0, P V of 0 beside
-    // the softmax of 1.  Order is pinned (a scheduling barrier after each product), the LDS fragment reads run a fixed number
-    // of products ahead, and a product is followed by its share of the other half's 16 registers (a product takes its wave 33
-    // cycles, a masked register 27, an unmasked one 18).
+
+    // ---- products and softmax.  Order is pinned (a scheduling barrier after each product), the LDS fragment reads run a fixed number
+    // of products ahead.
     // No maximum is looked for on the way: the exponentials are taken with the reference as it stands, and where a lane's
     // sum says that one of them may exceed the limit (or is no number, as with the first cells of a row: -mneg = -inf), the half is
     // done again with a new reference.  s keeps the logits for that.
-    // Cycles of a workgroup over the 32768-key turn 3.52 -> 3.34 million; the clock falls with the better use of the matrix pipeline
-    // (2.29 -> 2.23 GHz, dense heads 2.05 -> 1.98: the card's power is what bounds them), so that 1723 us became 1665.  Going on to
-    // overlap P V, the products of the next tile and a softmax between them all had 1780: it works on halves that nobody sees.
-    constexpr int SUB = (32 / C::RPI) * C::K_ISTR;         // LDS bytes from key r to key r + 32
     constexpr int NS = C::KSTEPS, NV = 2 * C::DBLK;        // products of a half
-    constexpr int ES = 16 / NS, EV = 16 / NV;              // registers of the other half's softmax per product
-    constexpr int RS = LS_RING_S < NS ? LS_RING_S : NS, RV = LS_RING_P < NV ? LS_RING_P : NV;
+    constexpr int RS = LS_RING_S, RV = QUEUES ? LS_RING_PH : LS_RING_P;
+    static_assert(RS <= NS && RV <= NV, "fragments in flight");
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    auto apart = [](int x) { asm volatile("" : "+v"(x)); return __builtin_amdgcn_readfirstlane(x); };      // a condition that is not joined with others
     struct Soft { uint32_t p[8]; float sum[2]; };          // packed probabilities and their sums
-    auto process = [&](int t) {
+    auto kload = [&](Frag<T>& f, const unsigned char* base, int c) { load_frag(f, base + kaddr[c & (C::KA - 1)] + 32 * (c & ~(C::KA - 1))); };
+    auto vload = [&](Frag<T>& f, const unsigned char* base, int k) {         // keys 16 (k / DBLK).., output block k % DBLK
+        const unsigned char* va = base + vaddr[k % C::DBLK] + 16 * (k / C::DBLK) * C::RB;
+        load_frag_tr(f, va, va + 8 * C::RB);
+    };
+    auto pack2 = [&](float lo, float hi) {
+        typedef __attribute__((ext_vector_type(2))) float f32x2;
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+        uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));   // v_cvt_pk_bf16_f32, round to nearest even
+        asm volatile("" : "+v"(u));                        // here, and not where it is used
+        return u;
+    };
+    auto pfrag = [&](const Soft& o, int h) {
+        struct U { uint32_t w[4]; } u = {o.p[4 * h], o.p[4 * h + 1], o.p[4 * h + 2], o.p[4 * h + 3]};
+        Frag<T> f;
+        f.v = __builtin_bit_cast(bf16x8, u);
+        return f;
+    };
+    // registers r .. r + E - 1 of a half, in step k of 16 / E; x: their exponents, one step ahead
+    auto exponents = [&](auto MASKED, auto EC, float (&x)[4], f32x16& s, uint32_t cells, int k) {
+        constexpr int E = decltype(EC)::value;
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int r = E * k + e;
+            if constexpr (decltype(MASKED)::value) s[r] = masked(s[r], cells, r);
+            x[e] = __builtin_fmaf(s[r], sc2, mneg);
+        }
+    };
+    auto soft_step = [&](auto MASKED, auto EC, float (&x)[4], f32x16& s, uint32_t cells, Soft& o, int k) {
+        constexpr int E = decltype(EC)::value;
+        float p[E];
+#pragma unroll
+        for (int e = 0; e < E; ++e) p[e] = fast_exp2(x[e]);
+        if (k + 1 < 16 / E) exponents(MASKED, EC, x, s, cells, k + 1);
+#pragma unroll
+        for (int e = 0; e < E; ++e) { if (E * k + e < 2) o.sum[e] = p[e]; else o.sum[e & 1] += p[e]; }
+#pragma unroll
+        for (int e = 0; e < E; e += 2) o.p[(E * k + e) / 2] = pack2(p[e], p[e + 1]);
+    };
+    auto soft_alone = [&](auto MASKED, auto EC, f32x16& s, uint32_t cells, Soft& o) {
+        float x[4];
+        exponents(MASKED, EC, x, s, cells, 0);
+#pragma unroll
+        for (int k = 0; k < 16 / decltype(EC)::value; ++k) soft_step(MASKED, EC, x, s, cells, o, k);
+    };
+    auto settle = [&](int t, f32x16& s, Soft& o) {         // the sums in, or the half once more with a new reference
+        float sum = o.sum[0] + o.sum[1];
+        if (__ballot(!(sum <= limit)) != 0ull) {
+            float mx = -INFINITY;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
+            mx = max32(mx) * sc2;
+            float m_new = fmaxf(mx, -mneg);                // in base 2
+            often = (often > t ? often : t) + 4;
+            if (often - t > SOFT_OFTEN) {
+                asm volatile("");                          // (rare: a branch, no selects)
+                often = SOFT_RISING;
+                if (limit < 0.f) {                         // back to the maxima, once
+                    if (limit == -2.f) m_new = fmaxf(mx, -mneg - SOFT_AHEAD);
+                    limit = t < n1 ? -4.f : SOFT_LIMIT;
+                } else if (t + 2 < n1) {
+                    m_new = mx > -mneg ? mx + SOFT_AHEAD : -mneg;
+                }
+            }
+            const float corr = m_new > -INFINITY ? fast_exp2(-mneg - m_new) : 1.f;
+            mneg = -m_new;
+            const float safe = m_new > -INFINITY ? mneg : 0.f;
+            l_run *= corr;
+#pragma unroll
+            for (int i = 0; i < C::DBLK; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) oacc[i][r] *= corr;
+            sum = 0.f;
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int r = 0; r < 16; r += 4) {
+                float p[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { p[e] = fast_exp2(__builtin_fmaf(s[r + e], sc2, safe)); sum += p[e]; }
+                o.p[r / 2] = pack2(p[0], p[1]);
+                o.p[r / 2 + 1] = pack2(p[2], p[3]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        l_run += sum;
+    };
+    // S of a half, beside it PER-th of SN transfers (none: 0)
+    auto scores = [&](auto SENDS, f32x16& x, const unsigned char* base, auto send) {
+        constexpr int SN = decltype(SENDS)::value;
+        static_assert(SN <= NS, "at most a transfer beside a product");
+        Frag<T> kf[NS];
+#pragma unroll
+        for (int c = 0; c < RS; ++c) kload(kf[c], base, c);
+        __builtin_amdgcn_sched_barrier(0);
+        x = zero16;
+#pragma unroll
+        for (int c = 0; c < NS; ++c) {
+            mma(x, kf[c], qf[c]);                          // x[r] = <k_{8(r/4)+4g+r%4}, q_row>
+            if (c + RS < NS) kload(kf[c + RS], base, c + RS);
+            if constexpr (SN > 0) if (c % (NS / SN) == NS / SN / 2) send(c / (NS / SN));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // O += P V of a half, beside it the masks of what comes next
+    auto values = [&](Frag<T> (&vf)[NV], const Soft& p, const unsigned char* base) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            mma(oacc[k % C::DBLK], vf[k], pfrag(p, k / C::DBLK));
+            if (k + RV < NV) vload(vf[k + RV], base, k + RV);
+            if (k < 4) mask_step(k);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // Queues: one half after the other; the other waves of the SIMD (three, four at d = 64) keep the matrix pipe busy beside a wave's softmax.
+    auto process_half = [&](auto SENDS, int t, const unsigned char* base, auto send) {
+        f32x16 x;
+        Soft o;
+        if (t != doubled) { doubled = t; limit = fminf(limit * 2.f, SOFT_LIMIT); }
+        scores(SENDS, x, base, send);
+        Frag<T> vf[NV];
+#pragma unroll
+        for (int k = 0; k < RV; ++k) vload(vf[k], base, k);                  // ahead of the softmax
+        auto soft = [&](auto MASKED) {
+#pragma unroll
+            for (int r = 0; r < 16; r += 2) {
+                if constexpr (decltype(MASKED)::value) { x[r] = masked(x[r], am[0], r); x[r + 1] = masked(x[r + 1], am[0], r + 1); }
+                const float e0 = fast_exp2(__builtin_fmaf(x[r], sc2, mneg)), e1 = fast_exp2(__builtin_fmaf(x[r + 1], sc2, mneg));
+                o.sum[0] = r ? o.sum[0] + e0 : e0;
+                o.sum[1] = r ? o.sum[1] + e1 : e1;
+                o.p[r / 2] = pack2(e0, e1);
+            }
+        };
+        if (halves & 4) soft(std::false_type{}); else soft(std::true_type{});
+        settle(t, x, o);
+        __builtin_amdgcn_sched_barrier(0);
+        values(vf, o, base);
+    };
+    // Pieces: a tile by halves; halves without an allowed cell are passed by.  With two halves the vector work of one runs beside the
+    // products of the other: S(1) beside the softmax of 0, P V of 0 beside the softmax of 1.  A product is followed by its share of the
+    // other half's 16 registers (a product takes its wave 33 cycles, a masked register 27, an unmasked one 18).
+    auto process_tile = [&](auto SENDS, int t, auto send) {
+        constexpr int ES = 16 / NS, EV = 16 / NV;          // registers of the other half's softmax per product
+        constexpr int SN = decltype(SENDS)::value / 2;     // transfers beside the products of a half's S
         f32x16 sa, sb;
         Soft pa, pb;
         limit = fminf(limit * 2.f, SOFT_LIMIT);
-        auto kload = [&](Frag<T>& f, const unsigned char* base, int c) { load_frag(f, base + kaddr[c & (C::KA - 1)] + 32 * (c & ~(C::KA - 1))); };
-        auto vload = [&](Frag<T>& f, const unsigned char* base, int k) {     // keys 16 (k / DBLK).., output block k % DBLK
-            const unsigned char* va = base + vaddr[k % C::DBLK] + 16 * (k / C::DBLK) * C::RB;
-            load_frag_tr(f, va, va + 8 * C::RB);
-        };
-        auto pack2 = [&](float lo, float hi) {
-            typedef __attribute__((ext_vector_type(2))) float f32x2;
-            typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-            uint32_t u = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));   // v_cvt_pk_bf16_f32, round to nearest even
-            asm volatile("" : "+v"(u));                    // here, and not where it is used
-            return u;
-        };
-        // registers r .. r + E - 1 of a half, in step k of 16 / E; x: their exponents, one step ahead
-        auto exponents = [&](auto MASKED, auto EC, float (&x)[4], f32x16& s, uint32_t am, int k) {
-            constexpr int E = decltype(EC)::value;
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-                const int r = E * k + e;
-                if constexpr (decltype(MASKED)::value) s[r] = masked(s[r], am, r);
-                x[e] = __builtin_fmaf(s[r], sc2, mneg);
-            }
-        };
-        auto soft_step = [&](auto MASKED, auto EC, float (&x)[4], f32x16& s, uint32_t am, Soft& o, int k) {
-            constexpr int E = decltype(EC)::value;
-            float p[E];
-#pragma unroll
-            for (int e = 0; e < E; ++e) p[e] = fast_exp2(x[e]);
-            if (k + 1 < 16 / E) exponents(MASKED, EC, x, s, am, k + 1);
-#pragma unroll
-            for (int e = 0; e < E; ++e) { if (E * k + e < 2) o.sum[e] = p[e]; else o.sum[e & 1] += p[e]; }
-#pragma unroll
-            for (int e = 0; e < E; e += 2) o.p[(E * k + e) / 2] = pack2(p[e], p[e + 1]);
-        };
-        auto settle = [&](f32x16& s, Soft& o) {            // the sums in, or the half once more with a new reference
-            float sum = o.sum[0] + o.sum[1];
-            if (__ballot(!(sum <= limit)) != 0ull) {
-                float mx = -INFINITY;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[r]);
-                mx = max32(mx) * sc2;
-                float m_new = fmaxf(mx, -mneg);            // in base 2
-                often = (often > t ? often : t) + 4;
-                if (often - t > SOFT_OFTEN) {
-                    asm volatile("");                      // (rare: a branch, no selects)
-                    often = SOFT_RISING;
-                    if (limit < 0.f) {                     // back to the maxima, once
-                        if (limit == -2.f) m_new = fmaxf(mx, -mneg - SOFT_AHEAD);
-                        limit = t < n1 ? -4.f : SOFT_LIMIT;
-                    } else if (t + 2 < n1) {
-                        m_new = mx > -mneg ? mx + SOFT_AHEAD : -mneg;
-                    }
-                }
-                const float corr = m_new > -INFINITY ? fast_exp2(-mneg - m_new) : 1.f;
-                mneg = -m_new;
-                const float safe = m_new > -INFINITY ? mneg : 0.f;
-                l_run *= corr;
-#pragma unroll
-                for (int i = 0; i < C::DBLK; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) oacc[i][r] *= corr;
-                sum = 0.f;
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int r = 0; r < 16; r += 4) {
-                    float p[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) { p[e] = fast_exp2(__builtin_fmaf(s[r + e], sc2, safe)); sum += p[e]; }
-                    o.p[r / 2] = pack2(p[0], p[1]);
-                    o.p[r / 2 + 1] = pack2(p[2], p[3]);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            l_run += sum;
-        };
-        auto pfrag = [&](const Soft& o, int h) {
-            struct U { uint32_t w[4]; } u = {o.p[4 * h], o.p[4 * h + 1], o.p[4 * h + 2], o.p[4 * h + 3]};
-            Frag<T> f;
-            f.v = __builtin_bit_cast(bf16x8, u);
-            return f;
-        };
-        using std::integral_constant;
-        auto scores = [&](f32x16& x, const unsigned char* base) {              // S of a half
-            Frag<T> kf[NS];
-#pragma unroll
-            for (int c = 0; c < RS; ++c) kload(kf[c], base, c);
-            __builtin_amdgcn_sched_barrier(0);
-            x = zero16;
-#pragma unroll
-            for (int c = 0; c < NS; ++c) {
-                mma(x, kf[c], qf[c]);                      // x[r] = <k_{8(r/4)+4g+r%4}, q_row>
-                if (c + RS < NS) kload(kf[c + RS], base, c + RS);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
-        auto values = [&](const Soft& p, const unsigned char* base) {          // P V of a half, beside it the masks of the next tile
-            Frag<T> vf[NV];
-#pragma unroll
-            for (int k = 0; k < RV; ++k) vload(vf[k], base, k);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int k = 0; k < NV; ++k) {
-                mma(oacc[k % C::DBLK], vf[k], pfrag(p, k / C::DBLK));
-                if (k + RV < NV) vload(vf[k + RV], base, k + RV);
-                if (k < 4) mask_step(k);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        };
         // (The accumulators change in straight code and under conditions without an else only: where both sides of a choice
         // changed them, the compiler, which gives every choice the form of two guarded parts, kept them twice and moved them.)
-        const unsigned char* t0 = tiles + (t & 1) * C::TILE_BYTES;
+        const unsigned char *t0 = tiles + buffer(2 * t), *t1 = t0 + C::HALF_BYTES;
         const int two = (halves & 3) == 3, h0 = (halves & 3) == 2;
         const uint32_t am0 = h0 ? am[1] : am[0];
-        scores(sa, t0 + h0 * SUB);
+        scores(integral_constant<int, SN>{}, sa, h0 ? t1 : t0, send);
         if (two) {
             auto first = [&](auto MASKED) {                // S of the second half beside the softmax of the first
                 Frag<T> kf[NS];
                 float x[4];
 #pragma unroll
-                for (int c = 0; c < RS; ++c) kload(kf[c], t0 + SUB, c);
+                for (int c = 0; c < RS; ++c) kload(kf[c], t1, c);
                 __builtin_amdgcn_sched_barrier(0);
                 sb = zero16;
 #pragma unroll
                 for (int c = 0; c < NS; ++c) {
                     mma(sb, kf[c], qf[c]);
-                    if (c + RS < NS) kload(kf[c + RS], t0 + SUB, c + RS);
+                    if (c + RS < NS) kload(kf[c + RS], t1, c + RS);
+                    if constexpr (SN > 0) if (c % (NS / SN) == NS / SN / 2) send(SN + c / (NS / SN));
                     if (c == 0) exponents(MASKED, integral_constant<int, ES>{}, x, sa, am0, 0);
                     else soft_step(MASKED, integral_constant<int, ES>{}, x, sa, am0, pa, c - 1);
                     __builtin_amdgcn_sched_barrier(0);
@@ -1606,52 +1651,53 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
             };
             if (halves & 4) first(std::false_type{}); else first(std::true_type{});
         } else {
-            float x[4];
-            exponents(std::true_type{}, integral_constant<int, 4>{}, x, sa, am0, 0);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) soft_step(std::true_type{}, integral_constant<int, 4>{}, x, sa, am0, pa, k);
+            for (int i = 0; i < SN; ++i) send(SN + i);
+            soft_alone(std::true_type{}, integral_constant<int, 4>{}, sa, am0, pa);
         }
-        settle(sa, pa);
+        settle(t, sa, pa);
         pb = pa;
         if (apart(two)) {
-            auto second = [&](auto MASKED) {               // P V of the first half beside the softmax of the second
-                Frag<T> vf[NV];
-                float x[4];
+            Frag<T> vf[NV];                                // P V of the first half beside the softmax of the second
+            float x[4];
 #pragma unroll
-                for (int k = 0; k < RV; ++k) vload(vf[k], t0, k);
+            for (int k = 0; k < RV; ++k) vload(vf[k], t0, k);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < NV; ++k) {
+                mma(oacc[k % C::DBLK], vf[k], pfrag(pa, k / C::DBLK));
+                if (k + RV < NV) vload(vf[k + RV], t0, k + RV);
+                if (k == 0) exponents(std::true_type{}, integral_constant<int, EV>{}, x, sb, am[1], 0);
+                else soft_step(std::true_type{}, integral_constant<int, EV>{}, x, sb, am[1], pb, k - 1);
                 __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int k = 0; k < NV; ++k) {
-                    mma(oacc[k % C::DBLK], vf[k], pfrag(pa, k / C::DBLK));
-                    if (k + RV < NV) vload(vf[k + RV], t0, k + RV);
-                    if (k == 0) exponents(MASKED, integral_constant<int, EV>{}, x, sb, am[1], 0);
-                    else soft_step(MASKED, integral_constant<int, EV>{}, x, sb, am[1], pb, k - 1);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                soft_step(MASKED, integral_constant<int, EV>{}, x, sb, am[1], pb, NV - 1);
-            };
-            second(std::true_type{});
-            settle(sb, pb);
+            }
+            soft_step(std::true_type{}, integral_constant<int, EV>{}, x, sb, am[1], pb, NV - 1);
+            settle(t, sb, pb);
         }
-        values(pb, t0 + ((halves & 2) ? 32 * C::RB : 0));
+        const unsigned char* tv = (halves & 2) ? t1 : t0;
+        Frag<T> vf[NV];
+#pragma unroll
+        for (int k = 0; k < RV; ++k) vload(vf[k], tv, k);
+        __builtin_amdgcn_sched_barrier(0);
+        values(vf, pb, tv);
     };
 
-    // What a packed tile needs besides its rows goes through LDS by transfers of its own: the ids of its columns two
-    // tiles ahead (slots past the end of the list repeat the last column), the bitmap words of its masks one tile ahead.
+    // What a packed tile needs besides its rows goes through LDS by transfers of its own: the ids of its columns ahead of them
+    // (slots past the end of the list repeat the last column), the bitmap words of its masks beside them.
     // (As loads into registers they made the compiler put waits for all outstanding memory operations, the transfers of
     // the next tile among them, into the tile loop.)
-    auto request_cols = [&](int t) {                       // column ids of packed tile t -> slot t & 3
+    auto request_cols = [&](int t) {                       // column ids of packed tile t -> slot t & 1
         if (wv == 0) {
             int i = (t - n1) * BN + lane;
             if (i > nv - 1) i = nv - 1;
-            dma4(vi, (uint32_t)i * 4u, colring_lds + (uint32_t)((t & 3) * BN * 4));
+            dma4(vi, (uint32_t)i * 4u, colring_lds + (uint32_t)((t & 1) * BN * 4));
         }
     };
-    auto block_at = [&](int t) -> int { return __builtin_amdgcn_readfirstlane((int)kbl[t - tbeg]); };
     int32_t mycol = -1;
     auto col_words_of = [&](int t) {                       // what the masks of packed tile t are made of, ahead of its transfers
-        const int32_t col = colring[(t & 3) * BN + lane];
-        mycol = (t - n1) * BN + lane < nv ? col : -1;
+        const int l = again(lane);
+        const int32_t col = colring[(t & 1) * BN + l];
+        mycol = (t - n1) * BN + l < nv ? col : -1;
         if (n1 > 0) {
             const uint32_t off = (uint32_t)((col_offset(posw, mycol < 0 ? 0 : mycol) >> 5) + OB_PAD) * 4u;
             dma4(obg, off, colbits_lds);
@@ -1660,66 +1706,157 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2)) void prefill_bf
     };
     auto masks_cols = [&]() {                              // once the transfers have landed
         ColWords cw = {0u, 0u};
-        if (n1 > 0) { cw.lo = colbits[wv * 128 + lane]; cw.hi = colbits[wv * 128 + 64 + lane]; }
-        const TileMask tm = col_mask(cw, posw, mycol, lane);
+        const int l = again(lane);
+        if (n1 > 0) { cw.lo = colbits[wv * 128 + l]; cw.hi = colbits[wv * 128 + 64 + l]; }
+        const TileMask tm = col_mask(cw, posw, mycol, l);
         am[0] = tm.am[0]; am[1] = tm.am[1];
-        halves = ((tm.act[0] ? 1 : 0) | (tm.act[1] ? 2 : 0)) & rows_mask;
+        halves = uniform(((tm.act[0] ? 1 : 0) | (tm.act[1] ? 2 : 0)) & rows_mask);
     };
 
-    if (ntiles > n1 && tbeg < ntiles && tbeg + 1 >= n1) {  // a packed tile among the first two
+    // transfers of two halves inside the context, one at a time
+    const unsigned char *ka = Kg, *va = Vg;
+    uint32_t to = 0u;                                      // K and V rows of up to two halves from ka, va on -> buffers from `to` on
+    auto send = [&](int i) {
+        const int h = i / (2 * C::IPW), j = i % (2 * C::IPW) / 2, rows = h * C::HB + j * C::RPI;
+        if (i & 1) dma16(va + rows * C::RB, (uint32_t)rowlane * C::RB + vcpart, vdst0 + to + (uint32_t)(h * C::HALF_BYTES + j * C::V_ISTR));
+        else dma16(ka + rows * C::RB, (uint32_t)rowlane * C::RB + kcpart, kdst0 + to + (uint32_t)(h * C::HALF_BYTES + j * C::K_ISTR));
+    };
+    auto aim = [&](int kh, uint32_t buf) {
+        const uint64_t at = (uint64_t)(uint32_t)kh * (uint32_t)(C::HB * C::RB);
+        ka = Kg + at; va = Vg + at; to = buf;
+    };
+    // The part's halves are 2 tbeg .. end - 1 (the second half of the last packed tile may have no columns).  Queues: the next half is
+    // fetched beside every half, the columns of a packed tile are requested a tile ahead; pieces: the next tile beside every tile, two ahead.
+    const int end = 2 * ntiles - (ntiles > n1 && (ntiles - n1) * BN - nv >= C::HB ? 1 : 0);
+    auto fetch = [&](int s) {                              // half s
+        if (s >= end) return;
+        if ((s >> 1) >= blocks) { issue_cols(s); return; }
+        const int kh = 2 * block_at(s >> 1) + (s & 1);
+        if ((int64_t)(kh + 1) * C::HB > n) { issue_half(kh, s); return; }
+        aim(kh, buffer(s));
+#pragma unroll
+        for (int i = 0; i < 2 * C::IPW; ++i) send(i);
+    };
+    if (tbeg < ntiles && tbeg + (QUEUES ? 0 : 1) >= n1) {  // a packed tile among the first ones
         if (tbeg >= n1) request_cols(tbeg);
-        if (tbeg + 1 < ntiles) request_cols(tbeg + 1);
+        if (!QUEUES && tbeg + 1 < ntiles) request_cols(tbeg + 1);
         wait_transfers();
     }
-    __syncthreads();                                       // kbl and the first column ids are visible
-    if (tbeg < n1) {
-        kb_next = block_at(tbeg);
-        keep_words(kb_next);
-        issue_k(kb_next, tbeg); issue_v(kb_next, tbeg);
-        for (int k = 0; k < 4; ++k) mask_step(k);
-        wait_transfers();
+    __syncthreads();                                       // the first column ids are visible, and the buffers are free
+    if (tbeg < blocks) {
+        kh_next = 2 * block_at(tbeg);
+        keep_words(kh_next);
     } else if (tbeg < ntiles) {
         col_words_of(tbeg);
-        issue_cols(tbeg);
-        wait_transfers();
-        masks_cols();
     }
-    kb_next = tbeg + 1 < n1 && tbeg + 1 < ntiles ? block_at(tbeg + 1) : 0;
+    fetch(2 * tbeg);
+    if (!QUEUES) fetch(2 * tbeg + 1);
+    if (tbeg < blocks) for (int k = 0; k < 4; ++k) mask_step(k);
+    wait_transfers();                                      // (on every path: the compiler has loads of its own under way)
+    if (tbeg >= blocks && tbeg < ntiles) masks_cols();
     __syncthreads();
 
-    for (int t = tbeg; t < ntiles; ++t) {
-        const bool next = t + 1 < ntiles;
-        if (next && t + 1 < n1) keep_words(kb_next);
-        if (t + 2 >= n1) {
-            if (t + 2 < ntiles) request_cols(t + 2);
-            if (t + 2 == n1 && often == SOFT_RISING) limit = -1.f;       // (no sum is less: every half from here on)
+    // As long as the next tile is a contiguous one ahead of the item's last, its halves lie inside the context, and there is little else to see to:
+    // 20 scalar instructions a tile instead of 90, its transfers in between the products of S (one after the other ahead of them they kept
+    // the wave for 600 of its 4000 cycles a tile).
+    const int plain = ntiles < n1 ? ntiles - 1 : n1 - 2;
+    int t = tbeg;
+    for (; t < plain; ++t) {
+        if constexpr (QUEUES) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (h == 0) ++kh_next;
+                else { keep_blocks(t + 1); kh_next = 2 * block_at(t + 1); }
+                keep_words(kh_next);
+                aim(kh_next, buffer(h + 1));
+                const int active = halves & 1;
+                if (active) process_half(integral_constant<int, 2 * C::IPW>{}, t, tiles + buffer(h), send);
+                if (apart(active) == 0) {
+#pragma unroll
+                    for (int i = 0; i < 2 * C::IPW; ++i) send(i);
+                    for (int k = 0; k < 4; ++k) mask_step(k);
+                }
+                wait_transfers();                          // this wave's transfers have landed
+                __syncthreads();
+            }
+        } else {
+            keep_blocks(t + 1);
+            kh_next = 2 * block_at(t + 1);
+            keep_words(kh_next);
+            aim(kh_next, buffer(2 * t + 2));
+            const int active = halves & 3;
+            if (active) process_tile(integral_constant<int, 4 * C::IPW>{}, t, send);
+            if (apart(active) == 0) {
+#pragma unroll
+                for (int i = 0; i < 4 * C::IPW; ++i) send(i);
+                for (int k = 0; k < 4; ++k) mask_step(k);
+            }
+            wait_transfers();
+            __syncthreads();
         }
-        if (next && t + 1 >= n1) { col_words_of(t + 1); issue_cols(t + 1); }
-        if (next && t + 1 < n1) { issue_k(kb_next, t + 1); issue_v(kb_next, t + 1); }
-        const int kb_after = t + 2 < n1 && t + 2 < ntiles ? (int)kbl[t + 2 - tbeg] : 0;
-        const int active = halves & 3;
-        if (active) process(t);                        // some of this wave's rows have an allowed cell here
-        if (apart(active) == 0) for (int k = 0; k < 4; ++k) mask_step(k);
-        kb_next = __builtin_amdgcn_readfirstlane(kb_after);
-        wait_transfers();                                  // this wave's transfers of tile t+1 have landed
-        if (next && t + 1 >= n1) masks_cols();
-        __syncthreads();
+    }
+    auto none = [](int) {};
+    if constexpr (QUEUES) {
+        for (int s = 2 * t; s < end; ++s) {
+            const int odd = s & 1;
+            t = s >> 1;
+            const bool next = s + 1 < end, packed = next && t + odd >= n1;         // of the next half
+            if (odd && t + 1 < blocks) keep_blocks(t + 1);
+            if (next && !packed) {
+                kh_next = odd ? 2 * block_at(t + 1) : kh_next + 1;
+                keep_words(kh_next);
+            }
+            if (!odd) {
+                if (t + 1 >= n1 && t + 1 < ntiles) request_cols(t + 1);
+                if (t + 2 == n1 && often == SOFT_RISING) limit = -1.f;       // (no sum is less: every half from here on)
+            } else if (packed) {
+                col_words_of(t + 1);
+            }
+            fetch(s + 1);
+            const int active = halves & 1, second = halves >> 1;
+            const uint32_t am1 = am[1];
+            if (active) process_half(integral_constant<int, 0>{}, t, tiles + buffer(s), none);
+            if (apart(active) == 0) for (int k = 0; k < 4; ++k) mask_step(k);
+            wait_transfers();
+            if (packed) {
+                if (odd) masks_cols();
+                else { am[0] = am1; halves = second; }
+            }
+            __syncthreads();
+        }
+    } else {
+        for (; t < ntiles; ++t) {
+            const bool next = t + 1 < ntiles, packed = next && t + 1 >= n1;        // of the next tile
+            if (next && !packed) {
+                keep_blocks(t + 1);
+                kh_next = 2 * block_at(t + 1);
+                keep_words(kh_next);
+            }
+            if (t + 2 >= n1 && t + 2 < ntiles) request_cols(t + 2);
+            if (t + 2 == n1 && often == SOFT_RISING) limit = -1.f;
+            if (packed) col_words_of(t + 1);
+            fetch(2 * t + 2);
+            fetch(2 * t + 3);
+            const int active = halves & 3;
+            if (active) process_tile(integral_constant<int, 0>{}, t, none);
+            if (apart(active) == 0) for (int k = 0; k < 4; ++k) mask_step(k);
+            wait_transfers();
+            if (packed) masks_cols();
+            __syncthreads();
+        }
     }
 
-    const float l_tot = l_run + xor32(l_run);
+    const float l_tot = sum32(l_run);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
     entries.ahead(a, lane, wv);                            // the next entry's place in the queue, under the stores below
-    // (the lane once more: addresses made of it are not to be kept in registers, or spilled, from one entry to the next)
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-    const int rl = ln & 31, gl = ln >> 5;
+    const int ln = again(lane), rl = ln & 31, gl = ln >> 5;
     if (en.in_parts(n1 + n2)) {
         store_part<C::DBLK>(a, en.slot(), wv, ln, oacc, -mneg, l_tot);
     } else if (rows_here) {
         // A lane holds four neighbouring values of its row at a time; through LDS (32 rows of this wave in the tile
         // buffers, which nobody reads any more) they become whole rows, 1 KB a store.  (Stored as they are, 8 bytes a
         // lane in 32 rows, they kept a wave for 4.5-7 thousand cycles an entry.)
-        constexpr int OS = C::RB + 16;                     // LDS bytes from row to row
+        constexpr int OS = C::OUT_ROW;
         unsigned char* ow = tiles + wv * (32 * OS);
 #pragma unroll
         for (int i = 0; i < C::DBLK; ++i)
@@ -1751,10 +1888,6 @@ static void launch_combine(const PrefillArgs& a, hipStream_t st, const hipEvent_
     else hipLaunchKernelGGL((combine_kernel<T, D, QUEUES>), grid, dim3(256), 0, st, a);
 }
 
-template <int D>
-static size_t prefill_bf16_smem(int tab_len) {
-    return 2 * (size_t)DirectCfg<D>::TILE_BYTES + 256 * 4 + 512 * 4 + (size_t)((tab_len + 7) & ~7) * 2 + 16;
-}
 template <typename T, int D>
 static size_t prefill_smem_t(int tab_len) {
     using C = TileCfg<T, D>;
@@ -1769,7 +1902,7 @@ static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t st, const h
         if (ev) hipExtLaunchKernelGGL((prefill_kernel<T, D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev[0], ev[1], 0, a);
         else hipLaunchKernelGGL((prefill_kernel<T, D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
     } else {
-        const size_t smem = prefill_bf16_smem<D>(a.tab_len);
+        const size_t smem = DirectCfg<D>::lds(QUEUES);
         if (ev) hipExtLaunchKernelGGL((prefill_bf16_kernel<D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev[0], ev[1], 0, a);
         else hipLaunchKernelGGL((prefill_bf16_kernel<D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
     }
@@ -1795,8 +1928,7 @@ hipError_t init_prefill_kernels() {
 }
 
 size_t prefill_smem_bytes(int dtype, int d, int tab_len) {
-    if (dtype == 0 && d == 128) return prefill_bf16_smem<128>(tab_len);
-    if (dtype == 0 && d == 64) return prefill_bf16_smem<64>(tab_len);
+    if (dtype == 0) return d == 128 ? DirectCfg<128>::lds(false) : DirectCfg<64>::lds(false);
     if (dtype == 1 && d == 128) return prefill_smem_t<float, 128>(tab_len);
     return prefill_smem_t<float, 64>(tab_len);
 }

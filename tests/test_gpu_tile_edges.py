@@ -1,0 +1,74 @@
+"""The tile loops of the bf16 attention at their edges, with the work in pieces and in queues: runs of contiguous tiles of every length up to a few
+and around 64 and 128 (a wave keeps 64 key blocks at a time), column lists that end at either half of a packed tile, contexts that end inside
+either half of a key block."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_13681_amd import binding, inputs
+from tests.gpu_util import Pipeline, dev_lists
+
+pytestmark = pytest.mark.gpu
+
+COLUMNS = [0, 1, 31, 32, 33, 64, 65, 96, 97, 129]
+DIAGONALS = [0, 1, 2, 66, 130, 64 * 61 + 1, 64 * 62 + 1, 64 * 63 + 1, 64 * 64 + 1, 64 * 65 + 1, 64 * 126 + 1, 64 * 128 + 1]      # 0 .. that many - 1
+
+
+@pytest.mark.parametrize("d,n,n_hat", [(128, 8448, 130), (128, 8400, 97), (128, 8425, 3), (64, 8448, 130), (64, 8470, 40)])
+def test_tile_loop_edges(oracle, d, n, n_hat):
+    print(f"tile loop edges d={d} n={n} n_hat={n_hat}", flush=True)
+    rng = np.random.default_rng(n)
+    heads = [(COLUMNS[(i + j) % len(COLUMNS)], s) for i, s in enumerate(DIAGONALS) for j in (0, 3, 7)]
+    Hq = len(heads)
+    v_idx, s_idx = np.zeros((1, Hq, n), np.int32), np.zeros((1, Hq, n), np.int32)
+    v_cnt, s_cnt = np.zeros((1, Hq), np.int32), np.zeros((1, Hq), np.int32)
+    for h, (c, s) in enumerate(heads):
+        s = min(s, n)
+        v_idx[0, h, :c] = np.sort(rng.choice(n - n_hat, size=c, replace=False)); v_cnt[0, h] = c
+        s_idx[0, h, :s] = np.arange(s); s_cnt[0, h] = s
+    q, k, v = inputs.make_plain(1, Hq, 4, n, n_hat, d, dtype="bf16", seed=n + d, q_scale=1.5)
+    ref, rlse = oracle.attend(q, k, v, v_idx, v_cnt, s_idx, s_cnt, mode=0)
+    pipe = Pipeline(q, k, v, 1, "bf16")
+    items = Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128)
+    tables = Hq * ((n + 31) // 32 * 4 + 64 + (n // 64 + 5) * 3) + items * 20 + 4096        # no room for parts: queues of whole items
+    for ctx, pieces in ((pipe.ctx, True), (binding.Context(workspace=tables), False)):
+        pipe.ctx = ctx
+        out, lse = pipe.prefill(dev_lists(v_idx, v_cnt, s_idx, s_cnt), sentinel=True)
+        assert (ctx.debug_prefill_queues(pipe.shape)[2] > 0) == pieces
+        assert ctx.ls_poll_status() == 0
+        o, l = out.float().cpu().numpy().reshape(ref.shape), lse.cpu().numpy().reshape(rlse.shape)
+        assert not np.isnan(o).any() and not np.isnan(l).any()
+        err = np.abs(o - ref)
+        assert err.max() <= 2e-2 and err.mean() <= 5e-3, (err.max(), err.mean())       # as everywhere for bf16
+        alive = np.isfinite(rlse)
+        np.testing.assert_array_equal(np.isfinite(l), alive)
+        assert np.abs(l[alive] - rlse[alive]).max() <= 2e-3
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d", [(6, 16, 4, 8100, 3000, 128), (6, 16, 4, 8100, 6100, 64)])
+def test_either_side_of_the_line(B, Hq, Hkv, n, n_hat, d):
+    """One call beyond the line between pieces and queues against calls of two thirds and one third of its batch, which lie below."""
+    print(f"either side of the line B={B} n={n} n_hat={n_hat} d={d}", flush=True)
+    tiles = lambda b: d * b * Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128) * ((n + 63) // 64)
+    assert tiles(B) > 262144 * 128 >= tiles(4)
+    rng = np.random.default_rng(n_hat)
+    v_idx, s_idx = np.zeros((B, Hq, n), np.int32), np.zeros((B, Hq, n), np.int32)
+    v_cnt, s_cnt = np.zeros((B, Hq), np.int32), np.zeros((B, Hq), np.int32)
+    for b in range(B):
+        for h in range(Hq):
+            kind = (b + h) % 4
+            s = np.arange(n) if kind == 0 else np.zeros(0, int) if kind == 1 else np.flatnonzero(rng.random(n) < (0.02 if kind == 2 else 0.2))
+            c = np.flatnonzero(rng.random(n) < (0.1 if kind == 1 else 0.01))
+            v_idx[b, h, :len(c)] = c; v_cnt[b, h] = len(c)
+            s_idx[b, h, :len(s)] = s; s_cnt[b, h] = len(s)
+    q, k, v = inputs.make_plain(B, Hq, Hkv, n, n_hat, d, dtype="bf16", seed=n_hat, q_scale=1.5)
+    whole = Pipeline(q, k, v, 1, "bf16")
+    out, lse = whole.prefill(dev_lists(v_idx, v_cnt, s_idx, s_cnt), sentinel=True)
+    tol = 4 * 2.0 ** -9 * float(np.abs(v).max())           # each side rounds every probability (2^-9 relative) and the result
+    for b in (slice(0, 4), slice(4, B)):
+        part, plse = Pipeline(q[b], k[b], v[b], 1, "bf16").prefill(dev_lists(v_idx[b], v_cnt[b], s_idx[b], s_cnt[b]), sentinel=True)
+        assert not torch.isnan(out[b]).any() and not torch.isnan(part).any()
+        assert (out[b].float() - part.float()).abs().max().item() <= tol
+        some = torch.isfinite(plse)
+        assert torch.equal(torch.isfinite(lse[b]), some)
+        assert (lse[b][some] - plse[some]).abs().max().item() <= 1e-4
