@@ -6,7 +6,7 @@
 //
 // The softmax normaliser of a row is only known after all keys were seen, and the line sums mix
 // rows with different normalisers, so the pass is split:
-//   stats_kernel   per (row, 128-key block): max and sum of exp of the scaled logits;
+//   stats_kernel   per (row, range of keys): a reference and the sum of exp of the scaled logits against it;
 //   merge_kernel   per row: global max m and 1/l;
 //   lines_kernel   recomputes the logits, forms A = exp2(x - m) / l, and reduces it
 //                  - over rows, in registers, to column sums / maxima (written once, in order);
@@ -18,15 +18,14 @@
 // diagonals_kernel adds each diagonal's cells in row order, on from where the band before it stopped.
 // Everything is summed in a fixed order, so results are bit-reproducible from run to run.
 //
-// Tile products run on 32x32 MFMA with K fragments held in registers: each wave owns 32 keys of a block
-// and meets every query head of the KV group and every 32-row group with them.  Those chunks of 32 query rows
+// Tile products run on 32x32 MFMA.  In lines_kernel (and stats_kernel in fp32) each wave owns 32 keys of a block, whose fragments it keeps in
+// registers, and meets every query head of the KV group and every 32-row group with them.  Those chunks of 32 query rows
 // come through LDS by global -> LDS transfers, two buffers, one barrier per chunk.  K rows go through LDS on
 // their way to the registers as well: read straight from global memory a fragment load touches 32 rows with
-// 32 bytes each.  What bounds the passes is vector instruction issue (71 and 52 % of all SIMD cycles in stats and
-// lines at 131072 keys, 4 cycles each, about 130 and 200 instructions per wave and chunk): what counts is few of
-// them (no masks where every row sees every key, no address arithmetic in the diagonal sums), and little enough
+// 32 bytes each.  What bounds lines_kernel is vector instruction issue (52 % of all SIMD cycles at 131072 keys, 4 cycles each)
+// and LDS: what counts is few instructions (no masks where every row sees every key, no address arithmetic in the diagonal sums), and little enough
 // LDS (33 to 38 KB) for four workgroups per CU.  Whole windows of 64 rows in LDS (100 KB, one workgroup per CU),
-// as one step: 131072 keys 234 + 832 us, now 202 + 310; retention score, 16384 keys, B 4: 79 + 102 us, now 38 + 43.
+// as one step: 131072 keys 832 us, by chunks 310; retention score, 16384 keys, B 4: 102 us, by chunks 43.
 #include <type_traits>
 
 #include "ls_device.h"
@@ -78,7 +77,7 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) { return (uint32_
 struct Chunk { int start, cnt, t0; };         // t0: window row of the first one (row r of the chunk: (t0 + r) % w)
 struct Chunks {
     int w, rows, rgs, count, first, end;      // `first`: window row at which a head's chunks begin; they reach row end - 1
-    __device__ __forceinline__ Chunks(int w_, int G, bool packed) : w(w_), rows(G * w_), rgs(packed ? 0 : (w_ + 31) / 32), count(packed ? (G * w_ + 31) / 32 : G * ((w_ + 31) / 32)), first(0), end(w_) {}
+    __host__ __device__ __forceinline__ Chunks(int w_, int G, bool packed) : w(w_), rows(G * w_), rgs(packed ? 0 : (w_ + 31) / 32), count(packed ? (G * w_ + 31) / 32 : G * ((w_ + 31) / 32)), first(0), end(w_) {}
     // the chunks that hold window rows t0 .. t1 - 1
     __device__ __forceinline__ Chunks(int w_, int G, int t0, int t1) : w(w_), rows(G * w_), rgs((t1 + 31) / 32 - t0 / 32), count(G * rgs), first(t0 & ~31), end(t1) {}
     __device__ __forceinline__ Chunk at(int c) const {
@@ -133,12 +132,201 @@ __device__ __forceinline__ int position_of(const ScoreArgs& a, int t) {
     return (int)(p < -1 ? -1 : p);
 }
 
-// ---- pass 1: per (row, key block) max and sum of exp2 -----------------------------------------
-// grid (nkb, B*Hkv, shares of the G heads).  part[(bk * nkb + kb) * G w + row] = {max, sum} over the 128 keys of block kb.
+// ---- pass 1: per (row, range of keys) max and sum of exp2 -----------------------------------------
+// grid (ranges of keys, B*Hkv, shares of the heads).  part[(bk * a.parts + range) * G w + row] = {max, sum} over the range's keys.
+//
+// bf16.  Bound by the reads of K where there are few rows, by vector and matrix issue where there are many.
+// A wave keeps 32 or 64 query rows in registers and meets the tiles of its range with them, three buffers of 64 keys
+// that the four waves fill and read together, the tile after the next under way at the barrier; a row is in a lane, and
+// its sum stays there until the end.  No maximum is looked for on the way: the reference is the maximum of the first 32 keys and moves
+// where a sum exceeds 2^30 (fp32 sums are as exact there; a reference of zero, with no look at the first keys, was not): three vector instructions a cell.
+// Against a workgroup per 128 keys with all rows passing through LDS (nine instructions a cell, K of all resident workgroups asked for at once
+// and nothing meanwhile, statistics of every 128 keys written), us: 131072 keys, 128 rows, 193 -> 138, 16384 keys, B 4, 64 heads, 104 -> 74, 32768 keys
+// 34 -> 24.5, 12347 17.6 -> 13.9, retention score, 16384 keys, B 4, 35 -> 27 (134 MB: 5 TB/s); of 5003 keys, d = 64, 6.5 -> 7.3: 2 us of a
+// workgroup are the way of its queries from memory.  Everything in 56 KB of LDS, two workgroups a CU: 155 at 131072 keys.
+template <int D>
+struct KeyTile {
+    static constexpr int KEYS = 64, BUFFERS = 3;
+    static constexpr int RB = D * 2, DS = RB / 16, RPI = 64 / DS, NI = KEYS / RPI, IPW = NI / 4;
+    static constexpr int ISTR = D == 128 ? 1088 : 1024;   // LDS bytes from one transfer to the next
+    static constexpr int BYTES = NI * ISTR, HALF = BYTES / 2;
+    static constexpr int KA = D == 128 ? 2 : 4;           // fragment address registers
+    // slot s of row r holds chunk s ^ swz(r): a fragment read touches every bank once a pass
+    __device__ static constexpr int swz(int row) { return D == 128 ? (row & 3) : (((row >> 1) & 3) | (((row >> 3) & 1) << 2)); }
+};
+constexpr int STATS_CHUNKS = 8;           // chunks of 32 rows of a workgroup
+constexpr float STATS_LIMIT = 1073741824.f;
+template <int D>
+__host__ __device__ constexpr int stats_lds() { return KeyTile<D>::BUFFERS * KeyTile<D>::BYTES; }
+
+template <int D>
+__device__ __forceinline__ void stats_stream(const ScoreArgs& a, unsigned char* smem) {
+    using C = KeyTile<D>;
+    using T = bf16_t;
+    constexpr int NS = D / 16;
+    float2 (*red)[STATS_CHUNKS][32] = reinterpret_cast<float2 (*)[STATS_CHUNKS][32]>(smem);      // [2 halves of a tile], once the tiles are done with
+    static_assert(C::BYTES >= 2 * STATS_CHUNKS * 32 * 8, "room for the waves' results");
+    const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bk = blockIdx.y, b = bk / a.Hkv, kvh = bk % a.Hkv;
+    const int64_t n = a.n;
+    const unsigned char* Kg = reinterpret_cast<const unsigned char*>(a.k) + (int64_t)bk * n * C::RB;
+    const unsigned char* Q0 = reinterpret_cast<const unsigned char*>(a.q) + (int64_t)(b * a.Hq + kvh * a.G) * a.w * C::RB;
+    const Chunks ch(a.w, a.G, packs(a.w));
+    const int c0 = a.stat_chunks * (int)blockIdx.z, here = ch.count - c0 < a.stat_chunks ? ch.count - c0 : a.stat_chunks;
+    // rows: waves side by side on chunks; few chunks: two waves share one, a half of each tile each (of one chunk, two waves only read K)
+    const int rw = here > 2 ? 4 : here, kw = here > 2 ? 1 : 2;
+    const int cw = wv % rw, kh = wv / rw;                  // this wave's first chunk and, where they share, its half
+    const bool works = kh < kw;
+    const int mine = !works ? 0 : cw + rw < here ? 2 : 1;  // chunks cw, cw + 4
+    const uint32_t nt = (uint32_t)((n + C::KEYS - 1) / C::KEYS);                  // (fewer than 2^16, and ranges fewer than 2^8)
+    const int t0 = (int)(nt * blockIdx.x / gridDim.x), t1 = (int)(nt * (blockIdx.x + 1) / gridDim.x);
+
+    if (a.done && blockIdx.x == 0 && blockIdx.z == 0)      // finish_kernel's counters
+        for (int h = tid; h < a.G; h += SCORE_THREADS) clear_shared(a.done + b * a.Hq + kvh * a.G + h);
+    // ---- transfers: wave wv fetches rows 16 wv .. 16 wv + 15 of a tile; keys beyond the context repeat the last one
+    const int rowlane = 16 * wv + lane / C::DS, sl = lane % C::DS;
+    const uint32_t part0 = 16u * (uint32_t)(sl ^ C::swz(rowlane));
+    const uint32_t lds0 = lds_address(smem) + (uint32_t)(wv * C::IPW * C::ISTR);
+    auto fetch = [&](int t, int buf) {
+        const int64_t key0 = (int64_t)t * C::KEYS, left = n - key0;
+        const int last = left < C::KEYS ? (int)left - 1 : C::KEYS - 1;
+        const unsigned char* src = uniform_ptr(Kg + key0 * C::RB);
+        const uint32_t dst = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds0 + (uint32_t)(buf * C::BYTES)));
+#pragma unroll
+        for (int i = 0; i < C::IPW; ++i) {
+            const int row = rowlane + C::RPI * i;
+            dma16(src, (uint32_t)(row < last ? row : last) * C::RB + (D == 128 ? part0 : part0 ^ (uint32_t)(64 * (i & 1))), dst + (uint32_t)(i * C::ISTR));
+        }
+    };
+    fetch(t0, 0);
+    // ---- the rows: fragments, by way of LDS like the keys (the last two buffers have a half for each wave), and the position each lane's row ends at
+    const int x = C::swz(r32);
+    int kaddr[C::KA];
+#pragma unroll
+    for (int j = 0; j < C::KA; ++j) kaddr[j] = (r32 / C::RPI) * C::ISTR + (r32 % C::RPI) * C::RB + 32 * (j ^ (x >> 1)) + 16 * (g ^ (x & 1));
+    Frag<T> q[2][NS];
+    int pos[2];
+    const uint32_t stage = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_address(smem) + (uint32_t)(C::BYTES + wv * C::HALF)));
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const Chunk k = ch.at(c0 + (i < mine ? cw + rw * i : cw));
+        if (i == 0 || mine == 2) {
+            const unsigned char* src = uniform_ptr(Q0 + (int64_t)k.start * C::RB);
+#pragma unroll
+            for (int j = 0; j < C::NI / 2; ++j) {
+                const int row = lane / C::DS + C::RPI * j;
+                dma16(src, (uint32_t)(row < k.cnt ? row : k.cnt - 1) * C::RB + 16u * (uint32_t)(sl ^ C::swz(row)), stage + (uint32_t)(j * C::ISTR));
+            }
+            wait_transfers();
+#pragma unroll
+            for (int c = 0; c < NS; ++c) load_frag(q[i][c], smem + C::BYTES + wv * C::HALF + kaddr[c & (C::KA - 1)] + 32 * (c & ~(C::KA - 1)));
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the stage may be filled again
+        }
+        int t = k.t0 + r32;
+        if (ch.rgs == 0) t &= a.w - 1;                     // packed windows: w is a power of two
+        pos[i] = t < a.w ? position_of(a, t) : INT_MAX;  // (rows that are none: not kept)
+    }
+    wait_transfers();
+    __syncthreads();                                       // the stages are free
+    if (t0 + 1 < t1) fetch(t0 + 1, 1);
+    const float sc = a.scale_log2e;
+    float mneg[2] = {INFINITY, INFINITY}, l[2] = {0.f, 0.f};      // reference of the lane's row in base 2, negated (+inf: no cell seen yet), and the sum against it
+    int buf = 0;
+    for (int t = t0; t < t1; ++t) {
+        // this wave's transfers of tile t have landed (those of the next are under way), and every wave is done with the tile before
+        if (t + 1 < t1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(C::IPW) : "memory"); else wait_transfers();
+        lds_barrier();
+        const int next = buf + 2 < 3 ? buf + 2 : buf - 1;
+        if (t + 2 < t1) fetch(t + 2, next);
+        const int64_t key0 = (int64_t)t * C::KEYS;
+        const bool open = __ballot((pos[0] < pos[1] ? pos[0] : pos[1]) < (int)key0 + C::KEYS - 1) == 0ull;      // this wave's rows see every key (of a context: n is an int's)
+        auto half = [&](int h, auto TWO, auto OPEN) {
+            constexpr int N = decltype(TWO)::value ? 2 : 1;
+            const unsigned char* base = smem + buf * C::BYTES + h * C::HALF;
+            f32x16 s[N];
+            {
+                Frag<T> kf[NS];
+                constexpr int AHEAD = 4;
+#pragma unroll
+                for (int c = 0; c < AHEAD; ++c) load_frag(kf[c], base + kaddr[c & (C::KA - 1)] + 32 * (c & ~(C::KA - 1)));
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) s[i][r] = 0.f;
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int c = 0; c < NS; ++c) {
+#pragma unroll
+                    for (int i = 0; i < N; ++i) mma(s[i], kf[c], q[i][c]);           // s[r] = <k_{8(r/4)+4g+r%4}, q_row>
+                    if (c + AHEAD < NS) load_frag(kf[c + AHEAD], base + kaddr[(c + AHEAD) & (C::KA - 1)] + 32 * ((c + AHEAD) & ~(C::KA - 1)));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if constexpr (!decltype(OPEN)::value) {
+                    const int lim = pos[i] - ((int)key0 + 32 * h + 4 * g);           // register r holds key 4g + 8(r/4) + r%4 of the half
+                    if (__ballot(lim >= 0) == 0ull) continue;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) if (8 * (r >> 2) + (r & 3) > lim) s[i][r] = -INFINITY;
+                }
+                float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) {
+                    s0 += fast_exp2(__builtin_fmaf(s[i][r], sc, mneg[i]));
+                    s1 += fast_exp2(__builtin_fmaf(s[i][r + 1], sc, mneg[i]));
+                }
+                float sum = s0 + s1;
+                if (__ballot(!(sum <= STATS_LIMIT)) != 0ull) {     // once more against the maximum (a row's first cells: mneg = inf)
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[i][r] * sc);
+                    const float m = fmaxf(mx, -mneg[i]);
+                    l[i] *= m > -INFINITY ? fast_exp2(-mneg[i] - m) : 1.f;
+                    mneg[i] = -m;
+                    const float safe = m > -INFINITY ? -m : 0.f;
+                    sum = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum += fast_exp2(__builtin_fmaf(s[i][r], sc, safe));
+                }
+                l[i] += sum;
+            }
+        };
+        auto tile = [&](auto TWO, auto OPEN) { for (int h = kh; h < 2; h += kw) half(h, TWO, OPEN); };
+        if (mine == 2) { if (open) tile(std::true_type{}, std::true_type{}); else tile(std::true_type{}, std::false_type{}); }
+        else if (mine == 1) { if (open) tile(std::false_type{}, std::true_type{}); else tile(std::false_type{}, std::false_type{}); }
+        buf = buf + 1 < 3 ? buf + 1 : 0;
+    }
+    wait_transfers();                                      // (none is under way)
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (i >= mine) break;
+        const float m = -mneg[i], M = halves_max(m);
+        const float sum = halves_sum(m > -INFINITY ? l[i] * fast_exp2(m - M) : 0.f);
+        if (g == 0) red[kh][cw + rw * i][r32] = make_float2(M, sum);
+    }
+    __syncthreads();
+    const int c = tid >> 5;
+    if (c < here) {
+        const Chunk k = ch.at(c0 + c);
+        float2 v = red[0][c][r32];
+        if (kw == 2) {
+            const float2 u = red[1][c][r32];
+            const float M = fmaxf(v.x, u.x), Ms = M > -INFINITY ? M : 0.f;
+            v = make_float2(M, v.y * fast_exp2(v.x - Ms) + u.y * fast_exp2(u.x - Ms));
+        }
+        if (r32 < k.cnt) reinterpret_cast<float2*>(a.part)[((int64_t)bk * a.parts + blockIdx.x) * (a.G * a.w) + k.start + r32] = v;
+    }
+}
+// fp32 (short contexts): a workgroup per 128 keys, which it keeps in registers while the chunks of rows pass.
 template <typename T, int D>
-__global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void stats_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 3 : 1)) void stats_kernel(ScoreArgs a) {
     using RT = RowTile<T, D>;
     extern __shared__ __align__(16) unsigned char smem[];
+    if constexpr (Elem<T>::bytes == 2) { stats_stream<D>(a, smem); return; }
+    else {
     unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
     unsigned char* qs = smem;                              // [2] chunks of queries and
     float2 (*red)[4][32] = reinterpret_cast<float2 (*)[4][32]>(smem + 2 * RT::BYTES);   // [RED_CHUNKS] results of the waves
@@ -222,11 +410,12 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
                 float L = 0.f;
 #pragma unroll
                 for (int w4 = 0; w4 < 4; ++w4) L += v[w4].y * fast_exp2(v[w4].x - Ms);
-                reinterpret_cast<float2*>(a.part)[((int64_t)bk * a.nkb + kb) * rows + kk.start + r] = make_float2(M, L);
+                reinterpret_cast<float2*>(a.part)[((int64_t)bk * a.parts + kb) * rows + kk.start + r] = make_float2(M, L);
             }
             first = c + 1;
             if (first < c1) __syncthreads();         // `red` is written again
         }
+    }
     }
 }
 
@@ -238,7 +427,7 @@ __global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
     const int rows = a.G * a.w, bk = blockIdx.y;
     const int row = blockIdx.x * 16 + (threadIdx.x & 15), k0 = threadIdx.x >> 4;           // as a reader of `part`
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;                                // as a lane of row wv
-    const float2* p = reinterpret_cast<const float2*>(a.part) + (int64_t)bk * a.nkb * rows + (row < rows ? row : rows - 1);
+    const float2* p = reinterpret_cast<const float2*>(a.part) + (int64_t)bk * a.parts * rows + (row < rows ? row : rows - 1);
     constexpr int KEEP = 4;                                // values a thread keeps from the first look (contexts up to 32768)
     float2 v[KEEP];
     float M = -INFINITY, L = 0.f;
@@ -246,12 +435,12 @@ __global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
     for (int i = 0; i < KEEP; ++i) {
         const int kb = k0 + 64 * i;
         v[i] = make_float2(-INFINITY, 0.f);
-        if (kb < a.nkb) v[i] = p[(int64_t)kb * rows];
+        if (kb < a.parts) v[i] = p[(int64_t)kb * rows];
     }
 #pragma unroll
     for (int i = 0; i < KEEP; ++i) M = fmaxf(M, v[i].x);
 #pragma unroll 4
-    for (int kb = k0 + 64 * KEEP; kb < a.nkb; kb += 64) M = fmaxf(M, p[(int64_t)kb * rows].x);
+    for (int kb = k0 + 64 * KEEP; kb < a.parts; kb += 64) M = fmaxf(M, p[(int64_t)kb * rows].x);
     x[k0][threadIdx.x & 15] = M;
     __syncthreads();
     M = x[lane][wv];
@@ -266,7 +455,7 @@ __global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
     for (int i = 0; i < KEEP; ++i)
         if (v[i].x != -INFINITY) L += v[i].y * fast_exp2(v[i].x - Mr);
 #pragma unroll 4
-    for (int kb = k0 + 64 * KEEP; kb < a.nkb; kb += 64) {
+    for (int kb = k0 + 64 * KEEP; kb < a.parts; kb += 64) {
         const float2 u = p[(int64_t)kb * rows];
         if (u.x != -INFINITY) L += u.y * fast_exp2(u.x - Mr);
     }
@@ -286,13 +475,13 @@ static int score_chunks(const ScoreArgs& a) { return a.G * ((a.w + 31) / 32); } 
 static bool folds(const ScoreArgs& a) { return a.nkb <= FOLD_BLOCKS && score_chunks(a) <= FOLD_CHUNKS; }
 __device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row) {
     const int rows = a.G * a.w;
-    const float2* p = reinterpret_cast<const float2*>(a.part) + (int64_t)bk * a.nkb * rows + row;
+    const float2* p = reinterpret_cast<const float2*>(a.part) + (int64_t)bk * a.parts * rows + row;
     float2 v[FOLD_BLOCKS];
     float l[FOLD_BLOCKS], M = -INFINITY;
 #pragma unroll
-    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) v[kb] = p[(int64_t)(kb < a.nkb ? kb : 0) * rows];
+    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) v[kb] = p[(int64_t)(kb < a.parts ? kb : 0) * rows];
 #pragma unroll
-    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) { if (kb >= a.nkb) v[kb] = make_float2(-INFINITY, 0.f); M = fmaxf(M, v[kb].x); }
+    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) { if (kb >= a.parts) v[kb] = make_float2(-INFINITY, 0.f); M = fmaxf(M, v[kb].x); }
 #pragma unroll
     for (int kb = 0; kb < FOLD_BLOCKS; ++kb) l[kb] = v[kb].x != -INFINITY ? v[kb].y * fast_exp2(v[kb].x - M) : 0.f;
 #pragma unroll
@@ -391,21 +580,24 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
                 const int rq = 8 * q4 + 4 * g;             // registers 4*q4 .. 4*q4+3 hold the chunk's rows rq .. rq+3
                 const f32x4 sa = *reinterpret_cast<const f32x4*>(rs + 2 * rq);            // m, 1/l of rows rq, rq+1
                 const f32x4 sb = *reinterpret_cast<const f32x4*>(rs + 2 * rq + 4);        // ... rq+2, rq+3
+                // (1 / sum in the exponent instead would take the product away, and cost six times the error: the offset has 2^-20 and more)
+                float pe[4];
                 const float mm[4] = {sa.x, sa.z, sb.x, sb.z}, il[4] = {sa.y, sa.w, sb.y, sb.w};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int row = rq + e;
-                    float p = fast_exp2(s[4 * q4 + e] * a.scale_log2e - mm[e]) * il[e];
+                    float p = fast_exp2(__builtin_fmaf(s[4 * q4 + e], a.scale_log2e, -mm[e])) * il[e];
                     if constexpr (decltype(MASKED)::value) {
                         int t = k.t0 + row;
                         if (MODE == 2 && packed) t &= a.w - 1;
                         p = ((row < k.cnt) & (klocal <= ql[t < a.w ? t : a.w - 1])) ? p : 0.f;
                     }
                     ps += p;
-                    if (MODE == 0 || MODE == 1) pm = fmaxf(pm, p);
+                    pe[e] = p;
                     if (MODE == 0) slab[(klocal - row + 31) * SLAB + row] = p;
                     if ((MODE == 1 || MODE == 3) && (unsigned)(row - lo) < (unsigned)cells && mykey < n) cell[(8 * q4 + e) * n] = p;
                 }
+                if (MODE == 0 || MODE == 1) { pm = fmaxf(fmaxf(pm, pe[0]), pe[1]); pm = fmaxf(fmaxf(pm, pe[2]), pe[3]); }
                 if (MODE == 2 && packed && (8 * (q4 + 1)) % a.w == 0) {                  // the last rows of a head
                     gsum += halves_sum(ps);                // (rows past the last head add zeros)
                     ps = 0.f;
@@ -430,7 +622,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
 #pragma unroll
                     for (int e = 0; e < 16; ++e) p[e] = slab[at + rb + e];
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) { dsum += p[e]; dmax = fmaxf(dmax, p[e]); }
+                    for (int e = 0; e < 16; e += 2) { dsum += p[e]; dsum += p[e + 1]; dmax = fmaxf(fmaxf(dmax, p[e]), p[e + 1]); }
                 }
             }
         }
@@ -560,10 +752,30 @@ static int head_shares(const ScoreArgs& a, int kv_heads) {
     while (a.G % (2 * z) == 0 && wgs * 2 * z <= (chunks >= 8 * z ? 2048 : 1024)) z *= 2;
     return z;
 }
+// Ranges of keys whose statistics are kept apart: as many as fill the chip with three workgroups a CU
+// (more than 64 cost merge_kernel what they save); no more than the blocks of 128 keys that `part` has room for.  Few rows a workgroup where there
+// is little work: eight / four / two chunks of rows, us, 131072 keys 140 / 157, 16384 keys, B 4, 75 / 81, 32768 24.0 / 24.4, 12347 16.0 / 13.8, 5003 of d = 64
+// 10.2 / 8.0 / 7.3.
+constexpr int STATS_PARTS = 64;
+static void stats_split(ScoreArgs& a, bool bf16) {
+    a.parts = a.nkb; a.stat_chunks = STATS_CHUNKS;
+    if (!bf16) return;
+    const int count = Chunks(a.w, a.G, packs(a.w)).count;
+    const int64_t work = (int64_t)a.B * a.Hkv * a.nkb * count;       // 128 keys by 32 rows
+    if (work <= 24576) a.stat_chunks = work < 2560 ? 2 : 4;
+    int r = 768 / (a.B * a.Hkv * ((count + a.stat_chunks - 1) / a.stat_chunks));
+    r = r > STATS_PARTS ? STATS_PARTS : r < 1 ? 1 : r;
+    a.parts = r < a.nkb ? r : a.nkb;
+}
 template <typename T, int D>
 static void launch_stats(const ScoreArgs& a, hipStream_t st) {
-    const size_t smem = stats_front<T, D>() + (size_t)a.w * 4;
-    hipLaunchKernelGGL((stats_kernel<T, D>), dim3(a.nkb, a.B * a.Hkv, packs(a.w) ? 1 : head_shares(a, a.B * a.Hkv)), dim3(SCORE_THREADS), smem, st, a);
+    if constexpr (Elem<T>::bytes == 2) {
+        const int z = (Chunks(a.w, a.G, packs(a.w)).count + a.stat_chunks - 1) / a.stat_chunks;
+        hipLaunchKernelGGL((stats_kernel<T, D>), dim3(a.parts, a.B * a.Hkv, z), dim3(SCORE_THREADS), stats_lds<D>(), st, a);
+    } else {
+        const size_t smem = stats_front<T, D>() + (size_t)a.w * 4;
+        hipLaunchKernelGGL((stats_kernel<T, D>), dim3(a.nkb, a.B * a.Hkv, packs(a.w) ? 1 : head_shares(a, a.B * a.Hkv)), dim3(SCORE_THREADS), smem, st, a);
+    }
 }
 template <typename T, int D, int MODE>
 static void launch_lines(const ScoreArgs& a, int kv_heads, hipStream_t st) {
@@ -594,6 +806,7 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     ScoreArgs a = a0;
     const int BK = a.B * a.Hkv;
     a.t0 = 0; a.t1 = a.w;
+    stats_split(a, Elem<T>::bytes == 2);
     launch_stats<T, D>(a, st);
     if (!folds(a)) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {
