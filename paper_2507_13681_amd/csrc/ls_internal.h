@@ -21,6 +21,7 @@ struct ScoreArgs {
     float* a_win;             // [BH][w][n]       the window matrix (mode 3), or [heads from bh_first on][t1 - t0][n] a band of it (mode 1)
     int64_t win_rows;         // mode 1: how many rows of a KV head's G heads the buffer takes, at least one
     // set by run_score for each launch
+    bool retain;              // mode 2: all rows in LDS
     int parts, stat_chunks;   // ranges of keys whose row statistics lie in `part`; chunks of rows of a workgroup of stats_kernel
     int bk0, bh_first;        // first KV head / query head
     int t0, t1;               // window rows whose matrix is written out

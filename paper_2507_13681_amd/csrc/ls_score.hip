@@ -468,27 +468,118 @@ __global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
         reinterpret_cast<float2*>(a.rowstat)[(int64_t)bk * rows + blockIdx.x * 16 + wv] = make_float2(M, L > 0.f ? 1.0f / L : 0.f);
 }
 
-// Short contexts: lines_kernel merges the statistics of its rows itself (every workgroup of a KV head again: at most
-// FOLD_BLOCKS * 8 bytes a row out of the L2), which takes a launch of 3.5 us away.  The same values in the same order.
-constexpr int FOLD_BLOCKS = 16, FOLD_CHUNKS = 32;
+// Short windows and contexts: lines_kernel merges the statistics of its rows itself, every workgroup again, which takes a launch away: the
+// retention score of 4096 entries, 8 rows of 32 heads (2 MB read so) 22.6 -> 20.6 us.  Beyond a few MB that costs more than the launch: ls_score of 5003
+// keys, d = 64 (10 MB) 35.8 -> 36.8, 8192 keys (50 MB) 38.2 -> 44.6.
+constexpr int FOLD_PARTS = 64, FOLD_CHUNKS = 32;
+constexpr int64_t FOLD_BYTES = 4 << 20;
 static int score_chunks(const ScoreArgs& a) { return a.G * ((a.w + 31) / 32); }           // at most: packed windows take fewer
-static bool folds(const ScoreArgs& a) { return a.nkb <= FOLD_BLOCKS && score_chunks(a) <= FOLD_CHUNKS; }
-__device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row) {
+// Four neighbouring lanes share a row's ranges; all of them get {max, 1 / sum}.
+__device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row, int part) {
     const int rows = a.G * a.w;
     const float2* p = reinterpret_cast<const float2*>(a.part) + (int64_t)bk * a.parts * rows + row;
-    float2 v[FOLD_BLOCKS];
-    float l[FOLD_BLOCKS], M = -INFINITY;
+    float2 v[FOLD_PARTS / 4];
+    float M = -INFINITY, L = 0.f;
 #pragma unroll
-    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) v[kb] = p[(int64_t)(kb < a.parts ? kb : 0) * rows];
+    for (int q = 0; q < FOLD_PARTS / 16; ++q) {            // as many loads at once as there are ranges
 #pragma unroll
-    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) { if (kb >= a.parts) v[kb] = make_float2(-INFINITY, 0.f); M = fmaxf(M, v[kb].x); }
+        for (int u = 4 * q; u < 4 * q + 4; ++u) v[u] = make_float2(-INFINITY, 0.f);
+        if (16 * q < a.parts) {
 #pragma unroll
-    for (int kb = 0; kb < FOLD_BLOCKS; ++kb) l[kb] = v[kb].x != -INFINITY ? v[kb].y * fast_exp2(v[kb].x - M) : 0.f;
+            for (int u = 4 * q; u < 4 * q + 4; ++u) v[u] = p[(int64_t)(4 * u + part < a.parts ? 4 * u + part : 0) * rows];
+        }
+    }
 #pragma unroll
-    for (int off = FOLD_BLOCKS / 2; off > 0; off >>= 1)
+    for (int u = 0; u < FOLD_PARTS / 4; ++u) if (4 * u + part >= a.parts) v[u] = make_float2(-INFINITY, 0.f);
 #pragma unroll
-        for (int i = 0; i < off; ++i) l[i] += l[i + off];
-    return make_float2(M, l[0] > 0.f ? 1.0f / l[0] : 0.f);
+    for (int u = 0; u < FOLD_PARTS / 4; ++u) M = fmaxf(M, v[u].x);
+    M = fmaxf(M, __shfl_xor(M, 1, 64));
+    M = fmaxf(M, __shfl_xor(M, 2, 64));
+#pragma unroll
+    for (int u = 0; u < FOLD_PARTS / 4; ++u) L += v[u].x != -INFINITY ? v[u].y * fast_exp2(v[u].x - M) : 0.f;
+    L += __shfl_xor(L, 1, 64);
+    L += __shfl_xor(L, 2, 64);
+    return make_float2(M, L > 0.f ? 1.0f / L : 0.f);
+}
+
+// ---- pass 2 of the retention score with few rows: all of them stay in LDS, the keys come by ----------------
+// grid (workgroups that share a KV head's key blocks, B*Hkv).  Bound by the reads of K.  A wave has its 32 keys of a block in registers and those of
+// the workgroup's next block on their way to its own stage; between blocks nobody waits for anybody.  Against a workgroup per block past which the chunks
+// come, a barrier each, us: 16384 entries, B 4, 128 rows a KV head 39 -> 31, 32768, B 2, d = 64 18.4 -> 13.8, 65536, 8 KV heads of 16 rows 26 -> 21.
+constexpr int RETAIN_CHUNKS = 4;
+template <int D>
+__host__ __device__ constexpr int retain_lds() { return (4 + RETAIN_CHUNKS) * RowTile<bf16_t, D>::BYTES + RETAIN_CHUNKS * 32 * 8; }
+template <int D>
+__device__ __forceinline__ void retain_stream(const ScoreArgs& a, unsigned char* smem) {
+    using T = bf16_t;
+    using RT = RowTile<T, D>;
+    unsigned char* qs = smem + 4 * RT::BYTES;              // the chunks
+    float2* rst = reinterpret_cast<float2*>(smem + (4 + RETAIN_CHUNKS) * RT::BYTES);          // max and 1 / sum of their rows
+    const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int bk = a.bk0 + blockIdx.y, bh0 = bk * a.G;     // (heads of a KV head lie together)
+    const int64_t n = a.n;
+    const unsigned char* Kg = reinterpret_cast<const unsigned char*>(a.k) + (int64_t)bk * n * RT::RB;
+    const unsigned char* Q0 = reinterpret_cast<const unsigned char*>(a.q) + (int64_t)bh0 * a.w * RT::RB;
+    const Chunks ch(a.w, a.G, packs(a.w));
+    unsigned char* stage = smem + wv * RT::BYTES;
+    auto fetch = [&](int kb) {                             // keys beyond the context repeat the last one
+        const int64_t key0 = (int64_t)kb * SB + 32 * wv, left = n - key0;
+        RT::fetch(Kg + (left > 0 ? key0 : n - 1) * RT::RB, left > 32 ? 32 : left > 0 ? (int)left : 1, lds_address(stage), lane, 0, 1);
+    };
+    int kb = blockIdx.x;
+    fetch(kb);
+    if (wv < ch.count) {
+        const Chunk k = ch.at(wv);
+        RT::fetch(Q0 + (int64_t)k.start * RT::RB, k.cnt, lds_address(qs + wv * RT::BYTES), lane, 0, 1);
+        if (lane < 32) rst[32 * wv + lane] = lane < k.cnt ? reinterpret_cast<const float2*>(a.rowstat)[(int64_t)bh0 * a.w + k.start + lane] : make_float2(INFINITY, 0.f);      // (no row: probabilities of zero)
+    }
+    wait_transfers();
+    __syncthreads();
+    for (;;) {
+        Frag<T> kf[D / 16];
+        RT::frags(kf, stage, r32, g);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         // the stage may be filled again
+        const int here = kb;
+        kb += (int)gridDim.x;
+        if (kb < a.nkb) fetch(kb);
+        const int64_t blk0 = (int64_t)here * SB, mykey = blk0 + 32 * wv + r32;
+        const bool open = blk0 + SB - 1 <= n - a.w;        // every row sees every key
+        float sum = 0.f;
+        auto chunks = [&](auto OPEN) {
+            for (int c = 0; c < ch.count; ++c) {
+                f32x16 s;
+                Frag<T> qf[D / 16];
+                RT::frags(qf, qs + c * RT::BYTES, r32, g);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+                for (int cc = 0; cc < D / 16; ++cc) mma(s, qf[cc], kf[cc]);          // s[r] = <q_{8(r/4)+4g+r%4}, k_lane>
+                const int t0 = ch.at(c).t0;
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) {
+                    const int rq = 8 * q4 + 4 * g;
+                    const f32x4 sa = *reinterpret_cast<const f32x4*>(rst + 32 * c + rq), sb = *reinterpret_cast<const f32x4*>(rst + 32 * c + rq + 2);
+                    const float mm[4] = {sa.x, sa.z, sb.x, sb.z}, il[4] = {sa.y, sa.w, sb.y, sb.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float p = fast_exp2(__builtin_fmaf(s[4 * q4 + e], a.scale_log2e, -mm[e]));
+                        if constexpr (decltype(OPEN)::value) sum = __builtin_fmaf(p, il[e], sum);
+                        else {
+                            int t = t0 + rq + e;
+                            if (ch.rgs == 0) t &= a.w - 1; // packed windows: w is a power of two
+                            sum += mykey <= n - a.w + t ? p * il[e] : 0.f;
+                        }
+                    }
+                }
+            }
+        };
+        if (open) chunks(std::true_type{}); else chunks(std::false_type{});
+        sum = halves_sum(sum);
+        if (g == 0 && mykey < n) a.gscore[(int64_t)bk * n + mykey] = sum;
+        if (kb >= a.nkb) break;
+        wait_transfers();                                  // this wave's keys of the next block
+    }
 }
 
 // ---- pass 2: line sums ------------------------------------------------------------------------
@@ -504,6 +595,7 @@ template <typename T, int D, int MODE, bool FOLD>
 __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void lines_kernel(ScoreArgs a) {
     using RT = RowTile<T, D>;
     extern __shared__ __align__(16) unsigned char smem[];
+    if constexpr (MODE == 2 && Elem<T>::bytes == 2 && !FOLD) { if (a.retain) { retain_stream<D>(a, smem); return; } }
     unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
     float* slab = reinterpret_cast<float*>(smem);          // [SLAB_DIAGS][SLAB] A by diagonals (MODE 0) and
     unsigned char* qs = smem + (MODE == 0 ? SLAB_BYTES : 0);           // [2] chunks of queries
@@ -535,9 +627,11 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         ql[t] = rel < -1 ? -1 : (rel > SB ? SB : (int32_t)rel);
     }
     if (FOLD)
-        for (int i = tid; i < 32 * (c1 - c0); i += SCORE_THREADS) {
+        for (int i4 = tid; i4 < 128 * (c1 - c0); i4 += SCORE_THREADS) {
+            const int i = i4 >> 2;
             const Chunk k = ch.at(c0 + i / 32);
-            reinterpret_cast<float2*>(rst)[i] = row_stats(a, bk, k.start + (i % 32 < k.cnt ? i % 32 : k.cnt - 1));
+            const float2 st = row_stats(a, bk, k.start + (i % 32 < k.cnt ? i % 32 : k.cnt - 1), i4 & 3);
+            if ((i4 & 3) == 0) reinterpret_cast<float2*>(rst)[i] = st;
         }
     Frag<T> kf[D / 16];
     k_frags<T, D>(kf, Kg, blk0 + 32 * wv, n, kst + wv * RT::BYTES, lane);
@@ -777,9 +871,14 @@ static void launch_stats(const ScoreArgs& a, hipStream_t st) {
         hipLaunchKernelGGL((stats_kernel<T, D>), dim3(a.nkb, a.B * a.Hkv, packs(a.w) ? 1 : head_shares(a, a.B * a.Hkv)), dim3(SCORE_THREADS), smem, st, a);
     }
 }
+// whether lines_kernel merges the statistics (of all KV heads: bands of explicit positions do it again)
+static bool folds(const ScoreArgs& a, int mode) {
+    const int64_t bytes = (int64_t)a.nkb * a.B * a.Hkv * (a.G * a.w) * a.parts * 8;      // of all workgroups together (each takes its share of the heads)
+    return a.parts <= FOLD_PARTS && score_chunks(a) <= FOLD_CHUNKS && (bytes <= FOLD_BYTES || (mode != 1 && a.nkb <= 16));
+}
 template <typename T, int D, int MODE>
 static void launch_lines(const ScoreArgs& a, int kv_heads, hipStream_t st) {
-    const bool fold = folds(a);
+    const bool fold = folds(a, MODE);
     const size_t smem = lines_front<T, D>(MODE) + (size_t)(a.w + 3) / 4 * 16 + (fold ? (size_t)score_chunks(a) * 256 : 512);
     const dim3 grid(a.nkb, kv_heads, MODE == 2 ? 1 : head_shares(a, kv_heads));
     if (fold) hipLaunchKernelGGL((lines_kernel<T, D, MODE, true>), grid, dim3(SCORE_THREADS), smem, st, a);
@@ -808,7 +907,7 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     a.t0 = 0; a.t1 = a.w;
     stats_split(a, Elem<T>::bytes == 2);
     launch_stats<T, D>(a, st);
-    if (!folds(a)) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
+    if (!folds(a, mode)) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {
         launch_lines<T, D, 0>(a, BK, st);
     } else if (mode == 1) {
@@ -830,7 +929,12 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
         launch_lines<T, D, 3>(a, BK, st);
         return hipGetLastError();
     } else {
-        launch_lines<T, D, 2>(a, BK, st);
+        const int share = 512 / BK < 1 ? 1 : 512 / BK < a.nkb ? 512 / BK : a.nkb;      // (64 KB of LDS: two workgroups a CU)
+        a.retain = Elem<T>::bytes == 2 && !folds(a, mode) && Chunks(a.w, a.G, packs(a.w)).count <= RETAIN_CHUNKS;
+        if constexpr (Elem<T>::bytes == 2) {
+            if (a.retain) hipLaunchKernelGGL((lines_kernel<T, D, 2, false>), dim3(share, BK), dim3(SCORE_THREADS), retain_lds<D>(), st, a);
+        }
+        if (!a.retain) launch_lines<T, D, 2>(a, BK, st);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(finish_kernel, dim3(a.BH, FINISH_SPLIT), dim3(1024), 0, st, a, mode == 0 ? 1 : 0);
