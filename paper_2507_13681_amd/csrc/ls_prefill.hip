@@ -326,6 +326,9 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // queues per item, and the wait for the longest item, which a short turn feels most.  The whole call, bf16, 32 heads of d = 128, queues -> pieces,
 // us: 2048 rows, all new, 92 -> 68; 1024 new of 8192 152 -> 124; 300 of 16384 89 -> 70; 100 of 131072 254 -> 230; 61 of 12347
 // 32.7 -> 30.3; 4 heads fp32, 256 of 1024 44 -> 38, 2048 all new 65 -> 37.
+// fp32: a tile keeps a workgroup's matrix cores busy for 8200 cycles, all that comes before the first one takes 13000: a few items' tiles
+// go to a workgroup each.  Two tiles a piece and on either side of a cut / one, us: 4 heads of 64, 256 rows of 1024 38.6 / 30.2, 8 heads, 40 of 700 29.0 / 21.8, 20 of
+// 4096 35.2 / 22.4, 700 of 3001 59.4 / 56.8, 4096, all new, 58.2 / 52.8.
 // The line.  What the pieces' estimates miss nothing evens out, and the row spreads the heads of a moment wider than the queues
 // do: the longer the run, the more both cost.  In bf16 the queues' kernel also has a workgroup more per CU (prefill_bf16_kernel).
 // Tiles here are those that dense heads would have, and a tile of d = 64 counts half.  Pieces / queues, the whole call, us, d = 128:
@@ -336,18 +339,19 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // all new, 417 / 487).  fp32, whose kernel is the same for both: 524288.
 // ---------------------------------------------------------------------------------------------
 constexpr int64_t PIECES_TILES = 262144, PIECES_TILES_F32 = 524288;
-constexpr int CUT_TILES = 2;                               // fewest tiles on either side of a cut (a part costs its result written and read: the time of two)
-__host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : base + 8; }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
+// fewest tiles on either side of a cut (a part costs its result written and read: the time of two bf16 tiles; one of fp32 takes four times as long)
+__host__ __device__ __forceinline__ int cut_tiles(uint32_t base) { return base == 32 ? 2 : 1; }
+__host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : WORK_COLS; }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
 
 struct Cut { int item, tile; };                            // a piece begins at this tile of this item
 // The cut `u` into an item of n1 contiguous and n2 packed tiles.
 __host__ __device__ __forceinline__ Cut cut_item(uint32_t base, uint32_t u, int item, int n1, int n2) {
     const int tiles = n1 + n2;
     int t = 0;
-    if (u >= base + CUT_TILES * WORK_TILE) {
+    if (u >= base + cut_tiles(base) * WORK_TILE) {
         const uint32_t v = u - base;
         t = v < n1 * WORK_TILE ? (int)(v / WORK_TILE) : n1 + (int)((v - n1 * WORK_TILE) / WORK_COLS);
-        if (t + CUT_TILES > tiles) t = tiles;
+        if (t + cut_tiles(base) > tiles) t = tiles;
     }
     return t > 0 && t >= tiles ? Cut{item + 1, 0} : Cut{item, t};
 }
@@ -358,8 +362,9 @@ __host__ __device__ __forceinline__ int part_slots(int64_t items, int pieces) { 
 __host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work, int64_t items, uint32_t most) {
     uint32_t pieces = work / piece_work(base), least = items < most ? (uint32_t)items : most;
     pieces = pieces > most ? most : pieces < least ? least : pieces;
-    // (at least two tiles a piece: no two cuts fall into one tile)
-    return pieces <= work / (2 * WORK_TILE) ? (int)pieces : work >= 2 * WORK_TILE ? (int)(work / (2 * WORK_TILE)) : 1;
+    // (more than the longer kind of tile a piece: no two cuts fall into one tile)
+    const uint32_t fewest = base == 32 ? 2 * WORK_TILE : WORK_COLS;
+    return pieces <= work / fewest ? (int)pieces : work >= fewest ? (int)(work / fewest) : 1;
 }
 // where piece p begins
 //
@@ -1041,6 +1046,9 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     const int posw = (int)blockpos + 32 * wv;              // the wave's first row
     const bool row_ok = (pos >= row0) && (pos < n);
     const bool rows_here = posw < n && posw + 31 >= row0;
+    const int64_t jb = blockpos / BN;                      // even
+    const int kb_hi = (int)(posmax / BN);
+    const uint8_t tab0 = tab[jb - (tid <= kb_hi ? tid : kb_hi) + 1];     // (with the queries: the list below waits for it)
     Frag<T> qf[C::KSTEPS];
     if (row_ok) {
         const T* qrow = Qg + (pos - row0) * D;
@@ -1053,12 +1061,10 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
     __syncthreads();
 
     // ---- ordered list of the key blocks phase 1 visits
-    const int64_t jb = blockpos / BN;                      // even
-    const int kb_hi = (int)(posmax / BN);
     int n1 = 0;
     for (int base = 0; base <= kb_hi; base += PREFILL_THREADS) {
         const int kb = base + tid;
-        const bool act = kb <= kb_hi && (tab[jb - kb + 1] & 1);
+        const bool act = kb <= kb_hi && ((base == 0 ? tab0 : tab[jb - kb + 1]) & 1);
         const uint64_t bal = __ballot(act);
         if (lane == 0) wcnt[wv] = __popcll(bal);
         __syncthreads();

@@ -72,3 +72,30 @@ def test_either_side_of_the_line(B, Hq, Hkv, n, n_hat, d):
         some = torch.isfinite(plse)
         assert torch.equal(torch.isfinite(lse[b]), some)
         assert (lse[b][some] - plse[some]).abs().max().item() <= 1e-4
+
+
+@pytest.mark.parametrize("Hq,Hkv,n,n_hat,d", [(1, 1, 64, 64, 64), (4, 1, 1024, 256, 64), (2, 1, 1000, 5, 128), (8, 8, 777, 300, 64), (16, 4, 2050, 131, 64)])
+def test_fp32_single_tiles(oracle, Hq, Hkv, n, n_hat, d):
+    """fp32 pieces of one tile: items of none, one and many tiles of either kind, cut after any of them."""
+    print(f"fp32 single tiles Hq={Hq} n={n} n_hat={n_hat} d={d}", flush=True)
+    rng = np.random.default_rng(n)
+    v_idx, s_idx = np.zeros((1, Hq, n), np.int32), np.zeros((1, Hq, n), np.int32)
+    v_cnt, s_cnt = np.zeros((1, Hq), np.int32), np.zeros((1, Hq), np.int32)
+    for h in range(Hq):
+        kind = (h + n) % 4                                 # some of both, columns only, one diagonal, all
+        c = np.flatnonzero(rng.random(n) < (0.3 if kind < 2 else 0.0))
+        s = np.arange(n) if kind == 3 else np.zeros(0, int) if kind == 1 else np.array([n // 2]) if kind == 2 else np.flatnonzero(rng.random(n) < 0.02)
+        v_idx[0, h, :len(c)] = c; v_cnt[0, h] = len(c)
+        s_idx[0, h, :len(s)] = s; s_cnt[0, h] = len(s)
+    q, k, v = inputs.make_plain(1, Hq, Hkv, n, n_hat, d, dtype="f32", seed=n, q_scale=1.5)
+    ref, rlse = oracle.attend(q, k, v, v_idx, v_cnt, s_idx, s_cnt, mode=0)
+    pipe = Pipeline(q, k, v, 1, "f32")
+    out, lse = pipe.prefill(dev_lists(v_idx, v_cnt, s_idx, s_cnt), sentinel=True)
+    assert pipe.ctx.ls_poll_status() == 0
+    o, l = out.cpu().numpy().reshape(ref.shape), lse.cpu().numpy().reshape(rlse.shape)
+    assert not np.isnan(o).any() and not np.isnan(l).any()
+    # sums of up to n products of fp32, exp2 of the hardware (2^-22): a few of those, times the largest value
+    assert np.abs(o - ref).max() <= 64 * 2.0 ** -23 * np.abs(v).max()
+    alive = np.isfinite(rlse)
+    np.testing.assert_array_equal(np.isfinite(l), alive)
+    assert np.abs(l[alive] - rlse[alive]).max() <= 1e-4
