@@ -371,7 +371,7 @@ namespace {
 // reads the work queues back finds them where the call put them).
 struct PrefillCarve {
     uint32_t* obits; uint32_t* upto; uint32_t* head_work; uint16_t* elist; uint8_t* tab; int32_t* misc;
-    uint32_t* rec; uint4* queue; uint2* split; int2* cuts; float* part_o; float* part_ml;
+    uint32_t* rec; uint32_t* arrived; uint4* queue; uint2* split; int2* cuts; float* part_o; float* part_ml;
     bool pieces;
     int nqb, grid, slots; int64_t pos0; int code;
 };
@@ -403,6 +403,7 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
         w.queue = bp.take<uint4>(items + slots);
         w.rec = w.pieces ? reinterpret_cast<uint32_t*>(w.queue) : per_item;
         w.upto = w.pieces ? per_item : nullptr;
+        w.arrived = w.pieces && ls::prefill_joins(s->dtype, (int64_t)items, w.grid) ? w.rec + items : nullptr;    // (the queues' entries would have four words an item)
         w.cuts = w.pieces ? bp.take<int2>((size_t)w.grid + 1) : nullptr;
         w.split = slots && !w.pieces ? bp.take<uint2>((size_t)slots) : nullptr;
         w.part_o = slots ? bp.take<float>((size_t)slots * 128 * s->d) : nullptr;
@@ -454,7 +455,7 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
     ls::PlanArgs p{};
     p.n = s->n; p.words = words; p.tab_len = tab_len; p.v_idx = v_idx; p.v_cnt = v_cnt; p.s_idx = s_idx; p.s_cnt = s_cnt;
     p.cap_v = cap_v; p.cap_s = cap_s; p.obits = w.obits; p.tab = w.tab; p.nqb = nqb; p.pos0 = pos0; p.dtype = s->dtype;
-    p.elist = w.elist; p.rec = w.rec; p.upto = w.upto; p.head_work = w.head_work; p.split_count = w.misc + 24; p.status = c->status;
+    p.elist = w.elist; p.rec = w.rec; p.upto = w.upto; p.arrived = w.arrived; p.head_work = w.head_work; p.split_count = w.misc + 24; p.status = c->status;
     hipError_t e = ls::launch_plan(p, BH, static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail(c, LS_EHIP, "ls_sparse_prefill(plan): %s", hipGetErrorString(e));
     if (!w.pieces) {
@@ -470,7 +471,7 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
     a.elist = w.elist; a.rec = w.rec; a.upto = w.upto; a.head_work = w.head_work;
     a.queue = w.pieces ? nullptr : w.queue; a.qlen = w.misc; a.qhead = w.misc + 8; a.qbase = w.misc + 16;
     a.split = w.split; a.split_count = w.misc + 24;
-    a.grid = w.grid; a.slots = w.slots; a.cuts = w.cuts; a.part_o = w.part_o; a.part_ml = w.part_ml;
+    a.grid = w.grid; a.slots = w.slots; a.cuts = w.cuts; a.arrived = w.arrived; a.part_o = w.part_o; a.part_ml = w.part_ml;
     a.pos0 = pos0;
     a.Hq = s->Hq; a.Hkv = s->Hkv; a.G = s->Hq / s->Hkv; a.BH = BH;
     a.nqb = nqb; a.dtype = s->dtype;
@@ -479,7 +480,7 @@ int ls_sparse_prefill(ls_ctx* c, const ls_shape* s, const void* q, const void* k
     std::array<hipEvent_t, 4> ev{};
     if (c->profile) {
         try { c->events.reserve(c->events.size() + 1); } catch (...) { return fail(c, LS_EHIP, "ls_sparse_prefill: out of memory for events"); }
-        for (size_t i = 0; i < (w.slots > 0 ? 4u : 2u); ++i)
+        for (size_t i = 0; i < (w.slots > 0 && !a.arrived ? 4u : 2u); ++i)
             if (hipEventCreate(&ev[i]) != hipSuccess) {
                 for (size_t j = 0; j < i; ++j) (void)hipEventDestroy(ev[j]);
                 return fail(c, LS_EHIP, "ls_sparse_prefill: hipEventCreate failed");
@@ -694,6 +695,8 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
         // an item belongs to the piece on which it begins
         for (int p = 0; p < pieces; ++p) {
             const int x = ls::prefill_piece_xcd(p, pieces);
+            cuts[1 + p].y &= (int)~ls::CUT_ON;
+            if (p + 2 <= pieces) cuts[2 + p].y &= (int)~ls::CUT_ON;
             *cuts_out += cuts[1 + p].y > 0 ? 1 : 0;
             const int2 from = cuts[1 + p], to = p + 1 < pieces ? cuts[2 + p] : make_int2((int)items, 0);
             for (int64_t i = from.x + (from.y > 0 ? 1 : 0); i < to.x + (to.y > 0 ? 1 : 0); ++i)

@@ -63,6 +63,8 @@ struct TopbArgs {
     uint32_t *hist, *state, *cnt;
 };
 
+constexpr uint32_t CUT_ON = 1u << 30;     // in a cut's tile word: the piece ends inside the item in which it begins
+
 struct PlanArgs {
     int64_t n;
     int words, tab_len;
@@ -76,6 +78,7 @@ struct PlanArgs {
     uint16_t* elist;          // [BH][tab_len + 1] the table entries with a selected diagonal, ascending
     uint32_t* rec;            // [BH][nqb] of each row block: key blocks it visits | columns it gathers << 13
     uint32_t* upto;           // [BH][nqb] work of the head's row blocks up to and including this one (null: not wanted)
+    uint32_t* arrived;        // [BH][nqb] cleared here for the parts of items (wanted with `upto`)
     uint32_t* head_work;      // [BH] work of all of them
     int32_t* split_count;     // [2] cleared here for sched_kernel
     int32_t* status;          // device status word of the context (bits LS_STAT_*), OR-ed into
@@ -113,7 +116,8 @@ struct PrefillArgs {
     // pieces (ls_prefill.hip): at most `grid`
     const uint32_t* rec;
     const uint32_t *upto, *head_work;
-    int2* cuts;               // [1 + pieces] their number, and where each piece begins {item, tile}
+    int2* cuts;               // [1 + pieces] their number, and where each piece begins {item, tile | CUT_ON (that flag with `arrived` only)}
+    uint32_t* arrived;        // [BH][nqb] tiles of the item's parts that are done, cleared by plan_kernel; null: combine_kernel puts the parts together
     // or work queues built by sched_kernel
     const uint4* queue;       // null: pieces
     const int32_t *qlen, *qbase;
@@ -194,6 +198,7 @@ int prefill_grid(int dtype, int d, int64_t items, bool pieces);
 int prefill_split_slots(int64_t items, int grid, bool pieces);      // parts' results that a call with so many (head, row block) items may use
 size_t prefill_slot_bytes(int d);
 int prefill_pieces_for(int64_t items, int grid, int slots);              // workgroups of a call in pieces with room for so many parts' results (0: queues)
+bool prefill_joins(int dtype, int64_t items, int grid);               // pieces: whether the attention kernel puts the parts together itself
 int prefill_piece_xcd(int p, int pieces);                                // XCD whose workgroup takes piece p
 
 }  // namespace ls

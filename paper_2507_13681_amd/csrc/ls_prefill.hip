@@ -301,6 +301,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
             pre += item_work(base, r.x, (r.y + BN - 1) / BN);
             a.rec[(int64_t)bh * a.nqb + q] = pack_item(r.x, r.y);
             if (a.upto) a.upto[(int64_t)bh * a.nqb + q] = pre;
+            if (a.arrived) a.arrived[(int64_t)bh * a.nqb + q] = 0u;
         }
         if (tid == 0) a.head_work[bh] = all;
     }
@@ -319,7 +320,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // as there are workgroups.  Every workgroup finds its own piece from the running sums that plan_kernel left behind: a scan over
 // the heads, a look through one head's row blocks.  Neighbouring pieces go to the same XCD, so that the query heads that
 // share K and V meet in one L2.  An item that a cut goes through is done in parts, whose unnormalised results go to slots of the
-// workspace and which combine_kernel puts together; a cut that would leave a few tiles on one side is moved to the
+// workspace and which combine_kernel puts together (join_parts, where there are many items); a cut that would leave a few tiles on one side is moved to the
 // end of the item.  A workspace that does not hold all parts gets fewer pieces, or queues (prefill_pieces_for).
 //
 // Against the work queues of sched_kernel (which serve what is larger) this saves a launch of one workgroup per XCD, a look at the
@@ -461,8 +462,9 @@ __device__ __forceinline__ Span my_span(const PrefillArgs& a, uint32_t* sh) {   
     s.from = find(ub, cb, u0, c0, hb, rb, &rec);
     if (more) s.to = find(ue, ce, u1, c1, he, re, nullptr);
     s.rec = rec != 0xFFFFFFFFu || s.from.item >= items ? rec : a.rec[s.from.item];      // (a cut moved to the next item: its record)
-    if (tid == 0) {                                        // for combine_kernel
-        a.cuts[1 + s.piece] = make_int2(s.from.item, s.from.tile);
+    if (tid == 0) {                                        // for whoever puts the parts together
+        if (!a.arrived) a.cuts[1 + s.piece] = make_int2(s.from.item, s.from.tile);
+        else put_shared_word(reinterpret_cast<uint64_t*>(a.cuts + 1 + s.piece), (uint32_t)s.from.item, (uint32_t)s.from.tile | (s.to.item == s.from.item && s.to.tile > 0 ? CUT_ON : 0u));
         if (s.piece == 0) a.cuts[0] = make_int2(s.pieces, 0);
     }
     return s;
@@ -664,6 +666,7 @@ int prefill_pieces_for(int64_t items, int grid, int slots) {
     if (grid > 512 && pieces >= 512) return items <= 5 * (int64_t)grid ? 512 : 0;
     return pieces > 1 && 4 * items * (grid - pieces) <= grid * pieces ? (int)pieces : 0;
 }
+bool prefill_joins(int dtype, int64_t items, int grid) { return dtype == 0 && items >= 2 * (int64_t)grid; }
 int prefill_piece_xcd(int p, int pieces) {
     for (int id = 0; id < 8; ++id)
         for (int j = id; piece_of(j, pieces) >= 0; j += 8) if (piece_of(j, pieces) == p) return id;
@@ -733,6 +736,7 @@ struct Entry {
 template <bool QUEUES> struct Entries;
 template <> struct Entries<true> {
     QueueSource src;
+    __device__ __forceinline__ Span span() const { return Span{}; }
     __device__ __forceinline__ void init(const PrefillArgs& a, int lane) { src.init(a, lane); }
     __device__ __forceinline__ void ahead(const PrefillArgs& a, int lane, int wv) { if (wv == 0) src.ahead(a, lane); }
     __device__ __forceinline__ bool next(const PrefillArgs& a, int lane, int wv, Entry& e) {
@@ -752,6 +756,7 @@ template <> struct Entries<false> {
     Span s;
     int at, last;
     uint32_t rec;                             // of item `at`
+    __device__ __forceinline__ const Span& span() const { return s; }
     __device__ __forceinline__ void init(const PrefillArgs& a, int lane) {
         __shared__ uint32_t span_s[8];
         s = my_span(a, span_s);
@@ -769,6 +774,9 @@ template <> struct Entries<false> {
     }
 };
 
+// Word of a.cuts: the tile at which a piece begins, and whether the piece ends inside the same item
+__device__ __forceinline__ int cut_tile(int y) { return y & (int)~CUT_ON; }
+
 // Unnormalised result of one part of a split item: accumulators lane by lane (16 bytes a lane, 1 KB a store) and
 // {reference, normaliser} per row.
 template <int DBLK>
@@ -780,6 +788,106 @@ __device__ __forceinline__ void store_part(const PrefillArgs& a, int slot, int w
         for (int rq = 0; rq < 4; ++rq)
             *reinterpret_cast<f32x4*>(o + (i * 4 + rq) * 256) = f32x4{oacc[i][4 * rq], oacc[i][4 * rq + 1], oacc[i][4 * rq + 2], oacc[i][4 * rq + 3]};
     if (lane < 32) reinterpret_cast<float2*>(a.part_ml)[(int64_t)slot * BM + 32 * wv + lane] = make_float2(m, l);
+}
+
+// Pieces, where there are at least two items to a workgroup: an item's parts are put together by the workgroup that comes to the end of its part last
+// (the count of the item's tiles that are done tells; plan_kernel has cleared it).  Where all others are there, its own part is not stored at all:
+// mostly the one at the end of a piece, since the next piece began with the other.  The parts are added in the order of their tiles,
+// so the result does not depend on who comes last, and nobody waits for anybody.  All threads of the workgroup call; returns whether oacc, m and l are
+// the item's now.
+//
+// Against combine_kernel this saves a launch and a write and a read of half of the parts: the attention of 8192 rows, all new, 32 heads of 128 266 -> 257 us,
+// of 64 216 -> 211, B 1, 64 heads, 2000 of 3000 rows 121 -> 114; one head dense and 100 diagonals of the others 114 -> 112, 82 -> 83, 65 -> 63.  What bounds it is what a
+// compute unit alone can read, 30 to 50 KB a us, part after part.  So not where an item has many parts (with combine_kernel / so,
+// us: 16 heads of 64, 1024 rows of 8192 47 / 57, 20 of 40000 66 / 112), nor where one dense head among others gives a few items many (16 heads of 64, 8192 of 20000 rows,
+// 1.3 items a workgroup 90 / 97).
+template <int DBLK, int NB>
+__device__ __forceinline__ bool join_parts(const PrefillArgs& a, const Entry& en, const Span& s, int total, int here, int wv, int lane, bool rows_here, f32x16 (&oacc)[DBLK], float& m, float& l) {
+    __shared__ uint32_t count_s;
+    uint32_t* count = a.arrived + en.item;
+    if (threadIdx.x == 0) count_s = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    bool last = __builtin_amdgcn_readfirstlane((int)count_s) + here == total;
+    __syncthreads();
+    const int64_t at = wv * (DBLK * 16 * 64) + 2 * lane;   // two values of a lane at a time, 512 bytes a store
+    const int piece = s.piece, pieces = s.pieces;
+    if (!last) {
+        if (rows_here) {
+            float* o = a.part_o + (int64_t)en.slot() * (BM * 32 * DBLK) + at;
+#pragma unroll
+            for (int i = 0; i < DBLK; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; r += 2) put_shared2(o + (16 * i + r) * 64, oacc[i][r], oacc[i][r + 1]);
+            if (lane < 32) put_shared2(a.part_ml + 2 * ((int64_t)en.slot() * BM + 32 * wv + lane), m, l);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (threadIdx.x == 0) count_s = __hip_atomic_fetch_add(count, (uint32_t)here, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        last = __builtin_amdgcn_readfirstlane((int)count_s) + here == total;
+    }
+    if (!last) return false;
+    if (!rows_here) return true;
+    // the item's pieces: from the one that does not begin inside it to the one that does not end inside it
+    auto cut = [&](int p) -> int2 {
+        const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(a.cuts + 1 + p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return make_int2(__builtin_amdgcn_readfirstlane((int)(uint32_t)u), __builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32)));
+    };
+    int first = piece, end = piece;
+    if (en.lo > 0)
+        for (;;) { --first; const int2 c = cut(first); if (c.x != en.item || cut_tile(c.y) == 0) break; }
+    if (en.hi >= 0)
+        for (;;) { ++end; if (!(cut(end).y & (int)CUT_ON)) break; }
+    auto slot_of = [&](int p) -> int64_t { return p == first ? begin_slot(en.item, first, (int64_t)a.BH * a.nqb, pieces) : p - 1; };
+    const int row = 32 * wv + (lane & 31);
+    f32x16 acc[DBLK];
+#pragma unroll
+    for (int i = 0; i < DBLK; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][r] = 0.f;
+    float M = -INFINITY, L = 0.f;
+    for (int p0 = first; p0 <= end; p0 += NB) {            // so many parts' loads in flight (the last part is repeated with weight 0)
+        float2 ml[NB], x[NB][DBLK * 8];
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            const int p = p0 + e < end ? p0 + e : end;
+            const float* o = a.part_o + slot_of(p) * (BM * 32 * DBLK) + at;
+            ml[e] = get_shared2(a.part_ml + 2 * (slot_of(p) * BM + row));
+#pragma unroll
+            for (int k = 0; k < DBLK * 8; ++k) x[e][k] = get_shared2(o + k * 128);
+        }
+        float m_new = M;
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            if (p0 + e == piece) {                         // (uniform; what is read of its slot may be anything)
+                ml[e] = make_float2(m, l);
+#pragma unroll
+                for (int k = 0; k < DBLK * 8; ++k) x[e][k] = make_float2(oacc[k / 8][2 * (k % 8)], oacc[k / 8][2 * (k % 8) + 1]);
+            }
+            if (p0 + e > end) ml[e].x = -INFINITY;
+            m_new = fmaxf(m_new, ml[e].x);
+        }
+        const float corr = M > -INFINITY ? fast_exp2(M - m_new) : 0.f;
+        M = m_new;
+        L *= corr;
+#pragma unroll
+        for (int i = 0; i < DBLK; ++i) acc[i] *= corr;
+#pragma unroll
+        for (int e = 0; e < NB; ++e) {
+            if (p0 + e > end) break;
+            const float wgt = ml[e].x > -INFINITY ? fast_exp2(ml[e].x - M) : 0.f;
+            L += ml[e].y * wgt;
+#pragma unroll
+            for (int k = 0; k < DBLK * 8; ++k) {
+                acc[k / 8][2 * (k % 8)] += x[e][k].x * wgt;
+                acc[k / 8][2 * (k % 8) + 1] += x[e][k].y * wgt;
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < DBLK; ++i) oacc[i] = acc[i];
+    m = M; l = L;
+    return true;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1852,13 +1960,16 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2) + (QUEUES ? 1 : 
         }
     }
 
-    const float l_tot = sum32(l_run);
-    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    float l_tot = sum32(l_run), m_tot = -mneg;
     entries.ahead(a, lane, wv);                            // the next entry's place in the queue, under the stores below
     const int ln = again(lane), rl = ln & 31, gl = ln >> 5;
-    if (en.in_parts(n1 + n2)) {
-        store_part<C::DBLK>(a, en.slot(), wv, ln, oacc, -mneg, l_tot);
-    } else if (rows_here) {
+    bool whole = !en.in_parts(n1 + n2);
+    if (!whole) {
+        if (!QUEUES && __builtin_expect(a.arrived != nullptr, 0)) whole = join_parts<C::DBLK, (D == 64 ? 2 : 1)>(a, en, entries.span(), n1 + n2, ntiles - tbeg, wv, ln, rows_here, oacc, m_tot, l_tot);
+        else store_part<C::DBLK>(a, en.slot(), wv, ln, oacc, m_tot, l_tot);
+    }
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    if (whole && rows_here) {
         // A lane holds four neighbouring values of its row at a time; through LDS (32 rows of this wave in the tile
         // buffers, which nobody reads any more) they become whole rows, 1 KB a store.  (Stored as they are, 8 bytes a
         // lane in 32 rows, they kept a wave for 4.5-7 thousand cycles an entry.)
@@ -1881,7 +1992,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2) + (QUEUES ? 1 : 
         }
         if (a.lse && gl == 0 && posw + rl >= row0 && posw + rl < n)
             a.lse[(int64_t)bh * a.n_hat + (posw + rl - row0)] =
-                l_tot > 0.f ? (log2f(l_tot) - mneg) * 0.69314718055994531f : -INFINITY;
+                l_tot > 0.f ? (log2f(l_tot) + m_tot) * 0.69314718055994531f : -INFINITY;
     }
     }                                                      // next entry
 }
@@ -1912,7 +2023,7 @@ static hipError_t launch_prefill_t(const PrefillArgs& a, hipStream_t st, const h
         if (ev) hipExtLaunchKernelGGL((prefill_bf16_kernel<D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), (uint32_t)smem, st, ev[0], ev[1], 0, a);
         else hipLaunchKernelGGL((prefill_bf16_kernel<D, QUEUES>), dim3(a.grid), dim3(PREFILL_THREADS), smem, st, a);
     }
-    launch_combine<T, D, QUEUES>(a, st, ev);
+    if (!a.arrived) launch_combine<T, D, QUEUES>(a, st, ev);
     return hipGetLastError();
 }
 template <typename T, int D>

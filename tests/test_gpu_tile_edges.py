@@ -99,3 +99,38 @@ def test_fp32_single_tiles(oracle, Hq, Hkv, n, n_hat, d):
     alive = np.isfinite(rlse)
     np.testing.assert_array_equal(np.isfinite(l), alive)
     assert np.abs(l[alive] - rlse[alive]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("Hq,Hkv,n,n_hat,d", [(64, 8, 2048, 2048, 128), (64, 64, 2500, 2101, 128), (64, 16, 3072, 3072, 64), (64, 8, 5003, 3050, 64)])
+def test_parts_joined_by_the_last(Hq, Hkv, n, n_hat, d):
+    """At least two items to a workgroup, heads of very unlike work (items of one part and of many, row blocks with few rows): against a call per
+    16 heads, whose parts are put together by a kernel of its own, and against itself, whoever came last."""
+    print(f"parts joined Hq={Hq} n={n} n_hat={n_hat} d={d}", flush=True)
+    items = lambda heads: heads * ((n - (n - n_hat) // 128 * 128 + 127) // 128)
+    grid = 512 if d == 128 else 768
+    assert items(Hq) >= 2 * grid > 2 * items(16)
+    rng = np.random.default_rng(n)
+    v_idx, s_idx = np.zeros((1, Hq, n), np.int32), np.zeros((1, Hq, n), np.int32)
+    v_cnt, s_cnt = np.zeros((1, Hq), np.int32), np.zeros((1, Hq), np.int32)
+    for h in range(Hq):
+        c = np.flatnonzero(rng.random(n) < (0.1, 0.0, 0.01, 0.5)[h % 4])
+        s = np.arange(n) if h % 16 == 5 else np.zeros(0, int) if h % 4 == 3 else np.flatnonzero(rng.random(n) < 0.01)
+        v_idx[0, h, :len(c)] = c; v_cnt[0, h] = len(c)
+        s_idx[0, h, :len(s)] = s; s_cnt[0, h] = len(s)
+    q, k, v = inputs.make_plain(1, Hq, Hkv, n, n_hat, d, dtype="bf16", seed=n, q_scale=1.5)
+    whole = Pipeline(q, k, v, 1, "bf16")
+    out, lse = whole.prefill(dev_lists(v_idx, v_cnt, s_idx, s_cnt), sentinel=True)
+    assert whole.ctx.debug_prefill_queues(whole.shape)[2] > 0
+    for _ in range(4):
+        again, lagain = whole.prefill(dev_lists(v_idx, v_cnt, s_idx, s_cnt), sentinel=True)
+        assert torch.equal(again, out) and torch.equal(lagain, lse)
+    assert whole.ctx.ls_poll_status() == 0
+    tol = 4 * 2.0 ** -9 * float(np.abs(v).max())           # each side rounds every probability (2^-9 relative) and the result
+    for h0 in range(0, Hq, 16):
+        h, g = slice(h0, h0 + 16), slice(h0 * Hkv // Hq, max(h0 * Hkv // Hq + 1, (h0 + 16) * Hkv // Hq))
+        part, plse = Pipeline(q[:, h], k[:, g], v[:, g], 1, "bf16").prefill(dev_lists(v_idx[:, h], v_cnt[:, h], s_idx[:, h], s_cnt[:, h]), sentinel=True)
+        assert not torch.isnan(out[:, h]).any() and not torch.isnan(part).any()
+        assert (out[:, h].float() - part.float()).abs().max().item() <= tol
+        some = torch.isfinite(plse)
+        assert torch.equal(torch.isfinite(lse[:, h]), some)
+        assert (lse[:, h][some] - plse[some]).abs().max().item() <= 1e-4
