@@ -803,16 +803,46 @@ template <int E> constexpr size_t WALK_LDS_BYTES = 2 * sizeof(WalkList<E>) + WAL
 __device__ __forceinline__ int walk_ld(const int* p) { return __builtin_amdgcn_readfirstlane(__atomic_load_n(p, __ATOMIC_RELAXED)); }
 __device__ __forceinline__ void walk_st(int* p, int v) { __atomic_store_n(p, v, __ATOMIC_RELAXED); }
 
+// The lines of a bitmap of up to 1024 words, ascending: line0 + bit goes to out[at + how many are before it] while that is below `cap`.  NT
+// threads from t = 0 on call, whole waves, of which wave wv0 is the first (of a workgroup whose other threads do the same for another map of as many
+// words); returns the number of lines.  stage: 32 * words numbers of LDS.  wsum: a word for each wave, not in use.
+//
+// A thread takes a word, several, or down to a quarter of one, whichever gives all of them something to do, and puts its lines into LDS: they go out
+// in whole lines of memory.  (Straight from the words each store instruction met up to 64 lines of memory: emit_kernel, 32 heads of 32768 lines
+// 9.5 -> 6.9 us, 12347 5.6 -> 4.6; merge_lines_kernel, 16 heads of 5003 lines, 10.5 -> 8.2; the walk of 1024 lines, which does it itself, 11.2 -> 9.3.)
+template <int NT>
+__device__ __forceinline__ uint32_t put_lines(const uint32_t* bm, int words, int line0, uint16_t* stage, uint32_t* wsum, int wv0, int32_t* out, uint32_t at, int cap, int t) {
+    const int lane = t & 63, wv = wv0 + __builtin_amdgcn_readfirstlane(t >> 6);
+    const int sh = 4 * words <= NT ? 2 : 2 * words <= NT ? 1 : 0, units = words << sh, bits = 32 >> sh;
+    const int per = (units + NT - 1) / NT, u0 = t * per < units ? t * per : units, u1 = u0 + per < units ? u0 + per : units;
+    auto unit = [&](int u) -> uint32_t { const uint32_t w = bm[u >> sh]; return sh == 0 ? w : (w >> ((u & ((1 << sh) - 1)) * bits)) & ((1u << bits) - 1u); };
+    uint32_t mine = 0u;
+    for (int u = u0; u < u1; ++u) mine += (uint32_t)__popc(unit(u));
+    const uint32_t upto = lanes_upto(mine);
+    if (lane == 63) wsum[wv] = upto;
+    __syncthreads();
+    uint32_t p = upto - mine, all = 0u;
+    for (int w = 0; w < NT / 64; ++w) { const uint32_t x = wsum[wv0 + w]; p += wv0 + w < wv ? x : 0u; all += x; }
+    for (int u = u0; u < u1; ++u)
+        for (uint32_t m = unit(u); m; m &= m - 1u) stage[p++] = (uint16_t)(u * bits + __ffs(m) - 1);
+    __syncthreads();
+    const uint32_t room = at < (uint32_t)cap ? (uint32_t)cap - at : 0u, go = all < room ? all : room;
+    for (uint32_t i = (uint32_t)t; i < go; i += NT) out[at + i] = line0 + (int32_t)stage[i];
+    return all;
+}
+constexpr int PUT_WORDS = 1024;
+constexpr size_t put_lines_bytes(int64_t n) { return (size_t)(n < 32 * PUT_WORDS ? (n + 31) / 32 * 32 : 32 * PUT_WORDS) * 2; }
+
 // Chosen prefixes -> ascending index lists of both lists of a head, by the workgroup that has walked them (half of its NT
-// threads a list).  bm: 2 * ceil(n / 32) words of LDS.  Up to EMIT_LINES lines; beyond, the 192 threads a list take longer than
-// emit_kernel's 1024 and its launch.  ls_select, 32 heads, launch / here, us: 1024 lines 24.9 / 22.1, 4096 28.9 / 27.8, 8192 38.0 /
-// 38.3, 12288 50.6 / 50.3, 16384 55.1 / 57.1, 32768 84.0 / 93.5; with exact overlaps 1024 86.2 / 84.8, 8192 93.4 / 93.2.
-constexpr int64_t EMIT_LINES = 8192;
+// threads a list).  bm: 2 * ceil(n / 32) words of LDS and 2 * put_lines_bytes(n) behind them.  Up to EMIT_LINES lines; beyond, the 192 threads a list
+// take longer than emit_kernel's 1024 and its launch.  ls_select, 32 heads, launch / here, us: 1024 lines 17.1 / 16.1, 4096 24.7 / 24.7, 8192
+// 33.5 / 34.8, 12288 39.4 / 41.2, 16384 42.1 / 45.0; 256 heads of 1500 27.0 / 24.7; with exact overlaps 1024 69.8 / 69.3, 8192 80.2 / 81.5.
+constexpr int64_t EMIT_LINES = 4096;
 template <int NT>
 __device__ __forceinline__ void emit_both(const SelectArgs& a, int bh, int cnt_s, int cnt_v, uint32_t* bm) {
     __shared__ uint32_t wsum[NT / 64];
     constexpr int H = NT / 2;
-    const int tid = threadIdx.x, list = tid >= H ? 1 : 0, t = tid - list * H, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, list = tid >= H ? 1 : 0, t = tid - list * H;
     const int n = (int)a.n, words = (n + 31) / 32, cnt = list == 0 ? cnt_s : cnt_v, cap = list == 0 ? a.cap_s : a.cap_v;
     const int32_t* sorted_idx = a.sidx + ((int64_t)list * a.BH + bh) * n;
     int32_t* out = list == 0 ? a.s_idx + (int64_t)bh * cap : a.v_idx + (int64_t)bh * cap;
@@ -829,22 +859,7 @@ __device__ __forceinline__ void emit_both(const SelectArgs& a, int bh, int cnt_s
             for (int j = 0; j < 8; ++j) atomicOr(&bm[x8[j] >> 5], 1u << (x8[j] & 31));
         }
     __syncthreads();
-    const int per = (words + H - 1) / H, w0 = t * per < words ? t * per : words, w1 = w0 + per < words ? w0 + per : words;
-    uint32_t mine = 0u;
-    for (int w = w0; w < w1; ++w) mine += (uint32_t)__popc(bm[w]);
-    const uint32_t upto = lanes_upto(mine);
-    if (lane == 63) wsum[wv] = upto;
-    __syncthreads();
-    uint32_t at = upto - mine;
-    for (int w = list * (H / 64); w < wv; ++w) at += wsum[w];
-    for (int w = w0; w < w1; ++w) {
-        uint32_t m = bm[w];
-        while (m) {
-            if (at < (uint32_t)cap) out[at] = 32 * w + __ffs(m) - 1;
-            m &= m - 1u;
-            ++at;
-        }
-    }
+    put_lines<H>(bm, words, 0, reinterpret_cast<uint16_t*>(bm + (2 - list) * words) + list * 32 * words, wsum, list * (H / 64), out, 0u, cap, t);
 }
 
 // ix[e] = the line at sorted position pos + e (the last line's index past the end of the list)
@@ -1243,7 +1258,7 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
     if (a.n > EMIT_LINES) return;
     emit_both<WALK_THREADS>(a, bh, cnt_s, cnt_v, reinterpret_cast<uint32_t*>(walk_lds));      // (not where `sync` lies)
 }
-static_assert(2 * sizeof(WalkList<4>) > EMIT_LINES / 4, "the bitmaps lie ahead of the rings");
+static_assert(2 * sizeof(WalkList<4>) > EMIT_LINES / 4 + 4 * EMIT_LINES, "the bitmaps and their lines lie ahead of the rings");
 
 // ---- Alg. 2 with the overlap of a candidate counted cell by cell ----------------------------------
 // The loop of Alg. 2 compares the marginal contributions of the two list heads (Sec. 5.1); the listing bounds the
@@ -1502,12 +1517,11 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
 }
 
 // ---- chosen prefix -> ascending index list --------------------------------------------------------
-// grid (2, BH); dynamic LDS: bitmap of n bits + per-wave word counts.
+// grid (2, BH); dynamic LDS: bitmap of n bits, lines of up to 1024 of its words.
 __global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
     extern __shared__ uint32_t bm[];
     __shared__ uint32_t wsum[16];
-    __shared__ uint32_t carry;
-    const int list = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int list = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
     const int64_t n = a.n;
     const int words = (int)((n + 31) / 32);
     const int64_t seg = ((int64_t)list * a.BH + bh) * n;
@@ -1521,7 +1535,6 @@ __global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
         return;
     }
     for (int i = tid; i < words; i += 1024) bm[i] = 0u;
-    if (tid == 0) carry = 0u;
     __syncthreads();
     for (int i0 = tid; i0 < cnt; i0 += 8 * 1024) {          // eight independent loads in flight per thread
         int32_t x8[8];
@@ -1531,28 +1544,11 @@ __global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
         for (int j = 0; j < 8; ++j) if (x8[j] >= 0) atomicOr(&bm[x8[j] >> 5], 1u << (x8[j] & 31));
     }
     __syncthreads();
-    for (int w0 = 0; w0 < words; w0 += 1024) {
-        const int wd = w0 + tid;
-        const uint32_t m = wd < words ? bm[wd] : 0u;
-        const uint32_t c = __popc(m);
-        uint32_t inc = c;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) { const uint32_t t = __shfl_up(inc, off, 64); if (lane >= off) inc += t; }
-        if (lane == 63) wsum[wv] = inc;
-        __syncthreads();
-        uint32_t pre = carry;
-        for (int w = 0; w < wv; ++w) pre += wsum[w];
-        uint32_t pos = pre + inc - c;
-        uint32_t mm = m;
-        while (mm) {
-            const int bit = __ffs(mm) - 1;
-            mm &= mm - 1;
-            if (pos < (uint32_t)cap) out[pos] = wd * 32 + bit;
-            ++pos;
-        }
-        __syncthreads();
-        if (tid == 1023) carry = pre + inc;
-        __syncthreads();
+    uint16_t* stage = reinterpret_cast<uint16_t*>(bm + words);
+    uint32_t at = 0u;
+    for (int w0 = 0; w0 < words; w0 += PUT_WORDS) {
+        if (w0 > 0) __syncthreads();                       // the last lines are out of `stage`
+        at += put_lines<1024>(bm + w0, words - w0 < PUT_WORDS ? words - w0 : PUT_WORDS, 32 * w0, stage, wsum, 0, out, at, cap, tid);
     }
 }
 
@@ -1564,12 +1560,10 @@ __global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
 __global__ __launch_bounds__(1024) void merge_lines_kernel(MergeArgs a) {
     extern __shared__ uint32_t bm[];
     __shared__ uint32_t wsum[16];
-    __shared__ uint32_t carry;
-    const int list = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int list = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
     const int64_t n = a.n;
     const int words = (int)((n + 31) / 32);
     for (int i = tid; i < words; i += 1024) bm[i] = 0u;
-    if (tid == 0) carry = 0u;
     __syncthreads();
     bool dropped = false;
     for (int src = 0; src < 2; ++src) {
@@ -1586,29 +1580,9 @@ __global__ __launch_bounds__(1024) void merge_lines_kernel(MergeArgs a) {
     int32_t* out = a.idx[list] + (int64_t)bh * a.cap[list];
     const int cap = a.cap[list];
     uint32_t total = 0;
-    for (int w0 = 0; w0 < words; w0 += 1024) {
-        const int wd = w0 + tid;
-        const uint32_t m = wd < words ? bm[wd] : 0u;
-        const uint32_t c = __popc(m);
-        uint32_t inc = c;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) { const uint32_t t = __shfl_up(inc, off, 64); if (lane >= off) inc += t; }
-        if (lane == 63) wsum[wv] = inc;
-        __syncthreads();
-        uint32_t pre = carry;
-        for (int w = 0; w < wv; ++w) pre += wsum[w];
-        uint32_t pos = pre + inc - c;
-        uint32_t mm = m;
-        while (mm) {
-            const int bit = __ffs(mm) - 1;
-            mm &= mm - 1;
-            if (pos < (uint32_t)cap) out[pos] = wd * 32 + bit;
-            ++pos;
-        }
-        __syncthreads();
-        if (tid == 1023) { carry = pre + inc; }
-        __syncthreads();
-        total = carry;
+    for (int w0 = 0; w0 < words; w0 += PUT_WORDS) {
+        if (w0 > 0) __syncthreads();
+        total += put_lines<1024>(bm + w0, words - w0 < PUT_WORDS ? words - w0 : PUT_WORDS, 32 * w0, reinterpret_cast<uint16_t*>(bm + words), wsum, 0, out, total, cap, tid);
     }
     if (tid == 0) {
         a.cnt[list][bh] = (int32_t)total;
@@ -1618,7 +1592,7 @@ __global__ __launch_bounds__(1024) void merge_lines_kernel(MergeArgs a) {
 }
 
 hipError_t run_merge_lines(const MergeArgs& a, hipStream_t st) {
-    const size_t smem = (size_t)((a.n + 31) / 32) * 4;
+    const size_t smem = (size_t)((a.n + 31) / 32) * 4 + put_lines_bytes(a.n);
     hipLaunchKernelGGL(merge_lines_kernel, dim3(2, a.BH), dim3(1024), smem, st, a);
     return hipGetLastError();
 }
@@ -1951,7 +1925,7 @@ __global__ __launch_bounds__(GATHER_THREADS) void gather_rows_kernel(GatherArgs 
 }
 
 static void launch_emit(const SelectArgs& a, hipStream_t st) {
-    if (a.n > EMIT_LINES) hipLaunchKernelGGL(emit_kernel, dim3(2, a.BH), dim3(1024), (size_t)((a.n + 31) / 32) * 4, st, a);
+    if (a.n > EMIT_LINES) hipLaunchKernelGGL(emit_kernel, dim3(2, a.BH), dim3(1024), (size_t)((a.n + 31) / 32) * 4 + put_lines_bytes(a.n), st, a);
 }
 // Ranges of 8192 lines, a fifth less than a workgroup takes (the samples miss by 4 % at most; beyond 65536 lines by more, and a halved
 // range counts again), and more of them, down to 512 lines, as long as there are compute units for one each: 8 heads of 8192 lines
@@ -2005,7 +1979,7 @@ hipError_t run_select_exact(const SelectArgs& a, hipStream_t st) {
     hipError_t e = sort_lines(a, st);
     if (e != hipSuccess) return e;
     const size_t smem = (size_t)((a.n + 31) / 32) * 4;
-    hipLaunchKernelGGL(walk_exact_kernel, dim3(a.BH), dim3(XW_THREADS), 2 * smem, st, a);
+    hipLaunchKernelGGL(walk_exact_kernel, dim3(a.BH), dim3(XW_THREADS), 2 * smem + (a.n <= EMIT_LINES ? 2 * put_lines_bytes(a.n) : 0), st, a);
     launch_emit(a, st);
     return hipGetLastError();
 }

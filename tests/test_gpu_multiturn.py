@@ -127,3 +127,33 @@ def test_first_turn_at_long_context_scale(oracle):
     rows = np.union1d(sample_rows(cfg, 16, rng), block_rows(cfg, sel, rng, random_blocks=4))
     print(f"[first_turn_131k] oracle attention on {len(rows)} rows", flush=True)
     check_attention(oracle, cfg, q, k, v, sel, out, lse, rows, mode=1)
+
+
+@pytest.mark.parametrize("n", [1, 32, 33, 255, 700, 8193, 16384, 16385, 32768, 32769, 70001, 262144])
+def test_merged_lines_at_word_edges(n):
+    """A thread writes a word of the bitmap out, several or a part of one, 1024 words at a time: no lines, all, every other, the ends only, a few."""
+    print(f"merged lines n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    sets = [np.zeros(0, int), np.arange(n), np.arange(0, n, 2), np.unique([0, n - 1]), np.flatnonzero(rng.random(n) < 0.01),
+            np.flatnonzero(rng.random(n) < 0.6), np.arange(n // 3, n - n // 3), np.arange(31, n, 32)]
+    Hq = len(sets)
+    shape = binding.make_shape(1, Hq, Hq, 64, n, 1, 1, "bf16")
+    lists = lambda pick: {k: v for kind, off in (("v", 0), ("s", 3)) for k, v in zip(
+        (kind + "_idx", kind + "_cnt"), _padded([sets[pick(h + off) % Hq] for h in range(Hq)], n))}
+    a, b = lists(lambda h: h), lists(lambda h: 3 * h + 1)
+    out = binding.alloc_select(shape, accounted=False)
+    ctx = binding.Context(workspace=1 << 20)
+    ctx.ls_merge_lines(shape, dev_lists(**a), dev_lists(**b), out)
+    assert ctx.ls_poll_status() == 0
+    got, want = host(out), _union(a, b, n)
+    for h in range(Hq):
+        for kind in ("v", "s"):
+            assert int(got[kind + "_cnt"][0, h]) == len(want[kind][0][h])
+            np.testing.assert_array_equal(got[kind + "_idx"][0, h, :len(want[kind][0][h])], want[kind][0][h])
+
+
+def _padded(rows, cap):
+    idx, cnt = np.zeros((1, len(rows), cap), np.int32), np.zeros((1, len(rows)), np.int32)
+    for h, x in enumerate(rows):
+        idx[0, h, :len(x)], cnt[0, h] = x, len(x)
+    return idx, cnt
