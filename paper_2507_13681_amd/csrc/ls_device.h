@@ -143,6 +143,29 @@ __device__ __forceinline__ float2 get_shared2(const float* p) {
 __device__ __forceinline__ uint32_t count_shared(uint32_t* c) { return __hip_atomic_fetch_add(c, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void clear_shared(uint32_t* c) { __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// sum over the lanes to the left and this one
+__device__ __forceinline__ uint32_t lanes_upto(uint32_t x) {
+    int32_t s = (int32_t)x;
+    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);       // row_shr:1, 2, 4, 8
+    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xA, 0xF, false);       // row_bcast15 into rows 1 and 3
+    s += __builtin_amdgcn_update_dpp(0, s, 0x143, 0xC, 0xF, false);       // row_bcast31 into rows 2 and 3
+    return (uint32_t)s;
+}
+
+// Sums over the sixteen waves before this one, and over all, of what each left in `red` (the sixteen in a row of lanes: a tenth of the
+// instructions that a loop over them takes, which a kernel that runs through its code once has to fetch)
+__device__ __forceinline__ uint32_t waves_before(const uint32_t* red, int lane, int wv, uint32_t& total) {
+    int32_t s = (int32_t)red[lane & 15];
+    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);       // row_shr:1, 2, 4, 8
+    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);
+    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);
+    total = (uint32_t)__builtin_amdgcn_readlane(s, 15);
+    return wv > 0 ? (uint32_t)__builtin_amdgcn_readlane(s, wv - 1) : 0u;
+}
 __device__ __forceinline__ float to_float(bf16_t x) { return bf2f(x.bits); }
 __device__ __forceinline__ float to_float(float x) { return x; }
 

@@ -82,44 +82,40 @@ constexpr float SOFT_AHEAD = 32.f;
 //           selected: the mask is plain causal then, or if the column list is not strictly ascending inside [0, n): its columns
 //           are ignored); upto, head_work: running sums of the work that is
 // ---------------------------------------------------------------------------------------------
-// Exclusive prefix sum over the 1024 threads of a workgroup (wave shuffles + one LDS round).
-// `wsum` must hold 16 words; returns the sum of `v` over the threads before this one and, in
-// `total`, the sum over all threads.
+// Exclusive prefix sum over the 1024 threads of a workgroup: returns the sum of `v` over the threads before this one and, in
+// `total`, the sum over all threads.  `wsum`: 16 words, FREE: that no earlier call's threads still read (a barrier less).
+template <bool FREE = false>
 __device__ __forceinline__ uint32_t block_scan_1024(uint32_t v, uint32_t* wsum, uint32_t& total) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) { const uint32_t t = __shfl_up(inc, off, 64); if (lane >= off) inc += t; }
-    __syncthreads();                                       // wsum may still be read from an earlier call
-    if (lane == 63) wsum[wv] = inc;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t upto = lanes_upto(v);
+    if (!FREE) __syncthreads();
+    if (lane == 63) wsum[wv] = upto;
     __syncthreads();
-    uint32_t before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < 16; ++w) { const uint32_t t = wsum[w]; all += t; if (w < wv) before += t; }
-    total = all;
-    return before + inc - v;
+    return waves_before(wsum, lane, wv, total) + upto - v;
 }
 
 constexpr int OB_PAD = 4;                    // zero words in front of a head's bitmap (rows above a tile's keys)
-// The same for the maximum: the largest `v` of the threads before this one (0 for the first).
+// The same for the maximum, with `wsum` free: the largest `v` of the threads before this one (0 for the first).
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp_larger(uint32_t x) { const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false); return o > x ? o : x; }
 __device__ __forceinline__ uint32_t block_max_1024(uint32_t v, uint32_t* wsum) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) { const uint32_t t = __shfl_up(inc, off, 64); if (lane >= off && t > inc) inc = t; }
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    auto row = [](uint32_t x) { x = dpp_larger<0x111, 0xF>(x); x = dpp_larger<0x112, 0xF>(x); x = dpp_larger<0x114, 0xF>(x); return dpp_larger<0x118, 0xF>(x); };      // row_shr:1, 2, 4, 8
+    uint32_t upto = row(v);
+    upto = dpp_larger<0x142, 0xA>(upto);                   // row_bcast15 into rows 1 and 3
+    upto = dpp_larger<0x143, 0xC>(upto);                   // row_bcast31 into rows 2 and 3
+    if (lane == 63) wsum[wv] = upto;
+    const uint32_t ex = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)upto, 0x138 /* wave_shr:1 */, 0xF, 0xF, false);
     __syncthreads();
-    if (lane == 63) wsum[wv] = inc;
-    uint32_t ex = __shfl_up(inc, 1, 64);
-    if (lane == 0) ex = 0u;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < 16; ++w) if (w < wv && wsum[w] > ex) ex = wsum[w];
-    return ex;
+    const uint32_t waves = row(wsum[lane & 15]), before = wv > 0 ? (uint32_t)__builtin_amdgcn_readlane((int)waves, wv - 1) : 0u;
+    return ex > before ? ex : before;
 }
 
 // grid (BH).  Bound by the round trips of one workgroup through the lists of its head: so many loads of 16 bytes are in flight as
 // there are registers for without losing a wave, and the bitmap is put together from neighbouring entries (one entry a lane, eight
-// loads of 4 bytes in flight: 131072 rows 81 us, now 52; 32768 26 -> 19.5, B 4, 64 heads of 16384 17.1 -> 14.7).
+// loads of 4 bytes in flight: 131072 rows 81 us, now 52; 32768 26 -> 19.5, B 4, 64 heads of 16384 17.1 -> 14.7).  Where the lists are short it is the steps behind
+// one another, a thousand cycles each: scans by DPP with a barrier instead of shuffles with two, the six words of a table entry read at once, 32-bit
+// column arithmetic: 5003 lines 11.2 -> 9.6 us, 8192 11.7 -> 9.4, 12347 7.2 -> 5.9 (start 1500 cycles, columns 1000 to 2000, diagonals 900 to 2400, bitmap out 1000,
+// table 630, entries 1400, row blocks 1700).
 constexpr int LS_MAX_BLOCKS = 262144 / 128 + 2;   // row blocks at the largest supported context
 constexpr int LS_MAX_TAB = 262144 / 64 + 8;  // table entries at the largest supported context
 __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
@@ -127,11 +123,12 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     __shared__ int total_bits;
     __shared__ uint8_t tabs[LS_MAX_TAB];
     __shared__ uint32_t colh[LS_MAX_BLOCKS];               // list position behind the last column that each row block is the first to see
-    __shared__ uint32_t wsum[16];
+    __shared__ uint32_t wsum[3][16];
     const int bh = blockIdx.x;
     const int64_t n = a.n;
     const int words = a.words;
     const int tid = threadIdx.x;
+    int nvl = a.v_cnt[bh]; if (nvl > a.cap_v) nvl = a.cap_v; if (nvl < 0) nvl = 0;
     int ns = a.s_cnt[bh]; if (ns > a.cap_s) ns = a.cap_s; if (ns < 0) ns = 0;
     const int32_t* si = a.s_idx + (int64_t)bh * a.cap_s;
     for (int i = tid; i < words; i += blockDim.x) sm[i] = 0u;
@@ -140,14 +137,15 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     __syncthreads();
     // The column list must be strictly ascending and inside [0, n) (the attention kernel gathers K / V rows through
     // a prefix of it): a head whose list is not has its columns ignored and the context's status word says so.  Diagonals outside [0, n) are skipped below and reported likewise.
-    int nvl = a.v_cnt[bh]; if (nvl > a.cap_v) nvl = a.cap_v; if (nvl < 0) nvl = 0;
     const int32_t* vl = a.v_idx + (int64_t)bh * a.cap_v;
     bool v_bad = false, s_bad = false;
     // the last column that each row block is the first to see leaves its list position behind (columns before the turn
     // count for the first block)
-    auto block_of = [&](int32_t c) -> int { return c < a.pos0 + BM ? 0 : (int)((c - a.pos0) / BM); };
-    auto mark_col = [&](int i, int32_t c, int32_t next, bool last) {
-        if (c >= 0 && c < n && (last || block_of(next) != block_of(c))) colh[block_of(c)] = (uint32_t)i + 1u;
+    const int pos0 = (int)a.pos0, n32 = (int)n;
+    static_assert(BM == 128, "a shift by 7");
+    auto block_of = [&](int32_t c) -> int { return c > pos0 ? (c - pos0) >> 7 : 0; };
+    auto mark_col = [&](int i, int32_t c, int block, int next, bool last) {        // (next: the next entry's block)
+        if (c >= 0 && c < n32 && (last || next != block)) colh[block] = (uint32_t)i + 1u;
     };
     if ((reinterpret_cast<uintptr_t>(vl) & 15) == 0 && a.cap_v % 4 == 0) {     // four entries per load (and the one before them)
         typedef __attribute__((ext_vector_type(4))) int32_t i32x4;
@@ -168,10 +166,11 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
                 if (i0 >= nvl) break;
                 int32_t prev = i0 > 0 ? before[u] : -1;
                 const int32_t c[4] = {c4[u].x, c4[u].y, c4[u].z, c4[u].w};
+                const int block[5] = {block_of(c[0]), block_of(c[1]), block_of(c[2]), block_of(c[3]), block_of(next[u])};
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    if (i0 + e < nvl) { v_bad = v_bad || c[e] <= prev || c[e] >= n; prev = c[e]; }
-                    if (i0 + e < nvl) mark_col(i0 + e, c[e], e < 3 ? c[(e + 1) & 3] : next[u], i0 + e == nvl - 1);
+                    if (i0 + e < nvl) { v_bad = v_bad || c[e] <= prev || c[e] >= n32; prev = c[e]; }
+                    if (i0 + e < nvl) mark_col(i0 + e, c[e], block[e], block[e + 1], i0 + e == nvl - 1);
                 }
             }
         }
@@ -179,7 +178,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
         for (int i = tid; i < nvl; i += blockDim.x) {
             const int32_t c = vl[i];
             v_bad = v_bad || c < 0 || c >= n || (i > 0 && vl[i - 1] >= c);
-            mark_col(i, c, i + 1 < nvl ? vl[i + 1] : 0, i == nvl - 1);
+            mark_col(i, c, block_of(c), block_of(i + 1 < nvl ? vl[i + 1] : 0), i == nvl - 1);
         }
     }
     v_bad = __syncthreads_or(v_bad);
@@ -238,24 +237,18 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     if ((tid & 63) == 0) atomicAdd(&total_bits, mine);
     // activity table
     for (int e = tid; e < a.tab_len; e += blockDim.x) {
-        const int64_t j = (int64_t)e - 1;
-        int64_t lo = 64 * j - 63, hi = 64 * j + 127;
-        const bool cut = lo < 0;
-        if (lo < 0) lo = 0;
-        if (hi > n - 1) hi = n - 1;
+        // the diagonals 64 j - 63 .. 64 j + 127 that there are: six words (bits beyond the context are zero)
+        const int j = e - 1;
         int cnt = 0;
-        if (hi >= lo) {
-            const int w0 = (int)(lo >> 5), w1 = (int)(hi >> 5);
-            for (int wd = w0; wd <= w1; ++wd) {
-                uint32_t m = sm[wd];
-                if (wd == w0) m &= 0xFFFFFFFFu << (lo & 31);
-                if (wd == w1) m &= 0xFFFFFFFFu >> (31 - (hi & 31));
-                cnt += __popc(m);
-            }
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const int wd = 2 * j - 2 + k;
+            const uint32_t m = sm[wd < 0 ? 0 : wd < words ? wd : words - 1];
+            cnt += wd >= 0 && wd < words ? __popc(k == 0 ? m & ~1u : m) : 0;
         }
         uint8_t f = 0;
         if (cnt > 0) f |= 1;
-        if (!cut && hi >= lo && cnt == (int)(hi - lo + 1) && hi == 64 * j + 127) f |= 2;
+        if (cnt == 191) f |= 2;
         a.tab[(int64_t)bh * a.tab_len + e] = f;
         tabs[e] = f;                                       // LDS copy for the counts below
     }
@@ -266,7 +259,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
     int mine2 = 0;
     for (int e = e0; e < e1; ++e) mine2 += tabs[e] & 1;
     uint32_t active_entries;
-    uint32_t run = block_scan_1024((uint32_t)mine2, wsum, active_entries);
+    uint32_t run = block_scan_1024<true>((uint32_t)mine2, wsum[0], active_entries);
     uint16_t* el = a.elist + (int64_t)bh * (a.tab_len + 1);
     uint16_t* below = reinterpret_cast<uint16_t*>(sm);     // [tab_len + 1]; the bitmap has been written out (the scan's barriers lie between)
     for (int e = e0; e < e1; ++e) {
@@ -282,7 +275,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
         const int q0 = tid * per < a.nqb ? tid * per : a.nqb, q1 = q0 + per < a.nqb ? q0 + per : a.nqb;
         uint32_t top = 0;                                  // positions grow with the block: a running maximum fills the gaps
         for (int q = q0; q < q1; ++q) top = top > colh[q] ? top : colh[q];
-        const uint32_t before = block_max_1024(top, wsum);             // (its barriers publish `below`)
+        const uint32_t before = block_max_1024(top, wsum[1]);          // (its barrier publishes `below`)
         const uint32_t base = work_base(a.dtype);
         uint32_t work = 0, all;
         auto visit = [&](int q, uint32_t& cols) -> uint2 {                       // {key blocks, columns}
@@ -294,7 +287,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
         };
         uint32_t cols = before;
         for (int q = q0; q < q1; ++q) { const uint2 r = visit(q, cols); work += item_work(base, r.x, (r.y + BN - 1) / BN); }
-        uint32_t pre = block_scan_1024(work, wsum, all);
+        uint32_t pre = block_scan_1024<true>(work, wsum[2], all);
         cols = before;
         for (int q = q0; q < q1; ++q) {
             const uint2 r = visit(q, cols);

@@ -35,6 +35,7 @@ constexpr int WALK_BLK = 1024;                 // entries of a sorted list the w
 static_assert(WALK_BLK == SELECT_HEAD_LINES, "order_kernel writes the walk's first block in order");
 constexpr int ORDER_THREADS = 1024;
 constexpr int ORDER_WAVES = 16;
+static_assert(ORDER_WAVES == 16, "waves_before adds a row of lanes");
 constexpr int ORDER_CHUNKS = 10;               // most lines of a workgroup, in 1024
 constexpr int ORDER_ONE = 4096;                // longest list that one workgroup puts in order
 constexpr int ORDER_SAMPLES = 2048;            // of a list, for the bounds of its ranges
@@ -45,18 +46,6 @@ constexpr size_t order_lds_bytes(int pt, int cap) { return (size_t)order_fine(pt
 static_assert(order_fine(4) * 2 >= 4096 * 4 && order_fine(8) >= 1024 * ORDER_CHUNKS, "room for order_bounds, a bin per line");
 constexpr int ORDER_SEGS = 320;                // most bins with more lines than that
 static_assert(1024 * ORDER_CHUNKS / (ORDER_FULL + 1) < ORDER_SEGS && 2 * ORDER_SEGS <= 1024 && 1024 * ORDER_CHUNKS <= 1 << 14, "words for each of them, places 14 bits");
-
-// sum over the lanes to the left and this one
-__device__ __forceinline__ uint32_t lanes_upto(uint32_t x) {
-    int32_t s = (int32_t)x;
-    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);       // row_shr:1, 2, 4, 8
-    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);
-    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);
-    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);
-    s += __builtin_amdgcn_update_dpp(0, s, 0x142, 0xA, 0xF, false);       // row_bcast15 into rows 1 and 3
-    s += __builtin_amdgcn_update_dpp(0, s, 0x143, 0xC, 0xF, false);       // row_bcast31 into rows 2 and 3
-    return (uint32_t)s;
-}
 
 // smallest / largest of the wave's, in lane 63
 template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp_min(uint32_t x) { const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp((int)x, (int)x, CTRL, ROWS, 0xF, false); return o < x ? o : x; }
@@ -72,18 +61,6 @@ __device__ __forceinline__ int width_of(uint32_t x) { return x == 0u ? 0 : 32 - 
 // What the workgroup keeps beside the keys: `red` for sums over the waves (two rounds that follow each other use different halves).
 struct OrderSync { uint32_t red[4][ORDER_WAVES], bin[2], rest[2], many[2]; int32_t cross[4]; uint16_t lines[ORDER_SEGS]; };
 
-// Sums over the waves before this one, and over all, of what each left in `red` (the sixteen in a row of lanes: a tenth of the
-// instructions that a loop over them takes, which a kernel that runs through its code once has to fetch)
-__device__ __forceinline__ uint32_t waves_before(const uint32_t* red, int lane, int wv, uint32_t& total) {
-    static_assert(ORDER_WAVES == 16, "a row of lanes");
-    int32_t s = (int32_t)red[lane & 15];
-    s += __builtin_amdgcn_update_dpp(0, s, 0x111, 0xF, 0xF, false);       // row_shr:1, 2, 4, 8
-    s += __builtin_amdgcn_update_dpp(0, s, 0x112, 0xF, 0xF, false);
-    s += __builtin_amdgcn_update_dpp(0, s, 0x114, 0xF, 0xF, false);
-    s += __builtin_amdgcn_update_dpp(0, s, 0x118, 0xF, 0xF, false);
-    total = (uint32_t)__builtin_amdgcn_readlane(s, 15);
-    return wv > 0 ? (uint32_t)__builtin_amdgcn_readlane(s, wv - 1) : 0u;
-}
 // Smallest and largest over the waves, of what each left in the two halves of `red`
 __device__ __forceinline__ void waves_extremes(const uint32_t (*red)[ORDER_WAVES], int lane, uint32_t& least, uint32_t& most) {
     least = (uint32_t)__builtin_amdgcn_readlane((int)lanes_min(red[0][lane & 15]), 63);
