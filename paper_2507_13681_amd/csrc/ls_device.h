@@ -166,6 +166,24 @@ __device__ __forceinline__ uint32_t waves_before(const uint32_t* red, int lane, 
     total = (uint32_t)__builtin_amdgcn_readlane(s, 15);
     return wv > 0 ? (uint32_t)__builtin_amdgcn_readlane(s, wv - 1) : 0u;
 }
+// Sum / largest over the wave, in every lane, as halves of 32, 16, 8, 4, 2 and 1 lanes put together one after the other.  (Where the halves of a
+// row agree already, row_ror:4 brings what lane ^ 4 has.  Six shuffles through LDS wait a hundred cycles each.)
+template <typename F>
+__device__ __forceinline__ float wave_join(float x, F f) {
+    auto u = [](float v) { return __builtin_bit_cast(uint32_t, v); };
+    auto fl = [](uint32_t v) { return __builtin_bit_cast(float, v); };
+    const auto h = __builtin_amdgcn_permlane32_swap(u(x), u(x), false, false);
+    x = f(fl((uint32_t)h[0]), fl((uint32_t)h[1]));
+    const auto q = __builtin_amdgcn_permlane16_swap(u(x), u(x), false, false);
+    x = f(fl((uint32_t)q[0]), fl((uint32_t)q[1]));
+    x = f(x, fl((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u(x), 0x128 /* row_ror:8 */, 0xF, 0xF, false)));
+    x = f(x, fl((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u(x), 0x124 /* row_ror:4 */, 0xF, 0xF, false)));
+    x = f(x, fl((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u(x), 0x4E /* quad_perm 2,3,0,1 */, 0xF, 0xF, false)));
+    return f(x, fl((uint32_t)__builtin_amdgcn_update_dpp(0, (int)u(x), 0xB1 /* quad_perm 1,0,3,2 */, 0xF, 0xF, false)));
+}
+__device__ __forceinline__ float wave_sum(float x) { return wave_join(x, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_largest(float x) { return wave_join(x, [](float a, float b) { return fmaxf(a, b); }); }
+
 __device__ __forceinline__ float to_float(bf16_t x) { return bf2f(x.bits); }
 __device__ __forceinline__ float to_float(float x) { return x; }
 

@@ -420,10 +420,11 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 3 : 1)) void 
 }
 
 // ---- merge: sixteen rows per workgroup; 64 threads of a row stride over the key blocks, then a fixed butterfly ----
-// grid (rows of a KV head / 16, B*Hkv).  Bound by the reads of `part`: the threads of sixteen neighbouring rows read 128
+// grid (rows of a KV head / 16, B*Hkv).  Bound by the reads of `part`, and where there are few by its steps (shuffles through LDS instead of DPP, and a barrier more
+// for each: merge and finish together 0.4 to 0.6 us more): the threads of sixteen neighbouring rows read 128
 // contiguous bytes (a wave per two rows, 16 bytes at a time: 25 us at 131072 keys).
 __global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
-    __shared__ float x[64][17];
+    __shared__ float x[64][17], most[16];
     const int rows = a.G * a.w, bk = blockIdx.y;
     const int row = blockIdx.x * 16 + (threadIdx.x & 15), k0 = threadIdx.x >> 4;           // as a reader of `part`
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;                                // as a lane of row wv
@@ -444,13 +445,10 @@ __global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
     x[k0][threadIdx.x & 15] = M;
     __syncthreads();
     M = x[lane][wv];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) M = fmaxf(M, __shfl_xor(M, off, 64));
+    M = wave_largest(M);
+    if (lane == 0) most[wv] = M;
     __syncthreads();
-    if (lane == 0) x[0][wv] = M;
-    __syncthreads();
-    const float Mr = x[0][threadIdx.x & 15];
-    __syncthreads();
+    const float Mr = most[threadIdx.x & 15];
 #pragma unroll
     for (int i = 0; i < KEEP; ++i)
         if (v[i].x != -INFINITY) L += v[i].y * fast_exp2(v[i].x - Mr);
@@ -462,8 +460,7 @@ __global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
     x[k0][threadIdx.x & 15] = L;
     __syncthreads();
     L = x[lane][wv];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) L += __shfl_xor(L, off, 64);
+    L = wave_sum(L);
     if (lane == 0 && blockIdx.x * 16 + wv < rows)
         reinterpret_cast<float2*>(a.rowstat)[(int64_t)bk * rows + blockIdx.x * 16 + wv] = make_float2(M, L > 0.f ? 1.0f / L : 0.f);
 }
@@ -780,6 +777,13 @@ __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguou
     const int64_t n = a.n;
     const int64_t per = ((n + FINISH_SPLIT - 1) / FINISH_SPLIT + 1023) / 1024 * 1024;   // this workgroup's range, whole rounds of threads
     const int64_t beg = (int64_t)part * per, end = beg + per < n ? beg + per : n;
+    // (asked for ahead of the diagonals' partials: one round trip for both)
+    float v4[4];
+    auto ask = [&](int64_t i0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { const int64_t i = i0 + j * 1024; v4[j] = i < end ? a.vert[(int64_t)bh * n + i] : 0.f; }
+    };
+    ask(beg + tid);
     if (contiguous) {
         for (int64_t o0 = beg + tid; o0 < end; o0 += 4 * 1024) {   // four diagonals per thread, all loads first
             float2 va[4], vb[4]; bool two[4];
@@ -804,23 +808,23 @@ __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguou
     }
     // this range's share of total = sum of the column sums: per thread in index order, then a fixed tree
     float acc = 0.f;
-    for (int64_t i0 = beg + tid; i0 < end; i0 += 4 * 1024) {
-        float v4[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { const int64_t i = i0 + j * 1024; v4[j] = i < end ? a.vert[(int64_t)bh * n + i] : 0.f; }
+    for (int64_t i0 = beg + tid; i0 < end;) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) if (i0 + j * 1024 < end) acc += v4[j];
+        i0 += 4 * 1024;
+        ask(i0);
     }
     red[tid] = acc;
     __syncthreads();
-    for (int s = 512; s >= 64; s >>= 1) {
-        if (tid < s) red[tid] += red[tid + s];
-        __syncthreads();
-    }
     if (tid >= 64) return;
-    acc = red[tid];
+    float r[16];
 #pragma unroll
-    for (int s = 32; s > 0; s >>= 1) acc += __shfl_down(acc, s, 64);
+    for (int w = 0; w < 16; ++w) r[w] = red[64 * w + tid];
+#pragma unroll
+    for (int s = 8; s > 0; s >>= 1)
+#pragma unroll
+        for (int w = 0; w < s; ++w) r[w] += r[w + s];
+    acc = wave_sum(r[0]);
     if (tid == 0) {
         float* share = a.part + (int64_t)bh * FINISH_SPLIT;            // `part` is free again once merge_kernel has run
         put_shared(share + part, acc);
