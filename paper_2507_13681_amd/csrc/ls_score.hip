@@ -586,8 +586,9 @@ __device__ __forceinline__ void retain_stream(const ScoreArgs& a, unsigned char*
 //         The chunks that hold the band's rows are passed; their columns are added to those of the chunks before them.
 // MODE 2: column sums only, summed over the G heads of the KV head (retention score)
 // MODE 3: the matrix A only
-// Four workgroups per CU cost bf16 the registers beyond 128, four of them spilled at d = 128 in MODE 0; with three ls_score of
-// 64 rows takes 39.6 instead of 36.5 us at 8192 keys, 98.1 instead of 96.3 at 32768, of 128 rows at 131072 keys 533 instead of 515.
+// Four workgroups per CU leave bf16 128 registers.  In MODE 0 what a row sees is arithmetic: with a table of the rows' limits in LDS, as for explicit
+// positions, ls_score took, us, 131072 keys 464 instead of 448, 16384, B 4, 64 heads, 267 / 248, 32768 88 / 82, 8192 37.5 / 35.2, 61 rows of 12347, half
+// of whose chunks have 29 rows, 51.5 / 47.9 (its reads beside the slab's, 13 more registers, four of them spilled).
 template <typename T, int D, int MODE, bool FOLD>
 __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void lines_kernel(ScoreArgs a) {
     using RT = RowTile<T, D>;
@@ -619,7 +620,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         RT::fetch(Q0 + (int64_t)k.start * RT::RB, k.cnt, qs_lds + (uint32_t)((c & 1) * RT::BYTES), lane, wv, 4);
         if (wv == 3 && !FOLD) dma4(uniform_ptr(st0), (uint32_t)(8 * (k.start + ((lane >> 1) < k.cnt ? lane >> 1 : k.cnt - 1)) + 4 * (lane & 1)), (uint32_t)__builtin_amdgcn_readfirstlane((int)(rst_lds + (uint32_t)((c & 1) * 256))));
     };
-    for (int t = tid; t < a.w; t += SCORE_THREADS) {
+    if (MODE != 0) for (int t = tid; t < a.w; t += SCORE_THREADS) {
         const int64_t rel = position_of(a, t) - blk0;      // key klocal of the block is visible to row t iff klocal <= rel
         ql[t] = rel < -1 ? -1 : (rel > SB ? SB : (int32_t)rel);
     }
@@ -664,6 +665,8 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         const int lo = MODE == 1 && a.t0 > k.t0 ? a.t0 - k.t0 : 0;
         const int cells = (MODE == 1 && a.t1 - k.t0 < k.cnt ? a.t1 - k.t0 : k.cnt) - lo;
         float* cell = MODE == 1 || MODE == 3 ? a.a_win + ((int64_t)(bh - a.bh_first) * (a.t1 - a.t0) + k.t0 - a.t0 + 4 * g) * n + mykey : nullptr;
+        // MODE 0: the rows that see this lane's key are those from its own on, see + 4 g .. see + 4 g + seen - 1 of the chunk
+        const int own = mykey - (n - a.w) - k.t0 > 0 ? (int)(mykey - (n - a.w)) - k.t0 : 0, see = own - 4 * g, seen = k.cnt > own ? k.cnt - own : 0;
         // MASKED: there are rows that do not exist (the last one is repeated) or keys that a row does not see
         auto rows = [&](auto MASKED) {
 #pragma unroll
@@ -679,9 +682,12 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
                     const int row = rq + e;
                     float p = fast_exp2(__builtin_fmaf(s[4 * q4 + e], a.scale_log2e, -mm[e])) * il[e];
                     if constexpr (decltype(MASKED)::value) {
-                        int t = k.t0 + row;
-                        if (MODE == 2 && packed) t &= a.w - 1;
-                        p = ((row < k.cnt) & (klocal <= ql[t < a.w ? t : a.w - 1])) ? p : 0.f;
+                        if (MODE == 0) p = (unsigned)(8 * q4 + e - see) < (unsigned)seen ? p : 0.f;
+                        else {
+                            int t = k.t0 + row;
+                            if (MODE == 2 && packed) t &= a.w - 1;
+                            p = ((row < k.cnt) & (klocal <= ql[t < a.w ? t : a.w - 1])) ? p : 0.f;
+                        }
                     }
                     ps += p;
                     pe[e] = p;

@@ -46,6 +46,23 @@ def test_scores_over_ranges(B, Hq, Hkv, n, w, d, rising):
             np.testing.assert_allclose(got[name].reshape(want.shape), want, rtol=1e-3, atol=1e-6 * w, err_msg=name)
 
 
+@pytest.mark.parametrize("n,w,d", [(1, 1, 64), (32, 32, 128), (33, 31, 64), (100, 97, 128), (128, 128, 64), (129, 1, 128), (160, 128, 128), (255, 127, 64), (257, 33, 128), (300, 61, 64)])
+def test_rows_that_see_a_part_of_a_block(n, w, d):
+    """Newest rows that begin, end or lie inside a block of 128 keys, and chunks of fewer than 32 rows."""
+    print(f"rows in a block n={n} w={w} d={d}", flush=True)
+    q, k, v = inputs.make_plain(1, 4, 2, n, w, d, dtype="bf16", seed=n + w, q_scale=1.5)
+    got = host(Pipeline(q, k, v, w, "bf16").score())
+    A = _window(q, k, np.arange(n - w, n), 1 / math.sqrt(d))
+    slash, smax = np.zeros((1, 4, n)), np.zeros((1, 4, n))
+    for t in range(w):
+        p = n - w + t
+        diag = A[:, :, t, :p + 1][..., ::-1]
+        slash[..., :p + 1] += diag
+        smax[..., :p + 1] = np.maximum(smax[..., :p + 1], diag)
+    for name, want in (("vert", A.sum(2)), ("vmax", A.max(2)), ("slash", slash), ("smax", smax), ("total", A.sum((2, 3)))):
+        np.testing.assert_allclose(got[name].reshape(want.shape), want, rtol=1e-3, atol=1e-6 * w, err_msg=name)      # as above
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,n,n_obs,d,budget", [(1, 4, 1, 300, 8, 128, 100), (2, 8, 1, 1025, 16, 64, 1000), (1, 8, 2, 4097, 32, 128, 64), (1, 3, 3, 8191, 5, 64, 77), (1, 8, 1, 2049, 16, 128, 512),
                                                       (1, 8, 1, 2050, 32, 128, 512)])
 def test_retention_with_few_rows(B, Hq, Hkv, n, n_obs, d, budget):
