@@ -176,8 +176,9 @@ __device__ __forceinline__ void stats_stream(const ScoreArgs& a, unsigned char* 
     const int c0 = a.stat_chunks * (int)blockIdx.z, here = ch.count - c0 < a.stat_chunks ? ch.count - c0 : a.stat_chunks;
     // rows: waves side by side on chunks; few chunks: two waves share one, a half of each tile each (of one chunk, two waves only read K)
     const int rw = here > 2 ? 4 : here, kw = here > 2 ? 1 : 2;
-    const int cw = wv % rw, kh = wv / rw;                  // this wave's first chunk and, where they share, its half
-    const bool works = kh < kw;
+    const int kh = wv / rw;                                // where they share: this wave's half
+    const bool works = kh < kw && wv % rw < here;          // (of three chunks, the fourth wave only reads K)
+    const int cw = works ? wv % rw : 0;                    // its first chunk
     const int mine = !works ? 0 : cw + rw < here ? 2 : 1;  // chunks cw, cw + 4
     const uint32_t nt = (uint32_t)((n + C::KEYS - 1) / C::KEYS);                  // (fewer than 2^16, and ranges fewer than 2^8)
     const int t0 = (int)(nt * blockIdx.x / gridDim.x), t1 = (int)(nt * (blockIdx.x + 1) / gridDim.x);

@@ -46,6 +46,33 @@ def test_scores_over_ranges(B, Hq, Hkv, n, w, d, rising):
             np.testing.assert_allclose(got[name].reshape(want.shape), want, rtol=1e-3, atol=1e-6 * w, err_msg=name)
 
 
+@pytest.mark.parametrize("Hq,Hkv,n,w,packed", [(24, 8, 14001, 32, False), (7, 1, 47003, 32, False), (48, 8, 14002, 16, True), (11, 1, 110003, 8, True)])
+def test_three_chunks_of_rows_for_four_waves(Hq, Hkv, n, w, packed):
+    """A workgroup of the statistics pass with three chunks of 32 rows, or of up to 32: its fourth wave has none, and no rows to read (in the last
+    KV head there are none behind).  `packed`: windows that share chunks, as the retention score has them."""
+    print(f"three chunks Hq={Hq} Hkv={Hkv} n={n} w={w}", flush=True)
+    G, d = Hq // Hkv, 64
+    chunks = -(-G * w // 32)
+    assert chunks % 4 == 3 and Hkv * -(-n // 128) * chunks >= 2560             # four chunks a workgroup
+    q, k, v = inputs.make_plain(1, Hq, Hkv, n, w, d, dtype="bf16", seed=n, q_scale=1.5)
+    A = _window(q, k, np.arange(n - w, n), 1 / math.sqrt(d))
+    if not packed:
+        got = host(Pipeline(q, k, v, w, "bf16").score())
+        for name, want in (("vert", A.sum(2)), ("vmax", A.max(2)), ("total", A.sum((2, 3)))):
+            np.testing.assert_allclose(got[name].reshape(want.shape), want, rtol=1e-3, atol=1e-6 * w, err_msg=name)      # as above
+        return
+    dev = lambda x: torch.from_numpy(x).cuda().to(torch.bfloat16)
+    shape, budget = binding.make_shape(1, Hq, Hkv, d, n, 1, w, "bf16"), 500
+    idx, cnt = torch.empty(1, Hkv, budget, dtype=torch.int32, device="cuda"), torch.empty(1, Hkv, dtype=torch.int32, device="cuda")
+    binding.Context(shape, budget).ls_kv_compress(shape, budget, dev(q), dev(k), dev(v), idx, cnt, None, None)
+    score = A.reshape(Hkv, G * w, n).sum(1)
+    for g in range(Hkv):
+        assert cnt[0, g].item() == budget
+        threshold = np.sort(score[g])[-budget]
+        for i in set(np.argsort(-score[g], kind="stable")[:budget]).symmetric_difference(idx[0, g].tolist()):
+            assert abs(score[g, i] - threshold) <= 1e-3 * threshold            # as below
+
+
 @pytest.mark.parametrize("n,w,d", [(1, 1, 64), (32, 32, 128), (33, 31, 64), (100, 97, 128), (128, 128, 64), (129, 1, 128), (160, 128, 128), (255, 127, 64), (257, 33, 128), (300, 61, 64)])
 def test_rows_that_see_a_part_of_a_block(n, w, d):
     """Newest rows that begin, end or lie inside a block of 128 keys, and chunks of fewer than 32 rows."""
