@@ -15,7 +15,7 @@ struct ScoreArgs {
     float scale_log2e;
     float* part;              // [B*Hkv][nkb][G*w][2] per key block max / sum of every row; later the shares of the totals
     float* rowstat;           // [BH*w][2]        row max, 1 / row sum
-    float* spart;             // [2][BH][n][2]    diagonal partial sum / max by key-block parity
+    float* spart;             // [2][BH][n][2]    mode 0: diagonal partial sum / max by key-block parity, or what neighbouring key blocks leave each other (edge, edge_total, edge_done)
     float *vert, *slash, *vmax, *smax, *total;
     float* gscore;            // [B*Hkv][n]       group-summed column sums (retention score)
     float* a_win;             // [BH][w][n]       the window matrix (mode 3), or [heads from bh_first on][t1 - t0][n] a band of it (mode 1)
@@ -23,10 +23,12 @@ struct ScoreArgs {
     // set by run_score for each launch
     bool retain;              // mode 2: all rows in LDS
     int parts, stat_chunks;   // ranges of keys whose row statistics lie in `part`; chunks of rows of a workgroup of stats_kernel
+    bool join;                // mode 0: lines_kernel joins the key blocks' results itself
+    int shares;               // mode 0: workgroups that share a KV head's query heads
     int bk0, bh_first;        // first KV head / query head
     int t0, t1;               // window rows whose matrix is written out
     int sums;                 // mode 1: the column sums of the chunks are added here (not on a chunk's later bands)
-    uint32_t* done;           // [BH] workgroups of finish_kernel finished per head, cleared by stats_kernel (null: not used)
+    uint32_t* done;           // [BH] workgroups of lines_kernel or finish_kernel that are done, of a head (the first of a share), cleared by stats_kernel (null: not used)
 };
 
 constexpr int SELECT_HEAD_LINES = 1024;   // lines at the front of each sorted list whose weight and maximum are stored in order

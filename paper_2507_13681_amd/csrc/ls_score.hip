@@ -113,7 +113,7 @@ __host__ __device__ constexpr int stats_front() {
 template <typename T, int D>
 __host__ __device__ constexpr int lines_front(int mode) {
     using RT = RowTile<T, D>;
-    return mode != 0 || 2 * RT::BYTES > SLAB_BYTES ? 4 * RT::BYTES : 2 * RT::BYTES + SLAB_BYTES;
+    return (mode != 0 && mode != 4) || 2 * RT::BYTES > SLAB_BYTES ? 4 * RT::BYTES : 2 * RT::BYTES + SLAB_BYTES;
 }
 // the larger / the sum of this lane's and lane ^ 32's value
 __device__ __forceinline__ float halves_max(float x) {
@@ -123,6 +123,24 @@ __device__ __forceinline__ float halves_max(float x) {
 __device__ __forceinline__ float halves_sum(float x) {
     const auto b = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
     return __builtin_bit_cast(float, (uint32_t)b[0]) + __builtin_bit_cast(float, (uint32_t)b[1]);
+}
+
+// What the key blocks of a head leave each other (MODE 4 of lines_kernel).  Block kb and the next share the w - 1 diagonals from
+// omin(kb) on: two sides' {sum, maximum}; a block's share of the total; and for each KV head and share of its heads how many of two neighbours are done, and
+// how many of 16 (all counting in one place, which lies in one line of memory for 32 heads, took 8 ns each: 16 heads of 20000 keys 50 us instead of 30).
+// All of it takes no more than 16 bytes a head and key.
+constexpr int EDGE_GROUP = 16;
+__device__ __forceinline__ float* edge(const ScoreArgs& a, int bh, int kb, int side) { return a.spart + (((int64_t)bh * (a.nkb - 1) + kb) * 2 + side) * (2 * (a.w - 1)); }
+__device__ __forceinline__ float* edge_total(const ScoreArgs& a, int bh) { return a.spart + (int64_t)a.BH * (a.nkb - 1) * (4 * (a.w - 1)) + (int64_t)bh * a.nkb; }
+__device__ __forceinline__ int edge_groups(int nkb) { return (nkb + EDGE_GROUP - 1) / EDGE_GROUP; }
+__device__ __forceinline__ int edge_counters(int nkb) { return nkb - 1 + edge_groups(nkb); }
+__device__ __forceinline__ uint32_t* edge_done(const ScoreArgs& a, int bk, int share) {
+    return reinterpret_cast<uint32_t*>(a.spart + (int64_t)a.BH * ((int64_t)(a.nkb - 1) * (4 * (a.w - 1)) + a.nkb)) + ((int64_t)bk * a.shares + share) * edge_counters(a.nkb);
+}
+// by the first workgroup of a KV head that gets to stats_kernel, for the kernels behind it
+__device__ __forceinline__ void clear_counters(const ScoreArgs& a, int bk, int tid) {
+    if (a.done) for (int h = tid; h < a.G; h += SCORE_THREADS) clear_shared(a.done + bk * a.G + h);
+    if (a.join) for (int i = tid; i < a.shares * edge_counters(a.nkb); i += SCORE_THREADS) clear_shared(edge_done(a, bk, 0) + i);
 }
 
 // window row t's position in the context
@@ -183,8 +201,7 @@ __device__ __forceinline__ void stats_stream(const ScoreArgs& a, unsigned char* 
     const uint32_t nt = (uint32_t)((n + C::KEYS - 1) / C::KEYS);                  // (fewer than 2^16, and ranges fewer than 2^8)
     const int t0 = (int)(nt * blockIdx.x / gridDim.x), t1 = (int)(nt * (blockIdx.x + 1) / gridDim.x);
 
-    if (a.done && blockIdx.x == 0 && blockIdx.z == 0)      // finish_kernel's counters
-        for (int h = tid; h < a.G; h += SCORE_THREADS) clear_shared(a.done + b * a.Hq + kvh * a.G + h);
+    if (blockIdx.x == 0 && blockIdx.z == 0) clear_counters(a, bk, tid);
     // ---- transfers: wave wv fetches rows 16 wv .. 16 wv + 15 of a tile; keys beyond the context repeat the last one
     const int rowlane = 16 * wv + lane / C::DS, sl = lane % C::DS;
     const uint32_t part0 = 16u * (uint32_t)(sl ^ C::swz(rowlane));
@@ -355,8 +372,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 3 : 1)) void 
     // every key of the block is visible to every row of a contiguous window: no masks (all but the last blocks)
     const bool open = a.q_pos == nullptr && (int64_t)(kb + 1) * SB - 1 <= n - a.w;
     const int rows = a.G * a.w;
-    if (a.done && kb == 0 && blockIdx.z == 0)              // finish_kernel's counters
-        for (int h = tid; h < a.G; h += SCORE_THREADS) clear_shared(a.done + b * a.Hq + kvh * a.G + h);
+    if (kb == 0 && blockIdx.z == 0) clear_counters(a, bk, tid);
     wait_transfers();
     __syncthreads();
     int first = c0;                                        // first chunk whose wave results are still in `red`
@@ -587,19 +603,21 @@ __device__ __forceinline__ void retain_stream(const ScoreArgs& a, unsigned char*
 //         The chunks that hold the band's rows are passed; their columns are added to those of the chunks before them.
 // MODE 2: column sums only, summed over the G heads of the KV head (retention score)
 // MODE 3: the matrix A only
-// Four workgroups per CU leave bf16 128 registers.  In MODE 0 what a row sees is arithmetic: with a table of the rows' limits in LDS, as for explicit
+// MODE 4: as 0; the block that is done last adds what it shares with its neighbours, and the total (joins)
+// Four workgroups per CU leave bf16 128 registers.  In MODE 0 and 4 what a row sees is arithmetic: with a table of the rows' limits in LDS, as for explicit
 // positions, ls_score took, us, 131072 keys 464 instead of 448, 16384, B 4, 64 heads, 267 / 248, 32768 88 / 82, 8192 37.5 / 35.2, 61 rows of 12347, half
 // of whose chunks have 29 rows, 51.5 / 47.9 (its reads beside the slab's, 13 more registers, four of them spilled).
 template <typename T, int D, int MODE, bool FOLD>
 __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void lines_kernel(ScoreArgs a) {
     using RT = RowTile<T, D>;
+    constexpr bool LINES = MODE == 0 || MODE == 4;
     extern __shared__ __align__(16) unsigned char smem[];
     if constexpr (MODE == 2 && Elem<T>::bytes == 2 && !FOLD) { if (a.retain) { retain_stream<D>(a, smem); return; } }
     unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
     float* slab = reinterpret_cast<float*>(smem);          // [SLAB_DIAGS][SLAB] A by diagonals (MODE 0) and
-    unsigned char* qs = smem + (MODE == 0 ? SLAB_BYTES : 0);           // [2] chunks of queries
-    int32_t* ql = reinterpret_cast<int32_t*>(smem + lines_front<T, D>(MODE));    // [w] last visible key of a row, relative to the block
-    float* rst = reinterpret_cast<float*>(ql + (a.w + 3) / 4 * 4);     // [2][32][2] max and 1 / sum of the chunks' rows (FOLD: of all chunks)
+    unsigned char* qs = smem + (LINES ? SLAB_BYTES : 0);           // [2] chunks of queries
+    int32_t* ql = reinterpret_cast<int32_t*>(smem + lines_front<T, D>(MODE));    // [w] last visible key of a row, relative to the block (MODE 4: [4][G], see wtot)
+    float* rst = reinterpret_cast<float*>(ql + (MODE == 4 ? 4 * a.G : (a.w + 3) / 4 * 4));     // [2][32][2] max and 1 / sum of the chunks' rows (FOLD: of all chunks)
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = blockIdx.x, bk = a.bk0 + blockIdx.y;
@@ -621,7 +639,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         RT::fetch(Q0 + (int64_t)k.start * RT::RB, k.cnt, qs_lds + (uint32_t)((c & 1) * RT::BYTES), lane, wv, 4);
         if (wv == 3 && !FOLD) dma4(uniform_ptr(st0), (uint32_t)(8 * (k.start + ((lane >> 1) < k.cnt ? lane >> 1 : k.cnt - 1)) + 4 * (lane & 1)), (uint32_t)__builtin_amdgcn_readfirstlane((int)(rst_lds + (uint32_t)((c & 1) * 256))));
     };
-    if (MODE != 0) for (int t = tid; t < a.w; t += SCORE_THREADS) {
+    if (!LINES) for (int t = tid; t < a.w; t += SCORE_THREADS) {
         const int64_t rel = position_of(a, t) - blk0;      // key klocal of the block is visible to row t iff klocal <= rel
         ql[t] = rel < -1 ? -1 : (rel > SB ? SB : (int32_t)rel);
     }
@@ -637,10 +655,11 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
     __syncthreads();
     fetch(c0);
     if (c0 + 1 < c1) fetch(c0 + 1);
-    if (MODE == 0) for (int i = tid; i < SLAB_DIAGS * SLAB; i += SCORE_THREADS) slab[i] = 0.f;
+    if (LINES) for (int i = tid; i < SLAB_DIAGS * SLAB; i += SCORE_THREADS) slab[i] = 0.f;
     // every key of the block is visible to every row of a contiguous window (all but the last blocks)
     const bool open = a.q_pos == nullptr && blk0 + SB - 1 <= n - a.w;
-    const int64_t omin = n - a.w - (blk0 + SB - 1);        // MODE 0: this thread adds diagonal omin + tid of the slab (at most 255, w <= 128)
+    const int64_t omin = n - a.w - (blk0 + SB - 1);        // MODE 0, 4: this thread adds diagonal omin + tid of the slab (at most 255, w <= 128)
+    float* wtot = reinterpret_cast<float*>(ql);            // MODE 4: the four waves' column sums of each head
     float gsum = 0.f, vsum = 0.f, vmx = 0.f, dsum = 0.f, dmax = 0.f;
     wait_transfers();
     __syncthreads();
@@ -666,7 +685,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         const int lo = MODE == 1 && a.t0 > k.t0 ? a.t0 - k.t0 : 0;
         const int cells = (MODE == 1 && a.t1 - k.t0 < k.cnt ? a.t1 - k.t0 : k.cnt) - lo;
         float* cell = MODE == 1 || MODE == 3 ? a.a_win + ((int64_t)(bh - a.bh_first) * (a.t1 - a.t0) + k.t0 - a.t0 + 4 * g) * n + mykey : nullptr;
-        // MODE 0: the rows that see this lane's key are those from its own on, see + 4 g .. see + 4 g + seen - 1 of the chunk
+        // MODE 0, 4: the rows that see this lane's key are those from its own on, see + 4 g .. see + 4 g + seen - 1 of the chunk
         const int own = mykey - (n - a.w) - k.t0 > 0 ? (int)(mykey - (n - a.w)) - k.t0 : 0, see = own - 4 * g, seen = k.cnt > own ? k.cnt - own : 0;
         // MASKED: there are rows that do not exist (the last one is repeated) or keys that a row does not see
         auto rows = [&](auto MASKED) {
@@ -683,7 +702,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
                     const int row = rq + e;
                     float p = fast_exp2(__builtin_fmaf(s[4 * q4 + e], a.scale_log2e, -mm[e])) * il[e];
                     if constexpr (decltype(MASKED)::value) {
-                        if (MODE == 0) p = (unsigned)(8 * q4 + e - see) < (unsigned)seen ? p : 0.f;
+                        if (LINES) p = (unsigned)(8 * q4 + e - see) < (unsigned)seen ? p : 0.f;
                         else {
                             int t = k.t0 + row;
                             if (MODE == 2 && packed) t &= a.w - 1;
@@ -692,10 +711,10 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
                     }
                     ps += p;
                     pe[e] = p;
-                    if (MODE == 0) slab[(klocal - row + 31) * SLAB + row] = p;
+                    if (LINES) slab[(klocal - row + 31) * SLAB + row] = p;
                     if ((MODE == 1 || MODE == 3) && (unsigned)(row - lo) < (unsigned)cells && mykey < n) cell[(8 * q4 + e) * n] = p;
                 }
-                if (MODE == 0 || MODE == 1) { pm = fmaxf(fmaxf(pm, pe[0]), pe[1]); pm = fmaxf(fmaxf(pm, pe[2]), pe[3]); }
+                if (LINES || MODE == 1) { pm = fmaxf(fmaxf(pm, pe[0]), pe[1]); pm = fmaxf(fmaxf(pm, pe[2]), pe[3]); }
                 if (MODE == 2 && packed && (8 * (q4 + 1)) % a.w == 0) {                  // the last rows of a head
                     gsum += halves_sum(ps);                // (rows past the last head add zeros)
                     ps = 0.f;
@@ -705,9 +724,9 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         if (open && k.cnt == 32) rows(std::false_type{}); else rows(std::true_type{});
         if (!(MODE == 2 && packed)) {
             vsum += halves_sum(ps);
-            if (MODE == 0 || MODE == 1) vmx = fmaxf(vmx, halves_max(pm));
+            if (LINES || MODE == 1) vmx = fmaxf(vmx, halves_max(pm));
         }
-        if (MODE == 0) {
+        if (LINES) {
             lds_barrier();                                 // the slab is whole
             const int u = k.t0 + (SB - 1) - tid + 31;      // this thread's diagonal in the slab
             if (tid < SB - 1 + a.w && u >= 0 && u < SLAB_DIAGS) {
@@ -729,20 +748,102 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         if (c + 2 < c1) fetch(c + 2);
         if (!(MODE == 2 && packed) && k.t0 + 32 >= ch.end) {   // the head's last chunk
             if (MODE == 2) gsum += vsum;
-            if ((MODE == 0 || (MODE == 1 && a.sums)) && g == 0 && mykey < n) {
+            if ((LINES || (MODE == 1 && a.sums)) && g == 0 && mykey < n) {
                 a.vert[(int64_t)bh * n + mykey] = vsum;
                 a.vmax[(int64_t)bh * n + mykey] = vmx;
             }
-            vsum = 0.f; vmx = 0.f;
-            if (MODE == 0) {
+            if (LINES) {
+                if (MODE == 4) {
+                    const float sum = wave_sum(g == 0 ? vsum : 0.f);
+                    if (lane == 0) wtot[4 * (bh - bh0) + wv] = sum;
+                }
                 const int64_t o = omin + tid;
-                if (tid < SB - 1 + a.w && o >= 0)
-                    reinterpret_cast<float2*>(a.spart)[((int64_t)(kb & 1) * a.BH + bh) * n + o] = make_float2(dsum, dmax);
+                if (tid < SB - 1 + a.w && o >= 0) {        // the first w - 1 the next block has too, those from SB on the one before
+                    if (MODE != 4) reinterpret_cast<float2*>(a.spart)[((int64_t)(kb & 1) * a.BH + bh) * n + o] = make_float2(dsum, dmax);
+                    else if (tid < a.w - 1) put_shared2(edge(a, bh, kb, 0) + 2 * tid, dsum, dmax);
+                    else if (tid >= SB && kb > 0) put_shared2(edge(a, bh, kb - 1, 1) + 2 * (tid - SB), dsum, dmax);
+                    else { a.slash[(int64_t)bh * n + o] = dsum; a.smax[(int64_t)bh * n + o] = dmax; }
+                }
                 dsum = 0.f; dmax = 0.f;
             }
+            vsum = 0.f; vmx = 0.f;
         }
     }
     if (MODE == 2 && g == 0 && mykey < n) a.gscore[(int64_t)bk * n + mykey] = gsum;
+    if constexpr (MODE == 4) {
+        // Of two neighbouring blocks the one that is done last adds the diagonals that they share, of all blocks the one that is done
+        // last the total; nobody waits for anybody.
+        __shared__ uint32_t met[2];                        // whether this block is done last of the one before and this one, and of this one and the next
+        const int heads = a.G / (int)gridDim.z, first = bh0 + heads * (int)blockIdx.z;
+        uint32_t* done = edge_done(a, bk, (int)blockIdx.z);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's sides are written
+        __syncthreads();
+        if (wv == 0 && lane < 2) {
+            const int at = kb - 1 + lane;
+            met[lane] = at >= 0 && at < a.nkb - 1 ? count_shared(done + at) : 0u;
+        }
+        if (wv == 3)                                       // (meanwhile: the total is this wave's)
+            for (int h = lane; h < heads; h += 64) {
+                const float* s4 = wtot + 4 * (first - bh0 + h);
+                put_shared(edge_total(a, first + h) + kb, (s4[0] + s4[1]) + (s4[2] + s4[3]));
+            }
+        __syncthreads();
+        if (wv == 3) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            int last = 0;
+            if (lane == 0) {
+                const int grp = kb / EDGE_GROUP, left = a.nkb - grp * EDGE_GROUP;
+                last = count_shared(done + a.nkb - 1 + grp) + 1u == (uint32_t)(left < EDGE_GROUP ? left : EDGE_GROUP) && count_shared(a.done + first) + 1u == (uint32_t)edge_groups(a.nkb);
+            }
+            if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+            for (int h = 0; h < heads; ++h) {                  // in a fixed order: a lane every 64th block, then the lanes
+                const float* t = edge_total(a, first + h);
+                float sum = 0.f;
+                for (int i0 = lane; i0 < a.nkb; i0 += 4 * 64) {
+                    float v[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = get_shared(t + (i0 + 64 * e < a.nkb ? i0 + 64 * e : lane));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) if (i0 + 64 * e < a.nkb) sum += v[e];
+                }
+                sum = wave_sum(sum);
+                if (lane == 0) a.total[first + h] = sum;
+            }
+            return;
+        }
+        const int each = a.w - 1, all = heads * each;
+        const bool take[2] = {met[0] == 1u, met[1] == 1u};
+        constexpr int NT = SCORE_THREADS - 64, U = 3;      // (all of a side's reads at once for four heads of 128 rows)
+        for (int i0 = tid; i0 < all; i0 += U * NT) {
+            float2 x[2][U], y[2][U];
+            int h[U], u[U];
+#pragma unroll
+            for (int e = 0; e < U; ++e) {
+                const int i = i0 + e * NT < all ? i0 + e * NT : i0;
+                h[e] = i / each; u[e] = i - h[e] * each;
+            }
+#pragma unroll
+            for (int side = 0; side < 2; ++side)
+                if (take[side]) {
+#pragma unroll
+                    for (int e = 0; e < U; ++e) {
+                        x[side][e] = get_shared2(edge(a, first + h[e], kb - 1 + side, 0) + 2 * u[e]);
+                        y[side][e] = get_shared2(edge(a, first + h[e], kb - 1 + side, 1) + 2 * u[e]);
+                    }
+                }
+#pragma unroll
+            for (int side = 0; side < 2; ++side) {
+                if (!take[side]) continue;
+                const int64_t o0 = n - a.w - ((int64_t)(kb - 1 + side) * SB + SB - 1);
+#pragma unroll
+                for (int e = 0; e < U; ++e) {
+                    if (i0 + e * NT >= all || o0 + u[e] < 0) continue;
+                    a.slash[(int64_t)(first + h[e]) * n + o0 + u[e]] = x[side][e].x + y[side][e].x;      // lower key block first
+                    a.smax[(int64_t)(first + h[e]) * n + o0 + u[e]] = fmaxf(x[side][e].y, y[side][e].y);
+                }
+            }
+        }
+    }
 }
 
 // ---- diagonals from the written matrix (explicit positions) ---------------------------------------
@@ -857,6 +958,12 @@ static int head_shares(const ScoreArgs& a, int kv_heads) {
     while (a.G % (2 * z) == 0 && wgs * 2 * z <= (chunks >= 8 * z ? 2048 : 1024)) z *= 2;
     return z;
 }
+// Whether lines_kernel adds what neighbouring key blocks have of a diagonal, and the totals, itself.  That saves finish_kernel's launch and round trips, and costs a
+// workgroup three round trips at its end, in which others of its CU have to keep it busy: where nearly all are there at once (1024 are).
+// finish_kernel / so, us: 1024 keys, fp32, 17.2 / 14.2; 32 heads, 64 rows, of 2048 keys 21.0 / 17.8, 8192 34.3 / 31.3, 61 of 12347 (1552 workgroups) 45.2 / 44.3; 16 heads of 64, 48 rows
+// of 5003 keys 23.9 / 19.4; more of them: sixteen chunks each 455 / 453 to 469 (128 rows of 131072), eight 82.4 / 81.7 and 89.3 / 90.6, four 90 / 94, two 35.1 / 37.7, one 31.6 /
+// 33.5 (20000 keys), 66 / 82 (32 KV heads of 32768).
+static bool joins(const ScoreArgs& a, int kv_heads) { return (int64_t)a.nkb * kv_heads * a.shares <= 1600; }
 // Ranges of keys whose statistics are kept apart: as many as fill the chip with three workgroups a CU
 // (more than 64 cost merge_kernel what they save); no more than the blocks of 128 keys that `part` has room for.  Few rows a workgroup where there
 // is little work: eight / four / two chunks of rows, us, 131072 keys 140 / 157, 16384 keys, B 4, 75 / 81, 32768 24.0 / 24.4, 12347 16.0 / 13.8, 5003 of d = 64
@@ -890,7 +997,7 @@ static bool folds(const ScoreArgs& a, int mode) {
 template <typename T, int D, int MODE>
 static void launch_lines(const ScoreArgs& a, int kv_heads, hipStream_t st) {
     const bool fold = folds(a, MODE);
-    const size_t smem = lines_front<T, D>(MODE) + (size_t)(a.w + 3) / 4 * 16 + (fold ? (size_t)score_chunks(a) * 256 : 512);
+    const size_t smem = lines_front<T, D>(MODE) + (MODE == 4 ? (size_t)a.G * 16 : (size_t)(a.w + 3) / 4 * 16) + (fold ? (size_t)score_chunks(a) * 256 : 512);
     const dim3 grid(a.nkb, kv_heads, MODE == 2 ? 1 : head_shares(a, kv_heads));
     if (fold) hipLaunchKernelGGL((lines_kernel<T, D, MODE, true>), grid, dim3(SCORE_THREADS), smem, st, a);
     else hipLaunchKernelGGL((lines_kernel<T, D, MODE, false>), grid, dim3(SCORE_THREADS), smem, st, a);
@@ -916,10 +1023,15 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     ScoreArgs a = a0;
     const int BK = a.B * a.Hkv;
     a.t0 = 0; a.t1 = a.w;
+    if (mode == 0) { a.shares = head_shares(a, BK); a.join = joins(a, BK); }
     stats_split(a, Elem<T>::bytes == 2);
     launch_stats<T, D>(a, st);
     if (!folds(a, mode)) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {
+        if (a.join) {
+            launch_lines<T, D, 4>(a, BK, st);
+            return hipGetLastError();
+        }
         launch_lines<T, D, 0>(a, BK, st);
     } else if (mode == 1) {
         int most, rows;
@@ -957,6 +1069,7 @@ static hipError_t init_score_t() {
     hipError_t e;
     if ((e = allow_full_lds(&stats_kernel<T, D>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 0, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 0, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&lines_kernel<T, D, 4, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 4, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 1, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 1, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 2, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 2, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 3, false>)) != hipSuccess) return e;

@@ -46,6 +46,29 @@ def test_scores_over_ranges(B, Hq, Hkv, n, w, d, rising):
             np.testing.assert_allclose(got[name].reshape(want.shape), want, rtol=1e-3, atol=1e-6 * w, err_msg=name)
 
 
+@pytest.mark.parametrize("Hq,Hkv,n,w,d", [(8, 8, 25600, 8, 64), (8, 8, 25601, 8, 64), (4, 1, 4096, 128, 128), (8, 2, 2049, 1, 64), (4, 2, 129, 128, 64), (12, 4, 6000, 97, 128)])
+def test_key_blocks_that_join_their_results(Hq, Hkv, n, w, d):
+    """As many workgroups as still add shared diagonals and totals themselves, and one row of blocks more; several groups of blocks, one, a block of one
+    key; no shared diagonals.  Again and again on one context: the same bits, whoever comes last."""
+    print(f"joined blocks Hq={Hq} Hkv={Hkv} n={n} w={w} d={d}", flush=True)
+    q, k, v = inputs.make_plain(1, Hq, Hkv, n, w, d, dtype="bf16", seed=n + w, q_scale=1.5)
+    pipe = Pipeline(q, k, v, w, "bf16")
+    got = host(pipe.score())
+    A = _window(q, k, np.arange(n - w, n), 1 / math.sqrt(d))
+    slash, smax = np.zeros((1, Hq, n)), np.zeros((1, Hq, n))
+    for t in range(w):
+        p = n - w + t
+        diag = A[:, :, t, :p + 1][..., ::-1]
+        slash[..., :p + 1] += diag
+        smax[..., :p + 1] = np.maximum(smax[..., :p + 1], diag)
+    for name, want in (("vert", A.sum(2)), ("vmax", A.max(2)), ("slash", slash), ("smax", smax), ("total", A.sum((2, 3)))):
+        np.testing.assert_allclose(got[name].reshape(want.shape), want, rtol=1e-3, atol=1e-6 * w, err_msg=name)      # as above
+    for _ in range(3):
+        again = host(pipe.score())
+        for name in got:
+            np.testing.assert_array_equal(again[name], got[name], err_msg=name)
+
+
 @pytest.mark.parametrize("Hq,Hkv,n,w,packed", [(24, 8, 14001, 32, False), (7, 1, 47003, 32, False), (48, 8, 14002, 16, True), (11, 1, 110003, 8, True)])
 def test_three_chunks_of_rows_for_four_waves(Hq, Hkv, n, w, packed):
     """A workgroup of the statistics pass with three chunks of 32 rows, or of up to 32: its fourth wave has none, and no rows to read (in the last
