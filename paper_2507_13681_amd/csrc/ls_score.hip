@@ -126,22 +126,33 @@ __device__ __forceinline__ float halves_sum(float x) {
 }
 
 // What the key blocks of a head leave each other (MODE 4 of lines_kernel).  Block kb and the next share the w - 1 diagonals from
-// omin(kb) on: two sides' {sum, maximum}; a block's share of the total; and for each KV head and share of its heads how many of two neighbours are done, and
-// how many of 16 (all counting in one place, which lies in one line of memory for 32 heads, took 8 ns each: 16 heads of 20000 keys 50 us instead of 30).
-// All of it takes no more than 16 bytes a head and key.
-constexpr int EDGE_GROUP = 16;
+// omin(kb) on: two sides' {sum, maximum}; a head's total has shares of so many blocks each (as in finish_kernel: the same sums in the same order); and for each KV head and share of
+// its heads the counts of two neighbours that are done, and of the blocks of a share (all counting in one place, which lies in one line of memory for 32 heads, took
+// 8 ns each: 16 heads of 20000 keys 50 us instead of 30).  All of it takes no more than 16 bytes a head and key.
+constexpr int FINISH_SPLIT = 8;            // shares of a total
+__host__ __device__ __forceinline__ int64_t share_keys(int64_t n) { return ((n + FINISH_SPLIT - 1) / FINISH_SPLIT + 1023) / 1024 * 1024; }      // whole rounds of 1024
+__device__ __forceinline__ int edge_groups(const ScoreArgs& a) { const int blocks = (int)(share_keys(a.n) / SB); return (a.nkb + blocks - 1) / blocks; }
+__device__ __forceinline__ int edge_counters(const ScoreArgs& a) { return a.nkb - 1 + edge_groups(a); }
 __device__ __forceinline__ float* edge(const ScoreArgs& a, int bh, int kb, int side) { return a.spart + (((int64_t)bh * (a.nkb - 1) + kb) * 2 + side) * (2 * (a.w - 1)); }
-__device__ __forceinline__ float* edge_total(const ScoreArgs& a, int bh) { return a.spart + (int64_t)a.BH * (a.nkb - 1) * (4 * (a.w - 1)) + (int64_t)bh * a.nkb; }
-__device__ __forceinline__ int edge_groups(int nkb) { return (nkb + EDGE_GROUP - 1) / EDGE_GROUP; }
-__device__ __forceinline__ int edge_counters(int nkb) { return nkb - 1 + edge_groups(nkb); }
+__device__ __forceinline__ float* edge_share(const ScoreArgs& a, int bh) { return a.spart + (int64_t)a.BH * (a.nkb - 1) * (4 * (a.w - 1)) + (int64_t)bh * edge_groups(a); }
 __device__ __forceinline__ uint32_t* edge_done(const ScoreArgs& a, int bk, int share) {
-    return reinterpret_cast<uint32_t*>(a.spart + (int64_t)a.BH * ((int64_t)(a.nkb - 1) * (4 * (a.w - 1)) + a.nkb)) + ((int64_t)bk * a.shares + share) * edge_counters(a.nkb);
+    return reinterpret_cast<uint32_t*>(edge_share(a, a.BH)) + ((int64_t)bk * a.shares + share) * edge_counters(a);
 }
 // by the first workgroup of a KV head that gets to stats_kernel, for the kernels behind it
 __device__ __forceinline__ void clear_counters(const ScoreArgs& a, int bk, int tid) {
     if (a.done) for (int h = tid; h < a.G; h += SCORE_THREADS) clear_shared(a.done + bk * a.G + h);
-    if (a.join) for (int i = tid; i < a.shares * edge_counters(a.nkb); i += SCORE_THREADS) clear_shared(edge_done(a, bk, 0) + i);
+    if (a.join) for (int i = tid; i < a.shares * edge_counters(a); i += SCORE_THREADS) clear_shared(edge_done(a, bk, 0) + i);
 }
+
+// a share of a total from what 16 times 64 places of its range have, and the total from its shares
+__device__ __forceinline__ float share_of(float (&r)[16]) {
+#pragma unroll
+    for (int s = 8; s > 0; s >>= 1)
+#pragma unroll
+        for (int w = 0; w < s; ++w) r[w] += r[w + s];
+    return wave_sum(r[0]);
+}
+__device__ __forceinline__ float total_of(const float (&p)[FINISH_SPLIT]) { return ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])); }
 
 // window row t's position in the context
 __device__ __forceinline__ int position_of(const ScoreArgs& a, int t) {
@@ -150,18 +161,16 @@ __device__ __forceinline__ int position_of(const ScoreArgs& a, int t) {
     return (int)(p < -1 ? -1 : p);
 }
 
-// ---- pass 1: per (row, range of keys) max and sum of exp2 -----------------------------------------
-// grid (ranges of keys, B*Hkv, shares of the heads).  part[(bk * a.parts + range) * G w + row] = {max, sum} over the range's keys.
-//
-// bf16.  Bound by the reads of K where there are few rows, by vector and matrix issue where there are many.
+// ---- pass 1: per row max and sum of exp2 over a range or a block of keys -----------------------------------------
+// The retention score's, bf16.  grid (ranges of keys, B*Hkv, shares of the heads).  part[(bk * a.parts + range) * G w + row] = {max, sum} over the range's keys.
+// Bound by the reads of K where there are few rows, by vector and matrix issue where there are many.
 // A wave keeps 32 or 64 query rows in registers and meets the tiles of its range with them, three buffers of 64 keys
 // that the four waves fill and read together, the tile after the next under way at the barrier; a row is in a lane, and
 // its sum stays there until the end.  No maximum is looked for on the way: the reference is the maximum of the first 32 keys and moves
 // where a sum exceeds 2^30 (fp32 sums are as exact there; a reference of zero, with no look at the first keys, was not): three vector instructions a cell.
 // Against a workgroup per 128 keys with all rows passing through LDS (nine instructions a cell, K of all resident workgroups asked for at once
-// and nothing meanwhile, statistics of every 128 keys written), us: 131072 keys, 128 rows, 193 -> 138, 16384 keys, B 4, 64 heads, 104 -> 74, 32768 keys
-// 34 -> 24.5, 12347 17.6 -> 13.9, retention score, 16384 keys, B 4, 35 -> 27 (134 MB: 5 TB/s); of 5003 keys, d = 64, 6.5 -> 7.3: 2 us of a
-// workgroup are the way of its queries from memory.  Everything in 56 KB of LDS, two workgroups a CU: 155 at 131072 keys.
+// and nothing meanwhile, statistics of every 128 keys written), us: 16384 keys, B 4, 64 heads of 16 rows, 35 -> 27 (134 MB: 5 TB/s), 131072 keys, 32 heads of 128 rows, 193 -> 138.
+// Everything in 56 KB of LDS, two workgroups a CU: 155 at 131072 keys.
 template <int D>
 struct KeyTile {
     static constexpr int KEYS = 64, BUFFERS = 3;
@@ -178,7 +187,8 @@ template <int D>
 __host__ __device__ constexpr int stats_lds() { return KeyTile<D>::BUFFERS * KeyTile<D>::BYTES; }
 
 template <int D>
-__device__ __forceinline__ void stats_stream(const ScoreArgs& a, unsigned char* smem) {
+__global__ __launch_bounds__(SCORE_THREADS, 3) void range_stats_kernel(ScoreArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
     using C = KeyTile<D>;
     using T = bf16_t;
     constexpr int NS = D / 16;
@@ -201,7 +211,6 @@ __device__ __forceinline__ void stats_stream(const ScoreArgs& a, unsigned char* 
     const uint32_t nt = (uint32_t)((n + C::KEYS - 1) / C::KEYS);                  // (fewer than 2^16, and ranges fewer than 2^8)
     const int t0 = (int)(nt * blockIdx.x / gridDim.x), t1 = (int)(nt * (blockIdx.x + 1) / gridDim.x);
 
-    if (blockIdx.x == 0 && blockIdx.z == 0) clear_counters(a, bk, tid);
     // ---- transfers: wave wv fetches rows 16 wv .. 16 wv + 15 of a tile; keys beyond the context repeat the last one
     const int rowlane = 16 * wv + lane / C::DS, sl = lane % C::DS;
     const uint32_t part0 = 16u * (uint32_t)(sl ^ C::swz(rowlane));
@@ -338,13 +347,13 @@ __device__ __forceinline__ void stats_stream(const ScoreArgs& a, unsigned char* 
         if (r32 < k.cnt) reinterpret_cast<float2*>(a.part)[((int64_t)bk * a.parts + blockIdx.x) * (a.G * a.w) + k.start + r32] = v;
     }
 }
-// fp32 (short contexts): a workgroup per 128 keys, which it keeps in registers while the chunks of rows pass.
+// Per (row, key block) max and sum, the scores of a turn: a workgroup per 128 keys, which it keeps in registers while the chunks of rows pass.  grid (nkb, B*Hkv, shares of the
+// G heads).  part[(bk * nkb + kb) * G w + row].  (Ranges, as above, take 25 instead of 34 us at 32768 keys and 138 instead of 193 at 131072.  But another order of these sums moves a head's
+// last line now and then: of 256 heads of 16384 keys one in 250 got a line more or less, and with it rows of the output that are not the same any more.)
 template <typename T, int D>
-__global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 3 : 1)) void stats_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void stats_kernel(ScoreArgs a) {
     using RT = RowTile<T, D>;
     extern __shared__ __align__(16) unsigned char smem[];
-    if constexpr (Elem<T>::bytes == 2) { stats_stream<D>(a, smem); return; }
-    else {
     unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
     unsigned char* qs = smem;                              // [2] chunks of queries and
     float2 (*red)[4][32] = reinterpret_cast<float2 (*)[4][32]>(smem + 2 * RT::BYTES);   // [RED_CHUNKS] results of the waves
@@ -433,7 +442,6 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 3 : 1)) void 
             if (first < c1) __syncthreads();         // `red` is written again
         }
     }
-    }
 }
 
 // ---- merge: sixteen rows per workgroup; 64 threads of a row stride over the key blocks, then a fixed butterfly ----
@@ -510,9 +518,14 @@ __device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row,
     M = fmaxf(M, __shfl_xor(M, 1, 64));
     M = fmaxf(M, __shfl_xor(M, 2, 64));
 #pragma unroll
-    for (int u = 0; u < FOLD_PARTS / 4; ++u) L += v[u].x != -INFINITY ? v[u].y * fast_exp2(v[u].x - M) : 0.f;
-    L += __shfl_xor(L, 1, 64);
+    for (int u = 0; u < FOLD_PARTS / 4; ++u) v[u].y = v[u].x != -INFINITY ? v[u].y * fast_exp2(v[u].x - M) : 0.f;
+#pragma unroll
+    for (int off = FOLD_PARTS / 8; off > 0; off >>= 1)     // (merge_kernel's order)
+#pragma unroll
+        for (int u = 0; u < off; ++u) v[u].y += v[u + off].y;
+    L = v[0].y;
     L += __shfl_xor(L, 2, 64);
+    L += __shfl_xor(L, 1, 64);
     return make_float2(M, L > 0.f ? 1.0f / L : 0.f);
 }
 
@@ -616,8 +629,8 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
     unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
     float* slab = reinterpret_cast<float*>(smem);          // [SLAB_DIAGS][SLAB] A by diagonals (MODE 0) and
     unsigned char* qs = smem + (LINES ? SLAB_BYTES : 0);           // [2] chunks of queries
-    int32_t* ql = reinterpret_cast<int32_t*>(smem + lines_front<T, D>(MODE));    // [w] last visible key of a row, relative to the block (MODE 4: [4][G], see wtot)
-    float* rst = reinterpret_cast<float*>(ql + (MODE == 4 ? 4 * a.G : (a.w + 3) / 4 * 4));     // [2][32][2] max and 1 / sum of the chunks' rows (FOLD: of all chunks)
+    int32_t* ql = reinterpret_cast<int32_t*>(smem + lines_front<T, D>(MODE));    // [w] last visible key of a row, relative to the block
+    float* rst = reinterpret_cast<float*>(ql + (a.w + 3) / 4 * 4);     // [2][32][2] max and 1 / sum of the chunks' rows (FOLD: of all chunks)
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kb = blockIdx.x, bk = a.bk0 + blockIdx.y;
@@ -659,7 +672,6 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
     // every key of the block is visible to every row of a contiguous window (all but the last blocks)
     const bool open = a.q_pos == nullptr && blk0 + SB - 1 <= n - a.w;
     const int64_t omin = n - a.w - (blk0 + SB - 1);        // MODE 0, 4: this thread adds diagonal omin + tid of the slab (at most 255, w <= 128)
-    float* wtot = reinterpret_cast<float*>(ql);            // MODE 4: the four waves' column sums of each head
     float gsum = 0.f, vsum = 0.f, vmx = 0.f, dsum = 0.f, dmax = 0.f;
     wait_transfers();
     __syncthreads();
@@ -700,7 +712,7 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const int row = rq + e;
-                    float p = fast_exp2(__builtin_fmaf(s[4 * q4 + e], a.scale_log2e, -mm[e])) * il[e];
+                    float p = fast_exp2(MODE == 2 ? __builtin_fmaf(s[4 * q4 + e], a.scale_log2e, -mm[e]) : s[4 * q4 + e] * a.scale_log2e - mm[e]) * il[e];
                     if constexpr (decltype(MASKED)::value) {
                         if (LINES) p = (unsigned)(8 * q4 + e - see) < (unsigned)seen ? p : 0.f;
                         else {
@@ -749,14 +761,10 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         if (!(MODE == 2 && packed) && k.t0 + 32 >= ch.end) {   // the head's last chunk
             if (MODE == 2) gsum += vsum;
             if ((LINES || (MODE == 1 && a.sums)) && g == 0 && mykey < n) {
-                a.vert[(int64_t)bh * n + mykey] = vsum;
+                if (MODE == 4) put_shared(a.vert + (int64_t)bh * n + mykey, vsum); else a.vert[(int64_t)bh * n + mykey] = vsum;
                 a.vmax[(int64_t)bh * n + mykey] = vmx;
             }
             if (LINES) {
-                if (MODE == 4) {
-                    const float sum = wave_sum(g == 0 ? vsum : 0.f);
-                    if (lane == 0) wtot[4 * (bh - bh0) + wv] = sum;
-                }
                 const int64_t o = omin + tid;
                 if (tid < SB - 1 + a.w && o >= 0) {        // the first w - 1 the next block has too, those from SB on the one before
                     if (MODE != 4) reinterpret_cast<float2*>(a.spart)[((int64_t)(kb & 1) * a.BH + bh) * n + o] = make_float2(dsum, dmax);
@@ -771,49 +779,21 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
     }
     if (MODE == 2 && g == 0 && mykey < n) a.gscore[(int64_t)bk * n + mykey] = gsum;
     if constexpr (MODE == 4) {
-        // Of two neighbouring blocks the one that is done last adds the diagonals that they share, of all blocks the one that is done
-        // last the total; nobody waits for anybody.
-        __shared__ uint32_t met[2];                        // whether this block is done last of the one before and this one, and of this one and the next
+        // Of two neighbouring blocks the one that is done last adds the diagonals that they share, of a share's blocks the last one that share, of all
+        // the last one the total; nobody waits for anybody.
+        __shared__ uint32_t met[3];                        // how many were done before: of the block before and this one, of this one and the next, of the share
         const int heads = a.G / (int)gridDim.z, first = bh0 + heads * (int)blockIdx.z;
-        uint32_t* done = edge_done(a, bk, (int)blockIdx.z);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's sides are written
+        const int blocks = (int)(share_keys(n) / SB), part = kb / blocks, left = a.nkb - part * blocks;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's sides and columns are written
         __syncthreads();
-        if (wv == 0 && lane < 2) {
-            const int at = kb - 1 + lane;
-            met[lane] = at >= 0 && at < a.nkb - 1 ? count_shared(done + at) : 0u;
+        if (tid < 3) {
+            const int at = tid == 2 ? a.nkb - 1 + part : kb - 1 + tid;
+            met[tid] = tid == 2 || (at >= 0 && at < a.nkb - 1) ? count_shared(edge_done(a, bk, (int)blockIdx.z) + at) : 0u;
         }
-        if (wv == 3)                                       // (meanwhile: the total is this wave's)
-            for (int h = lane; h < heads; h += 64) {
-                const float* s4 = wtot + 4 * (first - bh0 + h);
-                put_shared(edge_total(a, first + h) + kb, (s4[0] + s4[1]) + (s4[2] + s4[3]));
-            }
         __syncthreads();
-        if (wv == 3) {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            int last = 0;
-            if (lane == 0) {
-                const int grp = kb / EDGE_GROUP, left = a.nkb - grp * EDGE_GROUP;
-                last = count_shared(done + a.nkb - 1 + grp) + 1u == (uint32_t)(left < EDGE_GROUP ? left : EDGE_GROUP) && count_shared(a.done + first) + 1u == (uint32_t)edge_groups(a.nkb);
-            }
-            if (__builtin_amdgcn_readfirstlane(last) == 0) return;
-            for (int h = 0; h < heads; ++h) {                  // in a fixed order: a lane every 64th block, then the lanes
-                const float* t = edge_total(a, first + h);
-                float sum = 0.f;
-                for (int i0 = lane; i0 < a.nkb; i0 += 4 * 64) {
-                    float v[4];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = get_shared(t + (i0 + 64 * e < a.nkb ? i0 + 64 * e : lane));
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) if (i0 + 64 * e < a.nkb) sum += v[e];
-                }
-                sum = wave_sum(sum);
-                if (lane == 0) a.total[first + h] = sum;
-            }
-            return;
-        }
         const int each = a.w - 1, all = heads * each;
         const bool take[2] = {met[0] == 1u, met[1] == 1u};
-        constexpr int NT = SCORE_THREADS - 64, U = 3;      // (all of a side's reads at once for four heads of 128 rows)
+        constexpr int NT = SCORE_THREADS, U = 2;           // (all of a side's reads at once for four heads of 128 rows)
         for (int i0 = tid; i0 < all; i0 += U * NT) {
             float2 x[2][U], y[2][U];
             int h[U], u[U];
@@ -842,6 +822,36 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
                     a.smax[(int64_t)(first + h[e]) * n + o0 + u[e]] = fmaxf(x[side][e].y, y[side][e].y);
                 }
             }
+        }
+        if (met[2] + 1u != (uint32_t)(left < blocks ? left : blocks)) return;
+        for (int h = wv; h < heads; h += 4) {
+            const float* col = a.vert + (int64_t)(first + h) * n;
+            const int64_t beg = (int64_t)part * share_keys(n), end = beg + share_keys(n) < n ? beg + share_keys(n) : n;
+            float r[16];
+#pragma unroll
+            for (int w = 0; w < 16; ++w) r[w] = 0.f;
+            for (int64_t i0 = beg + lane; i0 - lane < end; i0 += 1024) {
+                float v[16];
+#pragma unroll
+                for (int w = 0; w < 16; ++w) v[w] = get_shared(col + (i0 + 64 * w < end ? i0 + 64 * w : beg));
+#pragma unroll
+                for (int w = 0; w < 16; ++w) if (i0 + 64 * w < end) r[w] += v[w];
+            }
+            const float share = share_of(r);
+            if (lane == 0) put_shared(edge_share(a, first + h) + part, share);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        if (wv > 0) return;
+        const int groups = edge_groups(a);
+        int last = 0;
+        if (lane == 0) last = count_shared(a.done + first) + 1u == (uint32_t)groups;
+        if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+        for (int h = lane; h < heads; h += 64) {
+            float p[FINISH_SPLIT];
+#pragma unroll
+            for (int i = 0; i < FINISH_SPLIT; ++i) p[i] = i < groups ? get_shared(edge_share(a, first + h) + i) : 0.f;
+            a.total[first + h] = total_of(p);
         }
     }
 }
@@ -878,12 +888,11 @@ __global__ __launch_bounds__(256) void diagonals_kernel(ScoreArgs a) {
 // grid (B*Hq, FINISH_SPLIT).  Diagonal o is met by keys n-w-o .. n-1-o (clipped at 0), i.e. by key blocks
 // kA = max(0, n-w-o)/SB and kB = (n-1-o)/SB, which are equal or adjacent.  The last of a head's workgroups to get to its
 // end (a counter per head, which stats_kernel has cleared) adds their shares of the total, in a fixed tree order.
-constexpr int FINISH_SPLIT = 8;            // workgroups per head (a head alone is a string of load round trips)
 __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguous) {
     __shared__ float red[1024];
     const int bh = blockIdx.x, part = blockIdx.y, tid = threadIdx.x;
     const int64_t n = a.n;
-    const int64_t per = ((n + FINISH_SPLIT - 1) / FINISH_SPLIT + 1023) / 1024 * 1024;   // this workgroup's range, whole rounds of threads
+    const int64_t per = share_keys(n);                     // this workgroup's range
     const int64_t beg = (int64_t)part * per, end = beg + per < n ? beg + per : n;
     // (asked for ahead of the diagonals' partials: one round trip for both)
     float v4[4];
@@ -928,11 +937,7 @@ __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguou
     float r[16];
 #pragma unroll
     for (int w = 0; w < 16; ++w) r[w] = red[64 * w + tid];
-#pragma unroll
-    for (int s = 8; s > 0; s >>= 1)
-#pragma unroll
-        for (int w = 0; w < s; ++w) r[w] += r[w + s];
-    acc = wave_sum(r[0]);
+    acc = share_of(r);
     if (tid == 0) {
         float* share = a.part + (int64_t)bh * FINISH_SPLIT;            // `part` is free again once merge_kernel has run
         put_shared(share + part, acc);
@@ -941,7 +946,7 @@ __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguou
             float p[FINISH_SPLIT];
 #pragma unroll
             for (int i = 0; i < FINISH_SPLIT; ++i) p[i] = get_shared(share + i);
-            a.total[bh] = ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+            a.total[bh] = total_of(p);
         }
     }
 }
@@ -963,15 +968,15 @@ static int head_shares(const ScoreArgs& a, int kv_heads) {
 // finish_kernel / so, us: 1024 keys, fp32, 17.2 / 14.2; 32 heads, 64 rows, of 2048 keys 21.0 / 17.8, 8192 34.3 / 31.3, 61 of 12347 (1552 workgroups) 45.2 / 44.3; 16 heads of 64, 48 rows
 // of 5003 keys 23.9 / 19.4; more of them: sixteen chunks each 455 / 453 to 469 (128 rows of 131072), eight 82.4 / 81.7 and 89.3 / 90.6, four 90 / 94, two 35.1 / 37.7, one 31.6 /
 // 33.5 (20000 keys), 66 / 82 (32 KV heads of 32768).
-static bool joins(const ScoreArgs& a, int kv_heads) { return (int64_t)a.nkb * kv_heads * a.shares <= 1600; }
+static bool joins(const ScoreArgs& a, int kv_heads) { return (int64_t)a.nkb * kv_heads * a.shares <= 1600 && a.n <= 16384; }
 // Ranges of keys whose statistics are kept apart: as many as fill the chip with three workgroups a CU
 // (more than 64 cost merge_kernel what they save); no more than the blocks of 128 keys that `part` has room for.  Few rows a workgroup where there
 // is little work: eight / four / two chunks of rows, us, 131072 keys 140 / 157, 16384 keys, B 4, 75 / 81, 32768 24.0 / 24.4, 12347 16.0 / 13.8, 5003 of d = 64
 // 10.2 / 8.0 / 7.3.
 constexpr int STATS_PARTS = 64;
-static void stats_split(ScoreArgs& a, bool bf16) {
+static void stats_split(ScoreArgs& a, bool ranges) {
     a.parts = a.nkb; a.stat_chunks = STATS_CHUNKS;
-    if (!bf16) return;
+    if (!ranges) return;
     const int count = Chunks(a.w, a.G, packs(a.w)).count;
     const int64_t work = (int64_t)a.B * a.Hkv * a.nkb * count;       // 128 keys by 32 rows
     if (work <= 24576) a.stat_chunks = work < 2560 ? 2 : 4;
@@ -980,14 +985,16 @@ static void stats_split(ScoreArgs& a, bool bf16) {
     a.parts = r < a.nkb ? r : a.nkb;
 }
 template <typename T, int D>
-static void launch_stats(const ScoreArgs& a, hipStream_t st) {
+static void launch_stats(const ScoreArgs& a, bool ranges, hipStream_t st) {
     if constexpr (Elem<T>::bytes == 2) {
-        const int z = (Chunks(a.w, a.G, packs(a.w)).count + a.stat_chunks - 1) / a.stat_chunks;
-        hipLaunchKernelGGL((stats_kernel<T, D>), dim3(a.parts, a.B * a.Hkv, z), dim3(SCORE_THREADS), stats_lds<D>(), st, a);
-    } else {
-        const size_t smem = stats_front<T, D>() + (size_t)a.w * 4;
-        hipLaunchKernelGGL((stats_kernel<T, D>), dim3(a.nkb, a.B * a.Hkv, packs(a.w) ? 1 : head_shares(a, a.B * a.Hkv)), dim3(SCORE_THREADS), smem, st, a);
+        if (ranges) {
+            const int z = (Chunks(a.w, a.G, packs(a.w)).count + a.stat_chunks - 1) / a.stat_chunks;
+            hipLaunchKernelGGL((range_stats_kernel<D>), dim3(a.parts, a.B * a.Hkv, z), dim3(SCORE_THREADS), stats_lds<D>(), st, a);
+            return;
+        }
     }
+    const size_t smem = stats_front<T, D>() + (size_t)a.w * 4;
+    hipLaunchKernelGGL((stats_kernel<T, D>), dim3(a.nkb, a.B * a.Hkv, packs(a.w) ? 1 : head_shares(a, a.B * a.Hkv)), dim3(SCORE_THREADS), smem, st, a);
 }
 // whether lines_kernel merges the statistics (of all KV heads: bands of explicit positions do it again)
 static bool folds(const ScoreArgs& a, int mode) {
@@ -997,7 +1004,7 @@ static bool folds(const ScoreArgs& a, int mode) {
 template <typename T, int D, int MODE>
 static void launch_lines(const ScoreArgs& a, int kv_heads, hipStream_t st) {
     const bool fold = folds(a, MODE);
-    const size_t smem = lines_front<T, D>(MODE) + (MODE == 4 ? (size_t)a.G * 16 : (size_t)(a.w + 3) / 4 * 16) + (fold ? (size_t)score_chunks(a) * 256 : 512);
+    const size_t smem = lines_front<T, D>(MODE) + (size_t)(a.w + 3) / 4 * 16 + (fold ? (size_t)score_chunks(a) * 256 : 512);
     const dim3 grid(a.nkb, kv_heads, MODE == 2 ? 1 : head_shares(a, kv_heads));
     if (fold) hipLaunchKernelGGL((lines_kernel<T, D, MODE, true>), grid, dim3(SCORE_THREADS), smem, st, a);
     else hipLaunchKernelGGL((lines_kernel<T, D, MODE, false>), grid, dim3(SCORE_THREADS), smem, st, a);
@@ -1024,8 +1031,9 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     const int BK = a.B * a.Hkv;
     a.t0 = 0; a.t1 = a.w;
     if (mode == 0) { a.shares = head_shares(a, BK); a.join = joins(a, BK); }
-    stats_split(a, Elem<T>::bytes == 2);
-    launch_stats<T, D>(a, st);
+    const bool ranges = mode == 2 && Elem<T>::bytes == 2;
+    stats_split(a, ranges);
+    launch_stats<T, D>(a, ranges, st);
     if (!folds(a, mode)) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {
         if (a.join) {
@@ -1068,6 +1076,7 @@ template <typename T, int D>
 static hipError_t init_score_t() {
     hipError_t e;
     if ((e = allow_full_lds(&stats_kernel<T, D>)) != hipSuccess) return e;
+    if constexpr (Elem<T>::bytes == 2) if ((e = allow_full_lds(&range_stats_kernel<D>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 0, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 0, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 4, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 4, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 1, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 1, true>)) != hipSuccess) return e;
