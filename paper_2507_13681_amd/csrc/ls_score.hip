@@ -6,19 +6,19 @@
 //
 // The softmax normaliser of a row is only known after all keys were seen, and the line sums mix
 // rows with different normalisers, so the pass is split:
-//   stats_kernel   per (row, range of keys): a reference and the sum of exp of the scaled logits against it;
+//   stats_kernel, range_stats_kernel   per (row, 128 keys), for the retention score per (row, range of keys): a reference and the sum of exp of the scaled logits against it;
 //   merge_kernel   per row: global max m and 1/l;
 //   lines_kernel   recomputes the logits, forms A = exp2(x - m) / l, and reduces it
 //                  - over rows, in registers, to column sums / maxima (written once, in order);
 //                  - over diagonals through an LDS copy of 32 rows of the 128-key slab at a time, one
 //                    thread per diagonal adding the rows in fixed order; a diagonal crosses at most two
-//                    key blocks, whose two partial results finish_kernel adds.
+//                    key blocks, whose two partial results finish_kernel adds, or the block of the two that is done last.
 // With explicit scoring positions (q_pos given) the diagonals of a slab are not a contiguous range: the
 // matrix A is then written out, band by band of as many KV heads and rows as the workspace takes, and
 // diagonals_kernel adds each diagonal's cells in row order, on from where the band before it stopped.
 // Everything is summed in a fixed order, so results are bit-reproducible from run to run.
 //
-// Tile products run on 32x32 MFMA.  In lines_kernel (and stats_kernel in fp32) each wave owns 32 keys of a block, whose fragments it keeps in
+// Tile products run on 32x32 MFMA.  In lines_kernel and stats_kernel each wave owns 32 keys of a block, whose fragments it keeps in
 // registers, and meets every query head of the KV group and every 32-row group with them.  Those chunks of 32 query rows
 // come through LDS by global -> LDS transfers, two buffers, one barrier per chunk.  K rows go through LDS on
 // their way to the registers as well: read straight from global memory a fragment load touches 32 rows with
@@ -186,7 +186,9 @@ constexpr float STATS_LIMIT = 1073741824.f;
 template <int D>
 __host__ __device__ constexpr int stats_lds() { return KeyTile<D>::BUFFERS * KeyTile<D>::BYTES; }
 
-template <int D>
+//
+// BLOCKS (the scores of a turn): the same way past the keys, but statistics of every 128 keys, in stats_kernel's operations and order (stats_split).
+template <int D, bool BLOCKS>
 __global__ __launch_bounds__(SCORE_THREADS, 3) void range_stats_kernel(ScoreArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     using C = KeyTile<D>;
@@ -203,13 +205,18 @@ __global__ __launch_bounds__(SCORE_THREADS, 3) void range_stats_kernel(ScoreArgs
     const Chunks ch(a.w, a.G, packs(a.w));
     const int c0 = a.stat_chunks * (int)blockIdx.z, here = ch.count - c0 < a.stat_chunks ? ch.count - c0 : a.stat_chunks;
     // rows: waves side by side on chunks; few chunks: two waves share one, a half of each tile each (of one chunk, two waves only read K)
-    const int rw = here > 2 ? 4 : here, kw = here > 2 ? 1 : 2;
+    const int rw = here > 2 ? 4 : here, kw = BLOCKS || here > 2 ? 1 : 2;
     const int kh = wv / rw;                                // where they share: this wave's half
     const bool works = kh < kw && wv % rw < here;          // (of three chunks, the fourth wave only reads K)
     const int cw = works ? wv % rw : 0;                    // its first chunk
     const int mine = !works ? 0 : cw + rw < here ? 2 : 1;  // chunks cw, cw + 4
     const uint32_t nt = (uint32_t)((n + C::KEYS - 1) / C::KEYS);                  // (fewer than 2^16, and ranges fewer than 2^8)
-    const int t0 = (int)(nt * blockIdx.x / gridDim.x), t1 = (int)(nt * (blockIdx.x + 1) / gridDim.x);
+    int t0 = (int)(nt * blockIdx.x / gridDim.x), t1 = (int)(nt * (blockIdx.x + 1) / gridDim.x);
+    if (BLOCKS) {                                          // whole blocks
+        t0 = 2 * (int)((uint32_t)a.nkb * blockIdx.x / gridDim.x); t1 = 2 * (int)((uint32_t)a.nkb * (blockIdx.x + 1) / gridDim.x);
+        if (t1 > (int)nt) t1 = (int)nt;
+        if (blockIdx.x == 0 && blockIdx.z == 0) clear_counters(a, bk, tid);
+    }
 
     // ---- transfers: wave wv fetches rows 16 wv .. 16 wv + 15 of a tile; keys beyond the context repeat the last one
     const int rowlane = 16 * wv + lane / C::DS, sl = lane % C::DS;
@@ -233,11 +240,12 @@ __global__ __launch_bounds__(SCORE_THREADS, 3) void range_stats_kernel(ScoreArgs
 #pragma unroll
     for (int j = 0; j < C::KA; ++j) kaddr[j] = (r32 / C::RPI) * C::ISTR + (r32 % C::RPI) * C::RB + 32 * (j ^ (x >> 1)) + 16 * (g ^ (x & 1));
     Frag<T> q[2][NS];
-    int pos[2];
+    int pos[2], start[2], cnt[2];
     const uint32_t stage = (uint32_t)__builtin_amdgcn_readfirstlane((int)(lds_address(smem) + (uint32_t)(C::BYTES + wv * C::HALF)));
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const Chunk k = ch.at(c0 + (i < mine ? cw + rw * i : cw));
+        start[i] = k.start; cnt[i] = k.cnt;
         if (i == 0 || mine == 2) {
             const unsigned char* src = uniform_ptr(Q0 + (int64_t)k.start * C::RB);
 #pragma unroll
@@ -259,6 +267,8 @@ __global__ __launch_bounds__(SCORE_THREADS, 3) void range_stats_kernel(ScoreArgs
     if (t0 + 1 < t1) fetch(t0 + 1, 1);
     const float sc = a.scale_log2e;
     float mneg[2] = {INFINITY, INFINITY}, l[2] = {0.f, 0.f};      // reference of the lane's row in base 2, negated (+inf: no cell seen yet), and the sum against it
+    // BLOCKS: {max, sum} of a block's halves of 32 keys, those of its first tile and those of its second; a lane of the first 32 has the first half of each, one of the others the second
+    float2 one[2], two[2] = {make_float2(-INFINITY, 0.f), make_float2(-INFINITY, 0.f)};
     int buf = 0;
     for (int t = t0; t < t1; ++t) {
         // this wave's transfers of tile t have landed (those of the next are under way), and every wave is done with the tile before
@@ -298,6 +308,19 @@ __global__ __launch_bounds__(SCORE_THREADS, 3) void range_stats_kernel(ScoreArgs
 #pragma unroll
                     for (int r = 0; r < 16; ++r) if (8 * (r >> 2) + (r & 3) > lim) s[i][r] = -INFINITY;
                 }
+                if constexpr (BLOCKS) {
+                    float mx = -INFINITY;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) { s[i][r] *= sc; mx = fmaxf(mx, s[i][r]); }
+                    mx = halves_max(mx);
+                    const float ms = mx == -INFINITY ? 0.f : mx;
+                    float sum = 0.f;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) sum += fast_exp2(s[i][r] - ms);
+                    sum = halves_sum(sum);
+                    if (g == h) two[i] = make_float2(mx, sum);
+                    continue;
+                }
                 float s0 = 0.f, s1 = 0.f;
 #pragma unroll
                 for (int r = 0; r < 16; r += 2) {
@@ -324,8 +347,25 @@ __global__ __launch_bounds__(SCORE_THREADS, 3) void range_stats_kernel(ScoreArgs
         if (mine == 2) { if (open) tile(std::true_type{}, std::true_type{}); else tile(std::true_type{}, std::false_type{}); }
         else if (mine == 1) { if (open) tile(std::false_type{}, std::true_type{}); else tile(std::false_type{}, std::false_type{}); }
         buf = buf + 1 < 3 ? buf + 1 : 0;
+        if (BLOCKS) {
+            if ((t & 1) == 0) { one[0] = two[0]; one[1] = two[1]; two[0] = two[1] = make_float2(-INFINITY, 0.f); }
+            if ((t & 1) != 0 || t + 1 == t1) {             // the block's last tile: four halves, in order
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    if (i >= mine) break;
+                    const float M = halves_max(fmaxf(one[i].x, two[i].x)), Ms = M == -INFINITY ? 0.f : M;
+                    const float u = one[i].y * fast_exp2(one[i].x - Ms), v = two[i].y * fast_exp2(two[i].x - Ms);
+                    const auto uu = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, u), __builtin_bit_cast(uint32_t, u), false, false);
+                    const auto vv = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), false, false);
+                    const float L = ((__builtin_bit_cast(float, (uint32_t)uu[0]) + __builtin_bit_cast(float, (uint32_t)uu[1])) + __builtin_bit_cast(float, (uint32_t)vv[0])) + __builtin_bit_cast(float, (uint32_t)vv[1]);
+                    if (lane < cnt[i]) reinterpret_cast<float2*>(a.part)[((int64_t)bk * a.nkb + (t >> 1)) * (a.G * a.w) + start[i] + lane] = make_float2(M, L);
+                    two[i] = make_float2(-INFINITY, 0.f);
+                }
+            }
+        }
     }
     wait_transfers();                                      // (none is under way)
+    if (BLOCKS) return;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -347,9 +387,9 @@ __global__ __launch_bounds__(SCORE_THREADS, 3) void range_stats_kernel(ScoreArgs
         if (r32 < k.cnt) reinterpret_cast<float2*>(a.part)[((int64_t)bk * a.parts + blockIdx.x) * (a.G * a.w) + k.start + r32] = v;
     }
 }
-// Per (row, key block) max and sum, the scores of a turn: a workgroup per 128 keys, which it keeps in registers while the chunks of rows pass.  grid (nkb, B*Hkv, shares of the
-// G heads).  part[(bk * nkb + kb) * G w + row].  (Ranges, as above, take 25 instead of 34 us at 32768 keys and 138 instead of 193 at 131072.  But another order of these sums moves a head's
-// last line now and then: of 256 heads of 16384 keys one in 250 got a line more or less, and with it rows of the output that are not the same any more.)
+// Per (row, key block) max and sum, the scores of short turns and of fp32: a workgroup per 128 keys, which it keeps in registers while the chunks of rows pass.  grid (nkb, B*Hkv, shares
+// of the G heads).  part[(bk * nkb + kb) * G w + row].  (These sums are taken in one order, whichever kernel does it: another one, as the retention score's, moves a head's last line now and
+// then, of 256 heads of 16384 keys one in 250, of 32 of 131072 one in 30, and with it rows of the output that are not the same any more.)
 template <typename T, int D>
 __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void stats_kernel(ScoreArgs a) {
     using RT = RowTile<T, D>;
@@ -965,31 +1005,39 @@ static int head_shares(const ScoreArgs& a, int kv_heads) {
 }
 // Whether lines_kernel adds what neighbouring key blocks have of a diagonal, and the totals, itself.  That saves finish_kernel's launch and round trips, and costs a
 // workgroup three round trips at its end, in which others of its CU have to keep it busy: where nearly all are there at once (1024 are).
-// finish_kernel / so, us: 1024 keys, fp32, 17.2 / 14.2; 32 heads, 64 rows, of 2048 keys 21.0 / 17.8, 8192 34.3 / 31.3, 61 of 12347 (1552 workgroups) 45.2 / 44.3; 16 heads of 64, 48 rows
-// of 5003 keys 23.9 / 19.4; more of them: sixteen chunks each 455 / 453 to 469 (128 rows of 131072), eight 82.4 / 81.7 and 89.3 / 90.6, four 90 / 94, two 35.1 / 37.7, one 31.6 /
-// 33.5 (20000 keys), 66 / 82 (32 KV heads of 32768).
+// finish_kernel / so, us: 1024 keys, fp32, 17.0 / 15.5; 32 heads, 64 rows, of 2048 keys 20.8 / 19.5, 8192 36.9 / 32.8; 16 heads of 64, 48 rows
+// of 5003 keys 23.9 / 20.4; more of them: eight chunks each 82.4 / 81.7 and 89.3 / 90.6, four 90 / 94, two 35.1 / 37.7, one 31.6 /
+// 33.5 (20000 keys), 66 / 82 (32 KV heads of 32768).  Beyond 16384 keys a share of the total is more than two reads a lane.
 static bool joins(const ScoreArgs& a, int kv_heads) { return (int64_t)a.nkb * kv_heads * a.shares <= 1600 && a.n <= 16384; }
 // Ranges of keys whose statistics are kept apart: as many as fill the chip with three workgroups a CU
 // (more than 64 cost merge_kernel what they save); no more than the blocks of 128 keys that `part` has room for.  Few rows a workgroup where there
 // is little work: eight / four / two chunks of rows, us, 131072 keys 140 / 157, 16384 keys, B 4, 75 / 81, 32768 24.0 / 24.4, 12347 16.0 / 13.8, 5003 of d = 64
 // 10.2 / 8.0 / 7.3.
 constexpr int STATS_PARTS = 64;
-static void stats_split(ScoreArgs& a, bool ranges) {
+// The ranges of keys of range_stats_kernel; 0: stats_kernel, for the scores of turns too short to fill the chip with ranges, or of so few rows that waves would stand idle.
+// ls_score, stats_kernel / range_stats_kernel, us: 8192 keys, 32 heads, 64 rows (4096 of the products below) 32.8 / 33.8, 12347 (6208) 48.5 / 48.6, 131072, 16 heads of 64, 32 rows (16384)
+// 85.1 / 83.4, 4 heads, 100 rows 91.6 / 86.6, 32768, 32 heads 88.5 / 82.9, 131072, 128 rows 508 / 486, 16384, B 4, 64 heads 274 / 262.
+static int stats_split(ScoreArgs& a, bool bf16, bool retention) {
     a.parts = a.nkb; a.stat_chunks = STATS_CHUNKS;
-    if (!ranges) return;
+    if (!bf16) return 0;
     const int count = Chunks(a.w, a.G, packs(a.w)).count;
     const int64_t work = (int64_t)a.B * a.Hkv * a.nkb * count;       // 128 keys by 32 rows
     if (work <= 24576) a.stat_chunks = work < 2560 ? 2 : 4;
     int r = 768 / (a.B * a.Hkv * ((count + a.stat_chunks - 1) / a.stat_chunks));
-    r = r > STATS_PARTS ? STATS_PARTS : r < 1 ? 1 : r;
-    a.parts = r < a.nkb ? r : a.nkb;
+    if (retention) r = r > STATS_PARTS ? STATS_PARTS : r;
+    r = r < 1 ? 1 : r < a.nkb ? r : a.nkb;
+    if (retention) a.parts = r;
+    else if (work < 8192 || count < 3) return 0;
+    return r;
 }
 template <typename T, int D>
-static void launch_stats(const ScoreArgs& a, bool ranges, hipStream_t st) {
+static void launch_stats(const ScoreArgs& a, int ranges, bool retention, hipStream_t st) {
     if constexpr (Elem<T>::bytes == 2) {
-        if (ranges) {
+        if (ranges > 0) {
             const int z = (Chunks(a.w, a.G, packs(a.w)).count + a.stat_chunks - 1) / a.stat_chunks;
-            hipLaunchKernelGGL((range_stats_kernel<D>), dim3(a.parts, a.B * a.Hkv, z), dim3(SCORE_THREADS), stats_lds<D>(), st, a);
+            const dim3 grid(ranges, a.B * a.Hkv, z);
+            if (retention) hipLaunchKernelGGL((range_stats_kernel<D, false>), grid, dim3(SCORE_THREADS), stats_lds<D>(), st, a);
+            else hipLaunchKernelGGL((range_stats_kernel<D, true>), grid, dim3(SCORE_THREADS), stats_lds<D>(), st, a);
             return;
         }
     }
@@ -1031,9 +1079,7 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     const int BK = a.B * a.Hkv;
     a.t0 = 0; a.t1 = a.w;
     if (mode == 0) { a.shares = head_shares(a, BK); a.join = joins(a, BK); }
-    const bool ranges = mode == 2 && Elem<T>::bytes == 2;
-    stats_split(a, ranges);
-    launch_stats<T, D>(a, ranges, st);
+    launch_stats<T, D>(a, stats_split(a, Elem<T>::bytes == 2, mode == 2), mode == 2, st);
     if (!folds(a, mode)) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {
         if (a.join) {
@@ -1076,7 +1122,8 @@ template <typename T, int D>
 static hipError_t init_score_t() {
     hipError_t e;
     if ((e = allow_full_lds(&stats_kernel<T, D>)) != hipSuccess) return e;
-    if constexpr (Elem<T>::bytes == 2) if ((e = allow_full_lds(&range_stats_kernel<D>)) != hipSuccess) return e;
+    if constexpr (Elem<T>::bytes == 2)
+        if ((e = allow_full_lds(&range_stats_kernel<D, false>)) != hipSuccess || (e = allow_full_lds(&range_stats_kernel<D, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 0, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 0, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 4, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 4, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 1, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 1, true>)) != hipSuccess) return e;

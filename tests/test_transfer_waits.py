@@ -74,7 +74,7 @@ def test_path_search_sees_a_missing_wait():
 KERNELS = {
     "ls_decode.hip": [("decode_kernelI", 4, 0)],
     "ls_prefill.hip": [("prefill_bf16_kernelI", 4, 0)],
-    "ls_score.hip": [("stats_kernelI", 4, 1), ("range_stats_kernelI", 2, 1), (r"lines_kernelI\w+Li0ELb", 8, 1), (r"lines_kernelI\w+Li4ELb", 8, 1), (r"lines_kernelI\w+Li[123]ELb", 24, 0)],
+    "ls_score.hip": [("stats_kernelI", 4, 1), ("range_stats_kernelI", 4, 1), (r"lines_kernelI\w+Li0ELb", 8, 1), (r"lines_kernelI\w+Li4ELb", 8, 1), (r"lines_kernelI\w+Li[123]ELb", 24, 0)],
 }
 
 
