@@ -536,36 +536,42 @@ __global__ __launch_bounds__(1024) void merge_kernel(ScoreArgs a) {
 constexpr int FOLD_PARTS = 64, FOLD_CHUNKS = 32;
 constexpr int64_t FOLD_BYTES = 4 << 20;
 static int score_chunks(const ScoreArgs& a) { return a.G * ((a.w + 31) / 32); }           // at most: packed windows take fewer
-// Four neighbouring lanes share a row's ranges; all of them get {max, 1 / sum}.
+// LANES neighbouring lanes (one or four) share a row's ranges, sixteen each at most; all of them get {max, 1 / sum}.
+template <int LANES>
 __device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row, int part) {
+    constexpr int PER = 16;
     const int rows = a.G * a.w;
     const float2* p = reinterpret_cast<const float2*>(a.part) + (int64_t)bk * a.parts * rows + row;
-    float2 v[FOLD_PARTS / 4];
-    float M = -INFINITY, L = 0.f;
+    float2 v[PER];
+    float M = -INFINITY;
 #pragma unroll
-    for (int q = 0; q < FOLD_PARTS / 16; ++q) {            // as many loads at once as there are ranges
+    for (int q = 0; q < PER / 4; ++q) {                    // as many loads at once as there are ranges
 #pragma unroll
         for (int u = 4 * q; u < 4 * q + 4; ++u) v[u] = make_float2(-INFINITY, 0.f);
-        if (16 * q < a.parts) {
+        if (4 * LANES * q < a.parts) {
 #pragma unroll
-            for (int u = 4 * q; u < 4 * q + 4; ++u) v[u] = p[(int64_t)(4 * u + part < a.parts ? 4 * u + part : 0) * rows];
+            for (int u = 4 * q; u < 4 * q + 4; ++u) v[u] = p[(int64_t)(LANES * u + part < a.parts ? LANES * u + part : 0) * rows];
         }
     }
 #pragma unroll
-    for (int u = 0; u < FOLD_PARTS / 4; ++u) if (4 * u + part >= a.parts) v[u] = make_float2(-INFINITY, 0.f);
+    for (int u = 0; u < PER; ++u) if (LANES * u + part >= a.parts) v[u] = make_float2(-INFINITY, 0.f);
 #pragma unroll
-    for (int u = 0; u < FOLD_PARTS / 4; ++u) M = fmaxf(M, v[u].x);
-    M = fmaxf(M, __shfl_xor(M, 1, 64));
-    M = fmaxf(M, __shfl_xor(M, 2, 64));
+    for (int u = 0; u < PER; ++u) M = fmaxf(M, v[u].x);
+    if (LANES == 4) {
+        M = fmaxf(M, __shfl_xor(M, 1, 64));
+        M = fmaxf(M, __shfl_xor(M, 2, 64));
+    }
 #pragma unroll
-    for (int u = 0; u < FOLD_PARTS / 4; ++u) v[u].y = v[u].x != -INFINITY ? v[u].y * fast_exp2(v[u].x - M) : 0.f;
+    for (int u = 0; u < PER; ++u) v[u].y = v[u].x != -INFINITY ? v[u].y * fast_exp2(v[u].x - M) : 0.f;
 #pragma unroll
-    for (int off = FOLD_PARTS / 8; off > 0; off >>= 1)     // (merge_kernel's order)
+    for (int off = PER / 2; off > 0; off >>= 1)            // (merge_kernel's order)
 #pragma unroll
         for (int u = 0; u < off; ++u) v[u].y += v[u + off].y;
-    L = v[0].y;
-    L += __shfl_xor(L, 2, 64);
-    L += __shfl_xor(L, 1, 64);
+    float L = v[0].y;
+    if (LANES == 4) {
+        L += __shfl_xor(L, 2, 64);
+        L += __shfl_xor(L, 1, 64);
+    }
     return make_float2(M, L > 0.f ? 1.0f / L : 0.f);
 }
 
@@ -696,13 +702,19 @@ __global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void 
         const int64_t rel = position_of(a, t) - blk0;      // key klocal of the block is visible to row t iff klocal <= rel
         ql[t] = rel < -1 ? -1 : (rel > SB ? SB : (int32_t)rel);
     }
-    if (FOLD)
-        for (int i4 = tid; i4 < 128 * (c1 - c0); i4 += SCORE_THREADS) {
-            const int i = i4 >> 2;
-            const Chunk k = ch.at(c0 + i / 32);
-            const float2 st = row_stats(a, bk, k.start + (i % 32 < k.cnt ? i % 32 : k.cnt - 1), i4 & 3);
-            if ((i4 & 3) == 0) reinterpret_cast<float2*>(rst)[i] = st;
-        }
+    if (FOLD) {
+        auto stats = [&](auto LANES) {
+            constexpr int N = decltype(LANES)::value;
+            for (int i0 = tid; i0 < 32 * N * (c1 - c0); i0 += SCORE_THREADS) {
+                const int i = i0 / N;
+                const Chunk k = ch.at(c0 + i / 32);
+                const float2 st = row_stats<N>(a, bk, k.start + (i % 32 < k.cnt ? i % 32 : k.cnt - 1), i0 % N);
+                if (i0 % N == 0) reinterpret_cast<float2*>(rst)[i] = st;
+            }
+        };
+        // (256 rows of 16 ranges by four lanes a row: the whole retention of 2048 entries 27.2 us instead of 25.1)
+        if (a.parts <= 16) stats(std::integral_constant<int, 1>{}); else stats(std::integral_constant<int, 4>{});
+    }
     Frag<T> kf[D / 16];
     k_frags<T, D>(kf, Kg, blk0 + 32 * wv, n, kst + wv * RT::BYTES, lane);
     __syncthreads();
@@ -1009,25 +1021,24 @@ static int head_shares(const ScoreArgs& a, int kv_heads) {
 // of 5003 keys 23.9 / 20.4; more of them: eight chunks each 82.4 / 81.7 and 89.3 / 90.6, four 90 / 94, two 35.1 / 37.7, one 31.6 /
 // 33.5 (20000 keys), 66 / 82 (32 KV heads of 32768).  Beyond 16384 keys a share of the total is more than two reads a lane.
 static bool joins(const ScoreArgs& a, int kv_heads) { return (int64_t)a.nkb * kv_heads * a.shares <= 1600 && a.n <= 16384; }
-// Ranges of keys whose statistics are kept apart: as many as fill the chip with three workgroups a CU
-// (more than 64 cost merge_kernel what they save); no more than the blocks of 128 keys that `part` has room for.  Few rows a workgroup where there
-// is little work: eight / four / two chunks of rows, us, 131072 keys 140 / 157, 16384 keys, B 4, 75 / 81, 32768 24.0 / 24.4, 12347 16.0 / 13.8, 5003 of d = 64
-// 10.2 / 8.0 / 7.3.
-constexpr int STATS_PARTS = 64;
-// The ranges of keys of range_stats_kernel; 0: stats_kernel, for the scores of turns too short to fill the chip with ranges, or of so few rows that waves would stand idle.
-// ls_score, stats_kernel / range_stats_kernel, us: 8192 keys, 32 heads, 64 rows (4096 of the products below) 32.8 / 33.8, 12347 (6208) 48.5 / 48.6, 131072, 16 heads of 64, 32 rows (16384)
+// The ranges of keys of range_stats_kernel; 0: stats_kernel, where there is little work, or so few rows that waves would stand idle.
+// As many as fill the chip with three workgroups a CU; for the retention score, which keeps their statistics apart, 64 at most (more cost merge_kernel what they save) and no
+// more than the blocks of 128 keys that `part` has room for.  Four chunks of rows a workgroup, eight where there is much work: eight / four, us, 131072 keys 140 / 157, 16384 keys, B 4, 75 / 81, 32768
+// 24.0 / 24.4, 12347 16.0 / 13.8.
+// The lines.  The kernels, stats_kernel / range_stats_kernel, us, retention score of 16 rows: 8 heads, 16384 keys (1024 of the products below) 5.9 / 9.3, 32 / 8 heads (2048) 8.5 / 9.6, 32768 keys (4096)
+// 16.9 / 13.9, 4 / 1 heads, 32768 (512) 5.1 / 8.8.  ls_score: 8192 keys, 32 heads, 64 rows (4096) 32.8 / 33.8, 12347 (6208) 48.5 / 48.6, 131072, 16 heads of 64, 32 rows (16384)
 // 85.1 / 83.4, 4 heads, 100 rows 91.6 / 86.6, 32768, 32 heads 88.5 / 82.9, 131072, 128 rows 508 / 486, 16384, B 4, 64 heads 274 / 262.
+constexpr int STATS_PARTS = 64;
 static int stats_split(ScoreArgs& a, bool bf16, bool retention) {
     a.parts = a.nkb; a.stat_chunks = STATS_CHUNKS;
-    if (!bf16) return 0;
     const int count = Chunks(a.w, a.G, packs(a.w)).count;
     const int64_t work = (int64_t)a.B * a.Hkv * a.nkb * count;       // 128 keys by 32 rows
-    if (work <= 24576) a.stat_chunks = work < 2560 ? 2 : 4;
+    if (!bf16 || work < (retention ? 3072 : 8192) || (!retention && count < 3)) return 0;
+    if (work <= 24576) a.stat_chunks = 4;
     int r = 768 / (a.B * a.Hkv * ((count + a.stat_chunks - 1) / a.stat_chunks));
     if (retention) r = r > STATS_PARTS ? STATS_PARTS : r;
     r = r < 1 ? 1 : r < a.nkb ? r : a.nkb;
     if (retention) a.parts = r;
-    else if (work < 8192 || count < 3) return 0;
     return r;
 }
 template <typename T, int D>

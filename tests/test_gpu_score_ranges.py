@@ -69,14 +69,14 @@ def test_key_blocks_that_join_their_results(Hq, Hkv, n, w, d):
             np.testing.assert_array_equal(again[name], got[name], err_msg=name)
 
 
-@pytest.mark.parametrize("Hq,Hkv,n,w,packed", [(24, 8, 44001, 32, False), (7, 1, 150003, 32, False), (48, 8, 14002, 16, True), (11, 1, 110003, 8, True)])
+@pytest.mark.parametrize("Hq,Hkv,n,w,packed", [(24, 8, 44001, 32, False), (7, 1, 150003, 32, False), (48, 8, 17002, 16, True), (11, 1, 140003, 8, True)])
 def test_three_chunks_of_rows_for_four_waves(Hq, Hkv, n, w, packed):
     """A workgroup of the statistics pass with three chunks of 32 rows, or of up to 32: its fourth wave has none, and no rows to read (in the last
     KV head there are none behind).  `packed`: windows that share chunks, as the retention score has them."""
     print(f"three chunks Hq={Hq} Hkv={Hkv} n={n} w={w}", flush=True)
     G, d = Hq // Hkv, 64
     chunks = -(-G * w // 32)
-    assert chunks % 4 == 3 and Hkv * -(-n // 128) * chunks >= (2560 if packed else 8192)       # four chunks a workgroup, ranges of keys
+    assert chunks % 4 == 3 and Hkv * -(-n // 128) * chunks >= (3072 if packed else 8192)       # four chunks a workgroup, ranges of keys
     q, k, v = inputs.make_plain(1, Hq, Hkv, n, w, d, dtype="bf16", seed=n, q_scale=1.5)
     A = _window(q, k, np.arange(n - w, n), 1 / math.sqrt(d))
     if not packed:
