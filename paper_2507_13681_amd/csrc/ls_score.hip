@@ -1005,14 +1005,13 @@ __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguou
 
 // Workgroups that share a KV head's query heads over one key block.  A grid of less than four workgroups per CU
 // (what the LDS takes) leaves SIMDs with too few waves to cover the chunks' barriers: the heads are then shared
-// out, at the price of reading K once more per share, which the L2 mostly answers.  Two such rounds still gain
-// while a workgroup keeps four chunks (16384 keys, w = 128: lines 33.7 -> 31.4 us), with fewer they lose
-// (8192 keys, w = 64: 20.6 -> 22.6 us).  1024 fp32 keys, 4 -> 16 workgroups per key block: 15.1 -> 6.2 us.
+// out, at the price of reading K once more per share, which the L2 mostly answers.  No further: a second round of workgroups costs more than it spreads.  ls_score, up to 2048 workgroups where
+// they keep four chunks / 1024, us: 64 heads, 64 rows of 8192 keys 54.4 / 49.9, B 4, 3000 keys 73.9 / 70.2, 32 heads, 16384 keys 55.9 / 52.9, 128 rows 82.1 / 80.7, 12347 keys
+// 48.4 / 47.8.  1024 fp32 keys, 4 -> 16 workgroups per key block: 15.1 -> 6.2 us.
 static int head_shares(const ScoreArgs& a, int kv_heads) {
     const int64_t wgs = (int64_t)a.nkb * kv_heads;
-    const int chunks = a.G * ((a.w + 31) / 32);
     int z = 1;
-    while (a.G % (2 * z) == 0 && wgs * 2 * z <= (chunks >= 8 * z ? 2048 : 1024)) z *= 2;
+    while (a.G % (2 * z) == 0 && wgs * 2 * z <= 1024) z *= 2;
     return z;
 }
 // Whether lines_kernel adds what neighbouring key blocks have of a diagonal, and the totals, itself.  That saves finish_kernel's launch and round trips, and costs a
