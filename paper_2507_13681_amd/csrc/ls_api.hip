@@ -130,6 +130,13 @@ inline float scale_log2e(const ls_shape* s) {
     return sc * 1.44269504088896340736f;
 }
 
+ls::ScoreArgs score_args(const ls_shape* s) {
+    ls::ScoreArgs a{};
+    a.n = s->n; a.w = s->w; a.G = s->Hq / s->Hkv; a.Hq = s->Hq; a.Hkv = s->Hkv; a.B = s->B; a.BH = s->B * s->Hq; a.nkb = nkb_of(s->n);
+    a.scale_log2e = scale_log2e(s);
+    return a;
+}
+
 // per key block max / sum of every scored row; later the 8 partial totals of every head
 inline size_t part_floats(const ls_shape* s) {
     const size_t BH = (size_t)s->B * s->Hq;
@@ -244,9 +251,8 @@ int ls_score(ls_ctx* c, const ls_shape* s, const void* q_win, const int64_t* q_p
     if (!aligned16(q_win) || !aligned16(k) || !aligned16(vert) || !aligned16(slash) || !aligned16(vmax) ||
         !aligned16(smax) || (q_pos && (reinterpret_cast<uintptr_t>(q_pos) & 7u)))
         return fail(c, LS_EINVAL, "ls_score: misaligned tensor");
-    ls::ScoreArgs a{};
-    a.q = q_win; a.k = k; a.q_pos = q_pos; a.n = s->n; a.w = s->w; a.G = s->Hq / s->Hkv; a.Hq = s->Hq;
-    a.Hkv = s->Hkv; a.B = s->B; a.BH = s->B * s->Hq; a.nkb = nkb_of(s->n); a.scale_log2e = scale_log2e(s);
+    ls::ScoreArgs a = score_args(s);
+    a.q = q_win; a.k = k; a.q_pos = q_pos;
     Bump bp{c->ws, c->ws_bytes, 0};
     a.part = bp.take<float>(part_floats(s));
     a.rowstat = bp.take<float>((size_t)a.BH * a.w * 2);
@@ -275,9 +281,8 @@ int ls_score_window(ls_ctx* c, const ls_shape* s, const void* q_win, const int64
     if (!q_win || !k || !a_win) return fail(c, LS_EINVAL, "ls_score_window: NULL tensor");
     if (!aligned16(q_win) || !aligned16(k) || !aligned16(a_win) || (q_pos && (reinterpret_cast<uintptr_t>(q_pos) & 7u)))
         return fail(c, LS_EINVAL, "ls_score_window: misaligned tensor");
-    ls::ScoreArgs a{};
-    a.q = q_win; a.k = k; a.q_pos = q_pos; a.n = s->n; a.w = s->w; a.G = s->Hq / s->Hkv; a.Hq = s->Hq;
-    a.Hkv = s->Hkv; a.B = s->B; a.BH = s->B * s->Hq; a.nkb = nkb_of(s->n); a.scale_log2e = scale_log2e(s);
+    ls::ScoreArgs a = score_args(s);
+    a.q = q_win; a.k = k; a.q_pos = q_pos;
     Bump bp{c->ws, c->ws_bytes, 0};
     a.part = bp.take<float>(part_floats(s));
     a.rowstat = bp.take<float>((size_t)a.BH * a.w * 2);
@@ -516,9 +521,8 @@ int kv_compress_on(const ErrSink& fail, const char* who, int device, unsigned ch
     if (!q_obs || !k || !keep_idx || !keep_cnt || (v_out && !v)) return fail(LS_EINVAL, "%s: NULL tensor", who);
     if (!aligned16(q_obs) || !aligned16(k) || !aligned16(v) || !aligned16(k_out) || !aligned16(v_out))
         return fail(LS_EINVAL, "%s: misaligned tensor", who);
-    ls::ScoreArgs a{};
-    a.q = q_obs; a.k = k; a.q_pos = nullptr; a.n = s->n; a.w = s->w; a.G = s->Hq / s->Hkv; a.Hq = s->Hq;
-    a.Hkv = s->Hkv; a.B = s->B; a.BH = s->B * s->Hq; a.nkb = nkb_of(s->n); a.scale_log2e = scale_log2e(s);
+    ls::ScoreArgs a = score_args(s);
+    a.q = q_obs; a.k = k; a.q_pos = nullptr;
     const int BK = s->B * s->Hkv;
     Bump bp{ws, ws_bytes, 0};
     a.part = bp.take<float>(part_floats(s));
@@ -714,6 +718,20 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
             }
     }
     *nqb_out = w.nqb;
+    return LS_OK;
+}
+
+int ls_debug_score_route(const ls_shape* s, int32_t mode, int32_t route[6], int64_t* begins) {
+    if (!route || mode < 0 || mode > 3 || check_shape(s, false, true, false)) return LS_EINVAL;
+    ls::ScoreArgs a = score_args(s);
+    const ls::ScoreRoute r = ls::score_route(a, s->dtype == LS_BF16, mode);
+    const int32_t words[6] = {r.ranges, r.chunks, r.shares, r.folds, r.joins, r.streams};
+    memcpy(route, words, sizeof(words));
+    const uint32_t units = (uint32_t)((s->n + r.unit - 1) / r.unit);
+    for (int x = 0; begins && x <= r.ranges && r.ranges > 0; ++x) {
+        const int64_t key = (int64_t)ls::range_begin(units, (uint32_t)r.ranges, (uint32_t)x) * r.unit;
+        begins[x] = key < s->n ? key : s->n;
+    }
     return LS_OK;
 }
 

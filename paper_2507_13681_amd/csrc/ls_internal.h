@@ -31,6 +31,23 @@ struct ScoreArgs {
     uint32_t* done;           // [BH] workgroups of lines_kernel or finish_kernel that are done, of a head (the first of a share), cleared by stats_kernel (null: not used)
 };
 
+// Where range x of `ranges` begins among `count` tiles or blocks of keys: floor(count * x / ranges).  That product passes 2^32 in ls_score, which has up to 768
+// ranges and takes up to 2^31 keys (2^24 blocks); these do not, with at most 2^16 ranges.
+__host__ __device__ inline uint32_t range_begin(uint32_t count, uint32_t ranges, uint32_t x) {
+    const uint32_t each = count / ranges, rest = count % ranges;
+    return each * x + rest * x / ranges;
+}
+// What of the scoring passes serves a call.
+struct ScoreRoute {
+    int ranges, unit;         // range_stats_kernel: ranges of keys, cut at multiples of `unit` keys; 0: stats_kernel
+    int chunks;               // of 32 query rows, a workgroup of range_stats_kernel at most
+    int shares;               // workgroups of stats_kernel that share a KV head's query heads
+    bool folds;               // no merge_kernel: lines_kernel merges the row statistics
+    bool joins;               // no finish_kernel: lines_kernel joins the key blocks' results
+    bool streams;             // retention: all query rows stay in LDS while the keys come by
+};
+ScoreRoute score_route(ScoreArgs& a, bool bf16, int mode);
+
 constexpr int SELECT_HEAD_LINES = 1024;   // lines at the front of each sorted list whose weight and maximum are stored in order
 
 // (The order decides which of its pointers walk_exact_kernel keeps in vector registers; with `w` last and `spin_limit` between the

@@ -210,13 +210,13 @@ __global__ __launch_bounds__(SCORE_THREADS, 3) void range_stats_kernel(ScoreArgs
     const bool works = kh < kw && wv % rw < here;          // (of three chunks, the fourth wave only reads K)
     const int cw = works ? wv % rw : 0;                    // its first chunk
     const int mine = !works ? 0 : cw + rw < here ? 2 : 1;  // chunks cw, cw + 4
-    const uint32_t nt = (uint32_t)((n + C::KEYS - 1) / C::KEYS);                  // (fewer than 2^16, and ranges fewer than 2^8)
-    int t0 = (int)(nt * blockIdx.x / gridDim.x), t1 = (int)(nt * (blockIdx.x + 1) / gridDim.x);
-    if (BLOCKS) {                                          // whole blocks
-        t0 = 2 * (int)((uint32_t)a.nkb * blockIdx.x / gridDim.x); t1 = 2 * (int)((uint32_t)a.nkb * (blockIdx.x + 1) / gridDim.x);
-        if (t1 > (int)nt) t1 = (int)nt;
-        if (blockIdx.x == 0 && blockIdx.z == 0) clear_counters(a, bk, tid);
-    }
+    const int nt = (int)((n + C::KEYS - 1) / C::KEYS);
+    constexpr int UNIT = BLOCKS ? SB / C::KEYS : 1;        // BLOCKS: whole blocks
+    const uint32_t units = BLOCKS ? (uint32_t)a.nkb : (uint32_t)nt;
+    const int t0 = UNIT * (int)range_begin(units, gridDim.x, blockIdx.x);
+    int t1 = UNIT * (int)range_begin(units, gridDim.x, blockIdx.x + 1);
+    if (t1 > nt) t1 = nt;
+    if (BLOCKS && blockIdx.x == 0 && blockIdx.z == 0) clear_counters(a, bk, tid);
 
     // ---- transfers: wave wv fetches rows 16 wv .. 16 wv + 15 of a tile; keys beyond the context repeat the last one
     const int rowlane = 16 * wv + lane / C::DS, sl = lane % C::DS;
@@ -1083,14 +1083,29 @@ static void window_bands(int64_t fit, int BK, int w, int* heads, int* rows) {
     }
 }
 
+// Which kernels a call takes (run_score_t launches them), and what they find of it in `a`.
+ScoreRoute score_route(ScoreArgs& a, bool bf16, int mode) {
+    ScoreRoute r{};
+    const int BK = a.B * a.Hkv;
+    if (mode == 0) { a.shares = head_shares(a, BK); a.join = joins(a, BK); }
+    r.ranges = stats_split(a, bf16, mode == 2);
+    r.unit = mode == 2 ? KeyTile<128>::KEYS : SB;
+    r.chunks = a.stat_chunks;
+    r.folds = folds(a, mode);
+    r.shares = packs(a.w) ? 1 : head_shares(a, BK);
+    r.joins = a.join;
+    r.streams = a.retain = mode == 2 && bf16 && !r.folds && Chunks(a.w, a.G, packs(a.w)).count <= RETAIN_CHUNKS;
+    return r;
+}
+
 template <typename T, int D>
 static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     ScoreArgs a = a0;
     const int BK = a.B * a.Hkv;
     a.t0 = 0; a.t1 = a.w;
-    if (mode == 0) { a.shares = head_shares(a, BK); a.join = joins(a, BK); }
-    launch_stats<T, D>(a, stats_split(a, Elem<T>::bytes == 2, mode == 2), mode == 2, st);
-    if (!folds(a, mode)) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
+    const ScoreRoute r = score_route(a, Elem<T>::bytes == 2, mode);
+    launch_stats<T, D>(a, r.ranges, mode == 2, st);
+    if (!r.folds) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {
         if (a.join) {
             launch_lines<T, D, 4>(a, BK, st);
@@ -1117,7 +1132,6 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
         return hipGetLastError();
     } else {
         const int share = 512 / BK < 1 ? 1 : 512 / BK < a.nkb ? 512 / BK : a.nkb;      // (64 KB of LDS: two workgroups a CU)
-        a.retain = Elem<T>::bytes == 2 && !folds(a, mode) && Chunks(a.w, a.G, packs(a.w)).count <= RETAIN_CHUNKS;
         if constexpr (Elem<T>::bytes == 2) {
             if (a.retain) hipLaunchKernelGGL((lines_kernel<T, D, 2, false>), dim3(share, BK), dim3(SCORE_THREADS), retain_lds<D>(), st, a);
         }

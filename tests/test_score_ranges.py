@@ -1,0 +1,18 @@
+"""How the scoring's statistics pass cuts the keys into ranges, on the CPU: the function that the kernel itself calls, through the test hook."""
+import pytest
+
+from paper_2507_13681_amd import binding
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,w,mode", [
+    (1, 32, 8, 32768, 64, 0), (4, 64, 8, 16384, 64, 0), (1, 32, 8, 131072, 256, 1), (2, 12, 4, 50001, 97, 3),
+    (4, 64, 8, 16384, 16, 2), (1, 8, 1, 262144, 256, 2), (3, 64, 8, 4000, 16, 2),
+    # one KV head and a window: ls_score takes as many keys as an int counts, and 768 ranges times 2^23 blocks are more than 2^32
+    (1, 3, 1, 715827968, 32, 0), (1, 4, 1, 800000001, 64, 0), (1, 4, 1, 2147483000, 64, 0), (1, 1, 1, 2147483000, 128, 0), (1, 8, 1, 1500000063, 256, 1)])
+def test_every_key_lies_in_one_range(B, Hq, Hkv, n, w, mode):
+    route = binding.score_route(binding.make_shape(B, Hq, Hkv, 64, n, 1, w, "bf16"), mode)
+    ranges, begins, unit = route["ranges"], route["begins"], 64 if mode == 2 else 128
+    units = -(-n // unit)
+    assert ranges > 1
+    assert begins == [min(n, units * x // ranges * unit) for x in range(ranges + 1)]       # in whole numbers of any size
+    assert begins[0] == 0 and begins[-1] == n and all(a < b for a, b in zip(begins, begins[1:]))
