@@ -1021,13 +1021,14 @@ static int head_shares(const ScoreArgs& a, int kv_heads) {
 // 33.5 (20000 keys), 66 / 82 (32 KV heads of 32768).  Beyond 16384 keys a share of the total is more than two reads a lane.
 static bool joins(const ScoreArgs& a, int kv_heads) { return (int64_t)a.nkb * kv_heads * a.shares <= 1600 && a.n <= 16384; }
 // The ranges of keys of range_stats_kernel; 0: stats_kernel, where there is little work, or so few rows that waves would stand idle.
-// As many as fill the chip with three workgroups a CU; for the retention score, which keeps their statistics apart, 64 at most (more cost merge_kernel what they save) and no
-// more than the blocks of 128 keys that `part` has room for.  Four chunks of rows a workgroup, eight where there is much work: eight / four, us, 131072 keys 140 / 157, 16384 keys, B 4, 75 / 81, 32768
+// As many as fill the chip with three workgroups a CU; for the retention score, which keeps their statistics apart, no more than the blocks of 128 keys that `part` has room for, and
+// no more than give every CU two workgroups (64 to 256 of them: beyond, merge_kernel takes what they save).  The whole ls_kv_compress, us, stats_kernel / 64 ranges / so: one KV head, 64
+// rows of 262144 keys 67 / 78 / 51, 128 of 131072 49 / 65 / 45, 256 67 / 75 / 56; two, 64 of 262144 87 / 90 / 74; four, 128 of 131072, d = 64, 74 / 72 / 64; eight, 64 ranges / 96: 131 / 133.  Four chunks of rows a workgroup, eight where there is much work: eight / four, us, 131072 keys 140 / 157, 16384 keys, B 4, 75 / 81, 32768
 // 24.0 / 24.4, 12347 16.0 / 13.8.
 // The lines.  The kernels, stats_kernel / range_stats_kernel, us, retention score of 16 rows: 8 heads, 16384 keys (1024 of the products below) 5.9 / 9.3, 32 / 8 heads (2048) 8.5 / 9.6, 32768 keys (4096)
 // 16.9 / 13.9, 4 / 1 heads, 32768 (512) 5.1 / 8.8.  ls_score: 8192 keys, 32 heads, 64 rows (4096) 32.8 / 33.8, 12347 (6208) 48.5 / 48.6, 131072, 16 heads of 64, 32 rows (16384)
 // 85.1 / 83.4, 4 heads, 100 rows 91.6 / 86.6, 32768, 32 heads 88.5 / 82.9, 131072, 128 rows 508 / 486, 16384, B 4, 64 heads 274 / 262.
-constexpr int STATS_PARTS = 64;
+constexpr int STATS_PARTS = 64, STATS_PARTS_MOST = 256;
 static int stats_split(ScoreArgs& a, bool bf16, bool retention) {
     a.parts = a.nkb; a.stat_chunks = STATS_CHUNKS;
     const int count = Chunks(a.w, a.G, packs(a.w)).count;
@@ -1035,7 +1036,10 @@ static int stats_split(ScoreArgs& a, bool bf16, bool retention) {
     if (!bf16 || work < (retention ? 3072 : 8192) || (!retention && count < 3)) return 0;
     if (work <= 24576) a.stat_chunks = 4;
     int r = 768 / (a.B * a.Hkv * ((count + a.stat_chunks - 1) / a.stat_chunks));
-    if (retention) r = r > STATS_PARTS ? STATS_PARTS : r;
+    if (retention) {
+        const int two = 512 / (a.B * a.Hkv), most = two < STATS_PARTS ? STATS_PARTS : two < STATS_PARTS_MOST ? two : STATS_PARTS_MOST;
+        r = r > most ? most : r;
+    }
     r = r < 1 ? 1 : r < a.nkb ? r : a.nkb;
     if (retention) a.parts = r;
     return r;

@@ -16,3 +16,10 @@ def test_every_key_lies_in_one_range(B, Hq, Hkv, n, w, mode):
     assert ranges > 1
     assert begins == [min(n, units * x // ranges * unit) for x in range(ranges + 1)]       # in whole numbers of any size
     assert begins[0] == 0 and begins[-1] == n and all(a < b for a, b in zip(begins, begins[1:]))
+
+
+@pytest.mark.parametrize("Hq,Hkv,n,w,d", [(4, 1, 262144, 16, 128), (8, 1, 131072, 32, 64), (8, 2, 262144, 16, 128), (16, 4, 131072, 32, 64), (3, 3, 262144, 31, 128)])
+def test_long_caches_of_few_heads_have_work_for_every_unit(Hq, Hkv, n, w, d):
+    """Retention: ranges enough for two workgroups on each of 256 compute units, or 256 of one head."""
+    route = binding.score_route(binding.make_shape(1, Hq, Hkv, d, n, 1, w, "bf16"), 2)
+    assert route["ranges"] * Hkv >= min(510, 256 * Hkv)
