@@ -264,13 +264,14 @@ def static_scratch_bytes() -> int:
 def score_route(shape: LsShape, mode: int) -> dict:
     """Which scoring kernels a call of this shape takes (test hook, no GPU needed); mode: 0 ls_score of the newest rows, 1 ls_score
     otherwise, 2 ls_kv_compress, 3 ls_score_window.  `begins`: where the ranges of the statistics pass begin, and n."""
-    lib, words = load_library(), (C.c_int32 * 6)()
+    lib, words = load_library(), (C.c_int32 * 9)()
     rc = lib.ls_debug_score_route(C.byref(shape), mode, words, None)
     if rc != 0:
         raise LoopServeError(f"ls_debug_score_route failed with {rc}")
     begins = (C.c_int64 * (words[0] + 1))()
     lib.ls_debug_score_route(C.byref(shape), mode, words, begins)
-    return dict(ranges=words[0], chunks=words[1], shares=words[2], folds=bool(words[3]), joins=bool(words[4]), streams=bool(words[5]), begins=list(begins))
+    return dict(ranges=words[0], chunks=words[1], shares=words[2], folds=bool(words[3]), joins=bool(words[4]), streams=bool(words[5]),
+                band_heads=words[6], band_rows=words[7], band_shares=words[8], begins=list(begins))
 
 
 def alloc_score(shape: LsShape, device="cuda"):

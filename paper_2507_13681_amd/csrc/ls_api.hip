@@ -143,6 +143,17 @@ inline size_t part_floats(const ls_shape* s) {
     const size_t a = BH * s->w * nkb_of(s->n) * 2, b = BH * 8;
     return a > b ? a : b;
 }
+void row_scratch(ls::ScoreArgs& a, const ls_shape* s, Bump& bp) {
+    a.part = bp.take<float>(part_floats(s));
+    a.rowstat = bp.take<float>((size_t)a.BH * a.w * 2);
+}
+// ... and bands of the window matrix in what is left
+void window_scratch(ls::ScoreArgs& a, const ls_shape* s, Bump& bp) {
+    row_scratch(a, s, bp);
+    const size_t row = (size_t)a.G * (size_t)a.n * 4;              // of a KV head's matrices
+    a.win_rows = bp.ok() ? (int64_t)((bp.cap - bp.off) / row) : 0;
+    a.a_win = reinterpret_cast<float*>(bp.base + bp.off);
+}
 // The window matrix of explicit scoring positions passes through what is left of the workspace, band by band.  The partial sums
 // of the diagonals, which that path does not need, leave room for four rows of every head, and any call gets by with those.
 // Asked for is room for the whole matrix up to WIN_BYTES, as much as the parts of long attention items take (ws_prefill).
@@ -254,16 +265,13 @@ int ls_score(ls_ctx* c, const ls_shape* s, const void* q_win, const int64_t* q_p
     ls::ScoreArgs a = score_args(s);
     a.q = q_win; a.k = k; a.q_pos = q_pos;
     Bump bp{c->ws, c->ws_bytes, 0};
-    a.part = bp.take<float>(part_floats(s));
-    a.rowstat = bp.take<float>((size_t)a.BH * a.w * 2);
     const int mode = (q_pos == nullptr && s->w <= 128) ? 0 : 1;
     if (mode == 0) {
+        row_scratch(a, s, bp);
         a.spart = bp.take<float>(2 * (size_t)a.BH * (size_t)a.n * 2);
     } else {
-        const size_t row = (size_t)a.G * (size_t)a.n * 4;              // of a KV head's matrices
-        a.win_rows = bp.ok() ? (int64_t)((bp.cap - bp.off) / row) : 0;
+        window_scratch(a, s, bp);
         if (a.win_rows == 0) return fail(c, LS_EWORKSPACE, "ls_score: workspace of %zu bytes is too small", c->ws_bytes);
-        a.a_win = reinterpret_cast<float*>(bp.base + bp.off);
     }
     a.done = c->counters;
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_score: workspace of %zu bytes is too small", c->ws_bytes);
@@ -284,8 +292,7 @@ int ls_score_window(ls_ctx* c, const ls_shape* s, const void* q_win, const int64
     ls::ScoreArgs a = score_args(s);
     a.q = q_win; a.k = k; a.q_pos = q_pos;
     Bump bp{c->ws, c->ws_bytes, 0};
-    a.part = bp.take<float>(part_floats(s));
-    a.rowstat = bp.take<float>((size_t)a.BH * a.w * 2);
+    row_scratch(a, s, bp);
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_score_window: workspace of %zu bytes is too small", c->ws_bytes);
     a.a_win = a_win;
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, LS_EHIP, "ls_score_window: hipSetDevice failed");
@@ -525,8 +532,7 @@ int kv_compress_on(const ErrSink& fail, const char* who, int device, unsigned ch
     a.q = q_obs; a.k = k; a.q_pos = nullptr;
     const int BK = s->B * s->Hkv;
     Bump bp{ws, ws_bytes, 0};
-    a.part = bp.take<float>(part_floats(s));
-    a.rowstat = bp.take<float>((size_t)a.BH * a.w * 2);
+    row_scratch(a, s, bp);
     a.gscore = bp.take<float>((size_t)BK * (size_t)a.n);
     uint32_t* tb_scratch = bp.take<uint32_t>(ls::topb_scratch_words(BK, s->n));
     if (!bp.ok()) return fail(LS_EWORKSPACE, "%s: needs %zu bytes of scratch, %zu are there", who, ws_compress(s), ws_bytes);
@@ -721,11 +727,15 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
     return LS_OK;
 }
 
-int ls_debug_score_route(const ls_shape* s, int32_t mode, int32_t route[6], int64_t* begins) {
+int ls_debug_score_route(const ls_shape* s, int32_t mode, int32_t route[9], int64_t* begins) {
     if (!route || mode < 0 || mode > 3 || check_shape(s, false, true, false)) return LS_EINVAL;
     ls::ScoreArgs a = score_args(s);
+    if (mode == 1) {
+        Bump bp{nullptr, ls_workspace_bytes(s, 0), 0};
+        window_scratch(a, s, bp);
+    }
     const ls::ScoreRoute r = ls::score_route(a, s->dtype == LS_BF16, mode);
-    const int32_t words[6] = {r.ranges, r.chunks, r.shares, r.folds, r.joins, r.streams};
+    const int32_t words[9] = {r.ranges, r.chunks, r.shares, r.folds, r.joins, r.streams, r.band_heads, r.band_rows, r.band_shares};
     memcpy(route, words, sizeof(words));
     const uint32_t units = (uint32_t)((s->n + r.unit - 1) / r.unit);
     for (int x = 0; begins && x <= r.ranges && r.ranges > 0; ++x) {

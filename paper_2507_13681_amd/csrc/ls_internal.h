@@ -45,6 +45,7 @@ struct ScoreRoute {
     bool folds;               // no merge_kernel: lines_kernel merges the row statistics
     bool joins;               // no finish_kernel: lines_kernel joins the key blocks' results
     bool streams;             // retention: all query rows stay in LDS while the keys come by
+    int band_heads, band_rows, band_shares;        // mode 1: KV heads and window rows of a band of the matrix, workgroups of the first that share a KV head's query heads
 };
 ScoreRoute score_route(ScoreArgs& a, bool bf16, int mode);
 

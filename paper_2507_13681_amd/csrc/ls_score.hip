@@ -1007,11 +1007,13 @@ __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguou
 // (what the LDS takes) leaves SIMDs with too few waves to cover the chunks' barriers: the heads are then shared
 // out, at the price of reading K once more per share, which the L2 mostly answers.  No further: a second round of workgroups costs more than it spreads.  ls_score, up to 2048 workgroups where
 // they keep four chunks / 1024, us: 64 heads, 64 rows of 8192 keys 54.4 / 49.9, B 4, 3000 keys 73.9 / 70.2, 32 heads, 16384 keys 55.9 / 52.9, 128 rows 82.1 / 80.7, 12347 keys
-// 48.4 / 47.8.  1024 fp32 keys, 4 -> 16 workgroups per key block: 15.1 -> 6.2 us.
-static int head_shares(const ScoreArgs& a, int kv_heads) {
+// 48.4 / 47.8; ls_score_window, 64 rows of 16384 keys 60.5 / 56.0, 128 of 8192 57.5 / 53.3.  1024 fp32 keys, 4 -> 16 workgroups per key block: 15.1 -> 6.2 us.
+// `band`: chunks of a band of explicit positions.  The band's launches wait for each other, and a second round fills the end of one: up to 2048 workgroups where they keep four of the band's chunks.
+// 1024 / so, us: B 4, 64 heads, 64 rows of 16384 keys 718 / 711, d = 64 645 / 629; where they keep two: 131072 keys, 128 rows 1306 / 1463, 32768 keys, 64 rows 180 / 194.
+static int head_shares(const ScoreArgs& a, int kv_heads, int band = 0) {
     const int64_t wgs = (int64_t)a.nkb * kv_heads;
     int z = 1;
-    while (a.G % (2 * z) == 0 && wgs * 2 * z <= 1024) z *= 2;
+    while (a.G % (2 * z) == 0 && wgs * 2 * z <= (band >= 8 * z ? 2048 : 1024)) z *= 2;
     return z;
 }
 // Whether lines_kernel adds what neighbouring key blocks have of a diagonal, and the totals, itself.  That saves finish_kernel's launch and round trips, and costs a
@@ -1063,11 +1065,12 @@ static bool folds(const ScoreArgs& a, int mode) {
     const int64_t bytes = (int64_t)a.nkb * a.B * a.Hkv * (a.G * a.w) * a.parts * 8;      // of all workgroups together (each takes its share of the heads)
     return a.parts <= FOLD_PARTS && score_chunks(a) <= FOLD_CHUNKS && (bytes <= FOLD_BYTES || (mode != 1 && a.nkb <= 16));
 }
+static int band_chunks(const ScoreArgs& a) { return a.G * ((a.t1 + 31) / 32 - a.t0 / 32); }
 template <typename T, int D, int MODE>
 static void launch_lines(const ScoreArgs& a, int kv_heads, hipStream_t st) {
     const bool fold = folds(a, MODE);
     const size_t smem = lines_front<T, D>(MODE) + (size_t)(a.w + 3) / 4 * 16 + (fold ? (size_t)score_chunks(a) * 256 : 512);
-    const dim3 grid(a.nkb, kv_heads, MODE == 2 ? 1 : head_shares(a, kv_heads));
+    const dim3 grid(a.nkb, kv_heads, MODE == 2 ? 1 : head_shares(a, kv_heads, MODE == 1 ? band_chunks(a) : 0));
     if (fold) hipLaunchKernelGGL((lines_kernel<T, D, MODE, true>), grid, dim3(SCORE_THREADS), smem, st, a);
     else hipLaunchKernelGGL((lines_kernel<T, D, MODE, false>), grid, dim3(SCORE_THREADS), smem, st, a);
 }
@@ -1098,6 +1101,12 @@ ScoreRoute score_route(ScoreArgs& a, bool bf16, int mode) {
     r.folds = folds(a, mode);
     r.shares = packs(a.w) ? 1 : head_shares(a, BK);
     r.joins = a.join;
+    if (mode == 1) {
+        window_bands(a.win_rows, BK, a.w, &r.band_heads, &r.band_rows);
+        ScoreArgs first = a;
+        first.t0 = 0; first.t1 = r.band_rows;
+        r.band_shares = head_shares(first, r.band_heads, band_chunks(first));
+    }
     r.streams = a.retain = mode == 2 && bf16 && !r.folds && Chunks(a.w, a.G, packs(a.w)).count <= RETAIN_CHUNKS;
     return r;
 }
@@ -1117,8 +1126,7 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
         }
         launch_lines<T, D, 0>(a, BK, st);
     } else if (mode == 1) {
-        int most, rows;
-        window_bands(a.win_rows, BK, a.w, &most, &rows);
+        const int most = r.band_heads, rows = r.band_rows;
         for (a.bk0 = 0; a.bk0 < BK; a.bk0 += most) {
             const int heads = BK - a.bk0 < most ? BK - a.bk0 : most;
             a.bh_first = a.bk0 * a.G;

@@ -1,4 +1,4 @@
-"""How the scoring's statistics pass cuts the keys into ranges, on the CPU: the function that the kernel itself calls, through the test hook."""
+"""How the scoring passes share out their work, on the CPU: the functions that the launches themselves call, through the test hook."""
 import pytest
 
 from paper_2507_13681_amd import binding
@@ -23,3 +23,13 @@ def test_long_caches_of_few_heads_have_work_for_every_unit(Hq, Hkv, n, w, d):
     """Retention: ranges enough for two workgroups on each of 256 compute units, or 256 of one head."""
     route = binding.score_route(binding.make_shape(1, Hq, Hkv, d, n, 1, w, "bf16"), 2)
     assert route["ranges"] * Hkv >= min(510, 256 * Hkv)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,w,d,heads,rows,shares", [
+    (4, 64, 8, 16384, 64, 64, 5, 32, 2), (4, 64, 8, 16384, 64, 128, 5, 32, 2),     # 640 workgroups of eight chunks, 1280 of four
+    (1, 32, 8, 131072, 128, 128, 1, 32, 1), (1, 32, 8, 32768, 64, 128, 2, 64, 2),  # two each with more than 1024
+    (1, 16, 4, 5003, 48, 64, 4, 48, 4)])
+def test_bands_are_shared_out_by_their_own_chunks(B, Hq, Hkv, n, w, d, heads, rows, shares):
+    """Explicit positions: a second round of workgroups where they keep four chunks of the band, not of the window."""
+    route = binding.score_route(binding.make_shape(B, Hq, Hkv, d, n, 1, w, "bf16"), 1)
+    assert (route["band_heads"], route["band_rows"], route["band_shares"]) == (heads, rows, shares)
