@@ -45,13 +45,13 @@ int ls_debug_copy_prefill_queues(ls_ctx* ctx, const ls_shape* shape, uint32_t* h
 
 /*
  * Which of the scoring passes' kernels a call of this shape takes and how it cuts the keys, without a GPU.  `mode`: 0 ls_score of the newest
- * rows (w <= 128), 1 ls_score otherwise, 2 ls_kv_compress, 3 ls_score_window.  route[0]: ranges of keys of the statistics pass (0: a workgroup per
+ * rows (w <= 128), 1 ls_score otherwise, 2 ls_kv_compress, 3 ls_score_window; `positions`: with explicit positions.  route[0]: ranges of keys of the statistics pass (0: a workgroup per
  * 128 keys), [1] chunks of 32 rows that a workgroup of it takes at most, [2] workgroups that share a KV head's query heads, [3] row statistics are merged by the second pass,
  * [4] key blocks join their results themselves, [5] the retention's second pass keeps its rows and streams the keys; mode 1, with the
  * workspace that ls_workspace_bytes states: [6] KV heads and [7] rows of a band of the window matrix, [8] workgroups of the first that share a KV head's query heads.  begins (may be NULL): of route[0] + 1
  * words, the key at which each range begins, and n.
  */
-int ls_debug_score_route(const ls_shape* shape, int32_t mode, int32_t route[9], int64_t* begins);
+int ls_debug_score_route(const ls_shape* shape, int32_t mode, int32_t positions, int32_t route[9], int64_t* begins);
 
 #ifdef __cplusplus
 }

@@ -86,7 +86,7 @@ def load_library():
     lib.ls_debug_set_counters.restype = C.c_int
     lib.ls_debug_set_counters.argtypes = [vp, i32, vp]
     lib.ls_debug_score_route.restype = C.c_int
-    lib.ls_debug_score_route.argtypes = [sp, i32, C.POINTER(i32), C.POINTER(i64)]
+    lib.ls_debug_score_route.argtypes = [sp, i32, i32, C.POINTER(i32), C.POINTER(i64)]
     lib.ls_debug_copy_prefill_queues.restype = C.c_int
     lib.ls_debug_copy_prefill_queues.argtypes = [vp, sp, vp, vp, C.POINTER(i32), C.POINTER(i32), vp]
     lib.ls_profile_enable.restype = C.c_int
@@ -261,15 +261,15 @@ def static_scratch_bytes() -> int:
 
 # -- convenience: allocate outputs with torch and run one call ----------------------------------
 
-def score_route(shape: LsShape, mode: int) -> dict:
+def score_route(shape: LsShape, mode: int, positions: bool = False) -> dict:
     """Which scoring kernels a call of this shape takes (test hook, no GPU needed); mode: 0 ls_score of the newest rows, 1 ls_score
-    otherwise, 2 ls_kv_compress, 3 ls_score_window.  `begins`: where the ranges of the statistics pass begin, and n."""
+    otherwise, 2 ls_kv_compress, 3 ls_score_window; positions: explicit ones.  `begins`: where the ranges of the statistics pass begin, and n."""
     lib, words = load_library(), (C.c_int32 * 9)()
-    rc = lib.ls_debug_score_route(C.byref(shape), mode, words, None)
+    rc = lib.ls_debug_score_route(C.byref(shape), mode, int(positions), words, None)
     if rc != 0:
         raise LoopServeError(f"ls_debug_score_route failed with {rc}")
     begins = (C.c_int64 * (words[0] + 1))()
-    lib.ls_debug_score_route(C.byref(shape), mode, words, begins)
+    lib.ls_debug_score_route(C.byref(shape), mode, int(positions), words, begins)
     return dict(ranges=words[0], chunks=words[1], shares=words[2], folds=bool(words[3]), joins=bool(words[4]), streams=bool(words[5]),
                 band_heads=words[6], band_rows=words[7], band_shares=words[8], begins=list(begins))
 

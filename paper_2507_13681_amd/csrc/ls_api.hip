@@ -727,14 +727,16 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
     return LS_OK;
 }
 
-int ls_debug_score_route(const ls_shape* s, int32_t mode, int32_t route[9], int64_t* begins) {
+int ls_debug_score_route(const ls_shape* s, int32_t mode, int32_t positions, int32_t route[9], int64_t* begins) {
     if (!route || mode < 0 || mode > 3 || check_shape(s, false, true, false)) return LS_EINVAL;
     ls::ScoreArgs a = score_args(s);
+    const int64_t any = 0;
+    if (positions) a.q_pos = &any;                         // (not looked at)
     if (mode == 1) {
         Bump bp{nullptr, ls_workspace_bytes(s, 0), 0};
         window_scratch(a, s, bp);
     }
-    const ls::ScoreRoute r = ls::score_route(a, s->dtype == LS_BF16, mode);
+    const ls::ScoreRoute r = ls::score_route(a, s->dtype == LS_BF16, s->d, mode);
     const int32_t words[9] = {r.ranges, r.chunks, r.shares, r.folds, r.joins, r.streams, r.band_heads, r.band_rows, r.band_shares};
     memcpy(route, words, sizeof(words));
     const uint32_t units = (uint32_t)((s->n + r.unit - 1) / r.unit);

@@ -47,7 +47,7 @@ struct ScoreRoute {
     bool streams;             // retention: all query rows stay in LDS while the keys come by
     int band_heads, band_rows, band_shares;        // mode 1: KV heads and window rows of a band of the matrix, workgroups of the first that share a KV head's query heads
 };
-ScoreRoute score_route(ScoreArgs& a, bool bf16, int mode);
+ScoreRoute score_route(ScoreArgs& a, bool bf16, int d, int mode);
 
 constexpr int SELECT_HEAD_LINES = 1024;   // lines at the front of each sorted list whose weight and maximum are stored in order
 

@@ -1031,7 +1031,13 @@ static bool joins(const ScoreArgs& a, int kv_heads) { return (int64_t)a.nkb * kv
 // 16.9 / 13.9, 4 / 1 heads, 32768 (512) 5.1 / 8.8.  ls_score: 8192 keys, 32 heads, 64 rows (4096) 32.8 / 33.8, 12347 (6208) 48.5 / 48.6, 131072, 16 heads of 64, 32 rows (16384)
 // 85.1 / 83.4, 4 heads, 100 rows 91.6 / 86.6, 32768, 32 heads 88.5 / 82.9, 131072, 128 rows 508 / 486, 16384, B 4, 64 heads 274 / 262.
 constexpr int STATS_PARTS = 64, STATS_PARTS_MOST = 256;
-static int stats_split(ScoreArgs& a, bool bf16, bool retention) {
+//
+// Explicit positions see parts of a context that differ from row to row, and the ranges of a KV head come out uneven: few and long ones are worse than none.  The whole ls_score, us,
+// stats_kernel / range_stats_kernel, d = 128: 3 to 12 ranges of eleven blocks, B 4, 64 heads, 16384 keys 703 / 715, B 8, 8192 701 / 720, B 16, 4096 725 / 741; 6 of four, B 4, 3000 162 / 159;
+// 24 of five, B 4, 32 heads, 16384 347 / 345; 96 of three, 32768 183 / 180; 48 of 21, 131072, 128 rows 1322 / 1306.  d = 64, whose keys are half as much to read, gains nothing:
+// 613 / 624, 623 / 658 (B 8), 320 / 324 (32 heads), 167 / 168 (32768), 1214 / 1240 (131072).
+constexpr int STATS_FEW = 16, STATS_LONG = 8;
+static int stats_split(ScoreArgs& a, bool bf16, int d, bool retention) {
     a.parts = a.nkb; a.stat_chunks = STATS_CHUNKS;
     const int count = Chunks(a.w, a.G, packs(a.w)).count;
     const int64_t work = (int64_t)a.B * a.Hkv * a.nkb * count;       // 128 keys by 32 rows
@@ -1043,6 +1049,7 @@ static int stats_split(ScoreArgs& a, bool bf16, bool retention) {
         r = r > most ? most : r;
     }
     r = r < 1 ? 1 : r < a.nkb ? r : a.nkb;
+    if (a.q_pos && (d == 64 || (r < STATS_FEW && a.nkb >= STATS_LONG * r))) { a.stat_chunks = STATS_CHUNKS; return 0; }
     if (retention) a.parts = r;
     return r;
 }
@@ -1091,11 +1098,11 @@ static void window_bands(int64_t fit, int BK, int w, int* heads, int* rows) {
 }
 
 // Which kernels a call takes (run_score_t launches them), and what they find of it in `a`.
-ScoreRoute score_route(ScoreArgs& a, bool bf16, int mode) {
+ScoreRoute score_route(ScoreArgs& a, bool bf16, int d, int mode) {
     ScoreRoute r{};
     const int BK = a.B * a.Hkv;
     if (mode == 0) { a.shares = head_shares(a, BK); a.join = joins(a, BK); }
-    r.ranges = stats_split(a, bf16, mode == 2);
+    r.ranges = stats_split(a, bf16, d, mode == 2);
     r.unit = mode == 2 ? KeyTile<128>::KEYS : SB;
     r.chunks = a.stat_chunks;
     r.folds = folds(a, mode);
@@ -1116,7 +1123,7 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     ScoreArgs a = a0;
     const int BK = a.B * a.Hkv;
     a.t0 = 0; a.t1 = a.w;
-    const ScoreRoute r = score_route(a, Elem<T>::bytes == 2, mode);
+    const ScoreRoute r = score_route(a, Elem<T>::bytes == 2, D, mode);
     launch_stats<T, D>(a, r.ranges, mode == 2, st);
     if (!r.folds) hipLaunchKernelGGL(merge_kernel, dim3((a.G * a.w + 15) / 16, BK), dim3(1024), 0, st, a);
     if (mode == 0) {

@@ -31,5 +31,16 @@ def test_long_caches_of_few_heads_have_work_for_every_unit(Hq, Hkv, n, w, d):
     (1, 16, 4, 5003, 48, 64, 4, 48, 4)])
 def test_bands_are_shared_out_by_their_own_chunks(B, Hq, Hkv, n, w, d, heads, rows, shares):
     """Explicit positions: a second round of workgroups where they keep four chunks of the band, not of the window."""
-    route = binding.score_route(binding.make_shape(B, Hq, Hkv, d, n, 1, w, "bf16"), 1)
+    route = binding.score_route(binding.make_shape(B, Hq, Hkv, d, n, 1, w, "bf16"), 1, True)
     assert (route["band_heads"], route["band_rows"], route["band_shares"]) == (heads, rows, shares)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,w,d,cut", [
+    (4, 64, 8, 16384, 64, 128, False), (8, 64, 8, 8192, 64, 128, False), (1, 32, 8, 32768, 64, 128, True), (1, 64, 8, 32768, 64, 128, True), (1, 32, 8, 131072, 256, 128, True), (4, 32, 8, 16384, 64, 128, True), (4, 64, 8, 3000, 64, 128, True),
+    (4, 64, 8, 16384, 64, 64, False), (1, 32, 8, 32768, 64, 64, False), (1, 16, 4, 131072, 64, 64, False)])
+def test_explicit_positions_have_no_few_long_ranges(B, Hq, Hkv, n, w, d, cut):
+    """Rows at explicit positions see parts of the context: a few long ranges come out uneven, and at d = 64 any gain nothing.  The newest rows of the same shapes are cut."""
+    shape, mode = binding.make_shape(B, Hq, Hkv, d, n, 1, w, "bf16"), 0 if w <= 128 else 1
+    ranges = binding.score_route(shape, 1, True)["ranges"]
+    assert (ranges >= 16 or -(-n // 128) < 8 * ranges) if cut else ranges == 0
+    assert binding.score_route(shape, mode)["ranges"] > 0 and binding.score_route(shape, 3, True)["ranges"] == ranges
