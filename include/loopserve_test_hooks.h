@@ -43,6 +43,9 @@ int ls_debug_set_counters(ls_ctx* ctx, int32_t value, void* hip_stream);
 int ls_debug_copy_prefill_queues(ls_ctx* ctx, const ls_shape* shape, uint32_t* host_queue, int32_t* host_qlen,
                                  int32_t* nqb_out, int32_t* cuts_out, void* hip_stream);
 
+/* 1: ls_sparse_prefill shares the work of such a turn out in pieces, 0: by work queues, if the workspace has room for the parts; without a GPU. */
+int ls_debug_prefill_in_pieces(const ls_shape* shape);
+
 /*
  * Which of the scoring passes' kernels a call of this shape takes and how it cuts the keys, without a GPU.  `mode`: 0 ls_score of the newest
  * rows (w <= 128), 1 ls_score otherwise, 2 ls_kv_compress, 3 ls_score_window; `positions`: with explicit positions.  route[0]: ranges of keys of the statistics pass (0: a workgroup per

@@ -85,6 +85,8 @@ def load_library():
     lib.ls_debug_set_walk_spin_limit.argtypes = [vp, i32]
     lib.ls_debug_set_counters.restype = C.c_int
     lib.ls_debug_set_counters.argtypes = [vp, i32, vp]
+    lib.ls_debug_prefill_in_pieces.restype = C.c_int
+    lib.ls_debug_prefill_in_pieces.argtypes = [sp]
     lib.ls_debug_score_route.restype = C.c_int
     lib.ls_debug_score_route.argtypes = [sp, i32, i32, C.POINTER(i32), C.POINTER(i64)]
     lib.ls_debug_copy_prefill_queues.restype = C.c_int
@@ -272,6 +274,14 @@ def score_route(shape: LsShape, mode: int, positions: bool = False) -> dict:
     lib.ls_debug_score_route(C.byref(shape), mode, int(positions), words, begins)
     return dict(ranges=words[0], chunks=words[1], shares=words[2], folds=bool(words[3]), joins=bool(words[4]), streams=bool(words[5]),
                 band_heads=words[6], band_rows=words[7], band_shares=words[8], begins=list(begins))
+
+
+def prefill_in_pieces(shape: LsShape) -> bool:
+    """Whether ls_sparse_prefill shares the work of such a turn out in pieces, not by work queues (test hook, no GPU needed)."""
+    rc = load_library().ls_debug_prefill_in_pieces(C.byref(shape))
+    if rc < 0:
+        raise LoopServeError(f"ls_debug_prefill_in_pieces failed with {rc}")
+    return rc == 1
 
 
 def alloc_score(shape: LsShape, device="cuda"):

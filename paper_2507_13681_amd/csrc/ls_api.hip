@@ -727,6 +727,11 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
     return LS_OK;
 }
 
+int ls_debug_prefill_in_pieces(const ls_shape* s) {
+    if (check_shape(s, true, false, true)) return LS_ESHAPE;
+    return ls::prefill_in_pieces(s->B * s->Hq, s->n, (int)row_blocks(s->n, s->n_hat), s->dtype, s->d) ? 1 : 0;
+}
+
 int ls_debug_score_route(const ls_shape* s, int32_t mode, int32_t positions, int32_t route[9], int64_t* begins) {
     if (!route || mode < 0 || mode > 3 || check_shape(s, false, true, false)) return LS_EINVAL;
     ls::ScoreArgs a = score_args(s);

@@ -328,11 +328,13 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // Tiles here are those that dense heads would have, and a tile of d = 64 counts half.  Pieces / queues, the whole call, us, d = 128:
 // 65536: 4096 rows, all new, 114 / 150; 129696: 2500 of 12347 253 / 285; 225216: 1000 of 50000 494 / 447; 262144: 8192, all new, 271 / 291,
 // 2048 of 32768 479 / 462; 282752: 64 heads, 6000, all new, 280 / 308; 396896 and more: 10000, all new, 353 / 350, 6000 of 9000, B 2, 508 / 477, 1000 of 131072
-// 785 / 679, 4096 of 8192, B 4, 605 / 538, 10923 of 32768 1957 / 1527.  d = 64: 524288: 16384 rows, 16 heads, 112 / 167, 8000 of 65536, 8 heads, 634 / 789;
-// 577536: 4000 of 9000, B 4, 500 / 505; 641024: 8000 of 20000 297 / 298; 704512 and more: 5462 of 16384, B 2, 682 / 635, 10923 of 32768 986 / 858 (but 20000,
-// all new, 417 / 487).  fp32, whose kernel is the same for both: 524288.
+// 785 / 679, 4096 of 8192, B 4, 605 / 538, 10923 of 32768 1957 / 1527.  fp32, whose kernel is the same for both: 524288.
+// At d = 64 few items that are long stay faster in pieces, and so do turns that are all of the context, whose items see half of it (what they see is counted there).  Pieces / queues, the
+// whole call, us, items and tiles: 320 of 289920 (64 heads, 547 rows of 115957) 1327 / 1433, 512 of 524288 (32 heads, 2000 of 131072) 1427 / 1596, 768 of 393216 1105 / 1157, 1008 of 516096 (16
+// heads, 8000 of 65536) 816 / 912, 1024 of 524288 1208 / 1291 and 1633 / 1669, 1280 of 500480 1314 / 1299, 1536 of 288000 652 / 682 and of 393216 1026 / 1036; 2048 of 524288 1620 / 1547 and 1251 / 1199, 2752
+// of 352256 756 / 742, 4032 of 516096 828 / 787.  64 heads, all new, which see 161312 (9000 rows) 417 / 447, 199712 (10000) 438 / 469; B 2, 262144 (8192) 643 / 619, 64 heads, 385440 (14000) 858 / 812.
 // ---------------------------------------------------------------------------------------------
-constexpr int64_t PIECES_TILES = 262144, PIECES_TILES_F32 = 524288;
+constexpr int64_t PIECES_TILES = 262144, PIECES_TILES_F32 = 524288, PIECES_SEEN_64 = 204800, PIECES_ITEMS_64 = 1536;
 // fewest tiles on either side of a cut (a part costs its result written and read: the time of two bf16 tiles; one of fp32 takes four times as long)
 __host__ __device__ __forceinline__ int cut_tiles(uint32_t base) { return base == 32 ? 2 : 1; }
 __host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : WORK_COLS; }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
@@ -645,7 +647,12 @@ int prefill_split_slots(int64_t items, int grid, bool pieces) {
     if (pieces) return part_slots(items, grid);
     return items > SPLIT_ITEMS ? 0 : items * ITEM_PARTS < SPLIT_SLOTS ? (int)items * ITEM_PARTS : SPLIT_SLOTS;
 }
-bool prefill_in_pieces(int BH, int64_t n, int nqb, int dtype, int d) { return (int64_t)BH * nqb * ((n + BN - 1) / BN) * d <= (dtype == 0 ? PIECES_TILES : PIECES_TILES_F32) * 128; }
+bool prefill_in_pieces(int BH, int64_t n, int nqb, int dtype, int d) {
+    const int64_t items = (int64_t)BH * nqb, keys = (n + BN - 1) / BN, tiles = items * keys * d / 128;
+    if (dtype != 0) return tiles <= PIECES_TILES_F32;
+    if (tiles <= PIECES_TILES || d != 64) return tiles <= PIECES_TILES;
+    return items <= PIECES_ITEMS_64 ? tiles <= 2 * PIECES_TILES : items * (keys - (BM / BN) * (nqb - 1) / 2) * d / 128 <= PIECES_SEEN_64;
+}
 
 // Pieces, of up to `grid`, whose parts `slots` hold; 0: the queues serve the call better.  Fewer pieces than workgroups make the run about
 // grid / pieces as long (of three places a CU only 5 % where two are filled), queues about a quarter of grid / items longer.  The whole

@@ -45,12 +45,12 @@ def test_tile_loop_edges(oracle, d, n, n_hat):
         assert np.abs(l[alive] - rlse[alive]).max() <= 2e-3
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d", [(6, 16, 4, 8100, 3000, 128), (6, 16, 4, 8100, 6100, 64)])
+@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d", [(6, 16, 4, 8100, 3000, 128), (8, 16, 4, 8100, 6100, 64)])
 def test_either_side_of_the_line(B, Hq, Hkv, n, n_hat, d):
-    """One call beyond the line between pieces and queues against calls of two thirds and one third of its batch, which lie below."""
+    """One call beyond the line between pieces and queues against calls of four of its dialogues and of the rest, which lie below."""
     print(f"either side of the line B={B} n={n} n_hat={n_hat} d={d}", flush=True)
-    tiles = lambda b: d * b * Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128) * ((n + 63) // 64)
-    assert tiles(B) > 262144 * 128 >= tiles(4)
+    in_pieces = lambda b: binding.prefill_in_pieces(binding.make_shape(b, Hq, Hkv, d, n, n_hat, 1, "bf16"))
+    assert not in_pieces(B) and in_pieces(4) and in_pieces(B - 4)
     rng = np.random.default_rng(n_hat)
     v_idx, s_idx = np.zeros((B, Hq, n), np.int32), np.zeros((B, Hq, n), np.int32)
     v_cnt, s_cnt = np.zeros((B, Hq), np.int32), np.zeros((B, Hq), np.int32)

@@ -1,17 +1,27 @@
-"""How ls_sparse_prefill shares its work among the workgroups: in pieces of about equal work up to 524288 tiles of 64 keys
-(counted as if every head were dense, half at d = 64), by work queues above.  One call over a batch that lies above that line is compared with calls
-over its parts, which lie below: the same cells summed in another order of tiles and parts."""
+"""How ls_sparse_prefill shares its work among the workgroups: in pieces of about equal work, and by work queues where the turn is larger.  One call over a batch
+that lies beyond the line is compared with calls over its parts, which lie below: the same cells summed in another order of tiles and parts."""
 import numpy as np
 import pytest
 import torch
 
-from paper_2507_13681_amd import inputs
-
-LINE = 524288 * 128
+from paper_2507_13681_amd import binding, inputs
 
 
-def _tiles(B, Hq, n, n_hat, d):
-    return d * B * Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128) * ((n + 63) // 64)
+def _in_pieces(B, Hq, Hkv, n, n_hat, d, dtype="bf16"):
+    return binding.prefill_in_pieces(binding.make_shape(B, Hq, Hkv, d, n, n_hat, 1, dtype))
+
+
+# tiles of 64 keys as if every head were dense, half at d = 64; items; of a turn that is all of the context, the tiles that it sees
+@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d,dtype,pieces", [
+    (1, 32, 8, 8192, 8192, 128, "bf16", True), (1, 32, 8, 8256, 8256, 128, "bf16", False),       # 262144 tiles
+    (1, 16, 4, 131072, 1024, 128, "bf16", True), (1, 16, 4, 131072, 1025, 128, "bf16", False), (1, 64, 8, 6000, 6000, 128, "bf16", False),
+    (1, 4, 1, 32768, 32768, 128, "f32", True), (1, 4, 1, 32832, 32832, 128, "f32", False),                                                     # 524288
+    (1, 64, 8, 115957, 547, 64, "bf16", True), (1, 32, 8, 131072, 2048, 64, "bf16", True), (1, 32, 8, 131072, 2049, 64, "bf16", False),        # few items: 524288
+    (3, 64, 8, 24576, 1024, 64, "bf16", True), (3, 64, 8, 24576, 1025, 64, "bf16", False),                                                     # 1536 items
+    (1, 64, 8, 9000, 9000, 64, "bf16", True), (1, 64, 8, 10000, 10000, 64, "bf16", True), (2, 64, 8, 8192, 8192, 64, "bf16", False),           # 204800 seen
+    (1, 64, 8, 16384, 8000, 64, "bf16", False), (1, 32, 8, 32768, 10923, 64, "bf16", False)])
+def test_where_the_line_lies(B, Hq, Hkv, n, n_hat, d, dtype, pieces):
+    assert _in_pieces(B, Hq, Hkv, n, n_hat, d, dtype) == pieces
 
 
 def _lists(rng, B, H, n):
@@ -40,15 +50,15 @@ def _lists(rng, B, H, n):
 def test_queues_and_pieces_agree(B, Hq, Hkv, n, n_hat, d, dtype):
     from tests.gpu_util import Pipeline, dev_lists
     print(f"queues and pieces B={B} Hq={Hq} n={n} n_hat={n_hat} d={d} {dtype}", flush=True)
-    cut = B // 2 + 1
-    assert _tiles(B, Hq, n, n_hat, d) > LINE >= _tiles(cut, Hq, n, n_hat, d)
+    cut = max(b for b in range(1, B) if _in_pieces(b, Hq, Hkv, n, n_hat, d, dtype))
+    assert not _in_pieces(B, Hq, Hkv, n, n_hat, d, dtype)
     q, k, v = inputs.make_plain(B, Hq, Hkv, n, n_hat, d, dtype=dtype, seed=n, q_scale=1.5)
     lists = _lists(np.random.default_rng(n), B, Hq, n)
     out, lse = Pipeline(q, k, v, 1, dtype).prefill(dev_lists(*lists), sentinel=True)
     # In bf16 each side rounds every probability (2^-9 relative, against references that differ) and the result: 4 * 2^-9 of
     # the largest value.  fp32: sums of at most n terms in another order, sqrt(n) * 2^-24 * 8 and room for exp's argument.
     tol = (4 * 2.0 ** -9 if dtype == "bf16" else 1e-5) * float(np.abs(v).max())
-    for b in (slice(0, cut), slice(cut, B)):
+    for b in (slice(b0, b0 + cut) for b0 in range(0, B, cut)):
         part, plse = Pipeline(q[b], k[b], v[b], 1, dtype).prefill(dev_lists(*(x[b] for x in lists)), sentinel=True)
         assert not torch.isnan(out[b]).any() and not torch.isnan(part).any()
         assert (out[b].float() - part.float()).abs().max().item() <= tol
@@ -62,7 +72,6 @@ def test_queues_and_pieces_agree(B, Hq, Hkv, n, n_hat, d, dtype):
 def test_items_are_shared_as_the_device_says(B, Hq, Hkv, n, n_hat, d):
     """Pieces and queues as the kernels left them: every item once, items of the one dense head cut; no cut without room for parts."""
     from tests.gpu_util import Pipeline, dev_lists
-    from paper_2507_13681_amd import binding
     print(f"items as shared B={B} Hq={Hq} n={n} n_hat={n_hat} d={d}", flush=True)
     q, k, v = inputs.make_plain(B, Hq, Hkv, n, n_hat, d, dtype="bf16", seed=n)
     every = np.broadcast_to(np.arange(n, dtype=np.int32), (B, Hq, n)).copy()
@@ -86,7 +95,6 @@ def test_items_are_shared_as_the_device_says(B, Hq, Hkv, n, n_hat, d):
 def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
     """A workspace with room for some of the parts: items are still cut, in fewer pieces or by the queues, to the same result."""
     from tests.gpu_util import Pipeline, dev_lists
-    from paper_2507_13681_amd import binding
     print(f"room for some parts Hq={Hq} n={n} n_hat={n_hat} d={d}", flush=True)
     q, k, v = inputs.make_plain(1, Hq, Hkv, n, n_hat, d, dtype="bf16", seed=n, q_scale=1.5)
     lists = dev_lists(*_lists(np.random.default_rng(n), 1, Hq, n))
@@ -95,7 +103,7 @@ def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
     items = Hq * ((n - (n - n_hat) // 128 * 128 + 127) // 128)
     places = 512 if d == 128 else 768
     slots, fewest = places - 1 + min(items, places - 1), 0.3          # fewest: share of them with which items are still cut
-    if _tiles(1, Hq, n, n_hat, d) > LINE:                             # (the longest part grows by half until all parts fit)
+    if not _in_pieces(1, Hq, Hkv, n, n_hat, d):                           # (the longest part grows by half until all parts fit)
         slots, fewest = 1024, 0.5
     tables = Hq * ((n + 31) // 32 * 4 + 64 + (n // 64 + 5) * 3) + items * 20 + 16384
     tol = 4 * 2.0 ** -9 * float(np.abs(v).max())                      # as between queues and pieces
@@ -121,7 +129,6 @@ def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
 def test_short_turns_of_many_heads(B, Hq, Hkv, n, n_hat, d):
     """Against the same call without room for parts: queues of whole items."""
     from tests.gpu_util import Pipeline, dev_lists
-    from paper_2507_13681_amd import binding
     print(f"short turns of many heads B={B} Hq={Hq} n={n} n_hat={n_hat} d={d}", flush=True)
     q, k, v = inputs.make_plain(B, Hq, Hkv, n, n_hat, d, dtype="bf16", seed=n, q_scale=1.5)
     lists = dev_lists(*_lists(np.random.default_rng(n), B, Hq, n))
