@@ -29,15 +29,9 @@
 
 namespace ls {
 
-#ifndef LS_RING_S
-#define LS_RING_S 4       // K fragments in flight ahead of the QK^T products
-#endif
-#ifndef LS_RING_P
-#define LS_RING_P 3       // V^T fragments in flight ahead of the P*V products
-#endif
-#ifndef LS_RING_PH
-#define LS_RING_PH 2      // ... with queues, where there are fewer registers
-#endif
+constexpr int RING_S = 4;        // K fragments in flight ahead of the QK^T products
+constexpr int RING_P = 3;        // V^T fragments in flight ahead of the P*V products
+constexpr int RING_P_QUEUES = 2; // ... with queues, where there are fewer registers
 constexpr int BM = 128;   // query rows per workgroup
 constexpr int BN = 64;    // keys per tile
 constexpr int PREFILL_THREADS = 256;
@@ -907,21 +901,8 @@ struct TileCfg {
     static constexpr int DBLK = D / 32;                   // 32-wide output column blocks
 };
 
-template <typename T>
-__device__ __forceinline__ void store_vt(unsigned char* vt, int stride, int d0, int col, const f32x4 raw);
-
-// raw holds 16 bytes of one V row: elements d0 .. d0+EPC-1; scatter them down column `col`.
-template <>
-__device__ __forceinline__ void store_vt<bf16_t>(unsigned char* vt, int stride, int d0, int col, const f32x4 raw) {
-    struct U4 { uint32_t w[4]; } u = __builtin_bit_cast(U4, raw);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        *reinterpret_cast<uint16_t*>(vt + (d0 + 2 * i) * stride + col * 2) = (uint16_t)(u.w[i] & 0xFFFFu);
-        *reinterpret_cast<uint16_t*>(vt + (d0 + 2 * i + 1) * stride + col * 2) = (uint16_t)(u.w[i] >> 16);
-    }
-}
-template <>
-__device__ __forceinline__ void store_vt<float>(unsigned char* vt, int stride, int d0, int col, const f32x4 raw) {
+// raw holds 16 bytes of one V row: elements d0 .. d0 + 3; scatter them down column `col`.
+__device__ __forceinline__ void store_vt(unsigned char* vt, int stride, int d0, int col, const f32x4 raw) {
     *reinterpret_cast<float*>(vt + (d0 + 0) * stride + col * 4) = raw.x;
     *reinterpret_cast<float*>(vt + (d0 + 1) * stride + col * 4) = raw.y;
     *reinterpret_cast<float*>(vt + (d0 + 2) * stride + col * 4) = raw.z;
@@ -1308,7 +1289,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
 #pragma unroll
         for (int i = 0; i < C::CPT; ++i) {
             *reinterpret_cast<f32x4*>(kt + rk * C::K_STRIDE + 16 * (ck0 + 4 * i)) = kreg[i];
-            store_vt<T>(vt, C::VT_STRIDE, (cv0 + i) * C::EPC, vcol, vreg[i]);
+            store_vt(vt, C::VT_STRIDE, (cv0 + i) * C::EPC, vcol, vreg[i]);
         }
         if (t >= n1 && tid < BN) colring[(t & 1) * BN + tid] = colv;
     };
@@ -1588,7 +1569,7 @@ __global__ __launch_bounds__(PREFILL_THREADS, (D == 64 ? 3 : 2) + (QUEUES ? 1 : 
     // sum says that one of them may exceed the limit (or is no number, as with the first cells of a row: -mneg = -inf), the half is
     // done again with a new reference.  s keeps the logits for that.
     constexpr int NS = C::KSTEPS, NV = 2 * C::DBLK;        // products of a half
-    constexpr int RS = LS_RING_S, RV = QUEUES ? LS_RING_PH : LS_RING_P;
+    constexpr int RS = RING_S, RV = QUEUES ? RING_P_QUEUES : RING_P;
     static_assert(RS <= NS && RV <= NV, "fragments in flight");
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     struct Soft { uint32_t p[8]; float sum[2]; };          // packed probabilities and their sums
