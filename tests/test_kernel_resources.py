@@ -11,6 +11,7 @@ from paper_2507_13681_amd import build
 NO_SCRATCH = {
     "ls_decode.hip": ["decode_kernel"],
     "ls_prefill.hip": ["plan_kernel", "sched_kernel", "prefill_bf16_kernel", "combine_kernel"],
+    "ls_score.hip": ["stats_kernel", "range_stats_kernel", "merge_kernel", "lines_kernel", "diagonals_kernel", "finish_kernel"],
     "ls_select.hip": ["order_kernel", "walk_kernel", "walk_exact_kernel", "emit_kernel", "merge_lines_kernel", "topb_one_kernel"],
 }
 
