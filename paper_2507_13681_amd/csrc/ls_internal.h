@@ -15,20 +15,20 @@ struct ScoreArgs {
     float scale_log2e;
     float* part;              // [B*Hkv][nkb][G*w][2] per key block max / sum of every row; later the shares of the totals
     float* rowstat;           // [BH*w][2]        row max, 1 / row sum
-    float* spart;             // [2][BH][n][2]    mode 0: diagonal partial sum / max by key-block parity, or what neighbouring key blocks leave each other (edge, edge_total, edge_done)
+    float* spart;             // [2][BH][n][2]    mode 0: diagonal partial sum / max by key-block parity, or what neighbouring key blocks leave each other (edge, edge_share, edge_done)
     float *vert, *slash, *vmax, *smax, *total;
     float* gscore;            // [B*Hkv][n]       group-summed column sums (retention score)
     float* a_win;             // [BH][w][n]       the window matrix (mode 3), or [heads from bh_first on][t1 - t0][n] a band of it (mode 1)
     int64_t win_rows;         // mode 1: how many rows of a KV head's G heads the buffer takes, at least one
     // set by run_score for each launch
     bool retain;              // mode 2: all rows in LDS
-    int parts, stat_chunks;   // ranges of keys whose row statistics lie in `part`; chunks of rows of a workgroup of stats_kernel
+    int parts, stat_chunks;   // ranges of keys whose row statistics lie in `part`; chunks of rows of a workgroup of range_stats_kernel, at most
     bool join;                // mode 0: lines_kernel joins the key blocks' results itself
     int shares;               // mode 0: workgroups that share a KV head's query heads
     int bk0, bh_first;        // first KV head / query head
     int t0, t1;               // window rows whose matrix is written out
     int sums;                 // mode 1: the column sums of the chunks are added here (not on a chunk's later bands)
-    uint32_t* done;           // [BH] workgroups of lines_kernel or finish_kernel that are done, of a head (the first of a share), cleared by stats_kernel (null: not used)
+    uint32_t* done;           // [BH] workgroups of lines_kernel or finish_kernel that are done, of a head (the first of a share), cleared by stats_kernel or range_stats_kernel (null: not used)
 };
 
 // Where range x of `ranges` begins among `count` tiles or blocks of keys: floor(count * x / ranges).  That product passes 2^32 in ls_score, which has up to 768

@@ -579,6 +579,8 @@ __device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row,
 // grid (workgroups that share a KV head's key blocks, B*Hkv).  Bound by the reads of K.  A wave has its 32 keys of a block in registers and those of
 // the workgroup's next block on their way to its own stage; between blocks nobody waits for anybody.  Against a workgroup per block past which the chunks
 // come, a barrier each, us: 16384 entries, B 4, 128 rows a KV head 39 -> 31, 32768, B 2, d = 64 18.4 -> 13.8, 65536, 8 KV heads of 16 rows 26 -> 21.
+// Four chunks of 32 rows: room for eight leaves a CU one workgroup at d = 128.  The whole ls_kv_compress, four / eight, us: 128 rows 73 / 82; 192 129 / 123, 256 120 / 124, 32768 entries, B 1, 81 / 82.  At d = 64
+// it leaves two, and more rows would gain: 192 99.6 / 79.2, 256 90.6 / 79.9, 32768 entries, B 1, 65 / 60.
 constexpr int RETAIN_CHUNKS = 4;
 template <int D>
 __host__ __device__ constexpr int retain_lds() { return (4 + RETAIN_CHUNKS) * RowTile<bf16_t, D>::BYTES + RETAIN_CHUNKS * 32 * 8; }
@@ -939,7 +941,7 @@ __global__ __launch_bounds__(256) void diagonals_kernel(ScoreArgs a) {
 // ---- finish: add the two diagonal partials, reduce the total ------------------------------------
 // grid (B*Hq, FINISH_SPLIT).  Diagonal o is met by keys n-w-o .. n-1-o (clipped at 0), i.e. by key blocks
 // kA = max(0, n-w-o)/SB and kB = (n-1-o)/SB, which are equal or adjacent.  The last of a head's workgroups to get to its
-// end (a counter per head, which stats_kernel has cleared) adds their shares of the total, in a fixed tree order.
+// end (a counter per head, which the statistics pass has cleared) adds their shares of the total, in a fixed tree order.
 __global__ __launch_bounds__(1024) void finish_kernel(ScoreArgs a, int contiguous) {
     __shared__ float red[1024];
     const int bh = blockIdx.x, part = blockIdx.y, tid = threadIdx.x;
@@ -1018,25 +1020,25 @@ static int head_shares(const ScoreArgs& a, int kv_heads, int band = 0) {
 }
 // Whether lines_kernel adds what neighbouring key blocks have of a diagonal, and the totals, itself.  That saves finish_kernel's launch and round trips, and costs a
 // workgroup three round trips at its end, in which others of its CU have to keep it busy: where nearly all are there at once (1024 are).
-// finish_kernel / so, us: 1024 keys, fp32, 17.0 / 15.5; 32 heads, 64 rows, of 2048 keys 20.8 / 19.5, 8192 36.9 / 32.8; 16 heads of 64, 48 rows
-// of 5003 keys 23.9 / 20.4; more of them: eight chunks each 82.4 / 81.7 and 89.3 / 90.6, four 90 / 94, two 35.1 / 37.7, one 31.6 /
-// 33.5 (20000 keys), 66 / 82 (32 KV heads of 32768).  Beyond 16384 keys a share of the total is more than two reads a lane.
+// The whole ls_score, finish_kernel / so, us: 1024 keys, fp32, 16.1 / 15.3; 32 heads, 64 rows, of 2048 keys 19.7 / 18.5, 8192 36.0 / 34.8, B 2 52.7 / 50.5, 12347 50.8 / 49.7, 16384 51.5 /
+// 50.8; 16 heads of 64, 48 rows of 5003 keys 22.2 / 20.8; 1536 workgroups, B 8, 3000 keys 75.4 / 74.0, B 3, 8192 70.7 / 70.8; 2048: B 4, 8192 89.0 / 85.2, but with fewer chunks of rows a workgroup,
+// MHA, four of 16384 44.6 / 47.7, two of 8192 45.2 / 46.7, one 38.9 / 40.8.  Beyond 16384 keys a share of the total is more than two reads a lane: 20000 60.8 / 63.5, 8 rows of 8 heads 29.7 / 32.7, 65536, 4 heads
+// 30.4 / 35.8.
 static bool joins(const ScoreArgs& a, int kv_heads) { return (int64_t)a.nkb * kv_heads * a.shares <= 1600 && a.n <= 16384; }
 // The ranges of keys of range_stats_kernel; 0: stats_kernel, where there is little work, or so few rows that waves would stand idle.
 // As many as fill the chip with three workgroups a CU; for the retention score, which keeps their statistics apart, no more than the blocks of 128 keys that `part` has room for, and
 // no more than give every CU two workgroups (64 to 256 of them: beyond, merge_kernel takes what they save).  The whole ls_kv_compress, us, stats_kernel / 64 ranges / so: one KV head, 64
 // rows of 262144 keys 67 / 78 / 51, 128 of 131072 49 / 65 / 45, 256 67 / 75 / 56; two, 64 of 262144 87 / 90 / 74; four, 128 of 131072, d = 64, 74 / 72 / 64; eight, 64 ranges / 96: 131 / 133.  Four chunks of rows a workgroup, eight where there is much work: eight / four, us, 131072 keys 140 / 157, 16384 keys, B 4, 75 / 81, 32768
 // 24.0 / 24.4, 12347 16.0 / 13.8.
-// The lines.  The kernels, stats_kernel / range_stats_kernel, us, retention score of 16 rows: 8 heads, 16384 keys (1024 of the products below) 5.9 / 9.3, 32 / 8 heads (2048) 8.5 / 9.6, 32768 keys (4096)
-// 16.9 / 13.9, 4 / 1 heads, 32768 (512) 5.1 / 8.8.  ls_score: 8192 keys, 32 heads, 64 rows (4096) 32.8 / 33.8, 12347 (6208) 48.5 / 48.6, 131072, 16 heads of 64, 32 rows (16384)
-// 85.1 / 83.4, 4 heads, 100 rows 91.6 / 86.6, 32768, 32 heads 88.5 / 82.9, 131072, 128 rows 508 / 486, 16384, B 4, 64 heads 274 / 262.
-constexpr int STATS_PARTS = 64, STATS_PARTS_MOST = 256;
+// The lines.  The whole call, stats_kernel / range_stats_kernel, us.  Retention score of 16 rows: 8 heads, 16384 keys (1024 of the products below) 25.7 / 27.8, 32 / 8 heads (2048) 28.8 / 29.1, 20000 keys
+// (2512) 39.2 / 37.2, 32768 (4096) 47.3 / 45.1, 4 / 1 heads, 32768 (512) 25.7 / 26.2, 131072 (2048) 43.4 / 40.1.  ls_score: 8192 keys, 32 heads, 64 rows (4096) 34.9 / 35.1, 12347 (6208) 50.1 / 48.2, 16384 (8192) 55.0 /
+// 50.0, 32768 91.1 / 84.3, 131072, 16 heads of 64, 32 rows 86.8 / 84.7, 4 heads, 100 rows 93 / 88, 32 heads, 128 rows 520 / 491, 16384, B 4, 64 heads 288 / 269.
 //
 // Explicit positions see parts of a context that differ from row to row, and the ranges of a KV head come out uneven: few and long ones are worse than none.  The whole ls_score, us,
 // stats_kernel / range_stats_kernel, d = 128: 3 to 12 ranges of eleven blocks, B 4, 64 heads, 16384 keys 703 / 715, B 8, 8192 701 / 720, B 16, 4096 725 / 741; 6 of four, B 4, 3000 162 / 159;
 // 24 of five, B 4, 32 heads, 16384 347 / 345; 96 of three, 32768 183 / 180; 48 of 21, 131072, 128 rows 1322 / 1306.  d = 64, whose keys are half as much to read, gains nothing:
 // 613 / 624, 623 / 658 (B 8), 320 / 324 (32 heads), 167 / 168 (32768), 1214 / 1240 (131072).
-constexpr int STATS_FEW = 16, STATS_LONG = 8;
+constexpr int STATS_PARTS = 64, STATS_PARTS_MOST = 256, STATS_FEW = 16, STATS_LONG = 8;
 static int stats_split(ScoreArgs& a, bool bf16, int d, bool retention) {
     a.parts = a.nkb; a.stat_chunks = STATS_CHUNKS;
     const int count = Chunks(a.w, a.G, packs(a.w)).count;

@@ -811,9 +811,10 @@ constexpr int PUT_WORDS = 1024;
 constexpr size_t put_lines_bytes(int64_t n) { return (size_t)(n < 32 * PUT_WORDS ? (n + 31) / 32 * 32 : 32 * PUT_WORDS) * 2; }
 
 // Chosen prefixes -> ascending index lists of both lists of a head, by the workgroup that has walked them (half of its NT
-// threads a list).  bm: 2 * ceil(n / 32) words of LDS and 2 * put_lines_bytes(n) behind them.  Up to EMIT_LINES lines; beyond, the 192 threads a list
-// take longer than emit_kernel's 1024 and its launch.  ls_select, 32 heads, launch / here, us: 1024 lines 17.1 / 16.1, 4096 24.7 / 24.7, 8192
-// 33.5 / 34.8, 12288 39.4 / 41.2, 16384 42.1 / 45.0; 256 heads of 1500 27.0 / 24.7; with exact overlaps 1024 69.8 / 69.3, 8192 80.2 / 81.5.
+// threads a list).  bm: 2 * ceil(n / 32) words of LDS and 2 * put_lines_bytes(n) behind them.  Up to EMIT_LINES lines; beyond, the 192 threads a list (walk_kernel; walk_exact_kernel
+// 512) take longer than emit_kernel's 1024 and its launch.  ls_select, 32 heads, launch / here, us: 1024 lines 17.1 / 16.1, 4096 24.7 / 24.7, 8192
+// 33.5 / 34.8, 12288 39.4 / 41.2, 16384 42.1 / 45.0; 256 heads of 1500 27.0 / 24.7; with exact overlaps (six seeds in turn; the walk differs more from seed to seed) 1024 69.8 / 69.3,
+// 4097 87.2 / 88.8, 6000 106.8 / 108.1, 64 heads 108.5 / 109.2, 8192 80.0 / 80.1, 64 heads 130.3 / 131.1.
 constexpr int64_t EMIT_LINES = 4096;
 template <int NT>
 __device__ __forceinline__ void emit_both(const SelectArgs& a, int bh, int cnt_s, int cnt_v, uint32_t* bm) {
