@@ -235,3 +235,30 @@ def test_retention_over_ranges(B, Hq, Hkv, n, n_obs, d, ranges, chunks, streams,
             threshold = np.sort(want)[-budget]
             for i in set(np.argsort(-want, kind="stable")[:budget]).symmetric_difference(idx[b, g].tolist()):
                 assert abs(want[i] - threshold) <= 1e-3 * threshold
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,w,d", [(1, 64, 8, 6200, 16, 128), (4, 32, 8, 6300, 32, 64), (2, 48, 8, 8100, 16, 64)])
+def test_retention_sums_chunk_by_chunk(B, Hq, Hkv, n, w, d):
+    """Rows of zeros: a key's score is the sum of 1 / L over the rows, L whole numbers, to the last bit as 32 rows at a time are added (eight by eight and four of them in a
+    lane, then the halves): through all rows at once the rounding errors are those of a sum four times as long."""
+    print(f"chunk by chunk B={B} Hq={Hq} n={n} w={w} d={d}", flush=True)
+    shape, budget = binding.make_shape(B, Hq, Hkv, d, n, 1, w, "bf16"), 100
+    assert binding.score_route(shape, 2)["streams"]
+    q, k = torch.zeros(B, Hq, w, d, device="cuda", dtype=torch.bfloat16), torch.randn(B, Hkv, n, d, device="cuda").to(torch.bfloat16)
+    idx, cnt = torch.empty(B, Hkv, budget, dtype=torch.int32, device="cuda"), torch.empty(B, Hkv, dtype=torch.int32, device="cuda")
+    score, ctx = torch.empty(B, Hkv, n, device="cuda"), binding.Context(shape, budget)
+    ctx.ls_kv_compress(shape, budget, q, k, None, idx, cnt, None, None)
+    ctx.debug_compress_score(shape, score)
+    rows, one = Hq // Hkv * w, np.float32(1)
+    il = [one / np.float32(n - w + r % w + 1) for r in range(rows)]
+    halves, through = [np.float32(0)] * 2, [np.float32(0)] * 2
+    for c in range(0, rows, 32):
+        for g in range(2):
+            ps = np.float32(0)
+            for r in range(16):                            # register r of a lane of half g
+                x = il[c + 8 * (r // 4) + 4 * g + r % 4]
+                ps, through[g] = ps + x, through[g] + x
+            halves[g] = halves[g] + ps
+    want = halves[0] + halves[1]
+    assert want != through[0] + through[1]                 # (these shapes tell the two orders apart)
+    assert (score[..., :n - w - 127] == float(want)).all()
