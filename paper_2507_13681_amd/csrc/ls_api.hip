@@ -157,8 +157,8 @@ void window_scratch(ls::ScoreArgs& a, const ls_shape* s, Bump& bp) {
 // The window matrix of explicit scoring positions passes through what is left of the workspace, band by band.  The partial sums
 // of the diagonals, which that path does not need, leave room for four rows of every head, and any call gets by with those.
 // Asked for is room for the whole matrix up to WIN_BYTES, as much as the parts of long attention items take (ws_prefill).
-// ls_score, 32 / 8 heads of 128, 64 rows, 32768 keys: 331 us through 16 MiB, 192 through 64, 158 to 185 with the whole matrix (256);
-// 12347 keys: 103 us through 47 MiB, 97 through 64, 84 whole (92); 131072 keys, 128 rows: 1615 through 64, 1399 through 224.
+// ls_score, 32 / 8 heads of 128, 64 rows, 32768 keys: 331 us through 16 MiB, 262 through 47, 189 through 64, 172 through 224, 158 with the whole matrix (256);
+// 12347 keys: 195 us through 16 MiB, 109 through 47, 92 through 64, 84 whole (96); 131072 keys, 128 rows: 2130 through 47, 1387 through 64, 1284 through 224, 1012 whole (2048).
 constexpr size_t WIN_BYTES = 64u << 20;
 size_t ws_score(const ls_shape* s, bool lines) {
     const size_t BH = (size_t)s->B * s->Hq;

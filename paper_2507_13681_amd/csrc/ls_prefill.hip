@@ -323,6 +323,8 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // 65536: 4096 rows, all new, 114 / 150; 129696: 2500 of 12347 253 / 285; 225216: 1000 of 50000 494 / 447; 262144: 8192, all new, 271 / 291,
 // 2048 of 32768 479 / 462; 282752: 64 heads, 6000, all new, 280 / 308; 396896 and more: 10000, all new, 353 / 350, 6000 of 9000, B 2, 508 / 477, 1000 of 131072
 // 785 / 679, 4096 of 8192, B 4, 605 / 538, 10923 of 32768 1957 / 1527.  fp32, whose kernel is the same for both: 524288.
+// That is of turns whose newest rows were scored, some heads of which come out dense.  Of rows scored at random positions all heads are alike, and up to 524288 the pieces stay ahead: 385024, 6000 of
+// 16384, 390 / 420, 377600, 64 heads, 3114 of 15093, 552 / 585 (newest rows 909 / 866), 524288, 4000 of 32768, 843 / 876; what was selected is not known here.
 // At d = 64 few items that are long stay faster in pieces, and so do turns that are all of the context, whose items see half of it (what they see is counted there).  Pieces / queues, the
 // whole call, us, items and tiles: 320 of 289920 (64 heads, 547 rows of 115957) 1327 / 1433, 512 of 524288 (32 heads, 2000 of 131072) 1427 / 1596, 768 of 393216 1105 / 1157, 1008 of 516096 (16
 // heads, 8000 of 65536) 816 / 912, 1024 of 524288 1208 / 1291 and 1633 / 1669, 1280 of 500480 1314 / 1299, 1536 of 288000 652 / 682 and of 393216 1026 / 1036; 2048 of 524288 1620 / 1547 and 1251 / 1199, 2752
