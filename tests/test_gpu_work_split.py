@@ -91,7 +91,7 @@ def test_items_are_shared_as_the_device_says(B, Hq, Hkv, n, n_hat, d):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("Hq,Hkv,n,n_hat,d", [(16, 4, 3001, 3001, 64), (8, 2, 4096, 4096, 128), (32, 8, 5003, 300, 128), (32, 8, 4099, 4099, 128),
-                                                (20, 4, 130001, 3300, 64)])      # queues whatever the room: beyond the line
+                                                (32, 8, 131001, 1100, 64), (20, 4, 130001, 3300, 64)])      # few long items; queues whatever the room: beyond the line
 def test_room_for_some_parts(Hq, Hkv, n, n_hat, d):
     """A workspace with room for some of the parts: items are still cut, in fewer pieces or by the queues, to the same result."""
     from tests.gpu_util import Pipeline, dev_lists
