@@ -36,15 +36,19 @@ constexpr int BM = 128;   // query rows per workgroup
 constexpr int BN = 64;    // keys per tile
 constexpr int PREFILL_THREADS = 256;
 
-// Work is counted in eighths of a contiguous tile: a packed tile takes longer (its rows are gathered), and an item takes as long as
+// Work is counted in eighths of a contiguous tile: a packed tile takes longer (its rows are gathered, and its loop has more to see to), and an item takes as long as
 // four tiles beside its own (queries, lists, the first tile's way from memory, the results; one tile in fp32, whose tiles take long).
-constexpr uint32_t WORK_TILE = 8, WORK_COLS = 9;
+// bf16: with packed tiles at nine eighths, as before the loop of contiguous tiles had its own short form, the pieces of heads of columns came last, 258 to 336 us where those of diagonals took 219 to 272 (2000
+// of 20000 rows).  9 / 10 / 11 / 12, the whole call, us: that turn 488 / 469 / 465 / 467, 3000 rows 611 / 592 / 581 / 584, 1000 of 32768 439 / 429 / 419 / 419, 500 of 65536 647 / 628 / 621 / 622;
+// fp32 has nine.
+constexpr uint32_t WORK_TILE = 8;
 // What an item is: the contiguous tiles (at most 4097) and the columns (at most 262144) of a row block.
 __host__ __device__ __forceinline__ uint32_t pack_item(uint32_t n1, uint32_t cols) { return n1 | cols << 13; }
 __host__ __device__ __forceinline__ int item_blocks(uint32_t r) { return (int)(r & 0x1FFFu); }
 __host__ __device__ __forceinline__ int item_cols(uint32_t r) { return (int)(r >> 13); }
 __host__ __device__ __forceinline__ uint32_t work_base(int dtype) { return dtype == 0 ? 32 : 8; }
-__host__ __device__ __forceinline__ uint32_t item_work(uint32_t base, uint32_t n1, uint32_t n2) { return base + n1 * WORK_TILE + n2 * WORK_COLS; }
+__host__ __device__ __forceinline__ uint32_t work_cols(uint32_t base) { return base == 32 ? 11 : 9; }        // of a packed tile
+__host__ __device__ __forceinline__ uint32_t item_work(uint32_t base, uint32_t n1, uint32_t n2) { return base + n1 * WORK_TILE + n2 * work_cols(base); }
 // A half's probabilities (relative to the running reference) may sum to this in a lane before the reference moves to the half's maximum;
 // in an item's first tiles to less (4, 8, 16: twice as much every tile).  bf16 is as exact up there as around one, but the probability
 // that is the reference is one, without rounding, and a row's largest cells mostly come early (the band beside the
@@ -333,7 +337,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 constexpr int64_t PIECES_TILES = 262144, PIECES_TILES_F32 = 524288, PIECES_SEEN_64 = 204800, PIECES_ITEMS_64 = 1536;
 // fewest tiles on either side of a cut (a part costs its result written and read: the time of two bf16 tiles; one of fp32 takes four times as long)
 __host__ __device__ __forceinline__ int cut_tiles(uint32_t base) { return base == 32 ? 2 : 1; }
-__host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : WORK_COLS; }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
+__host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : work_cols(base); }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
 
 struct Cut { int item, tile; };                            // a piece begins at this tile of this item
 // The cut `u` into an item of n1 contiguous and n2 packed tiles.
@@ -342,7 +346,7 @@ __host__ __device__ __forceinline__ Cut cut_item(uint32_t base, uint32_t u, int 
     int t = 0;
     if (u >= base + cut_tiles(base) * WORK_TILE) {
         const uint32_t v = u - base;
-        t = v < n1 * WORK_TILE ? (int)(v / WORK_TILE) : n1 + (int)((v - n1 * WORK_TILE) / WORK_COLS);
+        t = v < n1 * WORK_TILE ? (int)(v / WORK_TILE) : n1 + (int)((v - n1 * WORK_TILE) / work_cols(base));
         if (t + cut_tiles(base) > tiles) t = tiles;
     }
     return t > 0 && t >= tiles ? Cut{item + 1, 0} : Cut{item, t};
@@ -356,7 +360,7 @@ __host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work
     pieces = pieces > most ? most : pieces < least ? least : pieces;
     // (two bf16 tiles or a packed one of fp32 a piece, and more.  Of 512 fp32 pieces the smaller are 7/8 of that, less than a tile: two cuts may then fall into one, and what lies between
     // them is a part without tiles, which is written and weighs nothing)
-    const uint32_t fewest = base == 32 ? 2 * WORK_TILE : WORK_COLS;
+    const uint32_t fewest = base == 32 ? 2 * WORK_TILE : work_cols(base);
     return pieces <= work / fewest ? (int)pieces : work >= fewest ? (int)(work / fewest) : 1;
 }
 // where piece p begins
@@ -365,14 +369,15 @@ __host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work
 // took 220 us, 256 to 511 262 (first turn of 8192 rows), at d = 64 41, 50 and 60 us (5003 rows carried), and a CU left to its last
 // workgroup is not busy.  So where every place is taken the pieces of a place are that much larger or smaller.  Shares of
 // 64 / 64, 67 / 61, 70 / 58, 73 / 55, 76 / 52, the whole call, us: 8192 rows, all new, 300 / 296 / 291 / 290 / 297, 2048 of 32768 481 / 473 / 465 /
-// 460 / 475; at d = 64 64, 69, 74, 79, 84 for the first of three 90 / 88 / 88 / 88 / 87, 5003 rows, all new, 73 / 71 / 71 / 71 / 70.
+// 460 / 475; at d = 64 64, 69, 74, 79, 84 for the first of three 90 / 88 / 88 / 88 / 87, 5003 rows, all new, 73 / 71 / 71 / 71 / 70.  That was with 72 and 80; the loops as they are leave the first place 5 %
+// early so, and 72 and 80 / 74 and 84 / 76 and 88 take 3000 of 20000 rows 590 / 581 / 580, 8192, all new, 289.5 / 286 / 286, 100 of 131072 731 / 731 / 743, at d = 64 8000 of 16384 466 / 459 / 455, 1777 of 5003 150 / 148 / 147.
 //
 // But not where items of alike work come out in whole pieces, or pieces in whole items (few row blocks a head, `equal` in my_span): then equal
 // pieces leave most items uncut, and the query heads of a group, cut at the same tiles, meet at the same keys in the L2.  By place / equal,
 // us: 8 dialogues, 8 heads of 128, 2 rows of 98648 keys 551 / 326; 4, 64 heads, 4 rows of 11569, every diagonal, 237 / 164; 4, 32 heads of 64, columns, 331
 // rows of 9141 28 / 24; the other way 4, 32 heads, 84 rows of 1435 53 / 57, 2, 64 heads, one of them dense, 3 rows of 116925 115 / 124.  (Short turns of 10 to 130000
 // keys, 1 to 64 dialogues: of 108 that are so 27 gain more than 3 %, 7 lose more; of 51 that are not, 12 and 10.  fp32, whose tiles wait for no memory: 52 / 56.)
-constexpr uint32_t FIRST_OF_2 = 72, FIRST_OF_3 = 80;       // of 128, of 192 (the second of three: 64)
+constexpr uint32_t FIRST_OF_2 = 74, FIRST_OF_3 = 84;       // of 128, of 192 (the second of three: 64)
 __host__ __device__ __forceinline__ uint32_t cut_at(uint32_t total, int p, int pieces, bool equal) {
     if (!equal && (pieces == 512 || pieces == 768)) {                  // 32 CUs an XCD, whose workgroups take neighbouring pieces
         const uint32_t places = pieces / 256, xcd = (uint32_t)p / (32 * places), j = (uint32_t)p % (32 * places);
@@ -1379,8 +1384,8 @@ __global__ __launch_bounds__(PREFILL_THREADS, 2) void prefill_kernel(PrefillArgs
 // A tile of the 32768 keys' turn, three quarters diagonals, took a SIMD 2060 cycles with two halves and their transfers in one burst, 1830 with the
 // transfers in between the products and fewer scalar instructions, 1600 by halves.  The whole call, us (as it was / tiles / halves): 10923 of 32768 rows 1700 / 1615 /
 // 1580, all heads dense 4840 / 4750 / 4240, diagonals only 2055 / 1890 / 1850; 16384 of 131072 14670 / 13660 / 13600, B 4, 64 heads, 5462 of 16384 4120 / 3900 / 3660;
-// 8192 rows, all new (pieces) 275 / 266.  (What the clock gives back: 2.24 GHz as it was, 2.0 by halves.  On some cards it falls further while calls follow each other, and with it what
-// a turn of diagonals alone gains: 3000 new of 20000 rows 437 us alone as it was and 427 now, 5 % fewer cycles; one behind the other 441 and 449 on one card, 441 and 481, at 2.35 and 2.17 GHz, on another.)
+// 8192 rows, all new (pieces) 275 / 266.  (What the clock gives back: 2.24 GHz as it was, 2.0 by halves.  A workgroup of 2000 to 3000 of 20000 rows takes 13 % fewer
+// cycles in pieces than it did, at a clock that is 7 % lower: 2.15 to 2.19 GHz instead of 2.30 to 2.35.)
 // ---------------------------------------------------------------------------------------------
 template <int D>
 struct DirectCfg {
