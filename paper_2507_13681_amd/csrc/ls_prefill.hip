@@ -323,18 +323,17 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 // 4096 35.2 / 22.4, 700 of 3001 59.4 / 56.8, 4096, all new, 58.2 / 52.8.
 // The line.  What the pieces' estimates miss nothing evens out, and the row spreads the heads of a moment wider than the queues
 // do: the longer the run, the more both cost.  In bf16 the queues' kernel also has a workgroup more per CU (prefill_bf16_kernel).
-// Tiles here are those that dense heads would have, and a tile of d = 64 counts half.  Pieces / queues, the whole call, us, d = 128:
-// 65536: 4096 rows, all new, 114 / 150; 129696: 2500 of 12347 253 / 285; 225216: 1000 of 50000 494 / 447; 262144: 8192, all new, 271 / 291,
-// 2048 of 32768 479 / 462; 282752: 64 heads, 6000, all new, 280 / 308; 396896 and more: 10000, all new, 353 / 350, 6000 of 9000, B 2, 508 / 477, 1000 of 131072
-// 785 / 679, 4096 of 8192, B 4, 605 / 538, 10923 of 32768 1957 / 1527.  fp32, whose kernel is the same for both: 524288.
-// That is of turns whose newest rows were scored, some heads of which come out dense.  Of rows scored at random positions all heads are alike, and up to 524288 the pieces stay ahead: 385024, 6000 of
-// 16384, 390 / 420, 377600, 64 heads, 3114 of 15093, 552 / 585 (newest rows 909 / 866), 524288, 4000 of 32768, 843 / 876; what was selected is not known here.
-// At d = 64 few items that are long stay faster in pieces, and so do turns that are all of the context, whose items see half of it (what they see is counted there).  Pieces / queues, the
-// whole call, us, items and tiles: 320 of 289920 (64 heads, 547 rows of 115957) 1327 / 1433, 512 of 524288 (32 heads, 2000 of 131072) 1427 / 1596, 768 of 393216 1105 / 1157, 1008 of 516096 (16
-// heads, 8000 of 65536) 816 / 912, 1024 of 524288 1208 / 1291 and 1633 / 1669, 1280 of 500480 1314 / 1299, 1536 of 288000 652 / 682 and of 393216 1026 / 1036; 2048 of 524288 1620 / 1547 and 1251 / 1199, 2752
-// of 352256 756 / 742, 4032 of 516096 828 / 787.  64 heads, all new, which see 161312 (9000 rows) 417 / 447, 199712 (10000) 438 / 469; B 2, 262144 (8192) 643 / 619, 64 heads, 385440 (14000) 858 / 812.
+// Tiles here are those that dense heads would have, and a tile of d = 64 counts half.  Pieces / queues, the whole call, us, d = 128, up to
+// 262144 tiles: 4096 rows, all new, 114 / 150, 2500 of 12347 253 / 285, 2000 of 32768 660 / 692, 500 of 65536, 64 heads, 1030 / 1064 (but 1000 of 65536 773 / 752).
+// Up to 524288 what it takes beside the length is a few items a workgroup: fewer and longer ones are cut too often, and more of them the queues even out.  Items and tiles: 752 of 385024 (16 heads, 6000 of 32768)
+// 787 / 815, 768 of 393216 861 / 876, 1024 of 524288 (4000 of 32768) 949 / 1013, 1504 of 385024 581 / 589, 1536 of 288768 428 / 433, 1600 of 377600 836 / 851, 1664 of 520832 (64 heads, 3114 of 20000) 1041 /
+// 1122, 2560 of 401920 661 / 679; 192 of 393216 (700 of 131072) 1534 / 1482, 512 of 524288 1081 / 1046 and 1194 / 1178, 640 of 500480 1110 / 1087, 3072 of 433152 595 / 590, 4096 of 524288 (B 4, 4096 of 8192) 816 / 746.  (Rows scored at random
+// positions have no dense heads among the others, and pieces gain 5 to 10 %: 1504 items 380 / 420, 1600 537 / 571.)  At d = 64, where a workgroup has two thirds of the work, few items gain too, and more of them: 320 of
+// 289920 (64 heads, 547 of 115957) 1327 / 1433, 512 of 524288 1427 / 1596, 1536 of 393216 965 / 1054, 2048 of 524288 1563 / 1539 and 1170 / 1214, 2560 of 480000 901 / 942, 4032 of 516096 783 / 782, 5120 of 481280 859 / 863, 8192 of
+// 524288 616 / 600.  Turns that are all of the context see half of their tiles: 64 heads, 6000 rows (141376 seen) 337 / 363, 10000, 32 heads, 434 / 436, at d = 64 9000 417 / 447; 12000, 32 heads (283000), 497 / 490.
+// More: 3072 of 589824 1127 / 1066, 10923 of 32768 1957 / 1527.  fp32, whose kernel is the same for both: 524288.
 // ---------------------------------------------------------------------------------------------
-constexpr int64_t PIECES_TILES = 262144, PIECES_TILES_F32 = 524288, PIECES_SEEN_64 = 204800, PIECES_ITEMS_64 = 1536;
+constexpr int64_t PIECES_TILES = 262144, PIECES_TILES_MOST = 524288, PIECES_SEEN = 204800;
 // fewest tiles on either side of a cut (a part costs its result written and read: the time of two bf16 tiles; one of fp32 takes four times as long)
 __host__ __device__ __forceinline__ int cut_tiles(uint32_t base) { return base == 32 ? 2 : 1; }
 __host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : work_cols(base); }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
@@ -651,9 +650,9 @@ int prefill_split_slots(int64_t items, int grid, bool pieces) {
 }
 bool prefill_in_pieces(int BH, int64_t n, int nqb, int dtype, int d) {
     const int64_t items = (int64_t)BH * nqb, keys = (n + BN - 1) / BN, tiles = items * keys * d / 128;
-    if (dtype != 0) return tiles <= PIECES_TILES_F32;
-    if (tiles <= PIECES_TILES || d != 64) return tiles <= PIECES_TILES;
-    return items <= PIECES_ITEMS_64 ? tiles <= 2 * PIECES_TILES : items * (keys - (BM / BN) * (nqb - 1) / 2) * d / 128 <= PIECES_SEEN_64;
+    if (dtype != 0) return tiles <= PIECES_TILES_MOST;
+    const bool alike = d == 64 ? items <= 5120 : items >= 704 && items <= 2560;
+    return tiles <= (alike ? PIECES_TILES_MOST : PIECES_TILES) || items * (keys - (BM / BN) * (nqb - 1) / 2) * d / 128 <= PIECES_SEEN;
 }
 
 // Pieces, of up to `grid`, whose parts `slots` hold; 0: the queues serve the call better.  Fewer pieces than workgroups make the run about

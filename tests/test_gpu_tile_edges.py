@@ -45,7 +45,7 @@ def test_tile_loop_edges(oracle, d, n, n_hat):
         assert np.abs(l[alive] - rlse[alive]).max() <= 2e-3
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d", [(6, 16, 4, 8100, 3000, 128), (8, 16, 4, 8100, 6100, 64)])
+@pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d", [(8, 16, 4, 8100, 3000, 128), (8, 16, 4, 8100, 6100, 64)])
 def test_either_side_of_the_line(B, Hq, Hkv, n, n_hat, d):
     """One call beyond the line between pieces and queues against calls of four of its dialogues and of the rest, which lie below."""
     print(f"either side of the line B={B} n={n} n_hat={n_hat} d={d}", flush=True)

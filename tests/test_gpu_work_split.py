@@ -13,13 +13,15 @@ def _in_pieces(B, Hq, Hkv, n, n_hat, d, dtype="bf16"):
 
 # tiles of 64 keys as if every head were dense, half at d = 64; items; of a turn that is all of the context, the tiles that it sees
 @pytest.mark.parametrize("B,Hq,Hkv,n,n_hat,d,dtype,pieces", [
-    (1, 32, 8, 8192, 8192, 128, "bf16", True), (1, 32, 8, 8256, 8256, 128, "bf16", False),       # 262144 tiles
-    (1, 16, 4, 131072, 1024, 128, "bf16", True), (1, 16, 4, 131072, 1025, 128, "bf16", False), (1, 64, 8, 6000, 6000, 128, "bf16", False),
-    (1, 4, 1, 32768, 32768, 128, "f32", True), (1, 4, 1, 32832, 32832, 128, "f32", False),                                                     # 524288
-    (1, 64, 8, 115957, 547, 64, "bf16", True), (1, 32, 8, 131072, 2048, 64, "bf16", True), (1, 32, 8, 131072, 2049, 64, "bf16", False),        # few items: 524288
-    (3, 64, 8, 24576, 1024, 64, "bf16", True), (3, 64, 8, 24576, 1025, 64, "bf16", False),                                                     # 1536 items
-    (1, 64, 8, 9000, 9000, 64, "bf16", True), (1, 64, 8, 10000, 10000, 64, "bf16", True), (2, 64, 8, 8192, 8192, 64, "bf16", False),           # 204800 seen
-    (1, 64, 8, 16384, 8000, 64, "bf16", False), (1, 32, 8, 32768, 10923, 64, "bf16", False)])
+    (1, 4, 1, 131072, 4096, 128, "bf16", True), (1, 4, 1, 131072, 4097, 128, "bf16", False),                                                   # 262144 tiles, few items
+    (4, 32, 8, 4096, 4096, 128, "bf16", True), (4, 32, 8, 8192, 4096, 128, "bf16", False), (2, 64, 8, 12288, 2560, 128, "bf16", True), (2, 64, 8, 12288, 2561, 128, "bf16", False),      # many
+    (1, 11, 1, 47616, 8192, 128, "bf16", True), (1, 11, 1, 47616, 8064, 128, "bf16", False),                                                   # 704 items, 693
+    (1, 32, 8, 32768, 4096, 128, "bf16", True), (1, 32, 8, 32768, 4097, 128, "bf16", False),                                                   # 524288 tiles
+    (1, 4, 1, 32768, 32768, 128, "f32", True), (1, 4, 1, 32832, 32832, 128, "f32", False),
+    (1, 64, 8, 115957, 547, 64, "bf16", True), (1, 32, 8, 131072, 2048, 64, "bf16", True), (1, 32, 8, 131072, 2049, 64, "bf16", False),
+    (1, 64, 8, 12800, 10240, 64, "bf16", True), (1, 64, 8, 12800, 10241, 64, "bf16", False),                                                   # 5120 items
+    (1, 64, 8, 6000, 6000, 128, "bf16", True), (1, 32, 8, 10000, 10000, 128, "bf16", True), (1, 32, 8, 12000, 12000, 128, "bf16", False),      # 204800 seen
+    (2, 64, 8, 8192, 8192, 64, "bf16", False), (1, 32, 8, 32768, 10923, 64, "bf16", False)])
 def test_where_the_line_lies(B, Hq, Hkv, n, n_hat, d, dtype, pieces):
     assert _in_pieces(B, Hq, Hkv, n, n_hat, d, dtype) == pieces
 
