@@ -620,7 +620,7 @@ __device__ __forceinline__ int first_entry(int fe) {
 }
 // entry i of the wave's 64 E (i uniform).  The lane's registers are read first and the choice is among scalars: a choice among
 // the registers becomes an array in scratch memory, E stores and a load in the chain of every run.  (walk_exact_kernel, which
-// waits for that chain, 54.7 -> 49.7 us at 8192 lines; walk_kernel, whose other waves go on meanwhile, 13.2 us both at 12347.)
+// waits for that chain, a tenth less; walk_kernel, whose other waves go on meanwhile, 13.2 us both at 12347.)
 template <int E>
 __device__ __forceinline__ float pick_entry(const float (&v)[E], int i) {
     const int l = i / E;
@@ -635,7 +635,8 @@ __device__ __forceinline__ float pick_entry(const float (&v)[E], int i) {
 
 // Lane l holds the gains of the entries E l .. E l + E - 1.  x[e] = the sum behind entry e, starting from `sum` ahead of
 // lane `first`; valid in the lanes from `first` to the one returned.
-template <int E>
+// SIGNED: gains may be a little less than 0 (differences of sums that are the same but for their rounding); the sum then has to stay in the binade all the way.
+template <int E, bool SIGNED = false>
 __device__ __forceinline__ int chain_step(const float (&g)[E], int lane, int first, float sum, bool plain, float (&x)[E]) {
     const uint32_t sb = __builtin_bit_cast(uint32_t, sum), binade = sb & 0x7F800000u;
     if (plain || sb < (64u << 23) || sb > (250u << 23)) {  // (the first sum is 0, and gains may be negative in the end)
@@ -655,13 +656,23 @@ __device__ __forceinline__ int chain_step(const float (&g)[E], int lane, int fir
 #pragma unroll
     for (int e = 0; e < E; ++e) { xe = __fadd_rn(xe, g[e]); xo = __fadd_rn(xo, g[e]); least = fminf(least, g[e]); }
     const bool idle = lane < first;
-    const bool small = xo < __builtin_bit_cast(float, binade + 0x800000u) && least >= 0.f;
+    bool small = xo < __builtin_bit_cast(float, binade + 0x800000u) && least >= 0.f;
+    int32_t low = 0, high = 0;                             // how far below the start the stretch gets, and above it
+    if constexpr (SIGNED) {
+        if (__ballot(!idle && !(least >= 0.f)) != 0ull) {
+            float y = __builtin_bit_cast(float, even), lo = y, hi = y;
+#pragma unroll
+            for (int e = 0; e < E; ++e) { y = __fadd_rn(y, g[e]); lo = fminf(lo, y); hi = fmaxf(hi, y); }
+            small = hi < __builtin_bit_cast(float, binade + 0x7FFFFEu) && lo >= __builtin_bit_cast(float, binade + 2u);      // (a NaN is neither: an ordinary step)
+            low = (int32_t)(__builtin_bit_cast(uint32_t, lo) - even) - 2; high = (int32_t)(__builtin_bit_cast(uint32_t, hi) - even) + 2;      // (from an odd start a step more at most)
+        }
+    }
     ChainInc inc = {0, 0};
     if (small && !idle) inc = {(int32_t)(__builtin_bit_cast(uint32_t, xe) - even), (int32_t)(__builtin_bit_cast(uint32_t, xo) - (even + 1u))};
     const ChainInc before = chain_before(inc);
     const int32_t m0 = (int32_t)(sb & 0x7FFFFFu);
     const int32_t m = m0 + ((m0 & 1) ? before.o : before.e);               // less 2^23
-    const uint64_t leave = __ballot(!idle && (!small || m + ((m & 1) ? inc.o : inc.e) >= 1 << 23));
+    const uint64_t leave = __ballot(!idle && (!small || m + ((m & 1) ? inc.o : inc.e) >= 1 << 23 || (SIGNED && (m + low < 0 || m + high >= 1 << 23))));
     x[0] = __fadd_rn(__builtin_bit_cast(float, binade | ((uint32_t)m & 0x7FFFFFu)), g[0]);
 #pragma unroll
     for (int e = 1; e < E; ++e) x[e] = __fadd_rn(x[e - 1], g[e]);
@@ -669,14 +680,14 @@ __device__ __forceinline__ int chain_step(const float (&g)[E], int lane, int fir
 }
 // Adds entries 0 .. `limit` - 1 (the gains are 0 from there on) to `sum`, which is below `target`, in order until it
 // reaches the target or they are used up; returns how many were added.
-template <int E>
+template <int E, bool SIGNED = false>
 __device__ __forceinline__ int chain_until(const float (&g)[E], int lane, int limit, float target, float& sum) {
     if (limit == 0) return 0;
     int first = 0;
     bool plain = false;
     for (;;) {
         float x[E];
-        const int last = chain_step<E>(g, lane, first, sum, plain, x);
+        const int last = chain_step<E, SIGNED>(g, lane, first, sum, plain, x);
         int fe = E;
 #pragma unroll
         for (int e = E - 1; e >= 0; --e) fe = x[e] < target ? fe : e;
@@ -717,13 +728,29 @@ __device__ __forceinline__ float chain_prefix(const float (&g)[E], int lane, flo
     if (E * lane < again_end) put(again);
     return sum;
 }
+// The same for up to CHAIN_FEW entries, an entry a lane, one after the other: 400 cycles, a step of the scan 900
+constexpr int CHAIN_FEW = 16;
+__device__ __forceinline__ int chain_few(float g, int lane, int limit, float target, float& sum) {
+    if (limit == 0) return 0;
+    float x = 0.f;
+#pragma unroll
+    for (int p = 0; p < CHAIN_FEW; ++p) {                   // pass p settles lane p
+        float left = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), 0x138 /* wave_shr:1 */, 0xF, 0xF, true));
+        left = lane == 0 ? sum : left;
+        x = __fadd_rn(left, g);
+    }
+    const uint64_t reached = __ballot(lane < limit && !(x < target));
+    const int last = reached != 0ull ? __ffsll((unsigned long long)reached) - 1 : limit - 1;
+    sum = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), last));
+    return last + 1;
+}
 // the same with the gains in LDS (64 E floats, 16-byte aligned)
 template <int E>
 __device__ __forceinline__ int chain_lds(const float* gains, int lane, int limit, float target, float& sum) {
     float g[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) { g[e] = gains[E * lane + e]; g[e] = E * lane + e < limit ? g[e] : 0.f; }
-    return chain_until<E>(g, lane, limit, target, sum);
+    return chain_until<E, true>(g, lane, limit, target, sum);
 }
 
 // ---- the greedy loop ----------------------------------------------------------------------------
@@ -1247,20 +1274,20 @@ static_assert(2 * sizeof(WalkList<4>) > EMIT_LINES / 4 + 4 * EMIT_LINES, "the bi
 //     overlap(column b) = sum over scored rows t with o = p_t - b >= 0 and o taken      of A[t][b]
 // Everything else is the loop of walk_kernel (binary32, single roundings, cross-multiplied test).
 //
-// One workgroup per head.  The loop takes long runs from one list (a few per walk, of hundreds to thousands of picks),
+// One workgroup per head.  The loop takes runs from one list (up to a few dozen a walk, of one to thousands of picks),
 // and during a run the other list's head and taken set stand still.  So a round looks at many candidates of one
 // list at once: 64 when the list has just changed, then up to 1024, one per thread.  It needs
-//   - what the other list's taken set covers of each candidate: a bitmap says which of its W cells count, and only
-//     those are read (they miss the L2, a microsecond each: sixteen threads share the rows of one of 64
-//     candidates, so that one load per thread and 64 rows is all; with more candidates a thread reads its own
-//     line's cells eight at a time, and keeps the sum while the other list stands still);
-//   - what of the other head is covered at each candidate: its W cells, each with the candidate that takes the line
-//     it lies on;
-//   - the first candidate that fails the test, and the gains before it added in order by one wave.
-// What bounds it is the latency of a round, 4 to 6 us (dependent loads, five barriers, one wave's chain), so the
-// head with most runs.  Taken pick by pick it was 0.37 us a pick: 8192 lines, 32 heads, up to 3074 picks or 14
-// runs a head, 1160 us; then 66, and with no registers in scratch memory (pick_entry) a tenth less: 54.7 -> 49.7 on another
-// input of that size.  All candidates brought up to date after every run, with bitmaps of the lines taken since: 72 to 75 us.
+//   - what the other list's taken set covers of each candidate: a bitmap says which of its W cells count;
+//   - what of the other head is covered at each candidate: of its W cells those whose line is taken already, and those that earlier
+//     candidates lie on: a running sum over the candidates;
+//   - the first candidate that fails the test, and the gains before it added in order.
+// What bounds it is the latency of a round, so the head with most rounds (a dozen at 8192 lines): cells that miss the L2 take 2000 cycles, a step of a wave by itself five
+// cycles an instruction.  So a round of 64 candidates has two steps: four waves read what is covered of the candidates, a quarter of the rows each, a fifth what is covered of the other head, a
+// sixth what the candidates cover of it; then one wave does all the rest.  Cycles of such a round, 8192 lines: 5000 to 5500, of 1024 candidates 10000 and as many more as
+// cells take that are covered.  With one candidate in sixteen threads, the other head's cells added one after the other, and five barriers 7000 (13000 where the head crosses many candidates); the
+// cells of a list's next candidates fetched a turn ahead 6400 to 10000 (as many more of them are fetched as a CU has lines in flight).  The whole ls_select_exact, us, so / now: 32 heads, 8192
+// lines, six inputs, 60.9 / 47.2, 73.7 / 55.0, 67.4 / 50.4, 77.9 / 58.8, 73.9 / 54.2, 117.0 / 85.7; 32 heads, 1101 lines 53.7 / 36.8, 16 heads, 715 57.8 / 31.5, 4 heads, 3393 94.8 / 55.9.
+// Taken pick by pick it was 0.37 us a pick: up to 3074 picks or 14 runs a head 1160 us.
 
 // Sum of a double over the 64 lanes, the same value in every lane.  Data-parallel-primitive moves on the two
 // halves of the value instead of cross-lane reads through LDS: a shuffle of a double is two LDS round trips, six
@@ -1285,22 +1312,39 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
 }
 
 
+// of the lanes to the left
+__device__ __forceinline__ double lanes_before_f64(double x, double& all) {
+    x += dpp_f64<0x111, 0xF>(x);                           // row_shr:1, 2, 4, 8
+    x += dpp_f64<0x112, 0xF>(x);
+    x += dpp_f64<0x114, 0xF>(x);
+    x += dpp_f64<0x118, 0xF>(x);
+    x += dpp_f64<0x142, 0xA>(x);                           // row_bcast15 into rows 1 and 3
+    x += dpp_f64<0x143, 0xC>(x);                           // row_bcast31 into rows 2 and 3
+    const uint64_t u = __builtin_bit_cast(uint64_t, x);
+    all = __builtin_bit_cast(double, (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 63) << 32 | (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 63));
+    return dpp_f64<0x138, 0xF>(x);                         // wave_shr:1
+}
+
 constexpr int XW_THREADS = 1024;
 constexpr int XW_ROWS = 256;                   // longest window
 constexpr int XW_FEW = 64;                     // candidates of the first round of a run
-static_assert(16 * XW_FEW == XW_THREADS, "sixteen threads a candidate");
 constexpr int XW_AGAIN = 768;                  // entries of a block of the sorted list behind the head before the next one is loaded
+static_assert(XW_FEW == 64 && XW_AGAIN + XW_FEW <= XW_THREADS, "a lane each; the next candidates lie in the block");
 
 // grid (BH).  Dynamic LDS: two bitmaps of n bits.
 __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
     extern __shared__ uint32_t xw_maps[];
     __shared__ __align__(16) float gains[XW_THREADS];
-    __shared__ float cell[XW_ROWS];            // cells of the other head's line
-    __shared__ int32_t when[XW_ROWS];          // candidate whose line each lies on: -1 taken already, XW_NEVER none of this round
+    __shared__ int32_t lines[2][XW_THREADS];   // the block of each sorted list that its head is in
+    __shared__ float weights[2][XW_THREADS];
     __shared__ int32_t pos[XW_ROWS];           // positions of the scored rows
-    __shared__ int32_t lines[XW_FEW];          // of the candidates
-    __shared__ int32_t head_line, run_end, taken_now;
-    __shared__ float head_weight, sum_now;
+    __shared__ double parts[4][XW_FEW];        // few candidates: a quarter of what is covered of each
+    __shared__ double before[XW_FEW];          // ... what the candidates before it cover of the other head
+    __shared__ double crossed[XW_THREADS / 64];            // many: what each wave's cover of it
+    __shared__ double head_part;               // what the lines taken cover of it
+    __shared__ int32_t leaves;
+    struct Round { int32_t end, taken; float sum; };
+    __shared__ Round done[2];                  // (in turn: a wave may come to the next round's while another has yet to read this)
     constexpr int32_t XW_NEVER = 0x7FFFFFFF;
     const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1315,173 +1359,196 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
     const float target = a.alpha * a.total[bh], nh = (float)a.n_hat;
     const float* A = a.a_win + (int64_t)bh * W * a.n;
     auto length = [&](int line) { const float rest = (float)(n - line); return rest < nh ? rest : nh; };
+    auto is_taken = [](const uint32_t* map, int line) -> bool { return line >= 0 && ((map[line >> 5] >> (line & 31)) & 1u); };
 
-    // Of a list: its lines taken, and the thread's entry of the block of the sorted list loaded last: line, weight, and
-    // (valid) what the other list's lines taken so far cover of it.
-    // (`valid` is an int: the padding behind a bool would be swapped through scratch memory)
-    struct List { int id, taken, base, valid; int32_t line; float weight, covered; };
+    // Of a list: its lines taken, and the place in its order of the first line of the block in `lines`.
+    struct List { int id, taken, base; };
     auto load = [&](List& l) {
         l.base = l.taken;
         const int i = l.base + tid < n ? l.base + tid : n - 1;
-        l.line = a.sidx[((int64_t)l.id * a.BH + bh) * a.n + i];
-        l.weight = ((l.id == 0 ? a.slash : a.vert) + (int64_t)bh * a.n)[l.line];
-        l.covered = 0.f;
-        l.valid = 0;
+        const int32_t x = a.sidx[((int64_t)l.id * a.BH + bh) * a.n + i];
+        lines[l.id][tid] = x;
+        weights[l.id][tid] = l.base == 0 ? a.head_w[((int64_t)l.id * a.BH + bh) * WALK_BLK + (tid < n ? tid : n - 1)] : ((l.id == 0 ? a.slash : a.vert) + (int64_t)bh * a.n)[x];
     };
-    List X, O;                                 // the list whose lines are the candidates, and the other one
-    X.id = X.taken = 0; O.id = 1; O.taken = 0;
+    static_assert(WALK_BLK == XW_THREADS, "the first block's weights are there in order");
+    List X = {0, 0, 0}, O = {1, 0, 0};         // the list whose lines are the candidates, and the other one
     load(X);
     load(O);
+    __syncthreads();
     float sum = 0.f;
-    int head_of = -1, head_at = -1;            // list and sorted position whose cells `cell` holds
-    int most = XW_FEW;                         // candidates of the next round
+    int most = XW_FEW, round = 0;              // candidates of the next round
     bool decided = false;                      // its first candidate is known to be the next pick
     while (sum < target && (X.taken < n || O.taken < n)) {
         bool change = false;                   // to the other list
         if (X.taken == n) change = decided = true;
         else {
-            uint32_t * const map_x = X.id == 0 ? map_s : map_v;
+            uint32_t* const map_x = X.id == 0 ? map_s : map_v;
             const uint32_t* const map_o = X.id == 0 ? map_v : map_s;
             const bool has_o = O.taken < n, few = most == XW_FEW;
-            const int off = X.taken - X.base;  // the head's entry
-            const int C = XW_THREADS - off < most ? XW_THREADS - off : most;
-            const int j = tid - off;           // this thread's candidate
-            const bool cand = j >= 0 && j < C && X.base + tid < n;
-            const int j0 = 64 * wv - off;      // first candidate of this wave
-            const bool busy = j0 + 63 >= 0 && j0 < C;
-            const int32_t x = X.line;
-            if (has_o && tid == O.taken - O.base) { head_line = O.line; head_weight = O.weight; }
-            if (few && j >= 0 && j < C) lines[j] = x;
-            if (tid == 0) run_end = XW_NEVER;
-            __syncthreads();
-            const int32_t o = head_line;
-            // (the loads of this part are issued together: each takes a microsecond when it misses the L2)
-            float head_cell = 0.f;
-            bool head_moved = false;
-            if (has_o && tid < W) {
-                const int other = pos[tid] - o;            // the line of list X through this cell of the head
-                head_moved = head_of != O.id || head_at != O.taken;
-                if (head_moved) head_cell = A[other >= 0 ? (int64_t)tid * a.n + (O.id == 0 ? other : o) : 0];
-                head_cell = other >= 0 ? head_cell : 0.f;
-                when[tid] = other >= 0 && ((map_x[other >> 5] >> (other & 31)) & 1u) ? -1 : XW_NEVER;
-            }
-            head_of = O.id; head_at = O.taken;
-            if (few && O.taken > 0) {          // sixteen threads a candidate, every sixteenth row each
-                const int c = tid >> 4, x16 = lines[c];
-                double part = 0.0;
-                for (int t0 = 0; t0 < W; t0 += 64) {
-                    float v[4];
-                    bool on[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int t = t0 + 16 * u + (tid & 15);
-                        const int other = c < C && t < W ? pos[t] - x16 : -1;
-                        on[u] = other >= 0 && ((map_o[other >> 5] >> (other & 31)) & 1u);
-                        v[u] = A[on[u] ? (int64_t)t * a.n + (X.id == 0 ? other : x16) : 0];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) part += on[u] ? (double)v[u] : 0.0;
-                }
-                part += dpp_f64<0xB1, 0xF>(part);          // over sixteen lanes, as in wave_sum_f64
-                part += dpp_f64<0x4E, 0xF>(part);
-                part += dpp_f64<0x141, 0xF>(part);
-                part += dpp_f64<0x140, 0xF>(part);
-                if ((tid & 15) == 0) gains[c] = (float)part;
-            } else if (!few && busy && !X.valid && O.taken > 0) {          // a thread a candidate
-                double part = 0.0;
+            const int off = X.taken - X.base;  // the first candidate's place in the block: at most XW_AGAIN
+            int C = XW_THREADS - off < most ? XW_THREADS - off : most;
+            C = n - X.taken < C ? n - X.taken : C;
+            const int j = few ? lane : tid;    // this thread's candidate
+            const bool cand = j < C;
+            const int32_t x = lines[X.id][off + (cand ? j : 0)], o = has_o ? lines[O.id][O.taken - O.base] : 0;
+            const float weight = weights[X.id][off + (cand ? j : 0)], head_weight = has_o ? weights[O.id][O.taken - O.base] : 0.f;
+            // the rows from t0 on, up to 64, whose cell of line x lies on a taken line of the other list
+            auto rows_taken = [&](int t0) -> uint64_t {
                 auto word = [&](int wi) { return wi >= 0 && wi < words ? map_o[wi] : 0u; };
-                for (int t0 = 0; t0 < W; t0 += 64) {
-                    uint64_t on = 0ull;
-                    if (window) {
-                        const int b = n - W + t0 - x, wi = b >> 5, sh = b & 31;
-                        const uint64_t lo = ((uint64_t)word(wi + 1) << 32) | word(wi), hi = word(wi + 2);
-                        on = lo >> sh | (sh ? hi << (64 - sh) : 0ull);
-                        if (W - t0 < 64) on &= (1ull << (W - t0)) - 1ull;
-                    } else {
-                        for (int t = 0; t < 64 && t0 + t < W; ++t) {
-                            const int c = pos[t0 + t] - x;
-                            if (c >= 0) on |= (uint64_t)((word(c >> 5) >> (c & 31)) & 1u) << t;
-                        }
-                    }
-                    while (on) {               // eight cells in flight
-                        float v[8];
-                        uint64_t left = on;
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const int t = t0 + (left ? __ffsll((unsigned long long)left) - 1 : 0);
-                            v[u] = A[left ? (int64_t)t * a.n + (X.id == 0 ? pos[t] - x : x) : 0];
-                            left &= left - 1ull;
-                        }
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) { part += on ? (double)v[u] : 0.0; on &= on - 1ull; }
-                    }
+                uint64_t on = 0ull;
+                if (window) {
+                    const int b = n - W + t0 - x, wi = b >> 5, sh = b & 31;
+                    const uint64_t lo = ((uint64_t)word(wi + 1) << 32) | word(wi), hi = word(wi + 2);
+                    on = lo >> sh | (sh ? hi << (64 - sh) : 0ull);
+                    if (W - t0 < 64) on &= (1ull << (W - t0)) - 1ull;
+                } else {
+                    for (int t = 0; t < 64 && t0 + t < W; ++t) on |= (uint64_t)(is_taken(map_o, pos[t0 + t] - x) ? 1u : 0u) << t;
                 }
-                X.covered = (float)part;
-                X.valid = 1;
-            }
-            if (head_moved) cell[tid] = head_cell;
-            __syncthreads();
-            const float covered = O.taken == 0 ? 0.f : few ? gains[j >= 0 && j < XW_FEW ? j : 0] : X.covered;
-            const float gain = cand ? __fsub_rn(X.weight, covered) : 0.f;
-            if (has_o && cand) {               // does the candidate's line cross the other head's inside the window?
+                return on;
+            };
+            // of line x in row t, and (window) from where on the rows' lie how far apart
+            const uint32_t step = (uint32_t)n + (X.id == 0 ? 1u : 0u), row0 = (uint32_t)(X.id == 0 ? n - W - x : x);
+            auto row_cell = [&](int t) -> uint32_t { return window ? row0 + (uint32_t)t * step : (uint32_t)t * (uint32_t)n + (uint32_t)(X.id == 0 ? pos[t] - x : x); };
+            auto head_cell = [&](int t) { return (int64_t)t * a.n + (O.id == 0 ? pos[t] - o : o); };       // of the other head
+            // what of the other head is covered already, by one wave
+            auto head_taken = [&]() {
+                double part = 0.0;
+                bool any = false;
+                for (int t = lane; t < W; t += 64) {
+                    const bool in = is_taken(map_x, pos[t] - o);
+                    any |= in;
+                    const float v = A[in ? head_cell(t) : 0];
+                    part += in ? (double)v : 0.0;
+                }
+                part = __ballot(any) == 0ull ? 0.0 : wave_sum_f64(part);
+                if (lane == 0) head_part = part;
+            };
+            // what line x covers of it: the cell where they cross, if a scored row has one
+            auto crossing = [&]() -> double {
                 if (window) {
                     const int t = x + o - (n - W);
-                    if (t >= 0 && t < W) when[t] = j;
-                } else {
-                    for (int t = 0; t < W; ++t) if (pos[t] == x + o) when[t] = j;
+                    const bool in = cand && t >= 0 && t < W;
+                    const float v = A[in ? head_cell(t) : 0];
+                    return in ? (double)v : 0.0;
                 }
-            }
-            __syncthreads();
-            if (busy) {
-                bool stays = cand;
-                if (has_o) {
-                    // what of the other head is covered when the walk gets to this wave's candidates, and to each of them
-                    double part = 0.0;
-                    bool any = false;
-                    for (int t = lane; t < W; t += 64) {
-                        const int wh = when[t];
-                        const bool in = wh < j0 || wh == -1;
-                        any |= in;
-                        part += in ? (double)cell[t] : 0.0;
-                    }
-                    double head_covered = __ballot(any) == 0ull ? 0.0 : wave_sum_f64(part);
-                    for (int t0 = 0; t0 < W; t0 += 64) {
-                        const int wh = t0 + lane < W ? when[t0 + lane] : XW_NEVER;
-                        uint64_t mine = __ballot(wh >= 0 && wh >= j0 && wh < j0 + 64);
-                        while (mine) {
-                            const int t = __ffsll((unsigned long long)mine) - 1;
-                            mine &= mine - 1ull;
-                            head_covered += __builtin_amdgcn_readlane(wh, t) < j ? (double)cell[t0 + t] : 0.0;
+                double c = 0.0;
+                for (int t = 0; t < W; ++t) if (cand && pos[t] == x + o) c += (double)A[head_cell(t)];
+                return c;
+            };
+            // candidate j is taken before the other head
+            auto stays_at = [&](float gain, double head_covered) -> bool {
+                const float other_gain = __fsub_rn(head_weight, (float)head_covered);
+                float cx = __fsub_rn(length(x), (float)O.taken); if (cx < 1.0f) cx = 1.0f;
+                float co = __fsub_rn(length(o), (float)(X.taken + j)); if (co < 1.0f) co = 1.0f;
+                const float mine = __fmul_rn(gain, co), other = __fmul_rn(other_gain, cx);
+                return (X.id == 0 ? mine >= other : !(other >= mine)) || (j == 0 && decided);
+            };
+            if (few) {
+                if (wv < 4) {                  // a quarter of the rows each
+                    double p0 = 0.0, p1 = 0.0;
+                    for (int t0 = 0; O.taken > 0 && t0 < W; t0 += 64) {
+                        const uint32_t on = cand ? (uint32_t)(rows_taken(t0) >> (16 * wv)) & 0xFFFFu : 0u;
+                        if (__ballot(on != 0u) == 0ull) continue;
+                        float v[16];
+                        if (window) {          // (a row's cells from W before its first on: where there is none to be read, the one W behind that)
+                            const uint32_t at = (row0 + (uint32_t)W) * 4u, none = (uint32_t)W * 4u;
+#pragma unroll
+                            for (int u = 0; u < 16; ++u) {
+                                const int t = t0 + 16 * wv + u < W ? t0 + 16 * wv + u : W - 1;
+                                const unsigned char* row = reinterpret_cast<const unsigned char*>(A + (int64_t)t * step - W);
+                                v[u] = *reinterpret_cast<const float*>(row + (on >> u & 1u ? at : none));
+                            }
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < 16; ++u) v[u] = A[on >> u & 1u ? row_cell(t0 + 16 * wv + u) : 0u];
+                        }
+#pragma unroll
+                        for (int u = 0; u < 16; ++u) {
+                            const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe((int)on, u, 1);
+                            (u & 1 ? p1 : p0) += (double)__builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v[u]) & keep);
                         }
                     }
-                    const float other_gain = __fsub_rn(head_weight, (float)head_covered);
-                    float cx = __fsub_rn(length(x), (float)O.taken); if (cx < 1.0f) cx = 1.0f;
-                    float co = __fsub_rn(length(o), (float)(X.taken + j)); if (co < 1.0f) co = 1.0f;
-                    const float mine = __fmul_rn(gain, co), other = __fmul_rn(other_gain, cx);
-                    stays = cand && ((X.id == 0 ? mine >= other : !(other >= mine)) || (j == 0 && decided));
+                    parts[wv][lane] = p0 + p1;
+                } else if (wv == 4) {
+                    if (has_o) head_taken();
+                } else if (wv == 5) {
+                    double c = has_o ? crossing() : 0.0, all;
+                    if (__ballot(c != 0.0) != 0ull) c = lanes_before_f64(c, all);
+                    before[lane] = c;
                 }
-                const uint64_t leave = __ballot(j >= 0 && j < C && !stays);
-                if (leave != 0ull && lane == 0) atomicMin(&run_end, j0 + __ffsll((unsigned long long)leave) - 1);
-                if (j >= 0 && j < C) gains[j] = gain;
+                __syncthreads();
+                if (wv == 0) {
+                    const float covered = (float)((parts[0][lane] + parts[1][lane]) + (parts[2][lane] + parts[3][lane]));
+                    const float gain = cand ? __fsub_rn(weight, covered) : 0.f;
+                    const bool stays = cand && (!has_o || stays_at(gain, head_part + before[lane]));
+                    const uint64_t leave = __ballot(cand && !stays);
+                    const int end = leave != 0ull ? __ffsll((unsigned long long)leave) - 1 : XW_NEVER, run = end < C ? end : C;
+                    float s = sum;
+                    const float g[1] = {lane < run ? gain : 0.f};
+                    const int got = run <= CHAIN_FEW ? chain_few(g[0], lane, run, target, s) : chain_until<1, true>(g, lane, run, target, s);
+                    if (lane < got) atomicOr(&map_x[x >> 5], 1u << (x & 31));
+                    if (lane == 0) done[round & 1] = Round{end, got, s};
+                }
+            } else {
+                const bool busy = 64 * wv < C;
+                double part = 0.0, c = 0.0;
+                if (tid == 0) leaves = XW_NEVER;
+                if (has_o && busy) c = crossing();
+                if (O.taken > 0 && cand)
+                    for (int t0 = 0; t0 < W; t0 += 64) {
+                        uint64_t on = rows_taken(t0);
+                        while (on) {           // eight cells in flight
+                            float v[8];
+                            uint64_t left = on;
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) {
+                                v[u] = A[left ? row_cell(t0 + __ffsll((unsigned long long)left) - 1) : 0];
+                                left &= left - 1ull;
+                            }
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) { part += on ? (double)v[u] : 0.0; on &= on - 1ull; }
+                        }
+                    }
+                if (has_o && wv == 0) head_taken();
+                const float gain = cand ? __fsub_rn(weight, (float)part) : 0.f;
+                double all = 0.0;
+                if (__ballot(c != 0.0) != 0ull) c = lanes_before_f64(c, all);
+                if (lane == 0) crossed[wv] = all;
+                if (busy) gains[tid] = gain;
+                __syncthreads();
+                if (busy) {
+                    bool stays = cand;
+                    if (has_o) {
+                        double waves = head_part;
+                        for (int w = 0; w < wv; ++w) waves += crossed[w];
+                        stays = cand && stays_at(gain, waves + c);
+                    }
+                    const uint64_t leave = __ballot(cand && !stays);
+                    if (leave != 0ull && lane == 0) atomicMin(&leaves, 64 * wv + __ffsll((unsigned long long)leave) - 1);
+                }
+                __syncthreads();
+                if (wv == 0) {
+                    const int end = leaves, run = end < C ? end : C;
+                    float s = sum;
+                    const int got = run <= 64 ? chain_lds<1>(gains, lane, run, target, s) : chain_lds<16>(gains, lane, run, target, s);
+                    for (int i = lane; i < got; i += 64) { const int32_t y = lines[X.id][off + i]; atomicOr(&map_x[y >> 5], 1u << (y & 31)); }
+                    if (lane == 0) done[round & 1] = Round{end, got, s};
+                }
             }
             __syncthreads();
-            const int end = run_end, run = end < C ? end : C;
-            if (wv == 0) {
-                float s = sum;
-                const int got = run <= 64 ? chain_lds<1>(gains, lane, run, target, s) : chain_lds<16>(gains, lane, run, target, s);
-                if (lane == 0) { taken_now = got; sum_now = s; }
+            const Round r = done[round & 1];
+            const int run = r.end < C ? r.end : C;
+            sum = r.sum;
+            ++round;
+            X.taken += r.taken;
+            if (r.taken == run && X.taken < n && X.taken - X.base > XW_AGAIN) {
+                load(X);
+                __syncthreads();
             }
-            __syncthreads();
-            const int got = taken_now;
-            sum = sum_now;
-            if (j >= 0 && j < got) atomicOr(&map_x[x >> 5], 1u << (x & 31));
-            X.taken += got;
-            if (got > 0) O.valid = 0;
-            if (got == run && X.taken < n && X.taken - X.base > XW_AGAIN) load(X);
-            change = decided = end < C;        // then the first pick of the other list has been decided
+            change = decided = r.end < C;      // then the first pick of the other list has been decided
             most = XW_THREADS;
         }
-        if (change) { List t = X; X = O; O = t; most = XW_FEW; }
+        if (change) { const List t = X; X = O; O = t; most = XW_FEW; }
     }
     const int cnt_s = X.id == 0 ? X.taken : O.taken, cnt_v = X.id == 0 ? O.taken : X.taken;
     if (tid == 0) {
