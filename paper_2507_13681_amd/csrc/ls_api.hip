@@ -169,12 +169,21 @@ size_t ws_score(const ls_shape* s, bool lines) {
     }
     return b;
 }
-// (The selection itself takes 8 bytes per head and line beside its heads' first lines.  The 24 that a shape is stated to need are what
-// contexts have had from the start, and what the parts of attention items and the bands of the window matrix then find free in
-// a context sized for another turn: stating less would give such a program a smaller workspace than it has now.)
+// The order of a list, and with it each line's weight and maximum.  (Calls get by with those of the first lines, as contexts made for less may have
+// room for no more.)
 size_t ws_select(const ls_shape* s) {
     const size_t BH = (size_t)s->B * s->Hq;
     return 3 * up(2 * BH * (size_t)s->n * 4) + 2 * up(2 * BH * ls::SELECT_HEAD_LINES * 4);
+}
+void order_scratch(ls::SelectArgs& a, Bump& bp) {
+    const size_t lists = 2 * (size_t)a.BH, info = lists * ls::SELECT_RANGES;
+    a.sidx = bp.take<int32_t>(lists * (size_t)a.n);
+    const size_t more = 2 * up(info * 4) + up(2 * (size_t)a.BH * 4) + up(ls::SELECT_HEAD_LINES * 4);       // (the walk reads whole blocks of lines)
+    const int64_t whole = a.n > ls::SELECT_HEAD_LINES ? a.n : ls::SELECT_HEAD_LINES;
+    a.sorted = bp.ok() && bp.cap - bp.off >= 2 * up(lists * (size_t)whole * 4) + more;
+    a.kept = a.sorted ? whole : ls::SELECT_HEAD_LINES;
+    a.sorted_w = bp.take<float>(lists * (size_t)a.kept); a.sorted_m = bp.take<float>(lists * (size_t)a.kept);
+    if (a.sorted) { a.odd = bp.take<int32_t>(info); a.info = bp.take<int32_t>(info); a.open = bp.take<int32_t>(2 * (size_t)a.BH); }
 }
 inline int words_of(int64_t n) { return (int)((n + 31) / 32) + 8; }
 inline int tab_len_of(int64_t n) { return (int)(n / 64) + 4; }
@@ -316,9 +325,8 @@ int ls_select_exact(ls_ctx* c, const ls_shape* s, float alpha, const float* a_wi
     a.n = s->n; a.n_hat = s->n_hat; a.BH = s->B * s->Hq; a.alpha = alpha;
     a.vert = vert; a.slash = slash; a.vmax = vert; a.smax = slash; a.total = total;   // the maxima are not used: any readable array
     Bump bp{c->ws, c->ws_bytes, 0};
-    const size_t cnt = 2 * (size_t)a.BH * (size_t)a.n;
-    a.sidx = bp.take<int32_t>(cnt);
-    a.head_w = bp.take<float>(2 * (size_t)a.BH * ls::SELECT_HEAD_LINES); a.head_m = bp.take<float>(2 * (size_t)a.BH * ls::SELECT_HEAD_LINES);
+    order_scratch(a, bp);
+    a.sorted_m = nullptr; a.odd = nullptr; a.open = nullptr;
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_select_exact: workspace of %zu bytes is too small", c->ws_bytes);
     a.v_idx = v_idx; a.v_cnt = v_cnt; a.s_idx = s_idx; a.s_cnt = s_cnt; a.cap_v = cap_v; a.cap_s = cap_s;
     a.accounted = accounted; a.status = c->status; a.spin_limit = c->walk_spin_limit;
@@ -343,9 +351,7 @@ int ls_select(ls_ctx* c, const ls_shape* s, float alpha,
     a.n = s->n; a.n_hat = s->n_hat; a.BH = s->B * s->Hq; a.alpha = alpha;
     a.vert = vert; a.slash = slash; a.vmax = vmax; a.smax = smax; a.total = total;
     Bump bp{c->ws, c->ws_bytes, 0};
-    const size_t cnt = 2 * (size_t)a.BH * (size_t)a.n;
-    a.sidx = bp.take<int32_t>(cnt);
-    a.head_w = bp.take<float>(2 * (size_t)a.BH * ls::SELECT_HEAD_LINES); a.head_m = bp.take<float>(2 * (size_t)a.BH * ls::SELECT_HEAD_LINES);
+    order_scratch(a, bp);
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_select: workspace of %zu bytes is too small", c->ws_bytes);
     a.v_idx = v_idx; a.v_cnt = v_cnt; a.s_idx = s_idx; a.s_cnt = s_cnt; a.cap_v = cap_v; a.cap_s = cap_s;
     a.accounted = accounted; a.status = c->status; a.spin_limit = c->walk_spin_limit;

@@ -49,7 +49,8 @@ struct ScoreRoute {
 };
 ScoreRoute score_route(ScoreArgs& a, bool bf16, int d, int mode);
 
-constexpr int SELECT_HEAD_LINES = 1024;   // lines at the front of each sorted list whose weight and maximum are stored in order
+constexpr int SELECT_RANGES = 128;         // most ranges that a list is put in order by
+constexpr int SELECT_HEAD_LINES = 1024;   // lines at the front of each sorted list whose weight and maximum are stored in order at least
 
 // (The order decides which of its pointers walk_exact_kernel keeps in vector registers; with `w` last and `spin_limit` between the
 // pointers it takes 73.9 instead of 69.6 us for 16 heads of 907 lines, 51.2 instead of 49.7 for 32 of 8192.)
@@ -61,7 +62,13 @@ struct SelectArgs {
     int w;                    // rows of a_win
     const float *vert, *slash, *vmax, *smax, *total;
     int32_t* sidx;            // [2][BH][n] line indices in sorted order
-    float *head_w, *head_m;   // [2][BH][SELECT_HEAD_LINES] weight and largest entry of the first lines of each sorted list
+    int64_t kept;             // of each sorted list, the first lines whose weight and largest entry are there in order: n, or SELECT_HEAD_LINES
+    float *sorted_w, *sorted_m;            // [2][BH][kept] (sorted_m: null where nobody wants it)
+    int32_t* odd;             // [2][BH][SELECT_RANGES] whether a part of the list has a largest entry that is negative or no number; null: nobody has looked
+    int32_t* info;            // [2][BH][SELECT_RANGES] with `open`, of a range of the list: 0: in order, -1 - k: not, and k of the lines before it are
+    int32_t* open;            // [BH] the walk came to the end of what is in order, [BH] workgroups that have put their share of the rest in order; null: all of it is
+    int ranges;               // of a list
+    bool sorted;              // kept == n, and a block of lines may be read past the lists' ends
     int32_t *v_idx, *v_cnt, *s_idx, *s_cnt;
     int cap_v, cap_s;
     float* accounted;         // may be null

@@ -2,14 +2,16 @@
 //
 //   order_kernel  Desc_Sort: the n line weights of a list in descending order, equal weights in ascending index order.
 //                 The weights' range is cut into ranges of about as many lines each, a workgroup per range: it picks its
-//                 lines out of the list and ranks them inside LDS, so nothing is left to merge.
+//                 lines out of the list and ranks them inside LDS, so nothing is left to merge.  The last ranges of long lists
+//                 are left out where the ones before them outweigh what a walk can take.
 //   walk_kernel   one workgroup of six waves per head: the greedy loop of Alg. 2 in binary32 with the operands
 //                 and operation order of the definition.  One wave decides runs of up to 1024 picks from one
 //                 list with its lanes, one accumulates the running sum pick by pick behind it and finds
 //                 the pick that reaches the target, and two waves per list stage the sorted list and its
 //                 overlap prefix sums in LDS ahead of both.
 //   emit_kernel   one workgroup per (head, list): the chosen prefix of a sorted list becomes an
-//                 ascending index list (bitmap in LDS + prefix popcount).
+//                 ascending index list (bitmap in LDS + prefix popcount); a walk that came to the end of what is in order is
+//                 done again here.
 //   topb_*        Alg. 3: the `budget` largest scores per KV head, ties broken towards smaller indices, ascending output.
 //                 Up to TB_ONE_LEN scores one workgroup a head narrows the threshold by bins of equal span; beyond, a radix
 //                 select on the float bit patterns is spread over many, one launch per step.
@@ -40,6 +42,8 @@ constexpr int ORDER_CHUNKS = 10;               // most lines of a workgroup, in 
 constexpr int ORDER_ONE = 4096;                // longest list that one workgroup puts in order
 constexpr int ORDER_SAMPLES = 2048;            // of a list, for the bounds of its ranges
 constexpr int ORDER_WIDE = 65536;              // lists beyond: shorter ranges, with more room
+constexpr float ORDER_GOAL = 1.f + 1.f / 512;  // of the target: what lines before a range have to have of it for the range to be left out (its sums round otherwise than the walk's)
+constexpr int LAZY_LINES = 8193;               // shorter lists are put in order throughout: 32 heads of 8192 lines 17.3 us, lazily 17.4
 constexpr int ORDER_FULL = 32;                 // lines of the fullest bin that are still ranked against each other
 constexpr int order_fine(int pt) { return pt * 2 * ORDER_THREADS; }        // fine bins, where a thread has `pt` words of them
 constexpr size_t order_lds_bytes(int pt, int cap) { return (size_t)order_fine(pt) * 2 + 16 + 1024 * 4 + (size_t)cap * 12; }
@@ -59,7 +63,7 @@ __device__ __forceinline__ uint32_t lanes_max(uint32_t x) { return ~lanes_min(~x
 __device__ __forceinline__ int width_of(uint32_t x) { return x == 0u ? 0 : 32 - __builtin_clz(x); }
 
 // What the workgroup keeps beside the keys: `red` for sums over the waves (two rounds that follow each other use different halves).
-struct OrderSync { uint32_t red[4][ORDER_WAVES], bin[2], rest[2], many[2]; int32_t cross[4]; uint16_t lines[ORDER_SEGS]; };
+struct OrderSync { uint32_t red[4][ORDER_WAVES], count[4 * ORDER_WAVES], bin[2], rest[2], many[2], next; float mass[4 * ORDER_WAVES]; int32_t cross[4]; uint16_t lines[ORDER_SEGS]; };
 
 // Smallest and largest over the waves, of what each left in the two halves of `red`
 __device__ __forceinline__ void waves_extremes(const uint32_t (*red)[ORDER_WAVES], int lane, uint32_t& least, uint32_t& most) {
@@ -83,8 +87,9 @@ struct OrderBound { uint32_t key; int32_t line; bool earlier, later; };
 // sample i + 1 in the list).  The key is found to 20 bits of the samples' span, and to the last bit where more than `few`
 // samples lie in one such step; the line is given where as many samples have one weight: its lines then fall
 // to several ranges.  The same numbers in every workgroup of the list: a bound depends on its rank alone.
+// next: of the first line of range `next` (that is to have one) a key that is not greater.
 // hist: 4096 words of LDS.
-__device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int32_t (&pos)[2], int b, int nb, uint32_t few, uint32_t* hist, OrderSync& sync, OrderBound& from, OrderBound& to) {
+__device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int32_t (&pos)[2], int b, int nb, int next, uint32_t few, uint32_t* hist, OrderSync& sync, OrderBound& from, OrderBound& to, uint32_t& next_key) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     constexpr int PER = 2, S = ORDER_SAMPLES;
     static_assert(S == PER * ORDER_THREADS, "two a thread");
@@ -102,14 +107,16 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int
     for (int j = 0; j < PER; ++j) { at[j] = (key[j] - lo) >> sh; atomicAdd(&hist[at[j] >> 10], 1u); }
     __syncthreads();
     // bins of the two ranks, then the bins inside those (of both at once, in the halves of a word)
-    const uint32_t t0 = (uint32_t)(b * S / nb), t1 = (uint32_t)((b + 1) * S / nb);
+    const uint32_t t0 = (uint32_t)(b * S / nb), t1 = (uint32_t)((b + 1) * S / nb), t2 = (uint32_t)(next * S / nb);
     uint32_t all;
     uint32_t v = hist[tid], e = order_scan(v, sync.red[0], lane, wv, all);
     if (t0 >= e && t0 < e + v) { sync.bin[0] = (uint32_t)tid; sync.rest[0] = t0 - e; }
     if (t1 >= e && t1 < e + v) { sync.bin[1] = (uint32_t)tid; sync.rest[1] = t1 - e; }
+    if (t2 >= e && t2 < e + v) sync.next = (uint32_t)tid;
     if (b == nb - 1 && tid == 0) { sync.bin[1] = 1023u; sync.rest[1] = 0u; }             // (no bound: not looked at)
     __syncthreads();
     const uint32_t bin0 = sync.bin[0], bin1 = sync.bin[1];
+    next_key = next < nb ? lo + (sync.next << 10 << sh) : 0u;
     uint32_t rest0 = sync.rest[0], rest1 = sync.rest[1];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
@@ -184,17 +191,19 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int
 //   - counts the range's lines and those before it, and takes the former into LDS, in index order;
 //   - spreads them over bins, about one line each (below), and ranks the few lines of a bin against each other, by weight
 //     and then by index; bins with too many lines are spread again, each over as many bins as it has lines;
-//   - writes their indices (sidx) where they belong; the first WALK_BLK lines of the order get their weight and maximum written as
-//     well (head_w, head_m), so that the walk can start without a second round trip.
+//   - writes their indices (sidx), weights and maxima (sorted_w, sorted_m: of as many lines as there is room for, 1024 at least) where they belong, so that
+//     the walk reads what it needs as it lies.  (Fetched by the walk through the indices, 1024 lines took it 2500 cycles and more, of which it can go through them in 1500.)
 // The lines of a weight that has ranges to itself are written as they come, by one workgroup, and so are many lines of weights that
 // two ranges meet in.  A range of more than `cap` lines all the same (the samples missed them) is halved until it fits.
 //
-// What bounds it: latencies, one workgroup of sixteen waves per CU: 32768 lines, cycles of one of 4 workgroups: bounds and count 14800, lines
-// into LDS 14300, their span 1600, bins 14600, ranks and results 10200.  Beyond 65536 lines it is the look through the whole
-// list, which every range repeats.  A workgroup runs through its code once and has to fetch it: everything lies in LDS and the loops are
-// not unrolled over it.  (Keys and bins in registers, ten lines a thread, ranks by indirection and many equal weights
-// by digits, 30 KB of code and 88 bytes of scratch: 32 heads of 32768 lines 35 us, now 30; 256 heads of 16384 111 -> 96; 4096 10.8 -> 10.2;
-// 131072 243 both.  The kernel alone.)
+// What bounds it: the instructions of sixteen waves that look through the whole list twice, and latencies; one workgroup per CU.  32768 lines in eight ranges, cycles of a workgroup:
+// bounds 8000, count 11000, lines into LDS 9000, their span 1700, bins 9500, ranks and results 11000.  So the two looks take four lines a lane at once, eight instructions a line, with
+// the weights as they are where their sign allows it, in a short loop with the next lines under way (unrolled over 1024 lines it was half as long again: a workgroup runs through its
+// code once and has to fetch it), and two lists of lines that are not needed are not ranked.  A maximum is fetched when its line is placed and written with the next one.
+// 32 heads, the kernel alone, us, everything in order and only the first 1024 lines' weights / now: 32768 lines 28.6 / 25.5, 12347 18.5 / 17.0, 8192 15.5 / 17.2, 5003 (16 heads) 12.6 / 14.0,
+// 131072 226 / 141, 256 heads of 16384 104 / 92; the walk, which gains what short lists lose here, 24.0 / 15.5, 12.7 / 10.6, 16.1 / 13.8, 14.4 / 12.2, 123 / 52, 25.8 / 18.5.
+// (Keys and bins in registers, ten lines a thread, ranks by indirection and many equal weights by digits, 30 KB of code and 88 bytes of scratch: 32 heads of 32768 lines 35 us where the
+// bins in LDS took 30.)
 // Lists that crowd, 32 heads, the kernel alone, us, by digits / now / segments of 8192 sorted by digits and merged:
 // all but ten lines within 2^12 numbers 1024 lines 13.6 / 10.7 / 7.7, 4096 27.9 / 17.1 / 14.4, 32768 122 / 48 / 54, 131072 320 / 354 / 323; two thirds of one
 // weight, the others of 59 4096 31.9 / 21.6 / 17.7, 32768 96 / 47 / 59, 131072 300 / 238 / 326; two fifths zero 4096 25.6 / 18.3 / 15.0, 32768 34 / 33 / 53,
@@ -205,11 +214,15 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int
 // 59 weights 80862 lines 332 / 284 / 217 / 199, 131072 432 / 466 / 387 / 309, 262144 1020 / 1300 / 1240 / 880 (there each has two thirds of a range);
 // 300 weights 131072 406 / 462 / 329 / 315; two thirds of one weight 131072 356 / 281 / 215 / 328; within 2^12 numbers 262144 1745 / 1230 / 934 / 946.
 // (WHOLE: two workgroups per CU; 256 heads of 1500 lines, the whole ls_select, 29.4 -> 27.9.)
-template <int PT, bool WHOLE>
-__global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(SelectArgs a, int nb, int cap) {
+//
+// LAZY: range b, unless the lines of the ranges before it have `goal` of weight between them, which is more than a walk takes from a list: picks from
+// one list alone reach the target with that, and where columns and diagonals are both taken the overlaps stop the walk after a few of them, or each takes fewer (32 heads of 8192 to
+// 32768 lines went no deeper than 9100 lines, the mixed ones 170).  A walk that needs more, because overlaps are there but smaller than the last lines' weights, is emit_kernel's.
+// a.info of the range then says how many lines those are.  Whether the lines before range `next`, the workgroup's next one, have
+// as much is known as well once the lines have been counted: false, and said in a.info, if they have.
+template <int PT, bool WHOLE, bool LAZY>
+__device__ __forceinline__ bool order_range(const SelectArgs& a, const int list, const int bh, const int b, const int nb, const int next, const int cap, const float goal, unsigned char* order_lds, OrderSync& sync) {
     constexpr int FINE = order_fine(PT);
-    extern __shared__ __align__(16) unsigned char order_lds[];
-    __shared__ OrderSync sync;
     uint32_t* words = reinterpret_cast<uint32_t*>(order_lds);                            // of the fine bins: lines, then places, in pairs
     uint16_t* fine = reinterpret_cast<uint16_t*>(order_lds);                             // [FINE + 1] bin f's at f + 1; in the end bin f has the places from fine[f] up to fine[f + 1]
     uint32_t* coarse = reinterpret_cast<uint32_t*>(order_lds + FINE * 2 + 16);           // [1024]; later least and largest key of the bins that are too full
@@ -218,16 +231,47 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
     uint16_t* line = reinterpret_cast<uint16_t*>(spread + cap);                          // [cap] index, low half
     uint16_t* bins = line + cap;                                                         // [cap] fine bin | DONE | EQUAL; between two spreads, place in the order | DONE or first place of its bin
     constexpr uint32_t PLACE = 0x3FFFu, DONE = 0x4000u, EQUAL = 0x8000u;
-    const int list = blockIdx.x & 1, bh = blockIdx.x >> 1, b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = (int)a.n;
     const float* src = (list == 0 ? a.slash : a.vert) + (int64_t)bh * n;
     const float* mx = (list == 0 ? a.smax : a.vmax) + (int64_t)bh * n;
     int32_t* out = a.sidx + ((int64_t)list * a.BH + bh) * n;
-    const int64_t head = ((int64_t)list * a.BH + bh) * WALK_BLK;
-    const int per = (n + ORDER_THREADS - 1) / ORDER_THREADS * 64;
+    const int kept = (int)a.kept;                          // lines of the order whose weight and maximum are written as well
+    float* sorted_w = a.sorted_w + ((int64_t)list * a.BH + bh) * kept;
+    float* sorted_m = a.sorted_m ? a.sorted_m + ((int64_t)list * a.BH + bh) * kept : nullptr;
+    auto say = [&](int range, int what) { if (LAZY && tid == 0) a.info[((int64_t)list * a.BH + bh) * SELECT_RANGES + range] = what; };
+    const int per = (n + 4 * ORDER_THREADS - 1) / (4 * ORDER_THREADS) * 256;
     const int w0 = wv * per < n ? wv * per : n, w1 = w0 + per < n ? w0 + per : n;         // this wave's lines
+    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+    // f(first line, weights, how many of the four there are) for the wave's lines, four a lane, in the list's order, 256 at a time with the next under way; the last, of which
+    // there may be fewer, by themselves.
+    auto lines4 = [&](auto f) {
+        int i0 = w0;
+        const int rest = w0 + (w1 - w0) / 256 * 256 + 4 * lane, from = rest < n - 4 ? rest : n - 4;
+        f32x4u y = f32x4u{0.f, 0.f, 0.f, 0.f};
+        if (w1 == n && w0 < n) y = *reinterpret_cast<const f32x4u*>(src + from);
+        if (i0 + 256 <= w1) {
+            const float* at = src + w0 + 4 * lane;
+            f32x4u next4 = *reinterpret_cast<const f32x4u*>(at);
+#pragma unroll 1
+            for (;;) {
+                const f32x4u x = next4;
+                const bool again = i0 + 512 <= w1;
+                at += 256;
+                if (again) next4 = *reinterpret_cast<const f32x4u*>(at);
+                f(i0 + 4 * lane, x, std::integral_constant<int, 4>{});
+                i0 += 256;
+                if (!again) break;
+            }
+        }
+        if (i0 < w1) {                                     // (the list's end: a lane whose four would reach beyond it has the list's last four, and takes of them what is its own)
+            const int by = rest - from, some = w1 - rest;
+            const float p = (by & 1) ? y[1] : y[0], q = (by & 1) ? y[2] : y[1], r = (by & 1) ? y[3] : y[2];
+            const f32x4u x = {(by & 2) ? r : p, (by & 2) ? y[3] : q, r, y[3]};
+            f(rest, x, some < 0 ? 0 : some < 4 ? some : 4);
+        }
+    };
     // f(line, key, whether there is such a line) for the wave's lines, 64 at a time
     auto read = [&](auto f) {
         for (int i0 = w0; i0 < w1; i0 += 64 * 8) {
@@ -238,9 +282,20 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
             for (int j = 0; j < 8; ++j) { const int i = i0 + 64 * j + lane; f(i, desc_key(x[j]), i < w1); }
         }
     };
+    // (a maximum is written when the thread has its next one to ask for, which then does not wait for it)
+    float top = 0.f;
+    int top_at = -1;
+    auto settle = [&]() {
+        if (top_at < 0) return;
+        sorted_m[top_at] = top;
+        top_at = -1;
+    };
     auto put = [&](int at, int i, uint32_t k) {            // line i is the `at`-th of the order
         out[at] = i;
-        if (at < WALK_BLK) { a.head_w[head + at] = key_to_float(k); a.head_m[head + at] = mx[i]; }
+        if (at < kept) {
+            sorted_w[at] = key_to_float(k);
+            if (sorted_m) { settle(); top = mx[i]; top_at = at; }
+        }
     };
     auto lanes_before = [](uint64_t who) -> int { return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0u)); };
     // The range: the weights from `lo` to `end`.  With `ends` it begins or ends among lines of one weight, has all lines from key << 32 | index of
@@ -248,7 +303,18 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
     uint32_t lo = 0u, end = 0xFFFFFFFFu, front = 0u, back = 0u;
     uint64_t lo_line = 0u, end_line = ~0ull;
     bool ends = false, alone = false;                      // alone: `front` is its only weight
+    uint32_t next_key = 0u;
+    bool more = true;
     if (!WHOLE && nb > 1) {
+        // whether a maximum of the b-th part of the list is negative or no number, for the walk: asked for here, looked at behind the bounds
+        constexpr int PART = 8;
+        const int part = (n + nb - 1) / nb, part0 = b * part, part1 = part0 + part < n ? part0 + part : n;
+        float most_of[PART];
+#pragma unroll
+        for (int j = 0; j < PART; ++j) {
+            most_of[j] = 0.f;
+            if (a.odd && part0 + j * ORDER_THREADS < part1) { const int i = part0 + j * ORDER_THREADS + tid; most_of[j] = mx[i < part1 ? i : part0]; }
+        }
         uint32_t sample[2];
         int32_t where[2];
         OrderBound from, to;
@@ -261,27 +327,34 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
         // weights of so many samples are shared: two fifths of a range where it has room for that beside its own, a sixteenth where they would leave the
         // ranges unequal
         const uint32_t few = (uint32_t)(n > ORDER_WIDE ? 2 * ORDER_SAMPLES / (5 * nb) : ORDER_SAMPLES / (16 * nb));
-        order_bounds(sample, where, b, nb, few, words, sync, from, to);
+        order_bounds(sample, where, b, nb, next, few, words, sync, from, to, next_key);
+        if (a.odd) {
+            bool odd = false;
+#pragma unroll
+            for (int j = 0; j < PART; ++j) odd = odd || !(most_of[j] >= 0.f);
+            odd = __syncthreads_or(odd);
+            if (tid == 0) a.odd[((int64_t)list * a.BH + bh) * SELECT_RANGES + b] = odd ? 1 : 0;
+        }
         const bool last = b == nb - 1;
         if (b == 0) from = OrderBound{0u, -1, false, false};
         // A weight that has ranges to itself: the first of them takes all its lines, those at its ends none
         if (!last && to.line >= 0 && (to.earlier || to.later)) {
             if (from.line >= 0 && from.key == to.key) {
-                if (from.earlier) return;
+                if (from.earlier) { say(b, 0); return true; }
                 from.line = 0; to.line = 0x7FFFFFFF;
             } else {
                 to.line = -1;
             }
         }
         if (from.line >= 0 && (from.earlier || from.later) && (last || from.key != to.key)) {
-            if (from.key == 0xFFFFFFFFu) return;
+            if (from.key == 0xFFFFFFFFu) { say(b, 0); return true; }
             from.line = -1; ++from.key;
         }
         lo_line = (uint64_t)from.key << 32 | (uint32_t)(from.line > 0 ? from.line : 0);
         lo = from.key;
         if (!last) {
             const uint64_t behind = (uint64_t)to.key << 32 | (uint32_t)(to.line > 0 ? to.line : 0);
-            if (behind <= lo_line) return;                 // nothing (the bounds are the same for every thread)
+            if (behind <= lo_line) { say(b, 0); return true; }   // nothing (the bounds are the same for every thread)
             end_line = behind - 1u;
             end = to.key - 1u;
         }
@@ -296,56 +369,83 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
     if (!WHOLE && tid < 4) sync.cross[tid] = 0x7FFFFFFF;
     for (;;) {
         int before = w0, m = n;                            // lines of the range in the waves before, and in all (a list in one range: all lines)
-        bool picked = false;
+        bool picked = false, plain = false;
         const uint32_t span = hi - lo;
         if (!WHOLE && nb > 1) {
-            uint32_t here = 0u, below = 0u, fronts = 0u, backs = 0u;
-            auto counts = [&](auto ENDS) {
-                auto count = [&](int i, uint32_t k, bool any) {
-                    if (decltype(ENDS)::value) {
-                        const uint64_t x = (uint64_t)k << 32 | (uint32_t)i;
-                        const bool in = any && x - lo_line <= end_line - lo_line;
-                        here += in ? 1u : 0u; fronts += in && k == front ? 1u : 0u; backs += in && k == back ? 1u : 0u;
-                        below += any && x < lo_line ? 1u : 0u;
-                    } else {
-                        here += any && k - lo <= span ? 1u : 0u;
-                        below += any && k < lo ? 1u : 0u;
-                    }
-                };
-                // (their order does not matter here: 16 bytes a lane)
-                typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-                int i = w0 + 4 * lane;
-                for (; i - 4 * lane + 1024 <= w1; i += 1024) {
-                    f32x4u x[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x[j] = *reinterpret_cast<const f32x4u*>(src + i + 256 * j);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) count(i + 256 * j + e, desc_key(x[j][e]), true);
-                }
-                for (i += lane - 4 * lane; i - lane < w1; i += 64 * 4) {
-                    float x[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) x[j] = src[i + 64 * j < n ? i + 64 * j : n - 1];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) count(i + 64 * j, desc_key(x[j]), i + 64 * j < w1);
-                }
-            };
-            if (ends) counts(std::true_type{}); else counts(std::false_type{});
-            here = lanes_upto(here); below = lanes_upto(below);
-            __syncthreads();                               // `red` and the last range's lines are free again
+            // Weights as integers in the order of the floats: t, largest first.  (That of a weight of 0 or more is its bits, and of others the sign is enough where
+            // a range begins at 0 or more and ends there as well or nowhere.)
+            const int t_last = (int)(hi ^ 0x7FFFFFFFu), t_first = (int)(lo ^ 0x7FFFFFFFu), t_next = (int)(next_key ^ 0x7FFFFFFFu);
+            plain = t_first >= 0 && t_next >= 0 && (t_last >= 0 || t_last == (int)0x80000000);
+            // of this lane's lines: in the range, before it, before range `next`, of the weights at its ends; the weight of those before each
+            uint32_t here = 0u, below = 0u, short_of = 0u, fronts = 0u, backs = 0u;
+            float mass = 0.f, next_mass = 0.f;
             if (ends) {
-                fronts = lanes_upto(fronts); backs = front == back ? 0u : lanes_upto(backs);
-                if (lane == 63) { sync.red[2][wv] = fronts; sync.red[3][wv] = backs; }
+                lines4([&](int i, const f32x4u& w, auto some) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t k = desc_key(w[e]);
+                        const uint64_t x = (uint64_t)k << 32 | (uint32_t)(i + e);
+                        const bool any = e < some, in = any && x - lo_line <= end_line - lo_line, less = any && x < lo_line, before_next = any && k < next_key;
+                        here += in ? 1u : 0u; below += less ? 1u : 0u; fronts += in && k == front ? 1u : 0u; backs += in && k == back && front != back ? 1u : 0u;
+                        if (LAZY) { short_of += before_next ? 1u : 0u; mass += less ? w[e] : 0.f; next_mass += before_next ? w[e] : 0.f; }
+                    }
+                });
+            } else {
+                lines4([&](int, const f32x4u& w, auto some) {
+                    int t[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { const float x = w[e]; t[e] = __builtin_bit_cast(int, x); }      // (not of the vector's element: that is always the first)
+                    if (!plain) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) t[e] ^= (t[e] >> 31) & 0x7FFFFFFF;
+                    }
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool any = e < some, less = any && t[e] > t_first, before_next = any && t[e] > t_next;
+                        here += any && (uint32_t)t[e] - (uint32_t)t_last <= span ? 1u : 0u; below += less ? 1u : 0u;
+                        if (LAZY) { short_of += before_next ? 1u : 0u; mass += less ? w[e] : 0.f; next_mass += before_next ? w[e] : 0.f; }
+                    }
+                });
             }
-            if (lane == 63) { sync.red[0][wv] = here; sync.red[1][wv] = below; }
+            {
+                const uint32_t two = lanes_upto(here | below << 16);                     // (at most 16384 lines a wave)
+                if (LAZY) { short_of = lanes_upto(short_of); mass = wave_sum(mass); next_mass = wave_sum(next_mass); }
+                __syncthreads();                           // `red` and the last range's lines are free again
+                if (lane == 63) {
+                    sync.count[wv] = two & 0xFFFFu; sync.count[ORDER_WAVES + wv] = two >> 16; sync.count[2 * ORDER_WAVES + wv] = short_of;
+                    if (LAZY) { sync.mass[wv] = mass; sync.mass[ORDER_WAVES + wv] = next_mass; }
+                }
+                if (ends) {
+                    fronts = lanes_upto(fronts); backs = lanes_upto(backs);
+                    if (lane == 63) { sync.red[2][wv] = fronts; sync.red[3][wv] = backs; }
+                }
+            }
             __syncthreads();
-            uint32_t all, ahead;
-            before = (int)waves_before(sync.red[0], lane, wv, all);
-            (void)waves_before(sync.red[1], lane, wv, ahead);
-            m = (int)all;
-            if (base < 0) base = (int)ahead;
+            // sums over the waves, three at once in rows of sixteen lanes
+            int sums = (int)sync.count[lane];
+            sums += __builtin_amdgcn_update_dpp(0, sums, 0x111, 0xF, 0xF, false);        // row_shr:1, 2, 4, 8
+            sums += __builtin_amdgcn_update_dpp(0, sums, 0x112, 0xF, 0xF, false);
+            sums += __builtin_amdgcn_update_dpp(0, sums, 0x114, 0xF, 0xF, false);
+            sums += __builtin_amdgcn_update_dpp(0, sums, 0x118, 0xF, 0xF, false);
+            m = __builtin_amdgcn_readlane(sums, 15);
+            before = wv > 0 ? __builtin_amdgcn_readlane(sums, wv - 1) : 0;
+            const int ahead = __builtin_amdgcn_readlane(sums, 31);
+            if (LAZY && base < 0) {
+                float g = sync.mass[lane];
+                auto fl = [](int x) { return __builtin_bit_cast(float, x); };
+                g += fl(__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, g), 0x111, 0xF, 0xF, false));
+                g += fl(__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, g), 0x112, 0xF, 0xF, false));
+                g += fl(__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, g), 0x114, 0xF, 0xF, false));
+                g += fl(__builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, g), 0x118, 0xF, 0xF, false));
+                if (b > 0 && fl(__builtin_amdgcn_readlane(__builtin_bit_cast(int, g), 15)) >= goal) {
+                    say(b, -1 - ahead);
+                    if (next < nb) say(next, -1 - ahead);
+                    return false;
+                }
+                more = !(next < nb && fl(__builtin_amdgcn_readlane(__builtin_bit_cast(int, g), 31)) >= goal);
+                if (!more) say(next, -1 - __builtin_amdgcn_readlane(sums, 47));
+            }
+            if (base < 0) base = ahead;
             if (ends) {
                 uint32_t f_all, r_all;
                 const int f_before = (int)waves_before(sync.red[2], lane, wv, f_all), r_before = (int)waves_before(sync.red[3], lane, wv, r_all);
@@ -393,19 +493,47 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
             if (WHOLE) {
                 for (int p = tid; p < m; p += ORDER_THREADS) { const uint32_t k = desc_key(src[p]); keys[p] = k; extremes(k, true); }
             } else {
-                auto pick = [&](auto ENDS) {
+                if (ends) {
                     read([&](int i, uint32_t k, bool any) {
-                        const bool in = any && (decltype(ENDS)::value ? ((uint64_t)k << 32 | (uint32_t)i) - lo_line <= end_line - lo_line : k - lo <= span);
+                        const bool in = any && ((uint64_t)k << 32 | (uint32_t)i) - lo_line <= end_line - lo_line;
                         const uint64_t who = __ballot(in);
                         const int at = before + lanes_before(who);
                         if (in) { keys[at] = k; line[at] = (uint16_t)i; }
                         if ((i & 0xFFFF) == 0 && any) sync.cross[i >> 16] = before;
                         before += __popcll(who);
                     });
-                };
-                if (ends) pick(std::true_type{}); else if (!picked) pick(std::false_type{});
+                } else if (!picked) {                      // (the bits of their weights, for now)
+                    const int t_last = (int)(hi ^ 0x7FFFFFFFu);
+                    lines4([&](int i, const f32x4u& w, auto some) {
+                        bool in[4];
+                        float x[4];
+                        uint32_t mine = 0u;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            x[e] = w[e];
+                            int t = __builtin_bit_cast(int, x[e]);
+                            if (!plain) t ^= (t >> 31) & 0x7FFFFFFF;
+                            in[e] = e < some && (uint32_t)t - (uint32_t)t_last <= span;
+                            mine += in[e] ? 1u : 0u;
+                        }
+                        const uint32_t upto = lanes_upto(mine);
+                        int p = before + (int)(upto - mine);
+                        if (n > 65536 && (i & 0xFFFF) == 0 && some > 0) sync.cross[i >> 16] = p;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            if (in[e]) { keys[p] = __builtin_bit_cast(uint32_t, x[e]); line[p] = (uint16_t)(i + e); }
+                            p += in[e] ? 1 : 0;
+                        }
+                        before += __builtin_amdgcn_readlane((int)upto, 63);
+                    });
+                }
                 __syncthreads();
-                for (int p = tid; p < m; p += ORDER_THREADS) extremes(keys[p], true);
+                const bool bits = !ends && !picked;
+                for (int p = tid; p < m; p += ORDER_THREADS) {
+                    uint32_t k = keys[p];
+                    if (bits) { k = desc_key(__builtin_bit_cast(float, k)); keys[p] = k; }
+                    extremes(k, true);
+                }
             }
             agree();
             const int c1 = sync.cross[1], c2 = sync.cross[2], c3 = sync.cross[3];
@@ -565,6 +693,22 @@ __global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(Sel
         if (hi == end) break;
         lo = hi + 1u; hi = end;
     }
+    settle();
+    say(b, 0);
+    return more;
+}
+// grid (lists, nb or half as many: workgroup w then takes range w, and the one as many behind it if that is wanted)
+template <int PT, bool WHOLE, bool LAZY>
+__global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(SelectArgs a, int cap) {
+    extern __shared__ __align__(16) unsigned char order_lds[];
+    __shared__ OrderSync sync;
+    const int list = blockIdx.x & 1, bh = blockIdx.x >> 1, nb = a.ranges;
+    const float goal = LAZY ? a.alpha * a.total[bh] * ORDER_GOAL : 0.f;
+    for (int b = blockIdx.y; b < nb; b += (int)gridDim.y) {
+        if (!order_range<PT, WHOLE, LAZY>(a, list, bh, b, nb, b + (int)gridDim.y, cap, goal, order_lds, sync)) break;
+        if (WHOLE) break;
+        __syncthreads();
+    }
 }
 
 // ---- running sums in binary32, many additions at a time ------------------------------------------
@@ -678,6 +822,28 @@ __device__ __forceinline__ int chain_step(const float (&g)[E], int lane, int fir
     for (int e = 1; e < E; ++e) x[e] = __fadd_rn(x[e - 1], g[e]);
     return leave != 0ull ? __ffsll((unsigned long long)leave) - 1 : 63;
 }
+// All entries added to `sum` in one step, if it then stays in its binade and below `target` (no gain is negative, so that it was below it all the way):
+// the scan alone says so, without the lanes' own sums.  False, and nothing done, where it might not.
+// POSITIVE: every gain is known to be above 0.
+template <int E, bool POSITIVE = false>
+__device__ __forceinline__ bool chain_all(const float (&g)[E], float target, float& sum) {
+    const uint32_t sb = __builtin_bit_cast(uint32_t, sum), binade = sb & 0x7F800000u;
+    if (sb < (64u << 23) || sb > (250u << 23)) return false;
+    const uint32_t even = binade | 0x400000u;
+    float xe = __builtin_bit_cast(float, even), xo = __builtin_bit_cast(float, even + 1u), least = g[0];
+#pragma unroll
+    for (int e = 0; e < E; ++e) { xe = __fadd_rn(xe, g[e]); xo = __fadd_rn(xo, g[e]); if (!POSITIVE) least = fminf(least, g[e]); }
+    // (a NaN leaves xo a NaN)
+    if (__ballot(!(xo < __builtin_bit_cast(float, binade + 0x800000u) && (POSITIVE || least >= 0.f))) != 0ull) return false;
+    const ChainInc inc = {(int32_t)(__builtin_bit_cast(uint32_t, xe) - even), (int32_t)(__builtin_bit_cast(uint32_t, xo) - (even + 1u))};
+    const ChainInc all = chain_then(chain_before(inc), inc);       // of lane 63: 63 lanes of less than 2^22 each
+    const int32_t m0 = (int32_t)(sb & 0x7FFFFFu);
+    const int32_t m = m0 + __builtin_amdgcn_readlane((m0 & 1) ? all.o : all.e, 63);
+    const float x = __builtin_bit_cast(float, binade | (uint32_t)m);
+    if (m >= 1 << 23 || !(x < target)) return false;
+    sum = x;
+    return true;
+}
 // Adds entries 0 .. `limit` - 1 (the gains are 0 from there on) to `sum`, which is below `target`, in order until it
 // reaches the target or they are used up; returns how many were added.
 template <int E, bool SIGNED = false>
@@ -775,13 +941,11 @@ constexpr int WALK_THREADS = 384;              // wave 0 decides the runs, wave 
 // A lane looks at E list entries: a run has up to 64 E picks.  Short lists have short runs, long ones long: 4 / 8 / 16, ls_select of
 // 32 heads, us: 2048 lines 22.0 / 23.1 / 24.3, 4096 24.2 / 24.0 / 25.3, 12347 34.9 / 35.5 / 36.4, 16384 56.2 / 49.3 / 45.7, 32768 76.8 / 67.2 / 63.1,
 // 65536 157 / 137 / 128; 256 heads of 1500 lines 27.5 / 29.0 / 29.9.
-constexpr int64_t WALK_SHORT = 2048, WALK_LONG = 16384;        // up to: 4; from: 16
-// Where the picks go back and forth between the lists a run is one or a few, and its price is that of looking at all E entries.  Of
-// sixteen the deciding wave then looks at these few only, from a run of up to half of what they hold until one fills them.  The walk alone
-// with sixteen throughout / now, 32 heads of 32768 lines, us: runs of one to five picks 76.5 / 54.7, of one 489 / 320, one run to the end 18.8 / 18.3;
-// 131072 lines of a long turn 123 / 120.  (Eight throughout: 55.5, 346, 15.6; 131.  Beginning with the few: 32k turn 25.4 -> 27.1.  With the
-// sums over four entries a lane as well: 52.2, 308, 17.9; 130.  The same with eight entries instead of sixteen: 8192 lines of single picks
-// 95.8 -> 83.9, of a first turn 21.6 -> 23.0.)
+constexpr int64_t WALK_SHORT = 2048, WALK_LONG = 8192;         // up to: 4; from: 16
+// (With long runs taken unseen, below, sixteen pay from 8192 lines on: 8 / 16, the walk alone, 8192 lines 15.9 / 13.8, 5003 12.2 / 13.5.)
+// Where the picks go back and forth between the lists a run is one or a few, and its price is that of looking at all E entries.
+// The deciding wave then looks at these few only, from the beginning and from a run of up to half of what they hold until one fills them.  The walk alone
+// with sixteen throughout / so, 32 heads of 32768 lines, us: runs of one to five picks 76.5 / 54.7, of one 489 / 320.
 constexpr int WALK_NARROW = 4;
 constexpr int WALK_NBLK = 4;                   // blocks of a list resident in LDS (a ring over sorted positions)
 constexpr int WALK_CAP = WALK_BLK * WALK_NBLK;
@@ -794,13 +958,17 @@ static_assert(WALK_EB % 2 == 0 && 64 * 16 <= WALK_BLK, "a run never reaches beyo
 template <int E> struct WalkList { float cw[WALK_CAP + 64 * E], cl[WALK_CAP + 64 * E], pre[WALK_CAP + 64 * E]; };
 // One run of picks from one list: the gain of each pick, how many of them count, and whether the walk ends
 // after them because no line is left that adds anything.
-template <int E> struct WalkRun { float g[64 * E]; int which, limit, last, pad; };
+template <int E> struct WalkRun {
+    float g[72 * E];                                       // pick p at p + 2 (p / 16): lanes that read 4, 8 or 16 picks each meet all banks
+    int which, limit, last, pad;                           // (read as one)
+};
 // What the lanes need of a list when its head is at `h`: lane l looks at the entries h + l, h + 64 + l, ... (weight,
 // overlap prefix, length; whatever lies there past the end of the list), every lane at the head's own three values.
 // Re-read only when the head of that list moves.  (All of them lie in the head's block or the one after it.)
 template <int N> struct WalkView { float cw[N], pre[N], cl[N], w0, l0, ol0; };
-struct WalkSync { int staged[2], summed_blk[2], cur[2], summed, stop, done, err, runs, decided, cnt_s, cnt_v; float tot[2]; };
+struct WalkSync { int staged[2], summed_blk[2], cur[2], summed, stop, done, err, runs, decided, cnt_s, cnt_v, falls[2], need[2], cut, open; float tot[2]; };      // falls: a list's prefix sums do not rise throughout; need: blocks whose prefix sums are wanted; cut: a list is wanted further than it is in order; open: and the sum had not reached the target
 static_assert(offsetof(WalkSync, summed) % 8 == 0 && offsetof(WalkSync, stop) == offsetof(WalkSync, summed) + 4, "summed and stop are read as one 8-byte word");   // tot: a list's whole overlap sum
+constexpr int RUN_WHOLE = 2;                   // a run's `last`: it has all its picks, and every gain is above 0
 constexpr int WALK_RING = 4;                   // runs decided ahead of the running sum
 template <int E> constexpr size_t WALK_LDS_BYTES = 2 * sizeof(WalkList<E>) + WALK_RING * sizeof(WalkRun<E>) + sizeof(WalkSync);
 
@@ -912,26 +1080,45 @@ __device__ __forceinline__ int walk_first(const bool (&p)[E]) {
 //
 // The waves share only LDS.  Each list is staged in blocks of WALK_BLK sorted positions into a ring of WALK_NBLK
 // blocks: waves 1 / 3 write the weights and line lengths of a block (staged[l] = blocks written), waves 4 / 5
-// its overlap prefix sums, reading the maxima straight from global memory (summed_blk[l]); both load the next
-// block while they work on the current one.  Block b may be written once the deciding wave's head of that list
+// its overlap prefix sums (summed_blk[l]), 2700 cycles a block and only of blocks that the deciding wave has asked for (need[l]); both load the next
+// two blocks while they work on the current one.  Block b may be written once the deciding wave's head of that list
 // has reached block b - WALK_NBLK + 1 (cur[l] = the head's block): nothing before the head is read again.  The
 // deciding wave (0) needs the head's block and the one after it; it publishes cur[l] and runs = the number of
 // runs it has put into the ring of runs; the summing wave (2) publishes summed = the number of runs it has
 // taken out, and stop when the walk is over.  The summing wave writes the result; the deciding wave ends the
 // stagers through `done`.  Every wait is a bounded spin that also ends when another wave has reported a failed
 // wait, so all six waves leave in every case.
-template <int E>
-__device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* walk_lds) {
+// Most walks are one run from one list to the target (32 heads of 32768 lines: 29 of them, 96 to 9071 picks).  Once the other list's head adds nothing any more, 1024 picks need no look
+// at each, nor their overlap prefix sums (quick, below: 1300 cycles, looked at 3900), and their sum comes from the scan alone (chain_all: 1500, from 2500).
+// SORTED: the lists' weights and maxima lie in order; otherwise only those of the first block do.
+template <int E, bool SORTED>
+__device__ __forceinline__ void walk_head(const SelectArgs& a, const int bh, unsigned char* walk_lds) {
     using List = WalkList<E>;
     using Run = WalkRun<E>;
     constexpr int RUN = 64 * E;
     List* lists = reinterpret_cast<List*>(walk_lds);
     Run* ring = reinterpret_cast<Run*>(walk_lds + 2 * sizeof(List));
     WalkSync* sync = reinterpret_cast<WalkSync*>(walk_lds + 2 * sizeof(List) + WALK_RING * sizeof(Run));
-    const int bh = blockIdx.x, lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = (int)a.n;
     const int nblk = (n + WALK_BLK - 1) / WALK_BLK;
+    const bool informed = SORTED && a.odd != nullptr;      // order_kernel has looked at the maxima
+    // how far list l is in order, and (odd) whether a maximum of it is negative or no number
+    auto reach = [&](int l, int* odd) {
+        const int64_t of = ((int64_t)l * a.BH + bh) * SELECT_RANGES;
+        int x = 0, y = 0, far = n;
+        if (odd && informed) {
+            x = lane < a.ranges ? a.odd[of + lane] : 0; y = lane + 64 < a.ranges ? a.odd[of + lane + 64] : 0;
+        }
+        if (SORTED && a.open) {
+            const int p = lane < a.ranges ? a.info[of + lane] : 0, q = lane + 64 < a.ranges ? a.info[of + lane + 64] : 0;
+            const int at = p < 0 ? -1 - p : n, at2 = q < 0 ? -1 - q : n;
+            far = __builtin_amdgcn_readlane((int)lanes_min((uint32_t)(at < at2 ? at : at2)), 63);
+        }
+        if (odd) *odd = __ballot((x | y) != 0) != 0ull ? 1 : 0;
+        return far;
+    };
     const int64_t nh = a.n_hat;
     const int spin_limit = a.spin_limit;       // bound of every wait between the waves
     const int64_t seg_s = ((int64_t)0 * a.BH + bh) * a.n, seg_v = ((int64_t)1 * a.BH + bh) * a.n;
@@ -939,66 +1126,103 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
     if (threadIdx.x == 0) {
         sync->staged[0] = sync->staged[1] = 0; sync->summed_blk[0] = sync->summed_blk[1] = 0;
         sync->cur[0] = sync->cur[1] = 0; sync->done = 0; sync->err = 0;
-        sync->runs = 0; sync->summed = 0; sync->decided = 0; sync->stop = 0;
+        sync->runs = 0; sync->summed = 0; sync->decided = 0; sync->stop = 0; sync->falls[0] = sync->falls[1] = 0; sync->need[0] = sync->need[1] = 2; sync->cut = 0;
     }
-    __syncthreads();
-
+    // (every wave comes to one barrier here, the stagers once their first loads are under way)
+    // Its blocks by `even` and `odd` in turn, as the ring has room for them; `ready`: how many are there.  (In straight code: what one has
+    // asked for is still under way when the other waits for its own.)
+    int far = n;                               // a stager's list is in order up to there
+    auto stage_blocks = [&](const int* cur, const int* need, int* ready, auto even, auto odd) {
+        int b = 0, spins = 0;
+        const int blocks = (far + WALK_BLK - 1) / WALK_BLK;
+        auto room = [&]() {
+            for (;;) {
+                if (b >= blocks || walk_ld(&sync->done) != 0) return false;
+                if (b <= walk_ld(cur) + WALK_NBLK - 1 && (!need || b < walk_ld(need))) break;
+                __builtin_amdgcn_s_sleep(2);
+                if (++spins > spin_limit) { walk_st(&sync->err, 1); return false; }
+            }
+            spins = 0;
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            return true;
+        };
+        auto publish = [&]() {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+            ++b;
+            if (lane == 0) walk_st(ready, b);
+        };
+        while (room()) {
+            even(b);
+            publish();
+            if (!room()) break;
+            odd(b);
+            publish();
+        }
+    };
     if (wv == 1 || wv == 3) {
         // ------------------------------------------------------------------ weights and lengths of one list
         const int l = wv == 1 ? 0 : 1;
         List& L = lists[l];
         const int64_t seg = l == 0 ? seg_s : seg_v;
         const float* w_l = (l == 0 ? a.slash : a.vert) + (int64_t)bh * a.n;   // weights by line index
+        const float* sw = a.sorted_w + ((int64_t)l * a.BH + bh) * a.kept;     // ... in order
         const int32_t* i_l = a.sidx + seg;
         const int nh32 = (int)nh;
         constexpr int PER = WALK_BLK / 64;
-        // the block after the last one written to LDS (indices and weights), and the indices of the one after it:
-        // the weights are fetched through the indices, so the indices are requested a block earlier
-        float fw[PER]; int32_t fx[PER], fxn[PER];
+        // (What lies behind the list is read as well, inside the workspace, and nothing made of it.  One address for a block's loads:
+        // with a look at each entry's place a wave had 2 KB of code to fetch before its first one was asked for.)
+        struct Block { float w[PER]; int32_t x[PER]; };
         auto fetch_idx = [&](int b, int32_t (&x)[PER]) {
+            if (b >= nblk) return;
+            const int32_t* at = i_l + b * WALK_BLK + lane;
 #pragma unroll
-            for (int j = 0; j < PER; ++j) {
-                const int gi = b * WALK_BLK + lane + j * 64;
-                x[j] = i_l[gi < n ? gi : n - 1];
-            }
+            for (int j = 0; j < PER; ++j) x[j] = at[j * 64];
         };
-        auto fetch = [&](int b) {                          // fx <- fxn (block b), its weights, and block b + 1's indices
+        auto fetch_sorted = [&](int b, Block& f) {
+            if (b >= nblk) return;
+            const float* at = sw + b * WALK_BLK + lane;
 #pragma unroll
-            for (int j = 0; j < PER; ++j) { fx[j] = fxn[j]; fw[j] = w_l[fx[j]]; }
-            fetch_idx(b + 1, fxn);
+            for (int j = 0; j < PER; ++j) f.w[j] = at[j * 64];
+            fetch_idx(b, f.x);
         };
-        {                                                  // block 0: its weights were written in order by order_kernel
-            const float* hw = a.head_w + ((int64_t)l * a.BH + bh) * WALK_BLK;
-            fetch_idx(0, fx);
-#pragma unroll
-            for (int j = 0; j < PER; ++j) { const int gi = lane + j * 64; fw[j] = hw[gi < n ? gi : n - 1]; }
-            fetch_idx(1, fxn);
-        }
-        int b = 0;
-        int spins = 0;
-        while (walk_ld(&sync->done) == 0 && b < nblk) {
-            if (b > walk_ld(&sync->cur[l]) + WALK_NBLK - 1) {
-                __builtin_amdgcn_s_sleep(2);
-                if (++spins > spin_limit) { walk_st(&sync->err, 1); break; }
-                continue;
-            }
-            spins = 0;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        auto write = [&](int b, const Block& f) {
             const int slot = (b & (WALK_NBLK - 1)) * WALK_BLK;
+            float *cw = L.cw + slot + lane, *cl = L.cl + slot + lane;
+            auto length = [&](int x) { return (float)(n - x < nh32 ? n - x : nh32); };     // line length in the n_hat x n block
+            auto put = [&](auto WHOLE, int to) {
 #pragma unroll
-            for (int j = 0; j < PER; ++j) {
-                const int i = lane + j * 64;
-                const bool in = b * WALK_BLK + i < n;
-                const int len = n - fx[j] < nh32 ? n - fx[j] : nh32;       // line length in the n_hat x n block
-                L.cw[slot + i] = in ? fw[j] : 0.f;
-                L.cl[slot + i] = in ? (float)len : 1.f;
-                if (slot == 0 && 64 * j < RUN) { L.cw[WALK_CAP + i] = in ? fw[j] : 0.f; L.cl[WALK_CAP + i] = in ? (float)len : 1.f; }
-            }
-            fetch(b + 1);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            ++b;
-            if (lane == 0) walk_st(&sync->staged[l], b);
+                for (int j = 0; j < (decltype(WHOLE)::value == 2 ? E : PER); ++j) {
+                    const bool in = decltype(WHOLE)::value == 1 || b * WALK_BLK + lane + j * 64 < n;
+                    cw[to + j * 64] = in ? f.w[j] : 0.f;
+                    cl[to + j * 64] = in ? length(f.x[j]) : 1.f;
+                }
+            };
+            if ((b + 1) * WALK_BLK <= n) put(std::integral_constant<int, 1>{}, 0); else put(std::integral_constant<int, 0>{}, 0);
+            if (slot == 0) put(std::integral_constant<int, 2>{}, WALK_CAP);       // the first entries once more
+        };
+        if constexpr (SORTED) {                            // two blocks under way, in turn
+            Block even, odd;
+            fetch_sorted(0, even);
+            fetch_sorted(1, odd);
+            far = reach(l, nullptr);
+            __syncthreads();
+            stage_blocks(&sync->cur[l], nullptr, &sync->staged[l], [&](int b) { write(b, even); fetch_sorted(b + 2, even); }, [&](int b) { write(b, odd); fetch_sorted(b + 2, odd); });
+        } else {
+            // the block after the last one written to LDS (indices and weights), and the indices of the one after it:
+            // the weights are fetched through the indices, so the indices are requested a block earlier
+            Block f;
+            int32_t next[PER];
+            fetch_sorted(0, f);                            // (its weights are there in order)
+            fetch_idx(1, next);
+            __syncthreads();
+            auto block = [&](int b) {
+                write(b, f);
+#pragma unroll
+                for (int j = 0; j < PER; ++j) { f.x[j] = next[j]; f.w[j] = (b + 1) * WALK_BLK + lane + j * 64 < n ? w_l[f.x[j]] : 0.f; }
+                fetch_idx(b + 2, next);
+            };
+            stage_blocks(&sync->cur[l], nullptr, &sync->staged[l], block, block);
         }
         return;
     }
@@ -1010,35 +1234,55 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
         List& L = lists[l];
         const int32_t* i_l = a.sidx + (l == 0 ? seg_s : seg_v);
         const float* m_l = (l == 0 ? a.smax : a.vmax) + (int64_t)bh * a.n;     // maxima by line index
-        float m[WALK_EB], mn[WALK_EB];
-        int32_t ix[WALK_EB];                   // line indices of the block after the next one's maxima
-        {                                      // block 0: its maxima were written in order by order_kernel
-            const float* hm = a.head_m + ((int64_t)l * a.BH + bh) * WALK_BLK;
-#pragma unroll
-            for (int e = 0; e < WALK_EB; ++e) { const int i = WALK_EB * lane + e; const float t = hm[i < n ? i : n - 1]; m[e] = i < n ? t : 0.f; }
-        }
-        walk_indices<WALK_EB>(i_l, WALK_BLK + WALK_EB * lane, n, ix);
+        const float* sm = a.sorted_m + ((int64_t)l * a.BH + bh) * a.kept;      // ... in order
+        struct Block { float m[WALK_EB]; };
         float acc = 0.f;                       // overlap sum behind the last entry summed so far
-        int b = 0;
-        int spins = 0;
-        while (walk_ld(&sync->done) == 0 && b < nblk) {
-            if (b > walk_ld(&sync->cur[l]) + WALK_NBLK - 1) {
-                __builtin_amdgcn_s_sleep(2);
-                if (++spins > spin_limit) { walk_st(&sync->err, 1); break; }
-                continue;
-            }
-            spins = 0;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            walk_maxima<WALK_EB>(m_l, ix, (b + 1) * WALK_BLK + WALK_EB * lane, n, mn);
-            walk_indices<WALK_EB>(i_l, (b + 2) * WALK_BLK + WALK_EB * lane, n, ix);
-            acc = chain_prefix<WALK_EB>(m, lane, acc, L.pre + (b & (WALK_NBLK - 1)) * WALK_BLK, L.pre + WALK_CAP, (b & (WALK_NBLK - 1)) == 0 ? RUN : 0);
+        auto add = [&](int b, const Block& f) {
+            acc = chain_prefix<WALK_EB>(f.m, lane, acc, L.pre + (b & (WALK_NBLK - 1)) * WALK_BLK, L.pre + WALK_CAP, (b & (WALK_NBLK - 1)) == 0 ? RUN : 0);
+            if (!informed) {                               // (else order_kernel has said so)
+                bool odd = false;
 #pragma unroll
-            for (int e = 0; e < WALK_EB; ++e) m[e] = mn[e];
+                for (int e = 0; e < WALK_EB; ++e) odd = odd || !(f.m[e] >= 0.f);
+                if (__ballot(odd) != 0ull && lane == 0) walk_st(&sync->falls[l], 1);
+            }
             if (b == nblk - 1 && lane == 0) sync->tot[l] = acc;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_wave_barrier();
-            ++b;
-            if (lane == 0) walk_st(&sync->summed_blk[l], b);
+        };
+        typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+        auto fetch_sorted = [&](int b, Block& f) {         // (past the end of the list, as above)
+            if (b >= nblk) return;
+            const float* at = sm + b * WALK_BLK + WALK_EB * lane;
+#pragma unroll
+            for (int e = 0; e < WALK_EB; e += 4) {
+                const f32x4u v = *reinterpret_cast<const f32x4u*>(at + e);
+                f.m[e] = v.x; f.m[e + 1] = v.y; f.m[e + 2] = v.z; f.m[e + 3] = v.w;
+            }
+        };
+        auto ends = [&](int b, Block& f) {                 // the list ends in this block
+            if ((b + 1) * WALK_BLK <= n) return;
+#pragma unroll
+            for (int e = 0; e < WALK_EB; ++e) f.m[e] = b * WALK_BLK + WALK_EB * lane + e < n ? f.m[e] : 0.f;
+        };
+        if constexpr (SORTED) {
+            Block even, odd;
+            fetch_sorted(0, even);
+            fetch_sorted(1, odd);
+            far = reach(l, nullptr);
+            __syncthreads();
+            stage_blocks(&sync->cur[l], &sync->need[l], &sync->summed_blk[l], [&](int b) { ends(b, even); add(b, even); fetch_sorted(b + 2, even); }, [&](int b) { ends(b, odd); add(b, odd); fetch_sorted(b + 2, odd); });
+        } else {
+            Block f, g;
+            int32_t ix[WALK_EB];               // line indices of the block after the next one's maxima
+            fetch_sorted(0, f);
+            ends(0, f);
+            walk_indices<WALK_EB>(i_l, WALK_BLK + WALK_EB * lane, n, ix);
+            __syncthreads();
+            auto block = [&](int b) {
+                walk_maxima<WALK_EB>(m_l, ix, (b + 1) * WALK_BLK + WALK_EB * lane, n, g.m);
+                walk_indices<WALK_EB>(i_l, (b + 2) * WALK_BLK + WALK_EB * lane, n, ix);
+                add(b, f);
+                f = g;
+            };
+            stage_blocks(&sync->cur[l], &sync->need[l], &sync->summed_blk[l], block, block);
         }
         return;
     }
@@ -1050,8 +1294,9 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
         const float target = a.alpha * a.total[bh];
         float sum = 0.f;
         int cnt_s = 0, cnt_v = 0;              // lines taken from each list
+        __syncthreads();
         int k = 0;                             // runs summed
-        bool failed = false, all = false;
+        bool failed = false, all = false, open = false;
         while (sum < target) {
             bool have = false;
             int spins = 0;
@@ -1060,6 +1305,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
                 if (walk_ld(&sync->decided)) {                       // stored after the last run was published
                     have = walk_ld(&sync->runs) > k;
                     failed = !have && walk_ld(&sync->err) != 0;
+                    open = !have && walk_ld(&sync->cut) != 0;
                     break;
                 }
                 if (++spins > spin_limit || walk_ld(&sync->err)) { failed = true; break; }
@@ -1068,25 +1314,35 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             if (!have) break;                  // both lists were used up (or a wait ran into its bound)
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
             const Run& R = ring[k & (WALK_RING - 1)];
-            const int which = __builtin_amdgcn_readfirstlane(R.which);
-            const int limit = __builtin_amdgcn_readfirstlane(R.limit);
-            const int last = __builtin_amdgcn_readfirstlane(R.last);
-            float g[E];
-#pragma unroll
-            for (int e = 0; e < E; e += 2) {
-                const float2 t = *reinterpret_cast<const float2*>(&R.g[E * lane + e]);
-                g[e] = E * lane + e < limit ? t.x : 0.f; g[e + 1] = E * lane + e + 1 < limit ? t.y : 0.f;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // the slot may be written again
-            ++k;
-            if (lane == 0) walk_st(&sync->summed, k);
+            const int4 about = *reinterpret_cast<const int4*>(&R.which);
+            const int which = __builtin_amdgcn_readfirstlane(about.x), limit = __builtin_amdgcn_readfirstlane(about.y), last = __builtin_amdgcn_readfirstlane(about.z);
             // pick by pick, as the loop of the definition adds them; it stops after the pick that reaches the target
             // (one addition after the other took 3900 cycles a run)
-            const int taken = chain_until<E>(g, lane, limit, target, sum);
+            int taken = 0;
+            auto add = [&](auto ENTRIES) {
+                constexpr int N = decltype(ENTRIES)::value;
+                float g[N];
+                const float* at = &R.g[N * lane + 2 * (N * lane / 16)];
+#pragma unroll
+                for (int e = 0; e < N; e += 2) {
+                    const float2 t = *reinterpret_cast<const float2*>(at + e);
+                    g[e] = t.x; g[e + 1] = t.y;
+                }
+                if (N != E || last != RUN_WHOLE) {
+#pragma unroll
+                    for (int e = 0; e < N; ++e) g[e] = N * lane + e < limit ? g[e] : 0.f;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");         // the slot may be written again
+                ++k;
+                if (lane == 0) walk_st(&sync->summed, k);
+                if (N == E && last == RUN_WHOLE && chain_all<N, true>(g, target, sum)) taken = limit;
+                else taken = chain_until<N>(g, lane, limit, target, sum);
+            };
+            if (E > WALK_NARROW && limit <= 64 * WALK_NARROW) add(std::integral_constant<int, WALK_NARROW>{}); else add(std::integral_constant<int, E>{});
             const bool reached = !(sum < target);
             cnt_s += which == 0 ? taken : 0;
             cnt_v += which == 0 ? 0 : taken;
-            if (!reached && last) { all = true; break; }  // the pick after the last one has no positive gain
+            if (!reached && last == 1) { all = true; break; }  // the pick after the last one has no positive gain
         }
         if (lane == 0) {
             walk_st(&sync->stop, 1);
@@ -1096,6 +1352,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             // status word tells the caller.
             sync->cnt_s = (failed || all) ? n : cnt_s;
             sync->cnt_v = (failed || all) ? n : cnt_v;
+            sync->open = open ? 1 : 0;
             if (failed) atomicOr(a.status, STAT_WALK_TIMEOUT);
             if (a.accounted) a.accounted[bh] = sum;
         }
@@ -1108,36 +1365,110 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
     int blk_s = 0, blk_v = 0;                  // list would be kept in scratch memory); block each head is in
     int have_s = 0, have_v = 0;                // blocks of each list known to be resident (staged and summed)
     int published = 0;                         // runs handed to the summing wave
-    bool failed = false;
-
+    int ended = 0;                             // OVER: the sum has reached the target, FAILED: a wait has run into its bound
+    constexpr int OVER = 1, FAILED = 2, CUT = 3;           // CUT: a head has come to where its list is no longer in order
+    int need_s = 2, need_v = 2;                // blocks whose prefix sums have been asked for
+    int full = 1;                              // the last run had as many picks as were looked at
+    int column = 0;                            // it ended where the next pick is a column: no need to see that again
+    int falls_s = 0, falls_v = 0;
+    const int far_s = reach(0, &falls_s), far_v = reach(1, &falls_v);
     // until the head's block and the one after it (the first `want` blocks of list l) are resident
-    auto wait_blocks = [&](int l, int want) {
+    auto wait_blocks = [&](int l, int want, bool sums = true) __attribute__((always_inline)) {
         int spins = 0, have;
         for (;;) {
-            const int st = walk_ld(&sync->staged[l]), su = walk_ld(&sync->summed_blk[l]);
+            const int st = walk_ld(&sync->staged[l]), su = sums ? walk_ld(&sync->summed_blk[l]) : st;
             have = st < su ? st : su;
             if (have >= want) break;
+            if (walk_ld(&sync->stop)) { ended = OVER; break; }
             __builtin_amdgcn_s_sleep(1);
-            if (++spins > spin_limit || walk_ld(&sync->err)) { failed = true; break; }
+            if (++spins > spin_limit || walk_ld(&sync->err)) { ended = FAILED; break; }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        return have;
+        return __builtin_amdgcn_readfirstlane(have);
     };
 
+    auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };      // (what the compiler does not see to be: its branches then go by scalar conditions)
     auto lane0 = [](float x) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x))); };
     // blocks a view at head h reads: through the block of entry h + RUN - 1, and pre[h] itself
-    auto blocks_for = [&](int h) {
-        const int want = (h + RUN - 1) / WALK_BLK + 1;
-        return want < nblk ? want : nblk;
+    auto blocks_for = [&](int h, int far) {
+        const int want = (h + RUN - 1) / WALK_BLK + 1, all = (far + WALK_BLK - 1) / WALK_BLK;
+        return want < all ? want : all;
     };
-    have_s = wait_blocks(0, blocks_for(0));
-    have_v = wait_blocks(1, blocks_for(0));
+    __syncthreads();
+    have_s = wait_blocks(0, blocks_for(0, far_s));
+    have_v = wait_blocks(1, blocks_for(0, far_v));
+    // the last head whose view is resident, given the resident blocks (of a list that is all there and in order: any)
+    auto good = [&](int have, int far) {
+        if (have * WALK_BLK >= far) return far < n ? far - 1 : 0x7FFFFFFF;
+        return have * WALK_BLK - RUN;
+    };
+    int good_s = good(have_s, far_s), good_v = good(have_v, far_v);
+    // A free slot of the ring: published runs less runs taken out (one read with whether the walk is over, which ends the waiting as well)
+    auto slot_free = [&]() __attribute__((always_inline)) {
+        int spins = 0;
+        for (;;) {
+            const unsigned long long ss = __atomic_load_n(static_cast<const unsigned long long*>(__builtin_assume_aligned(&sync->summed, 8)), __ATOMIC_RELAXED);
+            if (__builtin_amdgcn_readfirstlane((int)(ss >> 32))) { ended = OVER; return false; }
+            if (published - __builtin_amdgcn_readfirstlane((int)ss) < WALK_RING) break;
+            __builtin_amdgcn_s_sleep(1);
+            if (++spins > spin_limit || walk_ld(&sync->err)) { ended = FAILED; return false; }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        return true;
+    };
+    auto hand_over = [&](Run& R, int which, int limit, int last) __attribute__((always_inline)) {
+        if (lane == 0) { R.which = which; R.limit = limit; R.last = last; }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        ++published;
+        if (lane == 0) walk_st(&sync->runs, published);
+    };
+    // Runs of RUN picks (at the list's end, of what is left) from list l, whose head is at h, without a look at each, where nothing can come between: the head adds something, the other list's head
+    // does not, and adds the less the more lines of this list are taken; the overlap of the other list's lines with these is `ol` throughout.  As long as the last
+    // of RUN picks adds something, mine * cost > 0 >= other * cost for all of them, since costs are 1 or more.  (Lines come in descending order, so that no gain
+    // between is less than the last, nor a NaN; the prefix sums rise where all maxima are 0 or more.)  So the prefix sums are not needed meanwhile (informed: not
+    // even to know that they rise).  Returns the head behind the runs; `have`: the list's blocks that are known to be there.
+    auto quick = [&](int l, int h, float ol, int have, int falls, int far) __attribute__((always_inline)) -> int {
+        const List& L = lists[l];
+        int blk = h / WALK_BLK;
+        while (h < far && !falls) {
+            if (have < blocks_for(h, far)) {
+                if (!informed && lane == 0) walk_st(&sync->need[l], blocks_for(h, far) + 1);
+                have = wait_blocks(l, blocks_for(h, far), !informed);
+                if (ended) break;
+            }
+            const int at = (h & (WALK_CAP - 1)) + lane, picks = far - h < RUN ? far - h : RUN;
+            float gain[E];
+#pragma unroll
+            for (int e = 0; e < E; ++e) gain[e] = __fsub_rn(L.cw[at + 64 * e], ol);
+            if (!informed) falls = walk_ld(&sync->falls[l]);
+            float last = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, gain[E - 1]), 63));
+            if (picks < RUN) last = __fsub_rn(lane0(L.cw[(h & (WALK_CAP - 1)) + picks - 1]), ol);
+            if (uniform(falls || !(last > 0.f))) break;
+            if (!slot_free()) break;
+            Run& R = ring[published & (WALK_RING - 1)];
+#pragma unroll
+            for (int e = 0; e < E; ++e) R.g[72 * e + lane + 2 * (lane / 16)] = gain[e];
+            hand_over(R, l, picks, picks < RUN ? 0 : RUN_WHOLE);
+            h = uniform(h + picks);
+            if (h < n && h / WALK_BLK != blk) {            // done reading the blocks left behind
+                blk = h / WALK_BLK;
+                if (lane == 0) walk_st(&sync->cur[l], blk);
+            }
+        }
+        return h;
+    };
 
+    // the prefix sums of the first `want` blocks of list l are wanted (those of one more than the views meet, so that they are there in time)
+    auto need_more = [&](int l, int want, int need) __attribute__((always_inline)) -> int {
+        if (want <= need) return need;
+        if (lane == 0) walk_st(&sync->need[l], want);
+        return want;
+    };
     // Decides run after run with N entries a lane, until the walk is over (false) or runs of another length would suit N better.
-    auto decide = [&](auto ENTRIES) -> bool {
+    auto decide = [&](auto ENTRIES) __attribute__((always_inline)) -> bool {
         constexpr int N = decltype(ENTRIES)::value;
         using View = WalkView<N>;
-        auto view = [&](int l, int h) {
+        auto view = [&](int l, int h) __attribute__((always_inline)) {
             const List& L = lists[l];
             View r;
             const int at = (h & (WALK_CAP - 1)) + lane;
@@ -1148,7 +1479,13 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
             return r;                                                      // sits right behind its last line
         };
         View S = view(0, is), V = view(1, iv);
-        while (!failed) {
+        bool old_s = false, old_v = false;     // the list's head has moved on, or its blocks were not all there
+        auto head = [&](int l, int h, View& r) __attribute__((always_inline)) {
+            const int at = h & (WALK_CAP - 1);
+            r.w0 = h < n ? lane0(lists[l].cw[at]) : 0.f;
+            r.ol0 = h < n ? lane0(lists[l].pre[at]) : lane0(sync->tot[l]);
+        };
+        while (!ended) {
             if (is >= n && iv >= n) break;
             // a head that has entered a new block frees the blocks behind it; a view that reaches into a block not
             // known to be resident yet is read again once that block is
@@ -1162,22 +1499,53 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 if (lane == 0) walk_st(&sync->cur[1], blk_v);
             }
-            if (is < n && have_s < blocks_for(is)) {
-                have_s = wait_blocks(0, blocks_for(is));
-                if (failed) break;
-                S = view(0, is);
+            if (is > good_s) {
+                if (is >= far_s && is < n) { ended = CUT; break; }
+                if (have_s < blocks_for(is, far_s)) {      // (an exhausted list: all of them, for its whole overlap sum)
+                    need_s = need_more(0, blocks_for(is, far_s) + 1, need_s);
+                    have_s = wait_blocks(0, blocks_for(is, far_s));
+                    if (ended) break;
+                    old_s = true;
+                }
+                good_s = good(have_s, far_s);
             }
-            if (iv < n && have_v < blocks_for(iv)) {
-                have_v = wait_blocks(1, blocks_for(iv));
-                if (failed) break;
-                V = view(1, iv);
+            if (iv > good_v) {
+                if (iv >= far_v && iv < n) { ended = CUT; break; }
+                if (have_v < blocks_for(iv, far_v)) {
+                    need_v = need_more(1, blocks_for(iv, far_v) + 1, need_v);
+                    have_v = wait_blocks(1, blocks_for(iv, far_v));
+                    if (ended) break;
+                    old_v = true;
+                }
+                good_v = good(have_v, far_v);
             }
+            // long runs (after one that took all it could: where picks go back and forth the look would cost a tenth)
+            if (full) {
+                if (old_s) head(0, is, S);
+                if (old_v) head(1, iv, V);
+                const float ds = __fsub_rn(S.w0, V.ol0), dv = __fsub_rn(V.w0, S.ol0);
+                const int to_s = uniform(is < n && (iv >= n || dv <= 0.f) && ds > 0.f), to_v = uniform(iv < n && (is >= n || ds <= 0.f) && dv > 0.f);
+                if (to_s | to_v) {
+                    const int from = to_s ? is : iv, to = quick(to_s ? 0 : 1, from, to_s ? V.ol0 : S.ol0, to_s ? have_s : have_v, to_s ? falls_s : falls_v, to_s ? far_s : far_v);
+                    if (ended) break;
+                    // (no choice between two variables to write to: they would lie in scratch memory)
+                    if (to != from) {
+                        is = to_s ? to : is; iv = to_s ? iv : to;
+                        blk_s = to_s && to < n ? to / WALK_BLK : blk_s; blk_v = to_s || to >= n ? blk_v : to / WALK_BLK;
+                        old_s = old_s || to_s; old_v = old_v || to_v;
+                        full = 0;
+                        continue;
+                    }
+                }
+            }
+            if (old_s) { S = view(0, is); old_s = false; }
+            if (old_v) { V = view(1, iv); old_v = false; }
             // entry e of lane l: the decision if the walk has taken 64 e + l more slashes (iv frozen)
             float gain[N];
             bool turn[N];                     // the pick goes to the other list
             const float fs = (float)is, fv = (float)iv;
-            int run = 0, which = 0;
-            if (is < n) {
+            int run = 0, which = 0, turns = 0;
+            if (is < n && !column) {
 #pragma unroll
                 for (int e = 0; e < N; ++e) {
                     const float ds = __fsub_rn(S.cw[e], V.ol0), dv = __fsub_rn(V.w0, S.pre[e]);
@@ -1186,7 +1554,8 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
                     gain[e] = ds;
                 }
                 run = iv < n ? walk_first(turn) : 64 * N;
-                run = run < n - is ? run : n - is;
+                turns = run < 64 * N && run < far_s - is;
+                run = uniform(run < far_s - is ? run : far_s - is);
             }
             if (run == 0) {
                 // the head pick is a vertical; entry e of lane l: the decision if 64 e + l more verticals are taken (is frozen)
@@ -1199,7 +1568,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
                     gain[e] = dv;
                 }
                 run = is < n ? walk_first(turn) : 64 * N;
-                run = run < n - iv ? run : n - iv;
+                run = uniform(run < far_v - iv ? run : far_v - iv);
             }
             if (run == 0) break;                   // cannot happen (entry 0 of lane 0 repeats the head's test); never spin
             // picks 0 .. run-1 come from list `which`; the walk ends early at a pick with no positive gain left
@@ -1213,53 +1582,43 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, unsigned char* wa
                     dead[e] = !(gain[e] > 0.f) && (!has || !((which == 0 ? __fsub_rn(V.w0, S.pre[e]) : __fsub_rn(S.w0, V.pre[e])) > 0.f));
                 stop_dead = walk_first(dead);
             }
-            const int limit = run < stop_dead ? run : stop_dead;
+            const int limit = uniform(run < stop_dead ? run : stop_dead);
+            full = limit == 64 * N;
+            column = which == 0 && turns;
             // the list's view after the run (read again above if it reaches into a block that is not resident yet)
             const View nxt = view(which, (which == 0 ? is : iv) + limit);
             // hand the run over: a free slot of the ring, the gains, then the count of published runs
-            bool stopped = false;
-            int spins = 0;
-            for (;;) {                             // one read: runs taken out of the ring, and whether the walk is over
-                const unsigned long long ss = __atomic_load_n(static_cast<const unsigned long long*>(__builtin_assume_aligned(&sync->summed, 8)), __ATOMIC_RELAXED);
-                if (__builtin_amdgcn_readfirstlane((int)(ss >> 32))) { stopped = true; break; }
-                if (published - __builtin_amdgcn_readfirstlane((int)ss) < WALK_RING) break;
-                __builtin_amdgcn_s_sleep(1);
-                if (++spins > spin_limit || walk_ld(&sync->err)) { failed = true; break; }
-            }
-            if (stopped || failed) break;
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            if (!slot_free()) break;
             Run& R = ring[published & (WALK_RING - 1)];
 #pragma unroll
-            for (int e = 0; e < N; ++e) R.g[64 * e + lane] = gain[e];
-            if (lane == 0) { R.which = which; R.limit = limit; R.last = stop_dead < run ? 1 : 0; }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            ++published;
-            if (lane == 0) walk_st(&sync->runs, published);
+            for (int e = 0; e < N; ++e) R.g[72 * e + lane + 2 * (lane / 16)] = gain[e];
+            hand_over(R, which, limit, stop_dead < run ? 1 : 0);
             if (stop_dead < run) break;            // nothing after this run can add to the sum
-            if (which == 0) { is += limit; S = nxt; } else { iv += limit; V = nxt; }
-            if (E == 16 && (N == E ? limit <= 32 * WALK_NARROW : limit == 64 * WALK_NARROW)) return true;
+            if (which == 0) { is = uniform(is + limit); S = nxt; } else { iv = uniform(iv + limit); V = nxt; }
+            if (E > WALK_NARROW && (N == E ? limit <= 32 * WALK_NARROW : limit == 64 * WALK_NARROW)) return true;
         }
         return false;
     };
-    bool wide = true;
-    while (wide ? decide(std::integral_constant<int, E>{}) : decide(std::integral_constant<int, (E == 16 ? WALK_NARROW : E)>{})) wide = !wide;
+    bool wide = false;
+    while (wide ? decide(std::integral_constant<int, E>{}) : decide(std::integral_constant<int, WALK_NARROW>{})) wide = !wide;
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (lane == 0) {
-        if (failed) walk_st(&sync->err, 1);
+        if (ended == FAILED) walk_st(&sync->err, 1);
+        if (ended == CUT) walk_st(&sync->cut, 1);
         walk_st(&sync->decided, 1);
         walk_st(&sync->done, 1);
     }
 }
 
 // grid (BH); dynamic LDS: WALK_LDS_BYTES<E>
-template <int E>
+template <int E, bool SORTED>
 __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
     extern __shared__ __align__(16) unsigned char walk_lds[];
-    walk_head<E>(a, walk_lds);
+    walk_head<E, SORTED>(a, blockIdx.x, walk_lds);
     __syncthreads();
     const WalkSync* sync = reinterpret_cast<const WalkSync*>(walk_lds + 2 * sizeof(WalkList<E>) + WALK_RING * sizeof(WalkRun<E>));
     const int bh = blockIdx.x, cnt_s = sync->cnt_s, cnt_v = sync->cnt_v;
-    if (threadIdx.x == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; }
+    if (threadIdx.x == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; if (a.open) { a.open[bh] = sync->open; a.open[a.BH + bh] = 0; } }
     if (a.n > EMIT_LINES) return;
     emit_both<WALK_THREADS>(a, bh, cnt_s, cnt_v, reinterpret_cast<uint32_t*>(walk_lds));      // (not where `sync` lies)
 }
@@ -1368,9 +1727,8 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
         const int i = l.base + tid < n ? l.base + tid : n - 1;
         const int32_t x = a.sidx[((int64_t)l.id * a.BH + bh) * a.n + i];
         lines[l.id][tid] = x;
-        weights[l.id][tid] = l.base == 0 ? a.head_w[((int64_t)l.id * a.BH + bh) * WALK_BLK + (tid < n ? tid : n - 1)] : ((l.id == 0 ? a.slash : a.vert) + (int64_t)bh * a.n)[x];
+        weights[l.id][tid] = i < a.kept ? a.sorted_w[((int64_t)l.id * a.BH + bh) * a.kept + i] : ((l.id == 0 ? a.slash : a.vert) + (int64_t)bh * a.n)[x];
     };
-    static_assert(WALK_BLK == XW_THREADS, "the first block's weights are there in order");
     List X = {0, 0, 0}, O = {1, 0, 0};         // the list whose lines are the candidates, and the other one
     load(X);
     load(O);
@@ -1563,37 +1921,72 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
 
 // ---- chosen prefix -> ascending index list --------------------------------------------------------
 // grid (2, BH); dynamic LDS: bitmap of n bits, lines of up to 1024 of its words.
+// A head whose walk came to where a list is no longer in order (a.open) is walked again here, once its workgroups (with few heads more than the two that a
+// head has anyhow, up to eight; of other heads they leave at once) have put the missing ranges in order: by the one of them that is done last.  ls_select of heads that all need it, us,
+// everything in order beforehand / the missing ranges by one workgroup / by eight: 8 heads of 12347 lines 56 / 198 / 129, 32 of 32768 97 / 314 / 270, 16 of 131072 368 / 1610 / 610.
+constexpr int REDO_CAP = 5120, REDO_MORE = 6;
+constexpr size_t REDO_LDS_BYTES = order_lds_bytes(4, REDO_CAP) > WALK_LDS_BYTES<8> ? order_lds_bytes(4, REDO_CAP) : WALK_LDS_BYTES<8>;
 __global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
-    extern __shared__ uint32_t bm[];
+    extern __shared__ __align__(16) uint32_t bm[];
     __shared__ uint32_t wsum[16];
-    const int list = blockIdx.x, bh = blockIdx.y, tid = threadIdx.x;
+    const int bh = blockIdx.y, tid = threadIdx.x;
     const int64_t n = a.n;
     const int words = (int)((n + 31) / 32);
-    const int64_t seg = ((int64_t)list * a.BH + bh) * n;
-    const int32_t* sorted_idx = a.sidx + seg;
-    const int cnt = list == 0 ? a.s_cnt[bh] : a.v_cnt[bh];
-    int32_t* out = list == 0 ? a.s_idx + (int64_t)bh * a.cap_s : a.v_idx + (int64_t)bh * a.cap_v;
-    const int cap = list == 0 ? a.cap_s : a.cap_v;
-    if (tid == 0 && cnt > cap) atomicOr(a.status, list == 0 ? STAT_S_TRUNCATED : STAT_V_TRUNCATED);
-    if (cnt >= n) {                                        // every line was taken: the list is 0 .. n-1
-        for (int64_t i = tid; i < n && i < cap; i += 1024) out[i] = (int32_t)i;
+    auto emit = [&](int list, int cnt) {
+        const int32_t* sorted_idx = a.sidx + ((int64_t)list * a.BH + bh) * n;
+        int32_t* out = list == 0 ? a.s_idx + (int64_t)bh * a.cap_s : a.v_idx + (int64_t)bh * a.cap_v;
+        const int cap = list == 0 ? a.cap_s : a.cap_v;
+        if (tid == 0 && cnt > cap) atomicOr(a.status, list == 0 ? STAT_S_TRUNCATED : STAT_V_TRUNCATED);
+        if (cnt >= n) {                                    // every line was taken: the list is 0 .. n-1
+            for (int64_t i = tid; i < n && i < cap; i += 1024) out[i] = (int32_t)i;
+            return;
+        }
+        for (int i = tid; i < words; i += 1024) bm[i] = 0u;
+        __syncthreads();
+        for (int i0 = tid; i0 < cnt; i0 += 8 * 1024) {     // eight independent loads in flight per thread
+            int32_t x8[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) { const int i = i0 + j * 1024; x8[j] = i < cnt ? sorted_idx[i] : -1; }
+#pragma unroll
+            for (int j = 0; j < 8; ++j) if (x8[j] >= 0) atomicOr(&bm[x8[j] >> 5], 1u << (x8[j] & 31));
+        }
+        __syncthreads();
+        uint16_t* stage = reinterpret_cast<uint16_t*>(bm + words);
+        uint32_t at = 0u;
+        for (int w0 = 0; w0 < words; w0 += PUT_WORDS) {
+            if (w0 > 0) __syncthreads();                   // the last lines are out of `stage`
+            at += put_lines<1024>(bm + w0, words - w0 < PUT_WORDS ? words - w0 : PUT_WORDS, 32 * w0, stage, wsum, 0, out, at, cap, tid);
+        }
+    };
+    if (!a.open || !__builtin_amdgcn_readfirstlane(a.open[bh])) {
+        if (blockIdx.x < 2) emit(blockIdx.x, blockIdx.x == 0 ? a.s_cnt[bh] : a.v_cnt[bh]);
         return;
     }
-    for (int i = tid; i < words; i += 1024) bm[i] = 0u;
-    __syncthreads();
-    for (int i0 = tid; i0 < cnt; i0 += 8 * 1024) {          // eight independent loads in flight per thread
-        int32_t x8[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { const int i = i0 + j * 1024; x8[j] = i < cnt ? sorted_idx[i] : -1; }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) if (x8[j] >= 0) atomicOr(&bm[x8[j] >> 5], 1u << (x8[j] & 31));
+    __shared__ OrderSync sync;
+    __shared__ int last;
+    unsigned char* lds = reinterpret_cast<unsigned char*>(bm);
+    for (int r = blockIdx.x; r < 2 * a.ranges; r += (int)gridDim.x) {
+        const int l = r >= a.ranges ? 1 : 0, b = r - l * a.ranges;
+        if (__builtin_amdgcn_readfirstlane(a.info[((int64_t)l * a.BH + bh) * SELECT_RANGES + b]) >= 0) continue;
+        (void)order_range<4, false, false>(a, l, bh, b, a.ranges, a.ranges, REDO_CAP, 0.f, lds, sync);
+        if (tid == 0) a.info[((int64_t)l * a.BH + bh) * SELECT_RANGES + b] = 0;
+        __syncthreads();
     }
+    __threadfence();                                       // (the others' L2 may be another: what was written goes to memory, and comes from there)
     __syncthreads();
-    uint16_t* stage = reinterpret_cast<uint16_t*>(bm + words);
-    uint32_t at = 0u;
-    for (int w0 = 0; w0 < words; w0 += PUT_WORDS) {
-        if (w0 > 0) __syncthreads();                       // the last lines are out of `stage`
-        at += put_lines<1024>(bm + w0, words - w0 < PUT_WORDS ? words - w0 : PUT_WORDS, 32 * w0, stage, wsum, 0, out, at, cap, tid);
+    if (tid == 0) last = count_shared(reinterpret_cast<uint32_t*>(a.open) + a.BH + bh) + 1u == gridDim.x;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+    __threadfence();
+    if (tid < WALK_THREADS) walk_head<8, true>(a, bh, lds); else __syncthreads();
+    __syncthreads();
+    const WalkSync* walk = reinterpret_cast<const WalkSync*>(lds + 2 * sizeof(WalkList<8>) + WALK_RING * sizeof(WalkRun<8>));
+    const int cnt_s = walk->cnt_s, cnt_v = walk->cnt_v;
+    __syncthreads();
+    if (tid == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; }
+    for (int list = 0; list < 2; ++list) {
+        emit(list, list == 0 ? cnt_s : cnt_v);
+        __syncthreads();
     }
 }
 
@@ -1970,58 +2363,74 @@ __global__ __launch_bounds__(GATHER_THREADS) void gather_rows_kernel(GatherArgs 
 }
 
 static void launch_emit(const SelectArgs& a, hipStream_t st) {
-    if (a.n > EMIT_LINES) hipLaunchKernelGGL(emit_kernel, dim3(2, a.BH), dim3(1024), (size_t)((a.n + 31) / 32) * 4 + put_lines_bytes(a.n), st, a);
+    if (a.n <= EMIT_LINES) return;
+    const size_t bytes = (size_t)((a.n + 31) / 32) * 4 + put_lines_bytes(a.n);
+    const int more = 256 / a.BH - 2, wgs = a.open && more > 0 ? 2 + (more < REDO_MORE ? more : REDO_MORE) : 2;
+    hipLaunchKernelGGL(emit_kernel, dim3(wgs, a.BH), dim3(1024), a.open && REDO_LDS_BYTES > bytes ? REDO_LDS_BYTES : bytes, st, a);
 }
 // Ranges of 8192 lines, a fifth less than a workgroup takes (the samples miss by 4 % at most; beyond 65536 lines by more, and a halved
 // range counts again), and more of them, down to 512 lines, as long as there are compute units for one each: 8 heads of 8192 lines
 // 33.2 us in 16 ranges, 36.7 in one; 512 workgroups instead of 256 take turns: 32 heads of 32768 lines 63.0 -> 75.5, of 8192 36.6 -> 45.8.
 // One range up to 4096 lines saves the look for its bounds: 32 heads of 4096 lines 25.7 -> 24.1, of 8192 36.6 -> 38.5.
-static hipError_t sort_lines(const SelectArgs& a, hipStream_t st) {
-    int64_t nb = 1;
+// lazy: the last ranges are put in order only where a walk may come to them.  A workgroup then has two ranges of half the length, far apart, as long as they have 1024 lines (up to
+// ORDER_WIDE): 32 heads of 32768 lines 33.0 -> 25.5 us, 12347 18.7 -> 17.0; of lists whose lines are all needed, 16500 of 32768 each, the whole ls_select 117 -> 122.
+static hipError_t sort_lines(SelectArgs& a, bool lazy, hipStream_t st) {
+    int64_t wgs = 1;
     if (a.n > ORDER_ONE) {
-        nb = a.n > ORDER_WIDE ? (a.n + 6553) / 6554 : (a.n + 8191) / 8192;
+        wgs = a.n > ORDER_WIDE ? (a.n + 6553) / 6554 : (a.n + 8191) / 8192;
         const int64_t fill = 256 / (2 * (int64_t)a.BH), most = (a.n + 511) / 512;
         const int64_t more = fill < most ? fill : most;
-        if (nb < more) nb = more;
+        if (wgs < more) wgs = more;
     }
+    lazy = lazy && wgs > 1 && a.open && a.n >= LAZY_LINES;
+    const int64_t nb = lazy && a.n <= ORDER_WIDE && 2 * wgs <= SELECT_RANGES && a.n >= 2048 * wgs ? 2 * wgs : wgs;
     int64_t chunks = nb == 1 ? (a.n + 1023) / 1024 : (a.n * 5 / (4 * nb) + 256 + 1023) / 1024;
     if (chunks > ORDER_CHUNKS || a.n > ORDER_WIDE) chunks = ORDER_CHUNKS;
     const int cap = (int)chunks * 1024;
-    const dim3 grid(2 * (unsigned)a.BH, (unsigned)nb);
-    auto launch = [&](auto kernel, int pt) { hipLaunchKernelGGL(kernel, grid, dim3(ORDER_THREADS), order_lds_bytes(pt, cap), st, a, (int)nb, cap); };
-    if (a.n <= 1024) launch(&order_kernel<1, true>, 1);
-    else if (a.n <= ORDER_ONE) launch(&order_kernel<4, true>, 4);
-    else if (cap <= 4096) launch(&order_kernel<4, false>, 4);
-    else launch(&order_kernel<8, false>, 8);
+    a.ranges = (int)nb;
+    if (!lazy) a.open = nullptr;
+    if (nb == 1) a.odd = nullptr;                          // (the walk's own look at the maxima comes as early)
+    const dim3 grid(2 * (unsigned)a.BH, (unsigned)wgs);
+    auto launch = [&](auto kernel, int pt) { hipLaunchKernelGGL(kernel, grid, dim3(ORDER_THREADS), order_lds_bytes(pt, cap), st, a, cap); };
+    if (a.n <= 1024) launch(&order_kernel<1, true, false>, 1);
+    else if (a.n <= ORDER_ONE) launch(&order_kernel<4, true, false>, 4);
+    else if (cap <= 6144) { if (lazy) launch(&order_kernel<4, false, true>, 4); else launch(&order_kernel<4, false, false>, 4); }
+    else { if (lazy) launch(&order_kernel<8, false, true>, 8); else launch(&order_kernel<8, false, false>, 8); }
     return hipGetLastError();
 }
 
 hipError_t init_select_kernels() {
     hipError_t e;
-    if ((e = allow_full_lds(&order_kernel<1, true>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&order_kernel<4, true>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&order_kernel<4, false>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&order_kernel<8, false>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&walk_kernel<4>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&walk_kernel<8>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&walk_kernel<16>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<1, true, false>)) != hipSuccess || (e = allow_full_lds(&order_kernel<4, true, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<4, false, false>)) != hipSuccess || (e = allow_full_lds(&order_kernel<4, false, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<8, false, false>)) != hipSuccess || (e = allow_full_lds(&order_kernel<8, false, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&walk_kernel<4, true>)) != hipSuccess || (e = allow_full_lds(&walk_kernel<4, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&walk_kernel<8, true>)) != hipSuccess || (e = allow_full_lds(&walk_kernel<8, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&walk_kernel<16, true>)) != hipSuccess || (e = allow_full_lds(&walk_kernel<16, false>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_exact_kernel)) != hipSuccess) return e;
     if ((e = allow_full_lds(&merge_lines_kernel)) != hipSuccess) return e;
     return allow_full_lds(&emit_kernel);
 }
 
-hipError_t run_select(const SelectArgs& a, hipStream_t st) {
-    hipError_t e = sort_lines(a, st);
+hipError_t run_select(const SelectArgs& a0, hipStream_t st) {
+    SelectArgs a = a0;
+    hipError_t e = sort_lines(a, a.accounted == nullptr, st);
     if (e != hipSuccess) return e;
-    if (a.n <= WALK_SHORT) hipLaunchKernelGGL(walk_kernel<4>, dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES<4>, st, a);
-    else if (a.n < WALK_LONG) hipLaunchKernelGGL(walk_kernel<8>, dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES<8>, st, a);
-    else hipLaunchKernelGGL(walk_kernel<16>, dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES<16>, st, a);
+    auto walk = [&](auto E) {
+        constexpr int N = decltype(E)::value;
+        if (a.sorted) hipLaunchKernelGGL((walk_kernel<N, true>), dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES<N>, st, a);
+        else hipLaunchKernelGGL((walk_kernel<N, false>), dim3(a.BH), dim3(WALK_THREADS), WALK_LDS_BYTES<N>, st, a);
+    };
+    if (a.n <= WALK_SHORT) walk(std::integral_constant<int, 4>{});
+    else if (a.n < WALK_LONG) walk(std::integral_constant<int, 8>{});
+    else walk(std::integral_constant<int, 16>{});
     launch_emit(a, st);
     return hipGetLastError();
 }
 
-hipError_t run_select_exact(const SelectArgs& a, hipStream_t st) {
-    hipError_t e = sort_lines(a, st);
+hipError_t run_select_exact(const SelectArgs& a0, hipStream_t st) {
+    SelectArgs a = a0;
+    hipError_t e = sort_lines(a, false, st);
     if (e != hipSuccess) return e;
     const size_t smem = (size_t)((a.n + 31) / 32) * 4;
     hipLaunchKernelGGL(walk_exact_kernel, dim3(a.BH), dim3(XW_THREADS), 2 * smem + (a.n <= EMIT_LINES ? 2 * put_lines_bytes(a.n) : 0), st, a);
