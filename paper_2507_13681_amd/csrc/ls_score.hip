@@ -579,6 +579,8 @@ __device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row,
 // grid (workgroups that share a KV head's key blocks, B*Hkv).  Bound by the reads of K.  A wave has its 32 keys of a block in registers and those of
 // the workgroup's next block on their way to its own stage; between blocks nobody waits for anybody.  Against a workgroup per block past which the chunks
 // come, a barrier each, us: 16384 entries, B 4, 128 rows a KV head 39 -> 31, 32768, B 2, d = 64 18.4 -> 13.8, 65536, 8 KV heads of 16 rows 26 -> 21.
+// Two chunks at once: B 4, 64 / 8 heads of 16384 entries, 16 rows 32.0 -> 30.2 us (134 MB: 4.4 TB/s), the whole ls_kv_compress 85.0 -> 83.4; 32768 entries, B 1, 52.8 -> 52.2.  (The products of one chunk beside
+// the probabilities of the one before, 193 registers: the same, the reads of K bound it.)
 // Four chunks of 32 rows: room for eight leaves a CU one workgroup at d = 128.  The whole ls_kv_compress, four / eight, us: 128 rows 73 / 82; 192 129 / 123, 256 120 / 124, 32768 entries, B 1, 81 / 82.  At d = 64
 // it leaves two, and more rows would gain: 192 99.6 / 79.2, 256 90.6 / 79.9, 32768 entries, B 1, 65 / 60.
 constexpr int RETAIN_CHUNKS = 4;
@@ -622,34 +624,59 @@ __device__ __forceinline__ void retain_stream(const ScoreArgs& a, unsigned char*
         const bool open = blk0 + SB - 1 <= n - a.w;        // every row sees every key
         float sum = 0.f;
         auto chunks = [&](auto OPEN) {
-            for (int c = 0; c < ch.count; ++c) {
-                f32x16 s;
-                Frag<T> qf[D / 16];
-                RT::frags(qf, qs + c * RT::BYTES, r32, g);
+            // N chunks at once: two, whose products do not wait for each other, in a pinned order (as many registers as two workgroups a CU leave: 163; one at a time 106)
+            auto some = [&](auto COUNT, int c0) {
+                constexpr int N = decltype(COUNT)::value, NS = D / 16, AHEAD = N == 1 ? NS : 2;
+                f32x16 s[N];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[r] = 0.f;
+                for (int i = 0; i < N; ++i)
 #pragma unroll
-                for (int cc = 0; cc < D / 16; ++cc) mma(s, qf[cc], kf[cc]);          // s[r] = <q_{8(r/4)+4g+r%4}, k_lane>
-                const int t0 = ch.at(c).t0;
-                float ps = 0.f;                            // of the chunk: one sum through all chunks costs precision (128 rows of 65536 keys, relative error 1.14e-7, so 0.81e-7)
+                    for (int r = 0; r < 16; ++r) s[i][r] = 0.f;
+                {
+                    Frag<T> qf[NS][N];
+                    auto load = [&](int cc, int i) { load_frag(qf[cc][i], qs + (c0 + i) * RT::BYTES + r32 * RT::RB + RT::FB * ((2 * cc + g) ^ (r32 & (RT::UPR - 1)))); };
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const int rq = 8 * q4 + 4 * g;
-                    const f32x4 sa = *reinterpret_cast<const f32x4*>(rst + 32 * c + rq), sb = *reinterpret_cast<const f32x4*>(rst + 32 * c + rq + 2);
-                    const float mm[4] = {sa.x, sa.z, sb.x, sb.z}, il[4] = {sa.y, sa.w, sb.y, sb.w};
+                    for (int cc = 0; cc < AHEAD; ++cc)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float p = fast_exp2(__builtin_fmaf(s[4 * q4 + e], a.scale_log2e, -mm[e]));
-                        if constexpr (decltype(OPEN)::value) ps = __builtin_fmaf(p, il[e], ps);
-                        else {
-                            int t = t0 + rq + e;
-                            if (ch.rgs == 0) t &= a.w - 1; // packed windows: w is a power of two
-                            ps += mykey <= n - a.w + t ? p * il[e] : 0.f;
+                        for (int i = 0; i < N; ++i) load(cc, i);
+                    if (N > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int cc = 0; cc < NS; ++cc) {
+#pragma unroll
+                        for (int i = 0; i < N; ++i) mma(s[i], qf[cc][i], kf[cc]);    // s[r] = <q_{8(r/4)+4g+r%4}, k_lane>
+                        if (cc + AHEAD < NS) {
+#pragma unroll
+                            for (int i = 0; i < N; ++i) load(cc + AHEAD, i);
                         }
+                        if (N > 1) __builtin_amdgcn_sched_barrier(0);
                     }
                 }
-                sum += ps;
-            }
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    const int c = c0 + i, t0 = ch.at(c).t0;
+                    float ps = 0.f;                        // of the chunk: one sum through all chunks costs precision (128 rows of 65536 keys, relative error 1.14e-7, so 0.81e-7)
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const int rq = 8 * q4 + 4 * g;
+                        const f32x4 sa = *reinterpret_cast<const f32x4*>(rst + 32 * c + rq), sb = *reinterpret_cast<const f32x4*>(rst + 32 * c + rq + 2);
+                        const float mm[4] = {sa.x, sa.z, sb.x, sb.z}, il[4] = {sa.y, sa.w, sb.y, sb.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float p = fast_exp2(__builtin_fmaf(s[i][4 * q4 + e], a.scale_log2e, -mm[e]));
+                            if constexpr (decltype(OPEN)::value) ps = __builtin_fmaf(p, il[e], ps);
+                            else {
+                                int t = t0 + rq + e;
+                                if (ch.rgs == 0) t &= a.w - 1; // packed windows: w is a power of two
+                                ps += mykey <= n - a.w + t ? p * il[e] : 0.f;
+                            }
+                        }
+                    }
+                    sum += ps;
+                }
+            };
+            int c = 0;
+            for (; c + 2 <= ch.count; c += 2) some(std::integral_constant<int, 2>{}, c);
+            if (c < ch.count) some(std::integral_constant<int, 1>{}, c);
         };
         if (open) chunks(std::true_type{}); else chunks(std::false_type{});
         sum = halves_sum(sum);
@@ -667,15 +694,15 @@ __device__ __forceinline__ void retain_stream(const ScoreArgs& a, unsigned char*
 // MODE 2: column sums only, summed over the G heads of the KV head (retention score)
 // MODE 3: the matrix A only
 // MODE 4: as 0; the block that is done last adds what it shares with its neighbours, and the total (joins)
-// Four workgroups per CU leave bf16 128 registers.  In MODE 0 and 4 what a row sees is arithmetic: with a table of the rows' limits in LDS, as for explicit
+// Four workgroups per CU leave bf16 128 registers (little data, and what stays in LDS, where the LDS leaves two or three: 256).  In MODE 0 and 4 what a row sees is arithmetic: with a table of the rows' limits in LDS, as for explicit
 // positions, ls_score took, us, 131072 keys 464 instead of 448, 16384, B 4, 64 heads, 267 / 248, 32768 88 / 82, 8192 37.5 / 35.2, 61 rows of 12347, half
 // of whose chunks have 29 rows, 51.5 / 47.9 (its reads beside the slab's, 13 more registers, four of them spilled).
 template <typename T, int D, int MODE, bool FOLD>
-__global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void lines_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? (MODE == 2 && FOLD ? 2 : 4) : 1)) void lines_kernel(ScoreArgs a) {
     using RT = RowTile<T, D>;
     constexpr bool LINES = MODE == 0 || MODE == 4;
     extern __shared__ __align__(16) unsigned char smem[];
-    if constexpr (MODE == 2 && Elem<T>::bytes == 2 && !FOLD) { if (a.retain) { retain_stream<D>(a, smem); return; } }
+    if constexpr (MODE == 2 && Elem<T>::bytes == 2 && FOLD) { if (a.retain) { retain_stream<D>(a, smem); return; } }
     unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
     float* slab = reinterpret_cast<float*>(smem);          // [SLAB_DIAGS][SLAB] A by diagonals (MODE 0) and
     unsigned char* qs = smem + (LINES ? SLAB_BYTES : 0);           // [2] chunks of queries
@@ -1156,7 +1183,7 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     } else {
         const int share = 512 / BK < 1 ? 1 : 512 / BK < a.nkb ? 512 / BK : a.nkb;      // (64 KB of LDS: two workgroups a CU)
         if constexpr (Elem<T>::bytes == 2) {
-            if (a.retain) hipLaunchKernelGGL((lines_kernel<T, D, 2, false>), dim3(share, BK), dim3(SCORE_THREADS), retain_lds<D>(), st, a);
+            if (a.retain) hipLaunchKernelGGL((lines_kernel<T, D, 2, true>), dim3(share, BK), dim3(SCORE_THREADS), retain_lds<D>(), st, a);
         }
         if (!a.retain) launch_lines<T, D, 2>(a, BK, st);
         return hipGetLastError();
