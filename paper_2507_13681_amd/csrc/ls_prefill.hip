@@ -336,7 +336,7 @@ __global__ __launch_bounds__(1024) void plan_kernel(PlanArgs a) {
 constexpr int64_t PIECES_TILES = 262144, PIECES_TILES_MOST = 524288, PIECES_SEEN = 204800;
 // fewest tiles on either side of a cut (a part costs its result written and read: the time of two bf16 tiles; one of fp32 takes four times as long)
 __host__ __device__ __forceinline__ int cut_tiles(uint32_t base) { return base == 32 ? 2 : 1; }
-__host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : work_cols(base); }    // the least of a piece where there are fewer items than workgroups: four bf16 tiles, one of fp32
+__host__ __device__ __forceinline__ uint32_t piece_work(uint32_t base) { return base == 32 ? 64 : WORK_TILE; }    // the most of a piece while there are workgroups left: four bf16 tiles, one of fp32
 
 struct Cut { int item, tile; };                            // a piece begins at this tile of this item
 // The cut `u` into an item of n1 contiguous and n2 packed tiles.
@@ -355,11 +355,12 @@ __host__ __device__ __forceinline__ Cut cut_item(uint32_t base, uint32_t u, int 
 __host__ __device__ __forceinline__ int part_slots(int64_t items, int pieces) { return pieces - 1 + (items < pieces ? (int)items : pieces - 1); }
 // Number of pieces, no more than `most`, and no more than the workgroups of the launch
 __host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work, int64_t items, uint32_t most) {
-    uint32_t pieces = work / piece_work(base), least = items < most ? (uint32_t)items : most;
+    uint32_t pieces = (base == 32 ? work : work + WORK_TILE - 1) / piece_work(base), least = items < most ? (uint32_t)items : most;
     pieces = pieces > most ? most : pieces < least ? least : pieces;
-    // (two bf16 tiles or a packed one of fp32 a piece, and more.  Of 512 fp32 pieces the smaller are 7/8 of that, less than a tile: two cuts may then fall into one, and what lies between
-    // them is a part without tiles, which is written and weighs nothing)
-    const uint32_t fewest = base == 32 ? 2 * WORK_TILE : work_cols(base);
+    // (Two bf16 tiles or one of fp32 a piece, and more.  Pieces a little shorter than a tile leave two cuts in one now and then, and what lies between
+    // them is a part without tiles, which is written and weighs nothing; pieces a little longer than one take up two, and the kernel lasts as
+    // long as these: 4 heads of 64, 256 rows of 1024, 18.3 us with 9 units a piece, 14.3 with 8; 40 rows of 300, the whole call, 26.7 / 22.1.)
+    const uint32_t fewest = base == 32 ? 2 * WORK_TILE : WORK_TILE - 1;
     return pieces <= work / fewest ? (int)pieces : work >= fewest ? (int)(work / fewest) : 1;
 }
 // where piece p begins
@@ -637,11 +638,18 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
 }
 
 // Launch of the attention kernel: the workgroups that are resident at once (256 CUs x per_cu, see prefill_bf16_kernel); any number drains the
-// queues, but a surplus one only starts when another ends and lengthens the run by its look at the queues.  Pieces: of few items a dozen each.
-constexpr int ITEM_PARTS = 12;
+// queues, but a surplus one only starts when another ends and lengthens the run by its look at the queues.
+//
+// Pieces: as many to an item as fill the chip, but no more than combine_kernel adds up in the time that they save.  The whole call, us, 12 / 24 / 48 of
+// an item: bf16, heads of 128, 64 rows of 65536, 4 heads 132 / 82 / 61, 61 rows, 32 heads (384 workgroups / 512) 177 / 152, with lists of few lines 82 / 84; one head of 64, 64 rows of 16384 43 / 34 / 31.
+// fp32, whose tiles keep a CU's matrix cores busy, up to one workgroup a CU; a few more would be two on some CUs: one head of 64, 64 rows of 16384 126 / 77 / 53,
+// 4 heads, 16 of 4096 47 / 35 / 34, but 512 of 4096 (240 workgroups / 480 / 512) 53 / 54 / 68, 32 heads, 64 of 2048 (384 / 512) 48 / 55.
+constexpr int ITEM_PARTS = 12, ITEM_PIECES = 48;
 int prefill_grid(int dtype, int d, int64_t items, bool pieces) {
     const int per_cu = dtype == 0 ? (d == 128 ? 2 : 3) + (pieces ? 0 : 1) : (d == 128 ? 1 : 2);
-    const int64_t most = pieces ? items * ITEM_PARTS : items + prefill_split_slots(items, 0, false);
+    int64_t most = items * ITEM_PIECES;
+    if (!pieces) most = items + prefill_split_slots(items, 0, false);
+    else if (dtype != 0 && most > 256) most = items * ITEM_PARTS > 256 ? items * ITEM_PARTS : 256;
     return (int)(most < 256 * per_cu ? most : 256 * per_cu);
 }
 int prefill_split_slots(int64_t items, int grid, bool pieces) {
