@@ -197,7 +197,7 @@ size_t ws_prefill(const ls_shape* s) {
     const int64_t n_hat = s->n_hat > 0 && s->n_hat <= s->n ? s->n_hat : s->n;
     const size_t items = BH * (size_t)row_blocks(s->n, n_hat);   // (head, row block) work items
     const bool pieces = ls::prefill_in_pieces((int)BH, s->n, (int)row_blocks(s->n, n_hat), s->dtype, s->d);
-    const int grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, pieces);
+    const int grid = ls::prefill_grid(s->dtype, s->d, s->n, (int64_t)items, pieces);
     const size_t slots = (size_t)ls::prefill_split_slots((int64_t)items, grid, pieces);
     return up(BH * (size_t)(words_of(s->n) + 4) * 4) + up(BH * (size_t)tab_len_of(s->n)) + up(items * 4) + up(BH * 4) + up(BH * (size_t)(tab_len_of(s->n) + 1) * 2) +
            up(26 * 4) + up((items + slots) * 16) + up(pieces ? ((size_t)grid + 1) * 8 : slots * 8) + up(slots * ls::prefill_slot_bytes(s->d)) + ALIGN;
@@ -436,14 +436,14 @@ const char* carve_prefill(ls_ctx* c, const ls_shape* s, PrefillCarve& w) {
         return slots;
     };
     w.pieces = ls::prefill_in_pieces(BH, s->n, w.nqb, s->dtype, s->d);
-    w.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, w.pieces);
+    w.grid = ls::prefill_grid(s->dtype, s->d, s->n, (int64_t)items, w.pieces);
     if (w.pieces) {
         w.grid = ls::prefill_pieces_for((int64_t)items, w.grid, most_slots());
         w.pieces = w.grid > 0;
         if (w.pieces && !take(ls::prefill_split_slots((int64_t)items, w.grid, true))) return "workspace is too small";
     }
     if (!w.pieces) {
-        w.grid = ls::prefill_grid(s->dtype, s->d, (int64_t)items, false);
+        w.grid = ls::prefill_grid(s->dtype, s->d, s->n, (int64_t)items, false);
         if (!take(most_slots())) return "workspace is too small";
     }
     w.code = LS_OK;

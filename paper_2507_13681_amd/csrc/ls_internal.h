@@ -221,7 +221,7 @@ hipError_t launch_prefill(const PrefillArgs& a, int dtype, int d, hipStream_t st
 size_t prefill_smem_bytes(int dtype, int d, int tab_len);
 int prefill_block_rows();
 bool prefill_in_pieces(int BH, int64_t n, int nqb, int dtype, int d);               // the work is shared out in pieces, or by queues
-int prefill_grid(int dtype, int d, int64_t items, bool pieces);
+int prefill_grid(int dtype, int d, int64_t n, int64_t items, bool pieces);
 int prefill_split_slots(int64_t items, int grid, bool pieces);      // parts' results that a call with so many (head, row block) items may use
 size_t prefill_slot_bytes(int d);
 int prefill_pieces_for(int64_t items, int grid, int slots);              // workgroups of a call in pieces with room for so many parts' results (0: queues)

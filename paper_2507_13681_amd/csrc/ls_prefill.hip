@@ -356,6 +356,7 @@ __host__ __device__ __forceinline__ int part_slots(int64_t items, int pieces) { 
 // Number of pieces, no more than `most`, and no more than the workgroups of the launch
 __host__ __device__ __forceinline__ int piece_count(uint32_t base, uint32_t work, int64_t items, uint32_t most) {
     uint32_t pieces = (base == 32 ? work : work + WORK_TILE - 1) / piece_work(base), least = items < most ? (uint32_t)items : most;
+    if (base != 32 && pieces > 256) pieces = work / work_cols(base) > 256 ? work / work_cols(base) : 256;      // two on some CUs are not the better for it: 4096 rows, all new, 8 heads of 64, 76.6 us, else 78.3
     pieces = pieces > most ? most : pieces < least ? least : pieces;
     // (Two bf16 tiles or one of fp32 a piece, and more.  Pieces a little shorter than a tile leave two cuts in one now and then, and what lies between
     // them is a part without tiles, which is written and weighs nothing; pieces a little longer than one take up two, and the kernel lasts as
@@ -644,12 +645,22 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
 // an item: bf16, heads of 128, 64 rows of 65536, 4 heads 132 / 82 / 61, 61 rows, 32 heads (384 workgroups / 512) 177 / 152, with lists of few lines 82 / 84; one head of 64, 64 rows of 16384 43 / 34 / 31.
 // fp32, whose tiles keep a CU's matrix cores busy, up to one workgroup a CU; a few more would be two on some CUs: one head of 64, 64 rows of 16384 126 / 77 / 53,
 // 4 heads, 16 of 4096 47 / 35 / 34, but 512 of 4096 (240 workgroups / 480 / 512) 53 / 54 / 68, 32 heads, 64 of 2048 (384 / 512) 48 / 55.
+// No more than there can be work for: 4 heads, 64 rows of 1024 keys, 192 workgroups / 20 28.5 / 28.0.  Where a dozen parts each take less than 15 MB of workspace, more do not take more than that: a caller's fixed 16 MB hold the same shapes as with a dozen.
 constexpr int ITEM_PARTS = 12, ITEM_PIECES = 48;
-int prefill_grid(int dtype, int d, int64_t items, bool pieces) {
+constexpr int64_t PIECES_BYTES = 15 << 20;
+int prefill_grid(int dtype, int d, int64_t n, int64_t items, bool pieces) {
     const int per_cu = dtype == 0 ? (d == 128 ? 2 : 3) + (pieces ? 0 : 1) : (d == 128 ? 1 : 2);
-    int64_t most = items * ITEM_PIECES;
-    if (!pieces) most = items + prefill_split_slots(items, 0, false);
-    else if (dtype != 0 && most > 256) most = items * ITEM_PARTS > 256 ? items * ITEM_PARTS : 256;
+    int64_t most;
+    if (pieces) {
+        const int64_t keys = (n + BN - 1) / BN, base = work_base(dtype), piece = piece_work(base);
+        const int64_t each = (base + keys * (WORK_TILE + work_cols(base)) + piece - 1) / piece;      // pieces of an item that visits every key both ways
+        const int64_t all = each < 2 ? 2 : each;           // (of one there is nothing to put together: a workspace without room for that takes the queues)
+        const int64_t dozen = items * (all < ITEM_PARTS ? all : ITEM_PARTS), fit = PIECES_BYTES / (int64_t)prefill_slot_bytes(d) - items;
+        most = items * (all < ITEM_PIECES ? all : ITEM_PIECES);
+        if (dtype != 0 && most > 256) most = 256;
+        if (dozen <= fit && most > fit) most = fit;
+        if (most < dozen) most = dozen;
+    } else most = items + prefill_split_slots(items, 0, false);
     return (int)(most < 256 * per_cu ? most : 256 * per_cu);
 }
 int prefill_split_slots(int64_t items, int grid, bool pieces) {

@@ -11,11 +11,11 @@ from tests.test_gpu_work_split import _lists
 pytestmark = pytest.mark.gpu
 
 
-# few row blocks: 48 workgroups each; fp32 up to 256 (5 blocks: 240, 6: 256), from 22 blocks on 12 each; bf16 up to every place (10: 480, 11: 512)
+# few row blocks: 48 workgroups each; fp32 up to 256 (5 blocks: 240, 6: 256), from 22 blocks on 12 each; bf16 up to what 15 MB of parts hold (d = 128: 4 blocks 192, 5 to 18 about 220), then up to every place (19: 512)
 @pytest.mark.parametrize("Hq,Hkv,n,n_hat,d,dtype", [
     (1, 1, 16384, 16, 64, "f32"), (4, 1, 1024, 256, 64, "f32"), (8, 2, 300, 40, 64, "f32"), (5, 1, 4097, 60, 128, "f32"), (6, 2, 6001, 3, 64, "f32"),
     (11, 1, 2001, 129, 64, "f32"), (3, 1, 64, 64, 64, "f32"), (2, 1, 1, 1, 128, "f32"),
-    (1, 1, 16384, 64, 64, "bf16"), (2, 1, 30011, 20, 128, "bf16"), (10, 2, 9001, 33, 128, "bf16"), (11, 1, 9000, 1, 128, "bf16"), (15, 5, 6000, 100, 64, "bf16")])
+    (1, 1, 16384, 64, 64, "bf16"), (2, 1, 30011, 20, 128, "bf16"), (10, 2, 9001, 33, 128, "bf16"), (11, 1, 9000, 1, 128, "bf16"), (18, 2, 5001, 70, 128, "bf16"), (19, 1, 7000, 9, 128, "bf16"), (15, 5, 6000, 100, 64, "bf16")])
 def test_many_parts_of_an_item(oracle, Hq, Hkv, n, n_hat, d, dtype):
     print(f"many parts Hq={Hq} n={n} n_hat={n_hat} d={d} {dtype}", flush=True)
     q, k, v = inputs.make_plain(1, Hq, Hkv, n, n_hat, d, dtype=dtype, seed=n, q_scale=1.5)
