@@ -33,6 +33,12 @@ int ls_debug_set_walk_spin_limit(ls_ctx* ctx, int32_t limit);
 int ls_debug_set_counters(ls_ctx* ctx, int32_t value, void* hip_stream);
 
 /*
+ * Sets every word of the context's workspace to `value`: what a call finds there is whatever an earlier one left, and the tests see that no
+ * result depends on it.
+ */
+int ls_debug_fill_workspace(ls_ctx* ctx, int32_t value, void* hip_stream);
+
+/*
  * Copies to the host how the most recent ls_sparse_prefill call on this context shared its items among the XCDs, as its kernels
  * left it in the workspace: its work queues, or in a call that needs none the items that begin on each XCD's workgroups (an item is one
  * block of 128 query rows of one head).  host_queue holds 8 arrays of B * Hq * nqb words, (batch * Hq + head) << 16 | row block, of

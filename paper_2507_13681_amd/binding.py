@@ -85,6 +85,8 @@ def load_library():
     lib.ls_debug_set_walk_spin_limit.argtypes = [vp, i32]
     lib.ls_debug_set_counters.restype = C.c_int
     lib.ls_debug_set_counters.argtypes = [vp, i32, vp]
+    lib.ls_debug_fill_workspace.restype = C.c_int
+    lib.ls_debug_fill_workspace.argtypes = [vp, i32, vp]
     lib.ls_debug_prefill_in_pieces.restype = C.c_int
     lib.ls_debug_prefill_in_pieces.argtypes = [sp]
     lib.ls_debug_score_route.restype = C.c_int
@@ -222,6 +224,9 @@ class Context:
 
     def debug_set_counters(self, value: int):
         self._check(self.lib.ls_debug_set_counters(self.h, value, _stream()))
+
+    def debug_fill_workspace(self, value: int):
+        self._check(self.lib.ls_debug_fill_workspace(self.h, value, _stream()))
 
     def debug_prefill_queues(self, shape):
         """Items of the last ls_sparse_prefill call by XCD (eight int arrays of item words), row blocks a head, cuts through items."""

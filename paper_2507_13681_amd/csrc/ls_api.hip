@@ -178,12 +178,12 @@ size_t ws_select(const ls_shape* s) {
 void order_scratch(ls::SelectArgs& a, Bump& bp) {
     const size_t lists = 2 * (size_t)a.BH, info = lists * ls::SELECT_RANGES;
     a.sidx = bp.take<int32_t>(lists * (size_t)a.n);
-    const size_t more = 2 * up(info * 4) + up(2 * (size_t)a.BH * 4) + up(ls::SELECT_HEAD_LINES * 4);       // (the walk reads whole blocks of lines)
+    const size_t more = up(info * 4) + up(2 * (size_t)a.BH * 4) + up(ls::SELECT_HEAD_LINES * 4);       // (the walk reads whole blocks of lines)
     const int64_t whole = a.n > ls::SELECT_HEAD_LINES ? a.n : ls::SELECT_HEAD_LINES;
     a.sorted = bp.ok() && bp.cap - bp.off >= 2 * up(lists * (size_t)whole * 4) + more;
     a.kept = a.sorted ? whole : ls::SELECT_HEAD_LINES;
     a.sorted_w = bp.take<float>(lists * (size_t)a.kept); a.sorted_m = bp.take<float>(lists * (size_t)a.kept);
-    if (a.sorted) { a.odd = bp.take<int32_t>(info); a.info = bp.take<int32_t>(info); a.open = bp.take<int32_t>(2 * (size_t)a.BH); }
+    if (a.sorted) { a.info = bp.take<int32_t>(info); a.open = bp.take<int32_t>(2 * (size_t)a.BH); }
 }
 inline int words_of(int64_t n) { return (int)((n + 31) / 32) + 8; }
 inline int tab_len_of(int64_t n) { return (int)(n / 64) + 4; }
@@ -326,7 +326,7 @@ int ls_select_exact(ls_ctx* c, const ls_shape* s, float alpha, const float* a_wi
     a.vert = vert; a.slash = slash; a.vmax = vert; a.smax = slash; a.total = total;   // the maxima are not used: any readable array
     Bump bp{c->ws, c->ws_bytes, 0};
     order_scratch(a, bp);
-    a.sorted_m = nullptr; a.odd = nullptr; a.open = nullptr;
+    a.sorted_m = nullptr; a.info = nullptr; a.open = nullptr;
     if (!bp.ok()) return fail(c, LS_EWORKSPACE, "ls_select_exact: workspace of %zu bytes is too small", c->ws_bytes);
     a.v_idx = v_idx; a.v_cnt = v_cnt; a.s_idx = s_idx; a.s_cnt = s_cnt; a.cap_v = cap_v; a.cap_s = cap_s;
     a.accounted = accounted; a.status = c->status; a.spin_limit = c->walk_spin_limit;
@@ -679,6 +679,14 @@ int ls_debug_set_counters(ls_ctx* c, int32_t value, void* stream) {
     if (hipSetDevice(c->device) != hipSuccess ||
         hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(c->counters), value, COUNTER_BYTES / 4, static_cast<hipStream_t>(stream)) != hipSuccess)
         return fail(c, LS_EHIP, "ls_debug_set_counters: hipMemsetD32Async failed");
+    return LS_OK;
+}
+
+int ls_debug_fill_workspace(ls_ctx* c, int32_t value, void* stream) {
+    if (!c) return LS_EINVAL;
+    if (hipSetDevice(c->device) != hipSuccess ||
+        hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(c->ws), value, c->ws_bytes / 4, static_cast<hipStream_t>(stream)) != hipSuccess)
+        return fail(c, LS_EHIP, "ls_debug_fill_workspace: hipMemsetD32Async failed");
     return LS_OK;
 }
 

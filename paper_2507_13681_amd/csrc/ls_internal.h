@@ -64,8 +64,8 @@ struct SelectArgs {
     int32_t* sidx;            // [2][BH][n] line indices in sorted order
     int64_t kept;             // of each sorted list, the first lines whose weight and largest entry are there in order: n, or SELECT_HEAD_LINES
     float *sorted_w, *sorted_m;            // [2][BH][kept] (sorted_m: null where nobody wants it)
-    int32_t* odd;             // [2][BH][SELECT_RANGES] whether a part of the list has a largest entry that is negative or no number; null: nobody has looked
-    int32_t* info;            // [2][BH][SELECT_RANGES] with `open`, of a range of the list: 0: in order, -1 - k: not, and k of the lines before it are
+    int32_t* info;            // [2][BH][SELECT_RANGES] of a range of the list: 0: in order, 1: and one of its largest entries is negative or no number, -1 - k: left out, and k of the
+                              // lines before it are in order (only with `open`); null: nobody has looked
     int32_t* open;            // [BH] the walk came to the end of what is in order, [BH] workgroups that have put their share of the rest in order; null: all of it is
     int ranges;               // of a list
     bool sorted;              // kept == n, and a block of lines may be read past the lists' ends

@@ -240,7 +240,7 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
     const int kept = (int)a.kept;                          // lines of the order whose weight and maximum are written as well
     float* sorted_w = a.sorted_w + ((int64_t)list * a.BH + bh) * kept;
     float* sorted_m = a.sorted_m ? a.sorted_m + ((int64_t)list * a.BH + bh) * kept : nullptr;
-    auto say = [&](int range, int what) { if (LAZY && tid == 0) a.info[((int64_t)list * a.BH + bh) * SELECT_RANGES + range] = what; };
+    auto say = [&](int range, int what) { if (a.info && tid == 0) a.info[((int64_t)list * a.BH + bh) * SELECT_RANGES + range] = what; };
     const int per = (n + 4 * ORDER_THREADS - 1) / (4 * ORDER_THREADS) * 256;
     const int w0 = wv * per < n ? wv * per : n, w1 = w0 + per < n ? w0 + per : n;         // this wave's lines
     typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -285,9 +285,11 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
     // (a maximum is written when the thread has its next one to ask for, which then does not wait for it)
     float top = 0.f;
     int top_at = -1;
+    bool odd = false;                                      // one of them is negative or no number
     auto settle = [&]() {
         if (top_at < 0) return;
         sorted_m[top_at] = top;
+        odd = odd || !(top >= 0.f);
         top_at = -1;
     };
     auto put = [&](int at, int i, uint32_t k) {            // line i is the `at`-th of the order
@@ -306,15 +308,6 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
     uint32_t next_key = 0u;
     bool more = true;
     if (!WHOLE && nb > 1) {
-        // whether a maximum of the b-th part of the list is negative or no number, for the walk: asked for here, looked at behind the bounds
-        constexpr int PART = 8;
-        const int part = (n + nb - 1) / nb, part0 = b * part, part1 = part0 + part < n ? part0 + part : n;
-        float most_of[PART];
-#pragma unroll
-        for (int j = 0; j < PART; ++j) {
-            most_of[j] = 0.f;
-            if (a.odd && part0 + j * ORDER_THREADS < part1) { const int i = part0 + j * ORDER_THREADS + tid; most_of[j] = mx[i < part1 ? i : part0]; }
-        }
         uint32_t sample[2];
         int32_t where[2];
         OrderBound from, to;
@@ -328,13 +321,6 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
         // ranges unequal
         const uint32_t few = (uint32_t)(n > ORDER_WIDE ? 2 * ORDER_SAMPLES / (5 * nb) : ORDER_SAMPLES / (16 * nb));
         order_bounds(sample, where, b, nb, next, few, words, sync, from, to, next_key);
-        if (a.odd) {
-            bool odd = false;
-#pragma unroll
-            for (int j = 0; j < PART; ++j) odd = odd || !(most_of[j] >= 0.f);
-            odd = __syncthreads_or(odd);
-            if (tid == 0) a.odd[((int64_t)list * a.BH + bh) * SELECT_RANGES + b] = odd ? 1 : 0;
-        }
         const bool last = b == nb - 1;
         if (b == 0) from = OrderBound{0u, -1, false, false};
         // A weight that has ranges to itself: the first of them takes all its lines, those at its ends none
@@ -694,7 +680,10 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
         lo = hi + 1u; hi = end;
     }
     settle();
-    say(b, 0);
+    if (a.info) {                                          // (the maxima that the range has written: of lines that nobody has put in order nobody takes any unseen)
+        const int any = __syncthreads_or(odd);
+        say(b, any ? 1 : 0);
+    }
     return more;
 }
 // grid (lists, nb or half as many: workgroup w then takes range w, and the one as many behind it if that is wanted)
@@ -1103,20 +1092,17 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, const int bh, uns
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = (int)a.n;
     const int nblk = (n + WALK_BLK - 1) / WALK_BLK;
-    const bool informed = SORTED && a.odd != nullptr;      // order_kernel has looked at the maxima
-    // how far list l is in order, and (odd) whether a maximum of it is negative or no number
+    const bool informed = SORTED && a.info != nullptr;     // order_kernel has looked at the maxima
+    // how far list l is in order, and (odd) whether a maximum of the lines up to there is negative or no number
     auto reach = [&](int l, int* odd) {
         const int64_t of = ((int64_t)l * a.BH + bh) * SELECT_RANGES;
-        int x = 0, y = 0, far = n;
-        if (odd && informed) {
-            x = lane < a.ranges ? a.odd[of + lane] : 0; y = lane + 64 < a.ranges ? a.odd[of + lane + 64] : 0;
-        }
+        int p = 0, q = 0, far = n;
+        if (informed) { p = lane < a.ranges ? a.info[of + lane] : 0; q = lane + 64 < a.ranges ? a.info[of + lane + 64] : 0; }
         if (SORTED && a.open) {
-            const int p = lane < a.ranges ? a.info[of + lane] : 0, q = lane + 64 < a.ranges ? a.info[of + lane + 64] : 0;
             const int at = p < 0 ? -1 - p : n, at2 = q < 0 ? -1 - q : n;
             far = __builtin_amdgcn_readlane((int)lanes_min((uint32_t)(at < at2 ? at : at2)), 63);
         }
-        if (odd) *odd = __ballot((x | y) != 0) != 0ull ? 1 : 0;
+        if (odd) *odd = __ballot(p > 0 || q > 0) != 0ull ? 1 : 0;
         return far;
     };
     const int64_t nh = a.n_hat;
@@ -1969,7 +1955,6 @@ __global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
         const int l = r >= a.ranges ? 1 : 0, b = r - l * a.ranges;
         if (__builtin_amdgcn_readfirstlane(a.info[((int64_t)l * a.BH + bh) * SELECT_RANGES + b]) >= 0) continue;
         (void)order_range<4, false, false>(a, l, bh, b, a.ranges, a.ranges, REDO_CAP, 0.f, lds, sync);
-        if (tid == 0) a.info[((int64_t)l * a.BH + bh) * SELECT_RANGES + b] = 0;
         __syncthreads();
     }
     __threadfence();                                       // (the others' L2 may be another: what was written goes to memory, and comes from there)
@@ -2389,7 +2374,7 @@ static hipError_t sort_lines(SelectArgs& a, bool lazy, hipStream_t st) {
     const int cap = (int)chunks * 1024;
     a.ranges = (int)nb;
     if (!lazy) a.open = nullptr;
-    if (nb == 1) a.odd = nullptr;                          // (the walk's own look at the maxima comes as early)
+    if (nb == 1) a.info = nullptr;                         // (the walk's own look at the maxima comes as early)
     const dim3 grid(2 * (unsigned)a.BH, (unsigned)wgs);
     auto launch = [&](auto kernel, int pt) { hipLaunchKernelGGL(kernel, grid, dim3(ORDER_THREADS), order_lds_bytes(pt, cap), st, a, cap); };
     if (a.n <= 1024) launch(&order_kernel<1, true, false>, 1);
