@@ -49,6 +49,13 @@ int ls_debug_fill_workspace(ls_ctx* ctx, int32_t value, void* hip_stream);
 int ls_debug_copy_prefill_queues(ls_ctx* ctx, const ls_shape* shape, uint32_t* host_queue, int32_t* host_qlen,
                                  int32_t* nqb_out, int32_t* cuts_out, void* hip_stream);
 
+/*
+ * How far the most recent call on this context, an ls_select of this shape that was not asked for the accounted mass, put its lists in order, as its kernels
+ * left it in the workspace: *ranges receives the ranges of each list (0: a call of this shape and workspace leaves none out), host_left [2][B * Hq] how many
+ * of them were left out to the end (diagonals, then columns), host_again [B * Hq] how many had been, of heads that were then walked again with everything in order (else 0).  Waits for the stream.
+ */
+int ls_debug_copy_select_order(ls_ctx* ctx, const ls_shape* shape, int32_t* host_left, int32_t* host_again, int32_t* ranges, void* hip_stream);
+
 /* 1: ls_sparse_prefill shares the work of such a turn out in pieces, 0: by work queues, if the workspace has room for the parts; without a GPU. */
 int ls_debug_prefill_in_pieces(const ls_shape* shape);
 

@@ -87,6 +87,8 @@ def load_library():
     lib.ls_debug_set_counters.argtypes = [vp, i32, vp]
     lib.ls_debug_fill_workspace.restype = C.c_int
     lib.ls_debug_fill_workspace.argtypes = [vp, i32, vp]
+    lib.ls_debug_copy_select_order.restype = C.c_int
+    lib.ls_debug_copy_select_order.argtypes = [vp, sp, vp, vp, vp, vp]
     lib.ls_debug_prefill_in_pieces.restype = C.c_int
     lib.ls_debug_prefill_in_pieces.argtypes = [sp]
     lib.ls_debug_score_route.restype = C.c_int
@@ -227,6 +229,14 @@ class Context:
 
     def debug_fill_workspace(self, value: int):
         self._check(self.lib.ls_debug_fill_workspace(self.h, value, _stream()))
+
+    def debug_select_order(self, shape):
+        """Of the last ls_select call: ranges a list (0: none are left out), how many were left out to the end [2][heads], how many of heads that were walked again."""
+        import numpy as np
+        heads = shape.B * shape.Hq
+        left, again, ranges = np.zeros((2, heads), np.int32), np.zeros(heads, np.int32), C.c_int32()
+        self._check(self.lib.ls_debug_copy_select_order(self.h, C.byref(shape), left.ctypes.data_as(C.c_void_p), again.ctypes.data_as(C.c_void_p), C.byref(ranges), _stream()))
+        return ranges.value, left, again
 
     def debug_prefill_queues(self, shape):
         """Items of the last ls_sparse_prefill call by XCD (eight int arrays of item words), row blocks a head, cuts through items."""

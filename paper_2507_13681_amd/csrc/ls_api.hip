@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <array>
 #include <mutex>
 #include <new>
@@ -738,6 +739,30 @@ int ls_debug_copy_prefill_queues(ls_ctx* c, const ls_shape* s, uint32_t* host_qu
             }
     }
     *nqb_out = w.nqb;
+    return LS_OK;
+}
+
+int ls_debug_copy_select_order(ls_ctx* c, const ls_shape* s, int32_t* host_left, int32_t* host_again, int32_t* ranges, void* stream) {
+    if (!c || !s || !host_left || !host_again || !ranges) return LS_EINVAL;
+    if (check_shape(s, true, false, true)) return LS_ESHAPE;
+    ls::SelectArgs a{};
+    a.n = s->n; a.BH = s->B * s->Hq;
+    Bump bp{c->ws, c->ws_bytes, 0};
+    order_scratch(a, bp);
+    if (!bp.ok()) return LS_EWORKSPACE;
+    *ranges = ls::select_ranges_left_out(a);
+    const size_t heads = (size_t)a.BH, lists = 2 * heads;
+    std::fill(host_left, host_left + lists, 0);
+    std::fill(host_again, host_again + heads, 0);
+    if (*ranges == 0) return LS_OK;
+    std::vector<int32_t> info;
+    try { info.resize(lists * ls::SELECT_RANGES); } catch (...) { return fail(c, LS_EHIP, "ls_debug_copy_select_order: out of memory"); }
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (hipSetDevice(c->device) != hipSuccess || hipMemcpyAsync(info.data(), a.info, info.size() * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipMemcpyAsync(host_again, a.open, heads * 4, hipMemcpyDeviceToHost, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
+        return fail(c, LS_EHIP, "ls_debug_copy_select_order: reading the workspace failed");
+    for (size_t l = 0; l < lists; ++l)
+        for (int b = 0; b < *ranges; ++b) host_left[l] += info[l * ls::SELECT_RANGES + (size_t)b] < 0 ? 1 : 0;
     return LS_OK;
 }
 

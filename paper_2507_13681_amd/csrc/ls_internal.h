@@ -66,7 +66,7 @@ struct SelectArgs {
     float *sorted_w, *sorted_m;            // [2][BH][kept] (sorted_m: null where nobody wants it)
     int32_t* info;            // [2][BH][SELECT_RANGES] of a range of the list: 0: in order, 1: and one of its largest entries is negative or no number, -1 - k: left out, and k of the
                               // lines before it are in order (only with `open`); null: nobody has looked
-    int32_t* open;            // [BH] the walk came to the end of what is in order, [BH] workgroups that have put their share of the rest in order; null: all of it is
+    int32_t* open;            // [BH] ranges that were left out, of heads whose walk came to the end of what is in order (else 0), [BH] workgroups that have put their share of the rest in order; null: all of it is
     int ranges;               // of a list
     bool sorted;              // kept == n, and a block of lines may be read past the lists' ends
     int32_t *v_idx, *v_cnt, *s_idx, *s_cnt;
@@ -209,6 +209,7 @@ struct MergeArgs {
 };
 hipError_t run_merge_lines(const MergeArgs& a, hipStream_t st);
 hipError_t run_select(const SelectArgs& a, hipStream_t st);
+int select_ranges_left_out(const SelectArgs& a);                      // ranges of each list of a call that may leave some of them out; else 0
 hipError_t run_select_exact(const SelectArgs& a, hipStream_t st);   // a_win, q_pos, w set; vmax / smax unused
 hipError_t run_topb(const TopbArgs& a, int BK, uint32_t* scratch, hipStream_t st);   // scratch: topb_scratch_words(BK, len) words
 size_t topb_scratch_words(int BK, int64_t len);

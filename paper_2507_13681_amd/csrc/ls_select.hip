@@ -1597,6 +1597,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, const int bh, uns
 }
 
 // grid (BH); dynamic LDS: WALK_LDS_BYTES<E>
+static_assert(2 * SELECT_RANGES <= WALK_THREADS, "a thread each");
 template <int E, bool SORTED>
 __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
     extern __shared__ __align__(16) unsigned char walk_lds[];
@@ -1604,7 +1605,12 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
     __syncthreads();
     const WalkSync* sync = reinterpret_cast<const WalkSync*>(walk_lds + 2 * sizeof(WalkList<E>) + WALK_RING * sizeof(WalkRun<E>));
     const int bh = blockIdx.x, cnt_s = sync->cnt_s, cnt_v = sync->cnt_v;
-    if (threadIdx.x == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; if (a.open) { a.open[bh] = sync->open; a.open[a.BH + bh] = 0; } }
+    int missing = 0;                                       // ranges that were left out, of a head that needs them
+    if (a.open && sync->open) {
+        const int l = (int)threadIdx.x >= a.ranges ? 1 : 0, b = (int)threadIdx.x - l * a.ranges;
+        missing = __syncthreads_count((int)threadIdx.x < 2 * a.ranges && a.info[((int64_t)l * a.BH + bh) * SELECT_RANGES + b] < 0);
+    }
+    if (threadIdx.x == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; if (a.open) { a.open[bh] = missing; a.open[a.BH + bh] = 0; } }
     if (a.n > EMIT_LINES) return;
     emit_both<WALK_THREADS>(a, bh, cnt_s, cnt_v, reinterpret_cast<uint32_t*>(walk_lds));      // (not where `sync` lies)
 }
@@ -1906,52 +1912,71 @@ __global__ __launch_bounds__(XW_THREADS) void walk_exact_kernel(SelectArgs a) {
 }
 
 // ---- chosen prefix -> ascending index list --------------------------------------------------------
-// grid (2, BH); dynamic LDS: bitmap of n bits, lines of up to 1024 of its words.
-// A head whose walk came to where a list is no longer in order (a.open) is walked again here, once its workgroups (with few heads more than the two that a
-// head has anyhow, up to eight; of other heads they leave at once) have put the missing ranges in order: by the one of them that is done last.  ls_select of heads that all need it, us,
-// everything in order beforehand / the missing ranges by one workgroup / by eight: 8 heads of 12347 lines 56 / 198 / 129, 32 of 32768 97 / 314 / 270, 16 of 131072 368 / 1610 / 610.
-constexpr int REDO_CAP = 5120, REDO_MORE = 6;
-constexpr size_t REDO_LDS_BYTES = order_lds_bytes(4, REDO_CAP) > WALK_LDS_BYTES<8> ? order_lds_bytes(4, REDO_CAP) : WALK_LDS_BYTES<8>;
-__global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
-    extern __shared__ __align__(16) uint32_t bm[];
-    __shared__ uint32_t wsum[16];
-    const int bh = blockIdx.y, tid = threadIdx.x;
+// The list of a head by a workgroup.  bm: bitmap of n bits, lines of up to 1024 of its words.
+__device__ __forceinline__ void emit_list(const SelectArgs& a, const int bh, const int list, const int cnt, uint32_t* bm, uint32_t* wsum) {
+    const int tid = threadIdx.x;
     const int64_t n = a.n;
     const int words = (int)((n + 31) / 32);
-    auto emit = [&](int list, int cnt) {
-        const int32_t* sorted_idx = a.sidx + ((int64_t)list * a.BH + bh) * n;
-        int32_t* out = list == 0 ? a.s_idx + (int64_t)bh * a.cap_s : a.v_idx + (int64_t)bh * a.cap_v;
-        const int cap = list == 0 ? a.cap_s : a.cap_v;
-        if (tid == 0 && cnt > cap) atomicOr(a.status, list == 0 ? STAT_S_TRUNCATED : STAT_V_TRUNCATED);
-        if (cnt >= n) {                                    // every line was taken: the list is 0 .. n-1
-            for (int64_t i = tid; i < n && i < cap; i += 1024) out[i] = (int32_t)i;
-            return;
-        }
-        for (int i = tid; i < words; i += 1024) bm[i] = 0u;
-        __syncthreads();
-        for (int i0 = tid; i0 < cnt; i0 += 8 * 1024) {     // eight independent loads in flight per thread
-            int32_t x8[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) { const int i = i0 + j * 1024; x8[j] = i < cnt ? sorted_idx[i] : -1; }
-#pragma unroll
-            for (int j = 0; j < 8; ++j) if (x8[j] >= 0) atomicOr(&bm[x8[j] >> 5], 1u << (x8[j] & 31));
-        }
-        __syncthreads();
-        uint16_t* stage = reinterpret_cast<uint16_t*>(bm + words);
-        uint32_t at = 0u;
-        for (int w0 = 0; w0 < words; w0 += PUT_WORDS) {
-            if (w0 > 0) __syncthreads();                   // the last lines are out of `stage`
-            at += put_lines<1024>(bm + w0, words - w0 < PUT_WORDS ? words - w0 : PUT_WORDS, 32 * w0, stage, wsum, 0, out, at, cap, tid);
-        }
-    };
-    if (!a.open || !__builtin_amdgcn_readfirstlane(a.open[bh])) {
-        if (blockIdx.x < 2) emit(blockIdx.x, blockIdx.x == 0 ? a.s_cnt[bh] : a.v_cnt[bh]);
+    const int32_t* sorted_idx = a.sidx + ((int64_t)list * a.BH + bh) * n;
+    int32_t* out = list == 0 ? a.s_idx + (int64_t)bh * a.cap_s : a.v_idx + (int64_t)bh * a.cap_v;
+    const int cap = list == 0 ? a.cap_s : a.cap_v;
+    if (tid == 0 && cnt > cap) atomicOr(a.status, list == 0 ? STAT_S_TRUNCATED : STAT_V_TRUNCATED);
+    if (cnt >= n) {                                        // every line was taken: the list is 0 .. n-1
+        for (int64_t i = tid; i < n && i < cap; i += 1024) out[i] = (int32_t)i;
         return;
     }
+    for (int i = tid; i < words; i += 1024) bm[i] = 0u;
+    __syncthreads();
+    for (int i0 = tid; i0 < cnt; i0 += 8 * 1024) {          // eight independent loads in flight per thread
+        int32_t x8[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { const int i = i0 + j * 1024; x8[j] = i < cnt ? sorted_idx[i] : -1; }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) if (x8[j] >= 0) atomicOr(&bm[x8[j] >> 5], 1u << (x8[j] & 31));
+    }
+    __syncthreads();
+    uint16_t* stage = reinterpret_cast<uint16_t*>(bm + words);
+    uint32_t at = 0u;
+    for (int w0 = 0; w0 < words; w0 += PUT_WORDS) {
+        if (w0 > 0) __syncthreads();                       // the last lines are out of `stage`
+        at += put_lines<1024>(bm + w0, words - w0 < PUT_WORDS ? words - w0 : PUT_WORDS, 32 * w0, stage, wsum, 0, out, at, cap, tid);
+    }
+}
+
+// Heads whose walk came to where a list is no longer in order (a.open) are walked again, by the whole launch: its workgroups share out such heads, those of a head put
+// its missing ranges in order, and the one of them that is done last walks.  Nobody waits for anybody.  At least BH workgroups.
+// The whole ls_select, us, everything in order beforehand / so, and where only one head in twenty needs it: 8 heads of 12347 lines 57 / 112, 55 / 100; 32 of 32768 107 / 195,
+// 102 / 165; 96 of 12347 90 / 226, 80 / 152; 256 of 16384 186 / 436, 159 / 261; 16 of 131072 369 / 528, 347 / 432.  (By two to eight workgroups of each head's own: 127, 107; 280, 164; 234, 151; 569, 251; 619, 517.)
+constexpr int REDO_CAP = 5120;
+constexpr size_t REDO_LDS_BYTES = order_lds_bytes(4, REDO_CAP) > WALK_LDS_BYTES<8> ? order_lds_bytes(4, REDO_CAP) : WALK_LDS_BYTES<8>;
+__device__ __forceinline__ int heads_open(const SelectArgs& a) {       // (each wave by itself)
+    int heads = 0;
+    for (int h0 = 0; h0 < a.BH; h0 += 64) heads += __popcll(__ballot(h0 + ((int)threadIdx.x & 63) < a.BH && a.open[h0 + (threadIdx.x & 63)] != 0));
+    return heads;
+}
+__device__ __forceinline__ void redo_heads(const SelectArgs& a, const int heads, uint32_t* bm, uint32_t* wsum) {
+    if (heads == 0) return;
     __shared__ OrderSync sync;
     __shared__ int last;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wgs = (int)(gridDim.x * gridDim.y), me = (int)(blockIdx.y * gridDim.x + blockIdx.x);
     unsigned char* lds = reinterpret_cast<unsigned char*>(bm);
-    for (int r = blockIdx.x; r < 2 * a.ranges; r += (int)gridDim.x) {
+    const int j = me % heads, part = me / heads, most = (wgs - 1 - j) / heads + 1;       // workgroups for the j-th of them
+    int bh = 0;
+    for (int h0 = 0, seen = 0; h0 < a.BH; h0 += 64) {
+        uint64_t who = __ballot(h0 + lane < a.BH && a.open[h0 + lane] != 0);
+        const int here = __popcll(who);
+        if (j >= seen && j < seen + here) {
+            for (int k = seen; k < j; ++k) who &= who - 1ull;
+            bh = h0 + __ffsll((unsigned long long)who) - 1;
+        }
+        seen += here;
+    }
+    bh = __builtin_amdgcn_readfirstlane(bh);
+    const int missing = __builtin_amdgcn_readfirstlane(a.open[bh]), parts = most < missing ? most : missing;
+    if (part >= parts) return;
+    __syncthreads();                                       // the workgroup's own list has been written
+    for (int r = part; r < 2 * a.ranges; r += parts) {
         const int l = r >= a.ranges ? 1 : 0, b = r - l * a.ranges;
         if (__builtin_amdgcn_readfirstlane(a.info[((int64_t)l * a.BH + bh) * SELECT_RANGES + b]) >= 0) continue;
         (void)order_range<4, false, false>(a, l, bh, b, a.ranges, a.ranges, REDO_CAP, 0.f, lds, sync);
@@ -1959,7 +1984,7 @@ __global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
     }
     __threadfence();                                       // (the others' L2 may be another: what was written goes to memory, and comes from there)
     __syncthreads();
-    if (tid == 0) last = count_shared(reinterpret_cast<uint32_t*>(a.open) + a.BH + bh) + 1u == gridDim.x;
+    if (tid == 0) last = count_shared(reinterpret_cast<uint32_t*>(a.open) + a.BH + bh) + 1u == (uint32_t)parts;
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(last) == 0) return;
     __threadfence();
@@ -1970,9 +1995,29 @@ __global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
     __syncthreads();
     if (tid == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; }
     for (int list = 0; list < 2; ++list) {
-        emit(list, list == 0 ? cnt_s : cnt_v);
+        emit_list(a, bh, list, list == 0 ? cnt_s : cnt_v, bm, wsum);
         __syncthreads();
     }
+}
+
+// grid (2, BH), or more than two; dynamic LDS as emit_list has it, REDO: at least REDO_LDS_BYTES.
+// REDO (up to EMIT_REDO_HEADS heads): the launch walks heads again as well.  Its 109 registers and its LDS leave a CU one workgroup, where the small kernel has two; where two workgroups a head are more
+// than the CUs that is a kernel of its own (redo_kernel), whose launch costs no more than the lists take longer: the whole ls_select, us, in one / by itself, 192 heads of 16384 lines 82.0 / 82.1, 256
+// 99.7 / 99.9, of 40000 214.5 / 213.6, 512 of 9000 142.9 / 142.3; 32 of 32768 43.8 / 44.6.  Calls that leave nothing out, and ls_select_exact, have the small kernel: 256 heads of 8000 lines 59.7 -> 57.9.
+template <bool REDO>
+__global__ __launch_bounds__(1024) void emit_kernel(SelectArgs a) {
+    extern __shared__ __align__(16) uint32_t bm[];
+    __shared__ uint32_t wsum[16];
+    const int bh = blockIdx.y;
+    const int open = a.open ? a.open[bh] : 0, cnt = blockIdx.x == 0 ? a.s_cnt[bh] : a.v_cnt[bh];
+    const int heads = REDO ? heads_open(a) : 0;
+    if (blockIdx.x < 2 && !__builtin_amdgcn_readfirstlane(open)) emit_list(a, bh, blockIdx.x, cnt, bm, wsum);
+    if constexpr (REDO) redo_heads(a, heads, bm, wsum);
+}
+__global__ __launch_bounds__(1024) void redo_kernel(SelectArgs a) {
+    extern __shared__ __align__(16) uint32_t bm[];
+    __shared__ uint32_t wsum[16];
+    redo_heads(a, heads_open(a), bm, wsum);
 }
 
 // ---- union of two selections ------------------------------------------------------------------------
@@ -2347,11 +2392,15 @@ __global__ __launch_bounds__(GATHER_THREADS) void gather_rows_kernel(GatherArgs 
         if (slot + u * per < cnt) *reinterpret_cast<f32x4*>(d + (int64_t)(slot + u * per) * row_bytes) = v[u];
 }
 
+constexpr int EMIT_REDO_HEADS = 128, REDO_MORE = 6;        // (with few heads up to six workgroups each more than the two that write the lists)
 static void launch_emit(const SelectArgs& a, hipStream_t st) {
     if (a.n <= EMIT_LINES) return;
-    const size_t bytes = (size_t)((a.n + 31) / 32) * 4 + put_lines_bytes(a.n);
-    const int more = 256 / a.BH - 2, wgs = a.open && more > 0 ? 2 + (more < REDO_MORE ? more : REDO_MORE) : 2;
-    hipLaunchKernelGGL(emit_kernel, dim3(wgs, a.BH), dim3(1024), a.open && REDO_LDS_BYTES > bytes ? REDO_LDS_BYTES : bytes, st, a);
+    const size_t bytes = (size_t)((a.n + 31) / 32) * 4 + put_lines_bytes(a.n), redo_bytes = REDO_LDS_BYTES > bytes ? REDO_LDS_BYTES : bytes;
+    if (!a.open || a.BH > EMIT_REDO_HEADS) hipLaunchKernelGGL(emit_kernel<false>, dim3(2, a.BH), dim3(1024), bytes, st, a);
+    if (!a.open) return;
+    const int more = 256 / a.BH - 2, wgs = 2 + (more < REDO_MORE ? more : REDO_MORE);
+    if (a.BH > EMIT_REDO_HEADS) hipLaunchKernelGGL(redo_kernel, dim3(a.BH < 256 ? 256 : a.BH), dim3(1024), redo_bytes, st, a);
+    else hipLaunchKernelGGL(emit_kernel<true>, dim3(wgs, a.BH), dim3(1024), redo_bytes, st, a);
 }
 // Ranges of 8192 lines, a fifth less than a workgroup takes (the samples miss by 4 % at most; beyond 65536 lines by more, and a halved
 // range counts again), and more of them, down to 512 lines, as long as there are compute units for one each: 8 heads of 8192 lines
@@ -2359,7 +2408,8 @@ static void launch_emit(const SelectArgs& a, hipStream_t st) {
 // One range up to 4096 lines saves the look for its bounds: 32 heads of 4096 lines 25.7 -> 24.1, of 8192 36.6 -> 38.5.
 // lazy: the last ranges are put in order only where a walk may come to them.  A workgroup then has two ranges of half the length, far apart, as long as they have 1024 lines (up to
 // ORDER_WIDE): 32 heads of 32768 lines 33.0 -> 25.5 us, 12347 18.7 -> 17.0; of lists whose lines are all needed, 16500 of 32768 each, the whole ls_select 117 -> 122.
-static hipError_t sort_lines(SelectArgs& a, bool lazy, hipStream_t st) {
+struct OrderPlan { int wgs, ranges; bool lazy; };          // of each list
+static OrderPlan order_plan(const SelectArgs& a, bool lazy) {
     int64_t wgs = 1;
     if (a.n > ORDER_ONE) {
         wgs = a.n > ORDER_WIDE ? (a.n + 6553) / 6554 : (a.n + 8191) / 8192;
@@ -2369,13 +2419,20 @@ static hipError_t sort_lines(SelectArgs& a, bool lazy, hipStream_t st) {
     }
     lazy = lazy && wgs > 1 && a.open && a.n >= LAZY_LINES;
     const int64_t nb = lazy && a.n <= ORDER_WIDE && 2 * wgs <= SELECT_RANGES && a.n >= 2048 * wgs ? 2 * wgs : wgs;
+    return OrderPlan{(int)wgs, (int)nb, lazy};
+}
+int select_ranges_left_out(const SelectArgs& a) { const OrderPlan p = order_plan(a, a.accounted == nullptr); return p.lazy ? p.ranges : 0; }
+static hipError_t sort_lines(SelectArgs& a, bool want_lazy, hipStream_t st) {
+    const OrderPlan p = order_plan(a, want_lazy);
+    const int nb = p.ranges;
+    const bool lazy = p.lazy;
     int64_t chunks = nb == 1 ? (a.n + 1023) / 1024 : (a.n * 5 / (4 * nb) + 256 + 1023) / 1024;
     if (chunks > ORDER_CHUNKS || a.n > ORDER_WIDE) chunks = ORDER_CHUNKS;
     const int cap = (int)chunks * 1024;
-    a.ranges = (int)nb;
+    a.ranges = nb;
     if (!lazy) a.open = nullptr;
     if (nb == 1) a.info = nullptr;                         // (the walk's own look at the maxima comes as early)
-    const dim3 grid(2 * (unsigned)a.BH, (unsigned)wgs);
+    const dim3 grid(2 * (unsigned)a.BH, (unsigned)p.wgs);
     auto launch = [&](auto kernel, int pt) { hipLaunchKernelGGL(kernel, grid, dim3(ORDER_THREADS), order_lds_bytes(pt, cap), st, a, cap); };
     if (a.n <= 1024) launch(&order_kernel<1, true, false>, 1);
     else if (a.n <= ORDER_ONE) launch(&order_kernel<4, true, false>, 4);
@@ -2394,7 +2451,8 @@ hipError_t init_select_kernels() {
     if ((e = allow_full_lds(&walk_kernel<16, true>)) != hipSuccess || (e = allow_full_lds(&walk_kernel<16, false>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_exact_kernel)) != hipSuccess) return e;
     if ((e = allow_full_lds(&merge_lines_kernel)) != hipSuccess) return e;
-    return allow_full_lds(&emit_kernel);
+    if ((e = allow_full_lds(&emit_kernel<false>)) != hipSuccess || (e = allow_full_lds(&emit_kernel<true>)) != hipSuccess) return e;
+    return allow_full_lds(&redo_kernel);
 }
 
 hipError_t run_select(const SelectArgs& a0, hipStream_t st) {

@@ -1,6 +1,6 @@
 """ls_select where the lists are put in order only as far as a walk can be expected to come: walks that go further, walks that end
 on the last line in order, maxima that do not let long runs through, and contexts with room for the first lines' weights only.  The
-oracle's selection exactly."""
+oracle's selection exactly, and that ranges were left out and heads walked again where a test is for that."""
 import numpy as np
 import pytest
 import torch
@@ -75,3 +75,40 @@ def test_walks_and_the_lines_in_order(n, room):
         if accounted:
             np.testing.assert_array_equal(gpu["accounted"], ref["accounted"])
         check_selection_exact(gpu, ref)
+    ranges, left, again = ctx.debug_select_order(shape)
+    if n < 8193 or room != "usual":
+        assert ranges == 0                                 # everything was put in order
+    else:
+        assert again[0] > 0 and left[0, 0] == 0           # "further"
+        assert again[1] == 0 and 0 < left[0, 1] < ranges   # "plain"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,n,further", [(8, 12347, 8), (32, 20000, 3), (96, 9000, 40), (128, 8200, 128), (129, 8200, 1), (200, 8193, 200), (300, 8300, 257), (1030, 8200, 7)])
+def test_heads_walked_again(oracle, H, n, further):
+    """Few heads and many, of which some or all need lines that were left out: workgroups that share a head, one a head, more heads than CUs and than threads."""
+    from tests.gpu_util import dev_scores, host
+    from tests.test_gpu_configs import check_selection_exact
+    print(f"heads walked again H={H} n={n}", flush=True)
+    rng = np.random.default_rng(H)
+    kinds = np.full(H, "plain", dtype=object)
+    kinds[rng.choice(H, further, replace=False)] = "further"
+    kinds[rng.choice(np.flatnonzero(kinds == "further"), further // 3, replace=False)] = "all"
+    two = {k: [_head(k, n, rng) for _ in range(2)] for k in ("plain", "further", "all")}
+    heads = [two[k][h % 2] for h, k in enumerate(kinds)]
+    pack = lambda hs: {k: np.ascontiguousarray(np.stack([np.asarray(h[i]) for h in hs])[None], dtype=np.float32) for i, k in enumerate(("slash", "vert", "smax", "vmax", "total"))}
+    n_hat = n // 3
+    some = oracle.select(pack(two["plain"] + two["further"] + two["all"]), n_hat, 1.0)
+    which = [2 * ["plain", "further", "all"].index(k) + h % 2 for h, k in enumerate(kinds)]
+    ref = {k: np.ascontiguousarray(x[:, which]) for k, x in some.items()}
+    shape = binding.make_shape(1, H, 1, 64, n, n_hat, 1, "f32", 0.0)
+    ctx, dev = binding.Context(shape), dev_scores(pack(heads))
+    for _ in range(2):                                     # the second call finds what the first has counted
+        out = binding.alloc_select(shape, accounted=False)
+        ctx.ls_select(shape, 1.0, dev["vert"], dev["slash"], dev["vmax"], dev["smax"], dev["total"], out["v_idx"], out["v_cnt"], out["s_idx"], out["s_cnt"])
+        assert ctx.ls_poll_status() == 0
+        check_selection_exact(host({k: x for k, x in out.items() if x is not None}), ref)
+    ranges, left, again = ctx.debug_select_order(shape)
+    assert ranges > 0
+    np.testing.assert_array_equal(again > 0, kinds != "plain")
+    assert (left[0, kinds == "plain"] > 0).all() and (left[:, kinds != "plain"] == 0).all()
