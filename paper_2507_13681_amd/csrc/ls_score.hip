@@ -586,10 +586,12 @@ __device__ __forceinline__ float2 row_stats(const ScoreArgs& a, int bk, int row,
 constexpr int RETAIN_CHUNKS = 4;
 template <int D>
 __host__ __device__ constexpr int retain_lds() { return (4 + RETAIN_CHUNKS) * RowTile<bf16_t, D>::BYTES + RETAIN_CHUNKS * 32 * 8; }
+// (The LDS leaves two workgroups a CU at d = 128, three at 64: no need for fewer than 256 registers.  A kernel of its own: inside lines_kernel, small retentions had its registers.)
 template <int D>
-__device__ __forceinline__ void retain_stream(const ScoreArgs& a, unsigned char* smem) {
+__global__ __launch_bounds__(SCORE_THREADS, 2) void retain_kernel(ScoreArgs a) {
     using T = bf16_t;
     using RT = RowTile<T, D>;
+    extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* qs = smem + 4 * RT::BYTES;              // the chunks
     float2* rst = reinterpret_cast<float2*>(smem + (4 + RETAIN_CHUNKS) * RT::BYTES);          // max and 1 / sum of their rows
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, g = lane >> 5;
@@ -694,15 +696,14 @@ __device__ __forceinline__ void retain_stream(const ScoreArgs& a, unsigned char*
 // MODE 2: column sums only, summed over the G heads of the KV head (retention score)
 // MODE 3: the matrix A only
 // MODE 4: as 0; the block that is done last adds what it shares with its neighbours, and the total (joins)
-// Four workgroups per CU leave bf16 128 registers (little data, and what stays in LDS, where the LDS leaves two or three: 256).  In MODE 0 and 4 what a row sees is arithmetic: with a table of the rows' limits in LDS, as for explicit
+// Four workgroups per CU leave bf16 128 registers (little data).  In MODE 0 and 4 what a row sees is arithmetic: with a table of the rows' limits in LDS, as for explicit
 // positions, ls_score took, us, 131072 keys 464 instead of 448, 16384, B 4, 64 heads, 267 / 248, 32768 88 / 82, 8192 37.5 / 35.2, 61 rows of 12347, half
 // of whose chunks have 29 rows, 51.5 / 47.9 (its reads beside the slab's, 13 more registers, four of them spilled).
 template <typename T, int D, int MODE, bool FOLD>
-__global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? (MODE == 2 && FOLD ? 2 : 4) : 1)) void lines_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(SCORE_THREADS, (Elem<T>::bytes == 2 ? 4 : 1)) void lines_kernel(ScoreArgs a) {
     using RT = RowTile<T, D>;
     constexpr bool LINES = MODE == 0 || MODE == 4;
     extern __shared__ __align__(16) unsigned char smem[];
-    if constexpr (MODE == 2 && Elem<T>::bytes == 2 && FOLD) { if (a.retain) { retain_stream<D>(a, smem); return; } }
     unsigned char* kst = smem;                             // [4 waves] K rows on their way to registers, then
     float* slab = reinterpret_cast<float*>(smem);          // [SLAB_DIAGS][SLAB] A by diagonals (MODE 0) and
     unsigned char* qs = smem + (LINES ? SLAB_BYTES : 0);           // [2] chunks of queries
@@ -1183,7 +1184,7 @@ static hipError_t run_score_t(const ScoreArgs& a0, int mode, hipStream_t st) {
     } else {
         const int share = 512 / BK < 1 ? 1 : 512 / BK < a.nkb ? 512 / BK : a.nkb;      // (64 KB of LDS: two workgroups a CU)
         if constexpr (Elem<T>::bytes == 2) {
-            if (a.retain) hipLaunchKernelGGL((lines_kernel<T, D, 2, true>), dim3(share, BK), dim3(SCORE_THREADS), retain_lds<D>(), st, a);
+            if (a.retain) hipLaunchKernelGGL(retain_kernel<D>, dim3(share, BK), dim3(SCORE_THREADS), retain_lds<D>(), st, a);
         }
         if (!a.retain) launch_lines<T, D, 2>(a, BK, st);
         return hipGetLastError();
@@ -1197,7 +1198,7 @@ static hipError_t init_score_t() {
     hipError_t e;
     if ((e = allow_full_lds(&stats_kernel<T, D>)) != hipSuccess) return e;
     if constexpr (Elem<T>::bytes == 2)
-        if ((e = allow_full_lds(&range_stats_kernel<D, false>)) != hipSuccess || (e = allow_full_lds(&range_stats_kernel<D, true>)) != hipSuccess) return e;
+        if ((e = allow_full_lds(&range_stats_kernel<D, false>)) != hipSuccess || (e = allow_full_lds(&range_stats_kernel<D, true>)) != hipSuccess || (e = allow_full_lds(&retain_kernel<D>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 0, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 0, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 4, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 4, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&lines_kernel<T, D, 1, false>)) != hipSuccess || (e = allow_full_lds(&lines_kernel<T, D, 1, true>)) != hipSuccess) return e;

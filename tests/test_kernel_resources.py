@@ -11,13 +11,13 @@ from paper_2507_13681_amd import build
 NO_SCRATCH = {
     "ls_decode.hip": ["decode_kernel"],
     "ls_prefill.hip": ["plan_kernel", "sched_kernel", "prefill_bf16_kernel", "combine_kernel"],
-    "ls_score.hip": ["stats_kernel", "range_stats_kernel", "merge_kernel", "lines_kernel", "diagonals_kernel", "finish_kernel"],
+    "ls_score.hip": ["stats_kernel", "range_stats_kernel", "merge_kernel", "lines_kernel", "retain_kernel", "diagonals_kernel", "finish_kernel"],
     "ls_select.hip": ["order_kernel", "walk_kernel", "walk_exact_kernel", "emit_kernel", "redo_kernel", "merge_lines_kernel", "topb_one_kernel"],
 }
 
 
 # instances of which a CU is to have so many waves on each of its SIMDs at once, by what their names contain: 512 registers are shared by them
-WAVES = {"ls_select.hip": {"emit_kernelILb0E": 8}}
+WAVES = {"ls_score.hip": {"lines_kernelINS_6bf16_t": 4}, "ls_select.hip": {"emit_kernelILb0E": 8}}
 
 
 def _kernels(tmp_path, source):

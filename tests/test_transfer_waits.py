@@ -116,7 +116,7 @@ def test_path_search_sees_a_wait_that_leaves_too_many():
 KERNELS = {
     "ls_decode.hip": [("decode_kernelI", 4, [])],
     "ls_prefill.hip": [("prefill_bf16_kernelI", 4, [])],
-    "ls_score.hip": [("range_stats_kernelILi128E", 2, [4]), ("range_stats_kernelILi64E", 2, [2]), ("stats_kernelI", 4, [MANY]), (r"lines_kernelI\w+Li[04]ELb", 16, [MANY]),
+    "ls_score.hip": [("range_stats_kernelILi128E", 2, [4]), ("range_stats_kernelILi64E", 2, [2]), ("stats_kernelI", 4, [MANY]), ("retain_kernelI", 2, []), (r"lines_kernelI\w+Li[04]ELb", 16, [MANY]),
                      (r"lines_kernelI\w+Li[123]ELb", 24, [])],
 }
 
