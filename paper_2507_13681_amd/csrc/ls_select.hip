@@ -240,7 +240,7 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
     const int kept = (int)a.kept;                          // lines of the order whose weight and maximum are written as well
     float* sorted_w = a.sorted_w + ((int64_t)list * a.BH + bh) * kept;
     float* sorted_m = a.sorted_m ? a.sorted_m + ((int64_t)list * a.BH + bh) * kept : nullptr;
-    auto say = [&](int range, int what) { if (a.info && tid == 0) a.info[((int64_t)list * a.BH + bh) * SELECT_RANGES + range] = what; };
+    auto say = [&](int range, int what) { if (!WHOLE && a.info && tid == 0) a.info[((int64_t)list * a.BH + bh) * SELECT_RANGES + range] = what; };
     const int per = (n + 4 * ORDER_THREADS - 1) / (4 * ORDER_THREADS) * 256;
     const int w0 = wv * per < n ? wv * per : n, w1 = w0 + per < n ? w0 + per : n;         // this wave's lines
     typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -289,7 +289,7 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
     auto settle = [&]() {
         if (top_at < 0) return;
         sorted_m[top_at] = top;
-        odd = odd || !(top >= 0.f);
+        if (!WHOLE) odd = odd || !(top >= 0.f);
         top_at = -1;
     };
     auto put = [&](int at, int i, uint32_t k) {            // line i is the `at`-th of the order
@@ -680,7 +680,7 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
         lo = hi + 1u; hi = end;
     }
     settle();
-    if (a.info) {                                          // (the maxima that the range has written: of lines that nobody has put in order nobody takes any unseen)
+    if (!WHOLE && a.info) {                                // (the maxima that the range has written: of lines that nobody has put in order nobody takes any unseen)
         const int any = __syncthreads_or(odd);
         say(b, any ? 1 : 0);
     }
@@ -1092,13 +1092,16 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, const int bh, uns
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = (int)a.n;
     const int nblk = (n + WALK_BLK - 1) / WALK_BLK;
-    const bool informed = SORTED && a.info != nullptr;     // order_kernel has looked at the maxima
+    // order_kernel has looked at the maxima (not of lists that are one range); it may have left ranges out (not of shorter lists, and not any more where a head is walked again)
+    static_assert(WALK_SHORT <= ORDER_ONE && LAZY_LINES > WALK_LONG, "lists that are walked four entries a lane are one range, those that lack ranges are walked by sixteen");
+    const bool informed = SORTED && E > 4 && a.info != nullptr;
+    constexpr bool SOME = SORTED && E == 16;
     // how far list l is in order, and (odd) whether a maximum of the lines up to there is negative or no number
     auto reach = [&](int l, int* odd) {
         const int64_t of = ((int64_t)l * a.BH + bh) * SELECT_RANGES;
         int p = 0, q = 0, far = n;
         if (informed) { p = lane < a.ranges ? a.info[of + lane] : 0; q = lane + 64 < a.ranges ? a.info[of + lane + 64] : 0; }
-        if (SORTED && a.open) {
+        if (SOME && a.open) {
             const int at = p < 0 ? -1 - p : n, at2 = q < 0 ? -1 - q : n;
             far = __builtin_amdgcn_readlane((int)lanes_min((uint32_t)(at < at2 ? at : at2)), 63);
         }
@@ -1605,12 +1608,17 @@ __global__ __launch_bounds__(WALK_THREADS) void walk_kernel(SelectArgs a) {
     __syncthreads();
     const WalkSync* sync = reinterpret_cast<const WalkSync*>(walk_lds + 2 * sizeof(WalkList<E>) + WALK_RING * sizeof(WalkRun<E>));
     const int bh = blockIdx.x, cnt_s = sync->cnt_s, cnt_v = sync->cnt_v;
-    int missing = 0;                                       // ranges that were left out, of a head that needs them
-    if (a.open && sync->open) {
-        const int l = (int)threadIdx.x >= a.ranges ? 1 : 0, b = (int)threadIdx.x - l * a.ranges;
-        missing = __syncthreads_count((int)threadIdx.x < 2 * a.ranges && a.info[((int64_t)l * a.BH + bh) * SELECT_RANGES + b] < 0);
+    if constexpr (E == 16 && SORTED) {
+        if (a.open) {
+            int missing = 0;                               // ranges that were left out, of a head that needs them
+            if (sync->open) {
+                const int l = (int)threadIdx.x >= a.ranges ? 1 : 0, b = (int)threadIdx.x - l * a.ranges;
+                missing = __syncthreads_count((int)threadIdx.x < 2 * a.ranges && a.info[((int64_t)l * a.BH + bh) * SELECT_RANGES + b] < 0);
+            }
+            if (threadIdx.x == 0) { a.open[bh] = missing; a.open[a.BH + bh] = 0; }
+        }
     }
-    if (threadIdx.x == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; if (a.open) { a.open[bh] = missing; a.open[a.BH + bh] = 0; } }
+    if (threadIdx.x == 0) { a.s_cnt[bh] = cnt_s; a.v_cnt[bh] = cnt_v; }
     if (a.n > EMIT_LINES) return;
     emit_both<WALK_THREADS>(a, bh, cnt_s, cnt_v, reinterpret_cast<uint32_t*>(walk_lds));      // (not where `sync` lies)
 }

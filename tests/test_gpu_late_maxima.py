@@ -68,3 +68,5 @@ def test_maxima_of_lines_that_are_not_put_in_order(oracle, n, H=32):
         else:
             ctx.debug_fill_workspace(fill)
         check_selection_exact(select(dev), ref)
+    ranges, left, again = ctx.debug_select_order(shape)
+    assert 0 < left[0, 0] < ranges and again[0] == 0       # "clean": the tests' premise
