@@ -39,7 +39,7 @@ constexpr int ORDER_THREADS = 1024;
 constexpr int ORDER_WAVES = 16;
 static_assert(ORDER_WAVES == 16, "waves_before adds a row of lanes");
 constexpr int ORDER_CHUNKS = 10;               // most lines of a workgroup, in 1024
-constexpr int ORDER_ONE = 4096;                // longest list that one workgroup puts in order
+constexpr int ORDER_ONE = 5120;                // longest list that one workgroup puts in order, whatever the number of lists
 constexpr int ORDER_SAMPLES = 2048;            // of a list, for the bounds of its ranges
 constexpr int ORDER_WIDE = 65536;              // lists beyond: shorter ranges, with more room
 constexpr float ORDER_GOAL = 1.f + 1.f / 512;  // of the target: what lines before a range have to have of it for the range to be left out (its sums round otherwise than the walk's)
@@ -307,7 +307,7 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
     bool ends = false, alone = false;                      // alone: `front` is its only weight
     uint32_t next_key = 0u;
     bool more = true;
-    if (!WHOLE && nb > 1) {
+    if (!WHOLE) {
         uint32_t sample[2];
         int32_t where[2];
         OrderBound from, to;
@@ -351,13 +351,13 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
         }
     }
     uint32_t hi = end;
-    int base = nb > 1 ? -1 : 0;                            // place of the range's first line in the order
+    int base = WHOLE ? 0 : -1;                             // place of the range's first line in the order
     if (!WHOLE && tid < 4) sync.cross[tid] = 0x7FFFFFFF;
     for (;;) {
         int before = w0, m = n;                            // lines of the range in the waves before, and in all (a list in one range: all lines)
         bool picked = false, plain = false;
         const uint32_t span = hi - lo;
-        if (!WHOLE && nb > 1) {
+        if (!WHOLE) {
             // Weights as integers in the order of the floats: t, largest first.  (That of a weight of 0 or more is its bits, and of others the sign is enough where
             // a range begins at 0 or more and ends there as well or nowhere.)
             const int t_last = (int)(hi ^ 0x7FFFFFFFu), t_first = (int)(lo ^ 0x7FFFFFFFu), t_next = (int)(next_key ^ 0x7FFFFFFFu);
@@ -687,8 +687,9 @@ __device__ __forceinline__ bool order_range(const SelectArgs& a, const int list,
     return more;
 }
 // grid (lists, nb or half as many: workgroup w then takes range w, and the one as many behind it if that is wanted)
+// WHOLE: a list in one range.  (Two workgroups a CU where their LDS leaves room for them.)
 template <int PT, bool WHOLE, bool LAZY>
-__global__ __launch_bounds__(ORDER_THREADS, WHOLE ? 8 : 4) void order_kernel(SelectArgs a, int cap) {
+__global__ __launch_bounds__(ORDER_THREADS, WHOLE && PT <= 4 ? 8 : 4) void order_kernel(SelectArgs a, int cap) {
     extern __shared__ __align__(16) unsigned char order_lds[];
     __shared__ OrderSync sync;
     const int list = blockIdx.x & 1, bh = blockIdx.x >> 1, nb = a.ranges;
@@ -2413,7 +2414,8 @@ static void launch_emit(const SelectArgs& a, hipStream_t st) {
 // Ranges of 8192 lines, a fifth less than a workgroup takes (the samples miss by 4 % at most; beyond 65536 lines by more, and a halved
 // range counts again), and more of them, down to 512 lines, as long as there are compute units for one each: 8 heads of 8192 lines
 // 33.2 us in 16 ranges, 36.7 in one; 512 workgroups instead of 256 take turns: 32 heads of 32768 lines 63.0 -> 75.5, of 8192 36.6 -> 45.8.
-// One range up to 4096 lines saves the look for its bounds: 32 heads of 4096 lines 25.7 -> 24.1, of 8192 36.6 -> 38.5.
+// One range saves the looks for its bounds and for its lines, which is more than fewer lines a workgroup save: up to 5120 lines, and where lists could have three or two ranges up to 6144 and 8192.  In ranges / in one, us:
+// 4 heads of 4200 lines 23.7 / 22.7, 16 26.1 / 24.8, of 5003 27.2 / 26.9, 32 of 4500 29.1 / 27.0, of 6000 30.8 / 30.9, of 8192 32.7 / 35.0; 40 of 5500 30.5 / 29.3, of 7000 33.5 / 34.0; 64 of 4200 30.7 / 27.8, of 7000 35.5 / 34.4, of 8192 36.9 / 36.7.
 // lazy: the last ranges are put in order only where a walk may come to them.  A workgroup then has two ranges of half the length, far apart, as long as they have 1024 lines (up to
 // ORDER_WIDE): 32 heads of 32768 lines 33.0 -> 25.5 us, 12347 18.7 -> 17.0; of lists whose lines are all needed, 16500 of 32768 each, the whole ls_select 117 -> 122.
 struct OrderPlan { int wgs, ranges; bool lazy; };          // of each list
@@ -2424,6 +2426,7 @@ static OrderPlan order_plan(const SelectArgs& a, bool lazy) {
         const int64_t fill = 256 / (2 * (int64_t)a.BH), most = (a.n + 511) / 512;
         const int64_t more = fill < most ? fill : most;
         if (wgs < more) wgs = more;
+        if (a.n <= (wgs == 2 ? 8192 : wgs == 3 ? 6144 : 0)) wgs = 1;
     }
     lazy = lazy && wgs > 1 && a.open && a.n >= LAZY_LINES;
     const int64_t nb = lazy && a.n <= ORDER_WIDE && 2 * wgs <= SELECT_RANGES && a.n >= 2048 * wgs ? 2 * wgs : wgs;
@@ -2442,8 +2445,9 @@ static hipError_t sort_lines(SelectArgs& a, bool want_lazy, hipStream_t st) {
     if (nb == 1) a.info = nullptr;                         // (the walk's own look at the maxima comes as early)
     const dim3 grid(2 * (unsigned)a.BH, (unsigned)p.wgs);
     auto launch = [&](auto kernel, int pt) { hipLaunchKernelGGL(kernel, grid, dim3(ORDER_THREADS), order_lds_bytes(pt, cap), st, a, cap); };
+    // (Lists in one range have an instance without these looks at any length: 256 heads of 4500 lines, the whole ls_select, 45.1 -> 41.7, of 8000 56.8 -> 53.0, 128 of 8192 39.2 -> 37.6.)
     if (a.n <= 1024) launch(&order_kernel<1, true, false>, 1);
-    else if (a.n <= ORDER_ONE) launch(&order_kernel<4, true, false>, 4);
+    else if (nb == 1) { if (cap <= 6144) launch(&order_kernel<4, true, false>, 4); else launch(&order_kernel<8, true, false>, 8); }
     else if (cap <= 6144) { if (lazy) launch(&order_kernel<4, false, true>, 4); else launch(&order_kernel<4, false, false>, 4); }
     else { if (lazy) launch(&order_kernel<8, false, true>, 8); else launch(&order_kernel<8, false, false>, 8); }
     return hipGetLastError();
@@ -2452,8 +2456,8 @@ static hipError_t sort_lines(SelectArgs& a, bool want_lazy, hipStream_t st) {
 hipError_t init_select_kernels() {
     hipError_t e;
     if ((e = allow_full_lds(&order_kernel<1, true, false>)) != hipSuccess || (e = allow_full_lds(&order_kernel<4, true, false>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&order_kernel<4, false, false>)) != hipSuccess || (e = allow_full_lds(&order_kernel<4, false, true>)) != hipSuccess) return e;
-    if ((e = allow_full_lds(&order_kernel<8, false, false>)) != hipSuccess || (e = allow_full_lds(&order_kernel<8, false, true>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<8, true, false>)) != hipSuccess || (e = allow_full_lds(&order_kernel<4, false, false>)) != hipSuccess) return e;
+    if ((e = allow_full_lds(&order_kernel<4, false, true>)) != hipSuccess || (e = allow_full_lds(&order_kernel<8, false, false>)) != hipSuccess || (e = allow_full_lds(&order_kernel<8, false, true>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_kernel<4, true>)) != hipSuccess || (e = allow_full_lds(&walk_kernel<4, false>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_kernel<8, true>)) != hipSuccess || (e = allow_full_lds(&walk_kernel<8, false>)) != hipSuccess) return e;
     if ((e = allow_full_lds(&walk_kernel<16, true>)) != hipSuccess || (e = allow_full_lds(&walk_kernel<16, false>)) != hipSuccess) return e;

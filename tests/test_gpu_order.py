@@ -73,3 +73,10 @@ def test_lists_in_ranges(oracle, n, kind, H=3):
 @pytest.mark.parametrize("n,kind", [(4097, "spread"), (5003, "few"), (6000, "zeros"), (8192, "crowd"), (8192, "equal")])
 def test_long_lists_of_many_heads(oracle, n, kind):
     test_lists_in_ranges(oracle, n, kind, H=130)
+
+
+# the longest lists in one range and the shortest in several: any number of heads, three ranges a list, two
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,kind,H", [(5120, "spread", 3), (5120, "crowd", 5), (5121, "few", 3), (6144, "zeros", 42), (6145, "zeros", 42), (8192, "nested", 60), (8191, "spread", 64), (8193, "spread", 64)])
+def test_one_range_or_several(oracle, n, kind, H):
+    test_lists_in_ranges(oracle, n, kind, H=H)
