@@ -80,3 +80,16 @@ def test_long_lists_of_many_heads(oracle, n, kind):
 @pytest.mark.parametrize("n,kind,H", [(5120, "spread", 3), (5120, "crowd", 5), (5121, "few", 3), (6144, "zeros", 42), (6145, "zeros", 42), (8192, "nested", 60), (8191, "spread", 64), (8193, "spread", 64)])
 def test_one_range_or_several(oracle, n, kind, H):
     test_lists_in_ranges(oracle, n, kind, H=H)
+
+
+# lines without weight, up to as many as are still ranked against each other at the end of a list in one range, and more; beside others of the last bin
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,none", [(1024, 33), (2000, 127), (4096, 128), (5003, 129), (5120, 128), (5121, 128)])
+def test_lines_without_weight(oracle, monkeypatch, n, none):
+    def weights(rng, n):
+        w = np.exp2(rng.uniform(-20, 0, n))
+        w[rng.choice(n, none, replace=False)] = 0
+        w[rng.choice(n, 3, replace=False)] = 2.0 ** -30                    # of the zeros' bin, but not zero
+        return w
+    monkeypatch.setitem(KINDS, "no weight", weights)
+    test_lists_in_ranges(oracle, n, "no weight", H=4)
