@@ -626,7 +626,8 @@ __global__ __launch_bounds__(SCORE_THREADS, 2) void retain_kernel(ScoreArgs a) {
         const bool open = blk0 + SB - 1 <= n - a.w;        // every row sees every key
         float sum = 0.f;
         auto chunks = [&](auto OPEN) {
-            // N chunks at once: two, whose products do not wait for each other, in a pinned order (as many registers as two workgroups a CU leave: 163; one at a time 106)
+            // N chunks at once: two, whose products do not wait for each other, in a pinned order (as many registers as two workgroups a CU leave: 163; one at a time 106).
+            // At d = 64, where a chunk's chain is half as long, one: the whole ls_kv_compress, two / one, us: B 2, 16 / 4 heads of 61338 entries, 16 rows 54.2 / 53.1, 65111, 8 / 2, 32 rows 43.8 / 42.6, B 4, 64 / 8, 16384 59.8 / 58.9.
             auto some = [&](auto COUNT, int c0) {
                 constexpr int N = decltype(COUNT)::value, NS = D / 16, AHEAD = N == 1 ? NS : 2;
                 f32x16 s[N];
@@ -677,8 +678,12 @@ __global__ __launch_bounds__(SCORE_THREADS, 2) void retain_kernel(ScoreArgs a) {
                 }
             };
             int c = 0;
-            for (; c + 2 <= ch.count; c += 2) some(std::integral_constant<int, 2>{}, c);
-            if (c < ch.count) some(std::integral_constant<int, 1>{}, c);
+            if constexpr (D == 128) {
+                for (; c + 2 <= ch.count; c += 2) some(std::integral_constant<int, 2>{}, c);
+                if (c < ch.count) some(std::integral_constant<int, 1>{}, c);
+            } else {
+                for (; c < ch.count; ++c) some(std::integral_constant<int, 1>{}, c);
+            }
         };
         if (open) chunks(std::true_type{}); else chunks(std::false_type{});
         sum = halves_sum(sum);
