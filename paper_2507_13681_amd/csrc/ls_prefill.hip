@@ -646,6 +646,7 @@ __global__ __launch_bounds__(SCHED_THREADS) void sched_kernel(SchedArgs a) {
 // fp32, whose tiles keep a CU's matrix cores busy, up to one workgroup a CU; a few more would be two on some CUs: one head of 64, 64 rows of 16384 126 / 77 / 53,
 // 4 heads, 16 of 4096 47 / 35 / 34, but 512 of 4096 (240 workgroups / 480 / 512) 53 / 54 / 68, 32 heads, 64 of 2048 (384 / 512) 48 / 55.
 // No more than there can be work for: 4 heads, 64 rows of 1024 keys, 192 workgroups / 20 28.5 / 28.0.  Where a dozen parts each take less than 15 MB of workspace, more do not take more than that: a caller's fixed 16 MB hold the same shapes as with a dozen.
+// (A step, no bound: at d = 128 18 row blocks are cut into 220 parts, 15 MB, 19 into 512, 35 MB, as from 43 on a dozen parts each are.  In a workspace made for a dozen they go in a dozen.)
 constexpr int ITEM_PARTS = 12, ITEM_PIECES = 48;
 constexpr int64_t PIECES_BYTES = 15 << 20;
 int prefill_grid(int dtype, int d, int64_t n, int64_t items, bool pieces) {

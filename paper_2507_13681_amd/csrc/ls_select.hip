@@ -203,7 +203,7 @@ __device__ __forceinline__ void order_bounds(const uint32_t (&key)[2], const int
 // bounds 8000, count 11000, lines into LDS 9000, their span 1700, bins 9500, ranks and results 11000.  So the two looks take four lines a lane at once, eight instructions a line, with
 // the weights as they are where their sign allows it, in a short loop with the next lines under way (unrolled over 1024 lines it was half as long again: a workgroup runs through its
 // code once and has to fetch it), and two lists of lines that are not needed are not ranked.  A maximum is fetched when its line is placed and written with the next one.
-// 32 heads, the kernel alone, us, everything in order and only the first 1024 lines' weights / now: 32768 lines 28.6 / 25.5, 12347 18.5 / 17.0, 8192 15.5 / 17.2, 5003 (16 heads) 12.6 / 14.0,
+// 32 heads, the kernel alone, us, everything in order and only the first 1024 lines' weights / now: 32768 lines 28.6 / 25.5, 12347 18.5 / 17.0, 8192 15.5 / 17.2, 5003 (16 heads) 12.6 / 14.0 (in one range 13.3),
 // 131072 226 / 141, 256 heads of 16384 104 / 92; the walk, which gains what short lists lose here, 24.0 / 15.5, 12.7 / 10.6, 16.1 / 13.8, 14.4 / 12.2, 123 / 52, 25.8 / 18.5.
 // (Keys and bins in registers, ten lines a thread, ranks by indirection and many equal weights by digits, 30 KB of code and 88 bytes of scratch: 32 heads of 32768 lines 35 us where the
 // bins in LDS took 30.)
