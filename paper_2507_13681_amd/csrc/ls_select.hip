@@ -939,7 +939,8 @@ constexpr int WALK_THREADS = 384;              // wave 0 decides the runs, wave 
 constexpr int64_t WALK_SHORT = 2048, WALK_LONG = 8192;         // up to: 4; from: 16
 // (With long runs taken unseen, below, sixteen pay from 8192 lines on: 8 / 16, the walk alone, 8192 lines 15.9 / 13.8, 5003 12.2 / 13.5.)
 // Where the picks go back and forth between the lists a run is one or a few, and its price is that of looking at all E entries.
-// The deciding wave then looks at these few only, from the beginning and from a run of up to half of what they hold until one fills them.  The walk alone
+// The deciding wave then looks at these few only, from the beginning and from three runs in a row of up to half of what they hold until one fills them.  (From one such run, where the runs of
+// one list are long and those of the other short: 32 heads of 32768 lines by the thousand picks 3743 / 3653 us, 64 of 8192 1208 / 1178, 32 of 12000 427 / 418, the whole ls_select.)  The walk alone
 // with sixteen throughout / so, 32 heads of 32768 lines, us: runs of one to five picks 76.5 / 54.7, of one 489 / 320.
 constexpr int WALK_NARROW = 4;
 constexpr int WALK_NBLK = 4;                   // blocks of a list resident in LDS (a ring over sorted positions)
@@ -1364,6 +1365,7 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, const int bh, uns
     constexpr int OVER = 1, FAILED = 2, CUT = 3;           // CUT: a head has come to where its list is no longer in order
     int need_s = 2, need_v = 2;                // blocks whose prefix sums have been asked for
     int full = 1;                              // the last run had as many picks as were looked at
+    int few_picks = 0;                         // wide looks in a row that found a short run
     int column = 0;                            // it ended where the next pick is a column: no need to see that again
     int falls_s = 0, falls_v = 0;
     const int far_s = reach(0, &falls_s), far_v = reach(1, &falls_v);
@@ -1590,7 +1592,8 @@ __device__ __forceinline__ void walk_head(const SelectArgs& a, const int bh, uns
             hand_over(R, which, limit, stop_dead < run ? 1 : 0);
             if (stop_dead < run) break;            // nothing after this run can add to the sum
             if (which == 0) { is = uniform(is + limit); S = nxt; } else { iv = uniform(iv + limit); V = nxt; }
-            if (E > WALK_NARROW && (N == E ? limit <= 32 * WALK_NARROW : limit == 64 * WALK_NARROW)) return true;
+            if (N == E) few_picks = limit <= 32 * WALK_NARROW ? few_picks + 1 : 0;
+            if (E > WALK_NARROW && (N == E ? few_picks >= 3 : limit == 64 * WALK_NARROW)) { few_picks = 0; return true; }
         }
         return false;
     };
